@@ -82,8 +82,9 @@ typedef void *(*pipad_alloc_fn)(size_t bytes, void *ctx);
  *   snaps   host array of k descriptors whose rowptr/colidx are device arrays; each must have
  *           snaps[t].n == n.  The inputs are only read and need not outlive the call.
  *   flags   0 or PIPAD_VALIDATE (costs one extra pass; returns PIPAD_ERR_BAD_CSR on violation;
- *           without it, non-canonical input gives undefined results but no out-of-range write
- *           as long as rowptr is a valid offset array into colidx)
+ *           without it, non-canonical input gives undefined results - or PIPAD_ERR_BAD_CSR where
+ *           it is noticed - but no out-of-range write as long as rowptr is a valid offset array
+ *           into colidx)
  *   alloc   NULL: the library allocates with hipMalloc and frees in pipad_frame_destroy();
  *           otherwise every device buffer is obtained through alloc(bytes, ctx) and no
  *           hipMalloc / hipFree is issued

@@ -91,7 +91,6 @@ struct AggArgs {
   int32_t order;      // 1: one slice after the other; 0: hub class parts so, the rows of all slices side by side
   int32_t sub_log2;   // log2 of the sub classes per XCD
   int32_t nclass;     // 8 << sub_log2
-  int64_t nv;         // class parts per part of the frame = nclass * n_units
   int64_t nvp;        // partial sums per slice: nclass per hub unit
   int32_t nt;         // non-temporal hints (bit 0: Y stores, bit 1: index streams)
   int32_t sg;         // coalescent kernel: snapshots per lane team (slices are snapshot groups)
@@ -100,10 +99,9 @@ struct AggArgs {
   const float *dinv;
   const int32_t *rows_short, *rows_long;
   const int32_t *item_row, *item_v0, *item_v1, *hub_rows, *hub_item_off;
-  const uint32_t *sptr;   // class parts of the split rows: see pipad_frame
-  const int32_t *scol;
+  const int32_t *sptr;    // class parts of the hub rows: see pipad_frame
+  const int32_t *scol_c, *scol_d;
   const float *swd;
-  int64_t total_c;        // entries of the common region of scol
   float *partial;
   const int32_t *rowptr_d[PIPAD_MAX_K];
   const int32_t *col_d[PIPAD_MAX_K];
@@ -493,11 +491,7 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
   const int64_t n_items = a.n_items, n_mid = a.n_long, n_short = a.n_short;
   const int b_wide = a.batch_wide, b_mid = a.batch_mid, b_short = a.batch_short;
   const bool split = w < split_blocks;                  // class parts of hub units
-#ifdef PIPAD_SPLIT_TEAM  // measurement builds: class parts walked by lane teams like short rows
-  const bool wide = !split && w < split_blocks + a.blocks_mid;
-#else
   const bool wide = w < split_blocks + a.blocks_mid;    // ... or whole mid rows: a wave per list
-#endif
   int cls = 0;  // column class of this wave's class parts
   if (split) {
     const int sub = (int)(w / wide_blocks);  // the sub classes come one after the other in time
@@ -519,23 +513,23 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
 #endif
   const int rows_here = (int)min((int64_t)batch, list_len - first);
   // entry lists: the class-grouped copies for hub units, the frame's CSRs for whole rows
-  const int32_t *colc = split ? a.scol : a.col_c;
+  const int32_t *colc = split ? a.scol_c : a.col_c;
   const float *wcs = split ? s.swc : s.wc;
-  const int32_t *cold = split ? a.scol + a.total_c : s.cd;
+  const int32_t *cold = split ? a.scol_d : s.cd;
   const float *wds = split ? a.swd : s.wd;
-  // hub units only: first class part in sptr == first partial sum; nclass of them per unit
+  // hub units only: first partial sum; nclass of them per unit
   const int64_t v_first = first * a.nclass + cls;
   int32_t r = 0, mc0 = 0, mc1 = 0, md0 = 0, md1 = 0;
   float mdi = 0.f;
   if (lane < rows_here) {
     r = list[first + lane];
     if (split) {
-      const int64_t v = v_first + (int64_t)lane * a.nclass;
-      mc0 = (int32_t)a.sptr[v];
-      mc1 = (int32_t)a.sptr[v + 1];
-      const int64_t vd = (int64_t)(1 + s.t) * a.nv + v;
-      md0 = (int32_t)((int64_t)a.sptr[vd] - a.total_c);
-      md1 = (int32_t)((int64_t)a.sptr[vd + 1] - a.total_c);
+      const int32_t *sp = a.sptr + (int64_t)cls * n_items + first + lane;
+      mc0 = sp[0];
+      mc1 = sp[n_items];
+      sp += (int64_t)(1 + s.t) * (a.nclass + 1) * n_items;
+      md0 = sp[0];
+      md1 = sp[n_items];
     } else {
       mc0 = a.rowptr_c[r]; mc1 = a.rowptr_c[r + 1];
       md0 = s.rpd[r]; md1 = s.rpd[r + 1];
@@ -584,7 +578,6 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
   const int nslots = wide ? nteams : 1;
 
   struct Item {
-    int src;  // place of the element in the wave's batch
     int32_t i, cs, clen, ds, dlen;
     float di;
     bool have;
@@ -596,7 +589,6 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
     const int li = step * per_step + (wide ? 0 : team);
     it.have = li < rows_here;
     const int src = __shfl(order, it.have ? li : 0, kWave);
-    it.src = src;
     it.i = __shfl(r, src, kWave);
     it.cs = __shfl(mc0, src, kWave);
     it.clen = __shfl(mc1, src, kWave) - it.cs;
@@ -641,10 +633,7 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
         walk<VEC, US, FAST>(colc, wcs, cur.cs, cur.clen, cur.fc, team_base, team_lanes, q, slot, nslots, s, a.ldx, cur.i, ntl, lds, acc);
         walk<VEC, US, FAST>(cold, wds, cur.ds, cur.dlen, cur.fd, team_base, team_lanes, q, slot, nslots, s, a.ldx, cur.i, ntl, lds, acc);
       }
-      if (split) {  // (PIPAD_SPLIT_TEAM builds only)
-        if (cur.have && s.fvalid)
-          VT::store(partial_slot(a, slice_seq, v_first + (int64_t)cur.src * a.nclass, fl, VEC), acc, kPartialNt);
-      } else if constexpr (UPD) {
+      if constexpr (UPD) {
         if (cur.have) finish_row_to_sink(a, s, sink, sink.cnt + team, fl, cur.i, cur.di, cur.xi, acc);
         sink.cnt += rows_now;  // teams 0 .. rows_now - 1 had a row
       } else {
@@ -904,16 +893,15 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_coalescent(const AggArgs a
 
   // Entry lists: short and mid rows are walked from the frame's CSRs, hub units from the
   // class-grouped copies (all classes of a unit are contiguous there, so a unit is one list).
-  const int32_t *const scol_d = a.scol + a.total_c;
+  const int32_t *const scol_d = a.scol_d;
   const float *const swd = a.swd;
-  const int64_t nu_nc = a.nv;  // class parts per part of the frame
 
   // Adds `clen` overlap entries starting at col[cs] (scales scale_v[cs ...] of snapshot group
   // member v) and this lane's own `dlen` exclusive entries starting at dcol[ds] / dw[ds].
   auto walk_row = [&](int32_t i, bool grouped, int32_t cs, int32_t clen, int32_t ds, int32_t dlen,
                       int team_base, int team_lanes, int q, int slot, int nslots,
                       typename VT::T &acc) __attribute__((always_inline)) {
-    const int32_t *colp = grouped ? a.scol : a.col_c;
+    const int32_t *colp = grouped ? a.scol_c : a.col_c;
     for (int32_t base = 0; base < clen; base += team_lanes) {
       const int32_t cnt = min(team_lanes, clen - base);
       int32_t c = i;
@@ -986,14 +974,14 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_coalescent(const AggArgs a
   // exclusive part.
   auto unit_lists = [&](int64_t un, int32_t *cs, int32_t *clen, int32_t *ds, int32_t *dlen)
       __attribute__((always_inline)) {
-    const int64_t vc = un * a.nclass;
-    const uint32_t c0 = a.sptr[vc], c1 = a.sptr[vc + a.nclass];
-    const int64_t vd = (int64_t)(1 + t) * nu_nc + vc;
-    const uint32_t d0 = a.sptr[vd], d1 = a.sptr[vd + a.nclass];
-    *cs = (int32_t)c0;
-    *clen = (int32_t)(c1 - c0);
-    *ds = (int32_t)((int64_t)d0 - a.total_c);
-    *dlen = (int32_t)(d1 - d0);
+    // (all classes of a unit are contiguous: from the start of the first to the end of the last)
+    const int64_t n_items = a.n_items;
+    const int32_t *sp = a.sptr + un;
+    *cs = sp[0];
+    *clen = sp[a.nclass * n_items] - *cs;
+    sp += (int64_t)(1 + t) * (a.nclass + 1) * n_items;
+    *ds = sp[0];
+    *dlen = sp[a.nclass * n_items] - *ds;
   };
 
   const int32_t *const p_items = a.item_row, *const p_mid = a.rows_long, *const p_short = a.rows_short;
@@ -1016,7 +1004,6 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_coalescent(const AggArgs a
   w -= a.blocks_wide;
   const bool long_rows = w < a.blocks_mid;
   if (!long_rows) w -= a.blocks_mid;
-  const int32_t *list = long_rows ? p_mid : p_short;
   const int64_t list_len = long_rows ? n_mid : n_short;
   const int batch = long_rows ? b_mid : b_short;
   const int64_t first = (w * kWavesPerBlock + wave) * batch;
@@ -1025,7 +1012,7 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_coalescent(const AggArgs a
   if (long_rows) {
     // ---- mid rows: a wave per row, finished at once
     for (int step = 0; step < rows_here; ++step) {
-      const int32_t i = list[first + step];
+      const int32_t i = p_mid[first + step];
       const int32_t cs = a.rowptr_c[i], ce = a.rowptr_c[i + 1];
       const int32_t ds = rpd[i];
       typename VT::T acc = VT::zero();
@@ -1038,7 +1025,7 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_coalescent(const AggArgs a
   // ---- short rows: a lane team per row
   int32_t r = 0, mc0 = 0, mc1 = 0;
   if (lane < rows_here) {
-    r = list[first + lane];
+    r = p_short[first + lane];
     mc0 = a.rowptr_c[r];
     mc1 = a.rowptr_c[r + 1];
   }
@@ -1207,13 +1194,12 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
   a.hub_rows = f->hub_rows;
   a.hub_item_off = f->hub_item_off;
   a.sptr = f->sptr;
-  a.scol = f->scol;
+  a.scol_c = f->scol_c;
+  a.scol_d = f->scol_d;
   a.swd = f->swd;
-  a.total_c = f->split_total[0];
   a.sub_log2 = f->sub_log2;
   a.nclass = f->nclass;
-  a.nv = (int64_t)f->n_units * f->nclass;
-  a.nvp = a.nv;
+  a.nvp = (int64_t)f->n_items * f->nclass;
   a.n_short = f->n_short;
   a.n_long = f->n_long;
   a.n_items = f->n_items;

@@ -2,34 +2,31 @@
 //
 // Section 4.1 ("Overlap-aware data transfer") regroups the topology of a snapshot group as one
 // overlap part plus one exclusive part per snapshot; Section 4.3 makes this the job of a data
-// preparation module that runs once.  Here it runs on the GPU, edge-parallel, in five steps:
+// preparation module that runs once.  Here it runs on the GPU over *tiles*: the entries of the
+// largest snapshot (the base) are cut into runs of 512 in (row, column) order, and a tile owns, of
+// every other snapshot, the contiguous stretch of entries that lies between its first entry and the
+// next tile's in that order.  Whatever is in all snapshots is therefore decided inside one tile, and
+// since the overlap holds the same entries in every snapshot, ONE prefix sum (the tiles' numbers of
+// common entries, C) places everything: an entry of snapshot t's exclusive part goes to its own
+// position in the input minus the common entries before it, row pointers likewise.
 //
-//   mark     one lane per stored entry of snapshot 0: find its row, then binary-search its column
-//            in the same row of every other snapshot.  An entry found everywhere is a common
-//            edge: a flag is set for it at the position where each snapshot holds it (a byte
-//            per stored entry, packed into one bit per entry afterwards).
-//   count    popcount per 64-entry word of every output part (common = set bits of snapshot 0's
-//            bitmap, delta_t = clear bits of snapshot t's bitmap) and one exclusive prefix sum
-//            over all words.
-//   rowptr   output row pointers are read off the prefix sums at the input row starts.
-//   scatter  every selected entry is written to prefix[word] + (set bits below it in its word),
-//            which keeps the ascending column order of the input (stable compaction); the
-//            per-entry column scales are written alongside.
-//   lists    rows binned by length into the work lists of the aggregation (short, mid, hub; very
-//            long rows cut into units), and the entries of the hub rows stored a second time,
-//            grouped by column class, with their scales.
+//   prepare  where every tile starts in every snapshot; D^-1/2; how many rows of every 256 are mid
+//            and hub rows (a row's class is decided by its longest input row alone)
+//   mark     a workgroup per tile: the stretches of the other snapshots are staged in LDS, every base
+//            entry looks itself up in all of them; one bit per base entry says whether it is common,
+//            and the exclusive entries of every snapshot are written out next to each other
+//   scan     prefix sums over the tiles' and the row blocks' counts; with them every data-dependent
+//            size is known and goes to the host
+//   rows     a thread per row, while the host sizes the outputs: row pointers of all parts and the
+//            work lists of the aggregation (short, mid, hub rows; very long rows cut into units)
+//   scatter  a wave per tile (or four) and part writes the entries in order, with their column scales
+//   fill     the entries of the hub rows a second time, grouped by column class, with their scales
 //
-// All integer work; the outputs are unique, so they are bit-exact regardless of scheduling (the
-// marks are plain byte stores with one writer each; the only atomics are integer additions that
-// sum up sizes).
+// All integer work; the outputs are unique, so they are bit-exact regardless of scheduling.
 #include <algorithm>
 #include <cstring>
 
 #include "pipad_internal.h"
-
-#ifndef PIPAD_DENSE_FACTOR
-#define PIPAD_DENSE_FACTOR 3  // exclusive entries from all / this on take the lane-per-entry scatter
-#endif
 
 namespace pipad {
 namespace {
@@ -40,27 +37,24 @@ struct Snaps {
   int32_t nnz[PIPAD_MAX_K];
 };
 
-struct Parts {  // part 0 = common (from snapshot 0), part 1+t = delta_t
-  uint64_t *bits[PIPAD_MAX_K];       // bitmap of snapshot t, ceil(nnz_t/64) words
-  uint8_t *flag8[PIPAD_MAX_K];       // t >= 1: one byte per stored entry, set by k_mark
-  uint32_t word_off[PIPAD_MAX_K + 2];  // first word of each part in the concatenated prefix array
-  int32_t *rowptr_out[PIPAD_MAX_K + 1];
-  int32_t *col_out[PIPAD_MAX_K + 1];
-  float *wc[PIPAD_MAX_K];  // column scales of the common entries, one array per snapshot
-  float *wd[PIPAD_MAX_K];  // column scales of the exclusive entries of snapshot t
+// What the kernels of the extraction share.
+struct Tiles {
+  int32_t n, k;
+  int32_t base;           // the snapshot that is cut into tiles: the one with most entries
+  int32_t ntiles;
+  int32_t tile_log2;      // base entries per tile
+  int32_t *brow;          // [ntiles + 1] row of every tile's first entry; n - 1 behind the last
+  int32_t *bound;         // [k][ntiles + 1] where every tile starts in snapshot t; nnz_t at the end
+  uint64_t *bits;         // a bit per base entry: it is common
+  uint64_t *hub_bits;     // ... it belongs to a hub row
+  uint16_t *wpre;         // per word of bits: common entries of the tile in the words before
+  uint2 *tile_cnt;        // [ntiles] common entries per tile, and those in hub rows
+  uint2 *tile_pre;        // [ntiles + 1] the same summed up over the tiles in front
+  int32_t *excl[PIPAD_MAX_K];  // [nnz_t] columns of a tile's exclusive entries, from the tile's start on
+  RowCounts *row_cnt;     // [row blocks] of every 256 rows
+  RowCounts *row_pre;     // [row blocks + 1] of the rows in front
+  uint32_t *bad;          // set when the snapshots turn out not to be canonical
 };
-
-__host__ __device__ inline int part_snapshot(int part) { return part == 0 ? 0 : part - 1; }
-
-// Selected entries of word w of a part, as a bit mask.
-__device__ inline uint64_t selected_word(const Parts &p, const Snaps &s, int part, uint32_t w) {
-  const int t = part_snapshot(part);
-  uint64_t b = p.bits[t][w];
-  if (part == 0) return b;
-  const int64_t left = (int64_t)s.nnz[t] - (int64_t)w * 64;
-  const uint64_t valid = left >= 64 ? ~0ull : ((1ull << left) - 1ull);
-  return ~b & valid;
-}
 
 // ---- validation -----------------------------------------------------------------------------
 // One wave per (snapshot, row): row pointer sanity, then column range / order / diagonal.
@@ -87,7 +81,7 @@ __global__ __launch_bounds__(kBlock) void k_validate(Snaps s, int32_t n, int32_t
   if (!ok) *bad = 1;
 }
 
-// ---- mark -----------------------------------------------------------------------------------
+// ---- bounds ---------------------------------------------------------------------------------
 // Last row i in [lo, hi] with rowptr[i] <= e, given rowptr[lo] <= e < rowptr[hi + 1].
 __device__ inline int32_t row_of_entry(const int32_t *rp, int32_t lo, int32_t hi, int32_t e) {
   while (lo < hi) {
@@ -97,247 +91,627 @@ __device__ inline int32_t row_of_entry(const int32_t *rp, int32_t lo, int32_t hi
   return lo;
 }
 
-// Position of column c in the ascending run col[a, b), or -1, given that col[g] == v != c for some
-// g in [a, b).  The search gallops outwards from g, so it costs O(log distance): adjacent
-// snapshots differ in few entries, so the offset of a column within its row barely moves from one
-// snapshot to the next.
-__device__ inline int32_t gallop_from(const int32_t *col, int32_t a, int32_t b, int32_t g,
-                                      int32_t v, int32_t c) {
-  int32_t lo, hi;  // the answer, if any, is the lower bound of c within [lo, hi)
-  if (v < c) {
-    int32_t prev = g, step = 1, cur;
-    while (true) {
-      cur = g + step;
-      if (cur >= b) { cur = b; break; }
-      if (col[cur] >= c) break;
-      prev = cur;
-      step <<= 1;
-    }
-    lo = prev + 1;
-    hi = cur;
-  } else {
-    int32_t next = g, step = 1, cur;
-    while (true) {
-      cur = g - step;
-      if (cur < a) { cur = a - 1; break; }
-      if (col[cur] < c) break;
-      next = cur;
-      step <<= 1;
-    }
-    lo = cur + 1;
-    hi = next;
-  }
+// First position in col[lo, hi) (ascending) that holds c or more.
+__device__ inline int32_t lower_bound(const int32_t *col, int32_t lo, int32_t hi, int32_t c) {
   while (lo < hi) {
     const int32_t mid = lo + ((hi - lo) >> 1);
     if (col[mid] < c) lo = mid + 1; else hi = mid;
   }
-  return (lo < b && col[lo] == c) ? lo : -1;
+  return lo;
 }
 
-// wave_row[w] = row that holds entry 64*w of snapshot 0, for w in [0, ceil(nnz0/64)); one extra
-// slot at the end receives n - 1.  One thread per row writes the (usually zero or one) slots whose
-// entry falls into its row, so k_mark needs no search over the whole row-pointer array.
-__global__ __launch_bounds__(kBlock) void k_wave_rows(const int32_t *rp0, int32_t n, int32_t nnz0,
-                                                       int32_t *wave_row) {
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i >= n) return;
-  const int32_t a = rp0[i], b = rp0[i + 1];
-  for (int64_t w = ((int64_t)a + kWave - 1) / kWave; w * kWave < b; ++w) wave_row[w] = (int32_t)i;
-  if (i == n - 1) wave_row[((int64_t)nnz0 + kWave - 1) / kWave] = n - 1;
-}
-
-// One lane per stored entry of snapshot 0.  The row of a wave's first entry and an upper bound for
-// the row of its last one come from wave_row; every lane then only searches between those two.
-//
-// Finding the entries' columns in the other snapshots: the 64 entries of a wave are a contiguous
-// stretch of snapshot 0 in (row, column) order, so their matches lie in a contiguous stretch of
-// every other snapshot, about as long and - adjacent snapshots differ little - at about the same
-// offset from the start of the first lane's row.  The wave stages that stretch (kMarkWindow
-// columns per snapshot, two coalesced loads) in LDS and every lane searches its own row's part of
-// the window there.  A lane whose row reaches beyond the window on a side where its column could
-// lie falls back to probing global memory: first at the same relative offset, then galloping.
-constexpr int kMarkGroup = 8;     // snapshots staged together (bounds registers and LDS)
-constexpr int kMarkWindow = 128;  // columns per snapshot staged by a wave
-constexpr int kMarkMargin = 32;   // window columns in front of the first lane's guessed place
-
-template <int KMAX>
-__global__ __launch_bounds__(kBlock) void k_mark(Snaps s, Parts p, int32_t n, int32_t k,
-                                                  const int32_t *wave_row) {
-  __shared__ int32_t win[kWavesPerBlock][kMarkGroup][kMarkWindow];
-  const int64_t e64 = (int64_t)blockIdx.x * kBlock + threadIdx.x;  // wave-aligned: 64 | kBlock
-  const int lane = threadIdx.x % kWave;
-  const int wv = threadIdx.x / kWave;
-  const int32_t nnz0 = s.nnz[0];
-  const bool in = e64 < nnz0;
-  const int32_t e = in ? (int32_t)e64 : nnz0 - 1;
-  const int32_t *rp0 = s.rowptr[0];
-  const int64_t nwaves0 = ((int64_t)nnz0 + kWave - 1) / kWave;
-  const int64_t w = min(e64 / kWave, nwaves0 - 1);  // waves past the end repeat the last one
-  // (clamped, so that a row-pointer array that is not a valid offset array cannot send the search
-  // out of range: its slots may then be unwritten)
-  const int32_t r_first = min(max(wave_row[w], 0), n - 1);
-  const int32_t r_last = min(max(wave_row[w + 1], r_first), n - 1);  // next wave's first row, or n - 1
-  const int32_t c = s.col[0][e];
-  // Row of the entry: the wave stages the row pointers of its candidate rows in LDS (one round
-  // trip to memory instead of one per step of a search) when they are few enough.
-  int32_t i, row_start;
-  const int32_t nrows = r_last - r_first + 1;
-  if (nrows == 1) {
-    i = r_first;
-    row_start = rp0[i];
-  } else if (nrows < kMarkWindow) {
-    int32_t *rs = win[wv][0];
-    const int32_t a0 = r_first + lane, a1 = a0 + kWave;
-    rs[lane] = a0 <= r_last ? rp0[a0] : INT32_MAX;
-    rs[lane + kWave] = a1 <= r_last ? rp0[a1] : INT32_MAX;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    int32_t cnt = 0;  // number of staged row pointers <= e (at least 1, fewer than kMarkWindow)
-#pragma unroll
-    for (int step = kMarkWindow / 2; step >= 1; step >>= 1)
-      if (rs[cnt + step - 1] <= e) cnt += step;
-    cnt = max(cnt, 1);
-    i = r_first + cnt - 1;
-    row_start = rs[cnt - 1];
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+// The same, looking outwards from position `at` first: O(log distance) steps.
+__device__ inline int32_t lower_bound_near(const int32_t *col, int32_t lo, int32_t hi, int32_t at, int32_t c) {
+  if (lo >= hi) return lo;
+  at = min(max(at, lo), hi - 1);
+  int32_t a = lo, b = hi;  // the answer lies in [a, b]
+  if (col[at] < c) {
+    a = at + 1;
+    for (int64_t step = 8; at + step < hi; step <<= 2) {
+      if (col[at + step] >= c) {
+        b = (int32_t)(at + step);
+        break;
+      }
+      a = (int32_t)(at + step + 1);
+    }
   } else {
-    i = row_of_entry(rp0, r_first, r_last, e);
-    row_start = rp0[i];
+    b = at;
+    for (int64_t step = 8; at - step >= lo; step <<= 2) {
+      if (col[at - step] < c) {
+        a = (int32_t)(at - step + 1);
+        break;
+      }
+      b = (int32_t)(at - step);
+    }
   }
-  const int32_t rel = e - row_start;  // offset of the entry within its row: the first guess
-  bool found = in;
-  int32_t pos[KMAX];
+  return lower_bound(col, a, b, c);
+}
+
+struct RowClasses {  // the thresholds of the row classes
+  int32_t short_max, mid_max, threshold, segment;
+};
+
+// Counts of 256 rows, a thread each.
+__device__ inline void count_rows(const RowClasses &rc, bool live, int64_t L, int64_t entries, int32_t common,
+                                  RowCounts *out) {
+  __shared__ uint32_t w_mid[kWavesPerBlock], w_hub[kWavesPerBlock], w_units[kWavesPerBlock],
+      w_common[kWavesPerBlock];
+  __shared__ uint64_t w_all[kWavesPerBlock];
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  const int cls = row_class(L, rc.short_max, rc.mid_max);
+  const uint64_t is_mid = __ballot(live && cls == 1), is_hub = __ballot(live && cls == 2);
+  const bool hub = is_hub >> lane & 1ull;
+  uint32_t units = 0, shared = 0;
+  uint64_t all = 0;
+  if (is_hub) {
+    units = hub ? hub_units(L, rc.threshold, rc.segment) : 0u;
+    shared = hub ? (uint32_t)common : 0u;
+    all = hub ? (uint64_t)entries : 0ull;
 #pragma unroll
-  for (int t = 0; t < KMAX; ++t) pos[t] = 0;
-  constexpr int G = kMarkGroup, W = kMarkWindow;
+    for (int m = kWave >> 1; m >= 1; m >>= 1) {
+      units += __shfl_xor(units, m, kWave);
+      shared += __shfl_xor(shared, m, kWave);
+      all += __shfl_xor(all, m, kWave);
+    }
+  }
+  if (lane == 0) {
+    w_mid[wave] = (uint32_t)__popcll(is_mid);
+    w_hub[wave] = (uint32_t)__popcll(is_hub);
+    w_units[wave] = units;
+    w_common[wave] = shared;
+    w_all[wave] = all;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    RowCounts c = {0, 0, 0, 0, 0};
 #pragma unroll
-  for (int t0 = 1; t0 < KMAX; t0 += G) {
-    if (t0 < k && __any(found)) {
-      int32_t lo[G], hi[G], P[G];
-      {
-        int32_t v0[G], v1[G];
+    for (int w = 0; w < kWavesPerBlock; ++w) {
+      c.common += w_common[w];
+      c.mid += w_mid[w]; c.hub += w_hub[w]; c.units += w_units[w]; c.entries += w_all[w];
+    }
+    *out = c;
+  }
+}
+
+// Eight lanes per tile boundary: they find its row together (a 9-way search: seven round trips to
+// memory for a million rows instead of twenty), then each of them its column in some of the
+// snapshots.
+__device__ inline void find_bounds(const Snaps &s, const Tiles &g, int64_t wave, int lane) {
+  constexpr int G = 8;
+  const int sub = lane & (G - 1), group0 = lane & ~(G - 1);
+  const int64_t c64 = wave * (kWave / G) + lane / G;
+  const bool search = c64 < g.ntiles;
+  const int32_t c = (int32_t)min(c64, (int64_t)g.ntiles);
+  const int64_t ldb = (int64_t)g.ntiles + 1;
+  const int32_t *rp = s.rowptr[g.base];
+  const int32_t e = search ? c << g.tile_log2 : 0;
+  int32_t lo = 0, hi = search ? g.n : 1;  // rp[lo] <= e < rp[hi]
+  while (__any(hi - lo > 1)) {
+    const int32_t step = (int32_t)(((int64_t)hi - lo + G) / (G + 1));
+    const int64_t idx = lo + (int64_t)(sub + 1) * step;
+    const int32_t v = rp[min(idx, (int64_t)g.n)];
+    const bool below = idx < hi && v <= e;
+    const int m = __popc((uint32_t)(__ballot(below) >> group0) & ((1u << G) - 1u));
+    lo += m * step;
+    hi = (int32_t)min((int64_t)hi, (int64_t)lo + max(step, 1));
+  }
+  if (c64 > g.ntiles) return;
+  if (sub == 0) g.brow[c] = search ? lo : max(g.n - 1, 0);
+  for (int t = sub; t < g.k; t += G) {
+    int32_t at;
+    if (!search) at = s.nnz[t];
+    else if (c == 0) at = 0;  // entries in front of the base's first one belong to the first tile
+    else if (t == g.base) at = e;
+    else {
+      const int32_t first = s.rowptr[t][lo];
+      at = lower_bound_near(s.col[t], first, s.rowptr[t][lo + 1], first + (e - rp[lo]), s.col[g.base][e]);
+    }
+    g.bound[t * ldb + c] = at;
+  }
+}
+
+// The first `bound_blocks` workgroups find the tiles' bounds (they wait for memory most of the
+// time), the others take 256 rows each: dinv_t[i] = (1 + |row i of snapshot t|)^-1/2, evaluated in
+// double and rounded once, and the counts the row lists are laid out by.
+__global__ __launch_bounds__(kBlock) void k_prepare(Snaps s, Tiles g, RowClasses rc, int32_t bound_blocks,
+                                                     float *dinv, float *dinv_nk) {
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  if ((int32_t)blockIdx.x < bound_blocks) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) *g.bad = 0;
+    find_bounds(s, g, (int64_t)blockIdx.x * kWavesPerBlock + wave, lane);
+    return;
+  }
+  const int64_t rb = (int64_t)blockIdx.x - bound_blocks;
+  const int64_t i64 = rb * kBlock + threadIdx.x;
+  const bool live = i64 < g.n;
+  const int32_t i = (int32_t)min(i64, (int64_t)g.n - 1);
+  int32_t longest = 0;
+  int64_t all = 0;
+  constexpr int CH = 4;  // snapshots whose row pointers are requested together
+  for (int t0 = 0; t0 < g.k; t0 += CH) {
+    int32_t a[CH], b[CH];
 #pragma unroll
-        for (int u = 0; u < G; ++u) {
-          const int t = t0 + u;
-          lo[u] = hi[u] = P[u] = 0;
-          v0[u] = v1[u] = INT32_MAX;
-          if (t < KMAX && t < k) {
-            lo[u] = s.rowptr[t][i];
-            hi[u] = s.rowptr[t][i + 1];
-          }
-        }
+    for (int u = 0; u < CH; ++u) {
+      const int32_t *rp = s.rowptr[min(t0 + u, g.k - 1)];
+      a[u] = rp[i];
+      b[u] = rp[i + 1];
+    }
+    float v[CH];
 #pragma unroll
-        for (int u = 0; u < G; ++u) {
-          const int t = t0 + u;
-          if (t < KMAX && t < k) {
-            P[u] = max(__shfl(lo[u] + rel, 0) - kMarkMargin, 0);
-            const int32_t a0 = P[u] + lane, a1 = a0 + kWave;
-            if (a0 < s.nnz[t]) v0[u] = s.col[t][a0];
-            if (a1 < s.nnz[t]) v1[u] = s.col[t][a1];
-          }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");  // earlier readers of win are done
-#pragma unroll
-        for (int u = 0; u < G; ++u) {
-          win[wv][u][lane] = v0[u];
-          win[wv][u][lane + kWave] = v1[u];
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    for (int u = 0; u < CH; ++u) {
+      const int32_t len = b[u] - a[u];
+      v[u] = (float)(1.0 / sqrt((double)(len + 1)));
+      if (t0 + u < g.k) {
+        longest = max(longest, len);
+        all += len;
+        if (live) dinv[(int64_t)(t0 + u) * g.n + i] = v[u];
       }
-      // The row's part of the window holds the match, if there is one, unless the row goes on in
-      // front of the window with columns that may still reach c, or likewise behind it.  The
-      // search is branch-free: window slots in front of the row's part count as smaller than c,
-      // slots behind it as larger, which keeps the predicate monotone over the whole window.
-      uint32_t outside = 0;  // snapshots this lane has to look up in global memory
+    }
+    if (live) {  // node-major copy for the scatter step (one line per node)
+      float *nk = dinv_nk + (int64_t)i * g.k + t0;
+      if ((g.k & 3) == 0) {
+        *reinterpret_cast<float4 *>(nk) = make_float4(v[0], v[1], v[2], v[3]);
+      } else {
 #pragma unroll
-      for (int u = 0; u < G; ++u) {
-        const int t = t0 + u;
-        if (t < KMAX && t < k) {
-          const int32_t *wu = win[wv][u];
-          const int32_t s0 = max(lo[u], P[u]) - P[u], s1 = min(hi[u], P[u] + W) - P[u];
-          // (bitwise operators on purpose: every LDS read is unconditional, no branches)
-          const int32_t w_first = wu[0], w_last = wu[W - 1];
-          const bool front_ok = (lo[u] >= P[u]) | ((P[u] < hi[u]) & (w_first <= c));
-          const bool back_ok = (hi[u] <= P[u] + W) | ((P[u] + W - 1 >= lo[u]) & (w_last >= c));
-          int32_t a = 0;  // slots counted as smaller than c, capped at W - 1
-#pragma unroll
-          for (int step = W / 2; step >= 1; step >>= 1) {
-            const int32_t idx = a + step - 1;
-            const int32_t v = wu[idx];
-            const bool below = (idx < s0) | ((idx < s1) & (v < c));
-            a += below ? step : 0;
-          }
-          const int32_t v_at = wu[a];
-          const bool hit = (a < s1) & (v_at == c);
-          const bool inwin = front_ok & back_ok;
-          pos[t] = P[u] + a;
-          if (hi[u] <= lo[u]) found = false;
-          else if (!inwin) outside |= 1u << u;
-          else found = found && hit;
-        }
-      }
-      if (outside != 0 && found) {
-#pragma unroll
-        for (int u = 0; u < G; ++u) {
-          const int t = t0 + u;
-          if (t < KMAX && t < k && (outside >> u & 1u) && found) {
-            const int32_t g = min(max(lo[u] + rel, lo[u]), hi[u] - 1);
-            const int32_t v = s.col[t][g];
-            pos[t] = v == c ? g : gallop_from(s.col[t], lo[u], hi[u], g, v, c);
-            found = pos[t] >= 0;
-          }
-        }
+        for (int u = 0; u < CH; ++u)
+          if (t0 + u < g.k) nk[u] = v[u];
       }
     }
   }
-  const uint64_t word = __ballot(found);
-  if (lane == 0 && in) p.bits[0][e64 >> 6] = word;
-  if (found) {
-    // plain byte stores (every byte has one writer); positions ascend with the lane, so the
-    // stores of a wave fall into a few cache lines
+  count_rows(rc, live, longest, all, 0, g.row_cnt + rb);
+}
+
+// ---- mark -----------------------------------------------------------------------------------
+// A workgroup per tile of T base entries.  The stretches of the other snapshots are all staged in
+// LDS at once, so that one round trip to memory covers them and no barrier stands between the
+// snapshots.  Two steps of search: first every 64th base entry's place in every snapshot (a thread
+// per place, over the whole stretch); between two of these places a wave's 64 entries lie evenly
+// enough that a look-up needs four LDS reads in the 15 places around the interpolated one, and only
+// where some lane does not find its column bracketed there the wave searches all that lies between.
+// Once it is known which base entries are common, their places in the windows get the sign bit, and
+// what has none is exclusive: a wave per snapshot writes it out.
+//
+// Bound by vector-ALU issue (1M-node R-MAT frame: 0.22 G wave instructions, 0.37 of 0.40 ms, when
+// the first look was taken at a row's or the tile's start and half of the waves had to search).
+// The tiles took over from byte flags in global memory (cleared, set, packed and counted by four
+// kernels) and a window per wave.
+template <int KM, int T>
+__global__ __launch_bounds__(kBlock) void k_mark(Snaps s, Tiles g, int32_t mid_max) {
+  constexpr int R = T / kBlock;       // base entries per thread
+  constexpr int CAP = T + T / 4;      // longest stretch that is staged; longer ones stay in memory
+  constexpr int WORDS = T / 64;
+  constexpr int U = KM - 1;           // snapshots besides the base
+  __shared__ int32_t rows[T];
+  __shared__ int32_t key_row[WORDS], key_col[WORDS];  // every 64th base entry
+  __shared__ int32_t place[U][WORDS + 1];             // ... and its place in every snapshot
+  __shared__ const int32_t *rp_of[U];
+  __shared__ int32_t start_of[U], len_of[U];
+  __shared__ uint64_t common[WORDS];
+  extern __shared__ int32_t lds[];    // 16 words that are only read, [k - 1][CAP], 16 more
+  int32_t *const wins = lds + 16;
+  const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+  const int32_t tile = blockIdx.x;
+  const int64_t ldb = (int64_t)g.ntiles + 1;
+  const int32_t *rp0 = s.rowptr[g.base], *col0 = s.col[g.base];
+  const int32_t e0 = tile * T;
+  const int32_t here = min(T, s.nnz[g.base] - e0);
+  const int32_t r0 = g.brow[tile], r1 = g.brow[tile + 1];
+  const int32_t nrows = r1 - r0 + 1;
+  const int others = g.k - 1;
+
+  int32_t c[R], row[R];
 #pragma unroll
-    for (int t = 1; t < KMAX; ++t)
-      if (t < k) p.flag8[t][pos[t]] = 1;
+  for (int q = 0; q < R; ++q) c[q] = col0[e0 + min(q * kBlock + tid, here - 1)];
+  int32_t bt[U], len[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int t = u + (u >= g.base ? 1 : 0);
+    bt[u] = len[u] = 0;
+    if (t < g.k) {
+      bt[u] = g.bound[t * ldb + tile];
+      len[u] = g.bound[t * ldb + tile + 1] - bt[u];
+    }
   }
+  // (all loads of the tile are requested before the first one is waited for: indices are clamped
+  // instead of branched around)
+  constexpr int Q = (CAP + kBlock - 1) / kBlock;
+  int32_t wv[U][Q], rv[R];
+  const bool rows_staged = nrows > 1 && nrows <= T;
+#pragma unroll
+  for (int q = 0; q < R; ++q) rv[q] = rp0[r0 + min(q * kBlock + tid, nrows - 1)];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int t = u + (u >= g.base ? 1 : 0);
+    const bool some = t < g.k && len[u] > 0;
+    const int32_t *col = some ? s.col[min(t, g.k - 1)] + bt[u] : col0 + e0;
+    const int32_t last = some ? len[u] - 1 : 0;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) wv[u][q] = col[min(q * kBlock + tid, last)];
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (tid == u && u < others) {
+      rp_of[u] = s.rowptr[u + (u >= g.base ? 1 : 0)];
+      start_of[u] = bt[u];
+      len_of[u] = len[u];
+    }
+  if (rows_staged)
+#pragma unroll
+    for (int q = 0; q < R; ++q) rows[q * kBlock + tid] = q * kBlock + tid < nrows ? rv[q] : INT32_MAX;
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (u < others)
+#pragma unroll
+      for (int q = 0; q < Q; ++q)
+        if (q * kBlock + tid < CAP) wins[u * CAP + q * kBlock + tid] = wv[u][q];
+  __syncthreads();
+  // rows of this thread's entries
+  if (nrows == 1) {
+#pragma unroll
+    for (int q = 0; q < R; ++q) row[q] = r0;
+  } else if (rows_staged) {
+    int top = 1;
+    while (2 * top <= nrows) top <<= 1;
+    int32_t cnt[R];  // staged row pointers <= e (at least 1, fewer than T)
+#pragma unroll
+    for (int q = 0; q < R; ++q) cnt[q] = 0;
+    for (int step = top; step >= 1; step >>= 1)
+#pragma unroll
+      for (int q = 0; q < R; ++q) {
+        const int32_t v = rows[min(cnt[q] + step, T) - 1];
+        cnt[q] += v <= e0 + min(q * kBlock + tid, here - 1) ? step : 0;
+      }
+#pragma unroll
+    for (int q = 0; q < R; ++q) row[q] = r0 + min(max(cnt[q], 1), nrows) - 1;
+  } else {
+#pragma unroll
+    for (int q = 0; q < R; ++q)
+      row[q] = row_of_entry(rp0, r0, r1, e0 + min(q * kBlock + tid, here - 1));
+  }
+#pragma unroll
+  for (int q = 0; q < R; ++q)
+    if (lane == 0) {
+      key_row[q * kWavesPerBlock + wave] = row[q];
+      key_col[q * kWavesPerBlock + wave] = c[q];
+    }
+  int32_t lo[U][R], hi[U][R];
+  bool found[R], hub[R];
+#pragma unroll
+  for (int q = 0; q < R; ++q) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int t = u + (u >= g.base ? 1 : 0);
+      const int32_t *rp = s.rowptr[min(t, g.k - 1)];
+      lo[u][q] = rp[row[q]];
+      hi[u][q] = rp[row[q] + 1];
+    }
+    found[q] = q * kBlock + tid < here;
+    hub[q] = rp0[row[q] + 1] - rp0[row[q]] > mid_max;
+  }
+  __syncthreads();
+  // places of every 64th entry (a word past the tile's end lies at the stretch's end)
+  for (int x = tid; x < others * (WORDS + 1); x += kBlock) {
+    const int u = x / (WORDS + 1), w = x - u * (WORDS + 1);
+    const int32_t l = len_of[u];
+    int32_t at = 0;
+    if (w * 64 >= here) {
+      at = l;
+    } else if (w > 0 && l <= CAP) {
+      const int32_t *rp = rp_of[u], *win = wins + u * CAP;
+      const int32_t i = key_row[w], cc = key_col[w];
+      const int32_t f0 = max(rp[i] - start_of[u], 0), f1 = min(rp[i + 1] - start_of[u], l);
+      at = f0;
+#pragma unroll
+      for (int step = T; step >= 1; step >>= 1) {
+        const int32_t idx = at + step - 1;
+        const int32_t v = win[min(idx, CAP - 1)];
+        at += (idx < f1) & (v < cc) ? step : 0;
+      }
+    }
+    place[u][w] = min(max(at, 0), l);
+  }
+  __syncthreads();
+  int32_t pos[U][R];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    if (u >= others) break;
+    const int32_t *win = wins + u * CAP;
+    const bool staged = len[u] <= CAP;
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+      pos[u][q] = 0;
+      hub[q] |= hi[u][q] - lo[u][q] > mid_max;
+      if (!__any(found[q])) continue;
+      if (staged) {
+        // (places in bytes from here on: an LDS address is one addition away)
+        const int w = q * kWavesPerBlock + wave;
+        const int32_t w0 = __builtin_amdgcn_readfirstlane(place[u][w]);
+        const int32_t w1 = max(__builtin_amdgcn_readfirstlane(place[u][w + 1]), w0);
+        const int32_t p0 = w0 * 4, p1 = w1 * 4;
+        const char *const wb = reinterpret_cast<const char *>(win);
+        auto at = [&](int32_t byte) { return *reinterpret_cast<const int32_t *>(wb + byte); };
+        // the part of the row's stretch that can hold the entry
+        const int32_t f0 = min(max(lo[u][q] - bt[u], w0), w1) * 4, end = min(max(hi[u][q] - bt[u], w0), w1) * 4;
+        const int32_t guess = p0 + ((__mul24(p1 - p0, lane) >> 6) & ~3) - 28;
+        int32_t a = max(min(guess, end - 60), f0);
+        int32_t z = min(a + 60, end);
+        const bool in_front = (a == f0) | (at(a - 4) < c[q]);
+        const bool behind = (z >= end) | (at(z) >= c[q]);
+        int step = 32;
+        if (__any(found[q] & !(in_front & behind))) {
+          a = f0;
+          z = end;
+          step = 4 << (31 - __builtin_clz(((p1 - p0) >> 2) + 1));
+          for (; step > 32; step >>= 1) {
+            const int32_t v = at(min(a + step, z) - 4);
+            a += v < c[q] ? step : 0;
+            a = min(a, max(z, f0));
+          }
+        }
+        // (a look past z reads the last column in front of it: if that is smaller, so are all, and the
+        // final min() puts the place at z)
+#pragma unroll
+        for (int s4 = 32; s4 >= 4; s4 >>= 1) {
+          const int32_t v = at(min(a + s4, z) - 4);
+          a += v < c[q] ? s4 : 0;
+        }
+        a = min(a, max(z, f0));
+        found[q] = found[q] & (a < end) & (at(a) == c[q]);
+        pos[u][q] = a >> 2;
+      } else if (found[q]) {
+        const int32_t *col = s.col[u + (u >= g.base ? 1 : 0)] + bt[u];
+        const int32_t f0 = max(lo[u][q] - bt[u], 0), f1 = min(hi[u][q] - bt[u], len[u]);
+        const int32_t a = f0 < f1 ? lower_bound(col, f0, f1, c[q]) : f1;
+        found[q] = a < f1 && col[a] == c[q];
+      }
+    }
+  }
+
+#pragma unroll
+  for (int q = 0; q < R; ++q) {
+    const uint64_t word = __ballot(found[q]), hubs = __ballot(hub[q]);
+    const int w = q * kWavesPerBlock + wave;
+    if (lane == 0) {
+      common[w] = word;
+      key_row[w] = __popcll(word & hubs);
+      if (w * 64 < here) {
+        const int64_t at = ((int64_t)tile << (g.tile_log2 - 6)) + w;
+        g.bits[at] = word;
+        g.hub_bits[at] = hubs;
+      }
+    }
+  }
+  __syncthreads();  // nobody searches the windows any more
+  uint32_t total = 0, in_hubs = 0;  // common entries of the tile (every thread)
+#pragma unroll
+  for (int w = 0; w < WORDS; ++w) {
+    if (tid == w && w * 64 < here) g.wpre[((int64_t)tile << (g.tile_log2 - 6)) + w] = (uint16_t)total;
+#pragma unroll
+    for (int q = 0; q < R; ++q)  // exclusive entries of the base
+      if (w == q * kWavesPerBlock + wave) {
+        const uint32_t x = q * kBlock + tid;
+        if ((int32_t)x < here && !found[q])
+          g.excl[g.base][e0 + x - total - (uint32_t)__popcll(common[w] & ((1ull << lane) - 1ull))] = c[q];
+      }
+    total += (uint32_t)__popcll(common[w]);
+    in_hubs += (uint32_t)key_row[w];
+  }
+  if (tid == 0) g.tile_cnt[tile] = make_uint2(total, in_hubs);
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    if (u >= others) break;
+    if (len[u] <= CAP)
+#pragma unroll
+      for (int q = 0; q < R; ++q)
+        if (found[q]) wins[u * CAP + pos[u][q]] = c[q] | INT32_MIN;
+  }
+  __syncthreads();
+
+  // exclusive entries of the other snapshots: a wave per snapshot
+  bool bad = false;
+  for (int u = wave; u < others; u += kWavesPerBlock) {
+    const int t = __builtin_amdgcn_readfirstlane(u + (u >= g.base ? 1 : 0));
+    const int32_t start = __builtin_amdgcn_readfirstlane(start_of[u]), l = __builtin_amdgcn_readfirstlane(len_of[u]);
+    bad |= l < 0;
+    int32_t *out = g.excl[t] + start;
+    const int32_t *col = s.col[t] + start;
+    int32_t kept = 0;
+    for (int32_t w = 0; w * 64 < l; ++w) {
+      const int32_t p = w * 64 + lane;
+      bool is = false;
+      int32_t v = 0;
+      if (l <= CAP) {
+        v = wins[u * CAP + min(p, CAP - 1)];
+        is = p < l && v >= 0;
+      } else if (p < l) {  // a stretch that was not staged: look the entry up in the base
+        v = col[p];
+        const int32_t i = row_of_entry(s.rowptr[t], 0, g.n - 1, start + p);
+        const int32_t a = max(rp0[i], e0), b = min(rp0[i + 1], e0 + here);
+        const int32_t at = a < b ? lower_bound(col0, a, b, v) : b;
+        is = !(at < b && col0[at] == v && (common[(at - e0) >> 6] >> ((at - e0) & 63) & 1ull));
+      }
+      const uint64_t word = __ballot(is);
+      if (is)
+        out[kept + (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(word >> 32),
+                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)word, 0))] = v;
+      kept += (int32_t)__popcll(word);
+    }
+    // In canonical snapshots every common entry is found once in each of them; anything else is
+    // reported, so that what follows never writes past the sizes computed from these counts.
+    bad |= (uint32_t)(l - kept) != total;
+  }
+  if (bad) *g.bad = 1;
 }
 
-// Packs the byte flags (0 or 1) of snapshots 1 .. k-1 into bitmaps (grid.y = t - 1).  A wave takes
-// 4096 flags in four coalesced 1 KB loads; a lane squeezes its 16 flags into 16 bits and four
-// neighbouring lanes merge into one word.  Flags behind a snapshot's last entry are padding inside
-// the cleared flag area, so they read as zero.
-constexpr int kPackPerWave = 4096;
+// ---- scan over the tiles and the row blocks -----------------------------------------------------
+// Exclusive prefix sums of the tiles' counts and of the row blocks' counts, the totals behind the
+// last.  Every workgroup takes a run of them and adds up what lies in front of the run itself (two
+// counts per 16-byte load, 20 loads per thread for the last run of 40k tiles), so that none waits for
+// another; the last one knows the sizes of the frame and sends them to the host (`out` may be host
+// memory: the host waits for `seq` to appear behind them).
+constexpr int kTileScanBlock = 1024;
+constexpr int kTileScanRun = 2 * kTileScanBlock;  // tiles a workgroup scans at a time
+constexpr int kTileScanMost = 64;                 // workgroups; with more tiles each takes several such runs
 
-__device__ inline uint32_t squeeze4(uint32_t x) {  // bytes b0..b3 in {0, 1} -> b0 | b1<<1 | b2<<2 | b3<<3
-  return (x * 0x01020408u) >> 24 & 0xfu;
+// Inclusive sum over the lanes up to this one: within rows of 16 lanes, then across the rows.
+__device__ __forceinline__ uint32_t wave_sum(uint32_t x) {
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);  // row_shr:1
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);  // row_shr:2
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);  // row_shr:4
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);  // row_shr:8
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);  // row_bcast:15
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);  // row_bcast:31
+  return x;
 }
 
-__global__ __launch_bounds__(kBlock) void k_pack(Snaps s, Parts p) {
-  const int t = blockIdx.y + 1;
-  const int32_t nnz = s.nnz[t];
+// Exclusive sums over the workgroup of N values per thread, and their totals.
+template <int N>
+__device__ inline void sum_block(const uint32_t (&v)[N], uint32_t (&before)[N], uint32_t (&total)[N]) {
+  constexpr int NW = kTileScanBlock / kWave;
+  static_assert(NW == 16, "the waves' sums are scanned in one row of lanes");
+  __shared__ uint32_t sums[N][NW];
   const int lane = threadIdx.x % kWave;
-  const int64_t base = ((int64_t)blockIdx.x * kWavesPerBlock + threadIdx.x / kWave) * kPackPerWave;
-  if (base >= nnz) return;  // whole wave
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
 #pragma unroll
-  for (int j = 0; j < kPackPerWave / (16 * kWave); ++j) {
-    const int64_t off = base + (int64_t)(j * kWave + lane) * 16;
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (off < nnz) v = *reinterpret_cast<const uint4 *>(p.flag8[t] + off);
-    const uint32_t bits16 =
-        squeeze4(v.x) | squeeze4(v.y) << 4 | squeeze4(v.z) << 8 | squeeze4(v.w) << 12;
-    unsigned long long part = (unsigned long long)bits16 << (16 * (lane & 3));
-    part |= __shfl_xor(part, 1);
-    part |= __shfl_xor(part, 2);
-    if ((lane & 3) == 0 && off < nnz) p.bits[t][off >> 6] = part;
+  for (int q = 0; q < N; ++q) {
+    const uint32_t inc = wave_sum(v[q]);
+    if (lane == kWave - 1) sums[q][wave] = inc;
+    before[q] = inc - v[q];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < N; ++q) {
+    const uint32_t x = wave_sum(sums[q][lane & (NW - 1)]);  // (lanes 0 .. 15 count)
+    total[q] = (uint32_t)__builtin_amdgcn_readlane((int)x, NW - 1);
+    if (wave > 0) before[q] += (uint32_t)__builtin_amdgcn_readlane((int)x, max(wave - 1, 0));
+  }
+  __syncthreads();
+}
+
+// RowCounts as 32-bit values whose sums over a workgroup do not overflow.
+constexpr int kRowSums = 6;
+__device__ inline void split_counts(const RowCounts &c, bool in, uint32_t (&v)[kRowSums]) {
+  v[0] = in ? c.mid : 0u;
+  v[1] = in ? c.hub : 0u;
+  v[2] = in ? c.units : 0u;
+  v[3] = in ? c.common : 0u;
+  v[4] = in ? (uint32_t)(c.entries & 0xfffffu) : 0u;
+  v[5] = in ? (uint32_t)(c.entries >> 20) : 0u;  // (a workgroup's rows hold fewer than 2^36 entries)
+}
+__device__ inline RowCounts join_counts(const RowCounts &front, const uint32_t (&v)[kRowSums]) {
+  RowCounts c;
+  c.entries = front.entries + (uint64_t)v[4] + ((uint64_t)v[5] << 20);
+  c.common = front.common + v[3];
+  c.mid = front.mid + v[0];
+  c.hub = front.hub + v[1];
+  c.units = front.units + v[2];
+  return c;
+}
+
+// Blocks [b0, b1) of `cnt`, scanned into `pre`; returns the counts in front of b1.  b0 is a multiple
+// of kTileScanBlock, or b1.
+__device__ inline RowCounts scan_rows(const RowCounts *cnt, RowCounts *pre, int64_t b0, int64_t b1) {
+  RowCounts front = {0, 0, 0, 0, 0};
+  for (int64_t base = 0; base < b1; base += kTileScanBlock) {
+    const int64_t at = base + threadIdx.x;
+    uint32_t v[kRowSums], before[kRowSums], total[kRowSums];
+    split_counts(cnt[min(at, b1 - 1)], at < b1, v);
+    sum_block(v, before, total);
+    if (at < b1 && at >= b0) pre[at] = join_counts(front, before);
+    front = join_counts(front, total);
+  }
+  return front;
+}
+
+struct ScanArgs {
+  const uint2 *tile_cnt;
+  uint2 *tile_pre;
+  const RowCounts *row_cnt;
+  RowCounts *row_pre;
+  const uint32_t *bad;
+  int32_t ntiles, k;
+  int64_t row_blocks;
+  int32_t tiles_per_block;      // a multiple of kTileScanRun
+  int64_t rows_per_block;
+};
+
+__global__ __launch_bounds__(kTileScanBlock) void k_scan_counts(ScanArgs a, FrameTotals *out, uint32_t seq) {
+  const int64_t t0 = min((int64_t)blockIdx.x * a.tiles_per_block, (int64_t)a.ntiles);
+  const int64_t t1 = min(t0 + a.tiles_per_block, (int64_t)a.ntiles);
+  uint32_t carry[2], mine[2] = {0, 0}, unused[2];
+  {
+    // what lies in front of the run
+    constexpr int AHEAD = 4;
+    for (int64_t base = 2 * (int64_t)threadIdx.x; base < t0; base += AHEAD * kTileScanRun) {
+      uint4 x[AHEAD];
+#pragma unroll
+      for (int q = 0; q < AHEAD; ++q)
+        x[q] = *reinterpret_cast<const uint4 *>(a.tile_cnt + min(base + (int64_t)q * kTileScanRun, (t0 - 1) & ~(int64_t)1));
+#pragma unroll
+      for (int q = 0; q < AHEAD; ++q)
+        if (base + (int64_t)q * kTileScanRun < t0) {
+          const bool both = base + (int64_t)q * kTileScanRun + 1 < t0;
+          mine[0] += x[q].x + (both ? x[q].z : 0u);
+          mine[1] += x[q].y + (both ? x[q].w : 0u);
+        }
+    }
+    sum_block(mine, unused, carry);
+  }
+  for (int64_t base = t0; base < t1; base += kTileScanRun) {
+    const int64_t at = base + 2 * (int64_t)threadIdx.x;
+    uint4 x = *reinterpret_cast<const uint4 *>(a.tile_cnt + min(at, (t1 - 1) & ~(int64_t)1));  // (padded to a pair)
+    if (at >= t1) x.x = x.y = 0;
+    if (at + 1 >= t1) x.z = x.w = 0;
+    const uint32_t v[2] = {x.x + x.z, x.y + x.w};
+    uint32_t before[2], total[2];
+    sum_block(v, before, total);
+    before[0] += carry[0];
+    before[1] += carry[1];
+    if (at < t1) a.tile_pre[at] = make_uint2(before[0], before[1]);
+    if (at + 1 < t1) a.tile_pre[at + 1] = make_uint2(before[0] + x.x, before[1] + x.y);
+    carry[0] += total[0];
+    carry[1] += total[1];
+  }
+  const int64_t b0 = min((int64_t)blockIdx.x * a.rows_per_block, a.row_blocks);
+  const RowCounts all = scan_rows(a.row_cnt, a.row_pre, b0, min(b0 + a.rows_per_block, a.row_blocks));
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+    a.tile_pre[a.ntiles] = make_uint2(carry[0], carry[1]);
+    a.row_pre[a.row_blocks] = all;
+    FrameTotals v;
+    v.nnz_c = carry[0];
+    v.mid = all.mid;
+    v.hub = all.hub;
+    v.units = all.units;
+    v.split_c = carry[1];
+    v.split_d = all.entries - (uint64_t)a.k * carry[1];  // (what the common entries take in every snapshot)
+    v.bad = *a.bad;
+    v.seq = 0;
+    *out = v;
+    __threadfence_system();
+    __hip_atomic_store(&out->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 
-// ---- count ----------------------------------------------------------------------------------
-// grid.y = part; cnt[word_off[part] + w] = number of selected entries in word w.
-__global__ __launch_bounds__(kBlock) void k_popcount(Snaps s, Parts p, uint32_t *cnt, uint32_t m) {
-  const int part = blockIdx.y;
-  if (part == 0 && blockIdx.x == 0 && threadIdx.x == 0) cnt[m - 1] = 0;  // the trailing word
-  const uint32_t nw = p.word_off[part + 1] - p.word_off[part];
-  const uint32_t w = blockIdx.x * kBlock + threadIdx.x;
-  if (w < nw) cnt[p.word_off[part] + w] = (uint32_t)__popcll(selected_word(p, s, part, w));
+// The transposed frame: the parts' row pointers are known, and with them everything but the totals.
+__global__ __launch_bounds__(kTileScanBlock) void k_scan_row_counts(const RowCounts *row_cnt, RowCounts *row_pre,
+                                                                     int64_t row_blocks, FrameTotals *out,
+                                                                     uint32_t seq) {
+  const RowCounts all = scan_rows(row_cnt, row_pre, 0, row_blocks);
+  if (threadIdx.x == 0) {
+    row_pre[row_blocks] = all;
+    FrameTotals v;
+    v.nnz_c = 0;
+    v.mid = all.mid;
+    v.hub = all.hub;
+    v.units = all.units;
+    v.split_c = all.common;
+    v.split_d = all.entries;
+    v.bad = 0;
+    v.seq = 0;
+    *out = v;
+    __threadfence_system();
+    __hip_atomic_store(&out->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
 }
 
 // ---- exclusive prefix sum over uint32 (three launches) ---------------------------------------
@@ -440,409 +814,545 @@ int exclusive_scan(uint32_t *data, uint32_t m, uint32_t *bsum, hipStream_t st) {
   return exclusive_scan(&data, 1, m, bsum, st);
 }
 
-// ---- row pointers of every part ---------------------------------------------------------------
-// grid.y = part; thread per row boundary i in [0, n].  pre = scanned popcounts (all parts
-// concatenated, one trailing word); differences are taken in uint32 so that a wrapped running
-// total over all parts cannot corrupt a single part (each part has < 2^31 entries).
-__global__ __launch_bounds__(kBlock) void k_rowptr(Snaps s, Parts p, const uint32_t *pre,
-                                                    int32_t n) {
-  const int part = blockIdx.y;
-  const int t = part_snapshot(part);
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i > n) return;
-  const uint32_t r = (uint32_t)s.rowptr[t][i];
-  const uint32_t w = r >> 6, bit = r & 63u;
-  const uint32_t off = p.word_off[part];
-  uint32_t v = pre[off + w] - pre[off];
-  if (bit) v += (uint32_t)__popcll(selected_word(p, s, part, w) & ((1ull << bit) - 1ull));
-  p.rowptr_out[part][i] = (int32_t)v;
-}
+// ---- rows ------------------------------------------------------------------------------------
+// The work lists of the aggregation.
+struct ListArgs {
+  RowClasses rc;
+  int32_t *rows_short, *rows_long, *hub_rows, *hub_item_off, *item_row, *item_v0, *item_v1, *item_c0, *item_d0;
+};
 
-// ---- per-row metadata: D^-1/2 ------------------------------------------------------------------
-// dinv_t[i] = (1 + |row i of snapshot t|)^-1/2, evaluated in double and rounded once.
-__global__ __launch_bounds__(kBlock) void k_dinv(Snaps s, int32_t n, int32_t k, float *dinv,
-                                                  float *dinv_nk) {
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i >= n) return;
-  for (int t = 0; t < k; ++t) {
-    const int32_t len = s.rowptr[t][i + 1] - s.rowptr[t][i];
-    const float v = (float)(1.0 / sqrt((double)(len + 1)));
-    dinv[(int64_t)t * n + i] = v;
-    dinv_nk[i * k + t] = v;  // node-major copy for the scatter step (one line per node)
+// Puts row i (called by every thread of a workgroup of 256 consecutive rows, `live` where there is a
+// row) on its list; `first` holds the counts in front of the workgroup's rows (as summed up from
+// count_rows).  place(entries, common) gives, for a hub row, where its common and its exclusive entries
+// start in the class-grouped copies, from what the hub rows in front of it hold.
+template <class Place>
+__device__ inline void list_row(const ListArgs &q, bool live, int32_t i, int64_t L, int32_t lc, int64_t entries,
+                                const RowCounts &first, Place place) {
+  __shared__ uint32_t w_mid[kWavesPerBlock], w_hub[kWavesPerBlock], w_units[kWavesPerBlock],
+      w_common[kWavesPerBlock];
+  __shared__ uint64_t w_all[kWavesPerBlock];
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  const int cls = row_class(L, q.rc.short_max, q.rc.mid_max);
+  const uint64_t is_mid = __ballot(live && cls == 1), is_hub = __ballot(live && cls == 2);
+  const bool hub = is_hub >> lane & 1ull;
+  // inclusive running sums over the wave's hub rows
+  const uint32_t my_units = hub ? hub_units(L, q.rc.threshold, q.rc.segment) : 0u;
+  const uint64_t my_all = hub ? (uint64_t)entries : 0ull;
+  uint32_t units = my_units, shared = hub ? (uint32_t)lc : 0u;
+  uint64_t all = my_all;
+  if (is_hub) {
+#pragma unroll
+    for (int s = 1; s < kWave; s <<= 1) {
+      const uint32_t u = __shfl_up(units, s, kWave), c = __shfl_up(shared, s, kWave);
+      const uint64_t a = __shfl_up(all, s, kWave);
+      if (lane >= s) { units += u; shared += c; all += a; }
+    }
+  }
+  if (lane == kWave - 1) {
+    w_mid[wave] = (uint32_t)__popcll(is_mid);
+    w_hub[wave] = (uint32_t)__popcll(is_hub);
+    w_units[wave] = units;
+    w_common[wave] = shared;
+    w_all[wave] = all;
+  }
+  __syncthreads();
+  if (!live) return;
+  uint32_t mid = first.mid, h = first.hub, u0 = first.units + units - my_units;
+  uint32_t common = first.common + shared - (hub ? (uint32_t)lc : 0u);
+  uint64_t e = first.entries + all - my_all;
+  for (int w = 0; w < wave; ++w) {
+    mid += w_mid[w];
+    h += w_hub[w];
+    u0 += w_units[w];
+    common += w_common[w];
+    e += w_all[w];
+  }
+  const uint64_t below = (1ull << lane) - 1ull;
+  mid += (uint32_t)__popcll(is_mid & below);
+  h += (uint32_t)__popcll(is_hub & below);
+  if (cls == 0) q.rows_short[(uint32_t)i - mid - h] = i;
+  if (cls == 1) q.rows_long[mid] = i;
+  if (hub) {
+    int32_t c0, d0;
+    place(e, common, &c0, &d0);
+    q.hub_rows[h] = i;
+    q.hub_item_off[h] = (int32_t)u0;
+    for (uint32_t u = 0; u < my_units; ++u) {
+      const int64_t v0 = (int64_t)u * q.rc.segment;
+      q.item_row[u0 + u] = i;
+      q.item_v0[u0 + u] = my_units == 1 ? 0 : (int32_t)v0;
+      q.item_v1[u0 + u] = my_units == 1 ? INT32_MAX : (int32_t)min(v0 + q.rc.segment, (int64_t)INT32_MAX);
+      q.item_c0[u0 + u] = c0 + (my_units == 1 ? 0 : (int32_t)min(v0, (int64_t)lc));
+      q.item_d0[u0 + u] = d0;
+    }
   }
 }
 
-// ---- row classes --------------------------------------------------------------------------------
-// Length L(i) = common + longest exclusive row decides the class (see pipad_frame); the three
-// arrays written here are turned into list positions by exclusive prefix sums.  split_total[p]
-// receives the number of entries that the hub rows hold in part p (0 = common, 1 + t = exclusive
-// part of snapshot t): the sizes of the class-grouped copies.  Integer atomics, one per
-// workgroup and part, so the result does not depend on scheduling.
+// Common entries of the base in front of entry e (nnz > 0 entries; no branches around the loads).
+__device__ inline int32_t common_before(const Tiles &g, int32_t nnz, int32_t e) {
+  const int32_t x = min(max(e, 0), nnz - 1), w = x >> 6;
+  const uint64_t bits = g.bits[w];
+  const uint32_t v = g.tile_pre[x >> g.tile_log2].x + g.wpre[w], all = g.tile_pre[g.ntiles].x;
+  return (int32_t)(e < nnz ? v + (uint32_t)__popcll(bits & ((1ull << (x & 63)) - 1ull)) : all);
+}
+
+// ... those of them that lie in hub rows.
+__device__ inline int32_t hub_common_before(const Tiles &g, int32_t nnz, int32_t e) {
+  if (e >= nnz) return (int32_t)g.tile_pre[g.ntiles].y;
+  const int32_t tile = e >> g.tile_log2, w = e >> 6;
+  uint32_t v = g.tile_pre[tile].y;
+  for (int32_t x = tile << (g.tile_log2 - 6); x < w; ++x) v += (uint32_t)__popcll(g.bits[x] & g.hub_bits[x]);
+  return (int32_t)(v + (uint32_t)__popcll(g.bits[w] & g.hub_bits[w] & ((1ull << (e & 63)) - 1ull)));
+}
+
+struct RowArgs {
+  int32_t *rowptr_c;
+  int32_t *rowptr_d[PIPAD_MAX_K];
+};
+
+// A thread per row i in [0, n].  The exclusive row pointer is the input's minus the common one; the
+// longest row a class is decided by is the longest input row (its common entries are in all of
+// them).
+__global__ __launch_bounds__(kBlock) void k_rows(Snaps s, Tiles g, RowArgs o, ListArgs q) {
+  const int64_t i64 = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  const int32_t i = (int32_t)min(i64, (int64_t)g.n), i1 = min(i + 1, g.n);
+  const bool live = i64 < g.n;
+  const int32_t nnz0 = s.nnz[g.base];
+  const int32_t *rp0 = s.rowptr[g.base];
+  const int32_t ea = rp0[i], eb = rp0[i1];
+  const RowCounts first = g.row_pre[blockIdx.x];
+  int32_t before = 0, after = 0, longest = 0;
+  if (nnz0 > 0) {
+    before = common_before(g, nnz0, ea);
+    after = common_before(g, nnz0, eb);
+  }
+  if (i64 <= g.n) o.rowptr_c[i] = before;
+  // (the clamps only ever act on snapshots that are not canonical: whatever they hold, the row
+  // pointers stay within the parts)
+  const int32_t nnz_c = (int32_t)g.tile_pre[g.ntiles].x;
+  int64_t all = 0;
+  constexpr int CH = 8;  // snapshots whose row pointers are requested together
+  for (int t0 = 0; t0 < g.k; t0 += CH) {
+    int32_t a[CH], b[CH];
+#pragma unroll
+    for (int u = 0; u < CH; ++u) {
+      const int32_t *rp = s.rowptr[min(t0 + u, g.k - 1)];
+      a[u] = rp[i];
+      b[u] = rp[i1];
+    }
+#pragma unroll
+    for (int u = 0; u < CH; ++u)
+      if (t0 + u < g.k) {
+        longest = max(longest, b[u] - a[u]);
+        all += b[u] - a[u];
+        if (i64 <= g.n) o.rowptr_d[t0 + u][i] = min(max(a[u] - before, 0), max(s.nnz[t0 + u] - nnz_c, 0));
+      }
+  }
+  if (i64 == g.n) {  // the end of the last hub row's units
+    const RowCounts total = g.row_pre[((int64_t)g.n + kBlock - 1) / kBlock];
+    q.hub_item_off[total.hub] = (int32_t)total.units;
+  }
+  list_row(q, live, i, longest, after - before, all, first, [&](uint64_t entries, uint32_t, int32_t *c0, int32_t *d0) {
+    *c0 = hub_common_before(g, nnz0, ea);
+    *d0 = (int32_t)((int64_t)entries - (int64_t)g.k * *c0);
+  });
+}
+
+// The same for a frame whose row pointers are in place (the transposed frame): the counts, then the
+// lists.
 struct PartRows {
   const int32_t *rowptr[PIPAD_MAX_K + 1];  // common, then the k exclusive parts
 };
 
-__global__ __launch_bounds__(kBlock) void k_classify(PartRows p, int32_t n, int32_t k,
-                                                      uint32_t *shortflag, uint32_t *hubflag,
-                                                      uint32_t *nseg, uint32_t *split_total,
-                                                      int32_t short_max, int32_t mid_max,
-                                                      int32_t threshold, int32_t segment) {
-  __shared__ uint32_t sums[PIPAD_MAX_K + 1];
-  for (int q = threadIdx.x; q <= k; q += kBlock) sums[q] = 0;
-  __syncthreads();
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i == n) {  // trailing entries of the arrays that get scanned
-    shortflag[n] = 0;
-    hubflag[n] = 0;
-    nseg[n] = 0;
-  } else if (i < n) {
-    const int32_t lc = p.rowptr[0][i + 1] - p.rowptr[0][i];
-    int32_t ldmax = 0;
-    for (int q = 1; q <= k; ++q) ldmax = max(ldmax, p.rowptr[q][i + 1] - p.rowptr[q][i]);
-    const int64_t total = (int64_t)lc + ldmax;
-    const int cls = row_class(total, short_max, mid_max);
-    shortflag[i] = cls == 0 ? 1u : 0u;
-    hubflag[i] = cls == 2 ? 1u : 0u;
-    nseg[i] = cls == 2 ? hub_units(total, threshold, segment) : 0u;
-    if (cls == 2)
-      for (int q = 0; q <= k; ++q) {  // (the few split rows read their row pointers a second time)
-        const int32_t len = p.rowptr[q][i + 1] - p.rowptr[q][i];
-        if (len) atomicAdd(&sums[q], (uint32_t)len);
-      }
+__device__ inline int64_t part_lengths(const PartRows &p, int32_t n, int32_t k, int32_t i, int32_t *lc, int64_t *L) {
+  const int32_t i1 = min(i + 1, n);
+  *lc = p.rowptr[0][i1] - p.rowptr[0][i];
+  int32_t longest = 0;
+  int64_t ld = 0;
+  for (int t = 1; t <= k; ++t) {
+    const int32_t len = p.rowptr[t][i1] - p.rowptr[t][i];
+    longest = max(longest, len);
+    ld += len;
   }
-  __syncthreads();
-  for (int q = threadIdx.x; q <= k; q += kBlock)
-    if (sums[q]) atomicAdd(&split_total[q], sums[q]);
+  *L = (int64_t)*lc + longest;
+  return ld;
 }
 
-// Turns the scanned class arrays into the row lists and the hub units.
-// Every row is in exactly one class, so its position in the mid list is i - (#short before i)
-// - (#hub before i).  A hub row that is not cut is one unit covering its whole entry list.
-__global__ __launch_bounds__(kBlock) void k_row_lists(int32_t n, const uint32_t *shortidx,
-                                                       const uint32_t *hubidx,
-                                                       const uint32_t *segoff, int32_t segment,
-                                                       int32_t *rows_short, int32_t *rows_long,
-                                                       int32_t *hub_rows, int32_t *hub_item_off,
-                                                       int32_t *item_row, int32_t *item_v0,
-                                                       int32_t *item_v1) {
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i > n) return;
-  if (i == n) {
-    hub_item_off[hubidx[n]] = (int32_t)segoff[n];
-    return;
-  }
-  const uint32_t si = shortidx[i], hi = hubidx[i];
-  if (shortidx[i + 1] != si) {
-    rows_short[si] = (int32_t)i;
-  } else if (hubidx[i + 1] != hi) {
-    const uint32_t first = segoff[i], last = segoff[i + 1];
-    hub_rows[hi] = (int32_t)i;
-    hub_item_off[hi] = (int32_t)first;
-    for (uint32_t q = first; q < last; ++q) {
-      item_row[q] = (int32_t)i;
-      const int64_t v0 = (int64_t)(q - first) * segment;
-      item_v0[q] = last - first == 1 ? 0 : (int32_t)v0;
-      item_v1[q] = last - first == 1 ? INT32_MAX : (int32_t)min(v0 + segment, (int64_t)INT32_MAX);
-    }
-  } else {
-    rows_long[(uint32_t)i - si - hi] = (int32_t)i;
-  }
+__global__ __launch_bounds__(kBlock) void k_count_rows(PartRows p, int32_t n, int32_t k, RowClasses rc, RowCounts *cnt) {
+  const int64_t i64 = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  int32_t lc;
+  int64_t L;
+  const int64_t entries = part_lengths(p, n, k, (int32_t)min(i64, (int64_t)n), &lc, &L);
+  count_rows(rc, i64 < n, L, entries, lc, cnt + blockIdx.x);
 }
 
-// ---- class-grouped copies of the split rows' entries ----------------------------------------------
+__global__ __launch_bounds__(kBlock) void k_list_rows(PartRows p, int32_t n, int32_t k, const RowCounts *cnt, ListArgs q) {
+  const int64_t i64 = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  const int32_t i = (int32_t)min(i64, (int64_t)n);
+  if (i64 == n) {
+    const RowCounts total = cnt[((int64_t)n + kBlock - 1) / kBlock];
+    q.hub_item_off[total.hub] = (int32_t)total.units;
+  }
+  int32_t lc;
+  int64_t L;
+  const int64_t entries = part_lengths(p, n, k, i, &lc, &L);
+  list_row(q, i64 < n, i, L, lc, entries, cnt[blockIdx.x], [](uint64_t e, uint32_t c, int32_t *c0, int32_t *d0) {
+    *c0 = (int32_t)c;
+    *d0 = (int32_t)e;
+  });
+}
+
+// ---- class-grouped copies of the hub rows' entries ------------------------------------------------
 struct SplitArgs {
-  int32_t n, n_units, k;
-  int32_t sub_log2;
-  int32_t team_log2;                       // delta fill: lanes per (unit, snapshot) team
-  const int32_t *item_row, *item_v0, *item_v1;
+  int32_t n_units, k, sub_log2;
+  const int32_t *item_row, *item_v0, *item_v1, *item_c0, *item_d0;
   const int32_t *rowptr[PIPAD_MAX_K + 1];  // parts: common, then exclusive
   const int32_t *col[PIPAD_MAX_K + 1];
-  const float *dinv_nk;                    // [n][k]
-  const float *wd[PIPAD_MAX_K];            // canonical scales of the exclusive parts
-  uint32_t *ulen;                          // [(k + 1) * n_units + 1]: lengths, then (scanned) starts
-  uint32_t *sptr;
-  int32_t *scol;
+  int32_t n;
+  const float *dinv, *dinv_nk;             // [k][n], [n][k]
+  int32_t *sptr, *scol_c, *scol_d;
   float *swc[PIPAD_MAX_K];
   float *swd;
-  uint32_t total_c;
 };
 
-// Entries [*a, *b) of part p's column array that unit u covers.
-__device__ inline void unit_range(const SplitArgs &g, int p, int32_t u, int32_t *a, int32_t *b) {
-  const int32_t row = g.item_row[u], v0 = g.item_v0[u], v1 = g.item_v1[u];
-  const int32_t cs = g.rowptr[0][row], lc = g.rowptr[0][row + 1] - cs;
-  if (p == 0) {
-    *a = cs + min(v0, lc);
-    *b = cs + min(v1, lc);
-  } else {
-    const int32_t ds = g.rowptr[p][row], ld = g.rowptr[p][row + 1] - ds;
-    *a = ds + min(max(v0 - lc, 0), ld);
-    *b = ds + min(max(v1 - lc, 0), ld);
-  }
-}
+constexpr int kFillWaves = 2;     // per workgroup
+constexpr int kFillPiece = 2048;  // entries a wave puts in class order in LDS at a time
 
-// ulen[p * n_units + u] = entries of unit u in part p (the trailing word is cleared).
-__global__ __launch_bounds__(kBlock) void k_unit_len(SplitArgs g) {
-  const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  const int64_t m = (int64_t)(g.k + 1) * g.n_units;
-  if (e > m) return;
-  if (e == m) { g.ulen[m] = 0; return; }
-  const int p = (int)(e / g.n_units);
-  int32_t a, b;
-  unit_range(g, p, (int32_t)(e - (int64_t)p * g.n_units), &a, &b);
-  g.ulen[e] = (uint32_t)(b - a);
-}
-
-// The class-grouped copy of one part of one unit by a team of TL = 1 << tl_log2 lanes (all of
-// them active and in step; lanes below `lane0` belong to other teams).  First pass: entries per
-// class; second pass: a stable scatter - a ballot per class gives every lane its rank among the
-// team's lanes of that class - which takes the entries' column scales along.
-template <int NC>
-__device__ inline void split_fill_part(const SplitArgs &g, int p, int32_t u, int tl_log2, int lane) {
-  const int tl = 1 << tl_log2;
-  const int q = lane & (tl - 1);      // lane within the team
-  const int lane0 = lane - q;
-  const uint64_t team_mask = (tl == kWave ? ~0ull : ((1ull << tl) - 1ull)) << lane0;
-  int32_t a, b;
-  unit_range(g, p, u, &a, &b);
-  const int32_t *col = g.col[p];
-#ifndef PIPAD_FILL_CHUNKS
-#define PIPAD_FILL_CHUNKS 8
-#endif
-  constexpr int UN = PIPAD_FILL_CHUNKS;  // chunks in flight per pass
-  uint32_t cnt[NC];
-#pragma unroll
-  for (int x = 0; x < NC; ++x) cnt[x] = 0;
-  for (int32_t e0 = a + q; e0 < b; e0 += UN * tl) {
-    int32_t cv[UN];
-#pragma unroll
-    for (int j = 0; j < UN; ++j) cv[j] = e0 + j * tl < b ? col[e0 + j * tl] : -1;
-#pragma unroll
-    for (int j = 0; j < UN; ++j) {
-      const uint32_t c = cv[j] >= 0 ? column_class(cv[j], g.sub_log2) : (uint32_t)NC;
-#pragma unroll
-      for (int x = 0; x < NC; ++x) cnt[x] += c == (uint32_t)x ? 1u : 0u;
-    }
-  }
-  uint32_t run[NC];  // next free position of every class (the same in all lanes of the team)
-  uint32_t next = g.ulen[(int64_t)p * g.n_units + u];
-  const int64_t v = ((int64_t)p * g.n_units + u) * NC;
-#pragma unroll
-  for (int x = 0; x < NC; ++x) {
-    uint32_t c = cnt[x];
-    for (int m = tl >> 1; m >= 1; m >>= 1) c += __shfl_xor(c, m, kWave);
-    run[x] = next;
-    if (q == 0) g.sptr[v + x] = next;
-    next += c;
-  }
-  const float *wd_t = g.wd[p > 0 ? p - 1 : 0];
-  for (int32_t base = a; base < b; base += UN * tl) {
-    int32_t cv[UN];
-    uint32_t pos[UN];
-#pragma unroll
-    for (int j = 0; j < UN; ++j) {
-      const int32_t e = base + j * tl + q;
-      cv[j] = e < b ? col[e] : -1;
-    }
-#pragma unroll
-    for (int j = 0; j < UN; ++j) {
-      const uint32_t cl = cv[j] >= 0 ? column_class(cv[j], g.sub_log2) : (uint32_t)NC;
-      pos[j] = 0;
-#pragma unroll
-      for (int x = 0; x < NC; ++x) {
-        const uint64_t mask = __ballot(cl == (uint32_t)x) & team_mask;
-        if (cl == (uint32_t)x) pos[j] = run[x] + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
-        run[x] += (uint32_t)__popcll(mask);
-      }
-    }
-    if (p == 0) {
-      // (the k scales of an overlap entry follow in k_split_scales, one lane per grouped entry)
-    } else {
-      float wv[UN];
-#pragma unroll
-      for (int j = 0; j < UN; ++j) wv[j] = cv[j] >= 0 ? wd_t[base + j * tl + q] : 0.f;
-#pragma unroll
-      for (int j = 0; j < UN; ++j)
-        if (cv[j] >= 0) g.swd[pos[j] - g.total_c] = wv[j];
-    }
-#pragma unroll
-    for (int j = 0; j < UN; ++j)
-      if (cv[j] >= 0) g.scol[pos[j]] = cv[j];
-  }
-}
-
-// Column scales of the grouped overlap entries: swc[t][e] = dinv_t[scol[e]], one lane per entry,
-// a node's k scales from the node-major copy of D^-1/2 (one line per node).
-__global__ __launch_bounds__(kBlock) void k_split_scales(SplitArgs g) {
-  const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (e >= g.total_c) return;
-  const float *row = g.dinv_nk + (int64_t)g.scol[e] * g.k;
+// The k scales of UN entries of the common copy, where `live`.
+template <int UN>
+__device__ __forceinline__ void store_scales(const SplitArgs &g, const int32_t (&c)[UN], const int32_t (&to)[UN],
+                                             const int32_t (&live)[UN]) {
   if ((g.k & 3) == 0) {
     for (int t = 0; t < g.k; t += 4) {
-      const float4 w4 = *reinterpret_cast<const float4 *>(row + t);
-      g.swc[t][e] = w4.x; g.swc[t + 1][e] = w4.y; g.swc[t + 2][e] = w4.z; g.swc[t + 3][e] = w4.w;
+      float4 w[UN];
+#pragma unroll
+      for (int r = 0; r < UN; ++r) w[r] = *reinterpret_cast<const float4 *>(g.dinv_nk + (int64_t)c[r] * g.k + t);
+#pragma unroll
+      for (int r = 0; r < UN; ++r)
+        if (live[r]) {
+          g.swc[t][to[r]] = w[r].x; g.swc[t + 1][to[r]] = w[r].y;
+          g.swc[t + 2][to[r]] = w[r].z; g.swc[t + 3][to[r]] = w[r].w;
+        }
     }
   } else {
-    for (int t = 0; t < g.k; ++t) g.swc[t][e] = row[t];
+    for (int t = 0; t < g.k; ++t) {
+      float w[UN];
+#pragma unroll
+      for (int r = 0; r < UN; ++r) w[r] = g.dinv_nk[(int64_t)c[r] * g.k + t];
+#pragma unroll
+      for (int r = 0; r < UN; ++r)
+        if (live[r]) g.swc[t][to[r]] = w[r];
+    }
   }
 }
 
-// One wave per unit: first the overlap part with the whole wave, then the k exclusive parts side
-// by side, a team of 64 / (k rounded up to a power of two) lanes per snapshot (the exclusive parts
-// of a unit are short where the overlap is large, and where it is small there are k of them to
-// keep the wave busy).
+// A wave per (unit, part): the part's entries of the unit, stably grouped by column class.  A piece
+// of 2048 entries (a whole unit, unless the options say otherwise) is read once into registers,
+// counted and put in class order in LDS with one ballot per class and 64 entries, and written out
+// in that order with the scales, so that neighbouring lanes store to neighbouring addresses.  On the
+// 1M-node R-MAT frame 0.24 ms (scattered from the input order, eight runs of stores at a time, and
+// the scales by another kernel: 0.29 ms); 0.81 GB fetched and 0.35 GB written, most of the fetches
+// lines of D^-1/2 for a few scales each.  A kernel for the scales alone that runs every class on
+// the XCD that gathers it later fetches a third of that but shares the lines it writes between
+// XCDs, and the two together were slower (0.26 ms).
 template <int NC>
-__global__ __launch_bounds__(kBlock) void k_split_fill(SplitArgs g) {
-  const int lane = threadIdx.x % kWave;
-  const int64_t id = (int64_t)blockIdx.x * kWavesPerBlock + threadIdx.x / kWave;
-  if (id == 0 && lane == 0)
-    g.sptr[(int64_t)(g.k + 1) * g.n_units * NC] = g.ulen[(int64_t)(g.k + 1) * g.n_units];
+__global__ __launch_bounds__(kFillWaves * kWave) void k_split_fill(SplitArgs g) {
+  constexpr int RND = kFillPiece / kWave;
+  __shared__ int32_t s_col[kFillWaves][kFillPiece];
+  __shared__ int32_t s_off[kFillWaves][NC];  // place in the copy minus place in the piece
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  const int64_t id = (int64_t)blockIdx.x * kFillWaves + wave;
   if (id >= g.n_units) return;
   const int32_t u = __builtin_amdgcn_readfirstlane((int32_t)id);
-  split_fill_part<NC>(g, 0, u, 6, lane);
-  for (int t0 = 0; t0 < g.k; t0 += kWave >> g.team_log2) {
-    const int t = t0 + (lane >> g.team_log2);
-    if (t < g.k) split_fill_part<NC>(g, 1 + t, u, g.team_log2, lane);
+  const int p = blockIdx.y;
+  const int32_t row = g.item_row[u], v0 = g.item_v0[u], v1 = g.item_v1[u];
+  const int32_t cs = g.rowptr[0][row], lc = g.rowptr[0][row + 1] - cs;
+  int32_t a, b, out;  // entries [a, b) of the part, first place in the copy
+  if (p == 0) {
+    a = cs + min(v0, lc);
+    b = cs + min(v1, lc);
+    out = g.item_c0[u];
+  } else {
+    int32_t ds = 0, ld = 0;
+    if (lane < g.k) {
+      ds = g.rowptr[1 + lane][row];
+      ld = g.rowptr[1 + lane][row + 1] - ds;
+    }
+    int32_t before = lane < p - 1 ? ld : 0;  // the row's entries in the exclusive parts in front
+#pragma unroll
+    for (int m = kWave >> 1; m >= 1; m >>= 1) before += __shfl_xor(before, m, kWave);
+    ds = __shfl(ds, p - 1, kWave);
+    ld = __shfl(ld, p - 1, kWave);
+    const int32_t q0 = min(max(v0 - lc, 0), ld), q1 = min(max(v1 - lc, 0), ld);
+    a = ds + q0;
+    b = ds + q1;
+    out = g.item_d0[u] + before + q0;
+  }
+  const int32_t *col = g.col[p];
+  const bool one_piece = b - a <= kFillPiece;
+  int32_t cv[RND];
+  auto load = [&](int32_t at) __attribute__((always_inline)) {
+#pragma unroll
+    for (int r = 0; r < RND; ++r) {
+      if (at + r * kWave >= b) break;
+      const int32_t v = col[min(at + r * kWave + lane, b - 1)];
+      cv[r] = at + r * kWave + lane < b ? v : -1;
+    }
+  };
+  int32_t cnt[NC];  // entries per class (wave-uniform)
+  auto count = [&](int32_t at) __attribute__((always_inline)) {
+#pragma unroll
+    for (int r = 0; r < RND; ++r) {
+      if (at + r * kWave >= b) break;
+      const uint32_t cl = cv[r] >= 0 ? column_class(cv[r], g.sub_log2) : (uint32_t)NC;
+#pragma unroll
+      for (int x = 0; x < NC; ++x) cnt[x] += __popcll(__ballot(cl == (uint32_t)x));
+    }
+  };
+#pragma unroll
+  for (int x = 0; x < NC; ++x) cnt[x] = 0;
+  for (int32_t at = a; at < b; at += kFillPiece) {
+    load(at);
+    count(at);
+  }
+  // the copy's class boundaries: sptr[(p * (NC + 1) + x) * n_units + u]
+  int32_t run[NC];
+  int32_t mine = 0, next = out;
+#pragma unroll
+  for (int x = 0; x < NC; ++x) {
+    run[x] = next;
+    if (lane == x) mine = next;
+    next += cnt[x];
+  }
+  if (lane == NC) mine = next;
+  if (lane <= NC) g.sptr[((int64_t)p * (NC + 1) + lane) * g.n_units + u] = mine;
+
+  int32_t *const stage = s_col[wave];
+  for (int32_t at = a; at < b; at += kFillPiece) {
+    int32_t local[NC];
+    if (!one_piece) {
+      load(at);
+#pragma unroll
+      for (int x = 0; x < NC; ++x) cnt[x] = 0;
+      count(at);
+    }
+    int32_t pos = 0;
+    int32_t off = 0;
+#pragma unroll
+    for (int x = 0; x < NC; ++x) {
+      local[x] = pos;
+      if (lane == x) off = run[x] - pos;
+      pos += cnt[x];
+      run[x] += cnt[x];
+    }
+    if (lane < NC) s_off[wave][lane] = off;
+#pragma unroll
+    for (int r = 0; r < RND; ++r) {
+      if (at + r * kWave >= b) break;
+      const uint32_t cl = cv[r] >= 0 ? column_class(cv[r], g.sub_log2) : (uint32_t)NC;
+      int32_t where = 0;
+#pragma unroll
+      for (int x = 0; x < NC; ++x) {
+        const uint64_t mask = __ballot(cl == (uint32_t)x);
+        if (cl == (uint32_t)x)
+          where = local[x] + (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                                                __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
+        local[x] += (int32_t)__popcll(mask);
+      }
+      if (cv[r] >= 0) stage[where] = cv[r];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const int32_t here = min(b - at, kFillPiece);
+    constexpr int UN = 4;  // entries per lane whose scales are requested together
+    for (int32_t j0 = lane; j0 < here; j0 += UN * kWave) {
+      int32_t c[UN], to[UN];
+#pragma unroll
+      for (int r = 0; r < UN; ++r) {
+        c[r] = stage[min(j0 + r * kWave, here - 1)];
+        to[r] = s_off[wave][column_class(c[r], g.sub_log2)] + j0 + r * kWave;
+      }
+      if (p > 0) {
+        float w[UN];
+#pragma unroll
+        for (int r = 0; r < UN; ++r) w[r] = g.dinv[(int64_t)(p - 1) * g.n + c[r]];
+#pragma unroll
+        for (int r = 0; r < UN; ++r)
+          if (j0 + r * kWave < here) {
+            g.scol_d[to[r]] = c[r];
+            g.swd[to[r]] = w[r];
+          }
+      } else {
+#pragma unroll
+        for (int r = 0; r < UN; ++r)
+          if (j0 + r * kWave < here) g.scol_c[to[r]] = c[r];
+        int32_t live[UN];
+#pragma unroll
+        for (int r = 0; r < UN; ++r) live[r] = j0 + r * kWave < here;
+        store_scales<UN>(g, c, to, live);
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   }
 }
 
 // ---- scatter ----------------------------------------------------------------------------------
-// Every selected entry is written to prefix[word] + (selected entries below it in its word), which
-// keeps the ascending column order of the input.  Besides the column index, the column scale
-// dinv_t[column] of the entry is stored: for a common entry once per snapshot, for an exclusive
-// entry for its own snapshot (dinv of one snapshot is 4 bytes per node: cache-resident).
-//
-// Common part: one lane per stored entry of snapshot 0 (most of them are selected); the entry's k
-// column scales come from the node-major copy of D^-1/2 (one line per node).
-// KV > 0: k == 4 * KV, a node's k scales are read as KV 16-byte pieces; KV == 0: any k, one by one.
-// The scales of a hub row's entries are never read from here (the aggregation takes them from the
-// class-grouped copy, k_split_scales): a wave whose 64 entries all lie in one hub row - most waves
-// of such a row - skips them.  wave_row / hubidx: as written by k_wave_rows and the scan of
-// k_classify's hub flags.
-template <int KV>
-__global__ __launch_bounds__(kBlock) void k_scatter_common(Snaps s, Parts p, const uint32_t *pre,
-                                                            const float *dinv_nk, int32_t k,
-                                                            const int32_t *wave_row,
-                                                            const uint32_t *hubidx, int32_t n) {
-  const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (e >= s.nnz[0]) return;
-  const uint32_t w = (uint32_t)(e >> 6), bit = (uint32_t)(e & 63);
-  const uint64_t sel = p.bits[0][w];
-  if (!((sel >> bit) & 1ull)) return;
-  const uint32_t dst = pre[w] - pre[0] + (uint32_t)__popcll(sel & ((1ull << bit) - 1ull));
-  const int32_t c = s.col[0][e];
-  p.col_out[0][dst] = c;
-  const int32_t r0 = wave_row[w], r1 = wave_row[w + 1];  // rows of this and of the next wave's first entry
-  if (r0 == r1) {
-    const int32_t r = min(max(r0, 0), n - 1);
-    if (hubidx[r + 1] != hubidx[r]) return;
-  }
-  if (KV > 0) {
-    const float4 *row = reinterpret_cast<const float4 *>(dinv_nk) + (int64_t)c * KV;
-    float4 v[KV > 0 ? KV : 1];
-#pragma unroll
-    for (int q = 0; q < KV; ++q) v[q] = row[q];
-#pragma unroll
-    for (int q = 0; q < KV; ++q) {
-      p.wc[4 * q + 0][dst] = v[q].x;
-      p.wc[4 * q + 1][dst] = v[q].y;
-      p.wc[4 * q + 2][dst] = v[q].z;
-      p.wc[4 * q + 3][dst] = v[q].w;
-    }
-  } else {
-    for (int u = 0; u < k; ++u) p.wc[u][dst] = dinv_nk[(int64_t)c * k + u];
-  }
-}
+// A wave per (run of TILES tiles, part); grid.y = part (0 = common, 1 + t = exclusive part of snapshot t).  The
+// selected entries keep the order of the input.  Besides the column index, the column scale
+// dinv_t[column] of the entry is stored: for a common entry once per snapshot (from the node-major
+// copy of D^-1/2: one line per node), for an exclusive entry for its own snapshot.  The scales of a
+// hub row's common entries are never read from here (the aggregation takes them from the
+// class-grouped copy), so they are skipped.
+struct OutParts {
+  int32_t *col[PIPAD_MAX_K + 1];
+  float *wc[PIPAD_MAX_K];
+  float *wd[PIPAD_MAX_K];
+};
 
-// Exclusive parts (grid.y = snapshot): usually few entries are selected.  A wave takes 64
-// consecutive 64-entry words; its selected entries are consecutive in the output, so lane l takes
-// the l-th, l + 64-th, ... of them: it finds the word (a search over the words' running counts)
-// and the bit (the r-th set bit of that word), and the wave's stores are contiguous.
-__device__ inline int nth_set_bit(uint64_t x, int r) {  // position of the r-th (0-based) set bit
-  int pos = 0;
-#pragma unroll
-  for (int width = 32; width >= 1; width >>= 1) {
-    const int c = __popcll(x & (((1ull << width) - 1ull) << pos));
-    if (r >= c) {
-      r -= c;
-      pos += width;
-    }
-  }
-  return pos;
-}
+constexpr int kScatterAhead = 4;  // words whose entries a wave has in flight
 
-__global__ __launch_bounds__(kBlock) void k_scatter_delta(Snaps s, Parts p, const uint32_t *pre,
-                                                           const float *dinv, int32_t n) {
-  const int t = blockIdx.y;
-  const int part = 1 + t;
-  const int lane = threadIdx.x % kWave;
-  const uint32_t nw = p.word_off[part + 1] - p.word_off[part];
-  const uint32_t w0 = (blockIdx.x * kWavesPerBlock + threadIdx.x / kWave) * kWave;  // first word of the wave
-  if (w0 >= nw) return;
-  const uint32_t w = w0 + lane;
-  const uint64_t sel = w < nw ? selected_word(p, s, part, w) : 0ull;
-  const uint32_t off = p.word_off[part];
-  const uint32_t dst0 = pre[off + w0] - pre[off];
-  int incl = __popcll(sel);  // running count of selected entries up to and including this word
+__device__ inline int running_count(uint64_t sel, int lane) {  // selected entries up to and including this word
+  int incl = __popcll(sel);
 #pragma unroll
   for (int d = 1; d < kWave; d <<= 1) {
     const int up = __shfl_up(incl, d, kWave);
     if (lane >= d) incl += up;
   }
-  const int total = __shfl(incl, kWave - 1, kWave);
-  const int excl = incl - __popcll(sel);
-  const uint32_t sel_lo = (uint32_t)sel, sel_hi = (uint32_t)(sel >> 32);
-  const int32_t *col = s.col[t] + (int64_t)w0 * 64;
-  const float *dinv_t = dinv + (int64_t)t * n;
-  for (int j0 = 0; j0 < total; j0 += kWave) {
-    const int j = min(j0 + lane, total - 1);
-    int wj = 0;  // the word that holds selected entry j: the first whose running count exceeds j
-#pragma unroll
-    for (int step = kWave >> 1; step >= 1; step >>= 1)
-      if (__shfl(incl, wj + step - 1, kWave) <= j) wj += step;
-    const int r = j - __shfl(excl, wj, kWave);
-    const uint64_t x = (uint64_t)(uint32_t)__shfl((int)sel_lo, wj, kWave) |
-                       ((uint64_t)(uint32_t)__shfl((int)sel_hi, wj, kWave) << 32);
-    const int32_t c = col[wj * 64 + nth_set_bit(x, r)];
-    const float d = dinv_t[c];
-    if (j0 + lane < total) {
-      p.col_out[part][dst0 + j] = c;
-      p.wd[t][dst0 + j] = d;
-    }
+  return incl;
+}
+
+__device__ inline uint64_t lane_word(uint64_t x, int l) {
+  return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, l) |
+         (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), l) << 32;
+}
+
+// KV > 0: k == 4 * KV, a node's k scales are read as KV 16-byte pieces; KV == 0: any k, one by one.
+template <int KV, int TILES>
+__global__ __launch_bounds__(kBlock) void k_scatter(Snaps s, Tiles g, OutParts o, const float *dinv,
+                                                     const float *dinv_nk) {
+  constexpr int WPT = kWave / TILES;  // words of a tile a wave takes at once
+  const int lane = threadIdx.x % kWave;
+  const int part = blockIdx.y;
+  const int64_t group = (int64_t)blockIdx.x * kWavesPerBlock + threadIdx.x / kWave;
+  const int64_t tile64 = group * TILES;
+  if (tile64 >= g.ntiles) return;
+  const int32_t tile0 = __builtin_amdgcn_readfirstlane((int32_t)tile64);
+  const int t = part == 0 ? g.base : part - 1;
+  const int32_t *bound = g.bound + t * ((int64_t)g.ntiles + 1);
+  const int32_t c0 = (int32_t)g.tile_pre[tile0].x;
+  const int32_t tile = tile0 + lane / WPT, j = lane % WPT;
+  int32_t e0 = 0, len = 0;
+  if (part == 0 && tile < g.ntiles) {
+    e0 = bound[tile];
+    len = bound[tile + 1] - e0;
   }
-}
-
-// Exclusive parts when most entries are selected (little overlap): one lane per stored entry.
-__global__ __launch_bounds__(kBlock) void k_scatter_delta_dense(Snaps s, Parts p,
-                                                                 const uint32_t *pre,
-                                                                 const float *dinv, int32_t n) {
-  const int t = blockIdx.y;
-  const int part = 1 + t;
-  const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (e >= s.nnz[t]) return;
-  const uint32_t w = (uint32_t)(e >> 6), bit = (uint32_t)(e & 63);
-  const uint64_t sel = selected_word(p, s, part, w);
-  if (!((sel >> bit) & 1ull)) return;
-  const uint32_t off = p.word_off[part];
-  const uint32_t dst = pre[off + w] - pre[off] + (uint32_t)__popcll(sel & ((1ull << bit) - 1ull));
-  const int32_t c = s.col[t][e];
-  p.col_out[part][dst] = c;
-  p.wd[t][dst] = dinv[(int64_t)t * n + c];
-}
-
-// Collects the data-dependent sizes into one small buffer for a single copy to the host:
-// out[0 .. k+1] = prefix at the start of every part (and the end of the last), then the numbers
-// of hub rows, hub units and short rows, then the k + 1 split totals.
-__global__ void k_totals(Parts p, const uint32_t *pre, int32_t k, int32_t n,
-                         const uint32_t *hubidx, const uint32_t *segoff,
-                         const uint32_t *shortidx, const uint32_t *split_total, uint32_t *out) {
-  const int q = threadIdx.x;
-  if (q <= k + 1) out[q] = pre[p.word_off[q]];
-  if (q <= k) out[k + 5 + q] = split_total[q];
-  if (q == 0) {
-    out[k + 2] = hubidx[n];
-    out[k + 3] = segoff[n];
-    out[k + 4] = shortidx[n];
+  const int32_t *col = s.col[t];
+  const int32_t nnz = s.nnz[t];
+  if (nnz == 0) return;
+  if (part == 0) {
+    uint64_t sel = 0, hub = 0;
+    if (j * 64 < len) {  // (a base tile has at most WPT words)
+      const int64_t at = ((int64_t)tile << (g.tile_log2 - 6)) + j;
+      sel = g.bits[at];
+      hub = g.hub_bits[at];
+    }
+    constexpr int UN = kScatterAhead;
+    const int32_t first = e0 + j * 64;
+    const int excl = running_count(sel, lane) - __popcll(sel);
+    int32_t *const out = o.col[0];
+#pragma unroll 1
+    for (int w0 = 0; w0 < kWave; w0 += UN) {
+      if (TILES == 1 && w0 * 64 >= __builtin_amdgcn_readfirstlane(len)) break;
+      uint64_t x[UN], need[UN], any = 0, scales = 0;
+#pragma unroll
+      for (int r = 0; r < UN; ++r) {
+        x[r] = lane_word(sel, w0 + r);
+        need[r] = x[r] & ~lane_word(hub, w0 + r);
+        any |= x[r];
+        scales |= need[r];
+      }
+      if (any == 0) continue;
+      int32_t c[UN], at[UN];
+#pragma unroll
+      for (int r = 0; r < UN; ++r) {
+        c[r] = col[min(__builtin_amdgcn_readlane(first, w0 + r) + lane, nnz - 1)];
+        at[r] = c0 + __builtin_amdgcn_readlane(excl, w0 + r) +
+                (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(x[r] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)x[r], 0));
+      }
+      if (scales == 0) {
+#pragma unroll
+        for (int r = 0; r < UN; ++r)
+          if (x[r] >> lane & 1ull) out[at[r]] = c[r];
+      } else if (KV > 0) {
+        float4 v[UN][KV > 0 ? KV : 1];
+#pragma unroll
+        for (int r = 0; r < UN; ++r) {
+          const int64_t node = need[r] >> lane & 1ull ? c[r] : 0;  // (one line for the lanes that need none)
+#pragma unroll
+          for (int q = 0; q < KV; ++q) v[r][q] = (reinterpret_cast<const float4 *>(dinv_nk) + node * KV)[q];
+        }
+#pragma unroll
+        for (int r = 0; r < UN; ++r) {
+          if (x[r] >> lane & 1ull) out[at[r]] = c[r];
+          if (need[r] >> lane & 1ull)
+#pragma unroll
+            for (int q = 0; q < KV; ++q) {
+              o.wc[4 * q + 0][at[r]] = v[r][q].x;
+              o.wc[4 * q + 1][at[r]] = v[r][q].y;
+              o.wc[4 * q + 2][at[r]] = v[r][q].z;
+              o.wc[4 * q + 3][at[r]] = v[r][q].w;
+            }
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < UN; ++r)
+          if (x[r] >> lane & 1ull) out[at[r]] = c[r];
+        for (int u = 0; u < g.k; ++u) {
+          float w[UN];
+#pragma unroll
+          for (int r = 0; r < UN; ++r) w[r] = dinv_nk[(int64_t)c[r] * g.k + u];
+#pragma unroll
+          for (int r = 0; r < UN; ++r)
+            if (need[r] >> lane & 1ull) o.wc[u][at[r]] = w[r];
+        }
+      }
+    }
+    return;
+  }
+  // exclusive part: the tiles' pieces of g.excl[t], one behind the other
+  int32_t from[TILES], upto[TILES];  // piece q: output places [upto[q - 1], upto[q])
+  int32_t total = 0;
+#pragma unroll
+  for (int q = 0; q < TILES; ++q) {
+    const int32_t x = min(tile0 + q, g.ntiles), y = min(x + 1, g.ntiles);
+    const int32_t start = bound[x];
+    from[q] = start - total;  // input place of an output place of this piece, minus the latter
+    total += (bound[y] - start) - (int32_t)(g.tile_pre[y].x - g.tile_pre[x].x);
+    upto[q] = total;
+  }
+  const int32_t *excl = g.excl[t];
+  int32_t *const out_col = o.col[part] + (bound[tile0] - c0);
+  float *const out_w = o.wd[t] + (bound[tile0] - c0);
+  const float *dinv_t = dinv + (int64_t)t * g.n;
+  constexpr int UN = kScatterAhead;
+  for (int32_t j0 = lane; j0 - lane < total; j0 += UN * kWave) {
+    int32_t c[UN];
+    float d[UN];
+#pragma unroll
+    for (int r = 0; r < UN; ++r) {
+      const int32_t j = min(j0 + r * kWave, total - 1);
+      int32_t at = from[0];
+#pragma unroll
+      for (int q = 1; q < TILES; ++q) at = j >= upto[q - 1] ? from[q] : at;
+      c[r] = excl[at + j];
+    }
+#pragma unroll
+    for (int r = 0; r < UN; ++r) d[r] = dinv_t[c[r]];
+#pragma unroll
+    for (int r = 0; r < UN; ++r)
+      if (j0 + r * kWave < total) {
+        out_col[j0 + r * kWave] = c[r];
+        out_w[j0 + r * kWave] = d[r];
+      }
   }
 }
 
@@ -854,20 +1364,54 @@ int scan_exclusive(uint32_t *const *data, int count, uint32_t m, uint32_t *bsum,
 
 size_t scan_block_words(uint32_t m) { return ((size_t)m + kScanTile - 1) / kScanTile; }
 
-// A few pinned host words per thread for the sizes a build reads back (allocated at the thread's
-// first build, kept until the process ends); null when pinned memory cannot be had.
-static uint32_t *pinned_words() {
-  thread_local uint32_t *buf = nullptr;
+// Pinned host memory per thread for the sizes a build reads back (allocated at the thread's first
+// build, kept until the process ends); null when pinned memory cannot be had.
+static FrameTotals *pinned_totals() {
+  thread_local FrameTotals *buf = nullptr;
   thread_local bool tried = false;
   if (!tried) {
     tried = true;
     void *ptr = nullptr;
-    if (hipHostMalloc(&ptr, sizeof(uint32_t) * (2 * PIPAD_MAX_K + 8), hipHostMallocPortable) == hipSuccess)
-      buf = static_cast<uint32_t *>(ptr);
-    else
+    if (hipHostMalloc(&ptr, sizeof(FrameTotals), hipHostMallocPortable) == hipSuccess) {
+      buf = static_cast<FrameTotals *>(ptr);
+      std::memset(buf, 0, sizeof(*buf));
+    } else {
       (void)hipGetLastError();
+    }
   }
   return buf;
+}
+
+TotalsTicket expect_totals(FrameTotals *device_totals) {
+  thread_local uint32_t seq = 0;
+  if (++seq == 0) ++seq;
+  FrameTotals *pinned = pinned_totals();
+  return pinned ? TotalsTicket{pinned, seq, true} : TotalsTicket{device_totals, seq, false};
+}
+
+int wait_totals(const TotalsTicket &ticket, hipStream_t st, FrameTotals *out) {
+  if (!ticket.on_host) {
+    PIPAD_HIP(hipMemcpyAsync(out, ticket.where, sizeof(*out), hipMemcpyDeviceToHost, st));
+    PIPAD_HIP(hipStreamSynchronize(st));
+    return PIPAD_OK;
+  }
+  // The kernel stored the sizes straight into the pinned words and the sequence number behind them;
+  // watching for it is several microseconds shorter than a copy and an event.  Every few thousand
+  // looks the stream is asked whether it is still running, so that a failed launch ends the wait.
+  for (uint32_t looks = 1;; ++looks) {
+    if (__atomic_load_n(&ticket.where->seq, __ATOMIC_ACQUIRE) == ticket.seq) break;
+    if (looks % 4096 == 0) {
+      const hipError_t e = hipStreamQuery(st);
+      if (e == hipSuccess) {
+        if (__atomic_load_n(&ticket.where->seq, __ATOMIC_ACQUIRE) == ticket.seq) break;
+        return hip_fail(hipErrorUnknown, "the scan of the sizes");
+      }
+      if (e != hipErrorNotReady) return hip_fail(e, "hipStreamQuery");
+      (void)hipGetLastError();  // "not ready" is no error of anyone's
+    }
+  }
+  *out = *ticket.where;
+  return PIPAD_OK;
 }
 
 void frame_take_options(pipad_frame *f) {
@@ -881,101 +1425,108 @@ void frame_take_options(pipad_frame *f) {
   f->nclass = kClasses << f->sub_log2;
 }
 
-int launch_classify(const pipad_frame *f, uint32_t *shortflag, uint32_t *hubflag, uint32_t *nseg,
-                    uint32_t *split_total, hipStream_t st) {
+void want_lists(Arena &a, pipad_frame *f, int64_t entries) {
+  // no more rows can be longer than a threshold than the entries of all snapshots together fill
+  const int64_t n = f->n;
+  const int64_t mids = std::min(n, entries / ((int64_t)f->short_max + 1));
+  const int64_t hubs = std::min(n, entries / ((int64_t)f->mid_max + 1));
+  const int64_t units = hubs ? hubs + entries / f->hub_segment : 0;
+  a.want(&f->rows_short, (size_t)n);
+  a.want(&f->rows_long, (size_t)mids);
+  a.want(&f->hub_rows, (size_t)hubs);
+  a.want(&f->hub_item_off, (size_t)hubs + 1);
+  a.want(&f->item_row, (size_t)units);
+  a.want(&f->item_v0, (size_t)units);
+  a.want(&f->item_v1, (size_t)units);
+  a.want(&f->item_c0, (size_t)units);
+  a.want(&f->item_d0, (size_t)units);
+}
+
+static RowClasses row_classes(const pipad_frame *f) {
+  return RowClasses{f->short_max, f->mid_max, f->hub_threshold, f->hub_segment};
+}
+
+static ListArgs list_args(const pipad_frame *f) {
+  ListArgs q;
+  q.rc = row_classes(f);
+  q.rows_short = f->rows_short;
+  q.rows_long = f->rows_long;
+  q.hub_rows = f->hub_rows;
+  q.hub_item_off = f->hub_item_off;
+  q.item_row = f->item_row;
+  q.item_v0 = f->item_v0;
+  q.item_v1 = f->item_v1;
+  q.item_c0 = f->item_c0;
+  q.item_d0 = f->item_d0;
+  return q;
+}
+
+size_t row_count_slots(int32_t n) { return ((size_t)n + kBlock - 1) / kBlock + 1; }
+
+int launch_list_rows(const pipad_frame *f, RowCounts *cnt, RowCounts *pre, const TotalsTicket &ticket, hipStream_t st) {
   PartRows p;
   std::memset(&p, 0, sizeof(p));
   p.rowptr[0] = f->rowptr_c;
   for (int t = 0; t < f->k; ++t) p.rowptr[1 + t] = f->rowptr_d[t];
-  PIPAD_HIP(hipMemsetAsync(split_total, 0, sizeof(uint32_t) * (size_t)(f->k + 1), st));
-  hipLaunchKernelGGL(k_classify, grid1((int64_t)f->n + 1, kBlock), dim3(kBlock), 0, st, p, f->n, f->k,
-                     shortflag, hubflag, nseg, split_total, f->short_max, f->mid_max,
-                     f->hub_threshold, f->hub_segment);
+  const dim3 blocks = grid1(f->n, kBlock);
+  hipLaunchKernelGGL(k_count_rows, blocks, dim3(kBlock), 0, st, p, f->n, f->k, row_classes(f), cnt);
+  hipLaunchKernelGGL(k_scan_row_counts, dim3(1), dim3(kTileScanBlock), 0, st, cnt, pre, (int64_t)blocks.x,
+                     ticket.where, ticket.seq);
+  hipLaunchKernelGGL(k_list_rows, grid1((int64_t)f->n + 1, kBlock), dim3(kBlock), 0, st, p, f->n, f->k, pre,
+                     list_args(f));
   PIPAD_HIP(hipGetLastError());
   return PIPAD_OK;
 }
 
-void launch_row_lists(int32_t n, const uint32_t *shortidx, const uint32_t *hubidx,
-                      const uint32_t *segoff, pipad_frame *f, hipStream_t st) {
-  hipLaunchKernelGGL(k_row_lists, grid1((int64_t)n + 1, kBlock), dim3(kBlock), 0, st, n, shortidx,
-                     hubidx, segoff, f->hub_segment, f->rows_short, f->rows_long, f->hub_rows,
-                     f->hub_item_off, f->item_row, f->item_v0, f->item_v1);
-}
-
-int set_list_sizes(pipad_frame *f, uint32_t n_hub, uint32_t n_items, uint32_t n_short,
-                   const uint32_t *split_total) {
-  f->n_hub = (int32_t)n_hub;
-  f->n_items = (int32_t)n_items;
-  f->n_short = (int32_t)n_short;
-  f->n_long = f->n - f->n_short - f->n_hub;
-  f->n_units = f->n_items;
-  f->split_all = 0;
-  for (int q = 0; q <= f->k; ++q) {
-    f->split_total[q] = split_total[q];
-    f->split_all += split_total[q];
-  }
-  if (f->split_all >= ((int64_t)1 << 31) ||
-      (int64_t)(f->k + 1) * f->n_units * f->nclass >= ((int64_t)1 << 31))
+int set_list_sizes(pipad_frame *f, const FrameTotals &v) {
+  f->n_hub = (int32_t)v.hub;
+  f->n_items = (int32_t)v.units;
+  f->n_long = (int32_t)v.mid;
+  f->n_short = f->n - f->n_long - f->n_hub;
+  f->split_c = (int64_t)v.split_c;
+  f->split_d = (int64_t)v.split_d;
+  if (f->split_c + f->split_d >= ((int64_t)1 << 31) ||
+      (int64_t)(f->k + 1) * f->n_items * (f->nclass + 1) >= ((int64_t)1 << 31))
     return PIPAD_ERR_TOO_LARGE;
   return PIPAD_OK;
 }
 
-void want_lists(Arena &a, pipad_frame *f, uint32_t **ulen, uint32_t **ubsum) {
-  a.want(&f->rows_short, (size_t)f->n_short);
-  a.want(&f->rows_long, (size_t)f->n_long);
-  a.want(&f->hub_rows, (size_t)f->n_hub);
-  a.want(&f->hub_item_off, (size_t)f->n_hub + 1);
-  a.want(&f->item_row, (size_t)f->n_items);
-  a.want(&f->item_v0, (size_t)f->n_items);
-  a.want(&f->item_v1, (size_t)f->n_items);
-  const size_t nu = (size_t)(f->k + 1) * f->n_units;
-  a.want(&f->sptr, nu * f->nclass + 1);
-  a.want(&f->scol, (size_t)f->split_all);
-  for (int t = 0; t < f->k; ++t) a.want(&f->swc[t], (size_t)f->split_total[0]);
-  a.want(&f->swd, (size_t)(f->split_all - f->split_total[0]));
-  a.want(ulen, nu + 1);
-  a.want(ubsum, scan_block_words((uint32_t)(nu + 1)) + 1);
+void want_split(Arena &a, pipad_frame *f) {
+  a.want(&f->sptr, (size_t)(f->k + 1) * (f->nclass + 1) * f->n_items);
+  a.want(&f->scol_c, (size_t)f->split_c);
+  a.want(&f->scol_d, (size_t)f->split_d);
+  for (int t = 0; t < f->k; ++t) a.want(&f->swc[t], (size_t)f->split_c);
+  a.want(&f->swd, (size_t)f->split_d);
 }
 
-int build_split_arrays(pipad_frame *f, uint32_t *ulen, uint32_t *bsum, hipStream_t st) {
-  if (f->n_units == 0) return PIPAD_OK;
+int build_split_arrays(pipad_frame *f, hipStream_t st) {
+  if (f->n_items == 0) return PIPAD_OK;
   SplitArgs g;
   std::memset(&g, 0, sizeof(g));
-  g.n = f->n;
-  g.n_units = f->n_units;
+  g.n_units = f->n_items;
   g.k = f->k;
   g.sub_log2 = f->sub_log2;
-  g.team_log2 = 6;
-  while (g.team_log2 > 0 && (kWave >> g.team_log2) < f->k) --g.team_log2;  // 64 / team lanes >= k
   g.item_row = f->item_row;
   g.item_v0 = f->item_v0;
   g.item_v1 = f->item_v1;
+  g.item_c0 = f->item_c0;
+  g.item_d0 = f->item_d0;
   g.rowptr[0] = f->rowptr_c;
   g.col[0] = f->col_c;
+  g.n = f->n;
+  g.dinv = f->dinv;
   g.dinv_nk = f->dinv_nk;
   for (int t = 0; t < f->k; ++t) {
     g.rowptr[1 + t] = f->rowptr_d[t];
     g.col[1 + t] = f->col_d[t];
-    g.wd[t] = f->wd[t];
     g.swc[t] = f->swc[t];
   }
-  g.ulen = ulen;
   g.sptr = f->sptr;
-  g.scol = f->scol;
+  g.scol_c = f->scol_c;
+  g.scol_d = f->scol_d;
   g.swd = f->swd;
-  g.total_c = (uint32_t)f->split_total[0];
-  const int64_t nu = (int64_t)(f->k + 1) * f->n_units;
-  hipLaunchKernelGGL(k_unit_len, grid1(nu + 1, kBlock), dim3(kBlock), 0, st, g);
-  PIPAD_HIP(hipGetLastError());
-  {
-    uint32_t *one = ulen;
-    const int rc = exclusive_scan(&one, 1, (uint32_t)(nu + 1), bsum, st);
-    if (rc != PIPAD_OK) return rc;
-  }
   auto fill = f->sub_log2 == 0 ? k_split_fill<8> : f->sub_log2 == 1 ? k_split_fill<16> : k_split_fill<32>;
-  hipLaunchKernelGGL(fill, grid1(f->n_units, kWavesPerBlock), dim3(kBlock), 0, st, g);
-  if (g.total_c > 0)
-    hipLaunchKernelGGL(k_split_scales, grid1(g.total_c, kBlock), dim3(kBlock), 0, st, g);
+  hipLaunchKernelGGL(fill, grid1(f->n_items, kFillWaves, f->k + 1), dim3(kFillWaves * kWave), 0, st, g);
   PIPAD_HIP(hipGetLastError());
   return PIPAD_OK;
 }
@@ -984,10 +1535,14 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
                   pipad_alloc_fn alloc, void *alloc_ctx, hipStream_t st, pipad_frame **out) {
   Snaps s;
   std::memset(&s, 0, sizeof(s));
+  int64_t entries = 0;
+  int32_t base = 0;
   for (int t = 0; t < k; ++t) {
     s.rowptr[t] = snaps[t].rowptr;
     s.col[t] = snaps[t].colidx;
     s.nnz[t] = snaps[t].nnz;
+    entries += s.nnz[t];
+    if (s.nnz[t] > s.nnz[base]) base = t;
   }
 
   pipad_frame *f = new (std::nothrow) pipad_frame;
@@ -1015,58 +1570,45 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
     (void)static_scratch(&unused_ptr, &unused_floats);
   }
 
-  // ---- sizes known up front: row pointers and D^-1/2 (persistent), all temporaries
-  Parts p;
-  std::memset(&p, 0, sizeof(p));
-  uint32_t nw[PIPAD_MAX_K];
-  for (int t = 0; t < k; ++t) {
-    nw[t] = (uint32_t)(((int64_t)s.nnz[t] + 63) / 64);
-
-  }
-  // parts: common uses snapshot 0's words, delta_t uses snapshot t's words
-  int64_t m64 = nw[0];
-  for (int t = 0; t < k; ++t) m64 += nw[t];
-  m64 += 1;  // trailing word so that prefix[end of last part] exists
-  if (m64 >= ((int64_t)1 << 31)) return fail(PIPAD_ERR_TOO_LARGE);
-  const uint32_t m = (uint32_t)m64;
-  p.word_off[0] = 0;
-  p.word_off[1] = nw[0];
-  for (int t = 0; t < k; ++t) p.word_off[2 + t] = p.word_off[1 + t] + nw[t];
-  const uint32_t scan_len_rows = (uint32_t)n + 1;
+  // ---- sizes known up front: row pointers, D^-1/2 and row lists (persistent), all temporaries
+  Tiles g;
+  std::memset(&g, 0, sizeof(g));
+  g.n = n;
+  g.k = k;
+  g.base = base;
+  // the stretches of all snapshots but the base are in LDS at once: 18 KB for k = 8, 38 KB for
+  // k = 16 with tiles of 512 entries; more snapshots get smaller tiles
+  g.tile_log2 = k <= 16 ? 9 : 8;
+  g.ntiles = (int32_t)(((int64_t)s.nnz[base] + (1 << g.tile_log2) - 1) >> g.tile_log2);
 
   Arena keep1;
   keep1.want(&f->rowptr_c, (size_t)n + 1);
   for (int t = 0; t < k; ++t) keep1.want(&f->rowptr_d[t], (size_t)n + 1);
   keep1.want(&f->dinv, (size_t)k * n);
   keep1.want(&f->dinv_nk, (size_t)k * n);
+  want_lists(keep1, f, entries);
   {
-    void *base = A.get(keep1.total);
-    if (!base) return fail(PIPAD_ERR_ALLOC);
-    keep1.assign(base);
+    void *base_ptr = A.get(keep1.total);
+    if (!base_ptr) return fail(PIPAD_ERR_ALLOC);
+    keep1.assign(base_ptr);
   }
-  p.rowptr_out[0] = f->rowptr_c;
-  for (int t = 0; t < k; ++t) p.rowptr_out[1 + t] = f->rowptr_d[t];
 
   Arena tmp;
-  size_t flag_bytes = 0;  // byte flags of snapshots 1 .. k-1 come first and are cleared together
-  for (int t = 1; t < k; ++t) {
-    tmp.want(&p.flag8[t], (size_t)s.nnz[t]);
-    flag_bytes = tmp.total;
-  }
-  for (int t = 0; t < k; ++t) tmp.want(&p.bits[t], (size_t)nw[t]);
-  uint32_t *pre = nullptr, *bsum = nullptr, *shortidx = nullptr, *hubidx = nullptr,
-           *segoff = nullptr, *totals = nullptr, *split_total = nullptr;
+  FrameTotals *totals = nullptr;
   int *dflags = nullptr;
-  tmp.want(&pre, (size_t)m);
-  tmp.want(&bsum, std::max(((size_t)m + kScanTile - 1) / kScanTile,
-                           3 * (((size_t)scan_len_rows + kScanTile - 1) / kScanTile)) + 1);
-  tmp.want(&shortidx, (size_t)scan_len_rows);
-  tmp.want(&hubidx, (size_t)scan_len_rows);
-  tmp.want(&segoff, (size_t)scan_len_rows);
-  int32_t *wave_row = nullptr;
-  tmp.want(&wave_row, (size_t)nw[0] + 2);
-  tmp.want(&totals, (size_t)2 * PIPAD_MAX_K + 8);
-  tmp.want(&split_total, (size_t)PIPAD_MAX_K + 1);
+  for (int t = 0; t < k; ++t) tmp.want(&g.excl[t], (size_t)s.nnz[t]);
+  const size_t base_words = ((size_t)s.nnz[base] + 63) / 64;
+  tmp.want(&g.bits, base_words);
+  tmp.want(&g.hub_bits, base_words);
+  tmp.want(&g.wpre, base_words);
+  tmp.want(&g.brow, (size_t)g.ntiles + 1);
+  tmp.want(&g.bound, ((size_t)g.ntiles + 1) * k);
+  tmp.want(&g.tile_cnt, (size_t)g.ntiles + 1);  // (read two at a time)
+  tmp.want(&g.tile_pre, (size_t)g.ntiles + 1);
+  tmp.want(&g.row_cnt, row_count_slots(n));
+  tmp.want(&g.row_pre, row_count_slots(n));
+  tmp.want(&g.bad, 1);
+  tmp.want(&totals, 1);
   tmp.want(&dflags, (size_t)64);
   if (alloc) {
     temp = alloc(tmp.total, alloc_ctx);
@@ -1086,8 +1628,6 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
     if (rc__ != 0) return fail(rc__);                     \
   } while (0)
 
-  if (flag_bytes) PIPAD_TRY(hipMemsetAsync(temp, 0, flag_bytes, st));
-
   if ((flags & PIPAD_VALIDATE) && n > 0) {
     PIPAD_TRY(hipMemsetAsync(dflags, 0, 256, st));
     hipLaunchKernelGGL(k_validate, grid1((int64_t)k * n, kWavesPerBlock), dim3(kBlock), 0, st, s, n,
@@ -1099,84 +1639,55 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
     if (bad) return fail(PIPAD_ERR_BAD_CSR);
   }
 
-  if (s.nnz[0] > 0) {
-    hipLaunchKernelGGL(k_wave_rows, grid1(n, kBlock), dim3(kBlock), 0, st, s.rowptr[0], n, s.nnz[0],
-                       wave_row);
-    // instances by the largest k they handle: fewer snapshots, fewer registers, more waves per CU
-    auto mark = k <= 8 ? k_mark<8> : k <= 16 ? k_mark<16> : k_mark<PIPAD_MAX_K>;
-    hipLaunchKernelGGL(mark, grid1(s.nnz[0], kBlock), dim3(kBlock), 0, st, s, p, n, k, wave_row);
+  const int32_t bound_blocks = (int32_t)(((int64_t)g.ntiles + 1 + kWavesPerBlock * 8 - 1) / (kWavesPerBlock * 8));
+  const int64_t row_blocks = ((int64_t)n + kBlock - 1) / kBlock;
+  hipLaunchKernelGGL(k_prepare, dim3((unsigned)(bound_blocks + row_blocks)), dim3(kBlock), 0, st, s, g, row_classes(f),
+                     bound_blocks, f->dinv, f->dinv_nk);
+  if (g.ntiles > 0) {
+    const int tile = 1 << g.tile_log2;
+    const size_t lds = ((size_t)(k - 1) * (tile + tile / 4) + 32) * sizeof(int32_t);
+    // instances by the most snapshots they handle: fewer snapshots, fewer registers, more waves per CU
+    auto mark = k <= 4 ? k_mark<4, 512> : k <= 8 ? k_mark<8, 512> : k <= 16 ? k_mark<16, 512> : k_mark<32, 256>;
+    hipLaunchKernelGGL(mark, dim3((unsigned)g.ntiles), dim3(kBlock), lds, st, s, g, f->mid_max);
+  }
+  const TotalsTicket ticket = expect_totals(totals);
+  {
+    ScanArgs a;
+    a.tile_cnt = g.tile_cnt;
+    a.tile_pre = g.tile_pre;
+    a.row_cnt = g.row_cnt;
+    a.row_pre = g.row_pre;
+    a.bad = g.bad;
+    a.ntiles = g.ntiles;
+    a.k = k;
+    a.row_blocks = row_blocks;
+    const int64_t runs = ((int64_t)g.ntiles + kTileScanRun - 1) / kTileScanRun;
+    const int64_t row_runs = (row_blocks + kTileScanBlock - 1) / kTileScanBlock;
+    const int64_t blocks = std::clamp<int64_t>(std::max(runs, row_runs), 1, kTileScanMost);
+    a.tiles_per_block = (int32_t)std::min<int64_t>((runs + blocks - 1) / blocks * kTileScanRun, 1 << 30);
+    a.rows_per_block = (row_runs + blocks - 1) / blocks * kTileScanBlock;
+    hipLaunchKernelGGL(k_scan_counts, dim3((unsigned)blocks), dim3(kTileScanBlock), 0, st, a, ticket.where, ticket.seq);
   }
   {
-    int32_t max_later = 0;
-    for (int t = 1; t < k; ++t) max_later = std::max(max_later, s.nnz[t]);
-    if (max_later > 0)
-      hipLaunchKernelGGL(k_pack, grid1(max_later, kPackPerWave * kWavesPerBlock, k - 1), dim3(kBlock), 0,
-                         st, s, p);
+    RowArgs o;
+    std::memset(&o, 0, sizeof(o));
+    o.rowptr_c = f->rowptr_c;
+    for (int t = 0; t < k; ++t) o.rowptr_d[t] = f->rowptr_d[t];
+    hipLaunchKernelGGL(k_rows, grid1((int64_t)n + 1, kBlock), dim3(kBlock), 0, st, s, g, o, list_args(f));
   }
-  uint32_t max_nw = 0;
-  for (int t = 0; t < k; ++t) max_nw = std::max(max_nw, nw[t]);
-  if (max_nw > 0)
-    hipLaunchKernelGGL(k_popcount, grid1(max_nw, kBlock, k + 1), dim3(kBlock), 0, st, s, p, pre, m);
-  else
-    PIPAD_TRY(hipMemsetAsync(pre, 0, sizeof(uint32_t) * (size_t)m, st));  // no entries at all
   PIPAD_TRY(hipGetLastError());
-  {
-    int rc = exclusive_scan(pre, m, bsum, st);
-    if (rc != 0) return fail(rc);
-  }
-  hipLaunchKernelGGL(k_rowptr, grid1((int64_t)n + 1, kBlock, k + 1), dim3(kBlock), 0, st, s, p,
-                     pre, n);
-  PIPAD_TRY(hipGetLastError());
-  {
-    const int rc = launch_classify(f, shortidx, hubidx, segoff, split_total, st);
-    if (rc != 0) return fail(rc);
-  }
-  {
-    uint32_t *three[3] = {shortidx, hubidx, segoff};
-    const int rc = exclusive_scan(three, 3, scan_len_rows, bsum, st);
-    if (rc != 0) return fail(rc);
-  }
 
-  // ---- the one host synchronisation: sizes of the data-dependent outputs.  The host waits for
-  // an event behind the copy, and D^-1/2 - which nothing before this point needs - is computed
-  // behind that event, while the host sizes and requests the output buffers.
-  uint32_t stack_totals[2 * PIPAD_MAX_K + 8];
-  uint32_t *host_totals = pinned_words();
-  hipLaunchKernelGGL(k_totals, dim3(1), dim3(kWave), 0, st, p, pre, k, n, hubidx, segoff, shortidx,
-                     split_total, totals);
-  PIPAD_TRY(hipGetLastError());
-  hipEvent_t copied = nullptr;
-  if (host_totals && hipEventCreateWithFlags(&copied, hipEventDisableTiming) != hipSuccess) {
-    (void)hipGetLastError();
-    copied = nullptr;
-  }
-  if (!copied) host_totals = stack_totals;
+  // ---- the one host synchronisation: sizes of the data-dependent outputs (k_rows runs meanwhile)
+  FrameTotals v;
   {
-    const hipError_t ce = hipMemcpyAsync(host_totals, totals, sizeof(uint32_t) * (size_t)(2 * k + 6),
-                                         hipMemcpyDeviceToHost, st);
-    if (ce != hipSuccess && copied) (void)hipEventDestroy(copied);
-    PIPAD_TRY(ce);
+    const int rc = wait_totals(ticket, st, &v);
+    if (rc != PIPAD_OK) return fail(rc);
   }
-  if (copied) {
-    hipError_t e = hipEventRecord(copied, st);
-    if (e == hipSuccess && n > 0)
-      hipLaunchKernelGGL(k_dinv, grid1(n, kBlock), dim3(kBlock), 0, st, s, n, k, f->dinv, f->dinv_nk);
-    if (e == hipSuccess) e = hipEventSynchronize(copied);
-    (void)hipEventDestroy(copied);
-    PIPAD_TRY(e);
-    PIPAD_TRY(hipGetLastError());
-  } else {
-    PIPAD_TRY(hipStreamSynchronize(st));
-    if (n > 0)
-      hipLaunchKernelGGL(k_dinv, grid1(n, kBlock), dim3(kBlock), 0, st, s, n, k, f->dinv, f->dinv_nk);
-    PIPAD_TRY(hipGetLastError());
-  }
-
-  f->nnz_c = (int32_t)(host_totals[1] - host_totals[0]);
-  for (int t = 0; t < k; ++t) f->nnz_d[t] = (int32_t)(host_totals[2 + t] - host_totals[1 + t]);
+  if (v.bad) return fail(PIPAD_ERR_BAD_CSR);
+  f->nnz_c = (int32_t)v.nnz_c;
+  for (int t = 0; t < k; ++t) f->nnz_d[t] = s.nnz[t] - f->nnz_c;
   {
-    const int rc = set_list_sizes(f, host_totals[k + 2], host_totals[k + 3], host_totals[k + 4],
-                                  host_totals + k + 5);
+    const int rc = set_list_sizes(f, v);
     if (rc != 0) return fail(rc);
   }
 
@@ -1187,46 +1698,35 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
     keep2.want(&f->wc[t], (size_t)f->nnz_c);
     keep2.want(&f->wd[t], (size_t)f->nnz_d[t]);
   }
-  uint32_t *ulen = nullptr, *ubsum = nullptr;
-  want_lists(keep2, f, &ulen, &ubsum);
+  want_split(keep2, f);
   {
-    void *base = A.get(keep2.total);
-    if (!base) return fail(PIPAD_ERR_ALLOC);
-    keep2.assign(base);
+    void *base_ptr = A.get(keep2.total);
+    if (!base_ptr) return fail(PIPAD_ERR_ALLOC);
+    keep2.assign(base_ptr);
   }
-  p.col_out[0] = f->col_c;
-  for (int t = 0; t < k; ++t) {
-    p.col_out[1 + t] = f->col_d[t];
-    p.wc[t] = f->wc[t];
-    p.wd[t] = f->wd[t];
-  }
-
-  if (s.nnz[0] > 0) {
-    auto scatter = k == 4 ? k_scatter_common<1> : k == 8 ? k_scatter_common<2>
-                 : k == 16 ? k_scatter_common<4> : k_scatter_common<0>;
-    hipLaunchKernelGGL(scatter, grid1(s.nnz[0], kBlock), dim3(kBlock), 0, st, s, p, pre, f->dinv_nk, k,
-                       wave_row, hubidx, n);
-  }
-  {
-    int64_t all = 0, excl = 0;
-    int32_t max_nnz = 0;
+  if (g.ntiles > 0) {
+    OutParts o;
+    std::memset(&o, 0, sizeof(o));
+    o.col[0] = f->col_c;
     for (int t = 0; t < k; ++t) {
-      all += s.nnz[t];
-      excl += f->nnz_d[t];
-      max_nnz = std::max(max_nnz, s.nnz[t]);
+      o.col[1 + t] = f->col_d[t];
+      o.wc[t] = f->wc[t];
+      o.wd[t] = f->wd[t];
     }
-    if (excl * PIPAD_DENSE_FACTOR > all) {  // mostly selected: a lane per entry
-      hipLaunchKernelGGL(k_scatter_delta_dense, grid1(max_nnz, kBlock, k), dim3(kBlock), 0, st, s, p,
-                         pre, f->dinv, n);
-    } else if (max_nw > 0) {
-      hipLaunchKernelGGL(k_scatter_delta, grid1(max_nw, kBlock, k), dim3(kBlock), 0, st, s, p, pre,
-                         f->dinv, n);
-    }
+    // A wave per tile has the shortest chain of dependent loads (20k-node frame: 9 us against 19 with
+    // four tiles per wave, 0.2M nodes: 65 against 74); with 8M entries and more per snapshot there
+    // are waves enough and fewer of them do better (1M nodes, 20M entries: 313 us against 339).
+    const int per_wave = g.ntiles < 16384 ? 1 : 4;
+    auto scatter = per_wave == 1 ? (k == 4 ? k_scatter<1, 1> : k == 8 ? k_scatter<2, 1>
+                                  : k == 16 ? k_scatter<4, 1> : k_scatter<0, 1>)
+                                 : (k == 4 ? k_scatter<1, 4> : k == 8 ? k_scatter<2, 4>
+                                  : k == 16 ? k_scatter<4, 4> : k_scatter<0, 4>);
+    hipLaunchKernelGGL(scatter, grid1(g.ntiles, kWavesPerBlock * per_wave, k + 1), dim3(kBlock), 0, st, s, g, o, f->dinv,
+                       f->dinv_nk);
+    PIPAD_TRY(hipGetLastError());
   }
-  launch_row_lists(n, shortidx, hubidx, segoff, f, st);
-  PIPAD_TRY(hipGetLastError());
   {
-    const int rc = build_split_arrays(f, ulen, ubsum, st);
+    const int rc = build_split_arrays(f, st);
     if (rc != 0) return fail(rc);
   }
   if (!alloc) {

@@ -78,15 +78,18 @@ struct pipad_frame {
   pipad::Options opt;                // the options as they stood when the frame was built
   int32_t short_max = 0, mid_max = 0, hub_threshold = 0, hub_segment = 0;
   int32_t n_short = 0, n_long = 0;
-  int32_t *rows_short = nullptr;     // [n_short] ascending row ids
+  int32_t *rows_short = nullptr;     // [n_short] ascending
   int32_t *rows_long = nullptr;      // [n_long] the mid rows
   int32_t n_hub = 0;
-  int32_t *hub_rows = nullptr;       // [n_hub] ascending row ids
+  int32_t *hub_rows = nullptr;       // [n_hub] ascending
   int32_t *hub_item_off = nullptr;   // [n_hub+1] first unit of each hub row
   int32_t n_items = 0;               // hub units
   int32_t *item_row = nullptr;       // [n_items]
   int32_t *item_v0 = nullptr;        // [n_items] the unit's range [v0, v1) of the row's virtual
   int32_t *item_v1 = nullptr;        //           entry list "common entries, then exclusive entries"
+
+  int32_t *item_c0 = nullptr;        // [n_items] where the unit's common entries start in scol_c
+  int32_t *item_d0 = nullptr;        // [n_items] where the row's exclusive entries start in scol_d
 
   // Column classes.  Every column belongs to one of nclass = 8 * sub classes (a hash of its
   // index); classes x * sub .. x * sub + sub - 1 are gathered by the workgroups that run on XCD x
@@ -94,20 +97,18 @@ struct pipad_frame {
   // classes of an XCD are taken one after the other in time, which divides the set of rows an L2
   // has to hold at any moment once more.  For every unit the entries of each part (0 = common,
   // 1 + t = exclusive part of snapshot t) are stored again, grouped by class (ascending column
-  // within a class):
-  //   scol[sptr[(p * n_units + u) * nclass + c] .. sptr[same + 1])   entries of class c
-  // with the common entries of all units first (split_total[0] of them), then part 1, and so on.
-  // swc[t] holds the column scales of the common region for snapshot t, swd those of all the
-  // exclusive regions (swd[e - split_total[0]] belongs to scol[e]).
+  // within a class), the common ones in scol_c, the exclusive ones in scol_d:
+  //   [sptr[(p * (nclass + 1) + c) * n_items + u], sptr[(p * (nclass + 1) + c + 1) * n_items + u])
+  // are the entries of class c of unit u in part p.  swc[t] holds the column scales of scol_c for
+  // snapshot t, swd those of scol_d.
   int32_t sub_log2 = 0;              // log2 of the sub classes per XCD
   int32_t nclass = 8;                // 8 << sub_log2
-  int32_t n_units = 0;               // == n_items
-  int64_t split_total[PIPAD_MAX_K + 1] = {};  // entries of split rows per part
-  int64_t split_all = 0;             // their sum
-  uint32_t *sptr = nullptr;          // [(k + 1) * n_units * nclass + 1]
-  int32_t *scol = nullptr;           // [split_all]
-  float *swc[PIPAD_MAX_K] = {};      // each [split_total[0]]
-  float *swd = nullptr;              // [split_all - split_total[0]]
+  int64_t split_c = 0, split_d = 0;  // common entries of the hub rows, exclusive ones of all parts
+  int32_t *sptr = nullptr;           // [(k + 1) * (nclass + 1) * n_items]
+  int32_t *scol_c = nullptr;         // [split_c]
+  int32_t *scol_d = nullptr;         // [split_d]
+  float *swc[PIPAD_MAX_K] = {};      // each [split_c]
+  float *swd = nullptr;              // [split_d]
 
   // Scratch for the partial sums of the class parts: nclass per hub unit * k * F floats, grown on
   // demand.
@@ -171,18 +172,39 @@ inline dim3 grid1(int64_t items, int per_block, int y = 1) {
 // In-place exclusive scans of `count` (<= 3) arrays of m words; bsum: count * scan_block_words(m).
 int scan_exclusive(uint32_t *const *data, int count, uint32_t m, uint32_t *bsum, hipStream_t st);
 size_t scan_block_words(uint32_t m);
-// Fills the frame's row lists from the scanned class flags (n + 1 words each).
-void launch_row_lists(int32_t n, const uint32_t *shortidx, const uint32_t *hubidx,
-                      const uint32_t *segoff, pipad_frame *f, hipStream_t st);
-// Row classes from the lengths of the frame's parts (row pointers in place): the three flag
-// arrays (n + 1 words each, to be scanned) and the k + 1 split totals.
-int launch_classify(const pipad_frame *f, uint32_t *shortflag, uint32_t *hubflag, uint32_t *nseg,
-                    uint32_t *split_total, hipStream_t st);
-// Takes the list sizes read back from the device; PIPAD_ERR_TOO_LARGE when an index space overflows.
-int set_list_sizes(pipad_frame *f, uint32_t n_hub, uint32_t n_items, uint32_t n_short,
-                   const uint32_t *split_total);
-// Registers the row lists, the class-grouped arrays and the scratch of build_split_arrays.
-void want_lists(Arena &a, pipad_frame *f, uint32_t **ulen, uint32_t **ubsum);
+// Counts of a run of rows: mid rows, hub rows and hub units, and what the hub rows hold: entries (of
+// all snapshots; of the exclusive parts where the parts are known) and, where known, common entries.
+struct RowCounts {
+  uint64_t entries;
+  uint32_t common, mid, hub, units;
+};
+// The data-dependent sizes as the host reads them.
+struct FrameTotals {
+  uint64_t split_c, split_d;  // common / exclusive entries of the hub rows
+  uint32_t nnz_c, mid, hub, units;
+  uint32_t bad;               // the snapshots are not canonical
+  uint32_t seq;               // which build these sizes belong to
+};
+// Where a kernel puts the sizes: pinned host memory of this thread, or device memory when there is
+// none.
+struct TotalsTicket {
+  FrameTotals *where;
+  uint32_t seq;
+  bool on_host;
+};
+TotalsTicket expect_totals(FrameTotals *device_totals);
+// Waits for the sizes (the one host synchronisation of a build).
+int wait_totals(const TotalsTicket &ticket, hipStream_t st, FrameTotals *out);
+// Registers the row lists of a frame whose snapshots hold `entries` entries together (upper bounds:
+// the lists are written before their sizes are known).
+void want_lists(Arena &a, pipad_frame *f, int64_t entries);
+// Lists the rows of a frame whose row pointers are in place; cnt, pre: row_count_slots(n) counts each.
+int launch_list_rows(const pipad_frame *f, RowCounts *cnt, RowCounts *pre, const TotalsTicket &ticket, hipStream_t st);
+size_t row_count_slots(int32_t n);
+// Takes the sizes; PIPAD_ERR_TOO_LARGE when an index space overflows.
+int set_list_sizes(pipad_frame *f, const FrameTotals &v);
+// Registers the class-grouped arrays.
+void want_split(Arena &a, pipad_frame *f);
 // Row classes and unit counts are the same for a frame and its transpose: one definition.
 __host__ __device__ inline int row_class(int64_t total, int32_t short_max, int32_t mid_max) {
   return total <= short_max ? 0 : total <= mid_max ? 1 : 2;  // short, mid, hub
@@ -192,10 +214,9 @@ __host__ __device__ inline uint32_t hub_units(int64_t total, int32_t threshold, 
 }
 // Copies the thresholds from the options into a new frame (clamped to what int32 sizes allow).
 void frame_take_options(pipad_frame *f);
-// The class-grouped copies of the split rows' entries (sptr, scol, swc, swd), once the frame's
-// parts, scales and row lists are in place.  `ulen` is scratch of (k + 1) * n_units + 1 words,
-// `bsum` of scan_block_words(that) words.
-int build_split_arrays(pipad_frame *f, uint32_t *ulen, uint32_t *bsum, hipStream_t st);
+// The class-grouped copies of the hub rows' entries (sptr, scol_c, scol_d, swc, swd), once the
+// frame's parts, D^-1/2 and row lists are in place.
+int build_split_arrays(pipad_frame *f, hipStream_t st);
 // Column class of a column index: the top 3 + sub_log2 bits of a multiplicative hash, so that the
 // class's XCD is class >> sub_log2.
 __host__ __device__ inline uint32_t column_class(int32_t j, int sub_log2) {

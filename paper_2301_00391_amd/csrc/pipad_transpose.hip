@@ -314,18 +314,6 @@ __global__ __launch_bounds__(kBlock) void k_part_scales(ScaleArgs g) {
   }
 }
 
-__global__ void k_class_totals(int32_t n, int32_t k, const uint32_t *hubidx, const uint32_t *segoff,
-                               const uint32_t *shortidx, const uint32_t *split_total,
-                               uint32_t *out) {
-  const int q = threadIdx.x;
-  if (q == 0) {
-    out[0] = hubidx[n];
-    out[1] = segoff[n];
-    out[2] = shortidx[n];
-  }
-  if (q <= k) out[3 + q] = split_total[q];
-}
-
 }  // namespace
 
 // The frame of the transposed patterns with the SAME D^-1/2: aggregating with it multiplies by
@@ -376,6 +364,11 @@ int transpose_frame(const pipad_frame *f, pipad_alloc_fn alloc, void *alloc_ctx,
     keep.want(&g->wd[t], (size_t)g->nnz_d[t]);
   }
   {
+    int64_t entries = g->nnz_c;  // a row's length counts its longest exclusive row only
+    for (int t = 0; t < k; ++t) entries += g->nnz_d[t];
+    want_lists(keep, g, entries);
+  }
+  {
     void *base = A.get(keep.total);
     if (!base) return fail(PIPAD_ERR_ALLOC);
     keep.assign(base);
@@ -411,10 +404,10 @@ int transpose_frame(const pipad_frame *f, pipad_alloc_fn alloc, void *alloc_ctx,
   const int64_t hist_len = std::max<int64_t>(tiles * kDigits, 1);
   if (total >= ((int64_t)1 << 31) || hist_len >= ((int64_t)1 << 31)) return fail(PIPAD_ERR_TOO_LARGE);
 
-  const uint32_t scan_len = (uint32_t)n + 1;
   Arena tmp;
-  uint32_t *key_a = nullptr, *key_b = nullptr, *hist = nullptr, *cnt = nullptr, *bsum = nullptr, *shortidx = nullptr,
-           *hubidx = nullptr, *segoff = nullptr, *totals = nullptr, *split_total = nullptr;
+  uint32_t *key_a = nullptr, *key_b = nullptr, *hist = nullptr, *cnt = nullptr, *bsum = nullptr;
+  RowCounts *row_cnt = nullptr, *row_pre = nullptr;
+  FrameTotals *totals = nullptr;
   int32_t *val_a = nullptr, *val_b = nullptr, *anchor = nullptr;
   tmp.want(&anchor, (size_t)anchors);
   tmp.want(&key_a, (size_t)total);
@@ -423,12 +416,10 @@ int transpose_frame(const pipad_frame *f, pipad_alloc_fn alloc, void *alloc_ctx,
   tmp.want(&val_b, (size_t)total);
   tmp.want(&hist, (size_t)hist_len);
   tmp.want(&cnt, (size_t)hist_len);
-  tmp.want(&bsum, std::max(scan_block_words((uint32_t)hist_len), 3 * scan_block_words(scan_len)) + 1);
-  tmp.want(&shortidx, (size_t)scan_len);
-  tmp.want(&hubidx, (size_t)scan_len);
-  tmp.want(&segoff, (size_t)scan_len);
-  tmp.want(&totals, (size_t)PIPAD_MAX_K + 8);
-  tmp.want(&split_total, (size_t)PIPAD_MAX_K + 1);
+  tmp.want(&bsum, scan_block_words((uint32_t)hist_len) + 1);
+  tmp.want(&row_cnt, row_count_slots(n));
+  tmp.want(&row_pre, row_count_slots(n));
+  tmp.want(&totals, 1);
   if (alloc) {
     temp = alloc(tmp.total, alloc_ctx);
     g->temp_ptr = temp;
@@ -499,39 +490,30 @@ int transpose_frame(const pipad_frame *f, pipad_alloc_fn alloc, void *alloc_ctx,
   PIPAD_TRY_T(hipGetLastError());
 
   // ---- row classes, work lists and the class-grouped copies, as in the build
+  const TotalsTicket ticket = expect_totals(totals);
   {
-    const int rc = launch_classify(g, shortidx, hubidx, segoff, split_total, st);
+    const int rc = launch_list_rows(g, row_cnt, row_pre, ticket, st);
+    if (rc != 0) return fail(rc);
+  }
+  FrameTotals v;
+  {
+    const int rc = wait_totals(ticket, st, &v);
     if (rc != 0) return fail(rc);
   }
   {
-    uint32_t *three[3] = {shortidx, hubidx, segoff};
-    const int rc = scan_exclusive(three, 3, scan_len, bsum, st);
-    if (rc != 0) return fail(rc);
-  }
-  uint32_t host_totals[PIPAD_MAX_K + 8] = {};
-  hipLaunchKernelGGL(k_class_totals, dim3(1), dim3(kWave), 0, st, n, k, hubidx, segoff, shortidx,
-                     split_total, totals);
-  PIPAD_TRY_T(hipGetLastError());
-  PIPAD_TRY_T(hipMemcpyAsync(host_totals, totals, sizeof(uint32_t) * (size_t)(k + 4),
-                             hipMemcpyDeviceToHost, st));
-  PIPAD_TRY_T(hipStreamSynchronize(st));
-  {
-    const int rc = set_list_sizes(g, host_totals[0], host_totals[1], host_totals[2], host_totals + 3);
+    const int rc = set_list_sizes(g, v);
     if (rc != 0) return fail(rc);
   }
 
   Arena lists;
-  uint32_t *ulen = nullptr, *ubsum = nullptr;
-  want_lists(lists, g, &ulen, &ubsum);
+  want_split(lists, g);
   {
     void *base = A.get(lists.total);
     if (!base) return fail(PIPAD_ERR_ALLOC);
     lists.assign(base);
   }
-  launch_row_lists(n, shortidx, hubidx, segoff, g, st);
-  PIPAD_TRY_T(hipGetLastError());
   {
-    const int rc = build_split_arrays(g, ulen, ubsum, st);
+    const int rc = build_split_arrays(g, st);
     if (rc != 0) return fail(rc);
   }
   if (!alloc) {
