@@ -413,24 +413,6 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
   static_assert(!UPD || (VEC == 4 && FAST), "the fused update rides on the fast float4 path");
   extern __shared__ __align__(16) float upd_lds[];  // UPD: W [K][Fo + 1], then the waves' tiles and row ids
   Sink sink;
-  if (UPD) {
-    const int K = 4 << a.ls_log2, ws = a.Fo + 1;
-    for (int idx = threadIdx.x; idx < K * a.Fo; idx += kBlock) {
-      const int kk = idx / a.Fo, o = idx - kk * a.Fo;
-      upd_lds[kk * ws + o] = kk < a.F ? a.W[(int64_t)kk * a.ldw + o] : 0.f;
-    }
-    // row K: the bias (a load from global memory inside the flush would make the wave wait for
-    // every gather it has in flight)
-    for (int o = threadIdx.x; o < a.Fo; o += kBlock) upd_lds[K * ws + o] = a.bias ? a.bias[o] : 0.f;
-    const int w_floats = ((K + 1) * ws + 3) & ~3;
-    float *tiles = upd_lds + w_floats;
-    sink.wl = upd_lds;
-    sink.tile = tiles + (threadIdx.x / kWave) * kTileRows * kTileStride;
-    sink.rows = reinterpret_cast<int32_t *>(tiles + kWavesPerBlock * kTileRows * kTileStride) +
-                (threadIdx.x / kWave) * kTileRows;
-    sink.cnt = 0;
-    __syncthreads();  // before any wave leaves
-  }
   // Row gathers in flight per lane.  Measured on MI355X (N = 1M R-MAT frame): 4 beats 2 and 8 on
   // both paths; deeper bursts only queue up in front of the L1's miss slots.  Teams of fewer
   // than 4 lanes get U = LS so that U entries per lane group still fit the 64 staged entries.
@@ -477,6 +459,27 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
   const int slice = (slice_seq - t_seq * a.fchunks) * a.k + selected_snapshot(a, t_seq);
   const Slice s = slice_setup(a, slice, fl, VEC);
   const bool ntl = a.nt & 2;
+
+  if (UPD && w < split_blocks) {
+    sink.cnt = 0;  // (class parts of hub units end in partial sums: no use for W)
+  } else if (UPD) {
+    const int K = 4 << a.ls_log2, ws = a.Fo + 1;
+    for (int idx = threadIdx.x; idx < K * a.Fo; idx += kBlock) {
+      const int kk = idx / a.Fo, o = idx - kk * a.Fo;
+      upd_lds[kk * ws + o] = kk < a.F ? a.W[(int64_t)kk * a.ldw + o] : 0.f;
+    }
+    // row K: the bias (a load from global memory inside the flush would make the wave wait for
+    // every gather it has in flight)
+    for (int o = threadIdx.x; o < a.Fo; o += kBlock) upd_lds[K * ws + o] = a.bias ? a.bias[o] : 0.f;
+    const int w_floats = ((K + 1) * ws + 3) & ~3;
+    float *tiles = upd_lds + w_floats;
+    sink.wl = upd_lds;
+    sink.tile = tiles + (threadIdx.x / kWave) * kTileRows * kTileStride;
+    sink.rows = reinterpret_cast<int32_t *>(tiles + kWavesPerBlock * kTileRows * kTileStride) +
+                (threadIdx.x / kWave) * kTileRows;
+    sink.cnt = 0;
+    __syncthreads();  // before any wave leaves
+  }
 
   // ---- what this wave works on: a batch of consecutive list elements.  Class parts of hub units
   //      (from the class-grouped copies, ending in a partial sum) and whole mid rows: the whole
@@ -1282,7 +1285,6 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
   // (Measured on N = 200k .. 500k frames: slices that follow one another lose 5-10 % with full
   // batches although the launch as a whole has waves enough; side by side gains as much.)
   {
-    const int64_t enough = 4 * 8192;  // waves
     a.batch_short = kShortRowsPerWave;
     a.batch_mid = kLongRowsPerWave;
     a.batch_wide = coalescent ? 1 : kWideUnitsPerWave;
@@ -1295,11 +1297,17 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
              (int64_t)(f->n_long + a.batch_mid - 1) / a.batch_mid * mult +
              (int64_t)(f->n_items + a.batch_wide - 1) / a.batch_wide * mult_wide;
     };
+    // With the update fused in, a workgroup first copies W to LDS and a wave multiplies 16 rows at a
+    // time, so batches stay longer (N = 200k, F = Fo = 64: 4 to 8 rows per wave take 1.36 ms, 32 take
+    // 0.90, 64 take 0.95), and shorter than a tile only where there would be hardly any waves.
+    const int64_t enough = fused ? 8192 : 4 * 8192;
+    int min_short = fused ? std::max(nteams, kTileRows) : nteams;
     while (waves() < enough &&
-           (a.batch_short > nteams || a.batch_mid > min_mid || a.batch_wide > 1)) {
-      if (a.batch_short > nteams) a.batch_short >>= 1;
+           (a.batch_short > min_short || a.batch_mid > min_mid || a.batch_wide > 1)) {
+      if (a.batch_short > min_short) a.batch_short >>= 1;
       if (a.batch_mid > min_mid) a.batch_mid >>= 1;
       if (a.batch_wide > 1) a.batch_wide >>= 1;
+      if (a.batch_short <= min_short && waves() < 2048) min_short = nteams;
     }
     a.batch_short = std::max(a.batch_short, nteams);
     a.batch_mid = std::max(a.batch_mid, min_mid);

@@ -1,0 +1,20 @@
+"""The aggregation at the sizes where it changes how rows are dealt to waves, against the oracle."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+import synth  # noqa: E402
+from test_gpu_parity import pipad, run_case, run_update_case, _reset_options  # noqa: E402,F401
+
+
+def power_law(n, edges, k, seed):
+    s = synth.graphs(n, edges, k, 0.1, "chung-lu", (2.1, 2.0 * edges / n), seed)
+    return [(s.rowptr[t], s.col[t]) for t in range(k)]
+
+
+@pytest.mark.parametrize("n,k", [(15, 2), (16, 1), (17, 3), (1029, 1), (8191, 2), (30_003, 3)])
+def test_fused_update_batches(pipad, n, k):  # noqa: F811
+    """Rows per wave of the fused update: fewer than a tile, a tile, several."""
+    run_update_case(pipad, n, power_law(n, 4 * n, k, n), 32, 16, seed=n, with_a=n % 2 == 0)
