@@ -10,6 +10,7 @@ from test_gpu_parity import pipad, run_case, run_update_case, _reset_options  # 
 
 
 def power_law(n, edges, k, seed):
+    edges = min(edges, n * (n - 1) // 8)
     s = synth.graphs(n, edges, k, 0.1, "chung-lu", (2.1, 2.0 * edges / n), seed)
     return [(s.rowptr[t], s.col[t]) for t in range(k)]
 
