@@ -121,15 +121,22 @@ struct AggArgs {
 template <int VEC> struct V;
 template <> struct V<4> {
   using T = float4;
+  // 16 bytes at any multiple of 4: the global memory instructions do not ask for more
+  typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
   static __device__ inline T zero() { return make_float4(0.f, 0.f, 0.f, 0.f); }
-  static __device__ inline T load(const float *p) { return *reinterpret_cast<const float4 *>(p); }
+  static __device__ inline T load(const float *p) {
+    const f4 q = *reinterpret_cast<const f4 *>(p);
+    return make_float4(q.x, q.y, q.z, q.w);
+  }
   static __device__ inline void store(float *p, T v, bool nt) {
+    const f4 q = {v.x, v.y, v.z, v.w};
     if (nt) {
-      typedef float f4 __attribute__((ext_vector_type(4)));
-      f4 q = {v.x, v.y, v.z, v.w};
+      // (the empty statements keep the two stores apart: merged into one they lose the hint)
+      asm volatile("");
       __builtin_nontemporal_store(q, reinterpret_cast<f4 *>(p));
+      asm volatile("");
     } else {
-      *reinterpret_cast<float4 *>(p) = v;
+      *reinterpret_cast<f4 *>(p) = q;
     }
   }
   static __device__ inline void fma(T &a, float w, T x) {
@@ -159,7 +166,13 @@ template <> struct V<1> {
   static __device__ inline T zero() { return 0.f; }
   static __device__ inline T load(const float *p) { return *p; }
   static __device__ inline void store(float *p, T v, bool nt) {
-    if (nt) __builtin_nontemporal_store(v, p); else *p = v;
+    if (nt) {
+      asm volatile("");
+      __builtin_nontemporal_store(v, p);
+      asm volatile("");
+    } else {
+      *p = v;
+    }
   }
   static __device__ inline void fma(T &a, float w, T x) { a = fmaf(w, x, a); }
   static __device__ inline void add(T &a, T b) { a += b; }
@@ -193,6 +206,9 @@ __device__ __forceinline__ Slice slice_setup(const AggArgs &a, int slice, int fl
   s.t = t;
   s.fcol = (fc << a.ls_log2) * vec + fl * vec;
   s.fvalid = s.fcol < a.F;
+  // F need not be a multiple of vec: the lane whose columns would go past the row's end takes the
+  // last vec columns (it computes and stores some of its neighbour's again, with the same bits)
+  s.fcol = min(s.fcol, max(a.F - vec, 0));
   const int col = s.fvalid ? s.fcol : 0;  // idle lanes read column 0 and never store
   s.xt = a.X[t];
   s.xb = a.X[t] + col;
@@ -1216,7 +1232,7 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
   a.nsel = subset ? nsubset : f->k;
   for (int q = 0; q < a.nsel; ++q)
     a.sel[q >> 3] |= (uint64_t)(subset ? subset[q] : q) << ((q & 7) * 8);
-  bool vec4 = F % 4 == 0 && ldx % 4 == 0 && ldy % 4 == 0;
+  bool aligned = F % 4 == 0 && ldx % 4 == 0 && ldy % 4 == 0;
   for (int t = 0; t < f->k; ++t) {
     a.rowptr_d[t] = f->rowptr_d[t];
     a.col_d[t] = f->col_d[t];
@@ -1225,8 +1241,12 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
     a.swc[t] = f->swc[t];
     a.X[t] = X[t];  // (null for a snapshot a subset call leaves out: never touched)
     a.Y[t] = Y ? Y[t] : nullptr;
-    if ((reinterpret_cast<uintptr_t>(X[t]) | reinterpret_cast<uintptr_t>(a.Y[t])) & 15u) vec4 = false;
+    if ((reinterpret_cast<uintptr_t>(X[t]) | reinterpret_cast<uintptr_t>(a.Y[t])) & 15u) aligned = false;
   }
+#ifndef V4MIN
+#define V4MIN 4
+#endif
+  const bool vec4 = aligned || F >= V4MIN;
   // the fast path needs 32-bit byte offsets into a snapshot's matrix
   const bool fast = (int64_t)f->n * ldx * 4 < ((int64_t)1 << 32) && !opt.agg_generic;
   // The update rides inside the aggregation kernel when a slice is a whole row of one snapshot
@@ -1240,7 +1260,7 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
     a.ldw = upd->ldw;
     a.ldh = upd->ldh;
     for (int t = 0; t < f->k; ++t) a.H[t] = upd->H[t];
-    fused = vec4 && F >= 16 && F <= 64 && upd->Fo >= 16 && upd->Fo <= 64 && upd->Fo % 16 == 0 && fast;
+    fused = aligned && F >= 16 && F <= 64 && upd->Fo >= 16 && upd->Fo <= 64 && upd->Fo % 16 == 0 && fast;
     if (!fused && !Y) return PIPAD_ERR_INVALID_ARG;  // the two-step form needs Y as its workspace
   }
   // Small F handed over as one concatenated operand: the coalescent kernel (snapshot groups).

@@ -19,3 +19,10 @@ def power_law(n, edges, k, seed):
 def test_fused_update_batches(pipad, n, k):  # noqa: F811
     """Rows per wave of the fused update: fewer than a tile, a tile, several."""
     run_update_case(pipad, n, power_law(n, 4 * n, k, n), 32, 16, seed=n, with_a=n % 2 == 0)
+
+
+@pytest.mark.parametrize("F", [4, 5, 6, 7, 9, 15, 17, 30, 63, 65, 66, 67, 127, 130])
+@pytest.mark.parametrize("layout", ["list", "wide"])
+def test_widths_that_are_no_multiple_of_a_vector(pipad, F, layout):  # noqa: F811
+    """Rows at any multiple of 4 bytes; the last lane of a slice shares columns with its neighbour."""
+    run_case(pipad, 1500, power_law(1500, 30_000, 3, F), F, seed=F, layout=layout)
