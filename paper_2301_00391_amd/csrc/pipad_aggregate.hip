@@ -1299,11 +1299,11 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
   if (a.order < 0) a.order = (int64_t)f->n * sw * 4 >= (int64_t)PIPAD_ORDER_BYTES ? 1 : 0;
 
   // Rows per wave: the full batches amortise the per-wave set-up (and let a wave request its next
-  // row while it gathers the current one) on big frames; a small frame gets shorter ones (down to
-  // one step per wave), until what runs together -- one slice, or all of them when they go side
-  // by side -- has a few waves for every slot of the chip or the batches cannot shrink further.
-  // (Measured on N = 200k .. 500k frames: slices that follow one another lose 5-10 % with full
-  // batches although the launch as a whole has waves enough; side by side gains as much.)
+  // row while it gathers the current one) on big frames; smaller ones get shorter batches, until what
+  // runs together - one slice, or all of them when they go side by side - has about 44 waves for
+  // every CU, and a lane team walks no more than some 70 entries one after the other.  Twice to
+  // four times as many waves were slower by 4 to 27 % (N = 20k .. 200k), half as many by as much, and
+  // longer chains by 2 to 4 % (N = 300k .. 500k, whatever the number of waves).
   {
     a.batch_short = kShortRowsPerWave;
     a.batch_mid = kLongRowsPerWave;
@@ -1320,14 +1320,18 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
     // With the update fused in, a workgroup first copies W to LDS and a wave multiplies 16 rows at a
     // time, so batches stay longer (N = 200k, F = Fo = 64: 4 to 8 rows per wave take 1.36 ms, 32 take
     // 0.90, 64 take 0.95), and shorter than a tile only where there would be hardly any waves.
-    const int64_t enough = fused ? 8192 : 4 * 8192;
+    const int64_t enough = fused ? 8192 : coalescent ? 4 * 8192 : 11 * 1024;
     int min_short = fused ? std::max(nteams, kTileRows) : nteams;
-    while (waves() < enough &&
-           (a.batch_short > min_short || a.batch_mid > min_mid || a.batch_wide > 1)) {
+    // entries that a lane team walks one after the other in a batch of short rows
+    auto chain = [&]() {
+      return fused || coalescent || f->n_short == 0 ? 0 : f->short_entries * a.batch_short / nteams / f->n_short;
+    };
+    while ((waves() < enough && (a.batch_short > min_short || a.batch_mid > min_mid || a.batch_wide > 1)) ||
+           (chain() > 70 && a.batch_short > min_short)) {
       if (a.batch_short > min_short) a.batch_short >>= 1;
       if (a.batch_mid > min_mid) a.batch_mid >>= 1;
       if (a.batch_wide > 1) a.batch_wide >>= 1;
-      if (a.batch_short <= min_short && waves() < 2048) min_short = nteams;
+      if (a.batch_short <= min_short && fused && waves() < 2048) min_short = nteams;
     }
     a.batch_short = std::max(a.batch_short, nteams);
     a.batch_mid = std::max(a.batch_mid, min_mid);

@@ -127,6 +127,17 @@ __device__ inline int32_t lower_bound_near(const int32_t *col, int32_t lo, int32
   return lower_bound(col, a, b, c);
 }
 
+// Inclusive sum over the lanes up to this one: within rows of 16 lanes, then across the rows.
+__device__ __forceinline__ uint32_t wave_sum(uint32_t x) {
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);  // row_shr:1
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);  // row_shr:2
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);  // row_shr:4
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);  // row_shr:8
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);  // row_bcast:15
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);  // row_bcast:31
+  return x;
+}
+
 struct RowClasses {  // the thresholds of the row classes
   int32_t short_max, mid_max, threshold, segment;
 };
@@ -135,7 +146,7 @@ struct RowClasses {  // the thresholds of the row classes
 __device__ inline void count_rows(const RowClasses &rc, bool live, int64_t L, int64_t entries, int32_t common,
                                   RowCounts *out) {
   __shared__ uint32_t w_mid[kWavesPerBlock], w_hub[kWavesPerBlock], w_units[kWavesPerBlock],
-      w_common[kWavesPerBlock];
+      w_common[kWavesPerBlock], w_short[kWavesPerBlock];
   __shared__ uint64_t w_all[kWavesPerBlock];
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   const int cls = row_class(L, rc.short_max, rc.mid_max);
@@ -154,7 +165,9 @@ __device__ inline void count_rows(const RowClasses &rc, bool live, int64_t L, in
       all += __shfl_xor(all, m, kWave);
     }
   }
-  if (lane == 0) {
+  const uint32_t in_short = wave_sum(live && cls == 0 ? (uint32_t)L : 0u);
+  if (lane == kWave - 1) {
+    w_short[wave] = in_short;
     w_mid[wave] = (uint32_t)__popcll(is_mid);
     w_hub[wave] = (uint32_t)__popcll(is_hub);
     w_units[wave] = units;
@@ -163,9 +176,10 @@ __device__ inline void count_rows(const RowClasses &rc, bool live, int64_t L, in
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    RowCounts c = {0, 0, 0, 0, 0};
+    RowCounts c = {0, 0, 0, 0, 0, 0};
 #pragma unroll
     for (int w = 0; w < kWavesPerBlock; ++w) {
+      c.short_entries += w_short[w];
       c.common += w_common[w];
       c.mid += w_mid[w]; c.hub += w_hub[w]; c.units += w_units[w]; c.entries += w_all[w];
     }
@@ -553,17 +567,6 @@ constexpr int kTileScanBlock = 1024;
 constexpr int kTileScanRun = 2 * kTileScanBlock;  // tiles a workgroup scans at a time
 constexpr int kTileScanMost = 64;                 // workgroups; with more tiles each takes several such runs
 
-// Inclusive sum over the lanes up to this one: within rows of 16 lanes, then across the rows.
-__device__ __forceinline__ uint32_t wave_sum(uint32_t x) {
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);  // row_shr:1
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);  // row_shr:2
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);  // row_shr:4
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);  // row_shr:8
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);  // row_bcast:15
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);  // row_bcast:31
-  return x;
-}
-
 // Exclusive sums over the workgroup of N values per thread, and their totals.
 template <int N>
 __device__ inline void sum_block(const uint32_t (&v)[N], uint32_t (&before)[N], uint32_t (&total)[N]) {
@@ -589,19 +592,21 @@ __device__ inline void sum_block(const uint32_t (&v)[N], uint32_t (&before)[N], 
 }
 
 // RowCounts as 32-bit values whose sums over a workgroup do not overflow.
-constexpr int kRowSums = 6;
+constexpr int kRowSums = 7;
 __device__ inline void split_counts(const RowCounts &c, bool in, uint32_t (&v)[kRowSums]) {
   v[0] = in ? c.mid : 0u;
   v[1] = in ? c.hub : 0u;
   v[2] = in ? c.units : 0u;
   v[3] = in ? c.common : 0u;
   v[4] = in ? (uint32_t)(c.entries & 0xfffffu) : 0u;
+  v[6] = in ? c.short_entries : 0u;
   v[5] = in ? (uint32_t)(c.entries >> 20) : 0u;  // (a workgroup's rows hold fewer than 2^36 entries)
 }
 __device__ inline RowCounts join_counts(const RowCounts &front, const uint32_t (&v)[kRowSums]) {
   RowCounts c;
   c.entries = front.entries + (uint64_t)v[4] + ((uint64_t)v[5] << 20);
   c.common = front.common + v[3];
+  c.short_entries = front.short_entries + v[6];
   c.mid = front.mid + v[0];
   c.hub = front.hub + v[1];
   c.units = front.units + v[2];
@@ -611,7 +616,7 @@ __device__ inline RowCounts join_counts(const RowCounts &front, const uint32_t (
 // Blocks [b0, b1) of `cnt`, scanned into `pre`; returns the counts in front of b1.  b0 is a multiple
 // of kTileScanBlock, or b1.
 __device__ inline RowCounts scan_rows(const RowCounts *cnt, RowCounts *pre, int64_t b0, int64_t b1) {
-  RowCounts front = {0, 0, 0, 0, 0};
+  RowCounts front = {0, 0, 0, 0, 0, 0};
   for (int64_t base = 0; base < b1; base += kTileScanBlock) {
     const int64_t at = base + threadIdx.x;
     uint32_t v[kRowSums], before[kRowSums], total[kRowSums];
@@ -682,6 +687,7 @@ __global__ __launch_bounds__(kTileScanBlock) void k_scan_counts(ScanArgs a, Fram
     v.mid = all.mid;
     v.hub = all.hub;
     v.units = all.units;
+    v.short_entries = all.short_entries;
     v.split_c = carry[1];
     v.split_d = all.entries - (uint64_t)a.k * carry[1];  // (what the common entries take in every snapshot)
     v.bad = *a.bad;
@@ -704,6 +710,7 @@ __global__ __launch_bounds__(kTileScanBlock) void k_scan_row_counts(const RowCou
     v.mid = all.mid;
     v.hub = all.hub;
     v.units = all.units;
+    v.short_entries = all.short_entries;
     v.split_c = all.common;
     v.split_d = all.entries;
     v.bad = 0;
@@ -1483,6 +1490,7 @@ int set_list_sizes(pipad_frame *f, const FrameTotals &v) {
   f->n_items = (int32_t)v.units;
   f->n_long = (int32_t)v.mid;
   f->n_short = f->n - f->n_long - f->n_hub;
+  f->short_entries = (int64_t)v.short_entries;
   f->split_c = (int64_t)v.split_c;
   f->split_d = (int64_t)v.split_d;
   if (f->split_c + f->split_d >= ((int64_t)1 << 31) ||

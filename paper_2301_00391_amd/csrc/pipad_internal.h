@@ -78,6 +78,7 @@ struct pipad_frame {
   pipad::Options opt;                // the options as they stood when the frame was built
   int32_t short_max = 0, mid_max = 0, hub_threshold = 0, hub_segment = 0;
   int32_t n_short = 0, n_long = 0;
+  int64_t short_entries = 0;         // lengths of the short rows together
   int32_t *rows_short = nullptr;     // [n_short] ascending
   int32_t *rows_long = nullptr;      // [n_long] the mid rows
   int32_t n_hub = 0;
@@ -177,11 +178,12 @@ size_t scan_block_words(uint32_t m);
 struct RowCounts {
   uint64_t entries;
   uint32_t common, mid, hub, units;
+  uint32_t short_entries;  // lengths of the short rows
 };
 // The data-dependent sizes as the host reads them.
 struct FrameTotals {
   uint64_t split_c, split_d;  // common / exclusive entries of the hub rows
-  uint32_t nnz_c, mid, hub, units;
+  uint32_t nnz_c, mid, hub, units, short_entries;
   uint32_t bad;               // the snapshots are not canonical
   uint32_t seq;               // which build these sizes belong to
 };

@@ -26,3 +26,8 @@ def test_fused_update_batches(pipad, n, k):  # noqa: F811
 def test_widths_that_are_no_multiple_of_a_vector(pipad, F, layout):  # noqa: F811
     """Rows at any multiple of 4 bytes; the last lane of a slice shares columns with its neighbour."""
     run_case(pipad, 1500, power_law(1500, 30_000, 3, F), F, seed=F, layout=layout)
+
+
+@pytest.mark.parametrize("n,edges,k", [(700, 3000, 1), (9000, 40_000, 5), (40_000, 400_000, 2)])
+def test_batches_of_short_rows(pipad, n, edges, k):  # noqa: F811
+    run_case(pipad, n, power_law(n, edges, k, n), 20, seed=n)
