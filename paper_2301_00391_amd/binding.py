@@ -126,9 +126,23 @@ def _copy_from_device(ptr: Optional[int], count: int, dtype: torch.dtype, device
     return torch.as_tensor(_DevArray(ptr, count, typestr), device=device).clone()
 
 
-def _stream_handle(stream) -> int:
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return int(s.cuda_stream)
+# The current stream of a device as a plain handle and the current device's index, without the
+# objects that torch.cuda.current_stream() and torch.cuda.device() make on every call: on small
+# frames the host side of a call takes longer than its kernels.
+_current_raw_stream = torch._C._cuda_getCurrentRawStream
+_current_device = torch._C._cuda_getDevice
+
+
+def _on_device(index: int, fn, *args) -> int:
+    """fn(*args) with the given device current."""
+    if _current_device() == index:
+        return fn(*args)
+    with torch.cuda.device(index):
+        return fn(*args)
+
+
+def _device_index(device) -> int:
+    return device.index if device.index is not None else torch.cuda.current_device()
 
 
 Snapshot = Tuple[torch.Tensor, torch.Tensor]  # (rowptr int32[n+1], colidx int32[nnz]) on the GPU
@@ -141,39 +155,53 @@ class Frame:
                  stream=None):
         self._h = handle
         self.n, self.k, self.device = n, k, device
+        self._index = _device_index(device)
         self._buffers = buffers  # torch tensors handed to the library through the allocator
         self._callback = callback  # the library may call it again (aggregate scratch)
         # torch's allocator hands memory out, and takes it back, in the order of the stream that
         # was current at the allocation; work on any other stream has to be waited for in close()
-        self._alloc_stream = torch.cuda.current_stream(device)
-        self._streams = {stream if stream is not None else self._alloc_stream}
+        self._alloc_stream = _current_raw_stream(self._index)
+        self._other_streams = {}
         self._temp = None
+        built_on = self._stream(stream)
         if callback is not None:
-            # the build's temporaries can go back to the allocator as soon as the build's kernels
-            # have run: remember the buffer and an event behind them
+            # the build's temporaries can go back to the allocator as soon as the build's kernels have
+            # run: at once where its order is that of the build's stream, else behind an event
             ptr, size = _vp(), ctypes.c_size_t()
             _check(load_library().pipad_frame_temporaries(handle, ctypes.byref(ptr), ctypes.byref(size)))
             if ptr.value:
                 held = [b for b in buffers if b.data_ptr() == ptr.value]
-                event = torch.cuda.Event()
-                event.record(next(iter(self._streams)))
-                self._temp = (held, event)
+                if built_on == self._alloc_stream:
+                    self._drop(held)
+                else:
+                    event = torch.cuda.Event()
+                    event.record(self._other_streams[built_on])
+                    self._temp = (held, event)
+
+    def _stream(self, stream) -> int:
+        """Handle of the stream a call runs on; streams other than the allocator's are remembered."""
+        raw = int(stream.cuda_stream) if stream is not None else _current_raw_stream(self._index)
+        if raw != self._alloc_stream and raw not in self._other_streams:
+            self._other_streams[raw] = stream if stream is not None else torch.cuda.current_stream(self._index)
+        return raw
+
+    def _drop(self, held: list) -> None:
+        gone = {id(b) for b in held}
+        self._buffers[:] = [b for b in self._buffers if id(b) not in gone]
 
     def _release_temporaries(self, wait: bool = False) -> None:
         if self._temp is not None and (wait or self._temp[1].query()):
             if wait:
                 self._temp[1].synchronize()
-            held = {id(b) for b in self._temp[0]}
-            self._buffers[:] = [b for b in self._buffers if id(b) not in held]
+            self._drop(self._temp[0])
             self._temp = None
 
     def close(self) -> None:
         if self._h:
             # work of this frame may still be running on streams other than the one its buffers
             # are ordered on
-            for s in self._streams:
-                if s != self._alloc_stream:
-                    s.synchronize()
+            for s in self._other_streams.values():
+                s.synchronize()
             load_library().pipad_frame_destroy(self._h)
             self._h = None
             self._temp = None
@@ -243,10 +271,9 @@ def frame_transpose(frame: Frame, allocator: str = "torch", stream=None) -> Fram
     lib = load_library()
     buffers, cb = _make_allocator(allocator, frame.device)
     out = _vp()
-    with torch.cuda.device(frame.device):
-        status = lib.pipad_frame_transpose(frame._h, ctypes.cast(cb, _vp) if cb is not None else None,
-                                           None, _stream_handle(stream), ctypes.byref(out))
-    _check(status)
+    raw = int(stream.cuda_stream) if stream is not None else _current_raw_stream(frame._index)
+    _check(_on_device(frame._index, lib.pipad_frame_transpose, frame._h,
+                      ctypes.cast(cb, _vp) if cb is not None else None, None, raw, ctypes.byref(out)))
     return Frame(out.value, frame.n, frame.k, frame.device, buffers, cb, stream)
 
 
@@ -263,25 +290,21 @@ def frame_build_overlap(snapshots: Sequence[Snapshot], validate: bool = False,
     rp0 = snapshots[0][0]
     n = rp0.numel() - 1
     device = rp0.device
-    arr = (_Csr * k)()
-    keep = []
-    for t, (rp, col) in enumerate(snapshots):
-        for x in (rp, col):
-            if x.dtype != torch.int32 or not x.is_cuda or not x.is_contiguous() or x.device != device:
-                raise ValueError("snapshots must be contiguous int32 tensors on one GPU")
-        keep.append((rp, col))
-        arr[t].n = rp.numel() - 1
-        arr[t].nnz = col.numel()
-        arr[t].rowptr = rp.data_ptr()
-        arr[t].colidx = col.data_ptr() if col.numel() else None
+    int32 = torch.int32
+    descr = []
+    for rp, col in snapshots:
+        if rp.dtype != int32 or not rp.is_cuda or not rp.is_contiguous() or rp.device != device or \
+                col.dtype != int32 or not col.is_cuda or not col.is_contiguous() or col.device != device:
+            raise ValueError("snapshots must be contiguous int32 tensors on one GPU")
+        nnz = col.numel()
+        descr.append((rp.numel() - 1, nnz, rp.data_ptr(), col.data_ptr() if nnz else None))
+    arr = (_Csr * k)(*descr)
     buffers, cb = _make_allocator(allocator, device)
     out = _vp()
-    with torch.cuda.device(device):
-        status = lib.pipad_frame_build_overlap(
-            n, k, arr, VALIDATE if validate else 0,
-            ctypes.cast(cb, _vp) if cb is not None else None, None,
-            _stream_handle(stream), ctypes.byref(out))
-    _check(status)
+    index = _device_index(device)
+    raw = int(stream.cuda_stream) if stream is not None else _current_raw_stream(index)
+    _check(_on_device(index, lib.pipad_frame_build_overlap, n, k, arr, VALIDATE if validate else 0,
+                      ctypes.cast(cb, _vp) if cb is not None else None, None, raw, ctypes.byref(out)))
     return Frame(out.value, n, k, device, buffers, cb, stream)
 
 
@@ -291,29 +314,39 @@ Features = Union[torch.Tensor, Sequence[torch.Tensor]]
 def _operand(x: Features, n: int, k: int, name: str) -> Tuple[List[int], int, int]:
     """Returns (k device pointers, row stride in elements, F).  Accepts a list of k [n, F] matrices
     sharing one row stride, or one [n, k, F] tensor (the physically concatenated coalescent operand)."""
+    float32 = torch.float32
     if isinstance(x, torch.Tensor):
         if x.dim() != 3 or x.shape[0] != n or x.shape[1] != k:
             raise ValueError(f"{name}: a single tensor must have shape [n, k, F]")
-        mats = [x[:, t, :] for t in range(k)]
-    else:
-        mats = list(x)
-        if len(mats) != k:
-            raise ValueError(f"{name}: need k = {k} matrices")
-    F = mats[0].shape[1]
-    ld = None
+        if x.dtype != float32 or not x.is_cuda:
+            raise ValueError(f"{name}: every matrix must be float32 [n, F] on the GPU")
+        F = x.shape[2]
+        s0, s1, s2 = x.stride()
+        if F > 1 and s2 != 1:
+            raise ValueError(f"{name}: feature columns must be contiguous")
+        first = x.data_ptr()
+        return [first + 4 * s1 * t for t in range(k)], (s0 if n > 1 else max(s0, F)), F
+    mats = list(x)
+    if len(mats) != k:
+        raise ValueError(f"{name}: need k = {k} matrices")
+    shape = mats[0].shape
+    F = shape[1]
+    if len(shape) != 2 or shape[0] != n:
+        raise ValueError(f"{name}: every matrix must be float32 [n, F] on the GPU")
+    strides = mats[0].stride()
+    if F > 1 and strides[1] != 1:
+        raise ValueError(f"{name}: feature columns must be contiguous")
     ptrs = []
     for m in mats:
-        if m.dtype != torch.float32 or not m.is_cuda or m.dim() != 2 or tuple(m.shape) != (n, F):
+        if m.dtype != float32 or not m.is_cuda or m.shape != shape:
             raise ValueError(f"{name}: every matrix must be float32 [n, F] on the GPU")
-        if F > 1 and m.stride(1) != 1:
-            raise ValueError(f"{name}: feature columns must be contiguous")
-        row = m.stride(0) if n > 1 else max(m.stride(0), F)
-        if ld is None:
-            ld = row
-        elif n > 1 and row != ld:
-            raise ValueError(f"{name}: all matrices must share one row stride")
+        if m.stride() != strides:
+            if F > 1 and m.stride(1) != 1:
+                raise ValueError(f"{name}: feature columns must be contiguous")
+            if n > 1 and m.stride(0) != strides[0]:
+                raise ValueError(f"{name}: all matrices must share one row stride")
         ptrs.append(m.data_ptr())
-    return ptrs, int(ld), int(F)
+    return ptrs, (strides[0] if n > 1 else max(strides[0], F)), F
 
 
 def frame_aggregate(frame: Frame, X: Features, Y: Optional[Features] = None, stream=None,
@@ -334,13 +367,10 @@ def frame_aggregate(frame: Frame, X: Features, Y: Optional[Features] = None, str
     yp, ldy, Fy = _operand(Y, n, k, "Y")
     if Fy != F:
         raise ValueError("X and Y must have the same number of feature columns")
-    xa = (_vp * k)(*xp)
-    ya = (_vp * k)(*yp)
+    array = _vp * k
     frame._release_temporaries()
-    frame._streams.add(stream if stream is not None else torch.cuda.current_stream(frame.device))
-    with torch.cuda.device(frame.device):
-        fn = lib.pipad_frame_aggregate_static if static_scratch else lib.pipad_frame_aggregate
-        _check(fn(frame._h, F, xa, ldx, ya, ldy, _stream_handle(stream)))
+    fn = lib.pipad_frame_aggregate_static if static_scratch else lib.pipad_frame_aggregate
+    _check(_on_device(frame._index, fn, frame._h, F, array(*xp), ldx, array(*yp), ldy, frame._stream(stream)))
     return Y
 
 
@@ -373,10 +403,8 @@ def frame_aggregate_subset(frame: Frame, snapshots: Sequence[int], X: Sequence[O
         xa[t], ya[t] = X[t].data_ptr(), Y[t].data_ptr()
     arr = (_i32 * len(sel))(*sel)
     frame._release_temporaries()
-    frame._streams.add(stream if stream is not None else torch.cuda.current_stream(frame.device))
-    with torch.cuda.device(frame.device):
-        _check(lib.pipad_frame_aggregate_subset(frame._h, len(sel), arr, F, xa, ldx, ya, ldy,
-                                                _stream_handle(stream)))
+    _check(_on_device(frame._index, lib.pipad_frame_aggregate_subset, frame._h, len(sel), arr, F, xa, ldx, ya, ldy,
+                      frame._stream(stream)))
 
 
 def frame_aggregate_update(frame: Frame, X: Features, W: torch.Tensor,
@@ -409,10 +437,8 @@ def frame_aggregate_update(frame: Frame, X: Features, W: torch.Tensor,
             raise ValueError("A must have F feature columns")
         aa = (_vp * k)(*ap)
     frame._release_temporaries()
-    frame._streams.add(stream if stream is not None else torch.cuda.current_stream(frame.device))
-    with torch.cuda.device(frame.device):
-        _check(lib.pipad_frame_aggregate_update(
-            frame._h, F, xa, ldx, W.data_ptr(), W.stride(0) if F > 1 else max(Fo, W.stride(0)),
-            bias.data_ptr() if bias is not None else None, Fo, aa, lda, ha, ldh,
-            _stream_handle(stream)))
+    _check(_on_device(
+        frame._index, lib.pipad_frame_aggregate_update,
+        frame._h, F, xa, ldx, W.data_ptr(), W.stride(0) if F > 1 else max(Fo, W.stride(0)),
+        bias.data_ptr() if bias is not None else None, Fo, aa, lda, ha, ldh, frame._stream(stream)))
     return H
