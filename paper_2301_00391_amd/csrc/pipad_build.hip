@@ -127,17 +127,6 @@ __device__ inline int32_t lower_bound_near(const int32_t *col, int32_t lo, int32
   return lower_bound(col, a, b, c);
 }
 
-// Inclusive sum over the lanes up to this one: within rows of 16 lanes, then across the rows.
-__device__ __forceinline__ uint32_t wave_sum(uint32_t x) {
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);  // row_shr:1
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);  // row_shr:2
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);  // row_shr:4
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);  // row_shr:8
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);  // row_bcast:15
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);  // row_bcast:31
-  return x;
-}
-
 struct RowClasses {  // the thresholds of the row classes
   int32_t short_max, mid_max, threshold, segment;
 };
@@ -721,106 +710,6 @@ __global__ __launch_bounds__(kTileScanBlock) void k_scan_row_counts(const RowCou
   }
 }
 
-// ---- exclusive prefix sum over uint32 (three launches) ---------------------------------------
-constexpr int kScanItems = 8;
-constexpr int kScanTile = kBlock * kScanItems;
-
-// Exclusive scan of one value per thread across the workgroup; returns the prefix, sets total.
-__device__ inline uint32_t block_exclusive_scan(uint32_t v, uint32_t &total) {
-  __shared__ uint32_t wave_sum[kWavesPerBlock];
-  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-  uint32_t inc = v;
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    const uint32_t up = __shfl_up(inc, d, kWave);
-    if (lane >= d) inc += up;
-  }
-  __syncthreads();  // protects wave_sum against the previous call's readers
-  if (lane == kWave - 1) wave_sum[wave] = inc;
-  __syncthreads();
-  uint32_t before = 0, all = 0;
-#pragma unroll
-  for (int w = 0; w < kWavesPerBlock; ++w) {
-    const uint32_t x = wave_sum[w];
-    if (w < wave) before += x;
-    all += x;
-  }
-  total = all;
-  return before + inc - v;
-}
-
-// Up to kScanBatch arrays of one length are scanned by the same three launches (grid.y = array).
-constexpr int kScanBatch = 3;
-struct ScanBatch {
-  uint32_t *data[kScanBatch];
-  uint32_t *bsum[kScanBatch];  // ceil(m / kScanTile) words each
-};
-
-__global__ __launch_bounds__(kBlock) void k_scan_reduce(ScanBatch b, uint32_t m) {
-  const uint32_t *data = b.data[blockIdx.y];
-  const uint32_t base = blockIdx.x * (uint32_t)kScanTile + threadIdx.x * kScanItems;
-  uint32_t s = 0;
-#pragma unroll
-  for (int q = 0; q < kScanItems; ++q)
-    if (base + q < m) s += data[base + q];
-  uint32_t total;
-  block_exclusive_scan(s, total);
-  if (threadIdx.x == 0) b.bsum[blockIdx.y][blockIdx.x] = total;
-}
-
-__global__ __launch_bounds__(kBlock) void k_scan_blocksums(ScanBatch b, uint32_t nb) {
-  uint32_t *bsum = b.bsum[blockIdx.x];
-  uint32_t carry = 0;
-  for (uint32_t base = 0; base < nb; base += kBlock) {
-    const uint32_t idx = base + threadIdx.x;
-    const uint32_t v = idx < nb ? bsum[idx] : 0u;
-    uint32_t total;
-    const uint32_t pre = block_exclusive_scan(v, total);
-    if (idx < nb) bsum[idx] = carry + pre;
-    carry += total;
-  }
-}
-
-__global__ __launch_bounds__(kBlock) void k_scan_apply(ScanBatch b, uint32_t m) {
-  uint32_t *data = b.data[blockIdx.y];
-  const uint32_t base = blockIdx.x * (uint32_t)kScanTile + threadIdx.x * kScanItems;
-  uint32_t v[kScanItems];
-  uint32_t s = 0;
-#pragma unroll
-  for (int q = 0; q < kScanItems; ++q) {
-    v[q] = base + q < m ? data[base + q] : 0u;
-    s += v[q];
-  }
-  uint32_t total;
-  uint32_t pre = block_exclusive_scan(s, total) + b.bsum[blockIdx.y][blockIdx.x];
-#pragma unroll
-  for (int q = 0; q < kScanItems; ++q) {
-    if (base + q < m) data[base + q] = pre;
-    pre += v[q];
-  }
-}
-
-// In-place exclusive scans of `count` arrays data[j][0..m); bsum holds count * ceil(m / kScanTile)
-// words.
-int exclusive_scan(uint32_t *const *data, int count, uint32_t m, uint32_t *bsum, hipStream_t st) {
-  if (m == 0 || count == 0) return PIPAD_OK;
-  const uint32_t nb = (m + kScanTile - 1) / kScanTile;
-  ScanBatch b;
-  for (int j = 0; j < kScanBatch; ++j) {
-    b.data[j] = data[j < count ? j : 0];
-    b.bsum[j] = bsum + (size_t)(j < count ? j : 0) * nb;
-  }
-  hipLaunchKernelGGL(k_scan_reduce, dim3(nb, count), dim3(kBlock), 0, st, b, m);
-  hipLaunchKernelGGL(k_scan_blocksums, dim3(count), dim3(kBlock), 0, st, b, nb);
-  hipLaunchKernelGGL(k_scan_apply, dim3(nb, count), dim3(kBlock), 0, st, b, m);
-  PIPAD_HIP(hipGetLastError());
-  return PIPAD_OK;
-}
-
-int exclusive_scan(uint32_t *data, uint32_t m, uint32_t *bsum, hipStream_t st) {
-  return exclusive_scan(&data, 1, m, bsum, st);
-}
-
 // ---- rows ------------------------------------------------------------------------------------
 // The work lists of the aggregation.
 struct ListArgs {
@@ -1364,12 +1253,6 @@ __global__ __launch_bounds__(kBlock) void k_scatter(Snaps s, Tiles g, OutParts o
 }
 
 }  // namespace
-
-int scan_exclusive(uint32_t *const *data, int count, uint32_t m, uint32_t *bsum, hipStream_t st) {
-  return exclusive_scan(data, count, m, bsum, st);
-}
-
-size_t scan_block_words(uint32_t m) { return ((size_t)m + kScanTile - 1) / kScanTile; }
 
 // Pinned host memory per thread for the sizes a build reads back (allocated at the thread's first
 // build, kept until the process ends); null when pinned memory cannot be had.

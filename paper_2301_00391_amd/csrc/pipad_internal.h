@@ -170,9 +170,6 @@ inline dim3 grid1(int64_t items, int per_block, int y = 1) {
 
 
 // Helpers of the build that the transposition shares (defined in pipad_build.hip).
-// In-place exclusive scans of `count` (<= 3) arrays of m words; bsum: count * scan_block_words(m).
-int scan_exclusive(uint32_t *const *data, int count, uint32_t m, uint32_t *bsum, hipStream_t st);
-size_t scan_block_words(uint32_t m);
 // Counts of a run of rows: mid rows, hub rows and hub units, and what the hub rows hold: entries (of
 // all snapshots; of the exclusive parts where the parts are known) and, where known, common entries.
 struct RowCounts {
@@ -226,6 +223,17 @@ __host__ __device__ inline uint32_t column_class(int32_t j, int sub_log2) {
 }
 constexpr int kClasses = 8;      // XCDs of the chip
 constexpr int kMaxSubLog2 = 2;   // at most 4 sub classes per XCD
+
+// Inclusive sum over the lanes up to this one: within rows of 16 lanes, then across the rows.
+__device__ __forceinline__ uint32_t wave_sum(uint32_t x) {
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);  // row_shr:1
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);  // row_shr:2
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);  // row_shr:4
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);  // row_shr:8
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);  // row_bcast:15
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);  // row_bcast:31
+  return x;
+}
 
 // The update that may follow the aggregation: H_t = Y_t W + bias.
 struct UpdateSpec {

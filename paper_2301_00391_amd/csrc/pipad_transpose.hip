@@ -4,22 +4,23 @@
 // of an intersection is the intersection of the transposes - and all 1 + k parts go through the
 // same launches.  Transposing a CSR pattern is a stable sort of its entries by column: rows arrive
 // in ascending order, so they leave in ascending order within every column, which makes the result
-// canonical CSR again.  The sort is a least-significant-digit radix sort on 7-bit digits of the
-// column index (measured against 6 and 8 bits on frames of 0.2M to 1M nodes), written for
-// 64-lane waves:
+// canonical CSR again.  The sort is a least-significant-digit radix sort with two digits of up to 10
+// bits for up to a million nodes (three, then four, beyond), written for 64-lane waves:
 //
-//   tiles      a part is cut into tiles of 2048 consecutive entries, one wave per tile
-//   histogram  per tile and digit value; lanes of a wave that hold the same digit find each other
-//              with one ballot per digit bit, and the lowest of them adds their number
-//   scan       one exclusive prefix sum over all counts in (part, digit value, tile) order: the
-//              position where a tile's entries with that digit start.  Parts never mix, because a
-//              part's counts add up to its size
-//   scatter    the wave goes through its tile 64 entries at a time, in order, and puts the tile in
-//              digit order in LDS: an entry lands at start[digit] + (entries with the same digit in
-//              lanes below), and the lowest lane of a digit moves start[digit] on.  The staged
-//              tile is then written out in that order, neighbouring lanes to neighbouring
-//              addresses (direct stores from the rounds go to 64 different places each: the
-//              staged form is 1.3-1.9x faster for the whole call)
+//   tiles      a part is cut into tiles of 2048, 4096 or 8192 consecutive entries, a workgroup of 8
+//              waves each
+//   histogram  per tile and digit value
+//   scan       a workgroup per part and 64 digit values (a lane each, the tiles dealt to its waves):
+//              the entries with that digit in the tiles in front, and in all tiles of the part
+//   scatter    every wave ranks its share of the tile, 64 entries at a time: lanes of equal digit
+//              find each other with one ballot per digit bit, the lowest of them moves the wave's
+//              count of that digit on.  With the waves' counts summed up the tile goes to LDS in
+//              digit order and is written out in that order, neighbouring lanes to neighbouring
+//              addresses (direct stores would go to 64 different places each).  The first pass
+//              reads the part's columns in place and finds the entries' rows itself
+//
+// The sorted columns then give the row pointers (every change of the column is a row's start) in the
+// kernel that writes the entries' scales.
 //
 // Integer work with unique results: outputs are bit-exact regardless of scheduling.
 #include <cstring>
@@ -29,35 +30,25 @@
 namespace pipad {
 namespace {
 
-#ifndef PIPAD_SORT_DIGIT
-#define PIPAD_SORT_DIGIT 7
-#endif
-constexpr int kDigitBits = PIPAD_SORT_DIGIT;
-constexpr int kDigits = 1 << kDigitBits;
-#ifndef PIPAD_SORT_TILE
-#define PIPAD_SORT_TILE 2048
-#endif
-constexpr int kTile = PIPAD_SORT_TILE;  // entries per wave
-constexpr int kRounds = kTile / kWave;
+constexpr int kMaxDigitBits = 10;
+constexpr int kMaxDigits = 1 << kMaxDigitBits;
+constexpr int kSortBlock = 512;                      // threads per workgroup of the sort
+constexpr int kSortWaves = kSortBlock / kWave;
 
 struct SortArgs {
   int32_t nparts;                       // 1 + k
   int32_t n;
+  int32_t shift, bits;                  // digit = (key >> shift) & (2^bits - 1)
+  int32_t first, last;                  // first pass: keys are the parts' columns; last: values are the result
   uint32_t part_off[PIPAD_MAX_K + 2];   // first entry of every part in the concatenated arrays
   uint32_t tile_off[PIPAD_MAX_K + 2];   // first tile of every part
-  uint32_t anchor_off[PIPAD_MAX_K + 2]; // first row anchor of every part (one per 64 entries, plus one)
   const int32_t *rowptr[PIPAD_MAX_K + 1];  // source parts
   const int32_t *col[PIPAD_MAX_K + 1];
-  int32_t *rowptr_out[PIPAD_MAX_K + 1];    // transposed parts
-  int32_t *col_out[PIPAD_MAX_K + 1];
-  const uint32_t *key_in;
-  const int32_t *val_in;
-  uint32_t *key_out;
-  int32_t *val_out;
-  uint32_t *hist;                       // [sum over parts of kDigits * tiles of the part]
-  uint32_t *cnt;                        // [tiles][kDigits]: the same counts, kept unscanned per tile
-  int32_t shift;                        // digit = (key >> shift) & 255
-  int32_t last;                         // last pass: values go to col_out of their part
+  int32_t *col_out[PIPAD_MAX_K + 1];       // transposed parts
+  const int32_t *key_in, *val_in;
+  int32_t *key_out, *val_out;
+  uint32_t *hist;                       // [tiles][digits]
+  uint32_t *total;                      // [nparts][digits] entries per digit value
 };
 
 // Part that holds position e of a concatenated array with the given part offsets.
@@ -67,7 +58,105 @@ __device__ inline int part_of(const uint32_t *off, int nparts, uint32_t e) {
   return p;
 }
 
-// Last row i in [lo, hi] with rowptr[i] <= e, given rowptr[lo] <= e < rowptr[hi + 1].
+struct TileRange {
+  int p;
+  uint32_t tile, tiles;  // tile number within the part, tiles of the part
+  uint32_t begin, count;  // first entry within the part, entries
+};
+
+template <int R>
+__device__ inline TileRange tile_range(const SortArgs &g, uint32_t t) {
+  TileRange r;
+  r.p = part_of(g.tile_off, g.nparts, t);
+  r.tile = t - g.tile_off[r.p];
+  r.tiles = g.tile_off[r.p + 1] - g.tile_off[r.p];
+  r.begin = r.tile * (uint32_t)(kSortBlock * R);
+  r.count = min((uint32_t)(kSortBlock * R), g.part_off[r.p + 1] - g.part_off[r.p] - r.begin);
+  return r;
+}
+
+__device__ inline const int32_t *tile_keys(const SortArgs &g, const TileRange &r) {
+  return (g.first ? g.col[r.p] : g.key_in + g.part_off[r.p]) + r.begin;
+}
+
+// R entries per thread; a wave's share of a tile is R * 64 consecutive entries.
+template <int R>
+__global__ __launch_bounds__(kSortBlock) void k_radix_hist(SortArgs g) {
+  __shared__ uint32_t cnt[kMaxDigits];
+  const TileRange r = tile_range<R>(g, blockIdx.x);
+  const int digits = 1 << g.bits;
+  for (int d = threadIdx.x; d < digits; d += kSortBlock) cnt[d] = 0;
+  const int32_t *keys = tile_keys(g, r);
+  uint32_t key[R];
+#pragma unroll
+  for (int q = 0; q < R; ++q) key[q] = (uint32_t)keys[min((uint32_t)(q * kSortBlock) + threadIdx.x, r.count - 1)];
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < R; ++q)
+    if ((uint32_t)(q * kSortBlock) + threadIdx.x < r.count) atomicAdd(&cnt[(key[q] >> g.shift) & (digits - 1)], 1u);
+  __syncthreads();
+  uint32_t *hist = g.hist + ((uint64_t)blockIdx.x << g.bits);
+  for (int d = threadIdx.x; d < digits; d += kSortBlock) hist[d] = cnt[d];
+}
+
+// A lane per digit value (64 of them per workgroup, grid.y = part): its counts in the part's tiles are
+// summed up over the tiles in front.  The tiles are dealt to the waves in runs: each sums up its run,
+// then goes through it again from what the runs in front hold.
+constexpr int kScanWaves = 16;
+__global__ __launch_bounds__(kScanWaves * kWave) void k_radix_scan(SortArgs g) {
+  __shared__ uint32_t sums[kScanWaves][kWave];
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  const int p = blockIdx.y;
+  const uint32_t digits = 1u << g.bits, d = blockIdx.x * kWave + lane, dc = min(d, digits - 1);
+  const uint32_t tiles = g.tile_off[p + 1] - g.tile_off[p];
+  const uint32_t run = (tiles + kScanWaves - 1) / kScanWaves;
+  const uint32_t t0 = min(wave * run, tiles), t1 = min(t0 + run, tiles);
+  uint32_t *hist = g.hist + ((uint64_t)g.tile_off[p] << g.bits) + dc;
+  constexpr int UN = 8;  // loads in flight
+  uint32_t sum = 0;
+  for (uint32_t t = t0; t < t1; t += UN) {
+    uint32_t c[UN];
+#pragma unroll
+    for (int q = 0; q < UN; ++q) c[q] = hist[(uint64_t)min(t + q, t1 - 1) << g.bits];
+#pragma unroll
+    for (int q = 0; q < UN; ++q) sum += t + q < t1 ? c[q] : 0u;
+  }
+  sums[wave][lane] = sum;
+  __syncthreads();
+  uint32_t at = 0, all = 0;
+  for (int w = 0; w < kScanWaves; ++w) {
+    const uint32_t x = sums[w][lane];
+    if (w < wave) at += x;
+    all += x;
+  }
+  if (wave == 0 && d < digits) g.total[((uint64_t)p << g.bits) + d] = all;
+  for (uint32_t t = t0; t < t1; t += UN) {
+    uint32_t c[UN];
+#pragma unroll
+    for (int q = 0; q < UN; ++q) c[q] = hist[(uint64_t)min(t + q, t1 - 1) << g.bits];
+#pragma unroll
+    for (int q = 0; q < UN; ++q)
+      if (t + q < t1) {
+        if (d < digits) hist[(uint64_t)(t + q) << g.bits] = at;
+        at += c[q];
+      }
+  }
+}
+
+// The lanes of the wave whose digit equals this lane's, lanes with `live` false excluded.
+__device__ inline uint64_t same_digit(uint32_t digit, int bits, bool live) {
+  uint64_t mask = __ballot(live);
+#pragma unroll
+  for (int b = 0; b < kMaxDigitBits; ++b)
+    if (b < bits) {
+      const bool bit = (digit >> b) & 1u;
+      const uint64_t bal = __ballot(bit);
+      mask &= bit ? bal : ~bal;
+    }
+  return mask;
+}
+
+// Last row i in [lo, hi] with rp[i] <= e, given rp[lo] <= e < rp[hi + 1].
 __device__ inline int32_t row_of_entry(const int32_t *rp, int32_t lo, int32_t hi, int32_t e) {
   while (lo < hi) {
     const int32_t mid = lo + ((hi - lo + 1) >> 1);
@@ -76,220 +165,206 @@ __device__ inline int32_t row_of_entry(const int32_t *rp, int32_t lo, int32_t hi
   return lo;
 }
 
-// anchor[p's first anchor + w] = row of part p that holds the part's entry 64 w, for every w with
-// 64 w < nnz_p, and one more slot per part that receives n - 1: one lane per (part, row) writes
-// the (usually zero or one) slots whose entry falls into its row, so that the entries' rows can
-// then be found by a search between two anchors instead of over all rows.
-__global__ __launch_bounds__(kBlock) void k_row_anchors(SortArgs g, int32_t *anchor) {
-  const int64_t id = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (id >= (int64_t)g.n * g.nparts) return;
-  const int p = (int)(id / g.n);
-  const int32_t i = (int32_t)(id - (int64_t)p * g.n);
-  const int32_t a = g.rowptr[p][i], b = g.rowptr[p][i + 1];
-  int32_t *mine = anchor + g.anchor_off[p];
-  for (int64_t w = ((int64_t)a + kWave - 1) / kWave; w * kWave < b; ++w) mine[w] = i;
-  if (i == g.n - 1) mine[((int64_t)b + kWave - 1) / kWave] = g.n - 1;
-}
-
-// Concatenates the parts: key = column of the entry, value = its row.  One lane per entry of a
-// part, 64 consecutive entries per wave (the grid is cut per part: blockIdx.y), so the rows of a
-// wave's entries lie between two neighbouring anchors.
-__global__ __launch_bounds__(kBlock) void k_sort_input(SortArgs g, const int32_t *anchor,
-                                                        uint32_t *key, int32_t *val) {
-  const int p = blockIdx.y;
-  const int64_t local64 = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  const int32_t nnz = (int32_t)(g.part_off[p + 1] - g.part_off[p]);
-  if (local64 >= nnz) return;
-  const int32_t local = (int32_t)local64;
-  const int32_t *mine = anchor + g.anchor_off[p];
-  const int32_t w = local / kWave;
-  const int32_t r_lo = min(max(mine[w], 0), g.n - 1);
-  const int32_t r_hi = min(max(mine[w + 1], r_lo), g.n - 1);
-  const uint32_t e = g.part_off[p] + (uint32_t)local;
-  key[e] = (uint32_t)g.col[p][local];
-  val[e] = row_of_entry(g.rowptr[p], r_lo, r_hi, local);
-}
-
-// The lanes of the wave whose digit equals this lane's (bit set = same digit), lanes with
-// `live` false excluded: one ballot per digit bit.
-__device__ inline uint64_t same_digit(uint32_t digit, bool live) {
-  uint64_t mask = __ballot(live);
-#pragma unroll
-  for (int b = 0; b < kDigitBits; ++b) {
-    const bool bit = (digit >> b) & 1u;
-    const uint64_t bal = __ballot(bit);
-    mask &= bit ? bal : ~bal;
+// The rows of two entries by a whole wave, half of it each: 32 places are looked at in one round trip.
+// Returns the half's own answer.
+__device__ inline int32_t wave_row_of_entry(const int32_t *rp, int32_t n, int32_t e, int lane) {
+  constexpr int H = kWave / 2;
+  const int sub = lane % H, shift = lane / H * H;
+  int32_t lo = 0, hi = n;  // rp[lo] <= e < rp[hi]
+  while (__any(hi - lo > 1)) {
+    const int32_t step = (int32_t)(((int64_t)hi - lo + H) / (H + 1));
+    const int64_t idx = lo + (int64_t)(sub + 1) * step;
+    const int32_t v = rp[min(idx, (int64_t)n)];
+    const int m = __popc((uint32_t)(__ballot(idx < hi && v <= e) >> shift));
+    lo += m * step;
+    hi = (int32_t)min((int64_t)hi, (int64_t)lo + max(step, 1));
   }
-  return mask;
+  return lo;
 }
 
-struct TileRange {
-  int p;
-  uint32_t tile, tiles, begin, end;  // tile number within the part, tiles of the part, entries
-};
-
-__device__ inline TileRange tile_range(const SortArgs &g, uint32_t t) {
-  TileRange r;
-  r.p = part_of(g.tile_off, g.nparts, t);
-  r.tile = t - g.tile_off[r.p];
-  r.tiles = g.tile_off[r.p + 1] - g.tile_off[r.p];
-  r.begin = g.part_off[r.p] + r.tile * (uint32_t)kTile;
-  r.end = min(r.begin + (uint32_t)kTile, g.part_off[r.p + 1]);
-  return r;
-}
-
-// hist[(first count of the part) + digit * tiles + tile] = entries of the tile with that digit.
-__global__ __launch_bounds__(kBlock) void k_radix_hist(SortArgs g) {
-  __shared__ uint32_t cnt[kWavesPerBlock][kDigits];
-  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-  const uint32_t t = blockIdx.x * kWavesPerBlock + wave;
-  if (t >= g.tile_off[g.nparts]) return;
-  const TileRange r = tile_range(g, t);
-  for (int d = lane; d < kDigits; d += kWave) cnt[wave][d] = 0;
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  // the whole tile is requested up front (kRounds loads in flight per lane)
-  uint32_t keys[kRounds];
+template <int R>
+__global__ __launch_bounds__(kSortBlock) void k_radix_scatter(SortArgs g) {
+  __shared__ uint16_t rank_of[kSortWaves][kMaxDigits];  // counts, then the first place in the tile, per wave
+  __shared__ int32_t stage[kSortBlock * R];             // the tile's keys, then its values, in digit order
+  __shared__ uint32_t to[kMaxDigits];                   // place in the part minus place in the tile
+  __shared__ uint32_t wave_total[kSortWaves], wave_front[kSortWaves];
+  const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+  const TileRange r = tile_range<R>(g, blockIdx.x);
+  const int digits = 1 << g.bits;
+  const int32_t *keys = tile_keys(g, r);
+  const uint32_t first = (uint32_t)wave * (R * kWave);  // of this wave's share
+  int32_t key[R], val[R];
 #pragma unroll
-  for (int q = 0; q < kRounds; ++q) {
-    const uint32_t e = r.begin + q * kWave + lane;
-    keys[q] = e < r.end ? g.key_in[e] : 0u;
+  for (int q = 0; q < R; ++q) key[q] = keys[min(first + q * kWave + lane, r.count - 1)];
+  if (!g.first) {
+#pragma unroll
+    for (int q = 0; q < R; ++q)
+      val[q] = g.val_in[g.part_off[r.p] + r.begin + min(first + q * kWave + lane, r.count - 1)];
+  } else if (first < r.count) {
+    const int32_t *rp = g.rowptr[r.p];
+    const int32_t e0 = (int32_t)(r.begin + first), e1 = (int32_t)(r.begin + min(first + R * kWave, r.count)) - 1;
+    const int32_t end = wave_row_of_entry(rp, g.n, lane < kWave / 2 ? e0 : e1, lane);
+    const int32_t r0 = __builtin_amdgcn_readlane(end, 0), r1 = __builtin_amdgcn_readlane(end, kWave - 1);
+    int32_t lo[R], hi[R];
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+      lo[q] = r0;
+      hi[q] = r1;
+    }
+    for (int32_t range = r1 - r0; range > 0; range >>= 1)  // (all of the lane's entries side by side)
+#pragma unroll
+      for (int q = 0; q < R; ++q) {
+        const int32_t mid = lo[q] + ((hi[q] - lo[q] + 1) >> 1);
+        const bool up = rp[mid] <= min(e0 + q * kWave + lane, e1);
+        lo[q] = up ? mid : lo[q];
+        hi[q] = up ? hi[q] : max(mid - 1, lo[q]);
+      }
+#pragma unroll
+    for (int q = 0; q < R; ++q) val[q] = lo[q];
   }
+  for (int x = tid; x < kSortWaves * kMaxDigits / 2; x += kSortBlock) reinterpret_cast<uint32_t *>(rank_of)[x] = 0;
+  __syncthreads();
+  uint16_t *const mine = rank_of[wave];
+  uint32_t rank[R];  // entries of the same digit in front, within the wave
 #pragma unroll
-  for (int q = 0; q < kRounds; ++q) {
-    const uint32_t e = r.begin + q * kWave + lane;
-    const bool live = e < r.end;
-    const uint32_t digit = (keys[q] >> g.shift) & (kDigits - 1);
-    const uint64_t mask = same_digit(digit, live);
-    if (live && (mask & ((1ull << lane) - 1ull)) == 0) cnt[wave][digit] += (uint32_t)__popcll(mask);
+  for (int q = 0; q < R; ++q) {
+    const bool live = first + q * kWave + lane < r.count;
+    const uint32_t digit = ((uint32_t)key[q] >> g.shift) & (digits - 1);
+    const uint64_t mask = same_digit(digit, g.bits, live);
+    const uint64_t below = mask & ((1ull << lane) - 1ull);
+    const uint32_t before = mine[digit];
+    rank[q] = before + (uint32_t)__popcll(below);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // all reads before the count moves on
+    if (live && below == 0) mine[digit] = (uint16_t)(before + (uint32_t)__popcll(mask));
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   }
-  const uint64_t hbase = (uint64_t)kDigits * g.tile_off[r.p];
-  for (int d = lane; d < kDigits; d += kWave) {
-    g.hist[hbase + (uint64_t)d * r.tiles + r.tile] = cnt[wave][d];
-    g.cnt[(uint64_t)t * kDigits + d] = cnt[wave][d];
-  }
-}
-
-// Stable scatter of one tile by the current digit, from the scanned counts.  The tile is first
-// put in digit order in LDS (an entry's place there: the tile's entries with smaller digits, plus
-// those with the same digit in front of it), then written out in that order, so that neighbouring
-// lanes store to neighbouring addresses: runs of tile / 2^bits entries per digit instead of 64
-// different places per store.
-constexpr int kScatterWaves = 2;  // per workgroup: 16 KB of staging each
-static_assert((size_t)kScatterWaves * kTile * 8 <= 60 * 1024, "the staged tiles must fit the LDS of a workgroup");
-
-__global__ __launch_bounds__(kScatterWaves * kWave) void k_radix_scatter(SortArgs g) {
-  __shared__ uint32_t s_key[kScatterWaves][kTile];
-  __shared__ int32_t s_val[kScatterWaves][kTile];
-  __shared__ uint32_t lstart[kScatterWaves][kDigits];  // next free place of a digit within the tile
-  __shared__ uint32_t gdelta[kScatterWaves][kDigits];  // global place = place within the tile + this
-  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-  const uint32_t t = blockIdx.x * kScatterWaves + wave;
-  if (t >= g.tile_off[g.nparts]) return;
-  const TileRange r = tile_range(g, t);
-  const uint64_t hbase = (uint64_t)kDigits * g.tile_off[r.p];
+  __syncthreads();
   {
-    uint32_t running = 0;
-    for (int d0 = 0; d0 < kDigits; d0 += kWave) {
-      const int d = d0 + lane;
-      const uint32_t c = d < kDigits ? g.cnt[(uint64_t)t * kDigits + d] : 0u;
-      uint32_t incl = c;
+    // places of the digits in the tile, and of the part's digits in the part: thread t takes digits
+    // 2 t and 2 t + 1
+    constexpr int PER = kMaxDigits / kSortBlock;
+    const uint32_t *hist = g.hist + ((uint64_t)blockIdx.x << g.bits), *total = g.total + ((uint64_t)r.p << g.bits);
+    uint32_t in_tile[PER], in_part[PER], before[PER], all = 0, all_part = 0;
 #pragma unroll
-      for (int s2 = 1; s2 < kWave; s2 <<= 1) {
-        const uint32_t up = __shfl_up(incl, s2, kWave);
-        if (lane >= s2) incl += up;
+    for (int q = 0; q < PER; ++q) {
+      const int d = tid * PER + q, dc = min(d, digits - 1);
+      before[q] = hist[dc];
+      in_part[q] = total[dc];
+      if (d >= digits) in_part[q] = 0;
+    }
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      in_tile[q] = 0;
+      for (int w = 0; w < kSortWaves; ++w) in_tile[q] += rank_of[w][tid * PER + q];
+      all += in_tile[q];
+      all_part += in_part[q];
+    }
+    const uint32_t incl = wave_sum(all), incl_part = wave_sum(all_part);
+    if (lane == kWave - 1) {
+      wave_total[wave] = incl;
+      wave_front[wave] = incl_part;
+    }
+    __syncthreads();
+    uint32_t at = incl - all, at_part = incl_part - all_part;
+    for (int w = 0; w < wave; ++w) {
+      at += wave_total[w];
+      at_part += wave_front[w];
+    }
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      const int d = tid * PER + q;
+      if (d < digits) to[d] = at_part + before[q] - at;  // (mod 2^32)
+      at_part += in_part[q];
+      for (int w = 0; w < kSortWaves; ++w) {
+        const uint32_t c = rank_of[w][d];
+        rank_of[w][d] = (uint16_t)at;
+        at += c;
       }
-      const uint32_t excl = running + incl - c;
-      if (d < kDigits) {
-        lstart[wave][d] = excl;
-        gdelta[wave][d] = g.hist[hbase + (uint64_t)d * r.tiles + r.tile] - excl;  // (mod 2^32)
-      }
-      running += __shfl(incl, kWave - 1, kWave);
     }
   }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  // the tile in two halves, each requested up front (kRounds / 2 loads in flight per lane)
-  for (int half = 0; half < 2; ++half) {
-    uint32_t keys[kRounds / 2];
-    int32_t vals[kRounds / 2];
+  __syncthreads();
 #pragma unroll
-    for (int q = 0; q < kRounds / 2; ++q) {
-      const uint32_t e = r.begin + (half * (kRounds / 2) + q) * kWave + lane;
-      keys[q] = e < r.end ? g.key_in[e] : 0u;
-      vals[q] = e < r.end ? g.val_in[e] : 0;
-    }
-#pragma unroll
-    for (int q = 0; q < kRounds / 2; ++q) {
-      const uint32_t e = r.begin + (half * (kRounds / 2) + q) * kWave + lane;
-      const bool live = e < r.end;
-      const uint32_t digit = (keys[q] >> g.shift) & (kDigits - 1);
-      const uint64_t mask = same_digit(digit, live);
-      const uint64_t below = mask & ((1ull << lane) - 1ull);
-      uint32_t lpos = 0;
-      if (live) lpos = lstart[wave][digit] + (uint32_t)__popcll(below);
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // all reads of lstart before it moves on
-      if (live && below == 0) lstart[wave][digit] += (uint32_t)__popcll(mask);
-      if (live) {
-        s_key[wave][lpos] = keys[q];
-        s_val[wave][lpos] = vals[q];
-      }
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    }
+  for (int q = 0; q < R; ++q) {
+    rank[q] += mine[((uint32_t)key[q] >> g.shift) & (digits - 1)];
+    if (first + q * kWave + lane < r.count) stage[rank[q]] = key[q];
   }
-  int32_t *const dst_col = g.col_out[r.p];
-  const uint32_t part_begin = g.part_off[r.p];
-  const uint32_t here = r.end - r.begin;
-  for (uint32_t j = lane; j < here; j += kWave) {
-    const uint32_t key = s_key[wave][j];
-    const int32_t val = s_val[wave][j];
-    const uint32_t pos = gdelta[wave][(key >> g.shift) & (kDigits - 1)] + j;
-    if (g.last) {
-      dst_col[pos - part_begin] = val;  // the transposed part's column indices: the old rows
-      g.key_out[pos] = key;             // (the sorted old columns still give the row pointers)
-    } else {
-      g.key_out[pos] = key;
-      g.val_out[pos] = val;
+  __syncthreads();
+  int32_t sorted[R];
+#pragma unroll
+  for (int q = 0; q < R; ++q) sorted[q] = stage[q * kSortBlock + tid];
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < R; ++q)
+    if (first + q * kWave + lane < r.count) stage[rank[q]] = val[q];
+  __syncthreads();
+  int32_t *const key_out = g.key_out + g.part_off[r.p];
+  int32_t *const val_out = g.last ? g.col_out[r.p] : g.val_out + g.part_off[r.p];
+#pragma unroll
+  for (int q = 0; q < R; ++q) {
+    const uint32_t j = (uint32_t)(q * kSortBlock) + tid;
+    if (j < r.count) {
+      const uint32_t pos = to[((uint32_t)sorted[q] >> g.shift) & (digits - 1)] + j;
+      key_out[pos] = sorted[q];
+      val_out[pos] = stage[j];
     }
   }
 }
 
-// Row pointers of every transposed part from its sorted keys: rowptr[p][i] = keys of part p
-// below i.  One lane per (part, i), i in [0, n].
-__global__ __launch_bounds__(kBlock) void k_rowptr_of_sorted(SortArgs g, const uint32_t *keys) {
-  const int64_t id = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  const int64_t per = (int64_t)g.n + 1;
-  if (id >= per * g.nparts) return;
-  const int p = (int)(id / per);
-  const uint32_t i = (uint32_t)(id - p * per);
-  uint32_t lo = g.part_off[p], hi = g.part_off[p + 1];
-  while (lo < hi) {
-    const uint32_t mid = lo + ((hi - lo) >> 1);
-    if (keys[mid] < i) lo = mid + 1; else hi = mid;
-  }
-  g.rowptr_out[p][i] = (int32_t)(lo - g.part_off[p]);
-}
-
-// Column scales of the transposed parts' entries: wc[t][e] = dinv_t[col_c[e]] for the overlap
-// part (a node's k scales from the node-major copy of D^-1/2), wd[t][e] = dinv_t[col_d_t[e]] for
-// the exclusive part of snapshot t.  One lane per entry of the concatenated parts.
-struct ScaleArgs {
+// Row pointers and scales of the transposed parts (grid.y = part), a lane per entry.  The sorted
+// columns change where a row of the transposed part starts: the lane behind a change writes the row
+// pointers of the rows in between (many at once by the whole wave).  wc_t[e] = dinv_t[col_c[e]] for the
+// overlap part (a node's k scales from the node-major copy of D^-1/2), wd_t[e] = dinv_t[col_d_t[e]] for
+// the exclusive part of snapshot t.
+struct FinishArgs {
   int32_t nparts, n, k;
   uint32_t part_off[PIPAD_MAX_K + 2];
-  const int32_t *col[PIPAD_MAX_K + 1];
+  const int32_t *key;                     // sorted columns of the source, part by part
+  const int32_t *col[PIPAD_MAX_K + 1];    // columns of the transposed parts
+  int32_t *rowptr[PIPAD_MAX_K + 1];
   const float *dinv, *dinv_nk;
   float *wc[PIPAD_MAX_K];
   float *wd[PIPAD_MAX_K];
 };
 
+// rp[lo .. hi] = v, per lane; long runs by the whole wave.
+__device__ inline void fill_run(int32_t *rp, int32_t lo, int32_t hi, int32_t v, int lane) {
+  constexpr int32_t kAlone = 8;
+  uint64_t many = __ballot(hi - lo >= kAlone);
+  if (hi - lo < kAlone)
+    for (int32_t x = lo; x <= hi; ++x) rp[x] = v;
+  while (many) {
+    const int l = __ffsll((unsigned long long)many) - 1;
+    many &= many - 1;
+    const int32_t a = __builtin_amdgcn_readlane(lo, l), b = __builtin_amdgcn_readlane(hi, l),
+                  w = __builtin_amdgcn_readlane(v, l);
+    for (int64_t x = (int64_t)a + lane; x <= b; x += kWave) rp[x] = w;
+  }
+}
+
 // KV > 0: k == 4 * KV, a node's k scales are read as KV 16-byte pieces and the k destination
 // arrays are fixed at compile time; KV == 0: any k, one by one.
 template <int KV>
-__global__ __launch_bounds__(kBlock) void k_part_scales(ScaleArgs g) {
+__global__ __launch_bounds__(kBlock) void k_finish_parts(FinishArgs g) {
+  const int lane = threadIdx.x % kWave;
+  const int p = blockIdx.y;
+  const int32_t nnz = (int32_t)(g.part_off[p + 1] - g.part_off[p]);
   const int64_t e64 = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (e64 >= g.part_off[g.nparts]) return;
-  const uint32_t e = (uint32_t)e64;
-  if (e < g.part_off[1]) {  // overlap part
-    const int32_t c = g.col[0][e];
+  int32_t *const rp = g.rowptr[p];
+  if (nnz == 0) {  // no entries: all workgroups of the part clear its row pointers
+    for (int64_t x = e64; x <= g.n; x += (int64_t)gridDim.x * kBlock) rp[x] = 0;
+    return;
+  }
+  if (e64 - lane >= nnz) return;  // whole wave
+  const bool live = e64 < nnz;
+  const int32_t e = (int32_t)min(e64, (int64_t)nnz - 1);
+  const int32_t *key = g.key + g.part_off[p];
+  const int32_t mine = key[e], prev = e > 0 ? key[max(e - 1, 0)] : -1;
+  const int32_t c = g.col[p][e];
+  fill_run(rp, prev + 1, live ? mine : prev, e, lane);
+  const bool end = e64 == nnz - 1;
+  fill_run(rp, mine + 1, end ? g.n : mine, nnz, lane);
+  if (!live) return;
+  if (p == 0) {
     if (KV > 0) {
       const float4 *row = reinterpret_cast<const float4 *>(g.dinv_nk) + (int64_t)c * KV;
       float4 v[KV > 0 ? KV : 1];
@@ -307,10 +382,7 @@ __global__ __launch_bounds__(kBlock) void k_part_scales(ScaleArgs g) {
       for (int t = 0; t < g.k; ++t) g.wc[t][e] = row[t];
     }
   } else {
-    const int p = part_of(g.part_off, g.nparts, e);
-    const uint32_t local = e - g.part_off[p];
-    const int32_t c = g.col[p][local];
-    g.wd[p - 1][local] = g.dinv[(int64_t)(p - 1) * g.n + c];
+    g.wd[p - 1][e] = g.dinv[(int64_t)(p - 1) * g.n + c];
   }
 }
 
@@ -378,45 +450,49 @@ int transpose_frame(const pipad_frame *f, pipad_alloc_fn alloc, void *alloc_ctx,
     return PIPAD_OK;
   }
 
-  // ---- the parts side by side, cut into tiles
+  // ---- the parts side by side, cut into tiles.  Long tiles make long runs of equal digits, and with
+  // them long stores; short ones make enough workgroups out of few entries.
   SortArgs s;
   std::memset(&s, 0, sizeof(s));
   s.nparts = k + 1;
   s.n = n;
-  int64_t total = 0, tiles = 0, anchors = 0;
+  int64_t total = 0, tiles = 0;
   int32_t max_nnz = 0;
   for (int p = 0; p <= k; ++p) {
     const int32_t nnz = p == 0 ? f->nnz_c : f->nnz_d[p - 1];
     s.part_off[p] = (uint32_t)total;
-    s.tile_off[p] = (uint32_t)tiles;
-    s.anchor_off[p] = (uint32_t)anchors;
     total += nnz;
-    tiles += (nnz + kTile - 1) / kTile;
-    anchors += (nnz + kWave - 1) / kWave + 2;
     max_nnz = std::max(max_nnz, nnz);
     s.rowptr[p] = p == 0 ? f->rowptr_c : f->rowptr_d[p - 1];
     s.col[p] = p == 0 ? f->col_c : f->col_d[p - 1];
-    s.rowptr_out[p] = p == 0 ? g->rowptr_c : g->rowptr_d[p - 1];
     s.col_out[p] = p == 0 ? g->col_c : g->col_d[p - 1];
   }
   s.part_off[k + 1] = (uint32_t)total;
+  if (total >= ((int64_t)1 << 31)) return fail(PIPAD_ERR_TOO_LARGE);
+  // Measured for the whole sort (entries per thread 4 / 8 / 16): 0.24M entries 32 / 39 / 85 us, 3.4M
+  // 114 / 93 / 126, 14M 595 / 446 / 498, 62M 1619 / 1118 / 982.
+  const int per_thread = total < ((int64_t)1 << 20) ? 4 : total < ((int64_t)1 << 25) ? 8 : 16;
+  const int64_t tile = (int64_t)kSortBlock * per_thread;
+  for (int p = 0; p <= k; ++p) {
+    s.tile_off[p] = (uint32_t)tiles;
+    tiles += ((int64_t)(s.part_off[p + 1] - s.part_off[p]) + tile - 1) / tile;
+  }
   s.tile_off[k + 1] = (uint32_t)tiles;
-  const int64_t hist_len = std::max<int64_t>(tiles * kDigits, 1);
-  if (total >= ((int64_t)1 << 31) || hist_len >= ((int64_t)1 << 31)) return fail(PIPAD_ERR_TOO_LARGE);
+  int bits = 1;
+  while (((int64_t)1 << bits) < n) ++bits;
+  const int passes = bits <= kMaxDigitBits - 1 ? 1 : (bits + kMaxDigitBits - 1) / kMaxDigitBits;
+  s.bits = (bits + passes - 1) / passes;
 
   Arena tmp;
-  uint32_t *key_a = nullptr, *key_b = nullptr, *hist = nullptr, *cnt = nullptr, *bsum = nullptr;
   RowCounts *row_cnt = nullptr, *row_pre = nullptr;
   FrameTotals *totals = nullptr;
-  int32_t *val_a = nullptr, *val_b = nullptr, *anchor = nullptr;
-  tmp.want(&anchor, (size_t)anchors);
+  int32_t *key_a = nullptr, *key_b = nullptr, *val_a = nullptr, *val_b = nullptr;
   tmp.want(&key_a, (size_t)total);
-  tmp.want(&key_b, (size_t)total);
-  tmp.want(&val_a, (size_t)total);
-  tmp.want(&val_b, (size_t)total);
-  tmp.want(&hist, (size_t)hist_len);
-  tmp.want(&cnt, (size_t)hist_len);
-  tmp.want(&bsum, scan_block_words((uint32_t)hist_len) + 1);
+  tmp.want(&key_b, passes > 1 ? (size_t)total : 0);
+  tmp.want(&val_a, passes > 1 ? (size_t)total : 0);
+  tmp.want(&val_b, passes > 2 ? (size_t)total : 0);
+  tmp.want(&s.hist, (size_t)tiles << s.bits);
+  tmp.want(&s.total, (size_t)s.nparts << s.bits);
   tmp.want(&row_cnt, row_count_slots(n));
   tmp.want(&row_pre, row_count_slots(n));
   tmp.want(&totals, 1);
@@ -431,61 +507,57 @@ int transpose_frame(const pipad_frame *f, pipad_alloc_fn alloc, void *alloc_ctx,
   if (!temp) return fail(PIPAD_ERR_ALLOC);
   tmp.assign(temp);
 
-  PIPAD_TRY_T(hipMemcpyAsync(g->dinv, f->dinv, sizeof(float) * (size_t)k * n,
-                             hipMemcpyDeviceToDevice, st));
-  PIPAD_TRY_T(hipMemcpyAsync(g->dinv_nk, f->dinv_nk, sizeof(float) * (size_t)k * n,
-                             hipMemcpyDeviceToDevice, st));
+  // (the two copies of D^-1/2 lie next to each other in every frame)
+  const size_t dinv_span = (size_t)(f->dinv_nk - f->dinv) + (size_t)k * n;
+  if (g->dinv_nk - g->dinv == f->dinv_nk - f->dinv && f->dinv_nk > f->dinv) {
+    PIPAD_TRY_T(hipMemcpyAsync(g->dinv, f->dinv, sizeof(float) * dinv_span, hipMemcpyDeviceToDevice, st));
+  } else {
+    PIPAD_TRY_T(hipMemcpyAsync(g->dinv, f->dinv, sizeof(float) * (size_t)k * n, hipMemcpyDeviceToDevice, st));
+    PIPAD_TRY_T(hipMemcpyAsync(g->dinv_nk, f->dinv_nk, sizeof(float) * (size_t)k * n, hipMemcpyDeviceToDevice, st));
+  }
 
   // ---- stable sort of all entries by column, digit by digit
-  const uint32_t *sorted_keys = key_a;
+  const int32_t *sorted_keys = key_a;
   if (total > 0) {
-    hipLaunchKernelGGL(k_row_anchors, grid1((int64_t)n * (k + 1), kBlock), dim3(kBlock), 0, st, s, anchor);
-    hipLaunchKernelGGL(k_sort_input, grid1(max_nnz, kBlock, k + 1), dim3(kBlock), 0, st, s, anchor,
-                       key_a, val_a);
-    PIPAD_TRY_T(hipGetLastError());
-    int bits = 1;
-    while (((int64_t)1 << bits) < n) ++bits;
-    const int passes = (bits + kDigitBits - 1) / kDigitBits;
-    s.hist = hist;
-    s.cnt = cnt;
     for (int pass = 0; pass < passes; ++pass) {
-      s.key_in = pass % 2 == 0 ? key_a : key_b;
-      s.val_in = pass % 2 == 0 ? val_a : val_b;
-      s.key_out = pass % 2 == 0 ? key_b : key_a;
-      s.val_out = pass % 2 == 0 ? val_b : val_a;
-      s.shift = pass * kDigitBits;
+      s.first = pass == 0;
       s.last = pass == passes - 1;
-      hipLaunchKernelGGL(k_radix_hist, grid1(tiles, kWavesPerBlock), dim3(kBlock), 0, st, s);
-      PIPAD_TRY_T(hipGetLastError());
-      {
-        uint32_t *one = hist;
-        const int rc = scan_exclusive(&one, 1, (uint32_t)hist_len, bsum, st);
-        if (rc != 0) return fail(rc);
-      }
-      hipLaunchKernelGGL(k_radix_scatter, grid1(tiles, kScatterWaves), dim3(kScatterWaves * kWave), 0, st, s);
+      s.shift = pass * s.bits;
+      // keys alternate between the two buffers; the values of the first and last pass live elsewhere
+      s.key_in = pass % 2 == 0 ? key_b : key_a;
+      s.key_out = pass % 2 == 0 ? key_a : key_b;
+      s.val_in = pass % 2 == 0 ? val_b : val_a;
+      s.val_out = pass % 2 == 0 ? val_a : val_b;
+      auto hist = per_thread == 16 ? k_radix_hist<16> : per_thread == 8 ? k_radix_hist<8> : k_radix_hist<4>;
+      auto scatter = per_thread == 16 ? k_radix_scatter<16> : per_thread == 8 ? k_radix_scatter<8> : k_radix_scatter<4>;
+      hipLaunchKernelGGL(hist, dim3((unsigned)tiles), dim3(kSortBlock), 0, st, s);
+      hipLaunchKernelGGL(k_radix_scan, grid1(1 << s.bits, kWave, k + 1), dim3(kScanWaves * kWave), 0, st, s);
+      hipLaunchKernelGGL(scatter, dim3((unsigned)tiles), dim3(kSortBlock), 0, st, s);
       PIPAD_TRY_T(hipGetLastError());
       sorted_keys = s.key_out;
     }
   }
-  hipLaunchKernelGGL(k_rowptr_of_sorted, grid1(((int64_t)n + 1) * (k + 1), kBlock), dim3(kBlock), 0, st,
-                     s, sorted_keys);
-  if (total > 0) {
-    ScaleArgs c;
+  {
+    FinishArgs c;
     std::memset(&c, 0, sizeof(c));
     c.nparts = k + 1;
     c.n = n;
     c.k = k;
     for (int p = 0; p <= k + 1; ++p) c.part_off[p] = s.part_off[p];
-    for (int p = 0; p <= k; ++p) c.col[p] = s.col_out[p];
+    c.key = sorted_keys;
     c.dinv = g->dinv;
     c.dinv_nk = g->dinv_nk;
+    for (int p = 0; p <= k; ++p) {
+      c.col[p] = s.col_out[p];
+      c.rowptr[p] = p == 0 ? g->rowptr_c : g->rowptr_d[p - 1];
+    }
     for (int t = 0; t < k; ++t) {
       c.wc[t] = g->wc[t];
       c.wd[t] = g->wd[t];
     }
-    auto scales = k == 4 ? k_part_scales<1> : k == 8 ? k_part_scales<2> : k == 16 ? k_part_scales<4>
-                                                                                   : k_part_scales<0>;
-    hipLaunchKernelGGL(scales, grid1(total, kBlock), dim3(kBlock), 0, st, c);
+    auto finish = k == 4 ? k_finish_parts<1> : k == 8 ? k_finish_parts<2> : k == 16 ? k_finish_parts<4>
+                                                                                      : k_finish_parts<0>;
+    hipLaunchKernelGGL(finish, grid1(std::max(max_nnz, 1), kBlock, k + 1), dim3(kBlock), 0, st, c);
   }
   PIPAD_TRY_T(hipGetLastError());
 
