@@ -234,39 +234,54 @@ struct Staged {
   float w;
 };
 
-// Entry base + q of a list, or (own row, weight 0) past its end: such a filler may be gathered
-// harmlessly, which lets the FAST inner loop run without bounds checks.
-__device__ __forceinline__ Raw fetch_entry(const int32_t *__restrict__ col, const float *__restrict__ w,
-                                  int32_t start, int32_t len, int32_t pos, int32_t self, bool nt) {
+// A row's two entry lists, walked as one: the common entries, then the exclusive ones.
+struct Lists {
+  const int32_t *colc, *cold;  // (the same for the whole wave)
+  const float *wc, *wd;
+};
+
+// Entry `pos` of a row whose lists start at cs / ds and hold clen / total - clen entries, or (own row,
+// weight 0) past their end: such a filler may be gathered harmlessly, which lets the FAST inner loop
+// run without bounds checks.
+__device__ __forceinline__ Raw fetch_entry(const Lists &l, int32_t cs, int32_t clen, int32_t ds, int32_t total,
+                                           int32_t pos, int32_t self, bool nt) {
   Raw r;
   r.c = self;
   r.w = 0.f;
-  if (pos < len) {
+  if (pos < total) {
+    const bool common = pos < clen;
+    const int32_t at = common ? cs + pos : ds + (pos - clen);
+    const int32_t *pc = (common ? l.colc : l.cold) + at;
+    const float *pw = (common ? l.wc : l.wd) + at;
     if (nt) {
-      r.c = __builtin_nontemporal_load(col + start + pos);
-      r.w = __builtin_nontemporal_load(w + start + pos);
+      r.c = __builtin_nontemporal_load(pc);
+      r.w = __builtin_nontemporal_load(pw);
     } else {
-      r.c = col[start + pos];
-      r.w = w[start + pos];
+      r.c = *pc;
+      r.w = *pw;
     }
   }
   return r;
 }
 
-// Adds sum_e w[e] * X[col[e], :] over the `len` entries starting at `start` to acc.
-//   first      entry q of the list, already fetched by the caller (fetch_entry(..., q, ...))
+// Adds sum_e w[e] * X[col[e], :] over a row's entries (see fetch_entry) to acc.
+//   first      entries q, q + team_lanes, ... of the row's first chunk, already fetched by the caller
 //   team_base  first lane of the team; team_lanes lanes fetch a chunk of entries together
 //   q          this lane's index within the team
 //   slot/nslots  the team's lane groups take entries slot, slot + nslots, ... of each chunk
-//   lds        this wave's 64 staging slots
-// A chunk is fetched with one coalesced load of indices and scales (the next chunk is requested
+//   lds        this wave's 64 * EPL staging slots
+// A chunk - EPL entries per lane of the team, so that a team of one or two lanes has eight to go on
+// with, too - is fetched with coalesced loads of indices and scales (the next chunk is requested
 // before the current chunk's gathers), turned into row offsets once per entry, and parked in LDS;
 // every lane group then picks its entry up with a single 8-byte LDS read, so the inner loop is
 // one LDS read, one add, one 16-byte gather and VEC fused multiply-adds per entry.
-// The FAST inner loop needs nslots * UNR to divide team_lanes.
-template <int VEC, int UNR, bool FAST>
-__device__ __forceinline__ void walk(const int32_t *__restrict__ col, const float *__restrict__ w,
-                            int32_t start, int32_t len, Raw first, int team_base, int team_lanes,
+// (One walk over both lists instead of one each: most rows have only a few exclusive entries, and a
+// walk of their own cost them a whole round of gathers.)
+// The FAST inner loop needs nslots * UNR to divide team_lanes * EPL.
+template <int VEC, int UNR, bool FAST, int EPL>
+__device__ __forceinline__ void walk(const Lists &l, int32_t cs, int32_t clen, int32_t ds, int32_t len,
+                            const Raw (&first)[EPL],
+                            int team_base, int team_lanes,
                             int q, int slot, int nslots, const Slice &s, int64_t ldx, int32_t self,
                             bool nt, Staged *lds, typename V<VEC>::T &acc) {
   using VT = V<VEC>;
@@ -276,14 +291,24 @@ __device__ __forceinline__ void walk(const int32_t *__restrict__ col, const floa
   const char *xbytes = reinterpret_cast<const char *>(s.xt);
   const uint32_t lane_bytes = (uint32_t)(s.fvalid ? s.fcol : 0) * 4u;
   const float *xcol = s.xb;
-  Raw mine = first, next = first;
-  for (int32_t base = 0; base < len; base += team_lanes) {
-    const int32_t cnt = min(team_lanes, len - base);
-    if (base + team_lanes < len) next = fetch_entry(col, w, start, len, base + team_lanes + q, self, nt);
-    Staged st;
-    st.off = FAST ? (uint32_t)mine.c * row_bytes : (uint32_t)mine.c;
-    st.w = mine.w;
-    lds[team_base + q] = st;
+  const int chunk = team_lanes * EPL;
+  Staged *const mine_lds = lds + team_base * EPL;
+  Raw mine[EPL], next[EPL];
+#pragma unroll
+  for (int j = 0; j < EPL; ++j) mine[j] = next[j] = first[j];
+  for (int32_t base = 0; base < len; base += chunk) {
+    const int32_t cnt = min(chunk, len - base);
+    if (base + chunk < len)
+#pragma unroll
+      for (int j = 0; j < EPL; ++j)
+        next[j] = fetch_entry(l, cs, clen, ds, len, base + chunk + j * team_lanes + q, self, nt);
+#pragma unroll
+    for (int j = 0; j < EPL; ++j) {
+      Staged st;
+      st.off = FAST ? (uint32_t)mine[j].c * row_bytes : (uint32_t)mine[j].c;
+      st.w = mine[j].w;
+      mine_lds[j * team_lanes + q] = st;
+    }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     for (int32_t e0 = 0; e0 < cnt; e0 += nslots * UNR) {
       Staged en[UNR];
@@ -291,8 +316,8 @@ __device__ __forceinline__ void walk(const int32_t *__restrict__ col, const floa
 #pragma unroll
       for (int u = 0; u < UNR; ++u) {
         int32_t e = e0 + u * nslots + slot;
-        if (!FAST) e = min(e, team_lanes - 1);
-        en[u] = lds[team_base + e];
+        if (!FAST) e = min(e, chunk - 1);
+        en[u] = mine_lds[e];
         if (!FAST && e0 + u * nslots + slot >= cnt) en[u].w = 0.f;
       }
 #pragma unroll
@@ -310,7 +335,8 @@ __device__ __forceinline__ void walk(const int32_t *__restrict__ col, const floa
       for (int u = 0; u < UNR; ++u) VT::fma(acc, en[u].w, x[u]);
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    mine = next;
+#pragma unroll
+    for (int j = 0; j < EPL; ++j) mine[j] = next[j];
   }
 }
 
@@ -423,18 +449,22 @@ __device__ __forceinline__ float *partial_slot(const AggArgs &a, int slice_seq, 
   return a.partial + (((int64_t)slice_seq * a.nvp + slot) << a.ls_log2) * vec + fl * vec;
 }
 
-template <int VEC, bool FAST, int U, bool UPD>
+#ifndef PIPAD_AGG_DEPTH
+#define PIPAD_AGG_DEPTH 4  // row gathers in flight per lane
+#endif
+// A wave-wide team has 64 / LS lane groups and a chunk of 64 * EPL entries, EPL >= 4 / LS (launch()).
+static_assert(PIPAD_AGG_DEPTH <= 4, "more gathers in flight than a chunk holds");
+
+template <int VEC, bool FAST, int EPL, bool UPD>
 __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
   using VT = V<VEC>;
   static_assert(!UPD || (VEC == 4 && FAST), "the fused update rides on the fast float4 path");
   extern __shared__ __align__(16) float upd_lds[];  // UPD: W [K][Fo + 1], then the waves' tiles and row ids
   Sink sink;
-  // Row gathers in flight per lane.  Measured on MI355X (N = 1M R-MAT frame): 4 beats 2 and 8 on
-  // both paths; deeper bursts only queue up in front of the L1's miss slots.  Teams of fewer
-  // than 4 lanes get U = LS so that U entries per lane group still fit the 64 staged entries.
-  constexpr int UL = FAST ? U : 1;  // wave-wide teams (hub units)
-  constexpr int US = FAST ? U : 1;  // row-wide teams (mid and short rows)
-  __shared__ Staged staging[kWavesPerBlock][kWave];
+  // Row gathers in flight per lane.  Measured on MI355X (N = 1M R-MAT frame): 4 beats 2 and 8;
+  // deeper bursts only queue up in front of the L1's miss slots.
+  constexpr int U = FAST ? PIPAD_AGG_DEPTH : 1;
+  __shared__ Staged staging[kWavesPerBlock][kWave * EPL];
   Staged *lds = staging[threadIdx.x / kWave];
   const int lane = threadIdx.x % kWave;
   const int wave = threadIdx.x / kWave;
@@ -532,10 +562,11 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
 #endif
   const int rows_here = (int)min((int64_t)batch, list_len - first);
   // entry lists: the class-grouped copies for hub units, the frame's CSRs for whole rows
-  const int32_t *colc = split ? a.scol_c : a.col_c;
-  const float *wcs = split ? s.swc : s.wc;
-  const int32_t *cold = split ? a.scol_d : s.cd;
-  const float *wds = split ? a.swd : s.wd;
+  Lists lists;
+  lists.colc = split ? a.scol_c : a.col_c;
+  lists.wc = split ? s.swc : s.wc;
+  lists.cold = split ? a.scol_d : s.cd;
+  lists.wd = split ? a.swd : s.wd;
   // hub units only: first partial sum; nclass of them per unit
   const int64_t v_first = first * a.nclass + cls;
   int32_t r = 0, mc0 = 0, mc1 = 0, md0 = 0, md1 = 0;
@@ -567,8 +598,8 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
   int order = lane;
 #ifndef PIPAD_NO_ROW_ORDER
   if (!wide && ((VEC * 4) << a.ls_log2) >= 128) {
-    constexpr int gpl = US;  // entries a lane group gathers per round
-    const int rounds = lane < rows_here ? (mc1 - mc0 + gpl - 1) / gpl + (md1 - md0 + gpl - 1) / gpl : 0;
+    constexpr int gpl = U;  // entries a lane group gathers per round
+    const int rounds = lane < rows_here ? (mc1 - mc0 + md1 - md0 + gpl - 1) / gpl : 0;
     int mx = rounds, sm = rounds;
 #pragma unroll
     for (int m = kWave >> 1; m >= 1; m >>= 1) {
@@ -597,10 +628,10 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
   const int nslots = wide ? nteams : 1;
 
   struct Item {
-    int32_t i, cs, clen, ds, dlen;
+    int32_t i, cs, clen, ds, len;  // len: both lists together
     float di;
     bool have;
-    Raw fc, fd;
+    Raw first[EPL];
     typename VT::T xi;
   };
   auto prefetch = [&](int step) __attribute__((always_inline)) {
@@ -612,11 +643,12 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
     it.cs = __shfl(mc0, src, kWave);
     it.clen = __shfl(mc1, src, kWave) - it.cs;
     it.ds = __shfl(md0, src, kWave);
-    it.dlen = __shfl(md1, src, kWave) - it.ds;
+    it.len = it.clen + __shfl(md1, src, kWave) - it.ds;
     it.di = __shfl(mdi, src, kWave);
-    if (!it.have) { it.clen = 0; it.dlen = 0; }
-    it.fc = fetch_entry(colc, wcs, it.cs, it.clen, q, it.i, ntl);
-    it.fd = fetch_entry(cold, wds, it.ds, it.dlen, q, it.i, ntl);
+    if (!it.have) { it.clen = 0; it.len = 0; }
+#pragma unroll
+    for (int j = 0; j < EPL; ++j)
+      it.first[j] = fetch_entry(lists, it.cs, it.clen, it.ds, it.len, j * team_lanes + q, it.i, ntl);
     it.xi = VT::zero();
     if (!split) it.xi = VT::load(s.xb + (int64_t)it.i * a.ldx);
     return it;
@@ -635,8 +667,8 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
     if (step + 1 < nsteps) nxt = prefetch(step + 1);
     typename VT::T acc = VT::zero();
     if (wide) {
-      walk<VEC, UL, FAST>(colc, wcs, cur.cs, cur.clen, cur.fc, team_base, team_lanes, q, slot, nslots, s, a.ldx, cur.i, ntl, lds, acc);
-      walk<VEC, UL, FAST>(cold, wds, cur.ds, cur.dlen, cur.fd, team_base, team_lanes, q, slot, nslots, s, a.ldx, cur.i, ntl, lds, acc);
+      walk<VEC, U, FAST>(lists, cur.cs, cur.clen, cur.ds, cur.len, cur.first, team_base, team_lanes, q, slot, nslots,
+                          s, a.ldx, cur.i, ntl, lds, acc);
       reduce_slots<VEC>(a.ls_log2, acc);
       if (split) {
         if (team == 0 && s.fvalid)
@@ -648,10 +680,9 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
         if (team == 0 && s.fvalid) finish_row<VEC>(a, s, cur.i, cur.di, cur.xi, acc);
       }
     } else {
-      if (cur.have) {
-        walk<VEC, US, FAST>(colc, wcs, cur.cs, cur.clen, cur.fc, team_base, team_lanes, q, slot, nslots, s, a.ldx, cur.i, ntl, lds, acc);
-        walk<VEC, US, FAST>(cold, wds, cur.ds, cur.dlen, cur.fd, team_base, team_lanes, q, slot, nslots, s, a.ldx, cur.i, ntl, lds, acc);
-      }
+      if (cur.have)
+        walk<VEC, U, FAST>(lists, cur.cs, cur.clen, cur.ds, cur.len, cur.first, team_base, team_lanes, q, slot, nslots,
+                            s, a.ldx, cur.i, ntl, lds, acc);
       if constexpr (UPD) {
         if (cur.have) finish_row_to_sink(a, s, sink, sink.cnt + team, fl, cur.i, cur.di, cur.xi, acc);
         sink.cnt += rows_now;  // teams 0 .. rows_now - 1 had a row
@@ -663,24 +694,24 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
   if constexpr (UPD) sink_flush(a, s, sink, lane);
 }
 
-#ifndef PIPAD_AGG_DEPTH
-#define PIPAD_AGG_DEPTH 4  // row gathers in flight per lane on the main path
-#endif
 #ifndef PIPAD_AGG_WAVES
 #define PIPAD_AGG_WAVES 1  // lower bound on waves per SIMD the register allocation must allow
 #endif
 
-template <int VEC, bool FAST, int U>
+// EPL: entries per lane and chunk; teams of 8 lanes and more get on with 1.  (Teams of 1 and 2 lanes with
+// one entry per lane, fetched and gathered one after the other: N = 500k, k = 4, F = 4 486 us, with 4
+// entries 375; 8 entries take too many registers.)
+template <int VEC, bool FAST, int EPL>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(PIPAD_AGG_WAVES)))
 void k_aggregate(const AggArgs a) {
-  aggregate_body<VEC, FAST, U, false>(a);
+  aggregate_body<VEC, FAST, EPL, false>(a);
 }
 
 // The same walk with the update fused in.  Its tile bookkeeping would push the register count
 // just past the limit for four waves per SIMD, which the gathers need to hide their latency.
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void k_aggregate_update(const AggArgs a) {
-  aggregate_body<4, true, 4, true>(a);
+  aggregate_body<4, true, 1, true>(a);
 }
 
 // Adds the partial sums of every hub row in a fixed order and finishes the row.  One wave per
@@ -1129,17 +1160,15 @@ int launch(const AggArgs &a, bool fast, hipStream_t st, bool fused_update = fals
       return PIPAD_OK;
     }
   }
-  // gathers in flight per lane x lane groups per wave must not exceed the 64 staged entries, so
-  // narrow teams get fewer
   if (blocks > 0) {
     if (!fast)
       hipLaunchKernelGGL((k_aggregate<VEC, false, 1>), grid, block, 0, st, a);
-    else if (a.ls_log2 >= 2)
-      hipLaunchKernelGGL((k_aggregate<VEC, true, PIPAD_AGG_DEPTH>), grid, block, 0, st, a);
-    else if (a.ls_log2 == 1)
+    else if (a.ls_log2 >= 3)
+      hipLaunchKernelGGL((k_aggregate<VEC, true, 1>), grid, block, 0, st, a);
+    else if (a.ls_log2 == 2)
       hipLaunchKernelGGL((k_aggregate<VEC, true, 2>), grid, block, 0, st, a);
     else
-      hipLaunchKernelGGL((k_aggregate<VEC, true, 1>), grid, block, 0, st, a);
+      hipLaunchKernelGGL((k_aggregate<VEC, true, 4>), grid, block, 0, st, a);
   }
   if (fin > 0) hipLaunchKernelGGL((k_split_finish<VEC>), dim3((unsigned)fin), dim3(kBlock), 0, st, a);
   PIPAD_HIP(hipGetLastError());
