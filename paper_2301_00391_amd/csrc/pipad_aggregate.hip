@@ -94,6 +94,7 @@ struct AggArgs {
   int64_t nvp;        // partial sums per slice: nclass per hub unit
   int32_t nt;         // non-temporal hints (bit 0: Y stores, bit 1: index streams)
   int32_t sg;         // coalescent kernel: snapshots per lane team (slices are snapshot groups)
+  int32_t whole_units;  // coalescent kernel: one partial sum per hub unit, not one per class part
   int64_t ldx, ldy;
   const int32_t *rowptr_c, *col_c;
   const float *dinv;
@@ -152,8 +153,15 @@ template <> struct V<4> {
 template <> struct V<2> {
   using T = float2;
   static __device__ inline T zero() { return make_float2(0.f, 0.f); }
-  static __device__ inline T load(const float *p) { return *reinterpret_cast<const float2 *>(p); }
-  static __device__ inline void store(float *p, T v, bool) { *reinterpret_cast<float2 *>(p) = v; }
+  typedef float f2 __attribute__((ext_vector_type(2), aligned(4)));
+  static __device__ inline T load(const float *p) {
+    const f2 q = *reinterpret_cast<const f2 *>(p);
+    return make_float2(q.x, q.y);
+  }
+  static __device__ inline void store(float *p, T v, bool) {
+    const f2 q = {v.x, v.y};
+    *reinterpret_cast<f2 *>(p) = q;
+  }
   static __device__ inline void fma(T &a, float w, T x) { a.x = fmaf(w, x.x, a.x); a.y = fmaf(w, x.y, a.y); }
   static __device__ inline void add(T &a, T b) { a.x += b.x; a.y += b.y; }
   static __device__ inline T scale(float w, T a) { return make_float2(w * a.x, w * a.y); }
@@ -901,227 +909,247 @@ __global__ __launch_bounds__(kBlock) void k_update_resident(const AggArgs a, int
 // is only a few bytes, which is the "bandwidth unsaturation" case of Section 3.2.  Here a lane team
 // covers the rows of SG consecutive snapshots side by side (SG*F <= 64 columns), so one decoded
 // column index of the overlap part drives ONE contiguous gather for SG snapshots -- the paper's
-// parallel aggregation as it stands, with 64-lane waves: LS = SG*F/VEC lanes per row, 64/LS rows
-// (short rows) or entries (long rows) side by side per wave.  Snapshot groups play the role of
-// slices (consecutive workgroups take consecutive groups).
-// Every lane keeps the scale of its own snapshot: a staged entry is the row offset plus SG scales.
-// The exclusive entries differ per snapshot, so each lane walks the list of its own snapshot.
-template <int VEC>
+// parallel aggregation as it stands, with 64-lane waves: LPS = ceil(F/VEC) lanes per snapshot, LS
+// lanes (SG * LPS, rounded up to a power of two) per row, 64/LS rows (short rows) or entries (mid
+// rows and class parts) side by side per wave.  Snapshot groups play the role of slices.
+// The exclusive entries differ per snapshot, so the lanes of a snapshot walk a list of their own: the
+// common entries, then that snapshot's exclusive ones, in the same loop as in k_aggregate (walk), with
+// those lanes as its team.  Hub units go by column class, each on the XCD that holds the class.
+// Bound: the lines that the gathers fetch (an entry's row is 8 to 256 bytes, a line 128), for small
+// frames the chain index - row pointers - entries - rows, which is therefore requested two steps
+// ahead.  Measured (wide operand; before: entries staged for all snapshots of a team one load
+// after the other, hub units whole, VEC from F's divisors): N = 1M R-MAT, k = 8, F = 2 617 -> 585 us
+// (5.1 TB/s of lines); 300k, k = 8, F = 6 467 -> 352; 300k, k = 16, F = 3 846 -> 510; 50k, k = 12,
+// F = 9 468 -> 139; 5k, k = 16, F = 5 74 -> 19; 200k, k = 8, F = 16 173 -> 175.
+struct CoalItem {
+  int32_t i, cs, clen, ds, len;  // len: both lists together (0: this lane has nothing to do)
+};
+
+template <int VEC, int EPL>
 __global__ __launch_bounds__(kBlock) void k_aggregate_coalescent(const AggArgs a) {
   using VT = V<VEC>;
-  extern __shared__ uint32_t coal_lds[];  // per wave: 64 row offsets, then 64 x SG scales
+  constexpr int U = 4;  // row gathers in flight per lane
+  __shared__ Staged staging[kWavesPerBlock][kWave * EPL];
+  Staged *lds = staging[threadIdx.x / kWave];
   const int lane = threadIdx.x % kWave;
   const int wave = threadIdx.x / kWave;
-  const int sg = a.sg;
-  uint32_t *lds_off = coal_lds + wave * (kWave * (1 + sg));
-  float *lds_w = reinterpret_cast<float *>(lds_off + kWave);
-  const int ls = 1 << a.ls_log2;
-  const int fl = lane & (ls - 1);
+  const int fl = lane & ((1 << a.ls_log2) - 1);
   const int team = lane >> a.ls_log2;
   const int nteams = kWave >> a.ls_log2;
 
+  // Class parts first, one snapshot group after the other (the class's XCD is the workgroup index
+  // mod 8); then the whole rows, the groups side by side: they share the entry lists.
   const int64_t b = blockIdx.x;
-  const int g = (int)(b % a.nslices);  // snapshot group
-  int64_t w = b / a.nslices;
+  const int64_t wide_blocks = (int64_t)kClasses * a.blocks_wide;  // per sub class
+  const int64_t split_blocks = a.whole_units ? a.blocks_wide : wide_blocks << a.sub_log2;
+  const int64_t r0 = b - split_blocks * a.nslices;
+  const bool split = r0 < 0;
+  int g;  // snapshot group
+  int64_t w;
+  if (split) {
+    g = (int)(b / split_blocks);
+    w = b - g * split_blocks;
+  } else {
+    g = (int)(r0 % a.nslices);
+    w = r0 / a.nslices;
+  }
 
-  // this lane's place in the group's row: VEC columns of snapshot t
-  const int pos = fl * VEC;
-  int u = pos / a.F;
-  int t = g * sg + u;
-  const bool valid = pos < sg * a.F && t < a.k;
-  if (!valid) { u = 0; t = g * sg; }
-  const int lane_col = valid ? g * sg * a.F + pos : g * sg * a.F;  // column within the wide row
-  const float *xlane = a.X[0] + lane_col;
+  // this lane's place in the group's row: VEC columns of snapshot t (F need not be a multiple of
+  // VEC: a snapshot's last lane takes its last VEC columns)
+  const int lps = (a.F + VEC - 1) / VEC;
+  int u = fl / lps;
+  int t = g * a.sg + u;
+  const bool valid = u < a.sg && t < a.k;
+  if (!valid) { u = 0; t = g * a.sg; }
+  const int lane_col = t * a.F + (valid ? min((fl - u * lps) * VEC, a.F - VEC) : 0);  // within the wide row
   float *ylane = a.Y[0] + lane_col;
   const float *dv = a.dinv + (int64_t)t * a.n;
   const int32_t *rpd = a.rowptr_d[t];
-  const int32_t *cd = a.col_d[t];
-  const float *wd = a.wd[t];
   const uint32_t row_bytes = (uint32_t)a.ldx * 4u;
   const char *xbytes = reinterpret_cast<const char *>(a.X[0]);
   const uint32_t lane_bytes = (uint32_t)lane_col * 4u;
 
-  // Entry lists: short and mid rows are walked from the frame's CSRs, hub units from the
-  // class-grouped copies (all classes of a unit are contiguous there, so a unit is one list).
-  const int32_t *const scol_d = a.scol_d;
-  const float *const swd = a.swd;
-
-  // Adds `clen` overlap entries starting at col[cs] (scales scale_v[cs ...] of snapshot group
-  // member v) and this lane's own `dlen` exclusive entries starting at dcol[ds] / dw[ds].
-  auto walk_row = [&](int32_t i, bool grouped, int32_t cs, int32_t clen, int32_t ds, int32_t dlen,
-                      int team_base, int team_lanes, int q, int slot, int nslots,
-                      typename VT::T &acc) __attribute__((always_inline)) {
-    const int32_t *colp = grouped ? a.scol_c : a.col_c;
-    for (int32_t base = 0; base < clen; base += team_lanes) {
-      const int32_t cnt = min(team_lanes, clen - base);
-      int32_t c = i;
-      if (q < cnt) c = colp[cs + base + q];
-      lds_off[team_base + q] = (uint32_t)c * row_bytes;
-      for (int v = 0; v < sg; ++v) {
-        const int tv = min(g * sg + v, a.k - 1);
-        const float *w_plain = a.wc[tv], *w_grouped = a.swc[tv];
-        const float *wv = grouped ? w_grouped : w_plain;
-        lds_w[(team_base + q) * sg + v] = q < cnt ? wv[cs + base + q] : 0.f;
-      }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      if (team_lanes >= 4 * nslots) {
-        // four gathers in flight; slots past cnt hold (own row, 0), so no bounds checks
-        for (int32_t e0 = 0; e0 < cnt; e0 += 4 * nslots) {
-          uint32_t off[4];
-          float wt[4];
-          typename VT::T x[4];
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const int32_t e = e0 + v * nslots + slot;
-            off[v] = lds_off[team_base + e];
-            wt[v] = lds_w[(team_base + e) * sg + u];
-          }
-#pragma unroll
-          for (int v = 0; v < 4; ++v)
-            x[v] = VT::load(reinterpret_cast<const float *>(xbytes + (off[v] + lane_bytes)));
-#pragma unroll
-          for (int v = 0; v < 4; ++v) VT::fma(acc, valid ? wt[v] : 0.f, x[v]);
-        }
-      } else {
-        for (int32_t e = slot; e < cnt; e += nslots) {
-          const uint32_t off = lds_off[team_base + e];
-          const float wt = lds_w[(team_base + e) * sg + u];
-          const typename VT::T x = VT::load(reinterpret_cast<const float *>(xbytes + (off + lane_bytes)));
-          VT::fma(acc, valid ? wt : 0.f, x);
-        }
-      }
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    }
-    if (valid) {
-      const int32_t *dcol = grouped ? scol_d : cd;
-      const float *dw = grouped ? swd : wd;
-      // four entries in flight; positions past the end read the list's first entry with weight 0
-      for (int32_t e = slot; e < dlen; e += 4 * nslots) {
-        int32_t j[4];
-        float wt[4];
-        typename VT::T x[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int32_t ev = e + v * nslots;
-          const bool live = ev < dlen;
-          j[v] = dcol[ds + (live ? ev : e)];
-          wt[v] = live ? dw[ds + ev] : 0.f;
-        }
-#pragma unroll
-        for (int v = 0; v < 4; ++v) x[v] = VT::load(xlane + (int64_t)j[v] * a.ldx);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) VT::fma(acc, wt[v], x[v]);
-      }
-    }
-  };
-  auto finish = [&](int32_t i, typename VT::T acc) __attribute__((always_inline)) {
-    if (!valid) return;
-    const float di = dv[i];
-    VT::fma(acc, di, VT::load(xlane + (int64_t)i * a.ldx));
-    VT::store(ylane + (int64_t)i * a.ldy, VT::scale(di, acc), a.nt & 1);
-  };
-  // Entry lists of unit un: the overlap part (the same for all lanes) and this lane's own
-  // exclusive part.
-  auto unit_lists = [&](int64_t un, int32_t *cs, int32_t *clen, int32_t *ds, int32_t *dlen)
-      __attribute__((always_inline)) {
-    // (all classes of a unit are contiguous: from the start of the first to the end of the last)
-    const int64_t n_items = a.n_items;
-    const int32_t *sp = a.sptr + un;
-    *cs = sp[0];
-    *clen = sp[a.nclass * n_items] - *cs;
-    sp += (int64_t)(1 + t) * (a.nclass + 1) * n_items;
-    *ds = sp[0];
-    *dlen = sp[a.nclass * n_items] - *ds;
-  };
-
   const int32_t *const p_items = a.item_row, *const p_mid = a.rows_long, *const p_short = a.rows_short;
   const int64_t n_items = a.n_items, n_mid = a.n_long, n_short = a.n_short;
-  const int b_mid = a.batch_mid, b_short = a.batch_short;
-  if (w < a.blocks_wide) {
-    // ---- one hub unit per wave: a partial sum
-    const int64_t item = w * kWavesPerBlock + wave;
-    if (item >= n_items) return;
-    const int32_t i = p_items[item];
-    int32_t cs, clen, ds, dlen;
-    unit_lists(item, &cs, &clen, &ds, &dlen);
-    typename VT::T acc = VT::zero();
-    walk_row(i, true, cs, clen, ds, dlen, 0, kWave, lane, team, nteams, acc);
-    reduce_slots<VEC>(a.ls_log2, acc);
-    if (team == 0 && valid)
-      VT::store(a.partial + (((int64_t)item * a.nslices + g) << a.ls_log2) * VEC + fl * VEC, acc, false);
-    return;
+  const int b_wide = a.batch_wide, b_mid = a.batch_mid, b_short = a.batch_short;
+  const bool wide = split || w < a.blocks_mid;  // the whole wave on one list
+  int cls = 0;
+  if (split && !a.whole_units) {
+    const int sub = (int)(w / wide_blocks);
+    w -= sub * wide_blocks;
+    cls = ((int)(w & (kClasses - 1)) << a.sub_log2) + sub;
+    w >>= 3;
+  } else if (!wide) {
+    w -= a.blocks_mid;
   }
-  w -= a.blocks_wide;
-  const bool long_rows = w < a.blocks_mid;
-  if (!long_rows) w -= a.blocks_mid;
-  const int64_t list_len = long_rows ? n_mid : n_short;
-  const int batch = long_rows ? b_mid : b_short;
+  const int32_t *list = split ? p_items : wide ? p_mid : p_short;
+  const int64_t list_len = split ? n_items : wide ? n_mid : n_short;
+  const int batch = split ? b_wide : wide ? b_mid : b_short;
   const int64_t first = (w * kWavesPerBlock + wave) * batch;
   if (first >= list_len) return;
   const int rows_here = (int)min((int64_t)batch, list_len - first);
-  if (long_rows) {
-    // ---- mid rows: a wave per row, finished at once
-    for (int step = 0; step < rows_here; ++step) {
-      const int32_t i = p_mid[first + step];
-      const int32_t cs = a.rowptr_c[i], ce = a.rowptr_c[i + 1];
-      const int32_t ds = rpd[i];
-      typename VT::T acc = VT::zero();
-      walk_row(i, false, cs, ce - cs, ds, rpd[i + 1] - ds, 0, kWave, lane, team, nteams, acc);
-      reduce_slots<VEC>(a.ls_log2, acc);
-      if (team == 0) finish(i, acc);
-    }
-    return;
+
+  // entry lists: the class-grouped copies for hub units, the frame's CSRs for whole rows
+  Lists lists;
+  {
+    const float *w_plain = a.wc[t], *w_grouped = a.swc[t];
+    const int32_t *d_plain = a.col_d[t];
+    const float *wd_plain = a.wd[t];
+    lists.colc = split ? a.scol_c : a.col_c;
+    lists.cold = split ? a.scol_d : d_plain;
+    lists.wc = split ? w_grouped : w_plain;
+    lists.wd = split ? a.swd : wd_plain;
   }
-  // ---- short rows: a lane team per row
+  // metadata of the batch: lane l holds element l (the exclusive lists are per snapshot and read one
+  // step ahead)
   int32_t r = 0, mc0 = 0, mc1 = 0;
   if (lane < rows_here) {
-    r = p_short[first + lane];
-    mc0 = a.rowptr_c[r];
-    mc1 = a.rowptr_c[r + 1];
+    r = list[first + lane];
+    const int32_t *pc = split ? a.sptr + (int64_t)cls * n_items + first + lane : a.rowptr_c + r;
+    mc0 = pc[0];
+    mc1 = pc[split ? n_items : 1];
   }
-  const int nsteps = (rows_here + nteams - 1) / nteams;
-  for (int step = 0; step < nsteps; ++step) {
-    const int li = step * nteams + team;
+  const int per_step = wide ? 1 : nteams;
+  // For the walk a team is the lanes of one snapshot, of one row or, wave-wide, of all lane groups:
+  // they fetch that snapshot's entries together (the next smaller power of two of them, so that a
+  // chunk is a multiple of U entries; the others do the same again).
+  const int fetchers = lps >= 8 ? 8 : lps >= 4 ? 4 : lps >= 2 ? 2 : 1;
+  const int team_lanes = wide ? nteams * fetchers : fetchers;
+  const int q = (wide ? team * fetchers : 0) + ((fl - u * lps) & (fetchers - 1));
+  const int team_base = (wide ? u * nteams : team * a.sg + u) * fetchers;
+  const int slot = wide ? team : 0;
+  const int nslots = wide ? nteams : 1;
+  Slice s;
+  s.xt = a.X[0];
+  s.fcol = lane_col;
+  s.fvalid = true;
+  s.xb = s.xt + lane_col;
+  auto meta = [&](int step, int part) __attribute__((always_inline)) {
+    CoalItem it;
+    const int li = step * per_step + (wide ? 0 : team);
     const bool have = li < rows_here;
     const int src = have ? li : 0;
-    const int32_t i = __shfl(r, src, kWave);
-    const int32_t cs = __shfl(mc0, src, kWave);
-    const int32_t ce = __shfl(mc1, src, kWave);  // every lane takes part: sources must be active
-    if (have) {
-      typename VT::T acc = VT::zero();
-      const int32_t ds = rpd[i];
-      walk_row(i, false, cs, ce - cs, ds, rpd[i + 1] - ds, team << a.ls_log2, ls, fl, 0, 1, acc);
-      finish(i, acc);
+    it.i = __shfl(r, src, kWave);
+    it.cs = __shfl(mc0, src, kWave);
+    it.clen = __shfl(mc1, src, kWave) - it.cs;
+    int64_t stride = 1;
+    const int32_t *pd = rpd + it.i;
+    if (split) {
+      stride = n_items;
+      pd = a.sptr + ((int64_t)(1 + t) * (a.nclass + 1) + cls + part) * n_items + first + src;
+    }
+    it.ds = pd[0];
+    it.len = it.clen + pd[stride] - it.ds;
+    if (!have || !valid) it.len = 0;
+    return it;
+  };
+  struct Fetched {
+    Raw e[EPL];
+  };
+  auto fetch = [&](const CoalItem &it) __attribute__((always_inline)) {
+    Fetched f;
+#pragma unroll
+    for (int v = 0; v < EPL; ++v)
+      f.e[v] = fetch_entry(lists, it.cs, it.clen, it.ds, it.len, v * team_lanes + q, it.i, false);
+    return f;
+  };
+  auto walk_item = [&](const CoalItem &it, const Fetched &f) __attribute__((always_inline)) {
+    typename VT::T acc = VT::zero();
+    walk<VEC, U, true>(lists, it.cs, it.clen, it.ds, it.len, f.e, team_base, team_lanes, q, slot, nslots, s,
+                       a.ldx, it.i, false, lds, acc);
+    return acc;
+  };
+
+  const int nsteps = (rows_here + per_step - 1) / per_step;
+  CoalItem m = meta(0, 0);
+  Fetched f = fetch(m);
+  CoalItem m_next = meta(1, 0);
+  for (int step = 0; step < nsteps; ++step) {
+    const CoalItem cur = m;
+    const Fetched cur_f = f;
+    const bool have = step * per_step + (wide ? 0 : team) < rows_here;
+    typename VT::T xi = VT::zero();
+    float di = 0.f;
+    if (!split) {
+      xi = VT::load(reinterpret_cast<const float *>(xbytes + ((uint32_t)cur.i * row_bytes + lane_bytes)));
+      di = dv[cur.i];
+    }
+    if (step + 1 < nsteps) {
+      m = m_next;
+      f = fetch(m);
+      m_next = meta(step + 2, 0);
+    }
+    typename VT::T acc = walk_item(cur, cur_f);
+    if (wide) reduce_slots<VEC>(a.ls_log2, acc);
+    if (split) {
+      int64_t at = (int64_t)g * a.nvp + (first + step) * (a.whole_units ? 1 : a.nclass) + cls;
+      if (a.whole_units) {
+        // no room for a partial sum per class part: the parts one after the other, added in the
+        // order in which k_hub_finish_coalescent adds them
+        at = (int64_t)g * n_items + first + step;
+        for (int part = 1; part < a.nclass; ++part) {
+          CoalItem it = meta(step, part);
+          const int64_t c0 = a.sptr[(int64_t)part * n_items + first + step];
+          const int64_t c1 = a.sptr[(int64_t)(part + 1) * n_items + first + step];
+          const int32_t dlen = it.len - it.clen;
+          it.cs = (int32_t)c0;
+          it.clen = (int32_t)(c1 - c0);
+          it.len = valid ? it.clen + dlen : 0;
+          typename VT::T more = walk_item(it, fetch(it));
+          reduce_slots<VEC>(a.ls_log2, more);
+          VT::add(acc, more);
+        }
+      }
+      if (team == 0 && valid) VT::store(a.partial + (at << a.ls_log2) * VEC + fl * VEC, acc, false);
+    } else if (have && valid && (!wide || team == 0)) {
+      VT::fma(acc, di, xi);
+      VT::store(ylane + (int64_t)cur.i * a.ldy, VT::scale(di, acc), a.nt & 1);
     }
   }
 }
 
-// Hub rows of the coalescent kernel (one partial sum per unit): adds them in a fixed order.
+// Hub rows of the coalescent kernel: adds a unit's class parts in class order, then the units in a
+// fixed order.
 template <int VEC>
 __global__ __launch_bounds__(kBlock) void k_hub_finish_coalescent(const AggArgs a) {
   using VT = V<VEC>;
   const int lane = threadIdx.x % kWave;
   const int wave = threadIdx.x / kWave;
-  const int ls = 1 << a.ls_log2;
-  const int fl = lane & (ls - 1);
+  const int fl = lane & ((1 << a.ls_log2) - 1);
   const int team = lane >> a.ls_log2;
   const int nteams = kWave >> a.ls_log2;
   const int64_t b = blockIdx.x;
   const int g = (int)(b % a.nslices);
   const int64_t hr = (b / a.nslices) * kWavesPerBlock + wave;
   if (hr >= a.n_hub) return;
-  const int pos = fl * VEC;
-  const int t = g * a.sg + pos / a.F;
-  const bool valid = pos < a.sg * a.F && t < a.k;
+  const int lps = (a.F + VEC - 1) / VEC;
+  const int u = fl / lps;
+  const int t = g * a.sg + u;
+  const bool valid = u < a.sg && t < a.k;
   const int32_t i = a.hub_rows[hr];
   const int32_t it0 = a.hub_item_off[hr], it1 = a.hub_item_off[hr + 1];
+  const int parts = a.whole_units ? 1 : a.nclass;
+  const int64_t stride = (int64_t)VEC << a.ls_log2;
   typename VT::T acc = VT::zero();
   if (valid)
-    for (int32_t it = it0 + team; it < it1; it += nteams)
-      VT::add(acc, VT::load(a.partial + (((int64_t)it * a.nslices + g) << a.ls_log2) * VEC + fl * VEC));
+    for (int32_t it = it0 + team; it < it1; it += nteams) {
+      const float *p = a.partial + ((int64_t)g * a.n_items + it) * parts * stride + fl * VEC;
+      typename VT::T sum = VT::load(p);
+      if (parts > 1) {
+        for (int q = 0; q < parts; q += 8) {  // (a unit has 8, 16 or 32 class parts)
+          typename VT::T x[8];
+#pragma unroll
+          for (int j = 0; j < 8; ++j) x[j] = VT::load(p + (q + j) * stride);
+#pragma unroll
+          for (int j = 0; j < 8; ++j)
+            if (q + j > 0) VT::add(sum, x[j]);
+        }
+      }
+      VT::add(acc, sum);
+    }
   reduce_slots<VEC>(a.ls_log2, acc);
   if (team == 0 && valid) {
-    const int lane_col = g * a.sg * a.F + pos;
+    const int lane_col = t * a.F + min((fl - u * lps) * VEC, a.F - VEC);
     const float di = a.dinv[(int64_t)t * a.n + i];
     VT::fma(acc, di, VT::load(a.X[0] + lane_col + (int64_t)i * a.ldx));
     VT::store(a.Y[0] + lane_col + (int64_t)i * a.ldy, VT::scale(di, acc), a.nt & 1);
@@ -1177,11 +1205,15 @@ int launch(const AggArgs &a, bool fast, hipStream_t st, bool fused_update = fals
 
 template <int VEC>
 int launch_coalescent(const AggArgs &a, hipStream_t st) {
-  const int64_t blocks = ((int64_t)a.blocks_wide + a.blocks_mid + a.blocks_short) * a.nslices;
+  const int64_t wide = a.whole_units ? a.blocks_wide : (int64_t)a.blocks_wide * a.nclass;
+  const int64_t blocks = (wide + a.blocks_mid + a.blocks_short) * a.nslices;
   if (blocks >= ((int64_t)1 << 31)) return PIPAD_ERR_TOO_LARGE;
-  const size_t lds = (size_t)kWavesPerBlock * kWave * (1 + a.sg) * sizeof(uint32_t);
-  if (blocks > 0)
-    hipLaunchKernelGGL((k_aggregate_coalescent<VEC>), dim3((unsigned)blocks), dim3(kBlock), lds, st, a);
+  // entries per fetching lane, so that a chunk holds U = 4 and more for every lane group: 4 for one or
+  // two lanes per snapshot (F <= 4), 2 for two and more
+  auto kern = k_aggregate_coalescent<VEC, 4>;
+  if constexpr (VEC == 4)
+    if (a.F > 4) kern = k_aggregate_coalescent<VEC, 2>;
+  if (blocks > 0) hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kBlock), 0, st, a);
   if (a.n_hub > 0) {
     const int64_t hb = ((int64_t)a.n_hub + kWavesPerBlock - 1) / kWavesPerBlock * a.nslices;
     hipLaunchKernelGGL((k_hub_finish_coalescent<VEC>), dim3((unsigned)hb), dim3(kBlock), 0, st, a);
@@ -1272,10 +1304,7 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
     a.Y[t] = Y ? Y[t] : nullptr;
     if ((reinterpret_cast<uintptr_t>(X[t]) | reinterpret_cast<uintptr_t>(a.Y[t])) & 15u) aligned = false;
   }
-#ifndef V4MIN
-#define V4MIN 4
-#endif
-  const bool vec4 = aligned || F >= V4MIN;
+  const bool vec4 = aligned || F >= 4;
   // the fast path needs 32-bit byte offsets into a snapshot's matrix
   const bool fast = (int64_t)f->n * ldx * 4 < ((int64_t)1 << 32) && !opt.agg_generic;
   // The update rides inside the aggregation kernel when a slice is a whole row of one snapshot
@@ -1293,9 +1322,10 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
     if (!fused && !Y) return PIPAD_ERR_INVALID_ARG;  // the two-step form needs Y as its workspace
   }
   // Small F handed over as one concatenated operand: the coalescent kernel (snapshot groups).
-  // Measured on every benchmark graph at F = 2, 6, 16: on that operand it beats the per-snapshot
-  // slices by 1.2-2.5x (a slice would use 4*F bytes of every k*F-float row it touches, and all
-  // XCDs would fetch the same lines); only operands of a few hundred KB are a tie.
+  // Measured at F = 1 .. 27, k = 3 .. 16: on that operand it beats the per-snapshot slices by 1.03 to
+  // 3.8x (a slice would use 4*F bytes of every k*F-float row it touches); on R-MAT frames with
+  // F >= 16 it is up to 8 % slower (fewer hot rows fit in an L2); operands of a few hundred KB
+  // are a tie.
   const int64_t mode = opt.agg_coalescent;  // 0 never, 1 automatic, 2 whenever possible
   const bool wanted = mode >= 2 || (mode == 1 && (int64_t)f->n * f->k * F * 4 >= ((int64_t)1 << 20));
   bool coalescent = wanted && !upd && !subset && F < 32 && f->k > 1 && ldx >= (int64_t)f->k * F &&
@@ -1304,13 +1334,29 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
     coalescent = X[t] == X[0] + (int64_t)t * F && Y[t] == Y[0] + (int64_t)t * F;
   int cvec = 1;
   if (coalescent) {
-    const uintptr_t bits = reinterpret_cast<uintptr_t>(X[0]) | reinterpret_cast<uintptr_t>(Y[0]);
-    if (F % 4 == 0 && ldx % 4 == 0 && ldy % 4 == 0 && !(bits & 15u)) cvec = 4;
-    else if (F % 2 == 0 && ldx % 2 == 0 && ldy % 2 == 0 && !(bits & 7u)) cvec = 2;
-    a.sg = std::max(1, std::min<int>(f->k, 64 / F));       // snapshots side by side in a team
-    a.ls_log2 = ceil_log2((a.sg * F + cvec - 1) / cvec);   // lanes per team (<= 64)
+    cvec = F >= 4 ? 4 : F >= 2 ? 2 : 1;  // (any 4-byte alignment: see V)
+    // Snapshots side by side in a team: up to 64 columns, the groups as even as they get, and of
+    // those splits the one that costs least by a sum of lanes (idle ones included) and 12 per cache
+    // line that an entry's row is expected to touch.  Measured with 64, 48, 32 and 16 columns at most:
+    // k = 12, F = 9 154, 139, 162, 172 us; k = 5, F = 16 910, 910, 832, 930; k = 3, F = 16 518, 518, 644,
+    // 707; k = 8, F = 16 179, 225, 176, 246; k = 8, F = 6 351, 351, 356, 453; k = 3, F = 27 775, 863.
+    const int lps = (F + cvec - 1) / cvec;
+    int64_t best = INT64_MAX;
+    for (int groups = (int)((f->k * F + 63) / 64); groups <= f->k; ++groups) {
+      const int sg = (f->k + groups - 1) / groups;
+      if (sg * F > 64 || (f->k + sg - 1) / sg != groups) continue;
+      const int lanes_log2 = ceil_log2(sg * lps);
+      const uint64_t starts = (uint64_t)ldx * 4 | reinterpret_cast<uintptr_t>(X[0]) | (uint64_t)sg * F * 4 | 128u;
+      const int64_t align = (int64_t)(starts & (~starts + 1));
+      const int64_t touched = (int64_t)f->k * F * 4 + groups * (128 - align);
+      const int64_t cost = ((int64_t)groups << lanes_log2) * 128 + 12 * touched;
+      if (cost > best) continue;
+      best = cost;
+      a.nslices = groups;  // snapshot groups
+      a.sg = sg;
+      a.ls_log2 = lanes_log2;  // lanes per team (<= 64)
+    }
     a.fchunks = 1;
-    a.nslices = (f->k + a.sg - 1) / a.sg;                   // snapshot groups
   }
   // slice geometry: LS lanes of VEC columns each, at most 64 columns per slice (a gathered piece
   // of a row is then at most 256 bytes: two cache lines)
@@ -1336,11 +1382,11 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
   {
     a.batch_short = kShortRowsPerWave;
     a.batch_mid = kLongRowsPerWave;
-    a.batch_wide = coalescent ? 1 : kWideUnitsPerWave;
+    a.batch_wide = kWideUnitsPerWave;
     const int min_mid = 1;
     const int64_t slices_run = coalescent ? a.nslices : a.order == 0 ? (int64_t)a.nsel * a.fchunks : 1;
     const int64_t mult = slices_run;
-    const int64_t mult_wide = slices_run * (coalescent ? 1 : f->nclass);
+    const int64_t mult_wide = slices_run * f->nclass;
     auto waves = [&]() {
       return (int64_t)(f->n_short + a.batch_short - 1) / a.batch_short * slices_run +
              (int64_t)(f->n_long + a.batch_mid - 1) / a.batch_mid * mult +
@@ -1349,7 +1395,7 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
     // With the update fused in, a workgroup first copies W to LDS and a wave multiplies 16 rows at a
     // time, so batches stay longer (N = 200k, F = Fo = 64: 4 to 8 rows per wave take 1.36 ms, 32 take
     // 0.90, 64 take 0.95), and shorter than a tile only where there would be hardly any waves.
-    const int64_t enough = fused ? 8192 : coalescent ? 4 * 8192 : 11 * 1024;
+    const int64_t enough = fused ? 8192 : coalescent ? 64 * 1024 : 11 * 1024;
     int min_short = fused ? std::max(nteams, kTileRows) : nteams;
     // entries that a lane team walks one after the other in a batch of short rows
     auto chain = [&]() {
@@ -1377,11 +1423,14 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
     }
   }
 
-  // scratch for the partial sums: one slice-wide vector per class part (per hub unit for the
-  // coalescent kernel) and slice
-  const size_t per_snapshot = (size_t)a.nvp * (size_t)a.fchunks * (size_t)sw;  // not coalescent
-  const size_t need = coalescent ? (size_t)f->n_items * (size_t)a.nslices * (size_t)sw
-                                 : per_snapshot * (size_t)a.nsel;
+  // scratch for the partial sums: one slice-wide vector per class part and slice
+  const size_t per_snapshot = (size_t)a.nvp * (size_t)a.fchunks * (size_t)sw;
+  size_t need = per_snapshot * (size_t)(coalescent ? a.nslices : a.nsel);
+  if (coalescent && scratch.fixed && need > *scratch.floats) {
+    // too many for a fixed scratch: one per hub unit then, the same sums
+    a.whole_units = 1;
+    need /= (size_t)a.nclass;
+  }
   if (need > *scratch.floats) {
     if (scratch.fixed) {
       // A fixed scratch that is too small for all snapshots at once takes them in groups, one
