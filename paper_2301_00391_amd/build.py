@@ -4,7 +4,7 @@
 
 -D passes a macro to every source: the measurement builds the profiles are taken with, e.g.
 -D PIPAD_PARTS_MASK=1 (only the class parts of the hub rows run: results incomplete),
--D PIPAD_AGG_DEPTH=8, -D PIPAD_NO_ROW_ORDER.  -o writes the library somewhere else than in-tree;
+-D PIPAD_AGG_DEPTH=2, -D PIPAD_NO_ROW_ORDER.  -o writes the library somewhere else than in-tree;
 the binding loads the file the environment variable PIPAD_LIBRARY names instead of the in-tree one.
 """
 from __future__ import annotations
