@@ -12,6 +12,7 @@ The names mirror ``include/pipad.h``:
 from __future__ import annotations
 
 import ctypes
+import itertools
 import os
 from typing import List, Optional, Sequence, Tuple, Union
 
@@ -151,20 +152,20 @@ Snapshot = Tuple[torch.Tensor, torch.Tensor]  # (rowptr int32[n+1], colidx int32
 class Frame:
     """Owner of one ``pipad_frame_t``.  Built by :func:`frame_build_overlap`."""
 
-    def __init__(self, handle: int, n: int, k: int, device, buffers: list, callback=None,
+    def __init__(self, handle: int, n: int, k: int, device, buffers: list, key: Optional[int] = None,
                  stream=None):
         self._h = handle
         self.n, self.k, self.device = n, k, device
         self._index = _device_index(device)
         self._buffers = buffers  # torch tensors handed to the library through the allocator
-        self._callback = callback  # the library may call it again (aggregate scratch)
+        self._key = key  # names the buffers to the library's callback, which it may use again (aggregate scratch)
         # torch's allocator hands memory out, and takes it back, in the order of the stream that
         # was current at the allocation; work on any other stream has to be waited for in close()
         self._alloc_stream = _current_raw_stream(self._index)
         self._other_streams = {}
         self._temp = None
         built_on = self._stream(stream)
-        if callback is not None:
+        if key is not None:
             # the build's temporaries can go back to the allocator as soon as the build's kernels have
             # run: at once where its order is that of the build's stream, else behind an event
             ptr, size = _vp(), ctypes.c_size_t()
@@ -205,11 +206,8 @@ class Frame:
             load_library().pipad_frame_destroy(self._h)
             self._h = None
             self._temp = None
-            # in place: the allocator callback's closure holds the same list, and ctypes callback
-            # objects sit in a reference cycle that only the garbage collector breaks - rebinding
-            # the attribute would keep every buffer alive until its next run
+            _owners.pop(self._key, None)
             self._buffers.clear()
-            self._callback = None
 
     def __del__(self):
         try:
@@ -247,34 +245,52 @@ class Frame:
         return _copy_from_device(ptr.value, self.k * self.n, torch.float32, self.device).view(self.k, self.n)
 
 
-def _make_allocator(allocator: str, device):
-    """(list that keeps the handed-out tensors alive, C callback or None)."""
-    buffers: list = []
-    if allocator == "library":
-        return buffers, None
-    if allocator != "torch":
-        raise ValueError("allocator must be 'torch' or 'library'")
+# The callback through which the library takes memory from PyTorch's caching allocator, and the frames'
+# buffers by the key it is called with.  One callback for all frames: a ctypes callback sits in a
+# reference cycle, and with one per frame the garbage collector walked the whole program every few
+# hundred frames (10 us per build, of 52, for frames of a thousand nodes).
+_owners: dict = {}  # key -> (list that keeps the handed-out tensors alive, device)
+_next_key = itertools.count(1).__next__
 
-    def _alloc(nbytes, _ctx):
-        try:
-            buf = torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
-            buffers.append(buf)
-            return buf.data_ptr()
-        except Exception:  # out of memory -> NULL -> PIPAD_ERR_ALLOC
-            return None
-    return buffers, ALLOC_FN(_alloc)
+
+def _allocate(nbytes, key):
+    try:
+        buffers, device = _owners[key]
+        buf = torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
+        buffers.append(buf)
+        return buf.data_ptr()
+    except Exception:  # out of memory -> NULL -> PIPAD_ERR_ALLOC
+        return None
+
+
+_allocate_callback = ALLOC_FN(_allocate)
+_ALLOCATE = ctypes.cast(_allocate_callback, _vp)
+
+
+def _build(index: int, n: int, k: int, device, allocator: str, stream, fn, *args) -> Frame:
+    """The frame that fn(*args, allocator, its context, stream, result) makes."""
+    if allocator not in ("torch", "library"):
+        raise ValueError("allocator must be 'torch' or 'library'")
+    buffers: list = []
+    key = None
+    if allocator == "torch":
+        key = _next_key()
+        _owners[key] = (buffers, device)
+    out = _vp()
+    raw = int(stream.cuda_stream) if stream is not None else _current_raw_stream(index)
+    try:
+        _check(_on_device(index, fn, *args, _ALLOCATE if key is not None else None, key, raw, ctypes.byref(out)))
+    except BaseException:
+        _owners.pop(key, None)
+        raise
+    return Frame(out.value, n, k, device, buffers, key, stream)
 
 
 def frame_transpose(frame: Frame, allocator: str = "torch", stream=None) -> Frame:
     """pipad_frame_transpose: the frame of the transposed patterns with the same D^-1/2; aggregating
     with it applies the transposed operator (the backward pass for directed patterns)."""
-    lib = load_library()
-    buffers, cb = _make_allocator(allocator, frame.device)
-    out = _vp()
-    raw = int(stream.cuda_stream) if stream is not None else _current_raw_stream(frame._index)
-    _check(_on_device(frame._index, lib.pipad_frame_transpose, frame._h,
-                      ctypes.cast(cb, _vp) if cb is not None else None, None, raw, ctypes.byref(out)))
-    return Frame(out.value, frame.n, frame.k, frame.device, buffers, cb, stream)
+    return _build(frame._index, frame.n, frame.k, frame.device, allocator, stream,
+                  load_library().pipad_frame_transpose, frame._h)
 
 
 def frame_build_overlap(snapshots: Sequence[Snapshot], validate: bool = False,
@@ -290,22 +306,19 @@ def frame_build_overlap(snapshots: Sequence[Snapshot], validate: bool = False,
     rp0 = snapshots[0][0]
     n = rp0.numel() - 1
     device = rp0.device
+    if not rp0.is_cuda:
+        raise ValueError("snapshots must be contiguous int32 tensors on one GPU")
+    index = _device_index(device)
     int32 = torch.int32
     descr = []
     for rp, col in snapshots:
-        if rp.dtype != int32 or not rp.is_cuda or not rp.is_contiguous() or rp.device != device or \
-                col.dtype != int32 or not col.is_cuda or not col.is_contiguous() or col.device != device:
+        if rp.dtype is not int32 or rp.get_device() != index or not rp.is_contiguous() or \
+                col.dtype is not int32 or col.get_device() != index or not col.is_contiguous():
             raise ValueError("snapshots must be contiguous int32 tensors on one GPU")
         nnz = col.numel()
         descr.append((rp.numel() - 1, nnz, rp.data_ptr(), col.data_ptr() if nnz else None))
-    arr = (_Csr * k)(*descr)
-    buffers, cb = _make_allocator(allocator, device)
-    out = _vp()
-    index = _device_index(device)
-    raw = int(stream.cuda_stream) if stream is not None else _current_raw_stream(index)
-    _check(_on_device(index, lib.pipad_frame_build_overlap, n, k, arr, VALIDATE if validate else 0,
-                      ctypes.cast(cb, _vp) if cb is not None else None, None, raw, ctypes.byref(out)))
-    return Frame(out.value, n, k, device, buffers, cb, stream)
+    return _build(index, n, k, device, allocator, stream, lib.pipad_frame_build_overlap,
+                  n, k, (_Csr * k)(*descr), VALIDATE if validate else 0)
 
 
 Features = Union[torch.Tensor, Sequence[torch.Tensor]]
