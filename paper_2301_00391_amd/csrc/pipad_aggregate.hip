@@ -360,6 +360,29 @@ __device__ __forceinline__ void walk(const Lists &l, int32_t cs, int32_t clen, i
 constexpr int kTileRows = 16;
 constexpr int kTileStride = 68;  // floats per tile row: 64 + 4, keeps 16-byte alignment
 
+// Copies rows [0, rows) of W (zeros from row F on) and, as row `rows`, the bias, for columns col0 ..
+// col0 + cols - 1 (zeros from Fo on); four elements per thread are requested together (one after
+// the other they cost a round trip to the L2 each).
+__device__ __forceinline__ void stage_weights(const AggArgs &a, float *lds, int rows, int cols, int col0, int ws) {
+  constexpr int B = 4;
+  const int total = rows * cols;
+  for (int base = threadIdx.x; base < total; base += B * kBlock) {
+    float v[B];
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      const int idx = min(base + u * kBlock, total - 1), kk = idx / cols;
+      v[u] = a.W[(int64_t)min(kk, a.F - 1) * a.ldw + min(col0 + idx - kk * cols, a.Fo - 1)];
+    }
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      const int idx = base + u * kBlock, kk = idx / cols, o = idx - kk * cols;
+      if (idx < total) lds[kk * ws + o] = kk < a.F && col0 + o < a.Fo ? v[u] : 0.f;
+    }
+  }
+  for (int o = threadIdx.x; o < cols; o += kBlock)
+    lds[rows * ws + o] = a.bias && col0 + o < a.Fo ? a.bias[col0 + o] : 0.f;
+}
+
 struct Sink {
   float *tile;        // this wave's [kTileRows][kTileStride]
   int32_t *rows;      // this wave's [kTileRows] row ids
@@ -806,96 +829,108 @@ __global__ __launch_bounds__(kBlock) void k_update(const AggArgs a) {
 }
 
 // The same multiplication with the weights resident in LDS: a workgroup copies W's rows (all K of
-// them, zero-padded to a multiple of 64) for the `cbw` output columns of its column block
-// (blockIdx.y) once and its waves then take kUpdTiles row tiles each.  A wave stages 16 rows x 64
-// columns of Y_t at a time in its LDS tile (coalesced row reads), feeds them to the MFMAs in the
-// k order of the fused kernel, and keeps the 16 x cbw results in registers across the K chunks.
-constexpr int kUpdTiles = 8;       // row tiles per wave
+// them, zero-padded to a multiple of 4) for the `cbw` output columns of its column block (blockIdx.y)
+// once and its waves then take per_wave row tiles each.  The product is formed transposed, W^T Y_t^T:
+// lane (m, g) supplies row m of the tile with four consecutive columns per 16-byte load (step j of a
+// block of 16 columns multiplies k = 4 g + j; what is left of K past the last block goes one column per
+// lane, k = 4 j + g), the next 64 columns on their way meanwhile, and gets back four consecutive columns
+// of H for one 16-byte store per accumulator tile.
+// Bound: the stream of Y and H.  (Rows of Y staged through an LDS tile 64 columns at a time, K padded to
+// a multiple of 64, dword stores, W copied one element after the other and 8 tiles per wave whatever
+// their number: N = 150k, k = 3, F = 128, Fo = 40 123 us, now 77 (3.9 TB/s); 39k, k = 8, F = 2, Fo = 128
+// 106, now 45; 1.7k, k = 4, F = 64, Fo = 10 18, now 6.)  An instance for every number of accumulator
+// tiles: with a test per tile instead the compiler hoists the operands of all of them (256 registers and
+// more), and without the fence below it takes W into registers ahead of the loop.
+constexpr int kUpdTiles = 8;       // row tiles per wave at most
 constexpr int kUpdMaxCols = 128;   // output columns per column block (8 accumulator tiles)
+constexpr int kUpdPad = 4;         // floats behind an LDS row of W: the lane groups' rows lie 16 banks apart
 
-template <int NT>  // 16-column accumulator tiles a wave keeps: NT * 16 >= cbw
-__global__ __launch_bounds__(kBlock) void k_update_resident(const AggArgs a, int cbw, int kpad) {
+template <int NT>  // 16-column accumulator tiles a wave keeps
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_update_resident(const AggArgs a, int kpad, int per_wave) {
+  constexpr int cbw = 16 * NT;
+  using VT = V<4>;
   extern __shared__ __align__(16) float upd_lds[];
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   const int m = lane & 15, g = lane >> 4;
-  const int ws = cbw + 1;
+  const int ws = cbw + kUpdPad;
   const int col0 = blockIdx.y * cbw;
-  for (int idx = threadIdx.x; idx < kpad * cbw; idx += kBlock) {
-    const int kk = idx / cbw, o = idx - kk * cbw;
-    upd_lds[kk * ws + o] =
-        (kk < a.F && col0 + o < a.Fo) ? a.W[(int64_t)kk * a.ldw + col0 + o] : 0.f;
-  }
-  for (int o = threadIdx.x; o < cbw; o += kBlock)
-    upd_lds[kpad * ws + o] = (a.bias && col0 + o < a.Fo) ? a.bias[col0 + o] : 0.f;
-  float *tile = upd_lds + (((kpad + 1) * ws + 3) & ~3) + wave * kTileRows * kTileStride;
+  stage_weights(a, upd_lds, kpad, cbw, col0, ws);
   __syncthreads();
   const int64_t tiles = ((int64_t)a.n + 15) / 16;
-  const int64_t first = ((int64_t)blockIdx.x * kWavesPerBlock + wave) * kUpdTiles;
-  const int64_t last = min(first + kUpdTiles, tiles * a.k);
-  const int chunks = kpad / 64;
-  // 16 rows x 64 columns of Y_t, lane = column: requested one (tile, chunk) ahead, so that the
-  // loads fly while the matrix cores work on the previous piece
-  // (the snapshot index is the same for the whole wave: said so explicitly, so that the matrix
-  // pointer is fetched once per tile through the scalar unit, not per load through a vector
-  // register; out-of-range elements are read from a clamped address and zeroed afterwards, so
-  // that the 16 loads go out together instead of one per branch)
-  auto request = [&](int64_t id, int kc, float (&v)[kTileRows]) {
+  const int64_t first = ((int64_t)blockIdx.x * kWavesPerBlock + wave) * per_wave;
+  const int64_t last = min(first + per_wave, tiles * a.k);
+  const int blocks = a.F / 16;                      // whole blocks of 16 columns
+  const int tail = (a.F - 16 * blocks + 3) / 4;     // steps behind them
+  const int chunks = max((blocks + 3) / 4, 1);
+  // four blocks of this lane's row (those past the last whole one repeat it; without a whole one they
+  // are not there) and, with the last chunk, the tail
+  auto request = [&](int64_t id, int chunk, float4 (&v)[4], float (&tv)[4]) __attribute__((always_inline)) {
     const int t = __builtin_amdgcn_readfirstlane((int)(id / tiles));
-    const float *yt = a.Y[t];
-    const int64_t row0 = (id - t * tiles) * 16;
-    const int col = kc * 64 + lane;
-    const float *src = yt + min(col, a.F - 1);
+    const float *src = a.Y[t] + min((id - t * tiles) * 16 + m, (int64_t)a.n - 1) * a.ldy;
+    if (blocks > 0)
 #pragma unroll
-    for (int j = 0; j < kTileRows; ++j) v[j] = src[min(row0 + j, (int64_t)a.n - 1) * a.ldy];
+      for (int b = 0; b < 4; ++b) v[b] = VT::load(src + 16 * min(4 * chunk + b, blocks - 1) + 4 * g);
+    if (tail > 0 && chunk == chunks - 1)
 #pragma unroll
-    for (int j = 0; j < kTileRows; ++j)
-      if (!(row0 + j < a.n && col < a.F)) v[j] = 0.f;
+      for (int j = 0; j < 4; ++j) tv[j] = src[min(16 * blocks + 4 * j + g, a.F - 1)];
   };
-  float nxt[kTileRows];
-  if (first < last) request(first, 0, nxt);
+  float4 nxt[4] = {};
+  float nxt_tail[4] = {};
+  if (first < last) request(first, 0, nxt, nxt_tail);
   for (int64_t id = first; id < last; ++id) {
     const int t = __builtin_amdgcn_readfirstlane((int)(id / tiles));
-    float *ht = a.H[t];
-    const int64_t row0 = (id - t * tiles) * 16;
+    const int64_t row = (id - t * tiles) * 16 + m;
+    asm volatile("" ::: "memory");
     mfma_f4 d[NT];
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) d[nt] = mfma_f4{0.f, 0.f, 0.f, 0.f};
-    for (int kc = 0; kc < chunks; ++kc) {
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");  // earlier readers of the tile
+    for (int chunk = 0; chunk < chunks; ++chunk) {
+      float4 cur[4];
+      float cur_tail[4];
 #pragma unroll
-      for (int j = 0; j < kTileRows; ++j) tile[j * kTileStride + lane] = nxt[j];
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      if (kc + 1 < chunks) request(id, kc + 1, nxt);
-      else if (id + 1 < last) request(id + 1, 0, nxt);
-      float av[16];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float4 v = *reinterpret_cast<const float4 *>(tile + m * kTileStride + g * 16 + 4 * q);
-        av[4 * q + 0] = v.x; av[4 * q + 1] = v.y; av[4 * q + 2] = v.z; av[4 * q + 3] = v.w;
+      for (int b = 0; b < 4; ++b) {
+        cur[b] = nxt[b];
+        cur_tail[b] = nxt_tail[b];
       }
+      if (chunk + 1 < chunks) request(id, chunk + 1, nxt, nxt_tail);
+      else if (id + 1 < last) request(id + 1, 0, nxt, nxt_tail);
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        if (16 * nt < cbw) {
-          const float *wcol = upd_lds + (kc * 64 + g * 16) * ws + 16 * nt + m;
-          float bv[16];
+      for (int b = 0; b < 4; ++b) {
+        __builtin_amdgcn_sched_barrier(0);  // (all blocks' operands at once would take too many registers)
+        if (4 * chunk + b >= blocks) break;
+        const float y[4] = {cur[b].x, cur[b].y, cur[b].z, cur[b].w};
+        const float *w = upd_lds + (64 * chunk + 16 * b + 4 * g) * ws + m;
 #pragma unroll
-          for (int ks = 0; ks < 16; ++ks) bv[ks] = wcol[ks * ws];
+        for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-          for (int ks = 0; ks < 16; ++ks)
-            d[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[ks], bv[ks], d[nt], 0, 0, 0);
+          for (int j = 0; j < 4; ++j)
+            d[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[j * ws + 16 * nt], y[j], d[nt], 0, 0, 0);
+      }
+      if (chunk == chunks - 1)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          if (j >= tail) break;
+          const int kk = 16 * blocks + 4 * j + g;
+          const float y = kk < a.F ? cur_tail[j] : 0.f;
+          const float *w = upd_lds + kk * ws + m;
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt)
+            d[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[16 * nt], y, d[nt], 0, 0, 0);
         }
-      }
     }
+    float *out = a.H[t] + row * a.ldh + col0 + 4 * g;
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
-      const int col = col0 + 16 * nt + m;
-      if (16 * nt < cbw && col < a.Fo) {
-        const float b = upd_lds[kpad * ws + 16 * nt + m];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int64_t orow = row0 + 4 * g + r;
-          if (orow < a.n) ht[orow * a.ldh + col] = d[nt][r] + b;
-        }
+      const float *b = upd_lds + kpad * ws + 16 * nt + 4 * g;
+      const float4 h = make_float4(d[nt][0] + b[0], d[nt][1] + b[1], d[nt][2] + b[2], d[nt][3] + b[3]);
+      const int left = a.Fo - (col0 + 16 * nt + 4 * g);  // columns from here on
+      if (row >= a.n) continue;
+      if (left >= 4) {
+        VT::store(out + 16 * nt, h, false);
+      } else {
+        if (left > 0) out[16 * nt] = h.x;
+        if (left > 1) out[16 * nt + 1] = h.y;
+        if (left > 2) out[16 * nt + 2] = h.z;
       }
     }
   }
@@ -1483,18 +1518,22 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
   const int rc = vec4 ? launch<4>(a, fast, st) : launch<1>(a, fast, st);
   if (rc != PIPAD_OK || !upd) return rc;
   const int64_t tiles = ((int64_t)f->n + 15) / 16 * f->k;
-  // weights resident in LDS when a column block of them fits (40 KB, tiles on top: under 64 KB), else straight from memory
-  const int kpad = (F + 63) / 64 * 64;
+  // weights resident in LDS when a column block of them fits (40 KB: four workgroups per CU), else straight
+  // from memory
+  const int kpad = (F + 3) / 4 * 4;
   int cbw = std::min((a.Fo + 15) / 16 * 16, kUpdMaxCols);
-  while (cbw > 16 && (size_t)(kpad + 1) * (cbw + 1) * 4 > (40u << 10)) cbw -= 16;
-  const size_t w_bytes = (((size_t)(kpad + 1) * (cbw + 1) + 3) & ~(size_t)3) * 4;
-  if (w_bytes <= (40u << 10)) {
-    const size_t lds = w_bytes + (size_t)kWavesPerBlock * kTileRows * kTileStride * 4;
-    const int64_t per_block = (int64_t)kWavesPerBlock * kUpdTiles;
-    const dim3 grid((unsigned)((tiles + per_block - 1) / per_block), (unsigned)((a.Fo + cbw - 1) / cbw));
-    auto kern = cbw <= 16 ? k_update_resident<1> : cbw <= 32 ? k_update_resident<2>
-              : cbw <= 64 ? k_update_resident<4> : k_update_resident<8>;
-    hipLaunchKernelGGL(kern, grid, dim3(kBlock), lds, st, a, cbw, kpad);
+  while (cbw > 16 && (size_t)(kpad + 1) * (cbw + kUpdPad) * 4 > (40u << 10)) cbw -= 16;
+  const size_t lds = (size_t)(kpad + 1) * (cbw + kUpdPad) * 4;
+  if (lds <= (40u << 10)) {
+    const int64_t col_blocks = (a.Fo + cbw - 1) / cbw;
+    // as many tiles per wave as leave 16 waves for every CU
+    const int per_wave = (int)std::clamp<int64_t>(tiles * col_blocks / 4096, 1, kUpdTiles);
+    const int64_t per_block = (int64_t)kWavesPerBlock * per_wave;
+    const dim3 grid((unsigned)((tiles + per_block - 1) / per_block), (unsigned)col_blocks);
+    void (*const kern[])(AggArgs, int, int) = {k_update_resident<1>, k_update_resident<2>, k_update_resident<3>,
+                                               k_update_resident<4>, k_update_resident<5>, k_update_resident<6>,
+                                               k_update_resident<7>, k_update_resident<8>};
+    hipLaunchKernelGGL(kern[cbw / 16 - 1], grid, dim3(kBlock), lds, st, a, kpad, per_wave);
   } else {
     hipLaunchKernelGGL(k_update, dim3((unsigned)((tiles + kWavesPerBlock - 1) / kWavesPerBlock)),
                        dim3(kBlock), 0, st, a);
