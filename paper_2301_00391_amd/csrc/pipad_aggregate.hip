@@ -541,13 +541,9 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
     sink.cnt = 0;  // (class parts of hub units end in partial sums: no use for W)
   } else if (UPD) {
     const int K = 4 << a.ls_log2, ws = a.Fo + 1;
-    for (int idx = threadIdx.x; idx < K * a.Fo; idx += kBlock) {
-      const int kk = idx / a.Fo, o = idx - kk * a.Fo;
-      upd_lds[kk * ws + o] = kk < a.F ? a.W[(int64_t)kk * a.ldw + o] : 0.f;
-    }
-    // row K: the bias (a load from global memory inside the flush would make the wave wait for
-    // every gather it has in flight)
-    for (int o = threadIdx.x; o < a.Fo; o += kBlock) upd_lds[K * ws + o] = a.bias ? a.bias[o] : 0.f;
+    // (row K: the bias; a load from global memory inside the flush would make the wave wait for every gather
+    // it has in flight)
+    stage_weights(a, upd_lds, K, a.Fo, 0, ws);
     const int w_floats = ((K + 1) * ws + 3) & ~3;
     float *tiles = upd_lds + w_floats;
     sink.wl = upd_lds;
