@@ -63,7 +63,9 @@ typedef struct pipad_frame pipad_frame_t;
 
 /* Optional device allocator.  Must return memory of at least `bytes` bytes, aligned to 256 bytes,
  * usable on `stream`'s device, or NULL on failure.  Memory obtained through the callback is owned
- * by the caller and must stay valid until pipad_frame_destroy(); the library never frees it.  The
+ * by the caller and must stay valid until pipad_frame_destroy(); the library never frees it.  What
+ * a pipad_frame_build_overlap or pipad_frame_transpose that fails has obtained is not in use any
+ * more when the call returns (it waits for what it has enqueued) and may go back at once.  The
  * callback and its ctx must stay callable until then too: besides the frame's own buffers it
  * serves the temporaries of the build (which the caller may take back early, see
  * pipad_frame_temporaries) and the scratch buffer of pipad_frame_aggregate. */

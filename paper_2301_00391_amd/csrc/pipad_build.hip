@@ -1446,8 +1446,10 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
   f->alloc = alloc;
   f->alloc_ctx = alloc_ctx;
   void *temp = nullptr;  // temporaries: from the callback (kept by the caller) or hipMalloc'd here
+  bool launched = false;  // something that uses the frame's memory may be running
   // every exit path below goes through fail() or the success return
   auto fail = [&](int code) {
+    if (launched) drain(st);
     if (temp && !alloc) (void)hipFree(temp);
     release(f);
     return code;
@@ -1519,6 +1521,7 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
     if (rc__ != 0) return fail(rc__);                     \
   } while (0)
 
+  launched = true;
   if ((flags & PIPAD_VALIDATE) && n > 0) {
     PIPAD_TRY(hipMemsetAsync(dflags, 0, 256, st));
     hipLaunchKernelGGL(k_validate, grid1((int64_t)k * n, kWavesPerBlock), dim3(kBlock), 0, st, s, n,

@@ -164,6 +164,12 @@ inline void release(pipad_frame *f) {
   delete f;
 }
 
+// A build that gives up hands its memory back at once (hipFree, or the caller's allocator, which may
+// give it to anyone): the kernels it has enqueued must have stopped writing to it by then.
+inline void drain(hipStream_t st) {
+  if (hipStreamSynchronize(st) != hipSuccess) (void)hipGetLastError();
+}
+
 inline dim3 grid1(int64_t items, int per_block, int y = 1) {
   return dim3((unsigned)((items + per_block - 1) / per_block), (unsigned)y);
 }

@@ -412,7 +412,9 @@ int transpose_frame(const pipad_frame *f, pipad_alloc_fn alloc, void *alloc_ctx,
   for (int t = 0; t < k; ++t) g->nnz_d[t] = f->nnz_d[t];
   Allocator A{alloc, alloc_ctx, g};
   void *temp = nullptr;
+  bool launched = false;  // something that uses the frame's memory may be running
   auto fail = [&](int code) {
+    if (launched) drain(st);
     if (temp && !alloc) (void)hipFree(temp);
     release(g);
     return code;
@@ -507,6 +509,7 @@ int transpose_frame(const pipad_frame *f, pipad_alloc_fn alloc, void *alloc_ctx,
   if (!temp) return fail(PIPAD_ERR_ALLOC);
   tmp.assign(temp);
 
+  launched = true;
   // (the two copies of D^-1/2 lie next to each other in every frame)
   const size_t dinv_span = (size_t)(f->dinv_nk - f->dinv) + (size_t)k * n;
   if (g->dinv_nk - g->dinv == f->dinv_nk - f->dinv && f->dinv_nk > f->dinv) {
