@@ -1407,9 +1407,13 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
   // Rows per wave: the full batches amortise the per-wave set-up (and let a wave request its next
   // row while it gathers the current one) on big frames; smaller ones get shorter batches, until what
   // runs together - one slice, or all of them when they go side by side - has about 44 waves for
-  // every CU, and a lane team walks no more than some 70 entries one after the other.  Twice to
-  // four times as many waves were slower by 4 to 27 % (N = 20k .. 200k), half as many by as much, and
-  // longer chains by 2 to 4 % (N = 300k .. 500k, whatever the number of waves).
+  // every CU, and a lane team does not walk too many entries one after the other: some 50 where the
+  // short rows hold most of the entries, 70 elsewhere.  Twice to four times as many waves were slower
+  // by 4 to 27 % (N = 20k .. 200k), half as many by as much.  Chains of 70, 50 and 35 (N = 60k .. 1M,
+  // k = 4 and 8): 50 against 70 is 0 to 5 % faster on Chung-Lu frames (N = 500k, k = 8, F = 128, hardly
+  // any overlap: 5233 -> 5042 us; longer than 70: 5284), where the short rows hold 51 to 74 % of the
+  // entries; on R-MAT frames, where they hold 24 to 28 %, it is a tie but for one loss of 3 % (N = 60k,
+  // F = 64), and 35 is up to 5 % slower than 70.
   {
     a.batch_short = kShortRowsPerWave;
     a.batch_mid = kLongRowsPerWave;
@@ -1432,8 +1436,11 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
     auto chain = [&]() {
       return fused || coalescent || f->n_short == 0 ? 0 : f->short_entries * a.batch_short / nteams / f->n_short;
     };
+    int64_t entries = f->nnz_c;  // of a snapshot
+    for (int t = 0; t < f->k; ++t) entries += f->nnz_d[t] / f->k;
+    const int64_t longest_chain = 2 * f->short_entries > entries ? 50 : 70;
     while ((waves() < enough && (a.batch_short > min_short || a.batch_mid > min_mid || a.batch_wide > 1)) ||
-           (chain() > 70 && a.batch_short > min_short)) {
+           (chain() > longest_chain && a.batch_short > min_short)) {
       if (a.batch_short > min_short) a.batch_short >>= 1;
       if (a.batch_mid > min_mid) a.batch_mid >>= 1;
       if (a.batch_wide > 1) a.batch_wide >>= 1;
