@@ -152,8 +152,11 @@ int pipad_frame_shape(const pipad_frame_t *frame, int32_t *n, int32_t *k);
  *   allocator; with the library's own allocator a buffer that is replaced is freed after a
  *   hipDeviceSynchronize).  All other calls only enqueue kernels on `stream`, without host
  *   synchronisation, so they can be recorded into a HIP graph (stream capture) once an eager call
- *   with the same or a larger k*F has sized the scratch; a call that would have to allocate while
- *   `stream` is being captured returns PIPAD_ERR_SCRATCH with nothing enqueued.
+ *   with the same or a larger k*F has sized the scratch, whichever form (one matrix per snapshot,
+ *   concatenated, with the update) either of them has.  A recorded call whose form takes more than
+ *   the eager one left (rows padded to the slice width do) makes do with it, in several launches and
+ *   with the same bits; it returns PIPAD_ERR_SCRATCH, with nothing enqueued, where there is not even
+ *   room for one snapshot.
  *   Two aggregations of the SAME frame must not run concurrently (they share that scratch).
  *   Results are deterministic: same inputs, same bits.
  */
@@ -190,7 +193,9 @@ int pipad_frame_aggregate_subset(pipad_frame_t *frame, int32_t nsel, const int32
  *   k snapshots at once the call goes through the snapshots in groups that fit, one launch after
  *   the other on `stream` (same bits); when it cannot hold one snapshot's it returns
  *   PIPAD_ERR_SCRATCH with nothing enqueued.  (The 1M-node benchmark frame at F = 64: 17 MB per
- *   snapshot, groups of 3.)
+ *   snapshot, groups of 3.)  A concatenated operand of F < 32 takes units * classes * k * F floats,
+ *   and where these do not fit units * k * F (the classes of a unit one after the other: slower,
+ *   same bits).
  *   All calls on one GPU share the array: calls that overlap in time on that GPU (different
  *   streams, or different frames) race on it and give wrong results; calls ordered on one stream
  *   are safe.  Nothing in the array has to be cleared between calls: every partial sum is written

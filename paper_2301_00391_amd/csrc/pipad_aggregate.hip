@@ -956,6 +956,18 @@ struct CoalItem {
   int32_t i, cs, clen, ds, len;  // len: both lists together (0: this lane has nothing to do)
 };
 
+// Where snapshot group g's partial sums of class part `cls` of a hub unit (of the whole unit, where that
+// is summed at once) start, as the place of column 0 of the wide row: the groups one after the other, in
+// each the columns of its snapshots side by side without gaps.  All of them take k * F floats per part,
+// which is no more than a call with the same F and one matrix per snapshot needs: what one call has
+// sized the scratch for, the other can do with.
+__device__ __forceinline__ float *unit_partial(const AggArgs &a, int g, int64_t unit, int cls) {
+  const int64_t parts = a.whole_units ? 1 : a.nclass;
+  const int64_t col0 = (int64_t)g * a.sg * a.F;  // the group's first column
+  const int width = min(a.sg, a.k - g * a.sg) * a.F;
+  return a.partial + col0 * (a.n_items * parts) + (unit * parts + cls) * width - col0;
+}
+
 template <int VEC, int EPL>
 __global__ __launch_bounds__(kBlock) void k_aggregate_coalescent(const AggArgs a) {
   using VT = V<VEC>;
@@ -1113,11 +1125,9 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_coalescent(const AggArgs a
     typename VT::T acc = walk_item(cur, cur_f);
     if (wide) reduce_slots<VEC>(a.ls_log2, acc);
     if (split) {
-      int64_t at = (int64_t)g * a.nvp + (first + step) * (a.whole_units ? 1 : a.nclass) + cls;
       if (a.whole_units) {
         // no room for a partial sum per class part: the parts one after the other, added in the
         // order in which k_hub_finish_coalescent adds them
-        at = (int64_t)g * n_items + first + step;
         for (int part = 1; part < a.nclass; ++part) {
           CoalItem it = meta(step, part);
           const int64_t c0 = a.sptr[(int64_t)part * n_items + first + step];
@@ -1131,7 +1141,7 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_coalescent(const AggArgs a
           VT::add(acc, more);
         }
       }
-      if (team == 0 && valid) VT::store(a.partial + (at << a.ls_log2) * VEC + fl * VEC, acc, false);
+      if (team == 0 && valid) VT::store(unit_partial(a, g, first + step, cls) + lane_col, acc, false);
     } else if (have && valid && (!wide || team == 0)) {
       VT::fma(acc, di, xi);
       VT::store(ylane + (int64_t)cur.i * a.ldy, VT::scale(di, acc), a.nt & 1);
@@ -1160,11 +1170,12 @@ __global__ __launch_bounds__(kBlock) void k_hub_finish_coalescent(const AggArgs 
   const int32_t i = a.hub_rows[hr];
   const int32_t it0 = a.hub_item_off[hr], it1 = a.hub_item_off[hr + 1];
   const int parts = a.whole_units ? 1 : a.nclass;
-  const int64_t stride = (int64_t)VEC << a.ls_log2;
+  const int stride = min(a.sg, a.k - g * a.sg) * a.F;  // (see unit_partial)
+  const int lane_col = t * a.F + min((fl - u * lps) * VEC, a.F - VEC);
   typename VT::T acc = VT::zero();
   if (valid)
     for (int32_t it = it0 + team; it < it1; it += nteams) {
-      const float *p = a.partial + ((int64_t)g * a.n_items + it) * parts * stride + fl * VEC;
+      const float *p = unit_partial(a, g, it, 0) + lane_col;
       typename VT::T sum = VT::load(p);
       if (parts > 1) {
         for (int q = 0; q < parts; q += 8) {  // (a unit has 8, 16 or 32 class parts)
@@ -1180,7 +1191,6 @@ __global__ __launch_bounds__(kBlock) void k_hub_finish_coalescent(const AggArgs 
     }
   reduce_slots<VEC>(a.ls_log2, acc);
   if (team == 0 && valid) {
-    const int lane_col = t * a.F + min((fl - u * lps) * VEC, a.F - VEC);
     const float di = a.dinv[(int64_t)t * a.n + i];
     VT::fma(acc, di, VT::load(a.X[0] + lane_col + (int64_t)i * a.ldx));
     VT::store(a.Y[0] + lane_col + (int64_t)i * a.ldy, VT::scale(di, acc), a.nt & 1);
@@ -1230,6 +1240,33 @@ int launch(const AggArgs &a, bool fast, hipStream_t st, bool fused_update = fals
       hipLaunchKernelGGL((k_aggregate<VEC, true, 4>), grid, block, 0, st, a);
   }
   if (fin > 0) hipLaunchKernelGGL((k_split_finish<VEC>), dim3((unsigned)fin), dim3(kBlock), 0, st, a);
+  PIPAD_HIP(hipGetLastError());
+  return PIPAD_OK;
+}
+
+// The update behind the aggregation, from the stored results of all snapshots.
+int launch_update(const AggArgs &a, hipStream_t st) {
+  const int64_t tiles = ((int64_t)a.n + 15) / 16 * a.k;
+  // weights resident in LDS when a column block of them fits (40 KB: four workgroups per CU), else straight
+  // from memory
+  const int kpad = (a.F + 3) / 4 * 4;
+  int cbw = std::min((a.Fo + 15) / 16 * 16, kUpdMaxCols);
+  while (cbw > 16 && (size_t)(kpad + 1) * (cbw + kUpdPad) * 4 > (40u << 10)) cbw -= 16;
+  const size_t lds = (size_t)(kpad + 1) * (cbw + kUpdPad) * 4;
+  if (lds <= (40u << 10)) {
+    const int64_t col_blocks = (a.Fo + cbw - 1) / cbw;
+    // as many tiles per wave as leave 16 waves for every CU
+    const int per_wave = (int)std::clamp<int64_t>(tiles * col_blocks / 4096, 1, kUpdTiles);
+    const int64_t per_block = (int64_t)kWavesPerBlock * per_wave;
+    const dim3 grid((unsigned)((tiles + per_block - 1) / per_block), (unsigned)col_blocks);
+    void (*const kern[])(AggArgs, int, int) = {k_update_resident<1>, k_update_resident<2>, k_update_resident<3>,
+                                               k_update_resident<4>, k_update_resident<5>, k_update_resident<6>,
+                                               k_update_resident<7>, k_update_resident<8>};
+    hipLaunchKernelGGL(kern[cbw / 16 - 1], grid, dim3(kBlock), lds, st, a, kpad, per_wave);
+  } else {
+    hipLaunchKernelGGL(k_update, dim3((unsigned)((tiles + kWavesPerBlock - 1) / kWavesPerBlock)),
+                       dim3(kBlock), 0, st, a);
+  }
   PIPAD_HIP(hipGetLastError());
   return PIPAD_OK;
 }
@@ -1461,37 +1498,43 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
     }
   }
 
-  // scratch for the partial sums: one slice-wide vector per class part and slice
-  const size_t per_snapshot = (size_t)a.nvp * (size_t)a.fchunks * (size_t)sw;
-  size_t need = per_snapshot * (size_t)(coalescent ? a.nslices : a.nsel);
-  if (coalescent && scratch.fixed && need > *scratch.floats) {
-    // too many for a fixed scratch: one per hub unit then, the same sums
-    a.whole_units = 1;
-    need /= (size_t)a.nclass;
+  // scratch for the partial sums: one slice-wide vector per class part and slice; k * F floats per class
+  // part for the coalescent kernel
+  const size_t per_snapshot = coalescent ? (size_t)a.nvp * (size_t)F : (size_t)a.nvp * (size_t)a.fchunks * (size_t)sw;
+  size_t need = per_snapshot * (size_t)a.nsel;
+  // It cannot grow where it is the fixed array, and not while the stream is being captured into a graph:
+  // growing means allocating.
+  bool fixed = scratch.fixed;
+  if (need > *scratch.floats && !fixed) {
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &capturing) != hipSuccess) (void)hipGetLastError();
+    fixed = capturing != hipStreamCaptureStatusNone;
   }
-  if (need > *scratch.floats) {
-    if (scratch.fixed) {
-      // A fixed scratch that is too small for all snapshots at once takes them in groups, one
-      // launch after the other on the stream (a snapshot's result does not depend on what runs
-      // beside it, so the bits are the same); it must hold one snapshot's partial sums.
-      const size_t group = coalescent || per_snapshot == 0 ? 0 : *scratch.floats / per_snapshot;
-      if (group == 0 || a.nsel <= 1) return PIPAD_ERR_SCRATCH;
+  if (need > *scratch.floats && fixed) {
+    if (coalescent) {
+      // one partial sum per hub unit then, the same sums
+      a.whole_units = 1;
+      need /= (size_t)a.nclass;
+      if (need > *scratch.floats) return PIPAD_ERR_SCRATCH;
+    } else {
+      // The snapshots in groups that fit, one launch after the other on the stream (a snapshot's
+      // result does not depend on what runs beside it, so the bits are the same); there must be room
+      // for one snapshot's partial sums.
+      const size_t group = *scratch.floats / per_snapshot;
+      if (group == 0) return PIPAD_ERR_SCRATCH;
       int32_t list[PIPAD_MAX_K];
       for (int q = 0; q < a.nsel; ++q) list[q] = subset ? subset[q] : q;
       for (int start = 0; start < a.nsel; start += (int)group) {
-        const int rc = aggregate_launch(f, F, X, ldx, Y, ldy, st, scratch, upd, list + start,
+        const int rc = aggregate_launch(f, F, X, ldx, Y, ldy, st, scratch, fused ? upd : nullptr, list + start,
                                         std::min<int>((int)group, a.nsel - start));
         if (rc != PIPAD_OK) return rc;
       }
-      return PIPAD_OK;
+      return upd && !fused ? launch_update(a, st) : PIPAD_OK;
     }
-    // growing means allocating: not while the stream is being captured into a graph
-    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &capturing) != hipSuccess) {
-      (void)hipGetLastError();
-    } else if (capturing != hipStreamCaptureStatusNone) {
-      return PIPAD_ERR_SCRATCH;
-    }
+  }
+  if (need > *scratch.floats) {
+    // (the fused update takes slices of up to 64 columns also where the option asks for narrower ones)
+    if (opt.slice_cols > 0) need = std::max(need, (size_t)a.nvp * (size_t)a.nsel * 64);
     void *ptr = nullptr;
     if (f->alloc) {
       // the caller's allocator owns the memory; a smaller buffer from before stays with it
@@ -1520,29 +1563,7 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
   if (fused) return launch<4>(a, fast, st, true);
   const int rc = vec4 ? launch<4>(a, fast, st) : launch<1>(a, fast, st);
   if (rc != PIPAD_OK || !upd) return rc;
-  const int64_t tiles = ((int64_t)f->n + 15) / 16 * f->k;
-  // weights resident in LDS when a column block of them fits (40 KB: four workgroups per CU), else straight
-  // from memory
-  const int kpad = (F + 3) / 4 * 4;
-  int cbw = std::min((a.Fo + 15) / 16 * 16, kUpdMaxCols);
-  while (cbw > 16 && (size_t)(kpad + 1) * (cbw + kUpdPad) * 4 > (40u << 10)) cbw -= 16;
-  const size_t lds = (size_t)(kpad + 1) * (cbw + kUpdPad) * 4;
-  if (lds <= (40u << 10)) {
-    const int64_t col_blocks = (a.Fo + cbw - 1) / cbw;
-    // as many tiles per wave as leave 16 waves for every CU
-    const int per_wave = (int)std::clamp<int64_t>(tiles * col_blocks / 4096, 1, kUpdTiles);
-    const int64_t per_block = (int64_t)kWavesPerBlock * per_wave;
-    const dim3 grid((unsigned)((tiles + per_block - 1) / per_block), (unsigned)col_blocks);
-    void (*const kern[])(AggArgs, int, int) = {k_update_resident<1>, k_update_resident<2>, k_update_resident<3>,
-                                               k_update_resident<4>, k_update_resident<5>, k_update_resident<6>,
-                                               k_update_resident<7>, k_update_resident<8>};
-    hipLaunchKernelGGL(kern[cbw / 16 - 1], grid, dim3(kBlock), lds, st, a, kpad, per_wave);
-  } else {
-    hipLaunchKernelGGL(k_update, dim3((unsigned)((tiles + kWavesPerBlock - 1) / kWavesPerBlock)),
-                       dim3(kBlock), 0, st, a);
-  }
-  PIPAD_HIP(hipGetLastError());
-  return PIPAD_OK;
+  return launch_update(a, st);
 }
 
 }  // namespace pipad
