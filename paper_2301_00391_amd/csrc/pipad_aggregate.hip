@@ -99,7 +99,7 @@ struct AggArgs {
   const int32_t *rowptr_c, *col_c;
   const float *dinv;
   const int32_t *rows_short, *rows_long;
-  const int32_t *item_row, *item_v0, *item_v1, *hub_rows, *hub_item_off;
+  const int32_t *item_row, *hub_rows, *hub_item_off;
   const int32_t *sptr;    // class parts of the hub rows: see pipad_frame
   const int32_t *scol_c, *scol_d;
   const float *swd;
@@ -1337,8 +1337,6 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
   a.rows_short = f->rows_short;
   a.rows_long = f->rows_long;
   a.item_row = f->item_row;
-  a.item_v0 = f->item_v0;
-  a.item_v1 = f->item_v1;
   a.hub_rows = f->hub_rows;
   a.hub_item_off = f->hub_item_off;
   a.sptr = f->sptr;
@@ -1372,7 +1370,7 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
     a.Y[t] = Y ? Y[t] : nullptr;
     if ((reinterpret_cast<uintptr_t>(X[t]) | reinterpret_cast<uintptr_t>(a.Y[t])) & 15u) aligned = false;
   }
-  const bool vec4 = aligned || F >= 4;
+  const bool vec4 = F >= 4;
   // the fast path needs 32-bit byte offsets into a snapshot's matrix
   const bool fast = (int64_t)f->n * ldx * 4 < ((int64_t)1 << 32) && !opt.agg_generic;
   // The update rides inside the aggregation kernel when a slice is a whole row of one snapshot
@@ -1455,14 +1453,11 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
     a.batch_short = kShortRowsPerWave;
     a.batch_mid = kLongRowsPerWave;
     a.batch_wide = kWideUnitsPerWave;
-    const int min_mid = 1;
     const int64_t slices_run = coalescent ? a.nslices : a.order == 0 ? (int64_t)a.nsel * a.fchunks : 1;
-    const int64_t mult = slices_run;
-    const int64_t mult_wide = slices_run * f->nclass;
     auto waves = [&]() {
-      return (int64_t)(f->n_short + a.batch_short - 1) / a.batch_short * slices_run +
-             (int64_t)(f->n_long + a.batch_mid - 1) / a.batch_mid * mult +
-             (int64_t)(f->n_items + a.batch_wide - 1) / a.batch_wide * mult_wide;
+      return ((int64_t)(f->n_short + a.batch_short - 1) / a.batch_short +
+              (int64_t)(f->n_long + a.batch_mid - 1) / a.batch_mid +
+              (int64_t)(f->n_items + a.batch_wide - 1) / a.batch_wide * f->nclass) * slices_run;
     };
     // With the update fused in, a workgroup first copies W to LDS and a wave multiplies 16 rows at a
     // time, so batches stay longer (N = 200k, F = Fo = 64: 4 to 8 rows per wave take 1.36 ms, 32 take
@@ -1476,15 +1471,14 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
     int64_t entries = f->nnz_c;  // of a snapshot
     for (int t = 0; t < f->k; ++t) entries += f->nnz_d[t] / f->k;
     const int64_t longest_chain = 2 * f->short_entries > entries ? 50 : 70;
-    while ((waves() < enough && (a.batch_short > min_short || a.batch_mid > min_mid || a.batch_wide > 1)) ||
+    while ((waves() < enough && (a.batch_short > min_short || a.batch_mid > 1 || a.batch_wide > 1)) ||
            (chain() > longest_chain && a.batch_short > min_short)) {
       if (a.batch_short > min_short) a.batch_short >>= 1;
-      if (a.batch_mid > min_mid) a.batch_mid >>= 1;
+      if (a.batch_mid > 1) a.batch_mid >>= 1;
       if (a.batch_wide > 1) a.batch_wide >>= 1;
       if (a.batch_short <= min_short && fused && waves() < 2048) min_short = nteams;
     }
     a.batch_short = std::max(a.batch_short, nteams);
-    a.batch_mid = std::max(a.batch_mid, min_mid);
     auto blocks_for = [](int64_t items, int per_wave) {
       return (int32_t)((items + (int64_t)kWavesPerBlock * per_wave - 1) / ((int64_t)kWavesPerBlock * per_wave));
     };
