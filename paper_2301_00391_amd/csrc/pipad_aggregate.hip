@@ -734,8 +734,8 @@ void k_aggregate(const AggArgs a) {
   aggregate_body<VEC, FAST, EPL, false>(a);
 }
 
-// The same walk with the update fused in.  Its tile bookkeeping would push the register count
-// just past the limit for four waves per SIMD, which the gathers need to hide their latency.
+// The same walk with the update fused in, held to the four waves per SIMD that its 120 registers allow
+// (left to the compiler: 853 us against 851 on N = 200k, k = 8, F = Fo = 64).
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void k_aggregate_update(const AggArgs a) {
   aggregate_body<4, true, 1, true>(a);
@@ -946,12 +946,16 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
 // The exclusive entries differ per snapshot, so the lanes of a snapshot walk a list of their own: the
 // common entries, then that snapshot's exclusive ones, in the same loop as in k_aggregate (walk), with
 // those lanes as its team.  Hub units go by column class, each on the XCD that holds the class.
-// Bound: the lines that the gathers fetch (an entry's row is 8 to 256 bytes, a line 128), for small
-// frames the chain index - row pointers - entries - rows, which is therefore requested two steps
-// ahead.  Measured (wide operand; before: entries staged for all snapshots of a team one load
-// after the other, hub units whole, VEC from F's divisors): N = 1M R-MAT, k = 8, F = 2 617 -> 585 us
-// (5.1 TB/s of lines); 300k, k = 8, F = 6 467 -> 352; 300k, k = 16, F = 3 846 -> 510; 50k, k = 12,
-// F = 9 468 -> 139; 5k, k = 16, F = 5 74 -> 19; 200k, k = 8, F = 16 173 -> 175.
+// Bound: the streams of indices and scales, where there are many entries: a common entry brings 4 bytes
+// of index and 4 of scale per snapshot out of k arrays, and a lane that fetches for itself (F <= 4 in
+// short rows) loads its entries a dword at a time, an instruction touching up to 64 lines.  N = 1M
+// R-MAT, k = 8, F = 2: with the row gathers replaced by zeros the kernel takes 435 of its 600 us and
+// fetches 1.57 of 2.75 GB, twice what lists and scales hold; the gathers (64 of the 128 bytes of a
+// line) add the rest.  For small frames the chain index - row pointers - entries - rows, which is
+// therefore requested two steps ahead.  Measured (wide operand; before: entries staged for all snapshots
+// of a team one load after the other, hub units whole, VEC from F's divisors): N = 1M R-MAT, k = 8, F = 2
+// 617 -> 585 us; 300k, k = 8, F = 6 467 -> 352; 300k, k = 16, F = 3 846 -> 510; 50k, k = 12, F = 9 468 ->
+// 139; 5k, k = 16, F = 5 74 -> 19; 200k, k = 8, F = 16 173 -> 175.
 struct CoalItem {
   int32_t i, cs, clen, ds, len;  // len: both lists together (0: this lane has nothing to do)
 };

@@ -274,8 +274,8 @@ __global__ __launch_bounds__(kBlock) void k_prepare(Snaps s, Tiles g, RowClasses
 // Once it is known which base entries are common, their places in the windows get the sign bit, and
 // what has none is exclusive: a wave per snapshot writes it out.
 //
-// Bound by vector-ALU issue (1M-node R-MAT frame: 0.22 G wave instructions, 0.37 of 0.40 ms, when
-// the first look was taken at a row's or the tile's start and half of the waves had to search).
+// Bound by vector-ALU issue: 0.235 G wave instructions on the 1M-node R-MAT frame, which at four
+// cycles each take 0.39 of the kernel's 0.44 ms; 0.75 GB are fetched meanwhile.
 // The tiles took over from byte flags in global memory (cleared, set, packed and counted by four
 // kernels) and a window per wave.
 template <int KM, int T>
@@ -946,11 +946,11 @@ __device__ __forceinline__ void store_scales(const SplitArgs &g, const int32_t (
 // of 2048 entries (a whole unit, unless the options say otherwise) is read once into registers,
 // counted and put in class order in LDS with one ballot per class and 64 entries, and written out
 // in that order with the scales, so that neighbouring lanes store to neighbouring addresses.  On the
-// 1M-node R-MAT frame 0.24 ms (scattered from the input order, eight runs of stores at a time, and
-// the scales by another kernel: 0.29 ms); 0.81 GB fetched and 0.35 GB written, most of the fetches
-// lines of D^-1/2 for a few scales each.  A kernel for the scales alone that runs every class on
-// the XCD that gathers it later fetches a third of that but shares the lines it writes between
-// XCDs, and the two together were slower (0.26 ms).
+// 1M-node R-MAT frame 0.25 ms (scattered from the input order, eight runs of stores at a time, and the
+// scales by another kernel: 0.29 ms); 0.75 GB fetched, most of it lines of D^-1/2 for a few scales
+// each, and 0.36 GB written: 4.4 TB/s, the rate of a plain copy.  A kernel for the scales alone that
+// runs every class on the XCD that gathers it later fetches a third of that but shares the lines it
+// writes between XCDs, and the two together were slower (0.26 ms).
 template <int NC>
 __global__ __launch_bounds__(kFillWaves * kWave) void k_split_fill(SplitArgs g) {
   constexpr int RND = kFillPiece / kWave;
@@ -1097,7 +1097,8 @@ __global__ __launch_bounds__(kFillWaves * kWave) void k_split_fill(SplitArgs g) 
 // dinv_t[column] of the entry is stored: for a common entry once per snapshot (from the node-major
 // copy of D^-1/2: one line per node), for an exclusive entry for its own snapshot.  The scales of a
 // hub row's common entries are never read from here (the aggregation takes them from the
-// class-grouped copy), so they are skipped.
+// class-grouped copy), so they are skipped.  On the 1M-node R-MAT frame 0.84 GB are fetched and 0.57 GB
+// written in 0.31 ms: 4.5 TB/s, the rate of a plain copy.
 struct OutParts {
   int32_t *col[PIPAD_MAX_K + 1];
   float *wc[PIPAD_MAX_K];
