@@ -279,7 +279,7 @@ const char *pipad_last_hip_error(void);
  *                    once for all snapshots); 2 (default): 0 while one slice's matrix is smaller
  *                    than 28 MiB, else 1.  Results do not depend on it.
  *   "agg_nt"         bit 0: non-temporal stores for Y (every element is written once and not read
- *                    again by the call: measured 1-2 % faster); bit 1: non-temporal loads for the
+ *                    again by the call: measured 1-6 % faster); bit 1: non-temporal loads for the
  *                    index and scale streams (no gain measured) (default 1)
  *   "slice_cols"     feature columns per slice, 1..64 (default 0 = 64)
  *   "agg_generic"    1 forces the bounds-checked kernel with 64-bit addresses (default 0: only for

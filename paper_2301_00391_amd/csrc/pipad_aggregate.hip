@@ -620,8 +620,8 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
   // bit.  order = index within the batch of the row taken as number `lane`; which rows a wave
   // works on does not change.  Not for slices narrower than a cache line, where neighbouring
   // rows share lines, and not for batches of similar rows, where the natural order keeps the
-  // rows of a step next to each other in memory (measured: 4 % faster on the R-MAT frame, 2-8 %
-  // slower on Chung-Lu frames and narrow slices when applied regardless).
+  // rows of a step next to each other in memory (R-MAT frames, k = 8, F = 64: N = 200k 610 -> 585 us,
+  // 1M 3926 -> 3865; Chung-Lu frames, where it is not triggered, 1 % slower when applied regardless).
   int order = lane;
 #ifndef PIPAD_NO_ROW_ORDER
   if (!wide && ((VEC * 4) << a.ls_log2) >= 128) {
@@ -1356,9 +1356,11 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
   a.n_hub = f->n_hub;
   a.nt = (int32_t)opt.agg_nt;
   // Workgroup order.  One slice after the other keeps one snapshot's matrix in the caches at a
-  // time; side by side shares the index streams between the slices, which wins (8-18 % measured
-  // on N = 200k, F <= 32) while a slice's matrix (N rows of the slice's width) is smaller than
-  // the eight L2s together; from PIPAD_ORDER_BYTES on the slices go one after the other.
+  // time; side by side shares the index streams between the slices, which wins while a slice's matrix
+  // (N rows of the slice's width) is smaller than the eight L2s together; from PIPAD_ORDER_BYTES on the
+  // slices go one after the other.  Measured, k = 8, the other order against the one taken: N = 100k,
+  // F = 64 328 us against 317, N = 200k, F = 32 364 against 348, F = 16 252 against 256; and beyond the
+  // line N = 200k, F = 64 724 against 714, R-MAT 1M 3910 against 3865, low-overlap 5735 against 5049.
   a.order = opt.agg_order >= 2 ? -1 : (int32_t)opt.agg_order;
   a.nsel = subset ? nsubset : f->k;
   for (int q = 0; q < a.nsel; ++q)
