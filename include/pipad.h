@@ -116,7 +116,7 @@ int pipad_frame_temporaries(pipad_frame_t *frame, void **ptr, size_t *bytes);
  * The call works with any ldx >= F; but with a power-of-two stride of several lines the memory
  * channel of a row is decided by a few bits of the node id, and when popular nodes share those
  * bits (ids of R-MAT-like generators do) their rows crowd onto a few channels: measured on a
- * 1M-node R-MAT frame at F = 64, ldx = 64 is 1-5 % slower than ldx = 96.  The padding is never
+ * 1M-node R-MAT frame at F = 64, ldx = 64 is 6-11 % slower than ldx = 96.  The padding is never
  * read.  Returns a negative pipad_status for F < 1. */
 int64_t pipad_recommended_row_stride(int32_t F);
 
@@ -155,8 +155,8 @@ int pipad_frame_shape(const pipad_frame_t *frame, int32_t *n, int32_t *k);
  *   with the same or a larger k*F has sized the scratch, whichever form (one matrix per snapshot,
  *   concatenated, with the update) either of them has.  A recorded call whose form takes more than
  *   the eager one left (rows padded to the slice width do) makes do with it, in several launches and
- *   with the same bits; it returns PIPAD_ERR_SCRATCH, with nothing enqueued, where there is not even
- *   room for one snapshot.
+ *   with the same bits; a call with a larger k*F than all before, which would have to allocate while
+ *   `stream` is being captured, returns PIPAD_ERR_SCRATCH with nothing enqueued.
  *   Two aggregations of the SAME frame must not run concurrently (they share that scratch).
  *   Results are deterministic: same inputs, same bits.
  */

@@ -1503,12 +1503,14 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
   const size_t per_snapshot = coalescent ? (size_t)a.nvp * (size_t)F : (size_t)a.nvp * (size_t)a.fchunks * (size_t)sw;
   size_t need = per_snapshot * (size_t)a.nsel;
   // It cannot grow where it is the fixed array, and not while the stream is being captured into a graph:
-  // growing means allocating.
+  // growing means allocating.  Captured, a call with a larger k * F than all before is refused; with
+  // no larger one it is only the padding of its slices that can be missing.
   bool fixed = scratch.fixed;
   if (need > *scratch.floats && !fixed) {
     hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &capturing) != hipSuccess) (void)hipGetLastError();
     fixed = capturing != hipStreamCaptureStatusNone;
+    if (fixed && (size_t)a.nvp * (size_t)a.nsel * (size_t)F > *scratch.floats) return PIPAD_ERR_SCRATCH;
   }
   if (need > *scratch.floats && fixed) {
     if (coalescent) {

@@ -76,6 +76,32 @@ def test_recorded_after_another_form_has_sized_the_scratch(pipad, k, sized, reco
     other.close()
 
 
+@pytest.mark.parametrize("layout", ["list", "wide"])
+def test_recorded_with_more_columns_than_any_eager_call(pipad, layout):  # noqa: F811
+    """Refused with nothing enqueued; the recording goes on."""
+    n, k = 500, 3
+    for key, value in (("short_max", 2), ("mid_max", 5), ("agg_coalescent", 2)):
+        pipad.set_option(key, value)
+    lists = churned(np.random.default_rng(8), n, k, 0.03, 0.8)
+    frame = pipad.frame_build_overlap([(torch.from_numpy(rp).cuda(), torch.from_numpy(c).cuda()) for rp, c in lists])
+    x, y = operand(n, k, 8, 1, layout), results(n, k, 8, layout)
+    wider, y_wider = operand(n, k, 17, 1, layout), results(n, k, 17, layout)
+    want = pipad.frame_aggregate(frame, x)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        with pytest.raises(pipad.PipadError) as info:
+            pipad.frame_aggregate(frame, wider, y_wider)
+        pipad.frame_aggregate(frame, x, y)
+    assert info.value.status == -6
+    graph.replay()
+    torch.cuda.synchronize()
+    for t in range(k):
+        assert torch.equal(*((a[:, t] if layout == "wide" else a[t]) for a in (y, want)))
+    assert all(torch.isnan(out).all() for out in y_wider)
+    frame.close()
+
+
 @pytest.mark.parametrize("k,F,rows", [(12, 9, 100_000), (21, 3, 150_000)])
 def test_fixed_array_and_many_units_on_the_concatenated_operand(pipad, k, F, rows):  # noqa: F811
     """Every row a unit: no room for the class parts, and room for one sum per unit only without the
