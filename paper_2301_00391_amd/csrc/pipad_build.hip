@@ -251,8 +251,8 @@ __global__ __launch_bounds__(kBlock) void k_prepare(Snaps s, Tiles g, RowClasses
       }
     }
     if (live) {  // node-major copy for the scatter step (one line per node)
-      float *nk = dinv_nk + (int64_t)i * g.k + t0;
-      if ((g.k & 3) == 0) {
+      float *nk = dinv_nk + (int64_t)i * node_stride(g.k) + t0;
+      if (g.k > 2) {  // (what lies behind the k-th value repeats it)
         *reinterpret_cast<float4 *>(nk) = make_float4(v[0], v[1], v[2], v[3]);
       } else {
 #pragma unroll
@@ -905,7 +905,7 @@ struct SplitArgs {
   const int32_t *rowptr[PIPAD_MAX_K + 1];  // parts: common, then exclusive
   const int32_t *col[PIPAD_MAX_K + 1];
   int32_t n;
-  const float *dinv, *dinv_nk;             // [k][n], [n][k]
+  const float *dinv, *dinv_nk;             // [k][n], [n][node_stride(k)]
   int32_t *sptr, *scol_c, *scol_d;
   float *swc[PIPAD_MAX_K];
   float *swd;
@@ -918,16 +918,19 @@ constexpr int kFillPiece = 2048;  // entries a wave puts in class order in LDS a
 template <int UN>
 __device__ __forceinline__ void store_scales(const SplitArgs &g, const int32_t (&c)[UN], const int32_t (&to)[UN],
                                              const int32_t (&live)[UN]) {
-  if ((g.k & 3) == 0) {
+  if (g.k > 2) {
+    const int32_t stride = node_stride(g.k);
     for (int t = 0; t < g.k; t += 4) {
       float4 w[UN];
 #pragma unroll
-      for (int r = 0; r < UN; ++r) w[r] = *reinterpret_cast<const float4 *>(g.dinv_nk + (int64_t)c[r] * g.k + t);
+      for (int r = 0; r < UN; ++r) w[r] = *reinterpret_cast<const float4 *>(g.dinv_nk + (int64_t)c[r] * stride + t);
 #pragma unroll
       for (int r = 0; r < UN; ++r)
         if (live[r]) {
-          g.swc[t][to[r]] = w[r].x; g.swc[t + 1][to[r]] = w[r].y;
-          g.swc[t + 2][to[r]] = w[r].z; g.swc[t + 3][to[r]] = w[r].w;
+          g.swc[t][to[r]] = w[r].x;
+          if (t + 1 < g.k) g.swc[t + 1][to[r]] = w[r].y;
+          if (t + 2 < g.k) g.swc[t + 2][to[r]] = w[r].z;
+          if (t + 3 < g.k) g.swc[t + 3][to[r]] = w[r].w;
         }
     }
   } else {
@@ -1122,8 +1125,9 @@ __device__ inline uint64_t lane_word(uint64_t x, int l) {
          (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), l) << 32;
 }
 
-// KV > 0: k == 4 * KV, a node's k scales are read as KV 16-byte pieces; KV == 0: any k, one by one.
-template <int KV, int TILES>
+// KV > 0: a node's k scales lie in KV 16-byte pieces, read together (FULL: k == 4 * KV); KV == 0: k <= 2 or
+// k > 16, one by one.
+template <int KV, bool FULL, int TILES>
 __global__ __launch_bounds__(kBlock) void k_scatter(Snaps s, Tiles g, OutParts o, const float *dinv,
                                                      const float *dinv_nk) {
   constexpr int WPT = kWave / TILES;  // words of a tile a wave takes at once
@@ -1194,9 +1198,9 @@ __global__ __launch_bounds__(kBlock) void k_scatter(Snaps s, Tiles g, OutParts o
 #pragma unroll
             for (int q = 0; q < KV; ++q) {
               o.wc[4 * q + 0][at[r]] = v[r][q].x;
-              o.wc[4 * q + 1][at[r]] = v[r][q].y;
-              o.wc[4 * q + 2][at[r]] = v[r][q].z;
-              o.wc[4 * q + 3][at[r]] = v[r][q].w;
+              if (FULL || 4 * q + 1 < g.k) o.wc[4 * q + 1][at[r]] = v[r][q].y;
+              if (FULL || 4 * q + 2 < g.k) o.wc[4 * q + 2][at[r]] = v[r][q].z;
+              if (FULL || 4 * q + 3 < g.k) o.wc[4 * q + 3][at[r]] = v[r][q].w;
             }
         }
       } else {
@@ -1206,7 +1210,7 @@ __global__ __launch_bounds__(kBlock) void k_scatter(Snaps s, Tiles g, OutParts o
         for (int u = 0; u < g.k; ++u) {
           float w[UN];
 #pragma unroll
-          for (int r = 0; r < UN; ++r) w[r] = dinv_nk[(int64_t)c[r] * g.k + u];
+          for (int r = 0; r < UN; ++r) w[r] = dinv_nk[(int64_t)c[r] * node_stride(g.k) + u];
 #pragma unroll
           for (int r = 0; r < UN; ++r)
             if (need[r] >> lane & 1ull) o.wc[u][at[r]] = w[r];
@@ -1479,7 +1483,7 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
   keep1.want(&f->rowptr_c, (size_t)n + 1);
   for (int t = 0; t < k; ++t) keep1.want(&f->rowptr_d[t], (size_t)n + 1);
   keep1.want(&f->dinv, (size_t)k * n);
-  keep1.want(&f->dinv_nk, (size_t)k * n);
+  keep1.want(&f->dinv_nk, (size_t)node_stride(k) * n);
   want_lists(keep1, f, entries);
   {
     void *base_ptr = A.get(keep1.total);
@@ -1612,10 +1616,15 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
     // four tiles per wave, 0.2M nodes: 65 against 74); with 8M entries and more per snapshot there
     // are waves enough and fewer of them do better (1M nodes, 20M entries: 313 us against 339).
     const int per_wave = g.ntiles < 16384 ? 1 : 4;
-    auto scatter = per_wave == 1 ? (k == 4 ? k_scatter<1, 1> : k == 8 ? k_scatter<2, 1>
-                                  : k == 16 ? k_scatter<4, 1> : k_scatter<0, 1>)
-                                 : (k == 4 ? k_scatter<1, 4> : k == 8 ? k_scatter<2, 4>
-                                  : k == 16 ? k_scatter<4, 4> : k_scatter<0, 4>);
+    using Scatter = void (*)(Snaps, Tiles, OutParts, const float *, const float *);
+    static const Scatter kernels[2][9] = {
+        {k_scatter<0, false, 1>, k_scatter<1, false, 1>, k_scatter<1, true, 1>, k_scatter<2, false, 1>,
+         k_scatter<2, true, 1>, k_scatter<3, false, 1>, k_scatter<3, true, 1>, k_scatter<4, false, 1>,
+         k_scatter<4, true, 1>},
+        {k_scatter<0, false, 4>, k_scatter<1, false, 4>, k_scatter<1, true, 4>, k_scatter<2, false, 4>,
+         k_scatter<2, true, 4>, k_scatter<3, false, 4>, k_scatter<3, true, 4>, k_scatter<4, false, 4>,
+         k_scatter<4, true, 4>}};
+    auto scatter = kernels[per_wave == 1 ? 0 : 1][k <= 2 || k > 16 ? 0 : node_stride(k) / 2 - (k % 4 ? 1 : 0)];
     hipLaunchKernelGGL(scatter, grid1(g.ntiles, kWavesPerBlock * per_wave, k + 1), dim3(kBlock), 0, st, s, g, o, f->dinv,
                        f->dinv_nk);
     PIPAD_TRY(hipGetLastError());

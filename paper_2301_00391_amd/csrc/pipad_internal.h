@@ -63,7 +63,7 @@ struct pipad_frame {
   int32_t *rowptr_d[PIPAD_MAX_K] = {};  // each [n+1]
   int32_t *col_d[PIPAD_MAX_K] = {};     // each [nnz_d[t]]
   float *dinv = nullptr;             // [k][n]: dinv[t*n + i]
-  float *dinv_nk = nullptr;          // [n][k]: the same values node-major (one line per node)
+  float *dinv_nk = nullptr;          // [n][node_stride(k)]: the same values node-major (one line per node)
   // Column scales stored per entry, so that the aggregation streams them instead of gathering
   // them: wc[t][e] = dinv_t[col_c[e]], wd[t][e] = dinv_t[col_d[t][e]].
   float *wc[PIPAD_MAX_K] = {};
@@ -222,6 +222,10 @@ void frame_take_options(pipad_frame *f);
 // The class-grouped copies of the hub rows' entries (sptr, scol_c, scol_d, swc, swd), once the
 // frame's parts, D^-1/2 and row lists are in place.
 int build_split_arrays(pipad_frame *f, hipStream_t st);
+// Floats per node of the node-major copy of D^-1/2: from three snapshots on a multiple of four, so that a
+// node's scales are read 16 bytes at a time whatever k is (R-MAT, N = 100k, k = 5: one scale after the
+// other k_split_fill took 44 us and k_scatter 34, so 35 and 20).
+__host__ __device__ inline int32_t node_stride(int32_t k) { return k <= 2 ? k : (k + 3) / 4 * 4; }
 // Column class of a column index: the top 3 + sub_log2 bits of a multiplicative hash, so that the
 // class's XCD is class >> sub_log2.
 __host__ __device__ inline uint32_t column_class(int32_t j, int sub_log2) {

@@ -341,9 +341,9 @@ __device__ inline void fill_run(int32_t *rp, int32_t lo, int32_t hi, int32_t v, 
   }
 }
 
-// KV > 0: k == 4 * KV, a node's k scales are read as KV 16-byte pieces and the k destination
-// arrays are fixed at compile time; KV == 0: any k, one by one.
-template <int KV>
+// KV > 0: a node's k scales lie in KV 16-byte pieces, read together (FULL: k == 4 * KV); KV == 0: k <= 2 or
+// k > 16, one by one.
+template <int KV, bool FULL>
 __global__ __launch_bounds__(kBlock) void k_finish_parts(FinishArgs g) {
   const int lane = threadIdx.x % kWave;
   const int p = blockIdx.y;
@@ -373,12 +373,12 @@ __global__ __launch_bounds__(kBlock) void k_finish_parts(FinishArgs g) {
 #pragma unroll
       for (int q = 0; q < KV; ++q) {
         g.wc[4 * q + 0][e] = v[q].x;
-        g.wc[4 * q + 1][e] = v[q].y;
-        g.wc[4 * q + 2][e] = v[q].z;
-        g.wc[4 * q + 3][e] = v[q].w;
+        if (FULL || 4 * q + 1 < g.k) g.wc[4 * q + 1][e] = v[q].y;
+        if (FULL || 4 * q + 2 < g.k) g.wc[4 * q + 2][e] = v[q].z;
+        if (FULL || 4 * q + 3 < g.k) g.wc[4 * q + 3][e] = v[q].w;
       }
     } else {
-      const float *row = g.dinv_nk + (int64_t)c * g.k;
+      const float *row = g.dinv_nk + (int64_t)c * node_stride(g.k);
       for (int t = 0; t < g.k; ++t) g.wc[t][e] = row[t];
     }
   } else {
@@ -430,7 +430,7 @@ int transpose_frame(const pipad_frame *f, pipad_alloc_fn alloc, void *alloc_ctx,
   keep.want(&g->rowptr_c, (size_t)n + 1);
   for (int t = 0; t < k; ++t) keep.want(&g->rowptr_d[t], (size_t)n + 1);
   keep.want(&g->dinv, (size_t)k * n);
-  keep.want(&g->dinv_nk, (size_t)k * n);
+  keep.want(&g->dinv_nk, (size_t)node_stride(k) * n);
   keep.want(&g->col_c, (size_t)g->nnz_c);
   for (int t = 0; t < k; ++t) {
     keep.want(&g->col_d[t], (size_t)g->nnz_d[t]);
@@ -511,12 +511,12 @@ int transpose_frame(const pipad_frame *f, pipad_alloc_fn alloc, void *alloc_ctx,
 
   launched = true;
   // (the two copies of D^-1/2 lie next to each other in every frame)
-  const size_t dinv_span = (size_t)(f->dinv_nk - f->dinv) + (size_t)k * n;
+  const size_t dinv_span = (size_t)(f->dinv_nk - f->dinv) + (size_t)node_stride(k) * n;
   if (g->dinv_nk - g->dinv == f->dinv_nk - f->dinv && f->dinv_nk > f->dinv) {
     PIPAD_TRY_T(hipMemcpyAsync(g->dinv, f->dinv, sizeof(float) * dinv_span, hipMemcpyDeviceToDevice, st));
   } else {
     PIPAD_TRY_T(hipMemcpyAsync(g->dinv, f->dinv, sizeof(float) * (size_t)k * n, hipMemcpyDeviceToDevice, st));
-    PIPAD_TRY_T(hipMemcpyAsync(g->dinv_nk, f->dinv_nk, sizeof(float) * (size_t)k * n, hipMemcpyDeviceToDevice, st));
+    PIPAD_TRY_T(hipMemcpyAsync(g->dinv_nk, f->dinv_nk, sizeof(float) * (size_t)node_stride(k) * n, hipMemcpyDeviceToDevice, st));
   }
 
   // ---- stable sort of all entries by column, digit by digit
@@ -558,8 +558,11 @@ int transpose_frame(const pipad_frame *f, pipad_alloc_fn alloc, void *alloc_ctx,
       c.wc[t] = g->wc[t];
       c.wd[t] = g->wd[t];
     }
-    auto finish = k == 4 ? k_finish_parts<1> : k == 8 ? k_finish_parts<2> : k == 16 ? k_finish_parts<4>
-                                                                                      : k_finish_parts<0>;
+    using Finish = void (*)(FinishArgs);
+    static const Finish kernels[] = {k_finish_parts<0, false>, k_finish_parts<1, false>, k_finish_parts<1, true>,
+                                     k_finish_parts<2, false>, k_finish_parts<2, true>,  k_finish_parts<3, false>,
+                                     k_finish_parts<3, true>,  k_finish_parts<4, false>, k_finish_parts<4, true>};
+    auto finish = kernels[k <= 2 || k > 16 ? 0 : node_stride(k) / 2 - (k % 4 ? 1 : 0)];
     hipLaunchKernelGGL(finish, grid1(std::max(max_nnz, 1), kBlock, k + 1), dim3(kBlock), 0, st, c);
   }
   PIPAD_TRY_T(hipGetLastError());

@@ -1,0 +1,33 @@
+"""The per-entry scales of all parts and of the class-grouped copies of the hub rows, against the oracle,
+for numbers of snapshots that no 16-byte piece of scales fits."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+import oracle  # noqa: E402
+import synth  # noqa: E402
+from _util import check_y, csr_to_coo  # noqa: E402
+from test_gpu_build_tiles import csr, rand_pairs  # noqa: E402
+from test_gpu_parity import pipad, run_case, _reset_options  # noqa: E402,F401
+
+
+@pytest.mark.parametrize("k", [1, 2, 3, 5, 6, 7, 11, 13, 17])
+def test_scales_of_any_number_of_snapshots(pipad, k):  # noqa: F811
+    rng = np.random.default_rng(k)
+    n, F = 500, 8
+    pool = rand_pairs(rng, n, 6000)
+    lists = [csr(n, pool[rng.random(len(pool)) < 0.9]) for _ in range(k)]
+    pipad.set_option("short_max", 4)
+    pipad.set_option("mid_max", 11)
+    run_case(pipad, n, lists, F, seed=k)
+    # the transposed frame writes them again
+    snaps = [(torch.from_numpy(rp).cuda(), torch.from_numpy(c).cuda()) for rp, c in lists]
+    back = pipad.frame_transpose(pipad.frame_build_overlap(snaps))
+    X = [synth.features(k, t, n, F) for t in range(k)]
+    Z = pipad.frame_aggregate(back, [torch.from_numpy(x).cuda() for x in X])
+    for t in range(k):
+        rows, cols = csr_to_coo(n, *lists[t])
+        z, bound = oracle.aggregate_transposed(n, rows, cols, X[t])
+        check_y(Z[t].cpu().numpy(), z, bound, f"transposed, snapshot {t}")
