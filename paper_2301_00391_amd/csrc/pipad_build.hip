@@ -909,10 +909,12 @@ struct SplitArgs {
   int32_t *sptr, *scol_c, *scol_d;
   float *swc[PIPAD_MAX_K];
   float *swd;
+  int32_t block_off[PIPAD_MAX_K + 2];      // first workgroup of every part
+  uint64_t whole;                          // bit p: part p takes a workgroup per unit, not a wave
 };
 
-constexpr int kFillWaves = 2;     // per workgroup
-constexpr int kFillPiece = 2048;  // entries a wave puts in class order in LDS at a time
+constexpr int kFillRounds = 8;                        // entries per lane and piece
+constexpr int kFillPiece = kFillRounds * kBlock;      // entries a workgroup puts in class order in LDS at a time
 
 // The k scales of UN entries of the common copy, where `live`.
 template <int UN>
@@ -945,25 +947,18 @@ __device__ __forceinline__ void store_scales(const SplitArgs &g, const int32_t (
   }
 }
 
-// A wave per (unit, part): the part's entries of the unit, stably grouped by column class.  A piece
-// of 2048 entries (a whole unit, unless the options say otherwise) is read once into registers,
-// counted and put in class order in LDS with one ballot per class and 64 entries, and written out
-// in that order with the scales, so that neighbouring lanes store to neighbouring addresses.  On the
-// 1M-node R-MAT frame 0.25 ms (scattered from the input order, eight runs of stores at a time, and the
-// scales by another kernel: 0.29 ms); 0.75 GB fetched, most of it lines of D^-1/2 for a few scales
-// each, and 0.36 GB written: 4.4 TB/s, the rate of a plain copy.  A kernel for the scales alone that
-// runs every class on the XCD that gathers it later fetches a third of that but shares the lines it
-// writes between XCDs, and the two together were slower (0.26 ms).
-template <int NC>
-__global__ __launch_bounds__(kFillWaves * kWave) void k_split_fill(SplitArgs g) {
-  constexpr int RND = kFillPiece / kWave;
-  __shared__ int32_t s_col[kFillWaves][kFillPiece];
-  __shared__ int32_t s_off[kFillWaves][NC];  // place in the copy minus place in the piece
-  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-  const int64_t id = (int64_t)blockIdx.x * kFillWaves + wave;
-  if (id >= g.n_units) return;
-  const int32_t u = __builtin_amdgcn_readfirstlane((int32_t)id);
-  const int p = blockIdx.y;
+// A part's entries of one unit, stably grouped by column class, by W waves.  A piece of them (8 per
+// lane) is read into registers, counted and put in class order in LDS with one ballot per class and 64
+// entries, and written out in that order with the scales, so that neighbouring lanes store to
+// neighbouring addresses.
+template <int NC, int W>
+__device__ __forceinline__ void fill_part(const SplitArgs &g, int32_t u, int p, int lane, int wave, int32_t *stage,
+                                          int32_t (*s_cnt)[NC], int32_t *s_off) {
+  constexpr int32_t share = kFillRounds * kWave, piece = W * share;  // of a wave, of the team
+  auto sync = [&]() __attribute__((always_inline)) {
+    if (W > 1) __syncthreads();
+    else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  };
   const int32_t row = g.item_row[u], v0 = g.item_v0[u], v1 = g.item_v1[u];
   const int32_t cs = g.rowptr[0][row], lc = g.rowptr[0][row + 1] - cs;
   int32_t a, b, out;  // entries [a, b) of the part, first place in the copy
@@ -980,74 +975,78 @@ __global__ __launch_bounds__(kFillWaves * kWave) void k_split_fill(SplitArgs g) 
     int32_t before = lane < p - 1 ? ld : 0;  // the row's entries in the exclusive parts in front
 #pragma unroll
     for (int m = kWave >> 1; m >= 1; m >>= 1) before += __shfl_xor(before, m, kWave);
-    ds = __shfl(ds, p - 1, kWave);
-    ld = __shfl(ld, p - 1, kWave);
+    ds = __builtin_amdgcn_readlane(ds, p - 1);
+    ld = __builtin_amdgcn_readlane(ld, p - 1);
     const int32_t q0 = min(max(v0 - lc, 0), ld), q1 = min(max(v1 - lc, 0), ld);
     a = ds + q0;
     b = ds + q1;
     out = g.item_d0[u] + before + q0;
   }
   const int32_t *col = g.col[p];
-  const bool one_piece = b - a <= kFillPiece;
-  int32_t cv[RND];
-  auto load = [&](int32_t at) __attribute__((always_inline)) {
+  int32_t cv[kFillRounds];
+  int32_t cnt[NC];  // this wave's entries per class (wave-uniform)
+  auto load_and_count = [&](int32_t at) __attribute__((always_inline)) {
+    const int32_t first = at + wave * share;
 #pragma unroll
-    for (int r = 0; r < RND; ++r) {
-      if (at + r * kWave >= b) break;
-      const int32_t v = col[min(at + r * kWave + lane, b - 1)];
-      cv[r] = at + r * kWave + lane < b ? v : -1;
+    for (int r = 0; r < kFillRounds; ++r) {
+      if (first + r * kWave >= b) break;
+      const int32_t v = col[min(first + r * kWave + lane, b - 1)];
+      cv[r] = first + r * kWave + lane < b ? v : -1;
     }
-  };
-  int32_t cnt[NC];  // entries per class (wave-uniform)
-  auto count = [&](int32_t at) __attribute__((always_inline)) {
 #pragma unroll
-    for (int r = 0; r < RND; ++r) {
-      if (at + r * kWave >= b) break;
+    for (int r = 0; r < kFillRounds; ++r) {
+      if (first + r * kWave >= b) break;
       const uint32_t cl = cv[r] >= 0 ? column_class(cv[r], g.sub_log2) : (uint32_t)NC;
 #pragma unroll
       for (int x = 0; x < NC; ++x) cnt[x] += __popcll(__ballot(cl == (uint32_t)x));
     }
   };
+  // lane x < NC: entries of class x that the team and that the waves in front of this one have counted
+  auto exchange = [&](int32_t *team, int32_t *front) __attribute__((always_inline)) {
+    int32_t mine = 0;
+#pragma unroll
+    for (int x = 0; x < NC; ++x)
+      if (lane == x) mine = cnt[x];
+    *team = mine;
+    *front = 0;
+    if (W == 1) return;
+    if (lane < NC) s_cnt[wave][lane] = mine;
+    __syncthreads();
+    *team = 0;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      const int32_t c = lane < NC ? s_cnt[w][lane] : 0;
+      *team += c;
+      if (w < wave) *front += c;
+    }
+    __syncthreads();
+  };
 #pragma unroll
   for (int x = 0; x < NC; ++x) cnt[x] = 0;
-  for (int32_t at = a; at < b; at += kFillPiece) {
-    load(at);
-    count(at);
-  }
+  for (int32_t at = a; at < b; at += piece) load_and_count(at);
+  int32_t team, front;
+  exchange(&team, &front);
   // the copy's class boundaries: sptr[(p * (NC + 1) + x) * n_units + u]
-  int32_t run[NC];
-  int32_t mine = 0, next = out;
-#pragma unroll
-  for (int x = 0; x < NC; ++x) {
-    run[x] = next;
-    if (lane == x) mine = next;
-    next += cnt[x];
-  }
-  if (lane == NC) mine = next;
-  if (lane <= NC) g.sptr[((int64_t)p * (NC + 1) + lane) * g.n_units + u] = mine;
+  int32_t run = out + (int32_t)wave_sum((uint32_t)team) - team;  // lane x: where class x goes on
+  if (wave == 0 && lane <= NC) g.sptr[((int64_t)p * (NC + 1) + lane) * g.n_units + u] = run;
 
-  int32_t *const stage = s_col[wave];
-  for (int32_t at = a; at < b; at += kFillPiece) {
-    int32_t local[NC];
-    if (!one_piece) {
-      load(at);
+  for (int32_t at = a; at < b; at += piece) {
+    if (b - a > piece) {
 #pragma unroll
       for (int x = 0; x < NC; ++x) cnt[x] = 0;
-      count(at);
+      load_and_count(at);
+      exchange(&team, &front);
     }
-    int32_t pos = 0;
-    int32_t off = 0;
+    const int32_t pos = (int32_t)wave_sum((uint32_t)team) - team;  // the class's first place in the piece
+    if (wave == 0 && lane < NC) s_off[lane] = run - pos;           // place in the copy minus place in the piece
+    run += team;
+    int32_t local[NC];
 #pragma unroll
-    for (int x = 0; x < NC; ++x) {
-      local[x] = pos;
-      if (lane == x) off = run[x] - pos;
-      pos += cnt[x];
-      run[x] += cnt[x];
-    }
-    if (lane < NC) s_off[wave][lane] = off;
+    for (int x = 0; x < NC; ++x) local[x] = __builtin_amdgcn_readlane(pos + front, x);
+    const int32_t first = at + wave * share;
 #pragma unroll
-    for (int r = 0; r < RND; ++r) {
-      if (at + r * kWave >= b) break;
+    for (int r = 0; r < kFillRounds; ++r) {
+      if (first + r * kWave >= b) break;
       const uint32_t cl = cv[r] >= 0 ? column_class(cv[r], g.sub_log2) : (uint32_t)NC;
       int32_t where = 0;
 #pragma unroll
@@ -1060,15 +1059,16 @@ __global__ __launch_bounds__(kFillWaves * kWave) void k_split_fill(SplitArgs g) 
       }
       if (cv[r] >= 0) stage[where] = cv[r];
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    const int32_t here = min(b - at, kFillPiece);
+    sync();
+    const int32_t here = min(b - at, piece);
     constexpr int UN = 4;  // entries per lane whose scales are requested together
-    for (int32_t j0 = lane; j0 < here; j0 += UN * kWave) {
+    for (int32_t j0 = wave * kWave + lane; j0 < here; j0 += UN * W * kWave) {
       int32_t c[UN], to[UN];
 #pragma unroll
       for (int r = 0; r < UN; ++r) {
-        c[r] = stage[min(j0 + r * kWave, here - 1)];
-        to[r] = s_off[wave][column_class(c[r], g.sub_log2)] + j0 + r * kWave;
+        const int32_t j = j0 + r * W * kWave;
+        c[r] = stage[min(j, here - 1)];
+        to[r] = s_off[column_class(c[r], g.sub_log2)] + j;
       }
       if (p > 0) {
         float w[UN];
@@ -1076,21 +1076,45 @@ __global__ __launch_bounds__(kFillWaves * kWave) void k_split_fill(SplitArgs g) 
         for (int r = 0; r < UN; ++r) w[r] = g.dinv[(int64_t)(p - 1) * g.n + c[r]];
 #pragma unroll
         for (int r = 0; r < UN; ++r)
-          if (j0 + r * kWave < here) {
+          if (j0 + r * W * kWave < here) {
             g.scol_d[to[r]] = c[r];
             g.swd[to[r]] = w[r];
           }
       } else {
-#pragma unroll
-        for (int r = 0; r < UN; ++r)
-          if (j0 + r * kWave < here) g.scol_c[to[r]] = c[r];
         int32_t live[UN];
 #pragma unroll
-        for (int r = 0; r < UN; ++r) live[r] = j0 + r * kWave < here;
+        for (int r = 0; r < UN; ++r) live[r] = j0 + r * W * kWave < here;
+#pragma unroll
+        for (int r = 0; r < UN; ++r)
+          if (live[r]) g.scol_c[to[r]] = c[r];
         store_scales<UN>(g, c, to, live);
       }
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    sync();
+  }
+}
+
+// A workgroup per unit of the parts that most of a unit's entries are in, a wave per unit of the others
+// (build_split_arrays): a wave alone goes through 2048 entries in 32 steps of memory round trips, and on
+// all but the largest frames there are too few of them to hide that.  A wave per unit of every part took
+// 35 us on an R-MAT frame with N = 100k, k = 5, now 14; N = 200k Chung-Lu, k = 8 28, now 21.  On the
+// 1M-node R-MAT frame 0.25 ms either way: 0.75 GB fetched, most of it lines of D^-1/2 for a few scales
+// each, and 0.36 GB written: 4.4 TB/s, the rate of a plain copy.  A kernel for the scales alone that
+// runs every class on the XCD that gathers it later fetches a third of that but shares the lines it
+// writes between XCDs, and the two together were slower (0.26 ms).
+template <int NC>
+__global__ __launch_bounds__(kBlock) void k_split_fill(SplitArgs g) {
+  __shared__ int32_t stage[kFillPiece];
+  __shared__ int32_t s_cnt[kWavesPerBlock][NC], s_off[kWavesPerBlock][NC];
+  const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  int p = 0;
+  while (p < g.k && (int32_t)blockIdx.x >= g.block_off[p + 1]) ++p;
+  const int32_t b = (int32_t)blockIdx.x - g.block_off[p];
+  if (g.whole >> p & 1ull) {
+    fill_part<NC, kWavesPerBlock>(g, b, p, lane, wave, stage, s_cnt, s_off[0]);
+  } else {
+    const int32_t u = b * kWavesPerBlock + wave;
+    if (u < g.n_units) fill_part<NC, 1>(g, u, p, lane, 0, stage + wave * (kFillPiece / kWavesPerBlock), s_cnt, s_off[wave]);
   }
 }
 
@@ -1422,7 +1446,19 @@ int build_split_arrays(pipad_frame *f, hipStream_t st) {
   g.scol_d = f->scol_d;
   g.swd = f->swd;
   auto fill = f->sub_log2 == 0 ? k_split_fill<8> : f->sub_log2 == 1 ? k_split_fill<16> : k_split_fill<32>;
-  hipLaunchKernelGGL(fill, grid1(f->n_items, kFillWaves, f->k + 1), dim3(kFillWaves * kWave), 0, st, g);
+  // a workgroup per unit for the parts that hold more than a quarter of a snapshot's entries, a wave elsewhere
+  int32_t blocks = 0;
+  for (int p = 0; p <= f->k; ++p) {
+    int64_t snapshot = f->nnz_c, longest = 0;
+    for (int t = 0; t < f->k; ++t) longest = std::max<int64_t>(longest, f->nnz_d[t]);
+    snapshot += longest;
+    const bool whole = 4 * (int64_t)(p == 0 ? f->nnz_c : f->nnz_d[p - 1]) > snapshot;
+    if (whole) g.whole |= 1ull << p;
+    g.block_off[p] = blocks;
+    blocks += whole ? f->n_items : (f->n_items + kWavesPerBlock - 1) / kWavesPerBlock;
+  }
+  g.block_off[f->k + 1] = blocks;
+  hipLaunchKernelGGL(fill, dim3((unsigned)blocks), dim3(kBlock), 0, st, g);
   PIPAD_HIP(hipGetLastError());
   return PIPAD_OK;
 }

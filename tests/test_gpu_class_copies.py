@@ -1,5 +1,6 @@
-"""The per-entry scales of all parts and of the class-grouped copies of the hub rows, against the oracle,
-for numbers of snapshots that no 16-byte piece of scales fits."""
+"""The per-entry scales and the class-grouped copies of the hub rows, against the oracle: numbers of
+snapshots that no 16-byte piece of scales fits, and hub units at the edges of the pieces (512 entries of a
+wave, 2048 of a workgroup) that are put in class order at a time."""
 import numpy as np
 import pytest
 
@@ -31,3 +32,23 @@ def test_scales_of_any_number_of_snapshots(pipad, k):  # noqa: F811
         rows, cols = csr_to_coo(n, *lists[t])
         z, bound = oracle.aggregate_transposed(n, rows, cols, X[t])
         check_y(Z[t].cpu().numpy(), z, bound, f"transposed, snapshot {t}")
+
+
+@pytest.mark.parametrize("segment", [2048, 1 << 20])
+@pytest.mark.parametrize("keep", [0.97, 0.2])
+@pytest.mark.parametrize("sub", [1, 4])
+def test_units_at_the_edges_of_a_piece(pipad, segment, keep, sub):  # noqa: F811
+    """Mostly common (a workgroup per unit of the common part, a wave elsewhere) and mostly exclusive."""
+    rng = np.random.default_rng(segment + sub)
+    n, k = 9000, 3
+    lengths = [511, 512, 513, 2047, 2048, 2049, 4100, n - 1]
+    hubs = np.concatenate([np.stack([np.full(m, 5 + 7 * q), rng.permutation(n)[:m]], 1)
+                           for q, m in enumerate(lengths)])
+    pool = np.concatenate([hubs, rand_pairs(rng, n, 2000)])
+    whole = csr(n, pool)
+    lists = [whole] + [csr(n, pool[rng.random(len(pool)) < keep]) for _ in range(k - 1)]
+    pipad.set_option("mid_max", 300)
+    pipad.set_option("hub_threshold", segment)
+    pipad.set_option("hub_segment", segment)
+    pipad.set_option("sub_classes", sub)
+    run_case(pipad, n, lists, 16, seed=1)
