@@ -12,8 +12,8 @@
 //
 //   prepare  where every tile starts in every snapshot; D^-1/2; how many rows of every 256 are mid
 //            and hub rows (a row's class is decided by its longest input row alone)
-//   mark     a workgroup per tile: the stretches of the other snapshots are staged in LDS, every base
-//            entry looks itself up in all of them; one bit per base entry says whether it is common,
+//   mark     a workgroup per tile, a wave per snapshot: the base's entries are in LDS, and every other
+//            snapshot walks along them with its own; one bit per base entry says whether it is common,
 //            and the exclusive entries of every snapshot are written out next to each other
 //   scan     prefix sums over the tiles' and the row blocks' counts; with them every data-dependent
 //            size is known and goes to the host
@@ -265,284 +265,357 @@ __global__ __launch_bounds__(kBlock) void k_prepare(Snaps s, Tiles g, RowClasses
 }
 
 // ---- mark -----------------------------------------------------------------------------------
-// A workgroup per tile of T base entries.  The stretches of the other snapshots are all staged in
-// LDS at once, so that one round trip to memory covers them and no barrier stands between the
-// snapshots.  Two steps of search: first every 64th base entry's place in every snapshot (a thread
-// per place, over the whole stretch); between two of these places a wave's 64 entries lie evenly
-// enough that a look-up needs four LDS reads in the 15 places around the interpolated one, and only
-// where some lane does not find its column bracketed there the wave searches all that lies between.
-// Once it is known which base entries are common, their places in the windows get the sign bit, and
-// what has none is exclusive: a wave per snapshot writes it out.
+// A workgroup per tile of T base entries, a wave per snapshot (two for k > 16).  The (row, column) of an
+// entry becomes ONE ascending 32-bit key: the number of the tile's base rows up to its row, times 2n + 2,
+// plus the column (a row that has no base entries in the tile gets keys that no base entry has).  A wave
+// finds the rows of its entries by writing, where a row starts in its stretch, what the row's keys start
+// with, and running a maximum over that; the base's wave puts its keys into LDS.  A lane has 10 entries
+// in a row (8 in the base), so that it looks for the first of them only and walks on from there: a look
+// or two per entry, and a search where the base has more than a few entries in between.  One bit per
+// snapshot and base entry says where that entry was found; who has all of them is common.
+// Tiles that own a longer stretch or more rows than can be gone through, and graphs with more nodes than
+// the keys have room for (4.1 M), find every entry's row by search and take 64-bit keys.
 //
-// Bound by vector-ALU issue: 0.235 G wave instructions on the 1M-node R-MAT frame, which at four
-// cycles each take 0.39 of the kernel's 0.44 ms; 0.75 GB are fetched meanwhile.
-// The tiles took over from byte flags in global memory (cleared, set, packed and counted by four
-// kernels) and a window per wave.
-template <int KM, int T>
-__global__ __launch_bounds__(kBlock) void k_mark(Snaps s, Tiles g, int32_t mid_max) {
-  constexpr int R = T / kBlock;       // base entries per thread
-  constexpr int CAP = T + T / 4;      // longest stretch that is staged; longer ones stay in memory
-  constexpr int WORDS = T / 64;
-  constexpr int U = KM - 1;           // snapshots besides the base
-  __shared__ int32_t rows[T];
-  __shared__ int32_t key_row[WORDS], key_col[WORDS];  // every 64th base entry
-  __shared__ int32_t place[U][WORDS + 1];             // ... and its place in every snapshot
-  __shared__ const int32_t *rp_of[U];
-  __shared__ int32_t start_of[U], len_of[U];
-  __shared__ uint64_t common[WORDS];
-  extern __shared__ int32_t lds[];    // 16 words that are only read, [k - 1][CAP], 16 more
-  int32_t *const wins = lds + 16;
-  const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
-  const int32_t tile = blockIdx.x;
+// Bound by instruction issue and the LDS round trips of the walk: 1M-node R-MAT frame, k = 8, 0.27 ms
+// (0.13 G vector instructions, 0.22 of it), against 0.44 for a look-up of every base entry in every
+// snapshot's window, four waves per tile and a look-up with a row's bounds from memory (0.235 G).
+// N = 200k Chung-Lu, k = 8 87 -> 55 us; R-MAT 100k, k = 5 31 -> 21; N = 20k, k = 4 12.2 -> 8.8; N = 2k 11 -> 7.
+// A number of entries per lane that follows the stretch (8 .. 12, in branches) was slower by 40 %.
+template <int T>
+struct Mark {
+  static constexpr int kRun = T / kWave;           // base entries per lane
+  static constexpr int kMost = kRun + kRun / 4;    // entries of another snapshot per lane
+  static constexpr int kCap = kMost * kWave;       // longest stretch that is taken at once
+  // base entry x lies at plane x % kRun, place x / kRun: lanes that are at neighbouring runs read
+  // neighbouring addresses
+  static constexpr int kPlane = 96;
+  static constexpr int kNone = kWave;              // behind the last entry: plane 0, place 64
+  // the next entry's place in an array of 32-bit words, in bytes: the next plane, or the first one's next place
+  static __device__ __forceinline__ uint32_t next(uint32_t at) {
+    return min(at + kPlane * 4u, at + kPlane * 4u - (kRun * kPlane * 4u - 4u));
+  }
+};
+constexpr int32_t kMarkRows = 4096;                // most rows of a tile that are gone through one by one
+
+__device__ __forceinline__ uint32_t wave_max(uint32_t x) {  // over the lanes up to this one
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false));  // row_shr:1
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false));  // row_shr:2
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false));  // row_shr:4
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false));  // row_shr:8
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false));  // row_bcast:15
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false));  // row_bcast:31
+  return x;
+}
+
+// Places of base entries are in bytes of the array they are looked up in.
+template <class K>
+__device__ __forceinline__ K mark_at(const K *keys, uint32_t at) {
+  return *reinterpret_cast<const K *>(reinterpret_cast<const char *>(keys) + at);
+}
+
+// The base's first entry that is not smaller than `key`, or the last one of a run that holds only
+// smaller ones.
+template <int T, class K>
+__device__ __forceinline__ uint32_t mark_search(const K *keys, K key) {
+  using S = Mark<T>;
+  uint32_t at = 0;
+#pragma unroll
+  for (uint32_t s = kWave / 2; s >= 1; s >>= 1) at += mark_at(keys + s, at) <= key ? s * (uint32_t)sizeof(K) : 0u;
+#pragma unroll
+  for (uint32_t s = S::kRun / 2; s >= 1; s >>= 1)
+    at += mark_at(keys + (s - 1) * S::kPlane, at) < key ? s * S::kPlane * (uint32_t)sizeof(K) : 0u;
+  return at;
+}
+
+// N consecutive entries of a list per lane from `first` on (`all`: every lane's lie inside the list).
+template <int N>
+__device__ __forceinline__ void load_run(const int32_t *col, int32_t nnz, int32_t first, bool all, int32_t (&c)[N]) {
+  typedef int32_t i4 __attribute__((ext_vector_type(4), aligned(4)));
+  if (all) {
+#pragma unroll
+    for (int q = 0; q < N / 4; ++q) {
+      const i4 v = *reinterpret_cast<const i4 *>(col + first + 4 * q);
+      c[4 * q] = v.x; c[4 * q + 1] = v.y; c[4 * q + 2] = v.z; c[4 * q + 3] = v.w;
+    }
+#pragma unroll
+    for (int j = N / 4 * 4; j < N; ++j) c[j] = col[first + j];
+  } else {
+#pragma unroll
+    for (int j = 0; j < N; ++j) c[j] = col[min(first + j, nnz - 1)];
+  }
+}
+
+// Where the base has entry e of snapshot t, which lies in rows [r0, r1].
+template <int T>
+__device__ __forceinline__ uint32_t mark_wide(const Snaps &s, int t, const uint64_t *keys, int32_t r0, int32_t r1, int32_t e) {
+  const uint32_t row = (uint32_t)row_of_entry(s.rowptr[t], r0, r1, e);
+  const uint64_t key = (uint64_t)row << 32 | (uint32_t)s.col[t][e];
+  const uint32_t at = mark_search<T>(keys, key);
+  return mark_at(keys, at) == key ? at / 2 : Mark<T>::kNone * 4;  // (in the array of 32-bit words)
+}
+
+// The base has a column twice in a row (the other snapshots' entries only ever find one of the two).
+template <int T, class K>
+__device__ __forceinline__ bool mark_twice(const K *keys, int32_t here, int lane) {
+  using S = Mark<T>;
+  bool twice = false;
+#pragma unroll
+  for (int j = 0; j < S::kRun; ++j)
+    twice |= (lane * S::kRun + j + 1 < here) & (keys[j * S::kPlane + lane] == keys[(j + 1) % S::kRun * S::kPlane + lane + (j + 1) / S::kRun]);
+  return twice;
+}
+
+template <int T, int L>  // L: snapshots per wave
+__global__ __launch_bounds__(16 * kWave) void k_mark(Snaps s, Tiles g, int32_t mid_max) {
+  using S = Mark<T>;
+  constexpr int R = S::kRun, E = S::kMost, PLANE = S::kPlane;
+  __shared__ uint64_t key_words[R * PLANE];  // 32- or 64-bit keys
+  __shared__ uint32_t present[R * PLANE];    // bit t: snapshot t has the entry (0 behind the last entry)
+  __shared__ uint32_t hub_row[T + 2];        // by number of the base row
+  __shared__ uint32_t shared_of[PIPAD_MAX_K];
+  extern __shared__ uint32_t tags[];         // [k][kCap]
+  uint32_t *const key32 = reinterpret_cast<uint32_t *>(key_words);
+  uint64_t *const key64 = key_words;
+  const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int nwaves = blockDim.x / kWave;
+  // (last tile first: where the ids are sorted by degree, and in R-MAT graphs, the last tiles have the most
+  // rows and take longest: R-MAT, N = 100k, k = 5 25 -> 21 us, 1M nodes 284 -> 272, Chung-Lu a tie)
+  const int32_t tile = g.ntiles - 1 - (int32_t)blockIdx.x;
   const int64_t ldb = (int64_t)g.ntiles + 1;
-  const int32_t *rp0 = s.rowptr[g.base], *col0 = s.col[g.base];
+  const int32_t *rp0 = s.rowptr[g.base];
   const int32_t e0 = tile * T;
   const int32_t here = min(T, s.nnz[g.base] - e0);
   const int32_t r0 = g.brow[tile], r1 = g.brow[tile + 1];
-  const int32_t nrows = r1 - r0 + 1;
-  const int others = g.k - 1;
+  const int32_t rfirst = tile == 0 ? 0 : r0;  // (the first tile owns what lies in front of the base, too)
+  const uint32_t all_bits = ~0u >> (32 - g.k);
+  const int32_t lb = min(lane, g.k - 1);
+  const int32_t my_b0 = g.bound[lb * ldb + tile], my_b1 = g.bound[lb * ldb + tile + 1];
+  for (int x = threadIdx.x; x < R * PLANE; x += blockDim.x) present[x] = x % PLANE < kWave ? 1u << g.base : 0u;
+  for (int x = threadIdx.x; x < T + 2; x += blockDim.x) hub_row[x] = 0;
+  __syncthreads();
 
-  int32_t c[R], row[R];
+  // keys of row number q (1, 2, ..) start at q * mult; those of rows without base entries behind it lie
+  // between its keys and those of row number q + 1 (in any order: nothing of the base lies there)
+  const uint32_t mult = 2u * (uint32_t)g.n + 2u;
+  const bool wide = (uint64_t)g.n >= 0x7fffffffu / (T + 2) || r1 - rfirst >= kMarkRows || __any(my_b1 - my_b0 > S::kCap);
+
+  int32_t start[L], len[L];
+  int32_t c[L][E];     // columns of this lane's entries
+  uint32_t key[L][E];  // ... their keys (of the base: row numbers)
+  uint32_t at[L][E];   // ... and where the base has them
+  bool bad = false;
 #pragma unroll
-  for (int q = 0; q < R; ++q) c[q] = col0[e0 + min(q * kBlock + tid, here - 1)];
-  int32_t bt[U], len[U];
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int t = u + (u >= g.base ? 1 : 0);
-    bt[u] = len[u] = 0;
-    if (t < g.k) {
-      bt[u] = g.bound[t * ldb + tile];
-      len[u] = g.bound[t * ldb + tile + 1] - bt[u];
-    }
+  for (int l = 0; l < L; ++l) {
+    const int t = wave + l * nwaves;
+    if (t >= g.k) break;
+    const int32_t nnz = s.nnz[t];
+    // (the clamps only act on snapshots that are not canonical)
+    start[l] = min(max(__builtin_amdgcn_readlane(my_b0, t), 0), nnz);
+    const int32_t end = __builtin_amdgcn_readlane(my_b1, t);
+    bad |= end < start[l];
+    len[l] = max(min(end, nnz) - start[l], 0);
+    const int per = t == g.base ? R : E;
+    if (len[l] > 0) load_run(s.col[t], nnz, start[l] + lane * per, start[l] + (kWave - 1) * per + E <= nnz, c[l]);
   }
-  // (all loads of the tile are requested before the first one is waited for: indices are clamped
-  // instead of branched around)
-  constexpr int Q = (CAP + kBlock - 1) / kBlock;
-  int32_t wv[U][Q], rv[R];
-  const bool rows_staged = nrows > 1 && nrows <= T;
+
+  if (!wide) {
 #pragma unroll
-  for (int q = 0; q < R; ++q) rv[q] = rp0[r0 + min(q * kBlock + tid, nrows - 1)];
+    for (int l = 0; l < L; ++l) {
+      const int t = wave + l * nwaves;
+      if (t >= g.k) break;
+      const bool base = t == g.base;
+      uint32_t *const tag = tags + t * S::kCap;
 #pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int t = u + (u >= g.base ? 1 : 0);
-    const bool some = t < g.k && len[u] > 0;
-    const int32_t *col = some ? s.col[min(t, g.k - 1)] + bt[u] : col0 + e0;
-    const int32_t last = some ? len[u] - 1 : 0;
+      for (int j = 0; j < E; ++j) tag[j * kWave + lane] = 0;
+      const int32_t *rp = s.rowptr[t];
+      uint32_t rank = 0;
+      constexpr int kAhead = 4;  // times 64 rows whose pointers are requested together
+      struct Rows {
+        int32_t a, b, a0, b0;
+      };
+      auto request = [&](int32_t rb) __attribute__((always_inline)) {
+        const int32_t r = min(rb + lane, r1);
+        return Rows{rp[r], rp[r + 1], rp0[r], rp0[r + 1]};
+      };
+      for (int32_t rb = rfirst; rb <= r1; rb += kAhead * kWave) {
+        Rows rows[kAhead];
 #pragma unroll
-    for (int q = 0; q < Q; ++q) wv[u][q] = col[min(q * kBlock + tid, last)];
-  }
+        for (int u = 0; u < kAhead; ++u)
+          if (rb + u * kWave <= r1) rows[u] = request(rb + u * kWave);
 #pragma unroll
-  for (int u = 0; u < U; ++u)
-    if (tid == u && u < others) {
-      rp_of[u] = s.rowptr[u + (u >= g.base ? 1 : 0)];
-      start_of[u] = bt[u];
-      len_of[u] = len[u];
-    }
-  if (rows_staged)
-#pragma unroll
-    for (int q = 0; q < R; ++q) rows[q * kBlock + tid] = q * kBlock + tid < nrows ? rv[q] : INT32_MAX;
-#pragma unroll
-  for (int u = 0; u < U; ++u)
-    if (u < others)
-#pragma unroll
-      for (int q = 0; q < Q; ++q)
-        if (q * kBlock + tid < CAP) wins[u * CAP + q * kBlock + tid] = wv[u][q];
-  __syncthreads();
-  // rows of this thread's entries
-  if (nrows == 1) {
-#pragma unroll
-    for (int q = 0; q < R; ++q) row[q] = r0;
-  } else if (rows_staged) {
-    int top = 1;
-    while (2 * top <= nrows) top <<= 1;
-    int32_t cnt[R];  // staged row pointers <= e (at least 1, fewer than T)
-#pragma unroll
-    for (int q = 0; q < R; ++q) cnt[q] = 0;
-    for (int step = top; step >= 1; step >>= 1)
-#pragma unroll
-      for (int q = 0; q < R; ++q) {
-        const int32_t v = rows[min(cnt[q] + step, T) - 1];
-        cnt[q] += v <= e0 + min(q * kBlock + tid, here - 1) ? step : 0;
+        for (int u = 0; u < kAhead; ++u) {
+          if (rb + u * kWave > r1) break;
+          const Rows row = rows[u];
+          const bool live = rb + u * kWave + lane <= r1;
+          const bool in_base = live & (max(row.a0, e0) < min(row.b0, e0 + here));
+          const uint64_t mask = __ballot(in_base);
+          const uint32_t q = rank + in_base + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                                                         __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
+          rank += (uint32_t)__popcll(mask);
+          const uint32_t p = (uint32_t)max(row.a - start[l], 0);
+          if (live & ((int32_t)p < min(row.b - start[l], len[l]))) {
+            if (base) tag[p % R * kWave + p / R] = q;
+            else tag[p % E * kWave + p / E] = __umul24(q, mult) + (in_base ? 0u : mult / 2u);
+          }
+          if (in_base & (row.b - row.a > mid_max)) hub_row[q] = 1;
+        }
       }
+      // what lies behind the list comes behind all of the base
+      if (!base && lane == 0 && len[l] < S::kCap) tag[len[l] % E * kWave + len[l] / E] = T * mult + mult / 2u;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      uint32_t most = 0;
 #pragma unroll
-    for (int q = 0; q < R; ++q) row[q] = r0 + min(max(cnt[q], 1), nrows) - 1;
-  } else {
+      for (int j = 0; j < E; ++j) {
+        most = max(most, tag[j * kWave + lane]);
+        key[l][j] = most;
+      }
+      const uint32_t front = __shfl_up(wave_max(most), 1, kWave);
+      most = lane > 0 ? front : 0u;
+      if (base) {
 #pragma unroll
-    for (int q = 0; q < R; ++q)
-      row[q] = row_of_entry(rp0, r0, r1, e0 + min(q * kBlock + tid, here - 1));
-  }
+        for (int j = 0; j < R; ++j) {
+          key[l][j] = max(key[l][j], most);
+          key32[j * PLANE + lane] = lane * R + j < here ? __umul24(key[l][j], mult) + (uint32_t)c[l][j] : ~0u;
+        }
+        if (lane == 0) key32[S::kNone] = ~0u;
+      } else {
 #pragma unroll
-  for (int q = 0; q < R; ++q)
-    if (lane == 0) {
-      key_row[q * kWavesPerBlock + wave] = row[q];
-      key_col[q * kWavesPerBlock + wave] = c[q];
-    }
-  int32_t lo[U][R], hi[U][R];
-  bool found[R], hub[R];
-#pragma unroll
-  for (int q = 0; q < R; ++q) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int t = u + (u >= g.base ? 1 : 0);
-      const int32_t *rp = s.rowptr[min(t, g.k - 1)];
-      lo[u][q] = rp[row[q]];
-      hi[u][q] = rp[row[q] + 1];
-    }
-    found[q] = q * kBlock + tid < here;
-    hub[q] = rp0[row[q] + 1] - rp0[row[q]] > mid_max;
-  }
-  __syncthreads();
-  // places of every 64th entry (a word past the tile's end lies at the stretch's end)
-  for (int x = tid; x < others * (WORDS + 1); x += kBlock) {
-    const int u = x / (WORDS + 1), w = x - u * (WORDS + 1);
-    const int32_t l = len_of[u];
-    int32_t at = 0;
-    if (w * 64 >= here) {
-      at = l;
-    } else if (w > 0 && l <= CAP) {
-      const int32_t *rp = rp_of[u], *win = wins + u * CAP;
-      const int32_t i = key_row[w], cc = key_col[w];
-      const int32_t f0 = max(rp[i] - start_of[u], 0), f1 = min(rp[i + 1] - start_of[u], l);
-      at = f0;
-#pragma unroll
-      for (int step = T; step >= 1; step >>= 1) {
-        const int32_t idx = at + step - 1;
-        const int32_t v = win[min(idx, CAP - 1)];
-        at += (idx < f1) & (v < cc) ? step : 0;
+        for (int j = 0; j < E; ++j) key[l][j] = max(key[l][j], most) + (uint32_t)c[l][j];
       }
     }
-    place[u][w] = min(max(at, 0), l);
-  }
-  __syncthreads();
-  int32_t pos[U][R];
+    __syncthreads();
 #pragma unroll
-  for (int u = 0; u < U; ++u) {
-    if (u >= others) break;
-    const int32_t *win = wins + u * CAP;
-    const bool staged = len[u] <= CAP;
+    for (int l = 0; l < L; ++l) {
+      const int t = wave + l * nwaves;
+      if (t >= g.k) break;
+      if (t == g.base) bad |= mark_twice<T>(key32, here, lane);
+      if (t == g.base || len[l] == 0) continue;
+      uint32_t x = mark_search<T>(key32, key[l][0]), v = mark_at(key32, x);
 #pragma unroll
-    for (int q = 0; q < R; ++q) {
-      pos[u][q] = 0;
-      hub[q] |= hi[u][q] - lo[u][q] > mid_max;
-      if (!__any(found[q])) continue;
-      if (staged) {
-        // (places in bytes from here on: an LDS address is one addition away)
-        const int w = q * kWavesPerBlock + wave;
-        const int32_t w0 = __builtin_amdgcn_readfirstlane(place[u][w]);
-        const int32_t w1 = max(__builtin_amdgcn_readfirstlane(place[u][w + 1]), w0);
-        const int32_t p0 = w0 * 4, p1 = w1 * 4;
-        const char *const wb = reinterpret_cast<const char *>(win);
-        auto at = [&](int32_t byte) { return *reinterpret_cast<const int32_t *>(wb + byte); };
-        // the part of the row's stretch that can hold the entry
-        const int32_t f0 = min(max(lo[u][q] - bt[u], w0), w1) * 4, end = min(max(hi[u][q] - bt[u], w0), w1) * 4;
-        const int32_t guess = p0 + ((__mul24(p1 - p0, lane) >> 6) & ~3) - 28;
-        int32_t a = max(min(guess, end - 60), f0);
-        int32_t z = min(a + 60, end);
-        const bool in_front = (a == f0) | (at(a - 4) < c[q]);
-        const bool behind = (z >= end) | (at(z) >= c[q]);
-        int step = 32;
-        if (__any(found[q] & !(in_front & behind))) {
-          a = f0;
-          z = end;
-          step = 4 << (31 - __builtin_clz(((p1 - p0) >> 2) + 1));
-          for (; step > 32; step >>= 1) {
-            const int32_t v = at(min(a + step, z) - 4);
-            a += v < c[q] ? step : 0;
-            a = min(a, max(z, f0));
+      for (int j = 0; j < E; ++j) {
+        const uint32_t k0 = key[l][j];
+        int looks = 6;
+        while (__builtin_amdgcn_ballot_w64(v < k0) != 0) {
+          if (v < k0) {
+            x = S::next(x);
+            v = mark_at(key32, x);
+          }
+          if (--looks == 0) {
+            x = mark_search<T>(key32, k0);
+            v = mark_at(key32, x);
           }
         }
-        // (a look past z reads the last column in front of it: if that is smaller, so are all, and the
-        // final min() puts the place at z)
-#pragma unroll
-        for (int s4 = 32; s4 >= 4; s4 >>= 1) {
-          const int32_t v = at(min(a + s4, z) - 4);
-          a += v < c[q] ? s4 : 0;
+        at[l][j] = S::kNone * 4u;
+        if (v == k0) {
+          at[l][j] = x;
+          __hip_atomic_fetch_or(present + x / 4u, 1u << t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
-        a = min(a, max(z, f0));
-        found[q] = found[q] & (a < end) & (at(a) == c[q]);
-        pos[u][q] = a >> 2;
-      } else if (found[q]) {
-        const int32_t *col = s.col[u + (u >= g.base ? 1 : 0)] + bt[u];
-        const int32_t f0 = max(lo[u][q] - bt[u], 0), f1 = min(hi[u][q] - bt[u], len[u]);
-        const int32_t a = f0 < f1 ? lower_bound(col, f0, f1, c[q]) : f1;
-        found[q] = a < f1 && col[a] == c[q];
       }
     }
-  }
-
+  } else {
 #pragma unroll
-  for (int q = 0; q < R; ++q) {
-    const uint64_t word = __ballot(found[q]), hubs = __ballot(hub[q]);
-    const int w = q * kWavesPerBlock + wave;
-    if (lane == 0) {
-      common[w] = word;
-      key_row[w] = __popcll(word & hubs);
-      if (w * 64 < here) {
-        const int64_t at = ((int64_t)tile << (g.tile_log2 - 6)) + w;
-        g.bits[at] = word;
-        g.hub_bits[at] = hubs;
+    for (int l = 0; l < L; ++l) {
+      const int t = wave + l * nwaves;
+      if (t != g.base) continue;
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+        const int32_t x = lane * R + j;
+        const int32_t row = row_of_entry(rp0, r0, r1, e0 + min(x, here - 1));
+        key64[j * PLANE + lane] = x < here ? (uint64_t)(uint32_t)row << 32 | (uint32_t)c[l][j] : ~0ull;
+        uint32_t hub = 0;
+        for (int u = 0; u < g.k; ++u) hub |= s.rowptr[u][row + 1] - s.rowptr[u][row] > mid_max;
+        hub_row[x] = hub;
+        key[l][j] = (uint32_t)x;
       }
     }
-  }
-  __syncthreads();  // nobody searches the windows any more
-  uint32_t total = 0, in_hubs = 0;  // common entries of the tile (every thread)
+    __syncthreads();
 #pragma unroll
-  for (int w = 0; w < WORDS; ++w) {
-    if (tid == w && w * 64 < here) g.wpre[((int64_t)tile << (g.tile_log2 - 6)) + w] = (uint16_t)total;
-#pragma unroll
-    for (int q = 0; q < R; ++q)  // exclusive entries of the base
-      if (w == q * kWavesPerBlock + wave) {
-        const uint32_t x = q * kBlock + tid;
-        if ((int32_t)x < here && !found[q])
-          g.excl[g.base][e0 + x - total - (uint32_t)__popcll(common[w] & ((1ull << lane) - 1ull))] = c[q];
+    for (int l = 0; l < L; ++l) {
+      const int t = wave + l * nwaves;
+      if (t >= g.k) break;
+      if (t == g.base) {
+        bad |= mark_twice<T>(key64, here, lane);
+        continue;
       }
-    total += (uint32_t)__popcll(common[w]);
-    in_hubs += (uint32_t)key_row[w];
-  }
-  if (tid == 0) g.tile_cnt[tile] = make_uint2(total, in_hubs);
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    if (u >= others) break;
-    if (len[u] <= CAP)
-#pragma unroll
-      for (int q = 0; q < R; ++q)
-        if (found[q]) wins[u * CAP + pos[u][q]] = c[q] | INT32_MIN;
+      for (int32_t p = lane; p - lane < len[l]; p += kWave) {
+        const uint32_t x = p < len[l] ? mark_wide<T>(s, t, key64, rfirst, r1, start[l] + p) : S::kNone * 4u;
+        if (x != S::kNone * 4u)
+          __hip_atomic_fetch_or(present + x / 4u, 1u << t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (len[l] <= S::kCap) tags[t * S::kCap + p] = x;
+      }
+    }
   }
   __syncthreads();
 
-  // exclusive entries of the other snapshots: a wave per snapshot
-  bool bad = false;
-  for (int u = wave; u < others; u += kWavesPerBlock) {
-    const int t = __builtin_amdgcn_readfirstlane(u + (u >= g.base ? 1 : 0));
-    const int32_t start = __builtin_amdgcn_readfirstlane(start_of[u]), l = __builtin_amdgcn_readfirstlane(len_of[u]);
-    bad |= l < 0;
-    int32_t *out = g.excl[t] + start;
-    const int32_t *col = s.col[t] + start;
-    int32_t kept = 0;
-    for (int32_t w = 0; w * 64 < l; ++w) {
-      const int32_t p = w * 64 + lane;
-      bool is = false;
-      int32_t v = 0;
-      if (l <= CAP) {
-        v = wins[u * CAP + min(p, CAP - 1)];
-        is = p < l && v >= 0;
-      } else if (p < l) {  // a stretch that was not staged: look the entry up in the base
-        v = col[p];
-        const int32_t i = row_of_entry(s.rowptr[t], 0, g.n - 1, start + p);
-        const int32_t a = max(rp0[i], e0), b = min(rp0[i + 1], e0 + here);
-        const int32_t at = a < b ? lower_bound(col0, a, b, v) : b;
-        is = !(at < b && col0[at] == v && (common[(at - e0) >> 6] >> ((at - e0) & 63) & 1ull));
+#pragma unroll
+  for (int l = 0; l < L; ++l) {
+    const int t = wave + l * nwaves;
+    if (t >= g.k) break;
+    int32_t *const out = g.excl[t] + start[l];
+    if (t == g.base) {
+      const int32_t mine = min(here - lane * R, R);
+      uint32_t common = 0, hub = 0;
+#pragma unroll
+      for (int j = 0; j < R; ++j)
+        if (j < mine) {
+          common |= (uint32_t)(present[j * PLANE + lane] == all_bits) << j;
+          hub |= hub_row[key[l][j]] << j;
+        }
+      const uint32_t cnt = (uint32_t)__popc(common), incl = wave_sum(cnt);
+      const uint32_t in_hubs = wave_sum((uint32_t)__popc(common & hub));
+      const uint32_t common2 = common | __shfl_down(common, 1, kWave) << R, hub2 = hub | __shfl_down(hub, 1, kWave) << R;
+      const int32_t word0 = (tile << (g.tile_log2 - 6)), word = lane * R / 64;  // of this lane's entries
+      if (word * 64 < here) {
+        if (lane * R % 64 == 0) g.wpre[word0 + word] = (uint16_t)(incl - cnt);
+        uint8_t *const bits = reinterpret_cast<uint8_t *>(g.bits + word0), *const hubs = reinterpret_cast<uint8_t *>(g.hub_bits + word0);
+        if (R == 8) {
+          bits[lane] = (uint8_t)common;
+          hubs[lane] = (uint8_t)hub;
+        } else if ((lane & 1) == 0) {  // (four entries per lane)
+          bits[lane / 2] = (uint8_t)common2;
+          hubs[lane / 2] = (uint8_t)hub2;
+        }
       }
-      const uint64_t word = __ballot(is);
-      if (is)
-        out[kept + (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(word >> 32),
-                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)word, 0))] = v;
-      kept += (int32_t)__popcll(word);
+      if (lane == kWave - 1) {
+        g.tile_cnt[tile] = make_uint2(incl, in_hubs);
+        shared_of[t] = incl;
+      }
+      uint32_t to = lane * R - (incl - cnt);
+#pragma unroll
+      for (int j = 0; j < R; ++j)
+        if ((j < mine) & !(common >> j & 1u)) out[to++] = c[l][j];
+    } else if (!wide) {
+      const int32_t mine = min(max(len[l] - lane * E, 0), E);
+      uint32_t excl = 0;
+      if (len[l] > 0)
+#pragma unroll
+        for (int j = 0; j < E; ++j) excl |= mark_at(present, at[l][j]) != all_bits ? 1u << j : 0u;
+      excl &= (1u << mine) - 1u;
+      const uint32_t cnt = (uint32_t)__popc(excl), incl = wave_sum(cnt);
+      uint32_t to = incl - cnt;
+#pragma unroll
+      for (int j = 0; j < E; ++j)
+        if (excl >> j & 1u) out[to++] = c[l][j];
+      if (lane == kWave - 1) shared_of[t] = (uint32_t)len[l] - incl;
+    } else {
+      uint32_t kept = 0;
+      const int32_t *col = s.col[t] + start[l];
+      for (int32_t p = lane; p - lane < len[l]; p += kWave) {
+        uint32_t x = S::kNone * 4u;
+        if (p < len[l]) x = len[l] <= S::kCap ? tags[t * S::kCap + p] : mark_wide<T>(s, t, key64, rfirst, r1, start[l] + p);
+        const bool is = p < len[l] && mark_at(present, x) != all_bits;
+        const uint64_t word = __ballot(is);
+        if (is)
+          out[kept + __builtin_amdgcn_mbcnt_hi((uint32_t)(word >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)word, 0))] = col[p];
+        kept += (uint32_t)__popcll(word);
+      }
+      if (lane == 0) shared_of[t] = (uint32_t)len[l] - kept;
     }
-    // In canonical snapshots every common entry is found once in each of them; anything else is
-    // reported, so that what follows never writes past the sizes computed from these counts.
-    bad |= (uint32_t)(l - kept) != total;
   }
+  // In canonical snapshots every common entry is found once in each of them; anything else is
+  // reported, so that what follows never writes past the sizes computed from these counts.
+  __syncthreads();
+  if (wave == 0 && lane < g.k) bad |= shared_of[lane] != shared_of[g.base];
   if (bad) *g.bad = 1;
 }
 
@@ -1510,8 +1583,8 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
   g.n = n;
   g.k = k;
   g.base = base;
-  // the stretches of all snapshots but the base are in LDS at once: 18 KB for k = 8, 38 KB for
-  // k = 16 with tiles of 512 entries; more snapshots get smaller tiles
+  // k_mark takes 4 bytes of LDS per entry of all stretches (20 KB for k = 8, 41 KB for k = 16 with tiles of
+  // 512 entries) and 11 KB per tile; more snapshots get smaller tiles
   g.tile_log2 = k <= 16 ? 9 : 8;
   g.ntiles = (int32_t)(((int64_t)s.nnz[base] + (1 << g.tile_log2) - 1) >> g.tile_log2);
 
@@ -1579,11 +1652,10 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
   hipLaunchKernelGGL(k_prepare, dim3((unsigned)(bound_blocks + row_blocks)), dim3(kBlock), 0, st, s, g, row_classes(f),
                      bound_blocks, f->dinv, f->dinv_nk);
   if (g.ntiles > 0) {
-    const int tile = 1 << g.tile_log2;
-    const size_t lds = ((size_t)(k - 1) * (tile + tile / 4) + 32) * sizeof(int32_t);
-    // instances by the most snapshots they handle: fewer snapshots, fewer registers, more waves per CU
-    auto mark = k <= 4 ? k_mark<4, 512> : k <= 8 ? k_mark<8, 512> : k <= 16 ? k_mark<16, 512> : k_mark<32, 256>;
-    hipLaunchKernelGGL(mark, dim3((unsigned)g.ntiles), dim3(kBlock), lds, st, s, g, f->mid_max);
+    const int cap = k <= 16 ? Mark<512>::kCap : Mark<256>::kCap, waves = k <= 16 ? k : (k + 1) / 2;
+    auto mark = k <= 16 ? k_mark<512, 1> : k_mark<256, 2>;
+    hipLaunchKernelGGL(mark, dim3((unsigned)g.ntiles), dim3((unsigned)(waves * kWave)), (size_t)k * cap * sizeof(uint32_t),
+                       st, s, g, f->mid_max);
   }
   const TotalsTicket ticket = expect_totals(totals);
   {
