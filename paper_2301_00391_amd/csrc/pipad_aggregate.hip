@@ -286,7 +286,12 @@ __device__ __forceinline__ Raw fetch_entry(const Lists &l, int32_t cs, int32_t c
 // (One walk over both lists instead of one each: most rows have only a few exclusive entries, and a
 // walk of their own cost them a whole round of gathers.)
 // The FAST inner loop needs nslots * UNR to divide team_lanes * EPL.
-template <int VEC, int UNR, bool FAST, int EPL>
+// ALONE: a lane takes exactly the entries that it fetches (one lane per row and snapshot, so that the lane
+// groups are the lanes of the team): nothing goes through LDS, whose bank conflicts took a third of the
+// coalescent kernel's time.  Same order of the sum.  N = 200k, k = 8, concatenated, F = 1 / 2 / 4 102 / 107 /
+// 111 -> 97 / 102 / 107 us; R-MAT 60k, k = 5 29 / 32.5 / 33.8 -> 27.7 / 30.8 / 32.4, 1M, k = 8 534 / 588 / 627 ->
+// 532 / 576 / 619; one matrix per snapshot, F = 1 and 4: 0 to 4 %.
+template <int VEC, int UNR, bool FAST, int EPL, bool ALONE = false>
 __device__ __forceinline__ void walk(const Lists &l, int32_t cs, int32_t clen, int32_t ds, int32_t len,
                             const Raw (&first)[EPL],
                             int team_base, int team_lanes,
@@ -310,6 +315,23 @@ __device__ __forceinline__ void walk(const Lists &l, int32_t cs, int32_t clen, i
 #pragma unroll
       for (int j = 0; j < EPL; ++j)
         next[j] = fetch_entry(l, cs, clen, ds, len, base + chunk + j * team_lanes + q, self, nt);
+    if constexpr (ALONE) {
+      static_assert(FAST, "");
+      typename VT::T x[EPL];
+#pragma unroll
+      for (int j = 0; j < EPL; ++j) {
+#ifdef PIPAD_NO_GATHER
+        x[j] = VT::zero();
+#else
+        x[j] = VT::load(reinterpret_cast<const float *>(xbytes + ((uint32_t)mine[j].c * row_bytes + lane_bytes)));
+#endif
+      }
+#pragma unroll
+      for (int j = 0; j < EPL; ++j) VT::fma(acc, mine[j].w, x[j]);
+#pragma unroll
+      for (int j = 0; j < EPL; ++j) mine[j] = next[j];
+      continue;
+    }
 #pragma unroll
     for (int j = 0; j < EPL; ++j) {
       Staged st;
@@ -486,7 +508,7 @@ __device__ __forceinline__ float *partial_slot(const AggArgs &a, int slice_seq, 
 // A wave-wide team has 64 / LS lane groups and a chunk of 64 * EPL entries, EPL >= 4 / LS (launch()).
 static_assert(PIPAD_AGG_DEPTH <= 4, "more gathers in flight than a chunk holds");
 
-template <int VEC, bool FAST, int EPL, bool UPD>
+template <int VEC, bool FAST, int EPL, bool UPD, bool ALONE = false>
 __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
   using VT = V<VEC>;
   static_assert(!UPD || (VEC == 4 && FAST), "the fused update rides on the fast float4 path");
@@ -694,7 +716,7 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
     if (step + 1 < nsteps) nxt = prefetch(step + 1);
     typename VT::T acc = VT::zero();
     if (wide) {
-      walk<VEC, U, FAST>(lists, cur.cs, cur.clen, cur.ds, cur.len, cur.first, team_base, team_lanes, q, slot, nslots,
+      walk<VEC, U, FAST, EPL, ALONE>(lists, cur.cs, cur.clen, cur.ds, cur.len, cur.first, team_base, team_lanes, q, slot, nslots,
                           s, a.ldx, cur.i, ntl, lds, acc);
       reduce_slots<VEC>(a.ls_log2, acc);
       if (split) {
@@ -708,7 +730,7 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
       }
     } else {
       if (cur.have)
-        walk<VEC, U, FAST>(lists, cur.cs, cur.clen, cur.ds, cur.len, cur.first, team_base, team_lanes, q, slot, nslots,
+        walk<VEC, U, FAST, EPL, ALONE>(lists, cur.cs, cur.clen, cur.ds, cur.len, cur.first, team_base, team_lanes, q, slot, nslots,
                             s, a.ldx, cur.i, ntl, lds, acc);
       if constexpr (UPD) {
         if (cur.have) finish_row_to_sink(a, s, sink, sink.cnt + team, fl, cur.i, cur.di, cur.xi, acc);
@@ -728,10 +750,10 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
 // EPL: entries per lane and chunk; teams of 8 lanes and more get on with 1.  (Teams of 1 and 2 lanes with
 // one entry per lane, fetched and gathered one after the other: N = 500k, k = 4, F = 4 486 us, with 4
 // entries 375; 8 entries take too many registers.)
-template <int VEC, bool FAST, int EPL>
+template <int VEC, bool FAST, int EPL, bool ALONE = false>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(PIPAD_AGG_WAVES)))
 void k_aggregate(const AggArgs a) {
-  aggregate_body<VEC, FAST, EPL, false>(a);
+  aggregate_body<VEC, FAST, EPL, false, ALONE>(a);
 }
 
 // The same walk with the update fused in, held to the four waves per SIMD that its 120 registers allow
@@ -972,7 +994,7 @@ __device__ __forceinline__ float *unit_partial(const AggArgs &a, int g, int64_t 
   return a.partial + col0 * (a.n_items * parts) + (unit * parts + cls) * width - col0;
 }
 
-template <int VEC, int EPL>
+template <int VEC, int EPL, bool ALONE>
 __global__ __launch_bounds__(kBlock) void k_aggregate_coalescent(const AggArgs a) {
   using VT = V<VEC>;
   constexpr int U = 4;  // row gathers in flight per lane
@@ -1102,7 +1124,7 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_coalescent(const AggArgs a
   };
   auto walk_item = [&](const CoalItem &it, const Fetched &f) __attribute__((always_inline)) {
     typename VT::T acc = VT::zero();
-    walk<VEC, U, true>(lists, it.cs, it.clen, it.ds, it.len, f.e, team_base, team_lanes, q, slot, nslots, s,
+    walk<VEC, U, true, EPL, ALONE>(lists, it.cs, it.clen, it.ds, it.len, f.e, team_base, team_lanes, q, slot, nslots, s,
                        a.ldx, it.i, false, lds, acc);
     return acc;
   };
@@ -1240,8 +1262,10 @@ int launch(const AggArgs &a, bool fast, hipStream_t st, bool fused_update = fals
       hipLaunchKernelGGL((k_aggregate<VEC, true, 1>), grid, block, 0, st, a);
     else if (a.ls_log2 == 2)
       hipLaunchKernelGGL((k_aggregate<VEC, true, 2>), grid, block, 0, st, a);
-    else
+    else if (a.ls_log2 == 1)
       hipLaunchKernelGGL((k_aggregate<VEC, true, 4>), grid, block, 0, st, a);
+    else
+      hipLaunchKernelGGL((k_aggregate<VEC, true, 4, true>), grid, block, 0, st, a);
   }
   if (fin > 0) hipLaunchKernelGGL((k_split_finish<VEC>), dim3((unsigned)fin), dim3(kBlock), 0, st, a);
   PIPAD_HIP(hipGetLastError());
@@ -1281,10 +1305,10 @@ int launch_coalescent(const AggArgs &a, hipStream_t st) {
   const int64_t blocks = (wide + a.blocks_mid + a.blocks_short) * a.nslices;
   if (blocks >= ((int64_t)1 << 31)) return PIPAD_ERR_TOO_LARGE;
   // entries per fetching lane, so that a chunk holds U = 4 and more for every lane group: 4 for one or
-  // two lanes per snapshot (F <= 4), 2 for two and more
-  auto kern = k_aggregate_coalescent<VEC, 4>;
+  // two lanes per snapshot (F <= 4), 2 for two and more; F == VEC is one lane per snapshot
+  auto kern = a.F == VEC ? k_aggregate_coalescent<VEC, 4, true> : k_aggregate_coalescent<VEC, 4, false>;
   if constexpr (VEC == 4)
-    if (a.F > 4) kern = k_aggregate_coalescent<VEC, 2>;
+    if (a.F > 4) kern = k_aggregate_coalescent<VEC, 2, false>;
   if (blocks > 0) hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kBlock), 0, st, a);
   if (a.n_hub > 0) {
     const int64_t hb = ((int64_t)a.n_hub + kWavesPerBlock - 1) / kWavesPerBlock * a.nslices;
