@@ -982,7 +982,7 @@ struct SplitArgs {
   int32_t *sptr, *scol_c, *scol_d;
   float *swc[PIPAD_MAX_K];
   float *swd;
-  int32_t block_off[PIPAD_MAX_K + 2];      // first workgroup of every part
+  int32_t block_off[PIPAD_MAX_K + 2];      // first workgroup of every part, in their natural order
   uint64_t whole;                          // bit p: part p takes a workgroup per unit, not a wave
 };
 
@@ -1171,8 +1171,11 @@ __device__ __forceinline__ void fill_part(const SplitArgs &g, int32_t u, int p, 
 // (build_split_arrays): a wave alone goes through 2048 entries in 32 steps of memory round trips, and on
 // all but the largest frames there are too few of them to hide that.  A wave per unit of every part took
 // 35 us on an R-MAT frame with N = 100k, k = 5, now 14; N = 200k Chung-Lu, k = 8 28, now 21.  On the
-// 1M-node R-MAT frame 0.25 ms either way: 0.75 GB fetched, most of it lines of D^-1/2 for a few scales
-// each, and 0.36 GB written: 4.4 TB/s, the rate of a plain copy.  A kernel for the scales alone that
+// 1M-node R-MAT frame 0.25 ms either way: most of what is fetched are lines of D^-1/2 for a few scales
+// each, and 0.36 GB are written.
+// An XCD takes a run of the exclusive parts' units, so that it reads one or two snapshots' D^-1/2 instead
+// of all: N = 200k, k = 8 60 -> 38 MB fetched, 21 -> 18.5 us; R-MAT 1M 250 -> 242; N = 100k 14 -> 13.2.  (The same in
+// k_scatter fetches a quarter less and takes as long: the L2s' requests bound it, one per gathered scale.)  A kernel for the scales alone that
 // runs every class on the XCD that gathers it later fetches a third of that but shares the lines it
 // writes between XCDs, and the two together were slower (0.26 ms).
 template <int NC>
@@ -1181,8 +1184,14 @@ __global__ __launch_bounds__(kBlock) void k_split_fill(SplitArgs g) {
   __shared__ int32_t s_cnt[kWavesPerBlock][NC], s_off[kWavesPerBlock][NC];
   const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   int p = 0;
-  while (p < g.k && (int32_t)blockIdx.x >= g.block_off[p + 1]) ++p;
-  const int32_t b = (int32_t)blockIdx.x - g.block_off[p];
+  int32_t b = blockIdx.x;
+  if (b >= align_xcd(g.block_off[1])) {
+    b = g.block_off[1] + xcd_run(b - align_xcd(g.block_off[1]), g.block_off[g.k + 1] - g.block_off[1]);
+    while (p < g.k + 1 && b >= g.block_off[p + 1]) ++p;
+  }
+  if (p > g.k) return;
+  b -= g.block_off[p];
+  if (p == 0 && b >= g.block_off[1]) return;
   if (g.whole >> p & 1ull) {
     fill_part<NC, kWavesPerBlock>(g, b, p, lane, wave, stage, s_cnt, s_off[0]);
   } else {
@@ -1531,7 +1540,8 @@ int build_split_arrays(pipad_frame *f, hipStream_t st) {
     blocks += whole ? f->n_items : (f->n_items + kWavesPerBlock - 1) / kWavesPerBlock;
   }
   g.block_off[f->k + 1] = blocks;
-  hipLaunchKernelGGL(fill, dim3((unsigned)blocks), dim3(kBlock), 0, st, g);
+  const int32_t excl = blocks - g.block_off[1];
+  hipLaunchKernelGGL(fill, dim3((unsigned)(align_xcd(g.block_off[1]) + align_xcd(excl))), dim3(kBlock), 0, st, g);
   PIPAD_HIP(hipGetLastError());
   return PIPAD_OK;
 }

@@ -234,6 +234,15 @@ __host__ __device__ inline uint32_t column_class(int32_t j, int sub_log2) {
 constexpr int kClasses = 8;      // XCDs of the chip
 constexpr int kMaxSubLog2 = 2;   // at most 4 sub classes per XCD
 
+// Workgroup b of a launch runs on XCD b mod 8.  `blocks` pieces of work are launched as align_xcd(blocks)
+// workgroups (from a multiple of 8 on); xcd_run gives workgroup b of them its piece so that an XCD has a
+// run of consecutive pieces, and with them a share of what the pieces read in common (pieces from `blocks` on
+// do not exist).
+__host__ __device__ inline int32_t align_xcd(int32_t blocks) { return (blocks + kClasses - 1) / kClasses * kClasses; }
+__device__ inline int32_t xcd_run(int32_t b, int32_t blocks) {
+  return b % kClasses * (align_xcd(blocks) / kClasses) + b / kClasses;
+}
+
 // Inclusive sum over the lanes up to this one: within rows of 16 lanes, then across the rows.
 __device__ __forceinline__ uint32_t wave_sum(uint32_t x) {
   x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);  // row_shr:1
