@@ -297,16 +297,6 @@ struct Mark {
 };
 constexpr int32_t kMarkRows = 4096;                // most rows of a tile that are gone through one by one
 
-__device__ __forceinline__ uint32_t wave_max(uint32_t x) {  // over the lanes up to this one
-  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false));  // row_shr:1
-  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false));  // row_shr:2
-  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false));  // row_shr:4
-  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false));  // row_shr:8
-  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false));  // row_bcast:15
-  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false));  // row_bcast:31
-  return x;
-}
-
 // Places of base entries are in bytes of the array they are looked up in.
 template <class K>
 __device__ __forceinline__ K mark_at(const K *keys, uint32_t at) {

@@ -17,7 +17,8 @@
 //              count of that digit on.  With the waves' counts summed up the tile goes to LDS in
 //              digit order and is written out in that order, neighbouring lanes to neighbouring
 //              addresses (direct stores would go to 64 different places each).  The first pass
-//              reads the part's columns in place and finds the entries' rows itself
+//              reads the part's columns in place and finds the entries' rows itself: where a row starts
+//              goes to LDS, a running maximum gives every entry its row
 //
 // The sorted columns then give the row pointers (every change of the column is a row's start) in the
 // kernel that writes the entries' scales.
@@ -34,6 +35,7 @@ constexpr int kMaxDigitBits = 10;
 constexpr int kMaxDigits = 1 << kMaxDigitBits;
 constexpr int kSortBlock = 512;                      // threads per workgroup of the sort
 constexpr int kSortWaves = kSortBlock / kWave;
+constexpr int32_t kRowsWalked = 4096;                // a wave's entries find their rows by going through so many at most
 
 struct SortArgs {
   int32_t nparts;                       // 1 + k
@@ -49,6 +51,9 @@ struct SortArgs {
   int32_t *key_out, *val_out;
   uint32_t *hist;                       // [tiles][digits]
   uint32_t *total;                      // [nparts][digits] entries per digit value
+  const float4 *dinv_from;              // first pass: D^-1/2, copied by workgroups behind the tiles'
+  float4 *dinv_to;
+  int64_t dinv_pieces;                  // of 16 bytes
 };
 
 // Part that holds position e of a concatenated array with the given part offsets.
@@ -83,6 +88,13 @@ __device__ inline const int32_t *tile_keys(const SortArgs &g, const TileRange &r
 template <int R>
 __global__ __launch_bounds__(kSortBlock) void k_radix_hist(SortArgs g) {
   __shared__ uint32_t cnt[kMaxDigits];
+  const uint32_t tiles = g.tile_off[g.nparts];
+  if (blockIdx.x >= tiles) {  // (5 us as a copy of its own, here hardly any)
+    const int64_t step = (int64_t)(gridDim.x - tiles) * kSortBlock;
+    for (int64_t x = (int64_t)(blockIdx.x - tiles) * kSortBlock + threadIdx.x; x < g.dinv_pieces; x += step)
+      g.dinv_to[x] = g.dinv_from[x];
+    return;
+  }
   const TileRange r = tile_range<R>(g, blockIdx.x);
   const int digits = 1 << g.bits;
   for (int d = threadIdx.x; d < digits; d += kSortBlock) cnt[d] = 0;
@@ -101,7 +113,8 @@ __global__ __launch_bounds__(kSortBlock) void k_radix_hist(SortArgs g) {
 
 // A lane per digit value (64 of them per workgroup, grid.y = part): its counts in the part's tiles are
 // summed up over the tiles in front.  The tiles are dealt to the waves in runs: each sums up its run,
-// then goes through it again from what the runs in front hold.
+// then goes through it again from what the runs in front hold.  Bound by its round trips to memory: with the
+// counts of up to 32 tiles kept in registers in between 5.6 us, loaded twice, eight at a time, 7.8 (840 tiles).
 constexpr int kScanWaves = 16;
 __global__ __launch_bounds__(kScanWaves * kWave) void k_radix_scan(SortArgs g) {
   __shared__ uint32_t sums[kScanWaves][kWave];
@@ -112,9 +125,18 @@ __global__ __launch_bounds__(kScanWaves * kWave) void k_radix_scan(SortArgs g) {
   const uint32_t run = (tiles + kScanWaves - 1) / kScanWaves;
   const uint32_t t0 = min(wave * run, tiles), t1 = min(t0 + run, tiles);
   uint32_t *hist = g.hist + ((uint64_t)g.tile_off[p] << g.bits) + dc;
-  constexpr int UN = 8;  // loads in flight
+  constexpr int UN = 8;      // loads in flight together
+  constexpr uint32_t KEEP = 32;  // counts of the run that stay in registers between the two goes
   uint32_t sum = 0;
-  for (uint32_t t = t0; t < t1; t += UN) {
+  uint32_t kept[KEEP];
+#pragma unroll
+  for (uint32_t u = 0; u < KEEP; u += UN)
+    if (t0 + u < t1)
+#pragma unroll
+      for (uint32_t q = u; q < u + UN; ++q) kept[q] = hist[(uint64_t)min(t0 + q, t1 - 1) << g.bits];
+#pragma unroll
+  for (uint32_t q = 0; q < KEEP; ++q) sum += t0 + q < t1 ? kept[q] : 0u;
+  for (uint32_t t = t0 + KEEP; t < t1; t += UN) {
     uint32_t c[UN];
 #pragma unroll
     for (int q = 0; q < UN; ++q) c[q] = hist[(uint64_t)min(t + q, t1 - 1) << g.bits];
@@ -130,7 +152,13 @@ __global__ __launch_bounds__(kScanWaves * kWave) void k_radix_scan(SortArgs g) {
     all += x;
   }
   if (wave == 0 && d < digits) g.total[((uint64_t)p << g.bits) + d] = all;
-  for (uint32_t t = t0; t < t1; t += UN) {
+#pragma unroll
+  for (uint32_t q = 0; q < KEEP; ++q)
+    if (t0 + q < t1) {
+      if (d < digits) hist[(uint64_t)(t0 + q) << g.bits] = at;
+      at += kept[q];
+    }
+  for (uint32_t t = t0 + KEEP; t < t1; t += UN) {
     uint32_t c[UN];
 #pragma unroll
     for (int q = 0; q < UN; ++q) c[q] = hist[(uint64_t)min(t + q, t1 - 1) << g.bits];
@@ -156,15 +184,6 @@ __device__ inline uint64_t same_digit(uint32_t digit, int bits, bool live) {
   return mask;
 }
 
-// Last row i in [lo, hi] with rp[i] <= e, given rp[lo] <= e < rp[hi + 1].
-__device__ inline int32_t row_of_entry(const int32_t *rp, int32_t lo, int32_t hi, int32_t e) {
-  while (lo < hi) {
-    const int32_t mid = lo + ((hi - lo + 1) >> 1);
-    if (rp[mid] <= e) lo = mid; else hi = mid - 1;
-  }
-  return lo;
-}
-
 // The rows of two entries by a whole wave, half of it each: 32 places are looked at in one round trip.
 // Returns the half's own answer.
 __device__ inline int32_t wave_row_of_entry(const int32_t *rp, int32_t n, int32_t e, int lane) {
@@ -182,6 +201,10 @@ __device__ inline int32_t wave_row_of_entry(const int32_t *rp, int32_t n, int32_
   return lo;
 }
 
+// Bound by the stores of the first pass: a tile of 4096 entries has 8 of each of 512 digits, 32 bytes to a
+// place.  The next tile's go right behind them, so an XCD takes a run of tiles and its L2 puts the lines
+// together (3.4 M entries: 38 -> 33 us; tiles dealt to the XCDs in turn, whole lines never met).  With rows
+// found by a running maximum instead of a binary search per entry 43 -> 38 us.
 template <int R>
 __global__ __launch_bounds__(kSortBlock) void k_radix_scatter(SortArgs g) {
   __shared__ uint16_t rank_of[kSortWaves][kMaxDigits];  // counts, then the first place in the tile, per wave
@@ -189,7 +212,9 @@ __global__ __launch_bounds__(kSortBlock) void k_radix_scatter(SortArgs g) {
   __shared__ uint32_t to[kMaxDigits];                   // place in the part minus place in the tile
   __shared__ uint32_t wave_total[kSortWaves], wave_front[kSortWaves];
   const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
-  const TileRange r = tile_range<R>(g, blockIdx.x);
+  const uint32_t tiles = g.tile_off[g.nparts], tile = (uint32_t)xcd_run((int32_t)blockIdx.x, (int32_t)tiles);
+  if (tile >= tiles) return;
+  const TileRange r = tile_range<R>(g, tile);
   const int digits = 1 << g.bits;
   const int32_t *keys = tile_keys(g, r);
   const uint32_t first = (uint32_t)wave * (R * kWave);  // of this wave's share
@@ -205,22 +230,50 @@ __global__ __launch_bounds__(kSortBlock) void k_radix_scatter(SortArgs g) {
     const int32_t e0 = (int32_t)(r.begin + first), e1 = (int32_t)(r.begin + min(first + R * kWave, r.count)) - 1;
     const int32_t end = wave_row_of_entry(rp, g.n, lane < kWave / 2 ? e0 : e1, lane);
     const int32_t r0 = __builtin_amdgcn_readlane(end, 0), r1 = __builtin_amdgcn_readlane(end, kWave - 1);
-    int32_t lo[R], hi[R];
+    if (r1 - r0 < kRowsWalked) {
+      // where a row starts in the share goes to LDS (rows without entries start nowhere), and a running
+      // maximum gives every entry its row
+      int32_t *const start = stage + first;
 #pragma unroll
-    for (int q = 0; q < R; ++q) {
-      lo[q] = r0;
-      hi[q] = r1;
-    }
-    for (int32_t range = r1 - r0; range > 0; range >>= 1)  // (all of the lane's entries side by side)
+      for (int q = 0; q < R; ++q) start[q * kWave + lane] = 0;
+      constexpr int AHEAD = 4;
+      for (int32_t rb = r0 + 1; rb <= r1; rb += AHEAD * kWave) {
+        int32_t a[AHEAD], b[AHEAD];
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+          const int32_t row = min(rb + u * kWave + lane, r1);
+          a[u] = rp[row];
+          b[u] = rp[row + 1];
+        }
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u)
+          if (rb + u * kWave + lane <= r1 && a[u] < b[u]) start[min(max(a[u] - e0, 0), R * kWave - 1)] = rb + u * kWave + lane;
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      int32_t row = r0;
 #pragma unroll
       for (int q = 0; q < R; ++q) {
-        const int32_t mid = lo[q] + ((hi[q] - lo[q] + 1) >> 1);
-        const bool up = rp[mid] <= min(e0 + q * kWave + lane, e1);
-        lo[q] = up ? mid : lo[q];
-        hi[q] = up ? hi[q] : max(mid - 1, lo[q]);
+        val[q] = (int32_t)max((uint32_t)row, wave_max((uint32_t)start[q * kWave + lane]));
+        row = __builtin_amdgcn_readlane(val[q], kWave - 1);
       }
+    } else {
+      int32_t lo[R], hi[R];
 #pragma unroll
-    for (int q = 0; q < R; ++q) val[q] = lo[q];
+      for (int q = 0; q < R; ++q) {
+        lo[q] = r0;
+        hi[q] = r1;
+      }
+      for (int32_t range = r1 - r0; range > 0; range >>= 1)  // (all of the lane's entries side by side)
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+          const int32_t mid = lo[q] + ((hi[q] - lo[q] + 1) >> 1);
+          const bool up = rp[mid] <= min(e0 + q * kWave + lane, e1);
+          lo[q] = up ? mid : lo[q];
+          hi[q] = up ? hi[q] : max(mid - 1, lo[q]);
+        }
+#pragma unroll
+      for (int q = 0; q < R; ++q) val[q] = lo[q];
+    }
   }
   for (int x = tid; x < kSortWaves * kMaxDigits / 2; x += kSortBlock) reinterpret_cast<uint32_t *>(rank_of)[x] = 0;
   __syncthreads();
@@ -243,7 +296,7 @@ __global__ __launch_bounds__(kSortBlock) void k_radix_scatter(SortArgs g) {
     // places of the digits in the tile, and of the part's digits in the part: thread t takes digits
     // 2 t and 2 t + 1
     constexpr int PER = kMaxDigits / kSortBlock;
-    const uint32_t *hist = g.hist + ((uint64_t)blockIdx.x << g.bits), *total = g.total + ((uint64_t)r.p << g.bits);
+    const uint32_t *hist = g.hist + ((uint64_t)tile << g.bits), *total = g.total + ((uint64_t)r.p << g.bits);
     uint32_t in_tile[PER], in_part[PER], before[PER], all = 0, all_part = 0;
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
@@ -317,6 +370,7 @@ __global__ __launch_bounds__(kSortBlock) void k_radix_scatter(SortArgs g) {
 // the exclusive part of snapshot t.
 struct FinishArgs {
   int32_t nparts, n, k;
+  int32_t block_off[PIPAD_MAX_K + 2];     // first workgroup of every part, in their natural order
   uint32_t part_off[PIPAD_MAX_K + 2];
   const int32_t *key;                     // sorted columns of the source, part by part
   const int32_t *col[PIPAD_MAX_K + 1];    // columns of the transposed parts
@@ -346,12 +400,21 @@ __device__ inline void fill_run(int32_t *rp, int32_t lo, int32_t hi, int32_t v, 
 template <int KV, bool FULL>
 __global__ __launch_bounds__(kBlock) void k_finish_parts(FinishArgs g) {
   const int lane = threadIdx.x % kWave;
-  const int p = blockIdx.y;
+  // (an XCD takes a run of the exclusive parts, so that it reads one or two snapshots' D^-1/2; no workgroup
+  // is launched for nothing where the parts differ in size: N = 200k, k = 4 27 -> 25 us)
+  int p = 0;
+  int32_t b = blockIdx.x;
+  if (b >= align_xcd(g.block_off[1])) {
+    b = g.block_off[1] + xcd_run(b - align_xcd(g.block_off[1]), g.block_off[g.nparts] - g.block_off[1]);
+    while (p < g.nparts && b >= g.block_off[p + 1]) ++p;
+  }
+  if (p == g.nparts || b >= g.block_off[p + 1]) return;
+  b -= g.block_off[p];
   const int32_t nnz = (int32_t)(g.part_off[p + 1] - g.part_off[p]);
-  const int64_t e64 = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  const int64_t e64 = (int64_t)b * kBlock + threadIdx.x;
   int32_t *const rp = g.rowptr[p];
   if (nnz == 0) {  // no entries: all workgroups of the part clear its row pointers
-    for (int64_t x = e64; x <= g.n; x += (int64_t)gridDim.x * kBlock) rp[x] = 0;
+    for (int64_t x = e64; x <= g.n; x += (int64_t)(g.block_off[p + 1] - g.block_off[p]) * kBlock) rp[x] = 0;
     return;
   }
   if (e64 - lane >= nnz) return;  // whole wave
@@ -459,12 +522,10 @@ int transpose_frame(const pipad_frame *f, pipad_alloc_fn alloc, void *alloc_ctx,
   s.nparts = k + 1;
   s.n = n;
   int64_t total = 0, tiles = 0;
-  int32_t max_nnz = 0;
   for (int p = 0; p <= k; ++p) {
     const int32_t nnz = p == 0 ? f->nnz_c : f->nnz_d[p - 1];
     s.part_off[p] = (uint32_t)total;
     total += nnz;
-    max_nnz = std::max(max_nnz, nnz);
     s.rowptr[p] = p == 0 ? f->rowptr_c : f->rowptr_d[p - 1];
     s.col[p] = p == 0 ? f->col_c : f->col_d[p - 1];
     s.col_out[p] = p == 0 ? g->col_c : g->col_d[p - 1];
@@ -510,13 +571,15 @@ int transpose_frame(const pipad_frame *f, pipad_alloc_fn alloc, void *alloc_ctx,
   tmp.assign(temp);
 
   launched = true;
-  // (the two copies of D^-1/2 lie next to each other in every frame)
-  const size_t dinv_span = (size_t)(f->dinv_nk - f->dinv) + (size_t)node_stride(k) * n;
-  if (g->dinv_nk - g->dinv == f->dinv_nk - f->dinv && f->dinv_nk > f->dinv) {
-    PIPAD_TRY_T(hipMemcpyAsync(g->dinv, f->dinv, sizeof(float) * dinv_span, hipMemcpyDeviceToDevice, st));
+  // The two copies of D^-1/2 lie next to each other in every frame, padded to 256 bytes.
+  const size_t dinv_bytes = (size_t)((char *)f->dinv_nk - (char *)f->dinv) + sizeof(float) * (size_t)node_stride(k) * n;
+  if ((char *)g->dinv_nk - (char *)g->dinv != (char *)f->dinv_nk - (char *)f->dinv) return fail(PIPAD_ERR_INVALID_ARG);
+  if (total == 0) {
+    PIPAD_TRY_T(hipMemcpyAsync(g->dinv, f->dinv, dinv_bytes, hipMemcpyDeviceToDevice, st));
   } else {
-    PIPAD_TRY_T(hipMemcpyAsync(g->dinv, f->dinv, sizeof(float) * (size_t)k * n, hipMemcpyDeviceToDevice, st));
-    PIPAD_TRY_T(hipMemcpyAsync(g->dinv_nk, f->dinv_nk, sizeof(float) * (size_t)node_stride(k) * n, hipMemcpyDeviceToDevice, st));
+    s.dinv_from = reinterpret_cast<const float4 *>(f->dinv);
+    s.dinv_to = reinterpret_cast<float4 *>(g->dinv);
+    s.dinv_pieces = (int64_t)((dinv_bytes + 15) / 16);
   }
 
   // ---- stable sort of all entries by column, digit by digit
@@ -533,9 +596,10 @@ int transpose_frame(const pipad_frame *f, pipad_alloc_fn alloc, void *alloc_ctx,
       s.val_out = pass % 2 == 0 ? val_a : val_b;
       auto hist = per_thread == 16 ? k_radix_hist<16> : per_thread == 8 ? k_radix_hist<8> : k_radix_hist<4>;
       auto scatter = per_thread == 16 ? k_radix_scatter<16> : per_thread == 8 ? k_radix_scatter<8> : k_radix_scatter<4>;
-      hipLaunchKernelGGL(hist, dim3((unsigned)tiles), dim3(kSortBlock), 0, st, s);
+      const int64_t copiers = pass == 0 ? std::min<int64_t>((s.dinv_pieces + kSortBlock - 1) / kSortBlock, 2048) : 0;
+      hipLaunchKernelGGL(hist, dim3((unsigned)(tiles + copiers)), dim3(kSortBlock), 0, st, s);
       hipLaunchKernelGGL(k_radix_scan, grid1(1 << s.bits, kWave, k + 1), dim3(kScanWaves * kWave), 0, st, s);
-      hipLaunchKernelGGL(scatter, dim3((unsigned)tiles), dim3(kSortBlock), 0, st, s);
+      hipLaunchKernelGGL(scatter, dim3((unsigned)align_xcd((int32_t)tiles)), dim3(kSortBlock), 0, st, s);
       PIPAD_TRY_T(hipGetLastError());
       sorted_keys = s.key_out;
     }
@@ -563,7 +627,16 @@ int transpose_frame(const pipad_frame *f, pipad_alloc_fn alloc, void *alloc_ctx,
                                      k_finish_parts<2, false>, k_finish_parts<2, true>,  k_finish_parts<3, false>,
                                      k_finish_parts<3, true>,  k_finish_parts<4, false>, k_finish_parts<4, true>};
     auto finish = kernels[k <= 2 || k > 16 ? 0 : node_stride(k) / 2 - (k % 4 ? 1 : 0)];
-    hipLaunchKernelGGL(finish, grid1(std::max(max_nnz, 1), kBlock, k + 1), dim3(kBlock), 0, st, c);
+    int64_t blocks = 0;
+    for (int p = 0; p <= k; ++p) {
+      const int64_t nnz = (int64_t)(s.part_off[p + 1] - s.part_off[p]);
+      c.block_off[p] = (int32_t)blocks;
+      blocks += nnz > 0 ? (nnz + kBlock - 1) / kBlock : std::min<int64_t>((int64_t)n / kBlock + 1, 1024);
+    }
+    c.block_off[k + 1] = (int32_t)blocks;
+    const int32_t first_excl = align_xcd(c.block_off[1]);
+    hipLaunchKernelGGL(finish, dim3((unsigned)(first_excl + align_xcd((int32_t)blocks - c.block_off[1]))), dim3(kBlock), 0,
+                       st, c);
   }
   PIPAD_TRY_T(hipGetLastError());
 
