@@ -423,9 +423,6 @@ __device__ __forceinline__ void sink_flush_ks(const AggArgs &a, const Slice &s, 
     const float4 v = *reinterpret_cast<const float4 *>(k.tile + m * kTileStride + g * KS + 4 * q);
     av[4 * q + 0] = v.x; av[4 * q + 1] = v.y; av[4 * q + 2] = v.z; av[4 * q + 3] = v.w;
   }
-  int32_t row[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) row[r] = k.rows[min(4 * g + r, kTileRows - 1)];
   const int ws = a.Fo + 1;
   for (int nt = 0; nt < a.Fo / 16; ++nt) {
     const float *wcol = k.wl + (g * KS) * ws + 16 * nt + m;
@@ -441,9 +438,16 @@ __device__ __forceinline__ void sink_flush_ks(const AggArgs &a, const Slice &s, 
       for (int ks = 0; ks < KB; ++ks)
         d = __builtin_amdgcn_mfma_f32_16x16x4f32(av[k0 + ks], bv[ks], d, 0, 0, 0);
     }
+    // (the tile's rows are in registers: their place takes the product)
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
-      if (4 * g + r < k.cnt) s.ht[(int64_t)row[r] * a.ldh + 16 * nt + m] = d[r] + b;
+    for (int r = 0; r < 4; ++r) k.tile[(4 * g + r) * kTileStride + 16 * nt + m] = d[r] + b;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  const int quads = a.Fo / 4;  // 16-byte pieces of a row of H
+  for (int x = lane; x < k.cnt * quads; x += kWave) {
+    const int row = x / quads, q = x - row * quads;
+    const float4 h = *reinterpret_cast<const float4 *>(k.tile + row * kTileStride + 4 * q);
+    V<4>::store(s.ht + (int64_t)k.rows[row] * a.ldh + 4 * q, h, a.nt & 1);
   }
 }
 
