@@ -88,7 +88,8 @@ struct AggArgs {
   int32_t blocks_wide, blocks_mid, blocks_short;
   int32_t batch_short, batch_mid, batch_wide;  // rows / class parts per wave
   int64_t blocks_per_phase;
-  int32_t order;      // 1: one slice after the other; 0: hub class parts so, the rows of all slices side by side
+  int32_t order;      // 1: one slice after the other; else hub class parts so and the rows of all slices side by
+                      // side, 0: in turn, 2: in a run of slices per XCD
   int32_t sub_log2;   // log2 of the sub classes per XCD
   int32_t nclass;     // 8 << sub_log2
   int64_t nvp;        // partial sums per slice: nclass per hub unit
@@ -554,8 +555,24 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
       w = b - slice_seq * split_blocks;
     } else {
       const int64_t r = b - hub_total;
-      slice_seq = (int)(r % nsl);
-      w = split_blocks + r / nsl;
+      if (a.order == 0) {
+        slice_seq = (int)(r % nsl);
+        w = split_blocks + r / nsl;
+      } else {
+        // The workgroups of a slice's mid rows, dealt into 8 parts, make 8 * nsl parts in slice order, of
+        // which XCD x takes nsl in a row: it only ever reads two or three of the matrices.  All mid
+        // rows first, then the short ones the same way.
+        const int x = (int)(r & (kClasses - 1));
+        int32_t i = (int32_t)(r / kClasses), part = a.blocks_mid / kClasses, start = 0;
+        if (i >= part * nsl) {
+          i -= part * nsl;
+          start = a.blocks_mid;
+          part = (int32_t)(a.blocks_per_phase - split_blocks - start) / kClasses;
+        }
+        const int32_t q = i / part, share = nsl * x + q;
+        slice_seq = share / kClasses;
+        w = split_blocks + start + (int64_t)(i - q * part) * kClasses + share % kClasses;
+      }
     }
   }
   const int t_seq = slice_seq / a.fchunks;
@@ -1389,6 +1406,7 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
   // slices go one after the other.  Measured, k = 8, the other order against the one taken: N = 100k,
   // F = 64 328 us against 317, N = 200k, F = 32 364 against 348, F = 16 252 against 256; and beyond the
   // line N = 200k, F = 64 724 against 714, R-MAT 1M 3910 against 3865, low-overlap 5735 against 5049.
+  // (Which of the two ways of side by side: below.)
   a.order = opt.agg_order >= 2 ? -1 : (int32_t)opt.agg_order;
   a.nsel = subset ? nsubset : f->k;
   for (int q = 0; q < a.nsel; ++q)
@@ -1471,7 +1489,23 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
   }
   const int sw = (1 << a.ls_log2) * vec;
   const int nteams = kWave >> a.ls_log2;
-  if (a.order < 0) a.order = (int64_t)f->n * sw * 4 >= (int64_t)PIPAD_ORDER_BYTES ? 1 : 0;
+  int64_t entries = f->nnz_c;  // of a snapshot
+  for (int t = 0; t < f->k; ++t) entries += f->nnz_d[t] / f->k;
+  if (a.order < 0) {
+    const int64_t matrix = (int64_t)f->n * sw * 4, slices = (int64_t)a.nsel * a.fchunks;
+    a.order = matrix >= (int64_t)PIPAD_ORDER_BYTES ? 1 : 0;
+    // Side by side, in turn: workgroup b, on XCD b mod 8, takes slice b mod `slices`, so that an XCD keeps to
+    // one or a few slices where their number divides 8, and goes through most of them otherwise, with
+    // more matrices in its L2 than that can hold.  Then an XCD gets a run of slices instead (order 2).
+    // Measured, k = 3 .. 16, 6 to 16 entries per row, R-MAT and Chung-Lu frames: 5 MiB matrices
+    // and more, 8 entries per row and more 5 to 26 % faster in the mean of each number of slices (N = 100k,
+    // k = 5, F = 30 132 -> 98 us; N = 120k, k = 12, F = 16 258 -> 180), 3 % slower at worst; with 6 entries
+    // per row it is the slices' parity that decides: odd numbers 5 to 13 % faster from 10 MiB on, others
+    // between 7 % faster and 4 % slower; smaller matrices and numbers that divide 8 up to 30 % slower.
+    if (a.order == 0 && !coalescent && !fused && kClasses % slices != 0 && matrix >= (5 << 20) &&
+        (entries >= 8 * (int64_t)f->n || (slices % 2 == 1 && matrix >= (10 << 20))))
+      a.order = 2;
+  }
 
   // Rows per wave: the full batches amortise the per-wave set-up (and let a wave request its next
   // row while it gathers the current one) on big frames; smaller ones get shorter batches, until what
@@ -1487,7 +1521,7 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
     a.batch_short = kShortRowsPerWave;
     a.batch_mid = kLongRowsPerWave;
     a.batch_wide = kWideUnitsPerWave;
-    const int64_t slices_run = coalescent ? a.nslices : a.order == 0 ? (int64_t)a.nsel * a.fchunks : 1;
+    const int64_t slices_run = coalescent ? a.nslices : a.order == 1 ? 1 : (int64_t)a.nsel * a.fchunks;
     auto waves = [&]() {
       return ((int64_t)(f->n_short + a.batch_short - 1) / a.batch_short +
               (int64_t)(f->n_long + a.batch_mid - 1) / a.batch_mid +
@@ -1502,11 +1536,23 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
     auto chain = [&]() {
       return fused || coalescent || f->n_short == 0 ? 0 : f->short_entries * a.batch_short / nteams / f->n_short;
     };
-    int64_t entries = f->nnz_c;  // of a snapshot
-    for (int t = 0; t < f->k; ++t) entries += f->nnz_d[t] / f->k;
     const int64_t longest_chain = 2 * f->short_entries > entries ? 50 : 70;
-    while ((waves() < enough && (a.batch_short > min_short || a.batch_mid > 1 || a.batch_wide > 1)) ||
-           (chain() > longest_chain && a.batch_short > min_short)) {
+    if (a.order == 2) {
+      // Runs of slices: 22000 waves of short rows and 2000 of mid ones in all; chains of 20 entries where
+      // the short rows hold most of them, of 70 elsewhere; two rows per lane team at least, so that there
+      // is something to put in order, where a team has 8 lanes and more.  (Of 360 frames the best of all
+      // batches is 2.4 % faster in the mean; the rule of the other orders is 4 % slower.)
+      a.batch_short = std::min(kShortRowsPerWave, 8 * nteams);
+      const int at_least = nteams <= 8 ? 2 * nteams : nteams;
+      const int64_t chain_max = 2 * f->short_entries > entries ? 20 : 70;
+      while (a.batch_short > at_least && (f->n_short * slices_run / a.batch_short < 22000 || chain() > chain_max))
+        a.batch_short >>= 1;
+      a.batch_mid = 4;
+      while (a.batch_mid > 1 && f->n_long * slices_run / a.batch_mid < 2000) a.batch_mid >>= 1;
+      while (a.batch_wide > 1 && (int64_t)f->n_items * f->nclass * slices_run / a.batch_wide < 2000) a.batch_wide >>= 1;
+    }
+    while (a.order != 2 && ((waves() < enough && (a.batch_short > min_short || a.batch_mid > 1 || a.batch_wide > 1)) ||
+           (chain() > longest_chain && a.batch_short > min_short))) {
       if (a.batch_short > min_short) a.batch_short >>= 1;
       if (a.batch_mid > 1) a.batch_mid >>= 1;
       if (a.batch_wide > 1) a.batch_wide >>= 1;
@@ -1520,7 +1566,8 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
     a.blocks_mid = blocks_for(f->n_long, a.batch_mid);
     a.blocks_short = blocks_for(f->n_short, a.batch_short);
     if (!coalescent) {
-      // phases start at multiples of 8 workgroups
+      // phases start at multiples of 8 workgroups, with runs of slices the short rows as well
+      if (a.order == 2) a.blocks_mid = align_xcd(a.blocks_mid);
       a.blocks_short += (kClasses - (a.blocks_mid + a.blocks_short) % kClasses) % kClasses;
       a.blocks_per_phase = ((int64_t)kClasses * a.blocks_wide << f->sub_log2) + a.blocks_mid + a.blocks_short;
     }
