@@ -36,7 +36,7 @@
 //   hub rows    split by class; a wave per class part, the 64/LS lane teams take different
 //               entries and are summed with cross-lane shuffles.  Rows beyond hub_threshold
 //               entries are first cut into units (the role the paper's sliced CSR plays for load
-//               balance, Section 4.1).
+//               balance, Section 4.1).  In small frames (plain_units) a workgroup walks a unit whole.
 //   mid rows    walked whole by a wave, the same way; self-loop, row scale and store at once.
 //   short rows  walked whole: a team of LS lanes (LS * VEC = slice width) per row, 64/LS rows
 //               side by side, row metadata for a whole batch loaded in one go.
@@ -96,11 +96,13 @@ struct AggArgs {
   int32_t nt;         // non-temporal hints (bit 0: Y stores, bit 1: index streams)
   int32_t sg;         // coalescent kernel: snapshots per lane team (slices are snapshot groups)
   int32_t whole_units;  // coalescent kernel: one partial sum per hub unit, not one per class part
+  int32_t plain;        // hub units are walked by a workgroup each, from the lists of the parts (nclass is 1 then)
+  int32_t direct;       // ... and every hub row is one unit: the row is finished there, no partial sums
   int64_t ldx, ldy;
   const int32_t *rowptr_c, *col_c;
   const float *dinv;
   const int32_t *rows_short, *rows_long;
-  const int32_t *item_row, *hub_rows, *hub_item_off;
+  const int32_t *item_row, *item_v0, *item_v1, *hub_rows, *hub_item_off;
   const int32_t *sptr;    // class parts of the hub rows: see pipad_frame
   const int32_t *scol_c, *scol_d;
   const float *swd;
@@ -513,7 +515,30 @@ __device__ __forceinline__ float *partial_slot(const AggArgs &a, int slice_seq, 
 // A wave-wide team has 64 / LS lane groups and a chunk of 64 * EPL entries, EPL >= 4 / LS (launch()).
 static_assert(PIPAD_AGG_DEPTH <= 4, "more gathers in flight than a chunk holds");
 
-template <int VEC, bool FAST, int EPL, bool UPD, bool ALONE = false>
+// What a wave of a workgroup walks of a plain hub unit: a quarter of the unit's range of the row's two
+// lists, taken as one.
+struct Piece {
+  int32_t i, cs, clen, ds, len;
+};
+__device__ __forceinline__ Piece unit_piece(const AggArgs &a, int64_t unit, const int32_t *rpd, int wave) {
+  Piece p;
+  p.i = a.item_row[unit];
+  const int32_t v0 = a.item_v0[unit], v1 = a.item_v1[unit];
+  p.cs = a.rowptr_c[p.i];
+  p.clen = a.rowptr_c[p.i + 1] - p.cs;
+  p.ds = rpd[p.i];
+  const int32_t end = min(v1, p.clen + rpd[p.i + 1] - p.ds);
+  const int32_t quarter = (max(end - v0, 0) + kWavesPerBlock - 1) / kWavesPerBlock;
+  const int32_t at = min(v0 + wave * quarter, end), skip = min(at, p.clen);
+  p.len = min(quarter, end - at);
+  p.cs += skip;
+  p.clen -= skip;
+  p.ds += at - skip;
+  return p;
+}
+
+// PLAIN: hub units as they are in a frame with plain_units.
+template <int VEC, bool FAST, int EPL, bool UPD, bool PLAIN, bool ALONE = false>
 __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
   using VT = V<VEC>;
   static_assert(!UPD || (VEC == 4 && FAST), "the fused update rides on the fast float4 path");
@@ -537,7 +562,7 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
   const int64_t b = blockIdx.x;
   const int nsub = 1 << a.sub_log2;
   const int64_t wide_blocks = (int64_t)kClasses * a.blocks_wide;  // per sub class
-  const int64_t split_blocks = nsub * wide_blocks;
+  const int64_t split_blocks = PLAIN ? a.n_items : nsub * wide_blocks;
   int slice_seq;
   int64_t w;  // workgroup index within the slice's phase: class parts, mid rows, short rows
   if (a.order == 1) {
@@ -580,7 +605,7 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
   const Slice s = slice_setup(a, slice, fl, VEC);
   const bool ntl = a.nt & 2;
 
-  if (UPD && w < split_blocks) {
+  if (UPD && w < split_blocks && !a.direct) {
     sink.cnt = 0;  // (class parts of hub units end in partial sums: no use for W)
   } else if (UPD) {
     const int K = 4 << a.ls_log2, ws = a.Fo + 1;
@@ -597,6 +622,43 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
     __syncthreads();  // before any wave leaves
   }
 
+  if (PLAIN && w < split_blocks) {
+    // ---- a hub unit by the whole workgroup, a quarter of its entries per wave, the waves' sums added in
+    //      order: a row of 2048 entries has 32 rounds of gathers one after the other (F = 64), as a mid row
+    //      of 512, and is finished here unless it is cut
+    __shared__ typename VT::T sums[kWavesPerBlock][kWave / VEC];
+    const Piece p = unit_piece(a, w, s.rpd, wave);
+    Lists l;
+    l.colc = a.col_c;
+    l.wc = s.wc;
+    l.cold = s.cd;
+    l.wd = s.wd;
+    Raw head[EPL];
+#pragma unroll
+    for (int j = 0; j < EPL; ++j) head[j] = fetch_entry(l, p.cs, p.clen, p.ds, p.len, j * kWave + lane, p.i, ntl);
+    const typename VT::T xi = VT::load(s.xb + (int64_t)p.i * a.ldx);
+    const float di = s.dv[p.i];
+    typename VT::T acc = VT::zero();
+    walk<VEC, U, FAST, EPL, ALONE>(l, p.cs, p.clen, p.ds, p.len, head, 0, kWave, lane, team, nteams, s, a.ldx, p.i, ntl, lds,
+                                   acc);
+    reduce_slots<VEC>(a.ls_log2, acc);
+    if (team == 0) sums[wave][fl] = acc;
+    __syncthreads();
+    if (wave > 0) return;
+#pragma unroll
+    for (int x = 1; x < kWavesPerBlock; ++x) VT::add(acc, sums[x][fl]);
+    if (!a.direct) {
+      if (team == 0 && s.fvalid) VT::store(partial_slot(a, slice_seq, w, fl, VEC), acc, kPartialNt);
+    } else if constexpr (UPD) {
+      if (team == 0) finish_row_to_sink(a, s, sink, 0, fl, p.i, di, xi, acc);
+      sink.cnt = 1;
+      sink_flush(a, s, sink, lane);
+    } else {
+      if (team == 0 && s.fvalid) finish_row<VEC>(a, s, p.i, di, xi, acc);
+    }
+    return;
+  }
+
   // ---- what this wave works on: a batch of consecutive list elements.  Class parts of hub units
   //      (from the class-grouped copies, ending in a partial sum) and whole mid rows: the whole
   //      wave on one list at a time, its lane groups taking different entries.  Short rows: one
@@ -609,7 +671,7 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
   const int32_t *const p_items = a.item_row, *const p_mid = a.rows_long, *const p_short = a.rows_short;
   const int64_t n_items = a.n_items, n_mid = a.n_long, n_short = a.n_short;
   const int b_wide = a.batch_wide, b_mid = a.batch_mid, b_short = a.batch_short;
-  const bool split = w < split_blocks;                  // class parts of hub units
+  const bool split = !PLAIN && w < split_blocks;        // class parts of hub units
   const bool wide = w < split_blocks + a.blocks_mid;    // ... or whole mid rows: a wave per list
   int cls = 0;  // column class of this wave's class parts
   if (split) {
@@ -771,17 +833,18 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
 // EPL: entries per lane and chunk; teams of 8 lanes and more get on with 1.  (Teams of 1 and 2 lanes with
 // one entry per lane, fetched and gathered one after the other: N = 500k, k = 4, F = 4 486 us, with 4
 // entries 375; 8 entries take too many registers.)
-template <int VEC, bool FAST, int EPL, bool ALONE = false>
+template <int VEC, bool FAST, int EPL, bool PLAIN, bool ALONE = false>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(PIPAD_AGG_WAVES)))
 void k_aggregate(const AggArgs a) {
-  aggregate_body<VEC, FAST, EPL, false, ALONE>(a);
+  aggregate_body<VEC, FAST, EPL, false, PLAIN, ALONE>(a);
 }
 
 // The same walk with the update fused in, held to the four waves per SIMD that its 120 registers allow
 // (left to the compiler: 853 us against 851 on N = 200k, k = 8, F = Fo = 64).
+template <bool PLAIN>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void k_aggregate_update(const AggArgs a) {
-  aggregate_body<4, true, 1, true>(a);
+  aggregate_body<4, true, 1, true, PLAIN>(a);
 }
 
 // Adds the partial sums of every hub row in a fixed order and finishes the row.  One wave per
@@ -1015,7 +1078,7 @@ __device__ __forceinline__ float *unit_partial(const AggArgs &a, int g, int64_t 
   return a.partial + col0 * (a.n_items * parts) + (unit * parts + cls) * width - col0;
 }
 
-template <int VEC, int EPL, bool ALONE>
+template <int VEC, int EPL, bool PLAIN, bool ALONE>
 __global__ __launch_bounds__(kBlock) void k_aggregate_coalescent(const AggArgs a) {
   using VT = V<VEC>;
   constexpr int U = 4;  // row gathers in flight per lane
@@ -1031,12 +1094,13 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_coalescent(const AggArgs a
   // mod 8); then the whole rows, the groups side by side: they share the entry lists.
   const int64_t b = blockIdx.x;
   const int64_t wide_blocks = (int64_t)kClasses * a.blocks_wide;  // per sub class
-  const int64_t split_blocks = a.whole_units ? a.blocks_wide : wide_blocks << a.sub_log2;
+  const int64_t split_blocks = PLAIN ? a.n_items : a.whole_units ? a.blocks_wide : wide_blocks << a.sub_log2;
   const int64_t r0 = b - split_blocks * a.nslices;
-  const bool split = r0 < 0;
+  const bool unit = r0 < 0;
+  const bool split = !PLAIN && unit;
   int g;  // snapshot group
   int64_t w;
-  if (split) {
+  if (unit) {
     g = (int)(b / split_blocks);
     w = b - g * split_blocks;
   } else {
@@ -1058,6 +1122,49 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_coalescent(const AggArgs a
   const uint32_t row_bytes = (uint32_t)a.ldx * 4u;
   const char *xbytes = reinterpret_cast<const char *>(a.X[0]);
   const uint32_t lane_bytes = (uint32_t)lane_col * 4u;
+
+  // For the walk a team is the lanes of one snapshot, of one row or, wave-wide, of all lane groups:
+  // they fetch that snapshot's entries together (the next smaller power of two of them, so that a
+  // chunk is a multiple of U entries; the others do the same again).
+  const int fetchers = lps >= 8 ? 8 : lps >= 4 ? 4 : lps >= 2 ? 2 : 1;
+  Slice s;
+  s.xt = a.X[0];
+  s.fcol = lane_col;
+  s.fvalid = true;
+  s.xb = s.xt + lane_col;
+
+  if (PLAIN && unit) {
+    // a hub unit by the whole workgroup, as in k_aggregate
+    __shared__ typename VT::T sums[kWavesPerBlock][kWave];
+    Piece p = unit_piece(a, w, rpd, wave);
+    if (!valid) p.len = 0;
+    Lists l;
+    l.colc = a.col_c;
+    l.wc = a.wc[t];
+    l.cold = a.col_d[t];
+    l.wd = a.wd[t];
+    const int team_lanes = nteams * fetchers, q = team * fetchers + ((fl - u * lps) & (fetchers - 1));
+    Raw head[EPL];
+#pragma unroll
+    for (int v = 0; v < EPL; ++v)
+      head[v] = fetch_entry(l, p.cs, p.clen, p.ds, p.len, v * team_lanes + q, p.i, false);
+    typename VT::T acc = VT::zero();
+    walk<VEC, U, true, EPL, ALONE>(l, p.cs, p.clen, p.ds, p.len, head, u * nteams * fetchers, team_lanes, q, team, nteams, s,
+                                   a.ldx, p.i, false, lds, acc);
+    reduce_slots<VEC>(a.ls_log2, acc);
+    if (team == 0) sums[wave][fl] = acc;
+    __syncthreads();
+    if (wave > 0 || team > 0 || !valid) return;
+#pragma unroll
+    for (int x = 1; x < kWavesPerBlock; ++x) VT::add(acc, sums[x][fl]);
+    if (a.direct) {
+      VT::fma(acc, dv[p.i], VT::load(reinterpret_cast<const float *>(xbytes + ((uint32_t)p.i * row_bytes + lane_bytes))));
+      VT::store(ylane + (int64_t)p.i * a.ldy, VT::scale(dv[p.i], acc), a.nt & 1);
+    } else {
+      VT::store(unit_partial(a, g, w, 0) + lane_col, acc, false);
+    }
+    return;
+  }
 
   const int32_t *const p_items = a.item_row, *const p_mid = a.rows_long, *const p_short = a.rows_short;
   const int64_t n_items = a.n_items, n_mid = a.n_long, n_short = a.n_short;
@@ -1100,20 +1207,11 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_coalescent(const AggArgs a
     mc1 = pc[split ? n_items : 1];
   }
   const int per_step = wide ? 1 : nteams;
-  // For the walk a team is the lanes of one snapshot, of one row or, wave-wide, of all lane groups:
-  // they fetch that snapshot's entries together (the next smaller power of two of them, so that a
-  // chunk is a multiple of U entries; the others do the same again).
-  const int fetchers = lps >= 8 ? 8 : lps >= 4 ? 4 : lps >= 2 ? 2 : 1;
   const int team_lanes = wide ? nteams * fetchers : fetchers;
   const int q = (wide ? team * fetchers : 0) + ((fl - u * lps) & (fetchers - 1));
   const int team_base = (wide ? u * nteams : team * a.sg + u) * fetchers;
   const int slot = wide ? team : 0;
   const int nslots = wide ? nteams : 1;
-  Slice s;
-  s.xt = a.X[0];
-  s.fcol = lane_col;
-  s.fvalid = true;
-  s.xb = s.xt + lane_col;
   auto meta = [&](int step, int part) __attribute__((always_inline)) {
     CoalItem it;
     const int li = step * per_step + (wide ? 0 : team);
@@ -1263,31 +1361,26 @@ int launch(const AggArgs &a, bool fast, hipStream_t st, bool fused_update = fals
   const int64_t phases = (int64_t)a.nsel * a.fchunks;
   const int64_t blocks = a.blocks_per_phase * phases;
   if (blocks >= ((int64_t)1 << 31)) return PIPAD_ERR_TOO_LARGE;
-  const int64_t fin = ((int64_t)a.n_hub + kWavesPerBlock - 1) / kWavesPerBlock * phases;
+  const int64_t fin = a.direct ? 0 : ((int64_t)a.n_hub + kWavesPerBlock - 1) / kWavesPerBlock * phases;
   if (fin >= ((int64_t)1 << 31)) return PIPAD_ERR_TOO_LARGE;
   const dim3 grid((unsigned)blocks), block(kBlock);
   if constexpr (VEC == 4) {
     if (fused_update) {
       if (!fast || a.ls_log2 < 2) return PIPAD_ERR_INVALID_ARG;  // the caller checked the shape
-      if (blocks > 0) hipLaunchKernelGGL(k_aggregate_update, grid, block, update_lds_bytes(a), st, a);
+      auto kern = a.plain ? k_aggregate_update<true> : k_aggregate_update<false>;
+      if (blocks > 0) hipLaunchKernelGGL(kern, grid, block, update_lds_bytes(a), st, a);
       if (fin > 0)
         hipLaunchKernelGGL((k_split_finish<4, true>), dim3((unsigned)fin), dim3(kBlock), 0, st, a);
       PIPAD_HIP(hipGetLastError());
       return PIPAD_OK;
     }
   }
-  if (blocks > 0) {
-    if (!fast)
-      hipLaunchKernelGGL((k_aggregate<VEC, false, 1>), grid, block, 0, st, a);
-    else if (a.ls_log2 >= 3)
-      hipLaunchKernelGGL((k_aggregate<VEC, true, 1>), grid, block, 0, st, a);
-    else if (a.ls_log2 == 2)
-      hipLaunchKernelGGL((k_aggregate<VEC, true, 2>), grid, block, 0, st, a);
-    else if (a.ls_log2 == 1)
-      hipLaunchKernelGGL((k_aggregate<VEC, true, 4>), grid, block, 0, st, a);
-    else
-      hipLaunchKernelGGL((k_aggregate<VEC, true, 4, true>), grid, block, 0, st, a);
-  }
+  void (*const kern[2][5])(AggArgs) = {
+      {k_aggregate<VEC, true, 4, false, true>, k_aggregate<VEC, true, 4, false>, k_aggregate<VEC, true, 2, false>,
+       k_aggregate<VEC, true, 1, false>, k_aggregate<VEC, false, 1, false>},
+      {k_aggregate<VEC, true, 4, true, true>, k_aggregate<VEC, true, 4, true>, k_aggregate<VEC, true, 2, true>,
+       k_aggregate<VEC, true, 1, true>, k_aggregate<VEC, false, 1, true>}};
+  if (blocks > 0) hipLaunchKernelGGL(kern[a.plain][fast ? std::min(a.ls_log2, 3) : 4], grid, block, 0, st, a);
   if (fin > 0) hipLaunchKernelGGL((k_split_finish<VEC>), dim3((unsigned)fin), dim3(kBlock), 0, st, a);
   PIPAD_HIP(hipGetLastError());
   return PIPAD_OK;
@@ -1322,16 +1415,17 @@ int launch_update(const AggArgs &a, hipStream_t st) {
 
 template <int VEC>
 int launch_coalescent(const AggArgs &a, hipStream_t st) {
-  const int64_t wide = a.whole_units ? a.blocks_wide : (int64_t)a.blocks_wide * a.nclass;
+  const int64_t wide = a.plain ? a.n_items : a.whole_units ? a.blocks_wide : (int64_t)a.blocks_wide * a.nclass;
   const int64_t blocks = (wide + a.blocks_mid + a.blocks_short) * a.nslices;
   if (blocks >= ((int64_t)1 << 31)) return PIPAD_ERR_TOO_LARGE;
   // entries per fetching lane, so that a chunk holds U = 4 and more for every lane group: 4 for one or
   // two lanes per snapshot (F <= 4), 2 for two and more; F == VEC is one lane per snapshot
-  auto kern = a.F == VEC ? k_aggregate_coalescent<VEC, 4, true> : k_aggregate_coalescent<VEC, 4, false>;
+  auto kern = a.plain ? (a.F == VEC ? k_aggregate_coalescent<VEC, 4, true, true> : k_aggregate_coalescent<VEC, 4, true, false>)
+                      : (a.F == VEC ? k_aggregate_coalescent<VEC, 4, false, true> : k_aggregate_coalescent<VEC, 4, false, false>);
   if constexpr (VEC == 4)
-    if (a.F > 4) kern = k_aggregate_coalescent<VEC, 2, false>;
+    if (a.F > 4) kern = a.plain ? k_aggregate_coalescent<VEC, 2, true, false> : k_aggregate_coalescent<VEC, 2, false, false>;
   if (blocks > 0) hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kBlock), 0, st, a);
-  if (a.n_hub > 0) {
+  if (a.n_hub > 0 && !a.direct) {
     const int64_t hb = ((int64_t)a.n_hub + kWavesPerBlock - 1) / kWavesPerBlock * a.nslices;
     hipLaunchKernelGGL((k_hub_finish_coalescent<VEC>), dim3((unsigned)hb), dim3(kBlock), 0, st, a);
   }
@@ -1392,9 +1486,13 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
   a.scol_c = f->scol_c;
   a.scol_d = f->scol_d;
   a.swd = f->swd;
-  a.sub_log2 = f->sub_log2;
-  a.nclass = f->nclass;
-  a.nvp = (int64_t)f->n_items * f->nclass;
+  a.item_v0 = f->item_v0;
+  a.item_v1 = f->item_v1;
+  a.plain = f->plain_units && f->n_items > 0;  // (without hub rows both kernels do the same; the other has fewer registers)
+  a.direct = a.plain && f->n_items == f->n_hub;
+  a.sub_log2 = f->plain_units ? 0 : f->sub_log2;
+  a.nclass = f->plain_units ? 1 : f->nclass;
+  a.nvp = a.direct ? 0 : (int64_t)f->n_items * a.nclass;
   a.n_short = f->n_short;
   a.n_long = f->n_long;
   a.n_items = f->n_items;
@@ -1525,7 +1623,8 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
     auto waves = [&]() {
       return ((int64_t)(f->n_short + a.batch_short - 1) / a.batch_short +
               (int64_t)(f->n_long + a.batch_mid - 1) / a.batch_mid +
-              (int64_t)(f->n_items + a.batch_wide - 1) / a.batch_wide * f->nclass) * slices_run;
+              (a.plain ? (int64_t)f->n_items * kWavesPerBlock
+                       : (int64_t)(f->n_items + a.batch_wide - 1) / a.batch_wide * f->nclass)) * slices_run;
     };
     // With the update fused in, a workgroup first copies W to LDS and a wave multiplies 16 rows at a
     // time, so batches stay longer (N = 200k, F = Fo = 64: 4 to 8 rows per wave take 1.36 ms, 32 take
@@ -1562,14 +1661,15 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
     auto blocks_for = [](int64_t items, int per_wave) {
       return (int32_t)((items + (int64_t)kWavesPerBlock * per_wave - 1) / ((int64_t)kWavesPerBlock * per_wave));
     };
-    a.blocks_wide = blocks_for(f->n_items, a.batch_wide);
+    a.blocks_wide = a.plain ? 0 : blocks_for(f->n_items, a.batch_wide);
     a.blocks_mid = blocks_for(f->n_long, a.batch_mid);
     a.blocks_short = blocks_for(f->n_short, a.batch_short);
     if (!coalescent) {
       // phases start at multiples of 8 workgroups, with runs of slices the short rows as well
       if (a.order == 2) a.blocks_mid = align_xcd(a.blocks_mid);
       a.blocks_short += (kClasses - (a.blocks_mid + a.blocks_short) % kClasses) % kClasses;
-      a.blocks_per_phase = ((int64_t)kClasses * a.blocks_wide << f->sub_log2) + a.blocks_mid + a.blocks_short;
+      const int64_t hub_blocks = a.plain ? f->n_items : (int64_t)kClasses * a.blocks_wide << f->sub_log2;
+      a.blocks_per_phase = hub_blocks + a.blocks_mid + a.blocks_short;
     }
   }
 

@@ -1405,7 +1405,18 @@ int wait_totals(const TotalsTicket &ticket, hipStream_t st, FrameTotals *out) {
   return PIPAD_OK;
 }
 
-void frame_take_options(pipad_frame *f) {
+// Frames whose hub rows need no column classes: up to 64k nodes with 4M entries in all snapshots together.  The
+// classes spread the gathers of long rows over the eight L2s, for a launch that copies these rows and one
+// that adds up their partial sums; where a matrix is not much larger than an L2 that costs more than it
+// gives.  R-MAT frames, classes against a workgroup per row: N = 10k, k = 5, F = 16 aggregation 14.2 -> 10.6 us, F = 64
+// 24.9 -> 20.8, with the build (F = 32) 66 -> 56; N = 32k, 20 entries per row, k = 4: F = 64 55 -> 56, with the build 92 -> 81;
+// N = 60k, k = 1 64 -> 56.  Chung-Lu, N = 40k, k = 4: F = 64 58 -> 55, with the build 85 -> 73.  Past the line: R-MAT,
+// N = 60k, 20 entries per row, k = 8: F = 64 167 -> 181.  (With a smaller mid_max rows that a wave does better with
+// would be among them.)
+constexpr int32_t kPlainNodes = 65536, kPlainRow = 512;
+constexpr int64_t kPlainEntries = (int64_t)4 << 20;
+
+void frame_take_options(pipad_frame *f, int64_t entries) {
   const int64_t lim = (int64_t)1 << 30;  // thresholds beyond any int32 row length mean "never"
   f->opt = options();
   f->short_max = (int32_t)std::clamp<int64_t>(f->opt.short_max, 0, lim);
@@ -1414,6 +1425,7 @@ void frame_take_options(pipad_frame *f) {
   f->hub_segment = (int32_t)std::clamp<int64_t>(f->opt.hub_segment, 1, lim);
   f->sub_log2 = f->opt.sub_classes >= 4 ? 2 : f->opt.sub_classes >= 2 ? 1 : 0;
   f->nclass = kClasses << f->sub_log2;
+  f->plain_units = f->n <= kPlainNodes && entries <= kPlainEntries && f->mid_max >= kPlainRow;
 }
 
 void want_lists(Arena &a, pipad_frame *f, int64_t entries) {
@@ -1475,8 +1487,8 @@ int set_list_sizes(pipad_frame *f, const FrameTotals &v) {
   f->n_long = (int32_t)v.mid;
   f->n_short = f->n - f->n_long - f->n_hub;
   f->short_entries = (int64_t)v.short_entries;
-  f->split_c = (int64_t)v.split_c;
-  f->split_d = (int64_t)v.split_d;
+  f->split_c = f->plain_units ? 0 : (int64_t)v.split_c;
+  f->split_d = f->plain_units ? 0 : (int64_t)v.split_d;
   if (f->split_c + f->split_d >= ((int64_t)1 << 31) ||
       (int64_t)(f->k + 1) * f->n_items * (f->nclass + 1) >= ((int64_t)1 << 31))
     return PIPAD_ERR_TOO_LARGE;
@@ -1484,6 +1496,7 @@ int set_list_sizes(pipad_frame *f, const FrameTotals &v) {
 }
 
 void want_split(Arena &a, pipad_frame *f) {
+  if (f->plain_units) return;
   a.want(&f->sptr, (size_t)(f->k + 1) * (f->nclass + 1) * f->n_items);
   a.want(&f->scol_c, (size_t)f->split_c);
   a.want(&f->scol_d, (size_t)f->split_d);
@@ -1492,7 +1505,7 @@ void want_split(Arena &a, pipad_frame *f) {
 }
 
 int build_split_arrays(pipad_frame *f, hipStream_t st) {
-  if (f->n_items == 0) return PIPAD_OK;
+  if (f->n_items == 0 || f->plain_units) return PIPAD_OK;
   SplitArgs g;
   std::memset(&g, 0, sizeof(g));
   g.n_units = f->n_items;
@@ -1555,7 +1568,7 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
   f->n = n;
   f->k = k;
   f->own_memory = alloc == nullptr;
-  frame_take_options(f);
+  frame_take_options(f, entries);
   Allocator A{alloc, alloc_ctx, f};
   f->alloc = alloc;
   f->alloc_ctx = alloc_ctx;
@@ -1655,7 +1668,7 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
     const int cap = k <= 16 ? Mark<512>::kCap : Mark<256>::kCap, waves = k <= 16 ? k : (k + 1) / 2;
     auto mark = k <= 16 ? k_mark<512, 1> : k_mark<256, 2>;
     hipLaunchKernelGGL(mark, dim3((unsigned)g.ntiles), dim3((unsigned)(waves * kWave)), (size_t)k * cap * sizeof(uint32_t),
-                       st, s, g, f->mid_max);
+                       st, s, g, f->plain_units ? INT32_MAX : f->mid_max);  // (the classes' copies hold the hub rows' scales)
   }
   const TotalsTicket ticket = expect_totals(totals);
   {

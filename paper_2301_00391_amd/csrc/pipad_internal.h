@@ -110,9 +110,12 @@ struct pipad_frame {
   int32_t *scol_d = nullptr;         // [split_d]
   float *swc[PIPAD_MAX_K] = {};      // each [split_c]
   float *swd = nullptr;              // [split_d]
+  // Small frames need no classes: a workgroup walks a unit from the lists of the parts themselves, and none
+  // of the arrays above is there.
+  bool plain_units = false;
 
-  // Scratch for the partial sums of the class parts: nclass per hub unit * k * F floats, grown on
-  // demand.
+  // Scratch for the partial sums of the class parts: nclass per hub unit * k * F floats (plain units: one
+  // per unit, none where every hub row is one unit), grown on demand.
   float *partial = nullptr;
   size_t partial_floats = 0;
 };
@@ -218,7 +221,7 @@ __host__ __device__ inline uint32_t hub_units(int64_t total, int32_t threshold, 
   return total <= threshold ? 1u : (uint32_t)((total + segment - 1) / segment);
 }
 // Copies the thresholds from the options into a new frame (clamped to what int32 sizes allow).
-void frame_take_options(pipad_frame *f);
+void frame_take_options(pipad_frame *f, int64_t entries);  // (of all snapshots)
 // The class-grouped copies of the hub rows' entries (sptr, scol_c, scol_d, swc, swd), once the
 // frame's parts, D^-1/2 and row lists are in place.
 int build_split_arrays(pipad_frame *f, hipStream_t st);

@@ -471,6 +471,7 @@ int transpose_frame(const pipad_frame *f, pipad_alloc_fn alloc, void *alloc_ctx,
   g->hub_segment = f->hub_segment;
   g->sub_log2 = f->sub_log2;
   g->nclass = f->nclass;
+  g->plain_units = f->plain_units;
   g->nnz_c = f->nnz_c;
   for (int t = 0; t < k; ++t) g->nnz_d[t] = f->nnz_d[t];
   Allocator A{alloc, alloc_ctx, g};
