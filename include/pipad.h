@@ -259,13 +259,15 @@ const char *pipad_last_hip_error(void);
  * Unknown keys, negative values and values beyond a key's range return PIPAD_ERR_INVALID_ARG.
  * Keys (row lengths count common + longest exclusive entries of a row; at most 2^30):
  *   "short_max"      rows with at most this many entries are walked whole by one small lane team,
- *                    several rows per wave (default 64)
+ *                    several rows per wave (default 64; left at that, 32 or 48 in frames of up
+ *                    to 393216 entries in all snapshots together)
  *   "mid_max"        rows up to this length are walked whole by one wave; longer rows ("hub rows")
  *                    are stored a second time with their entries grouped by a hash class of the
  *                    column, and the part of a row in class x is walked on XCD x only, whose L2
  *                    then caches just that class's rows of X; the 8 partial sums per row are added
  *                    up in a fixed order by a second kernel (default 512; below short_max: as
- *                    short_max)
+ *                    short_max).  At 512 and more, frames of up to 65536 nodes and 2^22 entries in
+ *                    all snapshots together have them walked by four waves each instead.
  *   "hub_threshold"  hub rows with more entries than this are first cut into units (default 2048)
  *   "hub_segment"    entries per unit of a cut row (default 2048)
  *   "sub_classes"    column classes per XCD, 1, 2 or 4 (other values are rounded down to these):

@@ -1416,10 +1416,22 @@ int wait_totals(const TotalsTicket &ticket, hipStream_t st, FrameTotals *out) {
 constexpr int32_t kPlainNodes = 65536, kPlainRow = 512;
 constexpr int64_t kPlainEntries = (int64_t)4 << 20;
 
+// Longest row that one lane team walks, where the option stands at its default of 64: a frame of few
+// entries has few waves, and the chain of such a row's gathers (a team of 8 lanes takes 16 rounds for 64
+// entries) is most of its time.  Measured up to 0.4M entries in all snapshots together, N = 1k .. 100k, F = 2 .. 128,
+// R-MAT and Chung-Lu: 32 against 64 is 10 to 13 % faster in the mean for k = 1 .. 4 (fused update 4 to 6 %), at worst
+// 7 % slower; for more snapshots, which bring more waves, 5 % and at worst 14 % slower, 48 is 4 % faster and at
+// worst 6 % slower.  With more entries 48 is between 19 % faster and 12 % slower, 32 up to 30 % slower
+// (the fused update with F = 16, k = 4, 0.5M entries 7 %).
+static int64_t short_rows_up_to(int64_t option, int32_t k, int64_t entries) {
+  if (option != Options().short_max || entries > (3 << 17)) return option;
+  return k <= 4 ? option / 2 : option / 4 * 3;
+}
+
 void frame_take_options(pipad_frame *f, int64_t entries) {
   const int64_t lim = (int64_t)1 << 30;  // thresholds beyond any int32 row length mean "never"
   f->opt = options();
-  f->short_max = (int32_t)std::clamp<int64_t>(f->opt.short_max, 0, lim);
+  f->short_max = (int32_t)std::clamp<int64_t>(short_rows_up_to(f->opt.short_max, f->k, entries), 0, lim);
   f->mid_max = (int32_t)std::clamp<int64_t>(f->opt.mid_max, f->short_max, lim);
   f->hub_threshold = (int32_t)std::clamp<int64_t>(f->opt.hub_threshold, 1, lim);
   f->hub_segment = (int32_t)std::clamp<int64_t>(f->opt.hub_segment, 1, lim);

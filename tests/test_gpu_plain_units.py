@@ -75,3 +75,11 @@ def test_other_paths(pipad, lengths):  # noqa: F811
         rows, cols = csr_to_coo(n, *lists[t])
         z, bound = oracle.aggregate_transposed(n, cols, rows, X[t])
         check_y(Z[t].cpu().numpy(), z, bound, f"transposed, snapshot {t}")
+
+
+@pytest.mark.parametrize("k", [1, 4, 5])
+@pytest.mark.parametrize("F,layout", [(4, "list"), (16, "list"), (64, "list"), (3, "wide")])
+def test_longest_row_of_a_lane_team(pipad, k, F, layout):  # noqa: F811
+    """Small frames leave rows of more than 32 or 48 entries to a whole wave."""
+    n, lists = frame_lists(k, 0.98, [31, 32, 33, 34, 47, 48, 49, 50, 63, 64, 65, 66], n=700)
+    run_case(pipad, n, lists, F, seed=k, layout=layout)
