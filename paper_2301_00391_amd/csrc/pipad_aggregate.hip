@@ -220,10 +220,12 @@ __device__ __forceinline__ Slice slice_setup(const AggArgs &a, int slice, int fl
   // F need not be a multiple of vec: the lane whose columns would go past the row's end takes the
   // last vec columns (it computes and stores some of its neighbour's again, with the same bits)
   s.fcol = min(s.fcol, max(a.F - vec, 0));
-  const int col = s.fvalid ? s.fcol : 0;  // idle lanes read column 0 and never store
+  // (idle lanes read the row's last columns as well, and never store: lines that the slice's other lanes touch.
+  // Reading column 0 instead brought another line of every gathered row into the last slice: N = 200k,
+  // k = 4, F = 96 783 -> 605 us, F = 100 993 -> 798.)
   s.xt = a.X[t];
-  s.xb = a.X[t] + col;
-  s.yb = a.Y[t] ? a.Y[t] + col : nullptr;
+  s.xb = a.X[t] + s.fcol;
+  s.yb = a.Y[t] ? a.Y[t] + s.fcol : nullptr;
   s.ht = a.H[t];
   s.dv = a.dinv + (int64_t)t * a.n;
   s.wc = a.wc[t];
@@ -305,7 +307,7 @@ __device__ __forceinline__ void walk(const Lists &l, int32_t cs, int32_t clen, i
   const uint32_t row_bytes = (uint32_t)ldx * 4u;
   // FAST addressing: wave-uniform matrix base + 32-bit (row offset + this lane's column offset)
   const char *xbytes = reinterpret_cast<const char *>(s.xt);
-  const uint32_t lane_bytes = (uint32_t)(s.fvalid ? s.fcol : 0) * 4u;
+  const uint32_t lane_bytes = (uint32_t)s.fcol * 4u;
   const float *xcol = s.xb;
   const int chunk = team_lanes * EPL;
   Staged *const mine_lds = lds + team_base * EPL;
@@ -626,7 +628,7 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
     // ---- a hub unit by the whole workgroup, a quarter of its entries per wave, the waves' sums added in
     //      order: a row of 2048 entries has 32 rounds of gathers one after the other (F = 64), as a mid row
     //      of 512, and is finished here unless it is cut
-    __shared__ typename VT::T sums[kWavesPerBlock][kWave / VEC];
+    __shared__ typename VT::T sums[kWavesPerBlock][kWave / 2];
     const Piece p = unit_piece(a, w, s.rpd, wave);
     Lists l;
     l.colc = a.col_c;
@@ -1575,9 +1577,17 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
     a.fchunks = 1;
   }
   // slice geometry: LS lanes of VEC columns each, at most 64 columns per slice (a gathered piece
-  // of a row is then at most 256 bytes: two cache lines)
+  // of a row is then at most 256 bytes: two cache lines).  Rows of 65 to 128 columns go in one slice where
+  // that touches fewer lines or there would be a half-empty second one: if they do not start at
+  // lines, so that two slices both fetch the line where they meet, or are no longer than three.  Two
+  // slices against one, k = 4, N = 200k Chung-Lu / 50k R-MAT / 500k Chung-Lu: dense rows, F = 66 751 / 139 / 1079 -> 550 /
+  // 114 / 827 us, F = 100 984 / 153 / 1398 -> 802 / 136 / 1111, F = 127 1238 / 186 / 1789 -> 1063 / 170 / 1456; rows on
+  // lines, F = 66 773 / 131 / 1122 -> 608 / 121 / 892, F = 80 603 / 124 / 919 -> 609 / 120 / 895, but F = 112
+  // 791 / 134 / 1157 -> 848 / 145 / 1206: two.
   const int vec = coalescent ? cvec : vec4 ? 4 : 1;
-  int max_cols = 64;
+  bool on_lines = ldx % 32 == 0;
+  for (int t = 0; t < f->k; ++t) on_lines = on_lines && reinterpret_cast<uintptr_t>(X[t]) % 128 == 0;
+  int max_cols = !fused && F <= (on_lines ? 96 : 128) ? 128 : 64;
   if (opt.slice_cols > 0 && !fused) max_cols = (int)std::min<int64_t>(64, opt.slice_cols);
   const int cols = std::min(F, max_cols);
   if (!coalescent) {

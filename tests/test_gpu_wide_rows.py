@@ -1,0 +1,52 @@
+"""Rows of more than 64 columns: one slice or two by where the rows start, the last slice not always full; against
+the oracle, with rows on cache lines, dense ones and ones that start anywhere."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+import oracle  # noqa: E402
+import synth  # noqa: E402
+from _util import check_y, csr_to_coo  # noqa: E402
+from test_gpu_build_tiles import csr, rand_pairs  # noqa: E402
+from test_gpu_parity import pipad, _reset_options  # noqa: E402,F401
+
+
+def matrices(values, ld, offset):
+    """Device copies of the matrices with row stride ld, `offset` floats behind where an allocation starts."""
+    got = []
+    for v in values:
+        n, F = v.shape
+        flat = torch.full((offset + n * ld,), float("nan"), device="cuda:0")
+        x = flat[offset:].view(n, ld)[:, :F]
+        x.copy_(torch.from_numpy(v))
+        got.append(x)
+    return got
+
+
+@pytest.mark.parametrize("hubs", [False, True])
+@pytest.mark.parametrize("F", [33, 64, 65, 66, 67, 80, 95, 96, 97, 100, 127, 128, 129, 160, 250])
+def test_any_start_of_a_row(pipad, F, hubs):  # noqa: F811
+    rng = np.random.default_rng(F)
+    n, k = 1300, 3
+    pool = rand_pairs(rng, n, 9 * n)
+    if hubs:
+        pool = np.concatenate([pool, np.stack([np.repeat([7, 900], 1250), rng.integers(0, n, 2500)], 1)])
+        pipad.set_option("mid_max", 200)  # class parts; else a workgroup per row or a wave
+    lists = [csr(n, pool[rng.random(len(pool)) < 0.9]) for _ in range(k)]
+    snaps = [(torch.from_numpy(rp).cuda(), torch.from_numpy(c).cuda()) for rp, c in lists]
+    frame = pipad.frame_build_overlap(snaps)
+    X = [synth.features(F, t, n, F) for t in range(k)]
+    ref = [oracle.aggregate(n, *csr_to_coo(n, *lists[t]), X[t], threads=8)[1:3] for t in range(k)]
+    lines = (F + 31) // 32 * 32
+    for ld, offset in ((lines, 0), (F, 0), (lines, 5), (F + 3, 1)):
+        xs = matrices(X, ld, offset)
+        Y = pipad.frame_aggregate(frame, xs)
+        for t in range(k):
+            check_y(Y[t].cpu().numpy(), *ref[t], f"stride {ld}, offset {offset}, snapshot {t}")
+        Z = pipad.frame_aggregate(frame, xs, static_scratch=True)
+        some = [torch.zeros_like(y) for y in Y]
+        pipad.frame_aggregate_subset(frame, [2, 1], xs, some)
+        assert all(torch.equal(a, b) for a, b in zip(Y, Z))
+        assert torch.equal(some[1], Y[1]) and torch.equal(some[2], Y[2])
