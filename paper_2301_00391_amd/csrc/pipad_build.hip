@@ -751,25 +751,29 @@ __global__ __launch_bounds__(kTileScanBlock) void k_scan_counts(ScanArgs a, Fram
 }
 
 // The transposed frame: the parts' row pointers are known, and with them everything but the totals.
+__device__ inline void send_totals(const RowCounts &all, FrameTotals *out, uint32_t seq) {
+  FrameTotals v;
+  v.nnz_c = 0;
+  v.mid = all.mid;
+  v.hub = all.hub;
+  v.units = all.units;
+  v.short_entries = all.short_entries;
+  v.split_c = all.common;
+  v.split_d = all.entries;
+  v.bad = 0;
+  v.seq = 0;
+  *out = v;
+  __threadfence_system();
+  __hip_atomic_store(&out->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 __global__ __launch_bounds__(kTileScanBlock) void k_scan_row_counts(const RowCounts *row_cnt, RowCounts *row_pre,
                                                                      int64_t row_blocks, FrameTotals *out,
                                                                      uint32_t seq) {
   const RowCounts all = scan_rows(row_cnt, row_pre, 0, row_blocks);
   if (threadIdx.x == 0) {
     row_pre[row_blocks] = all;
-    FrameTotals v;
-    v.nnz_c = 0;
-    v.mid = all.mid;
-    v.hub = all.hub;
-    v.units = all.units;
-    v.short_entries = all.short_entries;
-    v.split_c = all.common;
-    v.split_d = all.entries;
-    v.bad = 0;
-    v.seq = 0;
-    *out = v;
-    __threadfence_system();
-    __hip_atomic_store(&out->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    send_totals(all, out, seq);
   }
 }
 
@@ -945,17 +949,56 @@ __global__ __launch_bounds__(kBlock) void k_count_rows(PartRows p, int32_t n, in
   count_rows(rc, i64 < n, L, entries, lc, cnt + blockIdx.x);
 }
 
-__global__ __launch_bounds__(kBlock) void k_list_rows(PartRows p, int32_t n, int32_t k, const RowCounts *cnt, ListArgs q) {
+// Sums of up to 256 row blocks' counts, in front of block `upto` and of all, for every thread.
+__device__ inline void sum_row_counts(const RowCounts *cnt, int32_t blocks, int32_t upto, RowCounts *front, RowCounts *all) {
+  __shared__ uint32_t sums[2][kRowSums][kWavesPerBlock];
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, b = threadIdx.x;
+  const RowCounts c = cnt[min(b, max(blocks - 1, 0))];
+  uint32_t v[2][kRowSums];
+  split_counts(c, b < min(upto, blocks), v[0]);
+  split_counts(c, b < blocks, v[1]);
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int x = 0; x < kRowSums; ++x) {
+      const uint32_t sum = wave_sum(v[u][x]);
+      if (lane == kWave - 1) sums[u][x][wave] = sum;
+    }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int x = 0; x < kRowSums; ++x) {
+      v[u][x] = 0;
+#pragma unroll
+      for (int w = 0; w < kWavesPerBlock; ++w) v[u][x] += sums[u][x][w];
+    }
+  const RowCounts none = {0, 0, 0, 0, 0, 0};
+  *front = join_counts(none, v[0]);
+  *all = join_counts(none, v[1]);
+}
+
+// SUM: `cnt` holds the counts of every block, of which there are no more than a workgroup has threads, and each
+// workgroup adds up what it needs (a launch less, 4 us where launches decide); else what k_scan_row_counts
+// made of them.
+template <bool SUM>
+__global__ __launch_bounds__(kBlock) void k_list_rows(PartRows p, int32_t n, int32_t k, const RowCounts *cnt, ListArgs q,
+                                                       FrameTotals *out, uint32_t seq) {
   const int64_t i64 = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  const int32_t i = (int32_t)min(i64, (int64_t)n);
-  if (i64 == n) {
-    const RowCounts total = cnt[((int64_t)n + kBlock - 1) / kBlock];
-    q.hub_item_off[total.hub] = (int32_t)total.units;
+  const int32_t i = (int32_t)min(i64, (int64_t)n), row_blocks = (int32_t)(((int64_t)n + kBlock - 1) / kBlock);
+  RowCounts first, total;
+  if (SUM) {
+    sum_row_counts(cnt, row_blocks, (int32_t)blockIdx.x, &first, &total);
+    if (i64 == 0) send_totals(total, out, seq);
+  } else {
+    first = cnt[blockIdx.x];
+    total = cnt[row_blocks];
   }
+  if (i64 == n) q.hub_item_off[total.hub] = (int32_t)total.units;
   int32_t lc;
   int64_t L;
   const int64_t entries = part_lengths(p, n, k, i, &lc, &L);
-  list_row(q, i64 < n, i, L, lc, entries, cnt[blockIdx.x], [](uint64_t e, uint32_t c, int32_t *c0, int32_t *d0) {
+  list_row(q, i64 < n, i, L, lc, entries, first, [](uint64_t e, uint32_t c, int32_t *c0, int32_t *d0) {
     *c0 = (int32_t)c;
     *d0 = (int32_t)e;
   });
@@ -1485,10 +1528,12 @@ int launch_list_rows(const pipad_frame *f, RowCounts *cnt, RowCounts *pre, const
   for (int t = 0; t < f->k; ++t) p.rowptr[1 + t] = f->rowptr_d[t];
   const dim3 blocks = grid1(f->n, kBlock);
   hipLaunchKernelGGL(k_count_rows, blocks, dim3(kBlock), 0, st, p, f->n, f->k, row_classes(f), cnt);
-  hipLaunchKernelGGL(k_scan_row_counts, dim3(1), dim3(kTileScanBlock), 0, st, cnt, pre, (int64_t)blocks.x,
-                     ticket.where, ticket.seq);
-  hipLaunchKernelGGL(k_list_rows, grid1((int64_t)f->n + 1, kBlock), dim3(kBlock), 0, st, p, f->n, f->k, pre,
-                     list_args(f));
+  const bool sum = blocks.x <= kBlock;
+  if (!sum)
+    hipLaunchKernelGGL(k_scan_row_counts, dim3(1), dim3(kTileScanBlock), 0, st, cnt, pre, (int64_t)blocks.x,
+                       ticket.where, ticket.seq);
+  hipLaunchKernelGGL(sum ? k_list_rows<true> : k_list_rows<false>, grid1((int64_t)f->n + 1, kBlock), dim3(kBlock), 0, st, p,
+                     f->n, f->k, sum ? cnt : pre, list_args(f), ticket.where, ticket.seq);
   PIPAD_HIP(hipGetLastError());
   return PIPAD_OK;
 }

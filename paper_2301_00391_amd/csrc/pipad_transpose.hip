@@ -37,6 +37,10 @@ constexpr int kSortBlock = 512;                      // threads per workgroup of
 constexpr int kSortWaves = kSortBlock / kWave;
 constexpr int32_t kRowsWalked = 4096;                // a wave's entries find their rows by going through so many at most
 
+// Up to so many tiles in every part a workgroup of k_radix_scatter adds up the part's counts itself, which
+// takes as long as k_radix_scan but no launch: with the lists' sums made the same way (k_list_rows) N = 2k and
+// 8k, k = 3 and 4, transposition and aggregation 80 -> 69 us, N = 20k R-MAT 84 -> 79; with 32 tiles at most 81.
+constexpr uint32_t kFewTiles = 64;
 struct SortArgs {
   int32_t nparts;                       // 1 + k
   int32_t n;
@@ -205,7 +209,8 @@ __device__ inline int32_t wave_row_of_entry(const int32_t *rp, int32_t n, int32_
 // place.  The next tile's go right behind them, so an XCD takes a run of tiles and its L2 puts the lines
 // together (3.4 M entries: 38 -> 33 us; tiles dealt to the XCDs in turn, whole lines never met).  With rows
 // found by a running maximum instead of a binary search per entry 43 -> 38 us.
-template <int R>
+// FEW: no part has more than kFewTiles tiles (an instance of its own: as a branch it took 24 registers more).
+template <int R, bool FEW = false>
 __global__ __launch_bounds__(kSortBlock) void k_radix_scatter(SortArgs g) {
   __shared__ uint16_t rank_of[kSortWaves][kMaxDigits];  // counts, then the first place in the tile, per wave
   __shared__ int32_t stage[kSortBlock * R];             // the tile's keys, then its values, in digit order
@@ -298,13 +303,29 @@ __global__ __launch_bounds__(kSortBlock) void k_radix_scatter(SortArgs g) {
     constexpr int PER = kMaxDigits / kSortBlock;
     const uint32_t *hist = g.hist + ((uint64_t)tile << g.bits), *total = g.total + ((uint64_t)r.p << g.bits);
     uint32_t in_tile[PER], in_part[PER], before[PER], all = 0, all_part = 0;
+    if constexpr (FEW) {
+      // (all counts of the part, of which there are few, instead of a launch that adds them up)
 #pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      const int d = tid * PER + q, dc = min(d, digits - 1);
-      before[q] = hist[dc];
-      in_part[q] = total[dc];
-      if (d >= digits) in_part[q] = 0;
+      for (int q = 0; q < PER; ++q) before[q] = in_part[q] = 0;
+      const uint32_t *part = hist - ((uint64_t)r.tile << g.bits);
+#pragma unroll 8
+      for (uint32_t t = 0; t < r.tiles; ++t)
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+          const uint32_t c = part[((uint64_t)t << g.bits) + min(tid * PER + q, digits - 1)];
+          before[q] += t < r.tile ? c : 0u;
+          in_part[q] += c;
+        }
+    } else {
+#pragma unroll
+      for (int q = 0; q < PER; ++q) {
+        before[q] = hist[min(tid * PER + q, digits - 1)];
+        in_part[q] = total[min(tid * PER + q, digits - 1)];
+      }
     }
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
+      if (tid * PER + q >= digits) in_part[q] = 0;
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
       in_tile[q] = 0;
@@ -542,6 +563,9 @@ int transpose_frame(const pipad_frame *f, pipad_alloc_fn alloc, void *alloc_ctx,
     tiles += ((int64_t)(s.part_off[p + 1] - s.part_off[p]) + tile - 1) / tile;
   }
   s.tile_off[k + 1] = (uint32_t)tiles;
+  uint32_t most_tiles = 0;
+  for (int p = 0; p <= k; ++p) most_tiles = std::max(most_tiles, s.tile_off[p + 1] - s.tile_off[p]);
+  const bool few = per_thread == 4 && most_tiles <= kFewTiles;
   int bits = 1;
   while (((int64_t)1 << bits) < n) ++bits;
   const int passes = bits <= kMaxDigitBits - 1 ? 1 : (bits + kMaxDigitBits - 1) / kMaxDigitBits;
@@ -596,10 +620,13 @@ int transpose_frame(const pipad_frame *f, pipad_alloc_fn alloc, void *alloc_ctx,
       s.val_in = pass % 2 == 0 ? val_b : val_a;
       s.val_out = pass % 2 == 0 ? val_a : val_b;
       auto hist = per_thread == 16 ? k_radix_hist<16> : per_thread == 8 ? k_radix_hist<8> : k_radix_hist<4>;
-      auto scatter = per_thread == 16 ? k_radix_scatter<16> : per_thread == 8 ? k_radix_scatter<8> : k_radix_scatter<4>;
+      auto scatter = per_thread == 16 ? k_radix_scatter<16> : per_thread == 8 ? k_radix_scatter<8>
+                     : few             ? k_radix_scatter<4, true>
+                                       : k_radix_scatter<4>;
       const int64_t copiers = pass == 0 ? std::min<int64_t>((s.dinv_pieces + kSortBlock - 1) / kSortBlock, 2048) : 0;
       hipLaunchKernelGGL(hist, dim3((unsigned)(tiles + copiers)), dim3(kSortBlock), 0, st, s);
-      hipLaunchKernelGGL(k_radix_scan, grid1(1 << s.bits, kWave, k + 1), dim3(kScanWaves * kWave), 0, st, s);
+      if (!few)
+        hipLaunchKernelGGL(k_radix_scan, grid1(1 << s.bits, kWave, k + 1), dim3(kScanWaves * kWave), 0, st, s);
       hipLaunchKernelGGL(scatter, dim3((unsigned)align_xcd((int32_t)tiles)), dim3(kSortBlock), 0, st, s);
       PIPAD_TRY_T(hipGetLastError());
       sorted_keys = s.key_out;
