@@ -680,6 +680,24 @@ __device__ inline RowCounts scan_rows(const RowCounts *cnt, RowCounts *pre, int6
   return front;
 }
 
+// Sends the sizes of a frame to the host: `common` and `in_hubs` common entries, `exclusive` ones in hub rows.
+__device__ inline void send_totals(const RowCounts &all, uint32_t common, uint64_t in_hubs, uint64_t exclusive,
+                                   uint32_t bad, FrameTotals *out, uint32_t seq) {
+  FrameTotals v;
+  v.nnz_c = common;
+  v.mid = all.mid;
+  v.hub = all.hub;
+  v.units = all.units;
+  v.short_entries = all.short_entries;
+  v.split_c = in_hubs;
+  v.split_d = exclusive;
+  v.bad = bad;
+  v.seq = 0;
+  *out = v;
+  __threadfence_system();
+  __hip_atomic_store(&out->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 struct ScanArgs {
   const uint2 *tile_cnt;
   uint2 *tile_pre;
@@ -734,46 +752,19 @@ __global__ __launch_bounds__(kTileScanBlock) void k_scan_counts(ScanArgs a, Fram
   if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
     a.tile_pre[a.ntiles] = make_uint2(carry[0], carry[1]);
     a.row_pre[a.row_blocks] = all;
-    FrameTotals v;
-    v.nnz_c = carry[0];
-    v.mid = all.mid;
-    v.hub = all.hub;
-    v.units = all.units;
-    v.short_entries = all.short_entries;
-    v.split_c = carry[1];
-    v.split_d = all.entries - (uint64_t)a.k * carry[1];  // (what the common entries take in every snapshot)
-    v.bad = *a.bad;
-    v.seq = 0;
-    *out = v;
-    __threadfence_system();
-    __hip_atomic_store(&out->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    // (of all entries of the hub rows, what the common ones take in every snapshot is not exclusive)
+    send_totals(all, carry[0], carry[1], all.entries - (uint64_t)a.k * carry[1], *a.bad, out, seq);
   }
 }
 
 // The transposed frame: the parts' row pointers are known, and with them everything but the totals.
-__device__ inline void send_totals(const RowCounts &all, FrameTotals *out, uint32_t seq) {
-  FrameTotals v;
-  v.nnz_c = 0;
-  v.mid = all.mid;
-  v.hub = all.hub;
-  v.units = all.units;
-  v.short_entries = all.short_entries;
-  v.split_c = all.common;
-  v.split_d = all.entries;
-  v.bad = 0;
-  v.seq = 0;
-  *out = v;
-  __threadfence_system();
-  __hip_atomic_store(&out->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
 __global__ __launch_bounds__(kTileScanBlock) void k_scan_row_counts(const RowCounts *row_cnt, RowCounts *row_pre,
                                                                      int64_t row_blocks, FrameTotals *out,
                                                                      uint32_t seq) {
   const RowCounts all = scan_rows(row_cnt, row_pre, 0, row_blocks);
   if (threadIdx.x == 0) {
     row_pre[row_blocks] = all;
-    send_totals(all, out, seq);
+    send_totals(all, 0, all.common, all.entries, 0, out, seq);
   }
 }
 
@@ -868,6 +859,74 @@ __device__ inline int32_t hub_common_before(const Tiles &g, int32_t nnz, int32_t
   return (int32_t)(v + (uint32_t)__popcll(g.bits[w] & g.hub_bits[w] & ((1ull << (e & 63)) - 1ull)));
 }
 
+// Sums of up to 256 row blocks' counts, in front of block `upto` and of all, for every thread.
+__device__ inline void sum_row_counts(const RowCounts *cnt, int32_t blocks, int32_t upto, RowCounts *front, RowCounts *all) {
+  __shared__ uint32_t sums[2][kRowSums][kWavesPerBlock];
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, b = threadIdx.x;
+  const RowCounts c = cnt[min(b, max(blocks - 1, 0))];
+  uint32_t v[2][kRowSums];
+  split_counts(c, b < min(upto, blocks), v[0]);
+  split_counts(c, b < blocks, v[1]);
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int x = 0; x < kRowSums; ++x) {
+      const uint32_t sum = wave_sum(v[u][x]);
+      if (lane == kWave - 1) sums[u][x][wave] = sum;
+    }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int x = 0; x < kRowSums; ++x) {
+      v[u][x] = 0;
+#pragma unroll
+      for (int w = 0; w < kWavesPerBlock; ++w) v[u][x] += sums[u][x][w];
+    }
+  const RowCounts none = {0, 0, 0, 0, 0, 0};
+  *front = join_counts(none, v[0]);
+  *all = join_counts(none, v[1]);
+}
+
+// Up to so many tiles k_rows adds up itself, from LDS: 2^19 base entries.
+constexpr int kSumTiles = 4 * kBlock;
+
+// What lies in front of every tile, and of all of them, into `pre`.
+__device__ inline void sum_tiles(const Tiles &g, uint2 *pre) {
+  __shared__ uint32_t front[2][kWavesPerBlock];
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, t0 = 4 * (int)threadIdx.x;
+  uint32_t c[2][4] = {};
+#pragma unroll
+  for (int q = 0; q < 4; q += 2)
+    if (t0 + q < g.ntiles) {
+      const uint4 x = *reinterpret_cast<const uint4 *>(g.tile_cnt + t0 + q);  // (padded to a pair)
+      c[0][q] = x.x;
+      c[1][q] = x.y;
+      c[0][q + 1] = t0 + q + 1 < g.ntiles ? x.z : 0u;
+      c[1][q + 1] = t0 + q + 1 < g.ntiles ? x.w : 0u;
+    }
+  uint32_t at[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const uint32_t mine = c[u][0] + c[u][1] + c[u][2] + c[u][3], incl = wave_sum(mine);
+    if (lane == kWave - 1) front[u][wave] = incl;
+    at[u] = incl - mine;
+  }
+  __syncthreads();
+  for (int w = 0; w < wave; ++w) {
+    at[0] += front[0][w];
+    at[1] += front[1][w];
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    if (t0 + q < g.ntiles) pre[t0 + q] = make_uint2(at[0], at[1]);
+    at[0] += c[0][q];
+    at[1] += c[1][q];
+  }
+  if (threadIdx.x == kBlock - 1) pre[g.ntiles] = make_uint2(at[0], at[1]);
+  __syncthreads();
+}
+
 struct RowArgs {
   int32_t *rowptr_c;
   int32_t *rowptr_d[PIPAD_MAX_K];
@@ -876,14 +935,32 @@ struct RowArgs {
 // A thread per row i in [0, n].  The exclusive row pointer is the input's minus the common one; the
 // longest row a class is decided by is the longest input row (its common entries are in all of
 // them).
-__global__ __launch_bounds__(kBlock) void k_rows(Snaps s, Tiles g, RowArgs o, ListArgs q) {
+// SUM: neither the tiles' counts nor the row blocks' are summed up yet; they are few enough for every
+// workgroup to do that (a launch less, and the host gets the sizes as early: whole steps and slides, N = 2k ..
+// 60k, 62 .. 78 -> 59 .. 74 us).
+template <bool SUM>
+__global__ __launch_bounds__(kBlock) void k_rows(Snaps s, Tiles g, RowArgs o, ListArgs q, FrameTotals *out, uint32_t seq) {
   const int64_t i64 = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   const int32_t i = (int32_t)min(i64, (int64_t)g.n), i1 = min(i + 1, g.n);
   const bool live = i64 < g.n;
   const int32_t nnz0 = s.nnz[g.base];
   const int32_t *rp0 = s.rowptr[g.base];
   const int32_t ea = rp0[i], eb = rp0[i1];
-  const RowCounts first = g.row_pre[blockIdx.x];
+  RowCounts first, total;
+  if constexpr (SUM) {
+    __shared__ uint2 pre[kSumTiles + 1];
+    sum_row_counts(g.row_cnt, (int32_t)(((int64_t)g.n + kBlock - 1) / kBlock), (int32_t)blockIdx.x, &first, &total);
+    sum_tiles(g, pre);
+    if (blockIdx.x == 0) {
+      const uint2 all = pre[g.ntiles];
+      if (threadIdx.x == 0) send_totals(total, all.x, all.y, total.entries - (uint64_t)g.k * all.y, *g.bad, out, seq);
+      for (int t = threadIdx.x; t <= g.ntiles; t += kBlock) g.tile_pre[t] = pre[t];
+    }
+    g.tile_pre = pre;
+  } else {
+    first = g.row_pre[blockIdx.x];
+    total = g.row_pre[((int64_t)g.n + kBlock - 1) / kBlock];
+  }
   int32_t before = 0, after = 0, longest = 0;
   if (nnz0 > 0) {
     before = common_before(g, nnz0, ea);
@@ -911,10 +988,7 @@ __global__ __launch_bounds__(kBlock) void k_rows(Snaps s, Tiles g, RowArgs o, Li
         if (i64 <= g.n) o.rowptr_d[t0 + u][i] = min(max(a[u] - before, 0), max(s.nnz[t0 + u] - nnz_c, 0));
       }
   }
-  if (i64 == g.n) {  // the end of the last hub row's units
-    const RowCounts total = g.row_pre[((int64_t)g.n + kBlock - 1) / kBlock];
-    q.hub_item_off[total.hub] = (int32_t)total.units;
-  }
+  if (i64 == g.n) q.hub_item_off[total.hub] = (int32_t)total.units;  // the end of the last hub row's units
   list_row(q, live, i, longest, after - before, all, first, [&](uint64_t entries, uint32_t, int32_t *c0, int32_t *d0) {
     *c0 = hub_common_before(g, nnz0, ea);
     *d0 = (int32_t)((int64_t)entries - (int64_t)g.k * *c0);
@@ -949,35 +1023,6 @@ __global__ __launch_bounds__(kBlock) void k_count_rows(PartRows p, int32_t n, in
   count_rows(rc, i64 < n, L, entries, lc, cnt + blockIdx.x);
 }
 
-// Sums of up to 256 row blocks' counts, in front of block `upto` and of all, for every thread.
-__device__ inline void sum_row_counts(const RowCounts *cnt, int32_t blocks, int32_t upto, RowCounts *front, RowCounts *all) {
-  __shared__ uint32_t sums[2][kRowSums][kWavesPerBlock];
-  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, b = threadIdx.x;
-  const RowCounts c = cnt[min(b, max(blocks - 1, 0))];
-  uint32_t v[2][kRowSums];
-  split_counts(c, b < min(upto, blocks), v[0]);
-  split_counts(c, b < blocks, v[1]);
-#pragma unroll
-  for (int u = 0; u < 2; ++u)
-#pragma unroll
-    for (int x = 0; x < kRowSums; ++x) {
-      const uint32_t sum = wave_sum(v[u][x]);
-      if (lane == kWave - 1) sums[u][x][wave] = sum;
-    }
-  __syncthreads();
-#pragma unroll
-  for (int u = 0; u < 2; ++u)
-#pragma unroll
-    for (int x = 0; x < kRowSums; ++x) {
-      v[u][x] = 0;
-#pragma unroll
-      for (int w = 0; w < kWavesPerBlock; ++w) v[u][x] += sums[u][x][w];
-    }
-  const RowCounts none = {0, 0, 0, 0, 0, 0};
-  *front = join_counts(none, v[0]);
-  *all = join_counts(none, v[1]);
-}
-
 // SUM: `cnt` holds the counts of every block, of which there are no more than a workgroup has threads, and each
 // workgroup adds up what it needs (a launch less, 4 us where launches decide); else what k_scan_row_counts
 // made of them.
@@ -989,7 +1034,7 @@ __global__ __launch_bounds__(kBlock) void k_list_rows(PartRows p, int32_t n, int
   RowCounts first, total;
   if (SUM) {
     sum_row_counts(cnt, row_blocks, (int32_t)blockIdx.x, &first, &total);
-    if (i64 == 0) send_totals(total, out, seq);
+    if (i64 == 0) send_totals(total, 0, total.common, total.entries, 0, out, seq);
   } else {
     first = cnt[blockIdx.x];
     total = cnt[row_blocks];
@@ -1728,7 +1773,8 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
                        st, s, g, f->plain_units ? INT32_MAX : f->mid_max);  // (the classes' copies hold the hub rows' scales)
   }
   const TotalsTicket ticket = expect_totals(totals);
-  {
+  const bool sum = g.ntiles <= kSumTiles && row_blocks <= kBlock;
+  if (!sum) {
     ScanArgs a;
     a.tile_cnt = g.tile_cnt;
     a.tile_pre = g.tile_pre;
@@ -1750,7 +1796,8 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
     std::memset(&o, 0, sizeof(o));
     o.rowptr_c = f->rowptr_c;
     for (int t = 0; t < k; ++t) o.rowptr_d[t] = f->rowptr_d[t];
-    hipLaunchKernelGGL(k_rows, grid1((int64_t)n + 1, kBlock), dim3(kBlock), 0, st, s, g, o, list_args(f));
+    hipLaunchKernelGGL(sum ? k_rows<true> : k_rows<false>, grid1((int64_t)n + 1, kBlock), dim3(kBlock), 0, st, s, g, o,
+                       list_args(f), ticket.where, ticket.seq);
   }
   PIPAD_TRY(hipGetLastError());
 
