@@ -295,7 +295,7 @@ __device__ __forceinline__ Raw fetch_entry(const Lists &l, int32_t cs, int32_t c
 // groups are the lanes of the team): nothing goes through LDS, whose bank conflicts took a third of the
 // coalescent kernel's time.  Same order of the sum.  N = 200k, k = 8, concatenated, F = 1 / 2 / 4 102 / 107 /
 // 111 -> 97 / 102 / 107 us; R-MAT 60k, k = 5 29 / 32.5 / 33.8 -> 27.7 / 30.8 / 32.4, 1M, k = 8 534 / 588 / 627 ->
-// 532 / 576 / 619; one matrix per snapshot, F = 1 and 4: 0 to 4 %.
+// 532 / 576 / 619.
 template <int VEC, int UNR, bool FAST, int EPL, bool ALONE = false>
 __device__ __forceinline__ void walk(const Lists &l, int32_t cs, int32_t clen, int32_t ds, int32_t len,
                             const Raw (&first)[EPL],
@@ -1522,7 +1522,9 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
     a.Y[t] = Y ? Y[t] : nullptr;
     if ((reinterpret_cast<uintptr_t>(X[t]) | reinterpret_cast<uintptr_t>(a.Y[t])) & 15u) aligned = false;
   }
-  const bool vec4 = F >= 4;
+  // (four columns: four lanes of one each; a lane alone walked a row of 64 entries in 16 rounds, and 64 such rows
+  // waited for the longest.  N = 20k, k = 4 20.4 -> 10.9 us, 200k 126 -> 98, R-MAT 200k, k = 8 190 -> 167)
+  const bool vec4 = F > 4;
   // the fast path needs 32-bit byte offsets into a snapshot's matrix
   const bool fast = (int64_t)f->n * ldx * 4 < ((int64_t)1 << 32) && !opt.agg_generic;
   // The update rides inside the aggregation kernel when a slice is a whole row of one snapshot
@@ -1592,6 +1594,13 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
   const int cols = std::min(F, max_cols);
   if (!coalescent) {
     a.ls_log2 = ceil_log2((cols + vec - 1) / vec);
+    // One or two columns: a team of four lanes as well, idle ones among them, that fetch entries together (F = 1,
+    // N = 20k, k = 4 18.7 -> 10.4 us, 200k 102 -> 78, R-MAT 1M 579 -> 564; F = 2 13.9 -> 10.7, 88 -> 82, 606 -> 595).  Their
+    // partial sums, where there are any, take the room of four columns: only where every call with k
+    // snapshots needs that much, and the fixed scratch array holds it.
+    if (F <= 2 && opt.slice_cols == 0 &&
+        (a.nvp == 0 || (f->k >= 4 && a.nvp * 16 <= (int64_t)PIPAD_STATIC_SCRATCH_BYTES)))
+      a.ls_log2 = 2;
     a.fchunks = (F + ((1 << a.ls_log2) * vec) - 1) / ((1 << a.ls_log2) * vec);
     a.nslices = f->k * a.fchunks;
   }

@@ -1,5 +1,6 @@
-"""Rows of more than 64 columns: one slice or two by where the rows start, the last slice not always full; against
-the oracle, with rows on cache lines, dense ones and ones that start anywhere."""
+"""Rows of more than 64 columns: one slice or two by where the rows start, the last slice not always full; rows of
+one to four columns, lanes of one column each; against the oracle, with rows on cache lines, dense ones and ones
+that start anywhere."""
 import numpy as np
 import pytest
 
@@ -26,10 +27,10 @@ def matrices(values, ld, offset):
 
 
 @pytest.mark.parametrize("hubs", [False, True])
-@pytest.mark.parametrize("F", [33, 64, 65, 66, 67, 80, 95, 96, 97, 100, 127, 128, 129, 160, 250])
+@pytest.mark.parametrize("F", [1, 2, 3, 4, 5, 33, 64, 65, 66, 67, 80, 95, 96, 97, 100, 127, 128, 129, 160, 250])
 def test_any_start_of_a_row(pipad, F, hubs):  # noqa: F811
     rng = np.random.default_rng(F)
-    n, k = 1300, 3
+    n, k = 1300, 3 + F % 2
     pool = rand_pairs(rng, n, 9 * n)
     if hubs:
         pool = np.concatenate([pool, np.stack([np.repeat([7, 900], 1250), rng.integers(0, n, 2500)], 1)])
