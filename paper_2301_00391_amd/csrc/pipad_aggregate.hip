@@ -429,7 +429,7 @@ __device__ __forceinline__ void sink_flush_ks(const AggArgs &a, const Slice &s, 
     av[4 * q + 0] = v.x; av[4 * q + 1] = v.y; av[4 * q + 2] = v.z; av[4 * q + 3] = v.w;
   }
   const int ws = a.Fo + 1;
-  for (int nt = 0; nt < a.Fo / 16; ++nt) {
+  for (int nt = 0; nt * 16 < a.Fo; ++nt) {  // (what lies behind the last column is never stored)
     const float *wcol = k.wl + (g * KS) * ws + 16 * nt + m;
     const float b = k.wl[(4 * KS) * ws + 16 * nt + m];  // the bias sits behind W's last row
     mfma_f4 d = {0.f, 0.f, 0.f, 0.f};
@@ -448,11 +448,18 @@ __device__ __forceinline__ void sink_flush_ks(const AggArgs &a, const Slice &s, 
     for (int r = 0; r < 4; ++r) k.tile[(4 * g + r) * kTileStride + 16 * nt + m] = d[r] + b;
   }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  const int quads = a.Fo / 4;  // 16-byte pieces of a row of H
+  const int quads = (a.Fo + 3) / 4;  // 16-byte pieces of a row of H, the last one maybe shorter
   for (int x = lane; x < k.cnt * quads; x += kWave) {
     const int row = x / quads, q = x - row * quads;
     const float4 h = *reinterpret_cast<const float4 *>(k.tile + row * kTileStride + 4 * q);
-    V<4>::store(s.ht + (int64_t)k.rows[row] * a.ldh + 4 * q, h, a.nt & 1);
+    float *out = s.ht + (int64_t)k.rows[row] * a.ldh + 4 * q;
+    if (4 * q + 4 <= a.Fo) {
+      V<4>::store(out, h, a.nt & 1);
+    } else {
+      out[0] = h.x;
+      if (4 * q + 1 < a.Fo) out[1] = h.y;
+      if (4 * q + 2 < a.Fo) out[2] = h.z;
+    }
   }
 }
 
@@ -1391,14 +1398,19 @@ int launch(const AggArgs &a, bool fast, hipStream_t st, bool fused_update = fals
 // The update behind the aggregation, from the stored results of all snapshots.
 int launch_update(const AggArgs &a, hipStream_t st) {
   const int64_t tiles = ((int64_t)a.n + 15) / 16 * a.k;
-  // weights resident in LDS when a column block of them fits (40 KB: four workgroups per CU), else straight
-  // from memory
+  // Weights resident in LDS, in as few blocks of columns of the same width as fit 64 KB (every block reads all of
+  // Y), else straight from memory.  With at most 40 KB, for four workgroups per CU, blocks of 64 and 16 columns read
+  // Y twice: N = 200k, k = 4, F = 128, Fo = 80 277 -> 200 us, F = 80, Fo = 128 314 -> 217; R-MAT 60k, k = 8 195 -> 156, 239 -> 181.
   const int kpad = (a.F + 3) / 4 * 4;
-  int cbw = std::min((a.Fo + 15) / 16 * 16, kUpdMaxCols);
-  while (cbw > 16 && (size_t)(kpad + 1) * (cbw + kUpdPad) * 4 > (40u << 10)) cbw -= 16;
-  const size_t lds = (size_t)(kpad + 1) * (cbw + kUpdPad) * 4;
-  if (lds <= (40u << 10)) {
-    const int64_t col_blocks = (a.Fo + cbw - 1) / cbw;
+  int64_t col_blocks = 0;
+  int cbw = 0;
+  size_t lds = 0;
+  do {
+    ++col_blocks;
+    cbw = (int)((a.Fo + 16 * col_blocks - 1) / (16 * col_blocks)) * 16;
+    lds = (size_t)(kpad + 1) * (cbw + kUpdPad) * 4;
+  } while (cbw > 16 && (cbw > kUpdMaxCols || lds > (64u << 10)));
+  if (lds <= (64u << 10)) {
     // as many tiles per wave as leave 16 waves for every CU
     const int per_wave = (int)std::clamp<int64_t>(tiles * col_blocks / 4096, 1, kUpdTiles);
     const int64_t per_block = (int64_t)kWavesPerBlock * per_wave;
@@ -1538,7 +1550,10 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
     a.ldw = upd->ldw;
     a.ldh = upd->ldh;
     for (int t = 0; t < f->k; ++t) a.H[t] = upd->H[t];
-    fused = aligned && F >= 16 && F <= 64 && upd->Fo >= 16 && upd->Fo <= 64 && upd->Fo % 16 == 0 && fast;
+    // (Widths of H that are no multiples of 16 as well, where the aggregation is wanted too; without A they are
+    // refused.  What the update adds to the aggregation, behind it and inside: N = 200k, k = 4, F = 64, Fo = 8 / 20 / 40 51 / 61
+    // / 78 -> 29 / 35 / 47 us, F = 16 25 / 39 / 59 -> 10 / 17 / 28; R-MAT 60k, k = 8, F = 64 58 / 62 / 79 -> 33 / 43 / 55.)
+    fused = aligned && F >= 16 && F <= 64 && upd->Fo <= 64 && (Y || (upd->Fo >= 16 && upd->Fo % 16 == 0)) && fast;
     if (!fused && !Y) return PIPAD_ERR_INVALID_ARG;  // the two-step form needs Y as its workspace
   }
   // Small F handed over as one concatenated operand: the coalescent kernel (snapshot groups).

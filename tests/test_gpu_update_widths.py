@@ -1,0 +1,51 @@
+"""The update for widths of H that fill neither a tile of 16 columns nor a 16-byte piece, inside the aggregation
+kernel and behind it (one block of columns, or several of equal width); nothing is written behind a row."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+from test_gpu_build_tiles import csr, rand_pairs  # noqa: E402
+from test_gpu_parity import pipad, _reset_options  # noqa: E402,F401
+
+INSIDE = [(F, Fo) for F in (16, 20, 64) for Fo in (1, 7, 8, 15, 17, 30, 33, 48, 50, 63, 64)]
+BEHIND = [(128, 65), (128, 80), (128, 81), (128, 112), (128, 113), (128, 128), (96, 128), (100, 128), (30, 129), (7, 300),
+          (300, 20), (1100, 16)]
+
+
+@pytest.mark.parametrize("bias", [True, False])
+@pytest.mark.parametrize("F,Fo", INSIDE + BEHIND)
+def test_every_width(pipad, F, Fo, bias):  # noqa: F811
+    rng = np.random.default_rng(F + Fo)
+    n, k = 1003, 2
+    pool = np.concatenate([rand_pairs(rng, n, 8 * n), np.stack([np.full(900, 17), rng.integers(0, n, 900)], 1)])
+    lists = [csr(n, pool[rng.random(len(pool)) < 0.9]) for _ in range(k)]
+    snaps = [(torch.from_numpy(rp).cuda(), torch.from_numpy(c).cuda()) for rp, c in lists]
+    for mid_max in (512, 300):  # a workgroup per long row, or its class parts
+        pipad.set_option("mid_max", mid_max)
+        frame = pipad.frame_build_overlap(snaps)
+        X = [torch.empty((n, F), device="cuda:0").uniform_(-1, 1) for _ in range(k)]
+        W = torch.empty((F, Fo), device="cuda:0").uniform_(-1, 1)
+        b = torch.empty(Fo, device="cuda:0").uniform_(-1, 1) if bias else None
+        wide = [torch.full((n, Fo + 5), 77.0, device="cuda:0") for _ in range(k)]
+        A = [torch.zeros((n, F), device="cuda:0") for _ in range(k)]
+        pipad.frame_aggregate_update(frame, X, W, b, H=[h[:, :Fo] for h in wide], A=A)
+        Y = pipad.frame_aggregate(frame, X)
+        for t in range(k):
+            assert torch.equal(A[t], Y[t])
+            exact = Y[t].double() @ W.double() + (b.double() if bias else 0.0)
+            bound = Y[t].double().abs() @ W.double().abs() + (b.double().abs() if bias else 0.0)
+            assert bool(((wide[t][:, :Fo].double() - exact).abs() <= (F + 2) * 2.0 ** -24 * bound).all())
+            assert bool((wide[t][:, Fo:] == 77.0).all())
+
+
+@pytest.mark.parametrize("Fo", [8, 20, 50])
+def test_odd_widths_without_room_for_the_aggregation_stay_refused(pipad, Fo):  # noqa: F811
+    n, F = 300, 32
+    rng = np.random.default_rng(1)
+    rp, c = csr(n, rand_pairs(rng, n, 900))
+    frame = pipad.frame_build_overlap([(torch.from_numpy(rp).cuda(), torch.from_numpy(c).cuda())])
+    X, W = [torch.zeros((n, F), device="cuda:0")], torch.zeros((F, Fo), device="cuda:0")
+    with pytest.raises(Exception):
+        pipad.frame_aggregate_update(frame, X, W, H=[torch.zeros((n, Fo), device="cuda:0")])
