@@ -1552,8 +1552,12 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
     for (int t = 0; t < f->k; ++t) a.H[t] = upd->H[t];
     // (Widths of H that are no multiples of 16 as well, where the aggregation is wanted too; without A they are
     // refused.  What the update adds to the aggregation, behind it and inside: N = 200k, k = 4, F = 64, Fo = 8 / 20 / 40 51 / 61
-    // / 78 -> 29 / 35 / 47 us, F = 16 25 / 39 / 59 -> 10 / 17 / 28; R-MAT 60k, k = 8, F = 64 58 / 62 / 79 -> 33 / 43 / 55.)
-    fused = aligned && F >= 16 && F <= 64 && upd->Fo <= 64 && (Y || (upd->Fo >= 16 && upd->Fo % 16 == 0)) && fast;
+    // / 78 -> 29 / 35 / 47 us, F = 16 25 / 39 / 59 -> 10 / 17 / 28; R-MAT 60k, k = 8, F = 64 58 / 62 / 79 -> 33 / 43 / 55.  From
+    // 400k rows of all snapshots together on where a slice has more than 32 columns: with fewer, a wave's 16 rows four at
+    // a time take up to 1.5 times as long as rows of their own and a second launch; 32 and less are 4 to 30 % faster.)
+    const bool tiles = upd->Fo >= 16 && upd->Fo % 16 == 0;
+    const bool inside = tiles || (Y && (F <= 32 || (int64_t)f->n * f->k >= 400000));
+    fused = aligned && F >= 16 && F <= 64 && upd->Fo <= 64 && inside && fast;
     if (!fused && !Y) return PIPAD_ERR_INVALID_ARG;  // the two-step form needs Y as its workspace
   }
   // Small F handed over as one concatenated operand: the coalescent kernel (snapshot groups).
