@@ -173,9 +173,10 @@ int pipad_frame_aggregate(pipad_frame_t *frame, int32_t F, const float *const *X
  *                     nsel = 0 does nothing
  *   X, Y              host arrays of k device pointers as for pipad_frame_aggregate; only the
  *                     entries of the chosen snapshots are looked at (the others may be NULL)
- * Every chosen Y[t] gets exactly the bits pipad_frame_aggregate would give it.  Other rules
- * (device, stream, scratch, determinism) as for pipad_frame_aggregate; operands of F < 32 take
- * the per-snapshot kernel here, never the coalescent one. */
+ * Every chosen Y[t] gets exactly the bits pipad_frame_aggregate would give it, but for concatenated
+ * operands of F < 32: these take the per-snapshot kernel here, never the coalescent one, which sums
+ * a row in another order.  Other rules (device, stream, scratch, determinism) as for
+ * pipad_frame_aggregate. */
 int pipad_frame_aggregate_subset(pipad_frame_t *frame, int32_t nsel, const int32_t *snapshots,
                                  int32_t F, const float *const *X, int64_t ldx, float *const *Y,
                                  int64_t ldy, void *stream);

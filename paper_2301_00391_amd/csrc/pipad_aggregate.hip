@@ -1605,9 +1605,15 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
   // 114 / 827 us, F = 100 984 / 153 / 1398 -> 802 / 136 / 1111, F = 127 1238 / 186 / 1789 -> 1063 / 170 / 1456; rows on
   // lines, F = 66 773 / 131 / 1122 -> 608 / 121 / 892, F = 80 603 / 124 / 919 -> 609 / 120 / 895, but F = 112
   // 791 / 134 / 1157 -> 848 / 145 / 1206: two.
+  // The sums of a row depend on its slices, and a snapshot gets the same bits whichever others a call
+  // takes and wherever its matrix lies: so the strides alone decide, not the pointers.  Rows are taken to
+  // start at lines where ldx is a whole number of them, unless the snapshots lie side by side in a row that k
+  // times F columns fit in and F is no whole number of lines (two slices against one, N = 200k, k = 4, F = 112 / 120
+  // 794 / 945 -> 747 / 857 us; 50k R-MAT, k = 8 307 / 352 -> 268 / 308).  Matrices with whole lines from row to row that
+  // start off a line are taken for ones that do (F = 112 882 us, in one slice 749).
   const int vec = coalescent ? cvec : vec4 ? 4 : 1;
-  bool on_lines = ldx % 32 == 0;
-  for (int t = 0; t < f->k; ++t) on_lines = on_lines && reinterpret_cast<uintptr_t>(X[t]) % 128 == 0;
+  const bool side_by_side = f->k > 1 && ldx >= (int64_t)f->k * F;
+  const bool on_lines = ldx % 32 == 0 && !(side_by_side && F % 32 != 0);
   int max_cols = !fused && F <= (on_lines ? 96 : 128) ? 128 : 64;
   if (opt.slice_cols > 0 && !fused) max_cols = (int)std::min<int64_t>(64, opt.slice_cols);
   const int cols = std::min(F, max_cols);

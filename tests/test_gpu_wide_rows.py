@@ -51,3 +51,37 @@ def test_any_start_of_a_row(pipad, F, hubs):  # noqa: F811
         pipad.frame_aggregate_subset(frame, [2, 1], xs, some)
         assert all(torch.equal(a, b) for a, b in zip(Y, Z))
         assert torch.equal(some[1], Y[1]) and torch.equal(some[2], Y[2])
+
+
+@pytest.mark.parametrize("mid_max", [200, 512])
+@pytest.mark.parametrize("F", [97, 100, 112, 127, 128])
+def test_a_subset_gets_the_bits_of_the_whole_call_wherever_rows_start(pipad, F, mid_max):  # noqa: F811
+    """Row strides that are whole lines while the snapshots' matrices start on lines, off them, or some on and
+    some off (the concatenated operand: X[t] = base + t * F): every single snapshot gets the bits of the call
+    over all of them, and the bits do not depend on where a matrix lies."""
+    rng = np.random.default_rng(F)
+    n, k = 1300, 8
+    pool = np.concatenate([rand_pairs(rng, n, 9 * n), np.stack([np.repeat([7, 900], 1250), rng.integers(0, n, 2500)], 1),
+                           np.stack([np.repeat([30, 31, 32], 150), rng.integers(0, n, 450)], 1)])
+    pipad.set_option("mid_max", mid_max)  # hub rows by class, or by a workgroup each
+    lists = [csr(n, pool[rng.random(len(pool)) < 0.9]) for _ in range(k)]
+    frame = pipad.frame_build_overlap([(torch.from_numpy(rp).cuda(), torch.from_numpy(c).cuda()) for rp, c in lists])
+    X = [synth.features(F, t, n, F) for t in range(k)]
+    beside = torch.stack([torch.from_numpy(x) for x in X], 1).cuda()  # [n, k, F]; k * F is a multiple of 32 where F is one of 4
+    placed = {"on lines": matrices(X, 160, 0), "off lines": matrices(X, 160, 5),
+              "some": [m for t in range(k) for m in matrices(X[t:t + 1], 160, 4 * (t % 3))],
+              "side by side": [beside[:, t, :] for t in range(k)]}
+    results = {}
+    for what, xs in placed.items():
+        Y = results[what] = pipad.frame_aggregate(frame, xs, [torch.empty((n, F), device="cuda:0") for _ in range(k)])
+        for t in range(k):
+            one = torch.full((n, F), float("nan"), device="cuda:0")
+            pipad.frame_aggregate_subset(frame, [t], [xs[t] if u == t else None for u in range(k)],
+                                         [one if u == t else None for u in range(k)])
+            assert torch.equal(one, Y[t]), f"{what}, snapshot {t}"
+    for what in ("off lines", "some"):
+        assert all(torch.equal(a, b) for a, b in zip(results[what], results["on lines"])), what
+    for t in range(k):
+        bounds = oracle.aggregate(n, *csr_to_coo(n, *lists[t]), X[t], threads=8)[1:3]
+        check_y(results["on lines"][t].cpu().numpy(), *bounds, f"snapshot {t}")
+        check_y(results["side by side"][t].cpu().numpy(), *bounds, f"snapshot {t}, side by side")
