@@ -317,21 +317,23 @@ __device__ __forceinline__ uint32_t mark_search(const K *keys, K key) {
   return at;
 }
 
-// N consecutive entries of a list per lane from `first` on (`all`: every lane's lie inside the list).
+// N consecutive entries of a list per lane, `offset` of them behind `start` (`all`: every lane's lie inside the
+// list).
 template <int N>
-__device__ __forceinline__ void load_run(const int32_t *col, int32_t nnz, int32_t first, bool all, int32_t (&c)[N]) {
+__device__ __forceinline__ void load_run(const int32_t *col, int32_t nnz, int32_t start, int32_t offset, bool all, int32_t (&c)[N]) {
   typedef int32_t i4 __attribute__((ext_vector_type(4), aligned(4)));
   if (all) {
+    const int32_t *const run = col + start + offset;
 #pragma unroll
     for (int q = 0; q < N / 4; ++q) {
-      const i4 v = *reinterpret_cast<const i4 *>(col + first + 4 * q);
+      const i4 v = *reinterpret_cast<const i4 *>(run + 4 * q);
       c[4 * q] = v.x; c[4 * q + 1] = v.y; c[4 * q + 2] = v.z; c[4 * q + 3] = v.w;
     }
 #pragma unroll
-    for (int j = N / 4 * 4; j < N; ++j) c[j] = col[first + j];
+    for (int j = N / 4 * 4; j < N; ++j) c[j] = run[j];
   } else {
 #pragma unroll
-    for (int j = 0; j < N; ++j) c[j] = col[min(first + j, nnz - 1)];
+    for (int j = 0; j < N; ++j) c[j] = col[place_in(start, offset + j, nnz)];
   }
 }
 
@@ -405,7 +407,7 @@ __global__ __launch_bounds__(16 * kWave) void k_mark(Snaps s, Tiles g, int32_t m
     bad |= end < start[l];
     len[l] = max(min(end, nnz) - start[l], 0);
     const int per = t == g.base ? R : E;
-    if (len[l] > 0) load_run(s.col[t], nnz, start[l] + lane * per, start[l] + (kWave - 1) * per + E <= nnz, c[l]);
+    if (len[l] > 0) load_run(s.col[t], nnz, start[l], lane * per, reaches(start[l], (kWave - 1) * per + E, nnz), c[l]);
   }
 
   if (!wide) {
@@ -527,8 +529,8 @@ __global__ __launch_bounds__(16 * kWave) void k_mark(Snaps s, Tiles g, int32_t m
         bad |= mark_twice<T>(key64, here, lane);
         continue;
       }
-      for (int32_t p = lane; p - lane < len[l]; p += kWave) {
-        const uint32_t x = p < len[l] ? mark_wide<T>(s, t, key64, rfirst, r1, start[l] + p) : S::kNone * 4u;
+      for (uint32_t p = lane, end = (uint32_t)len[l]; p - lane < end; p += kWave) {
+        const uint32_t x = p < end ? mark_wide<T>(s, t, key64, rfirst, r1, start[l] + (int32_t)p) : S::kNone * 4u;
         if (x != S::kNone * 4u)
           __hip_atomic_fetch_or(present + x / 4u, 1u << t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         if (len[l] <= S::kCap) tags[t * S::kCap + p] = x;
@@ -600,10 +602,10 @@ __global__ __launch_bounds__(16 * kWave) void k_mark(Snaps s, Tiles g, int32_t m
     } else {
       uint32_t kept = 0;
       const int32_t *col = s.col[t] + start[l];
-      for (int32_t p = lane; p - lane < len[l]; p += kWave) {
+      for (uint32_t p = lane, end = (uint32_t)len[l]; p - lane < end; p += kWave) {
         uint32_t x = S::kNone * 4u;
-        if (p < len[l]) x = len[l] <= S::kCap ? tags[t * S::kCap + p] : mark_wide<T>(s, t, key64, rfirst, r1, start[l] + p);
-        const bool is = p < len[l] && mark_at(present, x) != all_bits;
+        if (p < end) x = len[l] <= S::kCap ? tags[t * S::kCap + p] : mark_wide<T>(s, t, key64, rfirst, r1, start[l] + (int32_t)p);
+        const bool is = p < end && mark_at(present, x) != all_bits;
         const uint64_t word = __ballot(is);
         if (is)
           out[kept + __builtin_amdgcn_mbcnt_hi((uint32_t)(word >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)word, 0))] = col[p];

@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "pipad.h"
+#include "pipad_ranges.h"
 
 namespace pipad {
 
