@@ -273,13 +273,22 @@ __global__ __launch_bounds__(kBlock) void k_prepare(Snaps s, Tiles g, RowClasses
 // in a row (8 in the base), so that it looks for the first of them only and walks on from there: a look
 // or two per entry, and a search where the base has more than a few entries in between.  One bit per
 // snapshot and base entry says where that entry was found; who has all of them is common.
-// Tiles that own a longer stretch or more rows than can be gone through, and graphs with more nodes than
-// the keys have room for (4.1 M), find every entry's row by search and take 64-bit keys.
+// Graphs with more nodes than these keys have room for (4.1 M; 8.3 M for k > 16) take an instance with 64-bit
+// keys: the row's number and the column.  (With a row searched in memory per entry instead, as below, N = 4.3M, k = 4
+// took 2215 us for the whole build and N = 8M, k = 8 7386, now 1303 and 4033.)
+// A tile that owns a longer stretch, or more rows than are gone through one by one, finds every entry's row by
+// search, first among samples of the row pointers in LDS, and takes 64-bit keys of row and column.  A long stretch
+// goes a piece at a time; where its entries were found waits in the memory that its exclusive entries will
+// take.  (A binary search in memory per entry, one after the other and twice in long stretches: whole build of frames whose
+// busy nodes move, N = 200k, k = 4 500 -> 229 us, N = 1M, k = 8 5770 -> 2604; four disjoint snapshots of 200k nodes 162 -> 140.
+// Going through 4096 rows at most instead of 16384: 4M nodes with 0.45M entries, k = 4 198 -> 180, 8M 375 -> 341; with a
+// lookup per base entry that was 170 and 328.)
 //
 // Bound by instruction issue and the LDS round trips of the walk: 1M-node R-MAT frame, k = 8, 0.27 ms
 // (0.13 G vector instructions, 0.22 of it), against 0.44 for a look-up of every base entry in every
 // snapshot's window, four waves per tile and a look-up with a row's bounds from memory (0.235 G).
-// N = 200k Chung-Lu, k = 8 87 -> 55 us; R-MAT 100k, k = 5 31 -> 21; N = 20k, k = 4 12.2 -> 8.8; N = 2k 11 -> 7.
+// N = 200k Chung-Lu, k = 8 87 -> 55 us; R-MAT 100k, k = 5 31 -> 21; N = 20k, k = 4 12.2 -> 8.8; N = 2k 11 -> 7; with 64-bit
+// keys N = 4.3M, k = 4 399 -> 292.
 // A number of entries per lane that follows the stretch (8 .. 12, in branches) was slower by 40 %.
 template <int T>
 struct Mark {
@@ -290,12 +299,14 @@ struct Mark {
   // neighbouring addresses
   static constexpr int kPlane = 96;
   static constexpr int kNone = kWave;              // behind the last entry: plane 0, place 64
-  // the next entry's place in an array of 32-bit words, in bytes: the next plane, or the first one's next place
+  // the next entry's place in an array of keys, in bytes: the next plane, or the first one's next place
+  template <class K>
   static __device__ __forceinline__ uint32_t next(uint32_t at) {
-    return min(at + kPlane * 4u, at + kPlane * 4u - (kRun * kPlane * 4u - 4u));
+    constexpr uint32_t B = sizeof(K);
+    return min(at + kPlane * B, at + kPlane * B - (kRun * kPlane * B - B));
   }
 };
-constexpr int32_t kMarkRows = 4096;                // most rows of a tile that are gone through one by one
+constexpr int32_t kMarkRows = 16384;               // most rows of a tile that are gone through one by one
 
 // Places of base entries are in bytes of the array they are looked up in.
 template <class K>
@@ -337,13 +348,81 @@ __device__ __forceinline__ void load_run(const int32_t *col, int32_t nnz, int32_
   }
 }
 
-// Where the base has entry e of snapshot t, which lies in rows [r0, r1].
-template <int T>
-__device__ __forceinline__ uint32_t mark_wide(const Snaps &s, int t, const uint64_t *keys, int32_t r0, int32_t r1, int32_t e) {
-  const uint32_t row = (uint32_t)row_of_entry(s.rowptr[t], r0, r1, e);
-  const uint64_t key = (uint64_t)row << 32 | (uint32_t)s.col[t][e];
-  const uint32_t at = mark_search<T>(keys, key);
-  return mark_at(keys, at) == key ? at / 2 : Mark<T>::kNone * 4;  // (in the array of 32-bit words)
+// Where the base has the ascending keys of a lane, as places in the array of 32-bit words, noted in `present`.
+template <int T, int N, class K>
+__device__ __forceinline__ void mark_walk(const K *keys, const K (&key)[N], uint32_t *present, uint32_t bit, uint32_t (&at)[N]) {
+  using S = Mark<T>;
+  uint32_t x = mark_search<T>(keys, key[0]);
+  K v = mark_at(keys, x);
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    const K k0 = key[j];
+    int looks = 6;
+    while (__builtin_amdgcn_ballot_w64(v < k0) != 0) {
+      if (v < k0) {
+        x = S::template next<K>(x);
+        v = mark_at(keys, x);
+      }
+      if (--looks == 0) {
+        x = mark_search<T>(keys, k0);
+        v = mark_at(keys, x);
+      }
+    }
+    at[j] = S::kNone * 4u;
+    if (v == k0) {
+      at[j] = x / (sizeof(K) / 4u);
+      __hip_atomic_fetch_or(present + at[j] / 4u, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+  }
+}
+
+// What the keys of a row start with (q: number of the tile's base rows up to it), and a key.
+template <class K>
+__device__ __forceinline__ uint32_t mark_row(uint32_t q, bool in_base, uint32_t mult) {
+  return sizeof(K) == 4 ? __umul24(q, mult) + (in_base ? 0u : mult / 2u) : 2u * q + (in_base ? 0u : 1u);
+}
+template <class K>
+__device__ __forceinline__ K mark_key(uint32_t row, int32_t col) {
+  return sizeof(K) == 4 ? (K)(row + (uint32_t)col) : (K)((uint64_t)row << 32 | (uint32_t)col);
+}
+
+// Every (1 << shift)-th row pointer of rows [lo, hi], so many that CAP words of LDS hold them; returns the shift.
+template <int CAP>
+__device__ __forceinline__ int sample_rows(const int32_t *rp, int32_t lo, int32_t hi, uint32_t *samples, int lane) {
+  int shift = 0;
+  while ((hi - lo) >> shift >= CAP) ++shift;
+  const int32_t last = (hi - lo) >> shift;
+  int32_t v[CAP / kWave];
+#pragma unroll
+  for (int q = 0; q < CAP / kWave; ++q) v[q] = rp[lo + (min(q * kWave + lane, last) << shift)];
+#pragma unroll
+  for (int q = 0; q < CAP / kWave; ++q) samples[q * kWave + lane] = (uint32_t)v[q];
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  return shift;
+}
+
+// Rows of N entries from start + offset on (behind start + last: that one's), which lie in rows [lo, hi]: first among
+// the samples, then between two of them, side by side, so that a step waits for memory once.
+template <int N>
+__device__ __forceinline__ void rows_of_run(const int32_t *rp, int32_t lo, int32_t hi, const uint32_t *samples, int shift,
+                                            int32_t start, int32_t offset, int32_t last, int32_t (&row)[N]) {
+  const int32_t last_sample = (hi - lo) >> shift;
+#pragma unroll
+  for (int j = 0; j < N; ++j) row[j] = 0;
+  for (int32_t step = last_sample > 0 ? 1 << (31 - __builtin_clz((uint32_t)last_sample)) : 0; step >= 1; step >>= 1)
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      const int32_t by = min(step, last_sample - row[j]);
+      if ((int32_t)samples[row[j] + by] <= start + min(offset + j, last)) row[j] += by;
+    }
+#pragma unroll
+  for (int j = 0; j < N; ++j) row[j] = lo + (row[j] << shift);
+  for (int32_t step = 1 << shift >> 1; step >= 1; step >>= 1)
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      const int32_t by = min(step, hi - row[j]);
+      if (rp[row[j] + by] <= start + min(offset + j, last)) row[j] += by;
+    }
 }
 
 // The base has a column twice in a row (the other snapshots' entries only ever find one of the two).
@@ -357,16 +436,16 @@ __device__ __forceinline__ bool mark_twice(const K *keys, int32_t here, int lane
   return twice;
 }
 
-template <int T, int L>  // L: snapshots per wave
-__global__ __launch_bounds__(16 * kWave) void k_mark(Snaps s, Tiles g, int32_t mid_max) {
+template <int T, int L, class K>  // L: snapshots per wave; K: 32- or 64-bit keys
+__global__ __launch_bounds__(16 * kWave) __attribute__((amdgpu_waves_per_eu(sizeof(K) == 4 ? 8 : 6))) void k_mark(Snaps s, Tiles g, int32_t mid_max) {
   using S = Mark<T>;
   constexpr int R = S::kRun, E = S::kMost, PLANE = S::kPlane;
-  __shared__ uint64_t key_words[R * PLANE];  // 32- or 64-bit keys
+  __shared__ uint64_t key_words[R * PLANE];  // keys of either width
   __shared__ uint32_t present[R * PLANE];    // bit t: snapshot t has the entry (0 behind the last entry)
   __shared__ uint32_t hub_row[T + 2];        // by number of the base row
   __shared__ uint32_t shared_of[PIPAD_MAX_K];
   extern __shared__ uint32_t tags[];         // [k][kCap]
-  uint32_t *const key32 = reinterpret_cast<uint32_t *>(key_words);
+  K *const keys = reinterpret_cast<K *>(key_words);
   uint64_t *const key64 = key_words;
   const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int nwaves = blockDim.x / kWave;
@@ -386,14 +465,14 @@ __global__ __launch_bounds__(16 * kWave) void k_mark(Snaps s, Tiles g, int32_t m
   for (int x = threadIdx.x; x < T + 2; x += blockDim.x) hub_row[x] = 0;
   __syncthreads();
 
-  // keys of row number q (1, 2, ..) start at q * mult; those of rows without base entries behind it lie
+  // 32-bit keys of row number q (1, 2, ..) start at q * mult; those of rows without base entries behind it lie
   // between its keys and those of row number q + 1 (in any order: nothing of the base lies there)
   const uint32_t mult = 2u * (uint32_t)g.n + 2u;
-  const bool wide = (uint64_t)g.n >= 0x7fffffffu / (T + 2) || r1 - rfirst >= kMarkRows || __any(my_b1 - my_b0 > S::kCap);
+  const bool wide = r1 - rfirst >= kMarkRows || __any(my_b1 - my_b0 > S::kCap);
 
   int32_t start[L], len[L];
   int32_t c[L][E];     // columns of this lane's entries
-  uint32_t key[L][E];  // ... their keys (of the base: row numbers)
+  K key[L][E];         // ... their keys (of the base: row numbers)
   uint32_t at[L][E];   // ... and where the base has them
   bool bad = false;
 #pragma unroll
@@ -447,32 +526,33 @@ __global__ __launch_bounds__(16 * kWave) void k_mark(Snaps s, Tiles g, int32_t m
           const uint32_t p = (uint32_t)max(row.a - start[l], 0);
           if (live & ((int32_t)p < min(row.b - start[l], len[l]))) {
             if (base) tag[p % R * kWave + p / R] = q;
-            else tag[p % E * kWave + p / E] = __umul24(q, mult) + (in_base ? 0u : mult / 2u);
+            else tag[p % E * kWave + p / E] = mark_row<K>(q, in_base, mult);
           }
           if (in_base & (row.b - row.a > mid_max)) hub_row[q] = 1;
         }
       }
       // what lies behind the list comes behind all of the base
-      if (!base && lane == 0 && len[l] < S::kCap) tag[len[l] % E * kWave + len[l] / E] = T * mult + mult / 2u;
+      if (!base && lane == 0 && len[l] < S::kCap) tag[len[l] % E * kWave + len[l] / E] = mark_row<K>(T, false, mult);
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      uint32_t most = 0;
+      uint32_t most = 0, row[E];
 #pragma unroll
       for (int j = 0; j < E; ++j) {
         most = max(most, tag[j * kWave + lane]);
-        key[l][j] = most;
+        row[j] = most;
       }
       const uint32_t front = __shfl_up(wave_max(most), 1, kWave);
       most = lane > 0 ? front : 0u;
       if (base) {
 #pragma unroll
         for (int j = 0; j < R; ++j) {
-          key[l][j] = max(key[l][j], most);
-          key32[j * PLANE + lane] = lane * R + j < here ? __umul24(key[l][j], mult) + (uint32_t)c[l][j] : ~0u;
+          row[j] = max(row[j], most);
+          key[l][j] = row[j];
+          keys[j * PLANE + lane] = lane * R + j < here ? mark_key<K>(mark_row<K>(row[j], true, mult), c[l][j]) : ~(K)0;
         }
-        if (lane == 0) key32[S::kNone] = ~0u;
+        if (lane == 0) keys[S::kNone] = ~(K)0;
       } else {
 #pragma unroll
-        for (int j = 0; j < E; ++j) key[l][j] = max(key[l][j], most) + (uint32_t)c[l][j];
+        for (int j = 0; j < E; ++j) key[l][j] = mark_key<K>(max(row[j], most), c[l][j]);
       }
     }
     __syncthreads();
@@ -480,60 +560,80 @@ __global__ __launch_bounds__(16 * kWave) void k_mark(Snaps s, Tiles g, int32_t m
     for (int l = 0; l < L; ++l) {
       const int t = wave + l * nwaves;
       if (t >= g.k) break;
-      if (t == g.base) bad |= mark_twice<T>(key32, here, lane);
+      if (t == g.base) bad |= mark_twice<T>(keys, here, lane);
       if (t == g.base || len[l] == 0) continue;
-      uint32_t x = mark_search<T>(key32, key[l][0]), v = mark_at(key32, x);
-#pragma unroll
-      for (int j = 0; j < E; ++j) {
-        const uint32_t k0 = key[l][j];
-        int looks = 6;
-        while (__builtin_amdgcn_ballot_w64(v < k0) != 0) {
-          if (v < k0) {
-            x = S::next(x);
-            v = mark_at(key32, x);
-          }
-          if (--looks == 0) {
-            x = mark_search<T>(key32, k0);
-            v = mark_at(key32, x);
-          }
-        }
-        at[l][j] = S::kNone * 4u;
-        if (v == k0) {
-          at[l][j] = x;
-          __hip_atomic_fetch_or(present + x / 4u, 1u << t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        }
-      }
+      mark_walk<T>(keys, key[l], present, 1u << t, at[l]);
     }
   } else {
 #pragma unroll
     for (int l = 0; l < L; ++l) {
       const int t = wave + l * nwaves;
       if (t != g.base) continue;
+      int32_t row[R];
+      const int shift = sample_rows<S::kCap>(rp0, r0, r1, tags + t * S::kCap, lane);
+      rows_of_run(rp0, r0, r1, tags + t * S::kCap, shift, e0, lane * R, here - 1, row);
 #pragma unroll
       for (int j = 0; j < R; ++j) {
         const int32_t x = lane * R + j;
-        const int32_t row = row_of_entry(rp0, r0, r1, e0 + min(x, here - 1));
-        key64[j * PLANE + lane] = x < here ? (uint64_t)(uint32_t)row << 32 | (uint32_t)c[l][j] : ~0ull;
-        uint32_t hub = 0;
-        for (int u = 0; u < g.k; ++u) hub |= s.rowptr[u][row + 1] - s.rowptr[u][row] > mid_max;
-        hub_row[x] = hub;
+        key64[j * PLANE + lane] = x < here ? mark_key<uint64_t>((uint32_t)row[j], c[l][j]) : ~0ull;
         key[l][j] = (uint32_t)x;
       }
+      if (lane == 0) key64[S::kNone] = ~0ull;
+    }
+    int shift[L];
+    constexpr int G = 5;  // (entries at a time: with all ten the kernel needs too many registers for eight waves per SIMD)
+    static_assert(E % G == 0, "");
+    auto find_rows = [&](int l, int t, int32_t first, int32_t left) __attribute__((always_inline)) {
+#pragma unroll
+      for (int h = 0; h < E; h += G) {
+        int32_t row[G];
+        rows_of_run(s.rowptr[t], rfirst, r1, tags + t * S::kCap, shift[l], first, lane * E + h, left - 1, row);
+#pragma unroll
+        for (int j = 0; j < G; ++j) key[l][h + j] = (uint32_t)row[j];
+      }
+    };
+#pragma unroll
+    for (int l = 0; l < L; ++l) {
+      const int t = wave + l * nwaves;
+      if (t >= g.k) break;
+      if (t == g.base || len[l] == 0) continue;
+      shift[l] = sample_rows<S::kCap>(s.rowptr[t], rfirst, r1, tags + t * S::kCap, lane);
+      find_rows(l, t, start[l], min(len[l], S::kCap));
     }
     __syncthreads();
 #pragma unroll
     for (int l = 0; l < L; ++l) {
       const int t = wave + l * nwaves;
       if (t >= g.k) break;
-      if (t == g.base) {
-        bad |= mark_twice<T>(key64, here, lane);
-        continue;
+#pragma unroll
+      for (int j = 0; j < R; ++j) {  // (the base's entries, by their places)
+        const int32_t x = lane * R + j, row = x < here ? (int32_t)(key64[j * PLANE + lane] >> 32) : r1;
+        if (s.rowptr[t][row + 1] - s.rowptr[t][row] > mid_max) hub_row[x] = 1;
       }
-      for (uint32_t p = lane, end = (uint32_t)len[l]; p - lane < end; p += kWave) {
-        const uint32_t x = p < end ? mark_wide<T>(s, t, key64, rfirst, r1, start[l] + (int32_t)p) : S::kNone * 4u;
-        if (x != S::kNone * 4u)
-          __hip_atomic_fetch_or(present + x / 4u, 1u << t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        if (len[l] <= S::kCap) tags[t * S::kCap + p] = x;
+      if (t == g.base) bad |= mark_twice<T>(key64, here, lane);
+      if (t == g.base || len[l] == 0) continue;
+      // a long stretch a piece at a time; where its entries were found is kept in what `excl` has for them
+      for (uint32_t done = 0; done < (uint32_t)len[l]; done += S::kCap) {
+        const int32_t first = start[l] + (int32_t)done, left = min(len[l] - (int32_t)done, S::kCap);
+        if (done > 0) {
+          load_run(s.col[t], start[l] + len[l], first, lane * E, left == S::kCap, c[l]);
+          find_rows(l, t, first, left);
+        }
+#pragma unroll
+        for (int h = 0; h < E; h += G) {
+          uint64_t wide_key[G];
+          uint32_t found[G];
+#pragma unroll
+          for (int j = 0; j < G; ++j)  // (behind the end: behind all of the base)
+            wide_key[j] = lane * E + h + j < left ? mark_key<uint64_t>((uint32_t)key[l][h + j], c[l][h + j]) : (uint64_t)~0u << 32;
+          mark_walk<T>(key64, wide_key, present, 1u << t, found);
+#pragma unroll
+          for (int j = 0; j < G; ++j) at[l][h + j] = found[j];
+        }
+        if (len[l] > S::kCap)
+#pragma unroll
+          for (int j = 0; j < E; ++j)
+            if (lane * E + j < left) g.excl[t][first + (lane * E + j)] = (int32_t)at[l][j];
       }
     }
   }
@@ -585,31 +685,28 @@ __global__ __launch_bounds__(16 * kWave) void k_mark(Snaps s, Tiles g, int32_t m
       for (int j = 0; j < R; ++j)
         if ((j < mine) & !(common >> j & 1u)) stage[to++] = (uint32_t)c[l][j];
       write_out(out, here - __builtin_amdgcn_readlane((int)incl, kWave - 1));
-    } else if (!wide) {
-      const int32_t mine = min(max(len[l] - lane * E, 0), E);
-      uint32_t excl = 0;
-      if (len[l] > 0)
-#pragma unroll
-        for (int j = 0; j < E; ++j) excl |= mark_at(present, at[l][j]) != all_bits ? 1u << j : 0u;
-      excl &= (1u << mine) - 1u;
-      const uint32_t cnt = (uint32_t)__popc(excl), incl = wave_sum(cnt);
-      uint32_t to = incl - cnt;
-#pragma unroll
-      for (int j = 0; j < E; ++j)
-        if (excl >> j & 1u) stage[to++] = (uint32_t)c[l][j];
-      write_out(out, __builtin_amdgcn_readlane((int)incl, kWave - 1));
-      if (lane == kWave - 1) shared_of[t] = (uint32_t)len[l] - incl;
     } else {
       uint32_t kept = 0;
-      const int32_t *col = s.col[t] + start[l];
-      for (uint32_t p = lane, end = (uint32_t)len[l]; p - lane < end; p += kWave) {
-        uint32_t x = S::kNone * 4u;
-        if (p < end) x = len[l] <= S::kCap ? tags[t * S::kCap + p] : mark_wide<T>(s, t, key64, rfirst, r1, start[l] + (int32_t)p);
-        const bool is = p < end && mark_at(present, x) != all_bits;
-        const uint64_t word = __ballot(is);
-        if (is)
-          out[kept + __builtin_amdgcn_mbcnt_hi((uint32_t)(word >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)word, 0))] = col[p];
-        kept += (uint32_t)__popcll(word);
+      for (uint32_t done = 0; done < (uint32_t)len[l]; done += S::kCap) {
+        const int32_t first = start[l] + (int32_t)done, left = min(len[l] - (int32_t)done, S::kCap);
+        if (len[l] > S::kCap) {  // (what has been written out lies in front of this piece)
+          load_run(s.col[t], start[l] + len[l], first, lane * E, left == S::kCap, c[l]);
+#pragma unroll
+          for (int j = 0; j < E; ++j) at[l][j] = lane * E + j < left ? (uint32_t)g.excl[t][first + (lane * E + j)] : S::kNone * 4u;
+        }
+        const int32_t mine = min(max(left - lane * E, 0), E);
+        uint32_t excl = 0;
+#pragma unroll
+        for (int j = 0; j < E; ++j) excl |= mark_at(present, at[l][j]) != all_bits ? 1u << j : 0u;
+        excl &= (1u << mine) - 1u;
+        const uint32_t cnt = (uint32_t)__popc(excl), incl = wave_sum(cnt);
+        uint32_t to = incl - cnt;
+#pragma unroll
+        for (int j = 0; j < E; ++j)
+          if (excl >> j & 1u) stage[to++] = (uint32_t)c[l][j];
+        const uint32_t count = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
+        write_out(out + kept, (int)count);
+        kept += count;
       }
       if (lane == 0) shared_of[t] = (uint32_t)len[l] - kept;
     }
@@ -1780,7 +1877,10 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
                      bound_blocks, f->dinv, f->dinv_nk);
   if (g.ntiles > 0) {
     const int cap = k <= 16 ? Mark<512>::kCap : Mark<256>::kCap, waves = k <= 16 ? k : (k + 1) / 2;
-    auto mark = k <= 16 ? k_mark<512, 1> : k_mark<256, 2>;
+    // (514 rows and the like times 2n + 2 columns have to fit a 32-bit key)
+    const bool large = n >= 0x7fffffff / ((k <= 16 ? 512 : 256) + 2);
+    auto mark = k <= 16 ? (large ? k_mark<512, 1, uint64_t> : k_mark<512, 1, uint32_t>)
+                        : (large ? k_mark<256, 2, uint64_t> : k_mark<256, 2, uint32_t>);
     hipLaunchKernelGGL(mark, dim3((unsigned)g.ntiles), dim3((unsigned)(waves * kWave)), (size_t)k * cap * sizeof(uint32_t),
                        st, s, g, f->plain_units ? INT32_MAX : f->mid_max);  // (the classes' copies hold the hub rows' scales)
   }

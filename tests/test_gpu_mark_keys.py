@@ -1,6 +1,6 @@
 """Overlap extraction at the edges of what its 32-bit keys hold and of what a lane walks: the number of
-nodes, stretches of 640 entries (320 for more than 16 snapshots), tiles with thousands of rows, and gaps in
-one list that the other walks over; against the oracle."""
+nodes, stretches of 640 entries (320 for more than 16 snapshots) and of several times that, tiles with
+thousands of rows, and gaps in one list that the other walks over; against the oracle."""
 import numpy as np
 import pytest
 
@@ -11,11 +11,9 @@ from test_gpu_build_tiles import csr, rand_pairs  # noqa: E402
 from test_gpu_parity import pipad, run_case  # noqa: E402,F401
 
 
-@pytest.mark.parametrize("k", [2, 18])
-@pytest.mark.parametrize("n", [4_177_984, 4_178_100, 4_200_000, 8_400_000, 16_800_000])
+@pytest.mark.parametrize("k,n", [(2, 4_177_982), (2, 4_177_983), (2, 4_177_984), (2, 4_178_100), (2, 4_200_000), (2, 8_400_000),
+                                 (2, 16_800_000), (18, 4_200_000), (18, 8_323_579), (18, 8_323_580), (18, 8_400_000)])
 def test_numbers_of_nodes_around_what_a_key_holds(pipad, n, k):  # noqa: F811
-    if k > 2 and n > 8_400_000:
-        pytest.skip("the oracle's time")
     rng = np.random.default_rng(n)
     # full rows at both ends, so that the largest keys (last row of a tile, last column) occur
     ends = np.stack([np.repeat([0, 1, n - 2, n - 1], 700), rng.integers(0, n, 2800)], 1)
@@ -54,3 +52,31 @@ def test_gaps_that_are_walked_over(pipad, gap):  # noqa: F811
     keep = (np.arange(len(pairs)) // gap) % 2 == 0
     lists = [csr(n, pairs), csr(n, pairs[keep]), csr(n, pairs[~keep]), csr(n, pairs[(np.arange(len(pairs)) // 3) % 2 == 0])]
     run_case(pipad, n, lists, 4, seed=gap)
+
+
+@pytest.mark.parametrize("k,mid_max", [(3, 512), (3, 100), (18, 100)])
+@pytest.mark.parametrize("rows", [16_381, 16_382, 16_383, 16_384, 70_001])
+def test_most_rows_of_a_tile(pipad, rows, k, mid_max):  # noqa: F811
+    """The base's first tile begins in row 0 and ends in row `rows`; there are `rows` + 1 of them."""
+    rng = np.random.default_rng(rows)
+    pipad.set_option("mid_max", mid_max)  # 100: the last row and the first are hub rows
+    n = rows + 5
+    ends = np.array([[0, c] for c in range(1, 110)] + [[rows, c] for c in range(1, 700)])
+    inner = np.stack([rng.integers(1, rows, 90), rng.integers(0, n, 90)], 1)
+    lists = [csr(n, np.concatenate([ends, inner[:30]]))]
+    lists += [csr(n, np.concatenate([ends[rng.random(len(ends)) < 0.9], inner[20 + t:]])) for t in range(k - 1)]
+    run_case(pipad, n, lists, 4, seed=rows)
+
+
+@pytest.mark.parametrize("k,mid_max", [(2, 512), (2, 100), (17, 100)])
+@pytest.mark.parametrize("extra", [313, 639, 640, 641, 1280, 1281, 7001])
+def test_stretches_of_several_pieces(pipad, extra, k, mid_max):  # noqa: F811
+    """Where the base has row 7 alone, the other snapshots have `extra` entries in front of it, as many behind, and
+    some of row 7 in between, so that common and exclusive entries lie in the first, in middle and in last pieces."""
+    pipad.set_option("mid_max", mid_max)
+    n, T = 9000, 512 if k <= 16 else 256
+    row7 = [[7, c] for c in range(100, 100 + 2 * T, 2)]
+    base = csr(n, row7 + [[8000, c] for c in range(20, 8000)] + [[8001, c] for c in range(20, 8000)])
+    others = [csr(n, [[6, c] for c in range(20, 20 + extra)] + row7[t:T:3] + [[7, c] for c in range(101, 201 + t, 2)]
+                  + [[8, c] for c in range(30, 30 + extra)] + [[8000, c] for c in range(20 + t, 500, 2)]) for t in range(k - 1)]
+    run_case(pipad, n, [base] + others, 4, seed=extra)
