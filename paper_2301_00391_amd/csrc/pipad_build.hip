@@ -376,6 +376,37 @@ __device__ __forceinline__ void mark_walk(const K *keys, const K (&key)[N], uint
   }
 }
 
+// The same by a search for every key, G of them side by side: where a stretch is shorter than 7/8 of the tile, some of the
+// wave's lanes are more than a few entries of the base further at every key.  Whole build, N = 1M Chung-Lu, k = 4, one snapshot
+// of 10M edges and three with 75 / 50 / 25 / 3 % of them 536 / 571 / 585 / 550 -> 528 / 512 / 490 / 460 us; stretches as
+// long as the tile take longer (R-MAT 1M, k = 8 946 -> 980).
+template <int T, int N, class K>
+__device__ __forceinline__ void mark_find(const K *keys, const K (&key)[N], uint32_t *present, uint32_t bit, uint32_t (&at)[N]) {
+  using S = Mark<T>;
+  constexpr int G = sizeof(K) == 4 ? N : 5;  // (ten 64-bit ones take too many registers)
+  static_assert(N % G == 0, "");
+#pragma unroll
+  for (int h = 0; h < N; h += G) {
+#pragma unroll
+    for (int j = h; j < h + G; ++j) at[j] = 0;
+#pragma unroll
+    for (uint32_t s = kWave / 2; s >= 1; s >>= 1)
+#pragma unroll
+      for (int j = h; j < h + G; ++j) at[j] += mark_at(keys + s, at[j]) <= key[j] ? s * (uint32_t)sizeof(K) : 0u;
+#pragma unroll
+    for (uint32_t s = S::kRun / 2; s >= 1; s >>= 1)
+#pragma unroll
+      for (int j = h; j < h + G; ++j)
+        at[j] += mark_at(keys + (s - 1) * S::kPlane, at[j]) < key[j] ? s * S::kPlane * (uint32_t)sizeof(K) : 0u;
+#pragma unroll
+    for (int j = h; j < h + G; ++j) {
+      const bool found = mark_at(keys, at[j]) == key[j];
+      at[j] = found ? at[j] / (sizeof(K) / 4u) : S::kNone * 4u;
+      if (found) __hip_atomic_fetch_or(present + at[j] / 4u, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+  }
+}
+
 // What the keys of a row start with (q: number of the tile's base rows up to it), and a key.
 template <class K>
 __device__ __forceinline__ uint32_t mark_row(uint32_t q, bool in_base, uint32_t mult) {
@@ -436,6 +467,8 @@ __device__ __forceinline__ bool mark_twice(const K *keys, int32_t here, int lane
   return twice;
 }
 
+// (Held to eight waves per SIMD with 32-bit keys.  Without spilled registers: a variant that kept 48 bytes of them in private
+// memory took 1337 us for the build of the 1M-node R-MAT frame, not 948.)
 template <int T, int L, class K>  // L: snapshots per wave; K: 32- or 64-bit keys
 __global__ __launch_bounds__(16 * kWave) __attribute__((amdgpu_waves_per_eu(sizeof(K) == 4 ? 8 : 6))) void k_mark(Snaps s, Tiles g, int32_t mid_max) {
   using S = Mark<T>;
@@ -562,7 +595,8 @@ __global__ __launch_bounds__(16 * kWave) __attribute__((amdgpu_waves_per_eu(size
       if (t >= g.k) break;
       if (t == g.base) bad |= mark_twice<T>(keys, here, lane);
       if (t == g.base || len[l] == 0) continue;
-      mark_walk<T>(keys, key[l], present, 1u << t, at[l]);
+      if (8 * len[l] > 7 * here) mark_walk<T>(keys, key[l], present, 1u << t, at[l]);
+      else mark_find<T>(keys, key[l], present, 1u << t, at[l]);
     }
   } else {
 #pragma unroll

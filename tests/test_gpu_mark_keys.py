@@ -80,3 +80,22 @@ def test_stretches_of_several_pieces(pipad, extra, k, mid_max):  # noqa: F811
     others = [csr(n, [[6, c] for c in range(20, 20 + extra)] + row7[t:T:3] + [[7, c] for c in range(101, 201 + t, 2)]
                   + [[8, c] for c in range(30, 30 + extra)] + [[8000, c] for c in range(20 + t, 500, 2)]) for t in range(k - 1)]
     run_case(pipad, n, [base] + others, 4, seed=extra)
+
+
+@pytest.mark.parametrize("k", [3, 17])
+@pytest.mark.parametrize("eighths,more", [(8, 0), (7, -1), (7, 0), (7, 1), (4, 0), (1, 0), (0, 3), (0, 0)])
+def test_stretches_shorter_than_the_tile(pipad, eighths, more, k):  # noqa: F811
+    """The other snapshots have that much of every tile of the base, common entries and their own."""
+    n, T = 4000, 512 if k <= 16 else 256
+    rng = np.random.default_rng(8 * eighths + more)
+    count = T * eighths // 8 + more
+    cols = 20 + 2 * np.arange(3 * T)
+    lists = [csr(n, [[7, c] for c in cols[:T]] + [[3000, c] for c in cols[:2 * T]])]
+    for t in range(k - 1):
+        pairs = []
+        for row, first in ((7, 0), (3000, 0), (3000, T)):
+            mine = np.sort(rng.permutation(T)[:count])
+            # a tenth of them lies between two entries of the base (behind its first, so that no tile loses them)
+            pairs += [[row, cols[first + x] + (x > 0 and x % 10 == t % 10)] for x in mine]
+        lists.append(csr(n, pairs))
+    run_case(pipad, n, lists, 4, seed=count)
