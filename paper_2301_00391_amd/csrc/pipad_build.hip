@@ -1276,7 +1276,9 @@ __device__ __forceinline__ void fill_part(const SplitArgs &g, int32_t u, int p, 
     b = ds + q1;
     out = g.item_d0[u] + before + q0;
   }
-  const int32_t *col = g.col[p];
+  // (from the unit's first entry on: places behind a list's end may pass 2^31, offsets in a unit of 2^30 entries do not)
+  const int32_t *col = g.col[p] + a;
+  b -= a;
   int32_t cv[kFillRounds];
   int32_t cnt[NC];  // this wave's entries per class (wave-uniform)
   auto load_and_count = [&](int32_t at) __attribute__((always_inline)) {
@@ -1317,15 +1319,15 @@ __device__ __forceinline__ void fill_part(const SplitArgs &g, int32_t u, int p, 
   };
 #pragma unroll
   for (int x = 0; x < NC; ++x) cnt[x] = 0;
-  for (int32_t at = a; at < b; at += piece) load_and_count(at);
+  for (int32_t at = 0; at < b; at += piece) load_and_count(at);
   int32_t team, front;
   exchange(&team, &front);
   // the copy's class boundaries: sptr[(p * (NC + 1) + x) * n_units + u]
   int32_t run = out + (int32_t)wave_sum((uint32_t)team) - team;  // lane x: where class x goes on
   if (wave == 0 && lane <= NC) g.sptr[((int64_t)p * (NC + 1) + lane) * g.n_units + u] = run;
 
-  for (int32_t at = a; at < b; at += piece) {
-    if (b - a > piece) {
+  for (int32_t at = 0; at < b; at += piece) {
+    if (b > piece) {
 #pragma unroll
       for (int x = 0; x < NC; ++x) cnt[x] = 0;
       load_and_count(at);
