@@ -1204,6 +1204,7 @@ struct SplitArgs {
   float *swc[PIPAD_MAX_K];
   float *swd;
   int32_t block_off[PIPAD_MAX_K + 2];      // first workgroup of every part, in their natural order
+  int32_t run_off[kClasses + 1];           // first workgroup of every XCD's run of the exclusive parts
   uint64_t whole;                          // bit p: part p takes a workgroup per unit, not a wave
 };
 
@@ -1248,7 +1249,7 @@ __device__ __forceinline__ void store_scales(const SplitArgs &g, const int32_t (
 template <int NC, int W>
 __device__ __forceinline__ void fill_part(const SplitArgs &g, int32_t u, int p, int lane, int wave, int32_t *stage,
                                           int32_t (*s_cnt)[NC], int32_t *s_off) {
-  constexpr int32_t share = kFillRounds * kWave, piece = W * share;  // of a wave, of the team
+  constexpr int32_t piece = W * kFillRounds * kWave;  // of the team
   auto sync = [&]() __attribute__((always_inline)) {
     if (W > 1) __syncthreads();
     else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -1279,19 +1280,22 @@ __device__ __forceinline__ void fill_part(const SplitArgs &g, int32_t u, int p, 
   // (from the unit's first entry on: places behind a list's end may pass 2^31, offsets in a unit of 2^30 entries do not)
   const int32_t *col = g.col[p] + a;
   b -= a;
+  // of a wave: every wave has a part of a short list (with 512 entries each, one wave after the other, N = 100k R-MAT, k = 5
+  // 13.9 us, now 13.0; R-MAT 1M, k = 8 243, now 240)
+  const int32_t share = W == 1 ? piece : min((b + W * kWave - 1) / (W * kWave), kFillRounds) * kWave;
   int32_t cv[kFillRounds];
   int32_t cnt[NC];  // this wave's entries per class (wave-uniform)
   auto load_and_count = [&](int32_t at) __attribute__((always_inline)) {
-    const int32_t first = at + wave * share;
+    const int32_t first = at + wave * share, end = min(first + share, b);
 #pragma unroll
     for (int r = 0; r < kFillRounds; ++r) {
-      if (first + r * kWave >= b) break;
+      if (first + r * kWave >= end) break;
       const int32_t v = col[min(first + r * kWave + lane, b - 1)];
       cv[r] = first + r * kWave + lane < b ? v : -1;
     }
 #pragma unroll
     for (int r = 0; r < kFillRounds; ++r) {
-      if (first + r * kWave >= b) break;
+      if (first + r * kWave >= end) break;
       const uint32_t cl = cv[r] >= 0 ? column_class(cv[r], g.sub_log2) : (uint32_t)NC;
 #pragma unroll
       for (int x = 0; x < NC; ++x) cnt[x] += __popcll(__ballot(cl == (uint32_t)x));
@@ -1339,10 +1343,10 @@ __device__ __forceinline__ void fill_part(const SplitArgs &g, int32_t u, int p, 
     int32_t local[NC];
 #pragma unroll
     for (int x = 0; x < NC; ++x) local[x] = __builtin_amdgcn_readlane(pos + front, x);
-    const int32_t first = at + wave * share;
+    const int32_t first = at + wave * share, end = min(first + share, b);
 #pragma unroll
     for (int r = 0; r < kFillRounds; ++r) {
-      if (first + r * kWave >= b) break;
+      if (first + r * kWave >= end) break;
       const uint32_t cl = cv[r] >= 0 ? column_class(cv[r], g.sub_log2) : (uint32_t)NC;
       int32_t where = 0;
 #pragma unroll
@@ -1397,7 +1401,9 @@ __device__ __forceinline__ void fill_part(const SplitArgs &g, int32_t u, int p, 
 // 1M-node R-MAT frame 0.25 ms either way: most of what is fetched are lines of D^-1/2 for a few scales
 // each, and 0.36 GB are written.
 // An XCD takes a run of the exclusive parts' units, so that it reads one or two snapshots' D^-1/2 instead
-// of all: N = 200k, k = 8 60 -> 38 MB fetched, 21 -> 18.5 us; R-MAT 1M 250 -> 242; N = 100k 14 -> 13.2.  (The same in
+// of all: N = 200k, k = 8 60 -> 38 MB fetched, 21 -> 18.5 us; R-MAT 1M 250 -> 242; N = 100k 14 -> 13.2.  The runs hold as
+// many entries each, as far as the parts' sizes tell: with as many workgroups each, N = 1M Chung-Lu, k = 4, one snapshot of 10M
+// edges and three with a quarter of them took 57 us, now 46; snapshots that double in size 73, now 62.  (The same in
 // k_scatter fetches a quarter less and takes as long: the L2s' requests bound it, one per gathered scale.)  A kernel for the scales alone that
 // runs every class on the XCD that gathers it later fetches a third of that but shares the lines it
 // writes between XCDs, and the two together were slower (0.26 ms).
@@ -1409,10 +1415,11 @@ __global__ __launch_bounds__(kBlock) void k_split_fill(SplitArgs g) {
   int p = 0;
   int32_t b = blockIdx.x;
   if (b >= align_xcd(g.block_off[1])) {
-    b = g.block_off[1] + xcd_run(b - align_xcd(g.block_off[1]), g.block_off[g.k + 1] - g.block_off[1]);
-    while (p < g.k + 1 && b >= g.block_off[p + 1]) ++p;
+    const int32_t x = b % kClasses;
+    b = g.run_off[x] + (b - align_xcd(g.block_off[1])) / kClasses;
+    if (b >= g.run_off[x + 1]) return;
+    while (b >= g.block_off[p + 1]) ++p;
   }
-  if (p > g.k) return;
   b -= g.block_off[p];
   if (p == 0 && b >= g.block_off[1]) return;
   if (g.whole >> p & 1ull) {
@@ -1780,18 +1787,47 @@ int build_split_arrays(pipad_frame *f, hipStream_t st) {
   auto fill = f->sub_log2 == 0 ? k_split_fill<8> : f->sub_log2 == 1 ? k_split_fill<16> : k_split_fill<32>;
   // a workgroup per unit for the parts that hold more than a quarter of a snapshot's entries, a wave elsewhere
   int32_t blocks = 0;
+  int64_t snapshot = f->nnz_c, longest = 0;
+  for (int t = 0; t < f->k; ++t) longest = std::max<int64_t>(longest, f->nnz_d[t]);
+  snapshot += longest;
+  double entries = 0;  // of the exclusive parts
   for (int p = 0; p <= f->k; ++p) {
-    int64_t snapshot = f->nnz_c, longest = 0;
-    for (int t = 0; t < f->k; ++t) longest = std::max<int64_t>(longest, f->nnz_d[t]);
-    snapshot += longest;
-    const bool whole = 4 * (int64_t)(p == 0 ? f->nnz_c : f->nnz_d[p - 1]) > snapshot;
+    const int64_t nnz = p == 0 ? f->nnz_c : f->nnz_d[p - 1];
+    const bool whole = 4 * nnz > snapshot;
     if (whole) g.whole |= 1ull << p;
     g.block_off[p] = blocks;
     blocks += whole ? f->n_items : (f->n_items + kWavesPerBlock - 1) / kWavesPerBlock;
+    if (p > 0) entries += (double)nnz;
   }
   g.block_off[f->k + 1] = blocks;
+  // where every XCD's run starts: at its share of the cost, a workgroup's being that of its entries, as far as the parts'
+  // sizes tell, and that of 500
   const int32_t excl = blocks - g.block_off[1];
-  hipLaunchKernelGGL(fill, dim3((unsigned)(align_xcd(g.block_off[1]) + align_xcd(excl))), dim3(kBlock), 0, st, g);
+  const double scale = entries > 0 ? (double)f->split_d / entries : 0.0, each = 500.0;
+  int32_t longest_run = 0;
+  double front = 0;  // of the parts that end before this run starts
+  g.run_off[0] = g.block_off[1];
+  for (int x = 1, p = 1; x <= kClasses; ++x) {
+    const double target = (scale * entries + each * excl) * x / kClasses;
+    for (;; ++p) {
+      const int32_t b = g.block_off[p + 1] - g.block_off[p];
+      const double part = scale * f->nnz_d[p - 1] + each * b;
+      if (p == f->k || front + part >= target) {
+        const double share = std::min(std::max((target - front) / part, 0.0), 1.0);
+        g.run_off[x] = std::max(g.run_off[x - 1], g.block_off[p] + (int32_t)(share * b));
+        break;
+      }
+      front += part;
+    }
+    if (x == kClasses) g.run_off[x] = blocks;
+    longest_run = std::max(longest_run, g.run_off[x] - g.run_off[x - 1]);
+  }
+  if (((int64_t)align_xcd(g.block_off[1]) + (int64_t)kClasses * longest_run) * kBlock >= ((int64_t)1 << 32)) {
+    // (more threads than a launch takes: as many workgroups for every XCD)
+    longest_run = align_xcd(excl) / kClasses;
+    for (int x = 0; x < kClasses; ++x) g.run_off[x] = g.block_off[1] + std::min(x * longest_run, excl);
+  }
+  hipLaunchKernelGGL(fill, dim3((unsigned)(align_xcd(g.block_off[1]) + kClasses * longest_run)), dim3(kBlock), 0, st, g);
   PIPAD_HIP(hipGetLastError());
   return PIPAD_OK;
 }

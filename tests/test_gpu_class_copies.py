@@ -52,3 +52,23 @@ def test_units_at_the_edges_of_a_piece(pipad, segment, keep, sub):  # noqa: F811
     pipad.set_option("hub_segment", segment)
     pipad.set_option("sub_classes", sub)
     run_case(pipad, n, lists, 16, seed=1)
+
+
+@pytest.mark.parametrize("units", [1, 3, 64, 301])
+@pytest.mark.parametrize("k", [1, 2, 4, 9])
+@pytest.mark.parametrize("sizes", ["first", "last", "growing", "one empty", "disjoint"])
+def test_parts_of_very_different_sizes(pipad, sizes, k, units):  # noqa: F811
+    """The exclusive parts' units are dealt to the XCDs by the parts' sizes: one part has everything, or each
+    twice what the one before has, or one has nothing, or all have as much and the common part nothing."""
+    rng = np.random.default_rng(k * units)
+    n = 1500
+    pool = np.concatenate([np.stack([np.full(m, 2 * q), rng.permutation(n)[:m]], 1)
+                           for q, m in enumerate(rng.integers(210, 700, units))] + [rand_pairs(rng, n, 800)])
+    pool = pool[rng.permutation(len(pool))]
+    m = len(pool)
+    share = {"first": lambda t: slice(0, m if t == 0 else m // 50), "last": lambda t: slice(0, m if t == k - 1 else m // 50),
+             "growing": lambda t: slice(0, m >> (k - 1 - t)), "one empty": lambda t: slice(0, 0 if t == k // 2 else m),
+             "disjoint": lambda t: slice(m * t // k, m * (t + 1) // k)}[sizes]
+    pipad.set_option("mid_max", 40)
+    pipad.set_option("short_max", 20)
+    run_case(pipad, n, [csr(n, pool[share(t)]) for t in range(k)], 8, seed=units)

@@ -8,7 +8,7 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 from test_gpu_build_tiles import csr, rand_pairs  # noqa: E402
-from test_gpu_parity import pipad, run_case  # noqa: E402,F401
+from test_gpu_parity import pipad, run_case, _reset_options  # noqa: E402,F401
 
 
 @pytest.mark.parametrize("k,n", [(2, 4_177_982), (2, 4_177_983), (2, 4_177_984), (2, 4_178_100), (2, 4_200_000), (2, 8_400_000),
