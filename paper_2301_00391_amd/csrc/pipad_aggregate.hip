@@ -1597,8 +1597,8 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
     }
     a.fchunks = 1;
   }
-  // slice geometry: LS lanes of VEC columns each, at most 64 columns per slice (a gathered piece
-  // of a row is then at most 256 bytes: two cache lines).  Rows of 65 to 128 columns go in one slice where
+  // slice geometry: LS lanes of VEC columns each, 64 columns per slice (a gathered piece of a row is then
+  // at most 256 bytes: two cache lines) or 128.  Rows of 65 to 128 columns go in one slice where
   // that touches fewer lines or there would be a half-empty second one: if they do not start at
   // lines, so that two slices both fetch the line where they meet, or are no longer than three.  Two
   // slices against one, k = 4, N = 200k Chung-Lu / 50k R-MAT / 500k Chung-Lu: dense rows, F = 66 751 / 139 / 1079 -> 550 /
@@ -1611,10 +1611,17 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
   // times F columns fit in and F is no whole number of lines (two slices against one, N = 200k, k = 4, F = 112 / 120
   // 794 / 945 -> 747 / 857 us; 50k R-MAT, k = 8 307 / 352 -> 268 / 308).  Matrices with whole lines from row to row that
   // start off a line are taken for ones that do (F = 112 882 us, in one slice 749).
+  // Frames of few rows take two slices all the same: they have too few waves, and in one slice there are half as many
+  // with half as many lane groups for a long row each.  Of 500 frames with F = 66 .. 127 and N = 1k .. 300k, operands in the caches
+  // and not: two slices up to 1.5 times as fast for k = 1 .. 3 below the line (N = 12k Chung-Lu, k = 1 15.6 against 10.8 us; N = 10k
+  // R-MAT, k = 2 22.1, 16.2; N = 15k, k = 2 30.2, 23.5), 5 to 25 % for k >= 4 (N = 1875 R-MAT, k = 4); past it one slice, up to
+  // 25 % (N = 43k, k = 2 34.8 against 44.1; N = 10k, k = 8 33.8, 41.0).  Over all of them 6 % better than one
+  // slice always, 0.5 % from the best of both; at worst 26 % slower than the other (N = 50 .. 58k Chung-Lu, k = 1).
   const int vec = coalescent ? cvec : vec4 ? 4 : 1;
   const bool side_by_side = f->k > 1 && ldx >= (int64_t)f->k * F;
   const bool on_lines = ldx % 32 == 0 && !(side_by_side && F % 32 != 0);
-  int max_cols = !fused && F <= (on_lines ? 96 : 128) ? 128 : 64;
+  const bool few_rows = (int64_t)f->n * f->k < (f->k == 1 ? 60000 : f->k <= 3 ? 50000 : 10000);
+  int max_cols = !fused && !few_rows && F <= (on_lines ? 96 : 128) ? 128 : 64;
   if (opt.slice_cols > 0 && !fused) max_cols = (int)std::min<int64_t>(64, opt.slice_cols);
   const int cols = std::min(F, max_cols);
   if (!coalescent) {

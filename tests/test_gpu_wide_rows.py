@@ -54,7 +54,7 @@ def test_any_start_of_a_row(pipad, F, hubs):  # noqa: F811
 
 
 @pytest.mark.parametrize("mid_max", [200, 512])
-@pytest.mark.parametrize("F", [97, 100, 112, 127, 128])
+@pytest.mark.parametrize("F", [65, 66, 80, 95, 96, 97, 100, 112, 127, 128])
 def test_a_subset_gets_the_bits_of_the_whole_call_wherever_rows_start(pipad, F, mid_max):  # noqa: F811
     """Row strides that are whole lines while the snapshots' matrices start on lines, off them, or some on and
     some off (the concatenated operand: X[t] = base + t * F): every single snapshot gets the bits of the call
@@ -85,3 +85,22 @@ def test_a_subset_gets_the_bits_of_the_whole_call_wherever_rows_start(pipad, F, 
         bounds = oracle.aggregate(n, *csr_to_coo(n, *lists[t]), X[t], threads=8)[1:3]
         check_y(results["on lines"][t].cpu().numpy(), *bounds, f"snapshot {t}")
         check_y(results["side by side"][t].cpu().numpy(), *bounds, f"snapshot {t}, side by side")
+
+
+@pytest.mark.parametrize("F", [66, 96, 100, 127])
+@pytest.mark.parametrize("n,k", [(59_999, 1), (60_000, 1), (16_666, 3), (16_667, 3), (2_499, 4), (2_500, 4)])
+def test_rows_of_all_snapshots_around_one_slice_and_two(pipad, n, k, F):  # noqa: F811
+    """n * k on both sides of where rows of 65 columns and more go in one slice."""
+    rng = np.random.default_rng(n)
+    pool = np.concatenate([rand_pairs(rng, n, 3 * n), np.stack([np.repeat([7, 900], 700), rng.integers(0, n, 1400)], 1),
+                           np.stack([np.repeat([30, 31, 32], 150), rng.integers(0, n, 450)], 1)])
+    lists = [csr(n, pool[rng.random(len(pool)) < 0.9]) for _ in range(k)]
+    frame = pipad.frame_build_overlap([(torch.from_numpy(rp).cuda(), torch.from_numpy(c).cuda()) for rp, c in lists])
+    X = [synth.features(F, t, n, F) for t in range(k)]
+    for xs in (matrices(X, 128, 0), matrices(X, F, 0)):
+        Y = pipad.frame_aggregate(frame, xs, [torch.empty((n, F), device="cuda:0") for _ in range(k)])
+        one = torch.full((n, F), float("nan"), device="cuda:0")
+        pipad.frame_aggregate_subset(frame, [k - 1], xs, [None] * (k - 1) + [one])
+        assert torch.equal(one, Y[k - 1])
+        for t in range(k):
+            check_y(Y[t].cpu().numpy(), *oracle.aggregate(n, *csr_to_coo(n, *lists[t]), X[t], threads=8)[1:3], f"snapshot {t}")
