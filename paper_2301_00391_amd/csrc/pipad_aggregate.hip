@@ -1398,10 +1398,16 @@ int launch(const AggArgs &a, bool fast, hipStream_t st, bool fused_update = fals
 // The update behind the aggregation, from the stored results of all snapshots.
 int launch_update(const AggArgs &a, hipStream_t st) {
   const int64_t tiles = ((int64_t)a.n + 15) / 16 * a.k;
-  // Weights resident in LDS, in as few blocks of columns of the same width as fit 64 KB (every block reads all of
-  // Y), else straight from memory.  With at most 40 KB, for four workgroups per CU, blocks of 64 and 16 columns read
-  // Y twice: N = 200k, k = 4, F = 128, Fo = 80 277 -> 200 us, F = 80, Fo = 128 314 -> 217; R-MAT 60k, k = 8 195 -> 156, 239 -> 181.
+  // Weights resident in LDS, in as few blocks of columns of the same width as fit (every block reads all of Y), else
+  // straight from memory.  64 KB of LDS, for two workgroups per CU, where Y is past the memory-side cache (256 MB): with
+  // at most 40 KB, for four, N = 200k, k = 4, F = 128, Fo = 80 277 -> 200 us, F = 80, Fo = 128 314 -> 217; N = 150k, k = 3, F = 200,
+  // Fo = 128 337 -> 272.  Where that cache holds Y, blocks of more than 32 columns get 53 KB, for three workgroups: N = 60k, k = 2, F = 128,
+  // Fo = 112 with 64 KB 79 us, now 55, F = 160, Fo = 96 87 and 61, F = 200, Fo = 64 72 and 49.  And 40 KB where there are fewer than
+  // 1024 workgroups for a block of columns, or 512 of longer rows: N = 3000, k = 1, F = 128, Fo = 112 15 and 11, N = 12k, k = 2 24 and 19, F = 200,
+  // Fo = 200 56 and 39, F = 384, Fo = 64 39 and 34; N = 30k, k = 2, F = 112, Fo = 96 38 and 31, but F = 384, Fo = 128 98 and 122.
   const int kpad = (a.F + 3) / 4 * 4;
+  const size_t two = 64u << 10, three = 53u << 10, four = 40u << 10;  // workgroups per CU
+  const bool far = (int64_t)a.n * a.k * a.F * 4 > (256 << 20), few = !far && tiles < (a.F < 256 ? 4096 : 2048);
   int64_t col_blocks = 0;
   int cbw = 0;
   size_t lds = 0;
@@ -1409,8 +1415,8 @@ int launch_update(const AggArgs &a, hipStream_t st) {
     ++col_blocks;
     cbw = (int)((a.Fo + 16 * col_blocks - 1) / (16 * col_blocks)) * 16;
     lds = (size_t)(kpad + 1) * (cbw + kUpdPad) * 4;
-  } while (cbw > 16 && (cbw > kUpdMaxCols || lds > (64u << 10)));
-  if (lds <= (64u << 10)) {
+  } while (cbw > 16 && (cbw > kUpdMaxCols || lds > (few ? four : far || cbw <= 32 ? two : three)));
+  if (lds <= two) {
     // as many tiles per wave as leave 16 waves for every CU
     const int per_wave = (int)std::clamp<int64_t>(tiles * col_blocks / 4096, 1, kUpdTiles);
     const int64_t per_block = (int64_t)kWavesPerBlock * per_wave;

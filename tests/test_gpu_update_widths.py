@@ -49,3 +49,20 @@ def test_odd_widths_without_room_for_the_aggregation_stay_refused(pipad, Fo):  #
     X, W = [torch.zeros((n, F), device="cuda:0")], torch.zeros((F, Fo), device="cuda:0")
     with pytest.raises(Exception):
         pipad.frame_aggregate_update(frame, X, W, H=[torch.zeros((n, Fo), device="cuda:0")])
+
+
+@pytest.mark.parametrize("n,k,F,Fo", [(32_735, 2, 128, 112), (32_800, 2, 128, 112), (32_800, 2, 200, 64), (16_300, 2, 300, 40),
+                                      (16_400, 2, 300, 40), (40_003, 2, 90, 127), (270_001, 2, 128, 112), (260_001, 2, 128, 112)])
+def test_blocks_of_columns_by_the_size_of_the_frame(pipad, n, k, F, Fo):  # noqa: F811
+    """Both sides of 4096 and 2048 tiles of 16 rows, and of results past 256 MB: other blocks of columns, the same values."""
+    rng = np.random.default_rng(F + Fo)
+    snaps = [(torch.from_numpy(rp).cuda(), torch.from_numpy(c).cuda()) for rp, c in [csr(n, rand_pairs(rng, n, 2 * n)) for _ in range(k)]]
+    frame = pipad.frame_build_overlap(snaps)
+    X = [torch.empty((n, F), device="cuda:0").uniform_(-1, 1) for _ in range(k)]
+    W, b = torch.empty((F, Fo), device="cuda:0").uniform_(-1, 1), torch.empty(Fo, device="cuda:0").uniform_(-1, 1)
+    A, H = [torch.zeros((n, F), device="cuda:0") for _ in range(k)], [torch.full((n, Fo), 77.0, device="cuda:0") for _ in range(k)]
+    pipad.frame_aggregate_update(frame, X, W, b, H=H, A=A)
+    for t in range(k):
+        exact = A[t].double() @ W.double() + b.double()
+        bound = A[t].double().abs() @ W.double().abs() + b.double().abs()
+        assert bool(((H[t].double() - exact).abs() <= (F + 2) * 2.0 ** -24 * bound).all())
