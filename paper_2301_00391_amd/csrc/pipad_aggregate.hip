@@ -1365,6 +1365,16 @@ inline size_t update_lds_bytes(const AggArgs &a) {
          (size_t)kWavesPerBlock * kTileRows * sizeof(int32_t);
 }
 
+// The instance for teams of 1 << ls_log2 lanes (rows of one column at a time have at most four columns).
+template <int VEC, bool PLAIN>
+void (*aggregate_kernel(bool fast, int ls_log2))(AggArgs) {
+  if (!fast) return k_aggregate<VEC, false, 1, PLAIN>;
+  if constexpr (VEC > 1)
+    if (ls_log2 >= 3) return k_aggregate<VEC, true, 1, PLAIN>;
+  return ls_log2 >= 2 ? k_aggregate<VEC, true, 2, PLAIN>
+         : ls_log2 == 1 ? k_aggregate<VEC, true, 4, PLAIN> : k_aggregate<VEC, true, 4, PLAIN, true>;
+}
+
 template <int VEC>
 int launch(const AggArgs &a, bool fast, hipStream_t st, bool fused_update = false) {
   const int64_t phases = (int64_t)a.nsel * a.fchunks;
@@ -1384,12 +1394,8 @@ int launch(const AggArgs &a, bool fast, hipStream_t st, bool fused_update = fals
       return PIPAD_OK;
     }
   }
-  void (*const kern[2][5])(AggArgs) = {
-      {k_aggregate<VEC, true, 4, false, true>, k_aggregate<VEC, true, 4, false>, k_aggregate<VEC, true, 2, false>,
-       k_aggregate<VEC, true, 1, false>, k_aggregate<VEC, false, 1, false>},
-      {k_aggregate<VEC, true, 4, true, true>, k_aggregate<VEC, true, 4, true>, k_aggregate<VEC, true, 2, true>,
-       k_aggregate<VEC, true, 1, true>, k_aggregate<VEC, false, 1, true>}};
-  if (blocks > 0) hipLaunchKernelGGL(kern[a.plain][fast ? std::min(a.ls_log2, 3) : 4], grid, block, 0, st, a);
+  auto kern = a.plain ? aggregate_kernel<VEC, true>(fast, a.ls_log2) : aggregate_kernel<VEC, false>(fast, a.ls_log2);
+  if (blocks > 0) hipLaunchKernelGGL(kern, grid, block, 0, st, a);
   if (fin > 0) hipLaunchKernelGGL((k_split_finish<VEC>), dim3((unsigned)fin), dim3(kBlock), 0, st, a);
   PIPAD_HIP(hipGetLastError());
   return PIPAD_OK;
@@ -1440,10 +1446,11 @@ int launch_coalescent(const AggArgs &a, hipStream_t st) {
   if (blocks >= ((int64_t)1 << 31)) return PIPAD_ERR_TOO_LARGE;
   // entries per fetching lane, so that a chunk holds U = 4 and more for every lane group: 4 for one or
   // two lanes per snapshot (F <= 4), 2 for two and more; F == VEC is one lane per snapshot
-  auto kern = a.plain ? (a.F == VEC ? k_aggregate_coalescent<VEC, 4, true, true> : k_aggregate_coalescent<VEC, 4, true, false>)
-                      : (a.F == VEC ? k_aggregate_coalescent<VEC, 4, false, true> : k_aggregate_coalescent<VEC, 4, false, false>);
-  if constexpr (VEC == 4)
-    if (a.F > 4) kern = a.plain ? k_aggregate_coalescent<VEC, 2, true, false> : k_aggregate_coalescent<VEC, 2, false, false>;
+  auto kern = a.plain ? k_aggregate_coalescent<VEC, 4, true, true> : k_aggregate_coalescent<VEC, 4, false, true>;
+  if constexpr (VEC > 1) {  // (VEC is F up to two columns, two for three, and four)
+    constexpr int EPL = VEC == 4 ? 2 : 4;
+    if (a.F > VEC) kern = a.plain ? k_aggregate_coalescent<VEC, EPL, true, false> : k_aggregate_coalescent<VEC, EPL, false, false>;
+  }
   if (blocks > 0) hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kBlock), 0, st, a);
   if (a.n_hub > 0 && !a.direct) {
     const int64_t hb = ((int64_t)a.n_hub + kWavesPerBlock - 1) / kWavesPerBlock * a.nslices;
