@@ -210,8 +210,10 @@ __device__ inline int32_t wave_row_of_entry(const int32_t *rp, int32_t n, int32_
 // together (3.4 M entries: 38 -> 33 us; tiles dealt to the XCDs in turn, whole lines never met).  With rows
 // found by a running maximum instead of a binary search per entry 43 -> 38 us.
 // FEW: no part has more than kFewTiles tiles (an instance of its own: as a branch it took 24 registers more).
+// (With 16 entries per thread held to the 128 registers that two workgroups per CU allow: 150 took the transposition of 58M
+// entries from 810 to 980 us.)
 template <int R, bool FEW = false>
-__global__ __launch_bounds__(kSortBlock) void k_radix_scatter(SortArgs g) {
+__global__ __launch_bounds__(kSortBlock) __attribute__((amdgpu_waves_per_eu(R == 16 ? 4 : 1))) void k_radix_scatter(SortArgs g) {
   __shared__ uint16_t rank_of[kSortWaves][kMaxDigits];  // counts, then the first place in the tile, per wave
   __shared__ int32_t stage[kSortBlock * R];             // the tile's keys, then its values, in digit order
   __shared__ uint32_t to[kMaxDigits];                   // place in the part minus place in the tile
@@ -262,22 +264,21 @@ __global__ __launch_bounds__(kSortBlock) void k_radix_scatter(SortArgs g) {
         row = __builtin_amdgcn_readlane(val[q], kWave - 1);
       }
     } else {
-      int32_t lo[R], hi[R];
 #pragma unroll
-      for (int q = 0; q < R; ++q) {
-        lo[q] = r0;
-        hi[q] = r1;
-      }
-      for (int32_t range = r1 - r0; range > 0; range >>= 1)  // (all of the lane's entries side by side)
+      for (int q = 0; q < R; ++q) val[q] = r0;
+      constexpr int G = R < 8 ? R : 8;  // entries that are searched for side by side
+      for (int32_t step = r1 > r0 ? 1 << (31 - __builtin_clz((uint32_t)(r1 - r0))) : 0; step >= 1; step >>= 1)
 #pragma unroll
-        for (int q = 0; q < R; ++q) {
-          const int32_t mid = lo[q] + ((hi[q] - lo[q] + 1) >> 1);
-          const bool up = rp[mid] <= min(e0 + q * kWave + lane, e1);
-          lo[q] = up ? mid : lo[q];
-          hi[q] = up ? hi[q] : max(mid - 1, lo[q]);
+        for (int h = 0; h < R; h += G) {
+          int32_t at[G];
+#pragma unroll
+          for (int q = 0; q < G; ++q) at[q] = rp[val[h + q] + min(step, r1 - val[h + q])];
+          // (left to itself the compiler waited for each load before the next: parts of few entries, N = 29k, k = 16 36 -> 25 us)
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int q = h; q < h + G; ++q)
+            if (at[q - h] <= min(e0 + q * kWave + lane, e1)) val[q] += min(step, r1 - val[q]);
         }
-#pragma unroll
-      for (int q = 0; q < R; ++q) val[q] = lo[q];
     }
   }
   for (int x = tid; x < kSortWaves * kMaxDigits / 2; x += kSortBlock) reinterpret_cast<uint32_t *>(rank_of)[x] = 0;
