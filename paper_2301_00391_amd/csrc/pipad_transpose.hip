@@ -63,7 +63,8 @@ struct SortArgs {
 // Part that holds position e of a concatenated array with the given part offsets.
 __device__ inline int part_of(const uint32_t *off, int nparts, uint32_t e) {
   int p = 0;
-  while (p + 1 < nparts && e >= off[p + 1]) ++p;
+  for (int step = nparts > 1 ? 1 << (31 - __builtin_clz(nparts - 1)) : 0; step >= 1; step >>= 1)
+    if (p + step < nparts && e >= off[p + step]) p += step;
   return p;
 }
 
@@ -392,7 +393,8 @@ __global__ __launch_bounds__(kSortBlock) __attribute__((amdgpu_waves_per_eu(R ==
 // the exclusive part of snapshot t.
 struct FinishArgs {
   int32_t nparts, n, k;
-  int32_t block_off[PIPAD_MAX_K + 2];     // first workgroup of every part, in their natural order
+  uint32_t block_off[PIPAD_MAX_K + 2];    // first workgroup of every part, in their natural order
+  int32_t step_xcd, step_block;           // from one XCD's exclusive workgroup to the next XCD's, and to its own next
   uint32_t part_off[PIPAD_MAX_K + 2];
   const int32_t *key;                     // sorted columns of the source, part by part
   const int32_t *col[PIPAD_MAX_K + 1];    // columns of the transposed parts
@@ -423,14 +425,16 @@ template <int KV, bool FULL>
 __global__ __launch_bounds__(kBlock) void k_finish_parts(FinishArgs g) {
   const int lane = threadIdx.x % kWave;
   // (an XCD takes a run of the exclusive parts, so that it reads one or two snapshots' D^-1/2; no workgroup
-  // is launched for nothing where the parts differ in size: N = 200k, k = 4 27 -> 25 us)
+  // is launched for nothing where the parts differ in size: N = 200k, k = 4 27 -> 25 us; with more than eight snapshots
+  // the workgroups go in turn, N = 29k, k = 16 with hardly any common entries 23 -> 18, transposition of N = 200k, k = 16 811 -> 761)
   int p = 0;
   int32_t b = blockIdx.x;
   if (b >= align_xcd(g.block_off[1])) {
-    b = g.block_off[1] + xcd_run(b - align_xcd(g.block_off[1]), g.block_off[g.nparts] - g.block_off[1]);
-    while (p < g.nparts && b >= g.block_off[p + 1]) ++p;
+    b -= align_xcd(g.block_off[1]);
+    b = g.block_off[1] + b % kClasses * g.step_xcd + b / kClasses * g.step_block;
+    p = part_of(g.block_off, g.nparts, (uint32_t)b);
   }
-  if (p == g.nparts || b >= g.block_off[p + 1]) return;
+  if ((uint32_t)b >= g.block_off[p + 1]) return;
   b -= g.block_off[p];
   const int32_t nnz = (int32_t)(g.part_off[p + 1] - g.part_off[p]);
   const int64_t e64 = (int64_t)b * kBlock + threadIdx.x;
@@ -659,12 +663,15 @@ int transpose_frame(const pipad_frame *f, pipad_alloc_fn alloc, void *alloc_ctx,
     int64_t blocks = 0;
     for (int p = 0; p <= k; ++p) {
       const int64_t nnz = (int64_t)(s.part_off[p + 1] - s.part_off[p]);
-      c.block_off[p] = (int32_t)blocks;
+      c.block_off[p] = (uint32_t)blocks;
       blocks += nnz > 0 ? (nnz + kBlock - 1) / kBlock : std::min<int64_t>((int64_t)n / kBlock + 1, 1024);
     }
-    c.block_off[k + 1] = (int32_t)blocks;
+    c.block_off[k + 1] = (uint32_t)blocks;
     const int32_t first_excl = align_xcd(c.block_off[1]);
-    hipLaunchKernelGGL(finish, dim3((unsigned)(first_excl + align_xcd((int32_t)blocks - c.block_off[1]))), dim3(kBlock), 0,
+    const int32_t excl_blocks = align_xcd((int32_t)blocks - c.block_off[1]);
+    c.step_xcd = k <= 8 ? excl_blocks / kClasses : 1;
+    c.step_block = k <= 8 ? 1 : kClasses;
+    hipLaunchKernelGGL(finish, dim3((unsigned)(first_excl + excl_blocks)), dim3(kBlock), 0,
                        st, c);
   }
   PIPAD_TRY_T(hipGetLastError());
