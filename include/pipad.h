@@ -275,16 +275,19 @@ const char *pipad_last_hip_error(void);
  *                    with more than one, the hub rows are walked in that many passes per
  *                    snapshot, each pass over a smaller share of X (default 1: on MI355X the passes
  *                    read less from memory but take longer)
- *   "agg_order"      order of the workgroups of one call.  1: the slices (64 columns of one
- *                    snapshot) one after the other, so that the caches hold one snapshot's
+ *   "agg_order"      order of the workgroups of one call.  1: the slices (up to 128 columns of
+ *                    one snapshot) one after the other, so that the caches hold one snapshot's
  *                    matrix at a time; 0: the same rows of all slices side by side, so that the
  *                    slices share the entry lists they have in common (the overlap part is read
- *                    once for all snapshots); 2 (default): 0 while one slice's matrix is smaller
- *                    than 28 MiB, else 1.  Results do not depend on it.
+ *                    once for all snapshots); 2 (default): side by side while one slice's matrix
+ *                    is smaller than 28 MiB, as with 0 or with a run of consecutive slices per XCD
+ *                    (where their number does not divide 8 and matrices and rows are long enough),
+ *                    else 1.  Results do not depend on it.
  *   "agg_nt"         bit 0: non-temporal stores for Y (every element is written once and not read
  *                    again by the call: measured 1-6 % faster); bit 1: non-temporal loads for the
  *                    index and scale streams (no gain measured) (default 1)
- *   "slice_cols"     feature columns per slice, 1..64 (default 0 = 64)
+ *   "slice_cols"     feature columns per slice, 1..64 (default 0: 64, and rows of 65 to 128 columns
+ *                    in one slice where their stride and the size of the frame make that faster)
  *   "agg_generic"    1 forces the bounds-checked kernel with 64-bit addresses (default 0: only for
  *                    matrices of 4 GB and more)
  *   "agg_coalescent" kernel for F < 32 on the concatenated operand that gathers the rows of

@@ -16,8 +16,9 @@
 // contraction), so there is no MFMA.
 //
 // How one launch covers the frame.  The coalescent feature row of a node (k snapshots x F
-// columns) is cut into *slices* of at most 64 columns of one snapshot, and the launch goes through
-// the slices one after the other (workgroups are dispatched in index order): the whole chip works
+// columns) is cut into *slices* of at most 64 columns of one snapshot (rows of 65 to 128 columns in
+// one slice where that is better), and the launch goes through the slices one after the other
+// (workgroups are dispatched in index order; small matrices side by side instead): the whole chip works
 // on one snapshot's matrix at a time, so the caches see one matrix instead of k.
 //
 // Column classes.  The chip has 8 XCDs, each with a private 4 MB L2; workgroup b runs on XCD
@@ -1064,9 +1065,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
 // Bound: the streams of indices and scales, where there are many entries: a common entry brings 4 bytes
 // of index and 4 of scale per snapshot out of k arrays, and a lane that fetches for itself (F <= 4 in
 // short rows) loads its entries a dword at a time, an instruction touching up to 64 lines.  N = 1M
-// R-MAT, k = 8, F = 2: with the row gathers replaced by zeros the kernel takes 435 of its 600 us and
-// fetches 1.57 of 2.75 GB, twice what lists and scales hold; the gathers (64 of the 128 bytes of a
-// line) add the rest.  For small frames the chain index - row pointers - entries - rows, which is
+// R-MAT, k = 8, F = 2: with the row gathers replaced by zeros the kernel takes 333 of its 583 us and
+// fetches 1.31 of 2.75 GB, half as much again as lists and scales hold; the gathers (64 of the 128 bytes of a
+// line) add the rest.  A load looks up 16 lines, the address units are busy for 83 % of the time.  For small frames the chain index - row pointers - entries - rows, which is
 // therefore requested two steps ahead.  Measured (wide operand; before: entries staged for all snapshots
 // of a team one load after the other, hub units whole, VEC from F's divisors): N = 1M R-MAT, k = 8, F = 2
 // 617 -> 585 us; 300k, k = 8, F = 6 467 -> 352; 300k, k = 16, F = 3 846 -> 510; 50k, k = 12, F = 9 468 ->
@@ -1567,7 +1568,8 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
     // refused.  What the update adds to the aggregation, behind it and inside: N = 200k, k = 4, F = 64, Fo = 8 / 20 / 40 51 / 61
     // / 78 -> 29 / 35 / 47 us, F = 16 25 / 39 / 59 -> 10 / 17 / 28; R-MAT 60k, k = 8, F = 64 58 / 62 / 79 -> 33 / 43 / 55.  From
     // 400k rows of all snapshots together on where a slice has more than 32 columns: with fewer, a wave's 16 rows four at
-    // a time take up to 1.5 times as long as rows of their own and a second launch; 32 and less are 4 to 30 % faster.)
+    // a time take up to 1.5 times as long as rows of their own and a second launch; 32 and less are 4 to 30 % faster, but for
+    // R-MAT frames with N = 300k .. 450k, k = 4 and 8, F = 16, Fo <= 24: with fresh operands up to 8 % slower.)
     const bool tiles = upd->Fo >= 16 && upd->Fo % 16 == 0;
     const bool inside = tiles || (Y && (F <= 32 || (int64_t)f->n * f->k >= 400000));
     fused = aligned && F >= 16 && F <= 64 && upd->Fo <= 64 && inside && fast;
@@ -1664,6 +1666,9 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
     // k = 5, F = 30 132 -> 98 us; N = 120k, k = 12, F = 16 258 -> 180), 3 % slower at worst; with 6 entries
     // per row it is the slices' parity that decides: odd numbers 5 to 13 % faster from 10 MiB on, others
     // between 7 % faster and 4 % slower; smaller matrices and numbers that divide 8 up to 30 % slower.
+    // (All with operands in the caches as far as they fit.  Of 80 frames inside the rule 15 % faster in the mean so, at worst
+    // 8 % slower; with operands that no cache holds 5 % faster, from 12 entries per row on 9 to 15 %, with 8 to 10 entries
+    // and matrices of less than 12 MiB 5 to 7 % slower, at worst 13.)
     if (a.order == 0 && !coalescent && !fused && kClasses % slices != 0 && matrix >= (5 << 20) &&
         (entries >= 8 * (int64_t)f->n || (slices % 2 == 1 && matrix >= (10 << 20))))
       a.order = 2;

@@ -1652,7 +1652,9 @@ int wait_totals(const TotalsTicket &ticket, hipStream_t st, FrameTotals *out) {
 // 24.9 -> 20.8, with the build (F = 32) 66 -> 56; N = 32k, 20 entries per row, k = 4: F = 64 55 -> 56, with the build 92 -> 81;
 // N = 60k, k = 1 64 -> 56.  Chung-Lu, N = 40k, k = 4: F = 64 58 -> 55, with the build 85 -> 73.  Past the line: R-MAT,
 // N = 60k, 20 entries per row, k = 8: F = 64 167 -> 181.  (With a smaller mid_max rows that a wave does better with
-// would be among them.)
+// would be among them.)  Of 200 frames below the line with hub rows, in the mean: steps 6 to 14 % faster, backward passes 3 to 11,
+// aggregations alone 4 to 26, the more the fewer entries, with operands in the caches and without; at worst 14 % slower
+// (R-MAT, N = 62k, k = 2, F = 32, aggregation alone).
 constexpr int32_t kPlainNodes = 65536, kPlainRow = 512;
 constexpr int64_t kPlainEntries = (int64_t)4 << 20;
 
@@ -1662,7 +1664,9 @@ constexpr int64_t kPlainEntries = (int64_t)4 << 20;
 // R-MAT and Chung-Lu: 32 against 64 is 10 to 13 % faster in the mean for k = 1 .. 4 (fused update 4 to 6 %), at worst
 // 7 % slower; for more snapshots, which bring more waves, 5 % and at worst 14 % slower, 48 is 4 % faster and at
 // worst 6 % slower.  With more entries 48 is between 19 % faster and 12 % slower, 32 up to 30 % slower
-// (the fused update with F = 16, k = 4, 0.5M entries 7 %).
+// (the fused update with F = 16, k = 4, 0.5M entries 7 %).  These with operands in the caches; of 200 frames with operands
+// that no cache holds 16 to 18 % faster for k = 1 .. 4 and up to 32 columns, 5 to 10 % otherwise, at worst 6 % slower (the
+// update 9 %; in the caches 13 %: R-MAT, N = 5k, k = 3, F = 64, Fo = 16).
 static int64_t short_rows_up_to(int64_t option, int32_t k, int64_t entries) {
   if (option != Options().short_max || entries > (3 << 17)) return option;
   return k <= 4 ? option / 2 : option / 4 * 3;
