@@ -82,15 +82,6 @@ __global__ __launch_bounds__(kBlock) void k_validate(Snaps s, int32_t n, int32_t
 }
 
 // ---- bounds ---------------------------------------------------------------------------------
-// Last row i in [lo, hi] with rowptr[i] <= e, given rowptr[lo] <= e < rowptr[hi + 1].
-__device__ inline int32_t row_of_entry(const int32_t *rp, int32_t lo, int32_t hi, int32_t e) {
-  while (lo < hi) {
-    const int32_t mid = lo + ((hi - lo + 1) >> 1);
-    if (rp[mid] <= e) lo = mid; else hi = mid - 1;
-  }
-  return lo;
-}
-
 // First position in col[lo, hi) (ascending) that holds c or more.
 __device__ inline int32_t lower_bound(const int32_t *col, int32_t lo, int32_t hi, int32_t c) {
   while (lo < hi) {
