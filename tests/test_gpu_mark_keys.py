@@ -23,6 +23,19 @@ def test_numbers_of_nodes_around_what_a_key_holds(pipad, n, k):  # noqa: F811
     run_case(pipad, n, lists, 1, seed=1, validate=False)
 
 
+@pytest.mark.parametrize("k,n", [(2, 4_177_982), (2, 4_177_983), (18, 8_323_579)])
+def test_the_largest_keys(pipad, n, k):  # noqa: F811
+    """Tiles of as many rows as entries, all in the last columns: the last row's number times the largest row of
+    keys; the other snapshots have some of them, and rows and columns beside them."""
+    rng = np.random.default_rng(n)
+    rows = np.arange(0, 3000, 2)
+    base = np.stack([rows, n - 1 - rows % 5], 1)
+    lists = [csr(n, base)]
+    for _ in range(k - 1):
+        lists.append(csr(n, np.concatenate([base[rng.random(len(base)) < 0.8], [[r, n - 1] for r in rng.integers(0, 3000, 150)]])))
+    run_case(pipad, n, lists, 1, seed=1, validate=False)
+
+
 @pytest.mark.parametrize("k,extra", [(2, 127), (2, 128), (2, 129), (17, 63), (17, 64), (17, 65)])
 def test_a_stretch_at_what_a_wave_takes(pipad, k, extra):  # noqa: F811
     """Snapshot 1 has `extra` entries more than the tile between its first entry and the next tile's."""
@@ -35,7 +48,8 @@ def test_a_stretch_at_what_a_wave_takes(pipad, k, extra):  # noqa: F811
 
 @pytest.mark.parametrize("rows", [63, 64, 65, 255, 256, 257, 4094, 4095, 4096, 4097])
 def test_rows_of_a_tile(pipad, rows):  # noqa: F811
-    """One tile of two full rows with empty rows, and rows that only the other snapshots have, in between."""
+    """Two full rows with empty rows, and rows that only the other snapshots have, in between: in one tile, or in three from
+    some 1900 rows on (test_most_rows_of_a_tile keeps more in one)."""
     n, k = 5000, 3
     between = [[r, (r * 7) % 90] for r in range(2, rows, 3)]
     ends = [[0, c] for c in range(1, 200)] + [[rows, c] for c in range(1, 250) if c != rows]
