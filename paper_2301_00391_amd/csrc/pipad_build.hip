@@ -22,6 +22,9 @@
 //   scatter  a wave per tile (or four) and part writes the entries in order, with their column scales
 //   fill     the entries of the hub rows a second time, grouped by column class, with their scales
 //
+// Small frames, whose launches take longer than their work, go in two: prepare and mark (a tile finds its own bounds), then the
+// sums, rows and scatter (every workgroup makes the sums that it needs), into room for as many entries as the parts can have.
+//
 // All integer work; the outputs are unique, so they are bit-exact regardless of scheduling.
 #include <algorithm>
 #include <cstring>
@@ -122,12 +125,12 @@ struct RowClasses {  // the thresholds of the row classes
   int32_t short_max, mid_max, threshold, segment;
 };
 
-// Counts of 256 rows, a thread each.
+// Counts of 256 rows, a thread each, by every 256 threads of the workgroup (`out`: theirs, or null).
 __device__ inline void count_rows(const RowClasses &rc, bool live, int64_t L, int64_t entries, int32_t common,
                                   RowCounts *out) {
-  __shared__ uint32_t w_mid[kWavesPerBlock], w_hub[kWavesPerBlock], w_units[kWavesPerBlock],
-      w_common[kWavesPerBlock], w_short[kWavesPerBlock];
-  __shared__ uint64_t w_all[kWavesPerBlock];
+  constexpr int W = 16;  // waves of a workgroup at most
+  __shared__ uint32_t w_mid[W], w_hub[W], w_units[W], w_common[W], w_short[W];
+  __shared__ uint64_t w_all[W];
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   const int cls = row_class(L, rc.short_max, rc.mid_max);
   const uint64_t is_mid = __ballot(live && cls == 1), is_hub = __ballot(live && cls == 2);
@@ -155,10 +158,11 @@ __device__ inline void count_rows(const RowClasses &rc, bool live, int64_t L, in
     w_all[wave] = all;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (threadIdx.x % kBlock == 0 && out) {
     RowCounts c = {0, 0, 0, 0, 0, 0};
 #pragma unroll
-    for (int w = 0; w < kWavesPerBlock; ++w) {
+    for (int u = 0; u < kWavesPerBlock; ++u) {
+      const int w = wave + u;
       c.short_entries += w_short[w];
       c.common += w_common[w];
       c.mid += w_mid[w]; c.hub += w_hub[w]; c.units += w_units[w]; c.entries += w_all[w];
@@ -204,19 +208,11 @@ __device__ inline void find_bounds(const Snaps &s, const Tiles &g, int64_t wave,
   }
 }
 
-// The first `bound_blocks` workgroups find the tiles' bounds (they wait for memory most of the
-// time), the others take 256 rows each: dinv_t[i] = (1 + |row i of snapshot t|)^-1/2, evaluated in
-// double and rounded once, and the counts the row lists are laid out by.
-__global__ __launch_bounds__(kBlock) void k_prepare(Snaps s, Tiles g, RowClasses rc, int32_t bound_blocks,
-                                                     float *dinv, float *dinv_nk) {
-  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-  if ((int32_t)blockIdx.x < bound_blocks) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) *g.bad = 0;
-    find_bounds(s, g, (int64_t)blockIdx.x * kWavesPerBlock + wave, lane);
-    return;
-  }
-  const int64_t rb = (int64_t)blockIdx.x - bound_blocks;
-  const int64_t i64 = rb * kBlock + threadIdx.x;
+// 256 rows (block rb of them): dinv_t[i] = (1 + |row i of snapshot t|)^-1/2, evaluated in double and rounded once, and
+// the counts the row lists are laid out by.
+__device__ __forceinline__ void prepare_rows(const Snaps &s, const Tiles &g, const RowClasses &rc, int64_t rb, float *dinv,
+                                             float *dinv_nk) {
+  const int64_t i64 = rb * kBlock + threadIdx.x % kBlock;
   const bool live = i64 < g.n;
   const int32_t i = (int32_t)min(i64, (int64_t)g.n - 1);
   int32_t longest = 0;
@@ -252,7 +248,55 @@ __global__ __launch_bounds__(kBlock) void k_prepare(Snaps s, Tiles g, RowClasses
       }
     }
   }
-  count_rows(rc, live, longest, all, 0, g.row_cnt + rb);
+  count_rows(rc, live, longest, all, 0, rb * kBlock < g.n ? g.row_cnt + rb : nullptr);
+}
+
+// The first `bound_blocks` workgroups find the tiles' bounds (they wait for memory most of the
+// time), the others take 256 rows each.
+__global__ __launch_bounds__(kBlock) void k_prepare(Snaps s, Tiles g, RowClasses rc, int32_t bound_blocks,
+                                                     float *dinv, float *dinv_nk) {
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  if ((int32_t)blockIdx.x < bound_blocks) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) *g.bad = 0;
+    find_bounds(s, g, (int64_t)blockIdx.x * kWavesPerBlock + wave, lane);
+    return;
+  }
+  prepare_rows(s, g, rc, (int64_t)blockIdx.x - bound_blocks, dinv, dinv_nk);
+}
+
+// The row of a tile's first entry (lanes 0 .. 31) and of the next tile's (lanes 32 .. 63) in the base: 32 places are looked at
+// in one round trip.  (e: the half's entry, which exists)
+__device__ __forceinline__ int32_t half_row_of_entry(const int32_t *rp, int32_t n, int32_t e, int lane) {
+  constexpr int H = kWave / 2;
+  const int sub = lane % H, shift = lane / H * H;
+  int32_t lo = 0, hi = n;  // rp[lo] <= e < rp[hi]
+  while (__any(hi - lo > 1)) {
+    const int32_t step = (int32_t)(((int64_t)hi - lo + H) / (H + 1));
+    const int64_t idx = lo + (int64_t)(sub + 1) * step;
+    const int32_t v = rp[min(idx, (int64_t)n)];
+    const int m = __popc((uint32_t)(__ballot(idx < hi && v <= e) >> shift));
+    lo += m * step;
+    hi = (int32_t)min((int64_t)hi, (int64_t)lo + max(step, 1));
+  }
+  return lo;
+}
+
+// First position in col[lo, hi) (ascending) that holds c or more, by half a wave.
+__device__ __forceinline__ int32_t half_lower_bound(const int32_t *col, int32_t lo, int32_t hi, int32_t c, int lane) {
+  constexpr int H = kWave / 2;
+  const int sub = lane % H, shift = lane / H * H;
+  while (__any(lo < hi)) {
+    const int32_t step = (int32_t)(((int64_t)hi - lo + H) / (H + 1));
+    const int64_t idx = lo + (int64_t)(sub + 1) * step - 1;
+    bool below = false;
+    if (lo < hi && idx < hi) below = col[idx] < c;
+    const int m = __popc((uint32_t)(__ballot(below) >> shift));
+    if (lo < hi) {
+      lo += m * step;
+      if (m < H) hi = (int32_t)min((int64_t)hi, (int64_t)lo + step - 1);  // (place lo + step - 1 was looked at)
+    }
+  }
+  return lo;
 }
 
 // ---- mark -----------------------------------------------------------------------------------
@@ -297,6 +341,7 @@ struct Mark {
     return min(at + kPlane * B, at + kPlane * B - (kRun * kPlane * B - B));
   }
 };
+constexpr uint32_t kBadTile = 1u << 21;            // in tile_cnt.y of a tile whose snapshots are not canonical (k_prepare_mark)
 constexpr int32_t kMarkRows = 16384;               // most rows of a tile that are gone through one by one
 
 // Places of base entries are in bytes of the array they are looked up in.
@@ -460,8 +505,9 @@ __device__ __forceinline__ bool mark_twice(const K *keys, int32_t here, int lane
 
 // (Held to eight waves per SIMD with 32-bit keys.  Without spilled registers: a variant that kept 48 bytes of them in private
 // memory took 1337 us for the build of the 1M-node R-MAT frame, not 948.)
-template <int T, int L, class K>  // L: snapshots per wave; K: 32- or 64-bit keys
-__global__ __launch_bounds__(16 * kWave) __attribute__((amdgpu_waves_per_eu(sizeof(K) == 4 ? 8 : 6))) void k_mark(Snaps s, Tiles g, int32_t mid_max) {
+// SELF: the waves find where the tile starts in their snapshots themselves (k_prepare_mark).
+template <int T, int L, class K, bool SELF>  // L: snapshots per wave; K: 32- or 64-bit keys
+__device__ __forceinline__ void mark_tile(const Snaps &s, const Tiles &g, int32_t mid_max) {
   using S = Mark<T>;
   constexpr int R = S::kRun, E = S::kMost, PLANE = S::kPlane;
   __shared__ uint64_t key_words[R * PLANE];  // keys of either width
@@ -480,11 +526,45 @@ __global__ __launch_bounds__(16 * kWave) __attribute__((amdgpu_waves_per_eu(size
   const int32_t *rp0 = s.rowptr[g.base];
   const int32_t e0 = tile * T;
   const int32_t here = min(T, s.nnz[g.base] - e0);
-  const int32_t r0 = g.brow[tile], r1 = g.brow[tile + 1];
-  const int32_t rfirst = tile == 0 ? 0 : r0;  // (the first tile owns what lies in front of the base, too)
   const uint32_t all_bits = ~0u >> (32 - g.k);
   const int32_t lb = min(lane, g.k - 1);
-  const int32_t my_b0 = g.bound[lb * ldb + tile], my_b1 = g.bound[lb * ldb + tile + 1];
+  int32_t r0, r1, my_b0, my_b1;
+  if constexpr (SELF) {
+    __shared__ int2 bounds[PIPAD_MAX_K];
+    const bool last = tile + 1 == g.ntiles;
+    const int32_t e = lane < kWave / 2 ? e0 : min(e0 + T, s.nnz[g.base] - 1);
+    const int32_t column = s.col[g.base][e], row = half_row_of_entry(rp0, g.n, e, lane);
+#pragma unroll
+    for (int l = 0; l < L; ++l) {
+      const int t = wave + l * nwaves;
+      if (t >= g.k) break;
+      const int32_t nnz = s.nnz[t];
+      int32_t at = e;
+      if (t != g.base) {
+        const int32_t first = s.rowptr[t][row], end = s.rowptr[t][row + 1];
+        at = half_lower_bound(s.col[t], min(max(first, 0), nnz), min(max(end, 0), nnz), column, lane);
+      }
+      // (entries in front of the base's first one belong to the first tile)
+      const int2 b = make_int2(tile == 0 ? 0 : __builtin_amdgcn_readlane(at, 0),
+                               last ? nnz : __builtin_amdgcn_readlane(at, kWave - 1));
+      if (lane == 0) {
+        bounds[t] = b;
+        g.bound[t * ldb + tile] = b.x;
+        if (last) g.bound[t * ldb + g.ntiles] = nnz;
+      }
+    }
+    r0 = __builtin_amdgcn_readlane(row, 0);
+    r1 = last ? g.n - 1 : __builtin_amdgcn_readlane(row, kWave - 1);
+    __syncthreads();
+    my_b0 = bounds[lb].x;
+    my_b1 = bounds[lb].y;
+  } else {
+    r0 = g.brow[tile];
+    r1 = g.brow[tile + 1];
+    my_b0 = g.bound[lb * ldb + tile];
+    my_b1 = g.bound[lb * ldb + tile + 1];
+  }
+  const int32_t rfirst = tile == 0 ? 0 : r0;  // (the first tile owns what lies in front of the base, too)
   for (int x = threadIdx.x; x < R * PLANE; x += blockDim.x) present[x] = x % PLANE < kWave ? 1u << g.base : 0u;
   for (int x = threadIdx.x; x < T + 2; x += blockDim.x) hub_row[x] = 0;
   __syncthreads();
@@ -702,7 +782,8 @@ __global__ __launch_bounds__(16 * kWave) __attribute__((amdgpu_waves_per_eu(size
         }
       }
       if (lane == kWave - 1) {
-        g.tile_cnt[tile] = make_uint2(incl, in_hubs);
+        if (SELF) hub_row[T + 1] = in_hubs;  // (no base row has this number)
+        else g.tile_cnt[tile] = make_uint2(incl, in_hubs);
         shared_of[t] = incl;
       }
       uint32_t to = lane * R - (incl - cnt);
@@ -740,7 +821,33 @@ __global__ __launch_bounds__(16 * kWave) __attribute__((amdgpu_waves_per_eu(size
   // reported, so that what follows never writes past the sizes computed from these counts.
   __syncthreads();
   if (wave == 0 && lane < g.k) bad |= shared_of[lane] != shared_of[g.base];
-  if (bad) *g.bad = 1;
+  if constexpr (SELF) {
+    const bool any = __syncthreads_or(bad);
+    if (threadIdx.x == 0) g.tile_cnt[tile] = make_uint2(shared_of[g.base], hub_row[T + 1] | (any ? kBadTile : 0u));
+  } else {
+    if (bad) *g.bad = 1;
+  }
+}
+
+template <int T, int L, class K>
+__global__ __launch_bounds__(16 * kWave) __attribute__((amdgpu_waves_per_eu(sizeof(K) == 4 ? 8 : 6))) void k_mark(Snaps s, Tiles g, int32_t mid_max) {
+  mark_tile<T, L, K, false>(s, g, mid_max);
+}
+
+// The same with what k_prepare does, in one launch: a workgroup per tile, whose waves find its bounds (a search by 32 lanes
+// per bound: three or four round trips for the row, one to three for the column), then workgroups of as many threads
+// for 256 rows per 256 threads.  For small frames (build_overlap), whose tiles are all under way at once: with more, the
+// searches add to the time for which a tile takes up its place.
+template <int T, int L>
+__global__ __launch_bounds__(16 * kWave) __attribute__((amdgpu_waves_per_eu(8))) void k_prepare_mark(Snaps s, Tiles g, int32_t mid_max, RowClasses rc,
+                                                                                                     float *dinv, float *dinv_nk) {
+  if ((int32_t)blockIdx.x < g.ntiles) {
+    mark_tile<T, L, uint32_t, true>(s, g, mid_max);
+    return;
+  }
+  const int blocks = blockDim.x / kBlock, sub = threadIdx.x / kBlock;
+  if (sub >= blocks) return;  // (a whole wave: the number of threads need not divide)
+  prepare_rows(s, g, rc, (int64_t)((int32_t)blockIdx.x - g.ntiles) * blocks + sub, dinv, dinv_nk);
 }
 
 // ---- scan over the tiles and the row blocks -----------------------------------------------------
@@ -993,14 +1100,20 @@ __device__ inline int32_t hub_common_before(const Tiles &g, int32_t nnz, int32_t
   return (int32_t)(v + (uint32_t)__popcll(g.bits[w] & g.hub_bits[w] & ((1ull << (e & 63)) - 1ull)));
 }
 
-// Sums of up to 256 row blocks' counts, in front of block `upto` and of all, for every thread.
+// Sums of a few row blocks' counts, in front of block `upto` and of all, for every thread.
 __device__ inline void sum_row_counts(const RowCounts *cnt, int32_t blocks, int32_t upto, RowCounts *front, RowCounts *all) {
   __shared__ uint32_t sums[2][kRowSums][kWavesPerBlock];
-  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, b = threadIdx.x;
-  const RowCounts c = cnt[min(b, max(blocks - 1, 0))];
-  uint32_t v[2][kRowSums];
-  split_counts(c, b < min(upto, blocks), v[0]);
-  split_counts(c, b < blocks, v[1]);
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  uint32_t v[2][kRowSums] = {};
+  for (int b = threadIdx.x; b < blocks; b += kBlock) {
+    uint32_t c[kRowSums];
+    split_counts(cnt[b], true, c);
+#pragma unroll
+    for (int x = 0; x < kRowSums; ++x) {
+      v[0][x] += b < upto ? c[x] : 0u;
+      v[1][x] += c[x];
+    }
+  }
 #pragma unroll
   for (int u = 0; u < 2; ++u)
 #pragma unroll
@@ -1022,27 +1135,44 @@ __device__ inline void sum_row_counts(const RowCounts *cnt, int32_t blocks, int3
   *all = join_counts(none, v[1]);
 }
 
-// Up to so many tiles k_rows adds up itself, from LDS: 2^19 base entries.
-constexpr int kSumTiles = 4 * kBlock;
+// Up to so many tiles k_rows_scatter adds up itself (2^20 base entries), and so many row blocks (262,144 rows).
+constexpr int kTilesEach = 8;  // per thread
+constexpr int kSumTiles = kTilesEach * kBlock;
+constexpr int kSumRowBlocks = 4 * kBlock;
 
-// What lies in front of every tile, and of all of them, into `pre`.
-__device__ inline void sum_tiles(const Tiles &g, uint2 *pre) {
-  __shared__ uint32_t front[2][kWavesPerBlock];
-  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, t0 = 4 * (int)threadIdx.x;
-  uint32_t c[2][4] = {};
+// The counts of tiles kTilesEach * threadIdx.x and those behind it, without the flags; returns whether a flag is set.
+__device__ __forceinline__ bool load_tiles(const Tiles &g, uint32_t (&c)[2][kTilesEach]) {
+  const int t0 = kTilesEach * (int)threadIdx.x;
+  uint32_t flags = 0;
 #pragma unroll
-  for (int q = 0; q < 4; q += 2)
+  for (int q = 0; q < kTilesEach; ++q) c[0][q] = c[1][q] = 0;
+#pragma unroll
+  for (int q = 0; q < kTilesEach; q += 2)
     if (t0 + q < g.ntiles) {
       const uint4 x = *reinterpret_cast<const uint4 *>(g.tile_cnt + t0 + q);  // (padded to a pair)
+      const bool both = t0 + q + 1 < g.ntiles;
       c[0][q] = x.x;
-      c[1][q] = x.y;
-      c[0][q + 1] = t0 + q + 1 < g.ntiles ? x.z : 0u;
-      c[1][q + 1] = t0 + q + 1 < g.ntiles ? x.w : 0u;
+      c[1][q] = x.y & (kBadTile - 1u);
+      c[0][q + 1] = both ? x.z : 0u;
+      c[1][q + 1] = both ? x.w & (kBadTile - 1u) : 0u;
+      flags |= x.y | (both ? x.w : 0u);
     }
+  return (flags & kBadTile) != 0;
+}
+
+// What lies in front of every tile, and of all of them, into `pre`; returns whether a tile's flag is set.
+__device__ inline bool sum_tiles(const Tiles &g, uint2 *pre) {
+  __shared__ uint32_t front[2][kWavesPerBlock];
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, t0 = kTilesEach * (int)threadIdx.x;
+  uint32_t c[2][kTilesEach];
+  const bool bad = load_tiles(g, c);
   uint32_t at[2];
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
-    const uint32_t mine = c[u][0] + c[u][1] + c[u][2] + c[u][3], incl = wave_sum(mine);
+    uint32_t mine = 0;
+#pragma unroll
+    for (int q = 0; q < kTilesEach; ++q) mine += c[u][q];
+    const uint32_t incl = wave_sum(mine);
     if (lane == kWave - 1) front[u][wave] = incl;
     at[u] = incl - mine;
   }
@@ -1052,13 +1182,38 @@ __device__ inline void sum_tiles(const Tiles &g, uint2 *pre) {
     at[1] += front[1][w];
   }
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
+  for (int q = 0; q < kTilesEach; ++q) {
     if (t0 + q < g.ntiles) pre[t0 + q] = make_uint2(at[0], at[1]);
     at[0] += c[0][q];
     at[1] += c[1][q];
   }
   if (threadIdx.x == kBlock - 1) pre[g.ntiles] = make_uint2(at[0], at[1]);
+  return __syncthreads_or(bad);
+}
+
+// Common entries in front of tile `upto` (the same for the workgroup), for every thread; `bad`: a tile's flag is set.
+__device__ inline uint32_t sum_tiles_before(const Tiles &g, int32_t upto, bool *bad) {
+  __shared__ uint32_t front[kWavesPerBlock], flag[kWavesPerBlock];
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, t0 = kTilesEach * (int)threadIdx.x;
+  uint32_t c[2][kTilesEach], mine = 0;
+  const bool here = load_tiles(g, c);
+#pragma unroll
+  for (int q = 0; q < kTilesEach; ++q) mine += t0 + q < upto ? c[0][q] : 0u;
+  const uint32_t incl = wave_sum(mine);
+  const uint64_t any = __ballot(here);
+  if (lane == kWave - 1) {
+    front[wave] = incl;
+    flag[wave] = any != 0;
+  }
   __syncthreads();
+  uint32_t sum = 0, flags = 0;
+#pragma unroll
+  for (int w = 0; w < kWavesPerBlock; ++w) {
+    sum += front[w];
+    flags |= flag[w];
+  }
+  *bad = flags != 0;
+  return sum;
 }
 
 struct RowArgs {
@@ -1070,10 +1225,9 @@ struct RowArgs {
 // longest row a class is decided by is the longest input row (its common entries are in all of
 // them).
 // SUM: neither the tiles' counts nor the row blocks' are summed up yet; they are few enough for every
-// workgroup to do that (a launch less, and the host gets the sizes as early: whole steps and slides, N = 2k ..
-// 60k, 62 .. 78 -> 59 .. 74 us).
+// workgroup to do that (k_rows_scatter).
 template <bool SUM>
-__global__ __launch_bounds__(kBlock) void k_rows(Snaps s, Tiles g, RowArgs o, ListArgs q, FrameTotals *out, uint32_t seq) {
+__device__ __forceinline__ void make_rows(const Snaps &s, Tiles g, const RowArgs &o, const ListArgs &q, FrameTotals *out, uint32_t seq) {
   const int64_t i64 = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   const int32_t i = (int32_t)min(i64, (int64_t)g.n), i1 = min(i + 1, g.n);
   const bool live = i64 < g.n;
@@ -1084,11 +1238,10 @@ __global__ __launch_bounds__(kBlock) void k_rows(Snaps s, Tiles g, RowArgs o, Li
   if constexpr (SUM) {
     __shared__ uint2 pre[kSumTiles + 1];
     sum_row_counts(g.row_cnt, (int32_t)(((int64_t)g.n + kBlock - 1) / kBlock), (int32_t)blockIdx.x, &first, &total);
-    sum_tiles(g, pre);
-    if (blockIdx.x == 0) {
+    const bool bad = sum_tiles(g, pre);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
       const uint2 all = pre[g.ntiles];
-      if (threadIdx.x == 0) send_totals(total, all.x, all.y, total.entries - (uint64_t)g.k * all.y, *g.bad, out, seq);
-      for (int t = threadIdx.x; t <= g.ntiles; t += kBlock) g.tile_pre[t] = pre[t];
+      send_totals(total, all.x, all.y, total.entries - (uint64_t)g.k * all.y, bad, out, seq);
     }
     g.tile_pre = pre;
   } else {
@@ -1127,6 +1280,10 @@ __global__ __launch_bounds__(kBlock) void k_rows(Snaps s, Tiles g, RowArgs o, Li
     *c0 = hub_common_before(g, nnz0, ea);
     *d0 = (int32_t)((int64_t)entries - (int64_t)g.k * *c0);
   });
+}
+
+__global__ __launch_bounds__(kBlock) void k_rows(Snaps s, Tiles g, RowArgs o, ListArgs q) {
+  make_rows<false>(s, g, o, q, nullptr, 0);
 }
 
 // The same for a frame whose row pointers are in place (the transposed frame): the counts, then the
@@ -1454,19 +1611,15 @@ __device__ inline uint64_t lane_word(uint64_t x, int l) {
 
 // KV > 0: a node's k scales lie in KV 16-byte pieces, read together (FULL: k == 4 * KV); KV == 0: k <= 2 or
 // k > 16, one by one.
-template <int KV, bool FULL, int TILES>
-__global__ __launch_bounds__(kBlock) void k_scatter(Snaps s, Tiles g, OutParts o, const float *dinv,
-                                                     const float *dinv_nk) {
+// common(x): common entries in front of tile x.
+template <int KV, bool FULL, int TILES, class Common>
+__device__ __forceinline__ void scatter_tiles(const Snaps &s, const Tiles &g, const OutParts &o, const float *dinv,
+                                              const float *dinv_nk, int part, int32_t tile0, Common common) {
   constexpr int WPT = kWave / TILES;  // words of a tile a wave takes at once
   const int lane = threadIdx.x % kWave;
-  const int part = blockIdx.y;
-  const int64_t group = (int64_t)blockIdx.x * kWavesPerBlock + threadIdx.x / kWave;
-  const int64_t tile64 = group * TILES;
-  if (tile64 >= g.ntiles) return;
-  const int32_t tile0 = __builtin_amdgcn_readfirstlane((int32_t)tile64);
   const int t = part == 0 ? g.base : part - 1;
   const int32_t *bound = g.bound + t * ((int64_t)g.ntiles + 1);
-  const int32_t c0 = (int32_t)g.tile_pre[tile0].x;
+  const int32_t c0 = (int32_t)common(tile0);
   const int32_t tile = tile0 + lane / WPT, j = lane % WPT;
   int32_t e0 = 0, len = 0;
   if (part == 0 && tile < g.ntiles) {
@@ -1554,7 +1707,7 @@ __global__ __launch_bounds__(kBlock) void k_scatter(Snaps s, Tiles g, OutParts o
     const int32_t x = min(tile0 + q, g.ntiles), y = min(x + 1, g.ntiles);
     const int32_t start = bound[x];
     from[q] = start - total;  // input place of an output place of this piece, minus the latter
-    total += (bound[y] - start) - (int32_t)(g.tile_pre[y].x - g.tile_pre[x].x);
+    total += (bound[y] - start) - (int32_t)(common(y) - common(x));
     upto[q] = total;
   }
   const int32_t *excl = g.excl[t];
@@ -1582,6 +1735,46 @@ __global__ __launch_bounds__(kBlock) void k_scatter(Snaps s, Tiles g, OutParts o
         out_w[j0 + r * kWave] = d[r];
       }
   }
+}
+
+template <int KV, bool FULL, int TILES>
+__global__ __launch_bounds__(kBlock) void k_scatter(Snaps s, Tiles g, OutParts o, const float *dinv,
+                                                     const float *dinv_nk) {
+  const int64_t tile64 = ((int64_t)blockIdx.x * kWavesPerBlock + threadIdx.x / kWave) * TILES;
+  if (tile64 >= g.ntiles) return;
+  scatter_tiles<KV, FULL, TILES>(s, g, o, dinv, dinv_nk, (int)blockIdx.y, __builtin_amdgcn_readfirstlane((int32_t)tile64),
+                                 [&](int32_t x) __attribute__((always_inline)) { return g.tile_pre[x].x; });
+}
+
+// Rows and entries of small frames in one launch behind k_prepare_mark: `row_wgs` workgroups make the rows (the first of them
+// sends the sizes to the host), those behind them write the entries, a wave per tile and part.  The outputs have room
+// for as many entries as the parts can have, so that nothing waits for the host; where a tile's flag says that the
+// snapshots are not canonical, no entries are written.
+template <int KV, bool FULL>
+__global__ __launch_bounds__(kBlock) void k_rows_scatter(Snaps s, Tiles g, RowArgs r, ListArgs q, OutParts o, int32_t row_wgs,
+                                                         const float *dinv, const float *dinv_nk, FrameTotals *out, uint32_t seq) {
+  if ((int32_t)blockIdx.x < row_wgs) {
+    make_rows<true>(s, g, r, q, out, seq);
+    return;
+  }
+  const int32_t groups = (g.ntiles + kWavesPerBlock - 1) / kWavesPerBlock, b = (int32_t)blockIdx.x - row_wgs;
+  const int part = b / groups;
+  const int32_t first = (b - part * groups) * kWavesPerBlock, tile0 = first + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  uint32_t mine[kWavesPerBlock];  // of the workgroup's tiles
+#pragma unroll
+  for (int w = 0; w < kWavesPerBlock; ++w) mine[w] = g.tile_cnt[min(first + w, g.ntiles - 1)].x;
+  bool bad;
+  uint32_t front = sum_tiles_before(g, first, &bad);
+  if (bad || tile0 >= g.ntiles) return;
+  uint32_t here = mine[0];
+#pragma unroll
+  for (int w = 1; w < kWavesPerBlock; ++w)
+    if (tile0 >= first + w) {
+      front += mine[w - 1];
+      here = mine[w];
+    }
+  scatter_tiles<KV, FULL, 1>(s, g, o, dinv, dinv_nk, part, tile0,
+                             [&](int32_t x) __attribute__((always_inline)) { return x == tile0 ? front : front + here; });
 }
 
 }  // namespace
@@ -1720,7 +1913,7 @@ int launch_list_rows(const pipad_frame *f, RowCounts *cnt, RowCounts *pre, const
   for (int t = 0; t < f->k; ++t) p.rowptr[1 + t] = f->rowptr_d[t];
   const dim3 blocks = grid1(f->n, kBlock);
   hipLaunchKernelGGL(k_count_rows, blocks, dim3(kBlock), 0, st, p, f->n, f->k, row_classes(f), cnt);
-  const bool sum = blocks.x <= kBlock;
+  const bool sum = blocks.x <= kSumRowBlocks;
   if (!sum)
     hipLaunchKernelGGL(k_scan_row_counts, dim3(1), dim3(kTileScanBlock), 0, st, cnt, pre, (int64_t)blocks.x,
                        ticket.where, ticket.seq);
@@ -1879,12 +2072,33 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
   g.tile_log2 = k <= 16 ? 9 : 8;
   g.ntiles = (int32_t)(((int64_t)s.nnz[base] + (1 << g.tile_log2) - 1) >> g.tile_log2);
 
+  const int64_t row_blocks = ((int64_t)n + kBlock - 1) / kBlock;
+  // Small frames take two launches instead of four (or five, with the sums in a launch of their own), and get room for as
+  // many entries as the parts can have (the overlap part at most those of the smallest snapshot, an exclusive part its
+  // snapshot's: 120 MB at most for all) together with what is sized up front, so that nothing waits for the host before
+  // it has the sizes.  Whole steps and slides: N = 2k, k = 4 55 -> 48 us, N = 20k, k = 4 59 -> 50, N = 1k .. 60k 60 to 80 ->
+  // 50 to 70; R-MAT 74k, k = 2 93 -> 78, Chung-Lu 125k, k = 1 62 -> 56.  Up to 2048 tiles and 20000 waves of k_prepare_mark, of
+  // which 8192 run together: N = 107k, k = 8 with 2000 tiles 190 -> 186, N = 45k, k = 12 with 1520 181 -> 178, but N = 113k,
+  // k = 16 with 1590 180 -> 187; with 3000 to 4000 tiles and k = 2 .. 6 3 to 13 % slower.
+  const bool small = g.ntiles <= kSumTiles && row_blocks <= kSumRowBlocks && (int64_t)g.ntiles * k <= 20000;
+  int32_t most_common = s.nnz[0];
+  for (int t = 1; t < k; ++t) most_common = std::min(most_common, s.nnz[t]);
+
   Arena keep1;
   keep1.want(&f->rowptr_c, (size_t)n + 1);
   for (int t = 0; t < k; ++t) keep1.want(&f->rowptr_d[t], (size_t)n + 1);
   keep1.want(&f->dinv, (size_t)k * n);
   keep1.want(&f->dinv_nk, (size_t)node_stride(k) * n);
   want_lists(keep1, f, entries);
+  auto want_parts = [&](Arena &a, int32_t common, const int32_t *exclusive) {
+    a.want(&f->col_c, (size_t)common);
+    for (int t = 0; t < k; ++t) {
+      a.want(&f->col_d[t], (size_t)exclusive[t]);
+      a.want(&f->wc[t], (size_t)common);
+      a.want(&f->wd[t], (size_t)exclusive[t]);
+    }
+  };
+  if (small) want_parts(keep1, most_common, s.nnz);
   {
     void *base_ptr = A.get(keep1.total);
     if (!base_ptr) return fail(PIPAD_ERR_ALLOC);
@@ -1899,12 +2113,12 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
   tmp.want(&g.bits, base_words);
   tmp.want(&g.hub_bits, base_words);
   tmp.want(&g.wpre, base_words);
-  tmp.want(&g.brow, (size_t)g.ntiles + 1);
+  tmp.want(&g.brow, small ? 0 : (size_t)g.ntiles + 1);
   tmp.want(&g.bound, ((size_t)g.ntiles + 1) * k);
   tmp.want(&g.tile_cnt, (size_t)g.ntiles + 1);  // (read two at a time)
-  tmp.want(&g.tile_pre, (size_t)g.ntiles + 1);
+  tmp.want(&g.tile_pre, small ? 0 : (size_t)g.ntiles + 1);
   tmp.want(&g.row_cnt, row_count_slots(n));
-  tmp.want(&g.row_pre, row_count_slots(n));
+  tmp.want(&g.row_pre, small ? 0 : row_count_slots(n));
   tmp.want(&g.bad, 1);
   tmp.want(&totals, 1);
   tmp.want(&dflags, (size_t)64);
@@ -1938,22 +2152,51 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
     if (bad) return fail(PIPAD_ERR_BAD_CSR);
   }
 
-  const int32_t bound_blocks = (int32_t)(((int64_t)g.ntiles + 1 + kWavesPerBlock * 8 - 1) / (kWavesPerBlock * 8));
-  const int64_t row_blocks = ((int64_t)n + kBlock - 1) / kBlock;
-  hipLaunchKernelGGL(k_prepare, dim3((unsigned)(bound_blocks + row_blocks)), dim3(kBlock), 0, st, s, g, row_classes(f),
-                     bound_blocks, f->dinv, f->dinv_nk);
-  if (g.ntiles > 0) {
-    const int cap = k <= 16 ? Mark<512>::kCap : Mark<256>::kCap, waves = k <= 16 ? k : (k + 1) / 2;
-    // (514 rows and the like times 2n + 2 columns have to fit a 32-bit key)
-    const bool large = n >= 0x7fffffff / ((k <= 16 ? 512 : 256) + 2);
-    auto mark = k <= 16 ? (large ? k_mark<512, 1, uint64_t> : k_mark<512, 1, uint32_t>)
-                        : (large ? k_mark<256, 2, uint64_t> : k_mark<256, 2, uint32_t>);
-    hipLaunchKernelGGL(mark, dim3((unsigned)g.ntiles), dim3((unsigned)(waves * kWave)), (size_t)k * cap * sizeof(uint32_t),
-                       st, s, g, f->plain_units ? INT32_MAX : f->mid_max);  // (the classes' copies hold the hub rows' scales)
-  }
+  // (514 rows and the like times 2n + 2 columns have to fit a 32-bit key)
+  const bool large = n >= 0x7fffffff / ((k <= 16 ? 512 : 256) + 2);
+  const int cap = k <= 16 ? Mark<512>::kCap : Mark<256>::kCap, waves = k <= 16 ? k : (k + 1) / 2;
+  const size_t mark_lds = (size_t)k * cap * sizeof(uint32_t);
+  const int32_t hub_min = f->plain_units ? INT32_MAX : f->mid_max;  // (the classes' copies hold the hub rows' scales)
+  RowArgs rows;
+  std::memset(&rows, 0, sizeof(rows));
+  rows.rowptr_c = f->rowptr_c;
+  for (int t = 0; t < k; ++t) rows.rowptr_d[t] = f->rowptr_d[t];
+  auto out_parts = [&]() {
+    OutParts o;
+    std::memset(&o, 0, sizeof(o));
+    o.col[0] = f->col_c;
+    for (int t = 0; t < k; ++t) {
+      o.col[1 + t] = f->col_d[t];
+      o.wc[t] = f->wc[t];
+      o.wd[t] = f->wd[t];
+    }
+    return o;
+  };
+  const int kv = k <= 2 || k > 16 ? 0 : node_stride(k) / 2 - (k % 4 ? 1 : 0);  // the instance for k snapshots
   const TotalsTicket ticket = expect_totals(totals);
-  const bool sum = g.ntiles <= kSumTiles && row_blocks <= kBlock;
-  if (!sum) {
+  if (small) {
+    const int threads = std::max(waves * kWave, kBlock);
+    const int64_t row_wgs = (row_blocks + threads / kBlock - 1) / (threads / kBlock);
+    if (n > 0)
+      hipLaunchKernelGGL((k <= 16 ? k_prepare_mark<512, 1> : k_prepare_mark<256, 2>), dim3((unsigned)(g.ntiles + row_wgs)),
+                         dim3((unsigned)threads), mark_lds, st, s, g, hub_min, row_classes(f), f->dinv, f->dinv_nk);
+    using RowsScatter = void (*)(Snaps, Tiles, RowArgs, ListArgs, OutParts, int32_t, const float *, const float *, FrameTotals *, uint32_t);
+    static const RowsScatter kernels[9] = {k_rows_scatter<0, false>, k_rows_scatter<1, false>, k_rows_scatter<1, true>,
+                                           k_rows_scatter<2, false>, k_rows_scatter<2, true>, k_rows_scatter<3, false>,
+                                           k_rows_scatter<3, true>, k_rows_scatter<4, false>, k_rows_scatter<4, true>};
+    const int32_t row_groups = (int32_t)grid1((int64_t)n + 1, kBlock).x;
+    const int32_t tile_groups = (int32_t)grid1(g.ntiles, kWavesPerBlock).x;
+    hipLaunchKernelGGL(kernels[kv], dim3((unsigned)(row_groups + tile_groups * (k + 1))), dim3(kBlock), 0, st, s, g, rows,
+                       list_args(f), out_parts(), row_groups, f->dinv, f->dinv_nk, ticket.where, ticket.seq);
+  } else {
+    const int32_t bound_blocks = (int32_t)(((int64_t)g.ntiles + 1 + kWavesPerBlock * 8 - 1) / (kWavesPerBlock * 8));
+    hipLaunchKernelGGL(k_prepare, dim3((unsigned)(bound_blocks + row_blocks)), dim3(kBlock), 0, st, s, g, row_classes(f),
+                       bound_blocks, f->dinv, f->dinv_nk);
+    if (g.ntiles > 0) {
+      auto mark = k <= 16 ? (large ? k_mark<512, 1, uint64_t> : k_mark<512, 1, uint32_t>)
+                          : (large ? k_mark<256, 2, uint64_t> : k_mark<256, 2, uint32_t>);
+      hipLaunchKernelGGL(mark, dim3((unsigned)g.ntiles), dim3((unsigned)(waves * kWave)), mark_lds, st, s, g, hub_min);
+    }
     ScanArgs a;
     a.tile_cnt = g.tile_cnt;
     a.tile_pre = g.tile_pre;
@@ -1969,18 +2212,12 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
     a.tiles_per_block = (int32_t)std::min<int64_t>((runs + blocks - 1) / blocks * kTileScanRun, 1 << 30);
     a.rows_per_block = (row_runs + blocks - 1) / blocks * kTileScanBlock;
     hipLaunchKernelGGL(k_scan_counts, dim3((unsigned)blocks), dim3(kTileScanBlock), 0, st, a, ticket.where, ticket.seq);
-  }
-  {
-    RowArgs o;
-    std::memset(&o, 0, sizeof(o));
-    o.rowptr_c = f->rowptr_c;
-    for (int t = 0; t < k; ++t) o.rowptr_d[t] = f->rowptr_d[t];
-    hipLaunchKernelGGL(sum ? k_rows<true> : k_rows<false>, grid1((int64_t)n + 1, kBlock), dim3(kBlock), 0, st, s, g, o,
-                       list_args(f), ticket.where, ticket.seq);
+    hipLaunchKernelGGL(k_rows, grid1((int64_t)n + 1, kBlock), dim3(kBlock), 0, st, s, g, rows, list_args(f));
   }
   PIPAD_TRY(hipGetLastError());
 
-  // ---- the one host synchronisation: sizes of the data-dependent outputs (k_rows runs meanwhile)
+  // ---- the one host synchronisation: sizes of the data-dependent outputs (k_rows, or what is left of
+  // k_rows_scatter, runs meanwhile)
   FrameTotals v;
   {
     const int rc = wait_totals(ticket, st, &v);
@@ -1995,29 +2232,16 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
   }
 
   Arena keep2;
-  keep2.want(&f->col_c, (size_t)f->nnz_c);
-  for (int t = 0; t < k; ++t) {
-    keep2.want(&f->col_d[t], (size_t)f->nnz_d[t]);
-    keep2.want(&f->wc[t], (size_t)f->nnz_c);
-    keep2.want(&f->wd[t], (size_t)f->nnz_d[t]);
-  }
+  if (!small) want_parts(keep2, f->nnz_c, f->nnz_d);
   want_split(keep2, f);
-  {
+  if (!small || (f->n_items > 0 && !f->plain_units)) {
     void *base_ptr = A.get(keep2.total);
     if (!base_ptr) return fail(PIPAD_ERR_ALLOC);
     keep2.assign(base_ptr);
   }
-  if (g.ntiles > 0) {
-    OutParts o;
-    std::memset(&o, 0, sizeof(o));
-    o.col[0] = f->col_c;
-    for (int t = 0; t < k; ++t) {
-      o.col[1 + t] = f->col_d[t];
-      o.wc[t] = f->wc[t];
-      o.wd[t] = f->wd[t];
-    }
-    // A wave per tile has the shortest chain of dependent loads (20k-node frame: 9 us against 19 with
-    // four tiles per wave, 0.2M nodes: 65 against 74); with 8M entries and more per snapshot there
+  if (g.ntiles > 0 && !small) {
+    // A wave per tile has the shortest chain of dependent loads (0.2M nodes: 65 us against 74 with four
+    // tiles per wave); with 8M entries and more per snapshot there
     // are waves enough and fewer of them do better (1M nodes, 20M entries: 313 us against 339).
     const int per_wave = g.ntiles < 16384 ? 1 : 4;
     using Scatter = void (*)(Snaps, Tiles, OutParts, const float *, const float *);
@@ -2028,9 +2252,8 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
         {k_scatter<0, false, 4>, k_scatter<1, false, 4>, k_scatter<1, true, 4>, k_scatter<2, false, 4>,
          k_scatter<2, true, 4>, k_scatter<3, false, 4>, k_scatter<3, true, 4>, k_scatter<4, false, 4>,
          k_scatter<4, true, 4>}};
-    auto scatter = kernels[per_wave == 1 ? 0 : 1][k <= 2 || k > 16 ? 0 : node_stride(k) / 2 - (k % 4 ? 1 : 0)];
-    hipLaunchKernelGGL(scatter, grid1(g.ntiles, kWavesPerBlock * per_wave, k + 1), dim3(kBlock), 0, st, s, g, o, f->dinv,
-                       f->dinv_nk);
+    hipLaunchKernelGGL(kernels[per_wave == 1 ? 0 : 1][kv], grid1(g.ntiles, kWavesPerBlock * per_wave, k + 1), dim3(kBlock), 0, st,
+                       s, g, out_parts(), f->dinv, f->dinv_nk);
     PIPAD_TRY(hipGetLastError());
   }
   {

@@ -1,0 +1,40 @@
+"""Frames that are built in two launches (a tile finds its bounds itself, rows and entries are made in one kernel), at the
+edges of that form's range and of its searches."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+from test_gpu_build_tiles import csr  # noqa: E402
+from test_gpu_parity import pipad, run_case  # noqa: E402,F401
+
+
+# 2048 tiles of 512 entries, 262,144 rows and 20,000 waves are the last ones (k > 16: tiles of 256 entries)
+@pytest.mark.parametrize("n,tiles,over,k", [(3000, 2048, 0, 2), (3000, 2048, 1, 2), (262_144, 500, 0, 2), (262_145, 500, 0, 2),
+                                            (2000, 1250, 0, 16), (2000, 1250, 1, 16), (1500, 1176, 0, 17), (1500, 1176, 1, 17),
+                                            (700, 0, 1, 1), (300, 0, 0, 3)])
+def test_edges(pipad, n, tiles, over, k):  # noqa: F811
+    rng = np.random.default_rng(n + tiles + k)
+    entries = tiles * (512 if k <= 16 else 256) + over
+    keys = np.unique(rng.integers(0, n * n, 2 * entries + 4000))
+    keys = keys[keys // n != keys % n]
+    keys = np.sort(rng.permutation(keys)[:entries])
+    assert len(keys) == entries
+    pairs = np.stack([keys // n, keys % n], 1)
+    run_case(pipad, n, [csr(n, pairs)] + [csr(n, pairs[rng.random(len(pairs)) < 0.9]) for _ in range(k - 1)], 3, seed=k)
+
+
+# A tile starts in a long row; the other snapshot has so many entries of that row, all of them in front of the tile's first
+# column, or all behind it (the search looks at 32 places at a time).
+@pytest.mark.parametrize("behind", [False, True])
+@pytest.mark.parametrize("length", [0, 1, 31, 32, 33, 34, 65, 66, 99, 1055, 1056, 1088, 1089, 1090, 1122])
+def test_row_lengths(pipad, length, behind):  # noqa: F811
+    def row(i, first, count):
+        return np.stack([np.full(count, i), np.arange(first, first + count)], 1)
+
+    n = 6000
+    lead, rest = row(2, 700, 16), row(9, 100, 40)
+    base = np.concatenate([lead, row(5, 2500, 800), rest, row(11, 12, 600)])  # the second tile starts at (5, 2996)
+    other = np.concatenate([lead[::2], row(5, 3000 if behind else 2996 - length, length), rest[1::2]])
+    run_case(pipad, n, [csr(n, base), csr(n, other)], 4, seed=length)
