@@ -1,0 +1,59 @@
+"""Concatenated operands whose rows are multiplied by their scales first (k_scale_rows): lane layouts and strides, and the
+same bits where there is no room for the products."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+import oracle  # noqa: E402
+import synth  # noqa: E402
+from _util import check_y, csr_to_coo  # noqa: E402
+from test_gpu_aggregate_batches import power_law  # noqa: E402
+from test_gpu_parity import pipad, _reset_options  # noqa: E402,F401
+
+
+# frames just past the rule 3 k entries > 10^7 + k n (4 F + 1)
+@pytest.mark.parametrize("n,entries,k,F,pad,plain", [(6000, 260_000, 16, 1, 0, True), (6000, 700_000, 7, 2, 0, False), (6000, 1_000_000, 4, 3, 1, True),
+                                                     (6000, 1_100_000, 4, 4, 3, False), (6000, 1_400_000, 3, 3, 0, False),
+                                                     (6000, 300_000, 16, 5, 0, True), (6000, 700_000, 6, 8, 1, False),
+                                                     (6000, 700_000, 7, 13, 0, False), (6000, 1_950_000, 2, 31, 0, True)])
+def test_against_the_oracle_and_without_room(pipad, n, entries, k, F, pad, plain):  # noqa: F811
+    pipad.set_option("agg_coalescent", 2)
+    if not plain:  # hub rows by class, several units each
+        pipad.set_option("mid_max", 300)
+        pipad.set_option("hub_segment", 700)
+        pipad.set_option("hub_threshold", 700)
+    lists = power_law(n, entries // 2, k, F)
+    shared = min(len(c) for _, c in lists)
+    assert 3 * k * shared > 10_000_000 + k * n * (4 * F + 1)
+    snaps = [(torch.from_numpy(rp).cuda(), torch.from_numpy(c).cuda()) for rp, c in lists]
+    frame, fresh = pipad.frame_build_overlap(snaps), pipad.frame_build_overlap(snaps)
+    store = torch.zeros((n, k * F + pad), device="cuda:0")
+    X = [store[:, pad + t * F:pad + (t + 1) * F] for t in range(k)]
+    for t in range(k):
+        X[t].copy_(torch.from_numpy(synth.features(3, t, n, F)))
+    out = torch.full_like(store, float("nan"))
+    Y = [out[:, pad + t * F:pad + (t + 1) * F] for t in range(k)]
+    pipad.frame_aggregate(frame, X, Y)
+    want = out.clone()
+    for t in (0, k - 1):
+        _, yd, bound, _ = oracle.aggregate(n, *csr_to_coo(n, *lists[t]), synth.features(3, t, n, F), threads=8)
+        check_y(Y[t].cpu().numpy(), yd, bound, f"snapshot {t}")
+    out.fill_(float("nan"))
+    pipad.frame_aggregate(frame, X, Y, static_scratch=True)
+    assert torch.equal(out[:, pad:], want[:, pad:])
+    # recorded on a frame whose scratch holds the partial sums and no more
+    parts = [torch.zeros((n, F), device="cuda:0") for _ in range(k)]
+    pipad.frame_aggregate(fresh, parts, [torch.empty_like(p) for p in parts])
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        pipad.frame_aggregate(fresh, X, Y)
+    for _ in range(3):
+        out.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out[:, pad:], want[:, pad:])
+    frame.close()
+    fresh.close()
