@@ -1378,15 +1378,23 @@ __device__ __forceinline__ void store_scales(const SplitArgs &g, const int32_t (
           if (t + 3 < g.k) g.swc[t + 3][to[r]] = w[r].w;
         }
     }
+  } else if (g.k == 2) {
+    float2 w[UN];
+#pragma unroll
+    for (int r = 0; r < UN; ++r) w[r] = reinterpret_cast<const float2 *>(g.dinv_nk)[c[r]];
+#pragma unroll
+    for (int r = 0; r < UN; ++r)
+      if (live[r]) {
+        g.swc[0][to[r]] = w[r].x;
+        g.swc[1][to[r]] = w[r].y;
+      }
   } else {
-    for (int t = 0; t < g.k; ++t) {
-      float w[UN];
+    float w[UN];
 #pragma unroll
-      for (int r = 0; r < UN; ++r) w[r] = g.dinv_nk[(int64_t)c[r] * g.k + t];
+    for (int r = 0; r < UN; ++r) w[r] = g.dinv_nk[c[r]];
 #pragma unroll
-      for (int r = 0; r < UN; ++r)
-        if (live[r]) g.swc[t][to[r]] = w[r];
-    }
+    for (int r = 0; r < UN; ++r)
+      if (live[r]) g.swc[0][to[r]] = w[r];
   }
 }
 
@@ -1609,8 +1617,9 @@ __device__ inline uint64_t lane_word(uint64_t x, int l) {
          (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), l) << 32;
 }
 
-// KV > 0: a node's k scales lie in KV 16-byte pieces, read together (FULL: k == 4 * KV); KV == 0: k <= 2 or
-// k > 16, one by one.
+// KV > 0: a node's k scales lie in KV 16-byte pieces, read together (FULL: k == 4 * KV); KV == 0: k <= 2, read at once (500k-node
+// R-MAT frame, k = 2, 65 us one after the other, now 44; k_split_fill 31 and 25), or k > 16, a piece after the other (150k nodes,
+// k = 18, 353 us a scale after the other, now 277).
 // common(x): common entries in front of tile x.
 template <int KV, bool FULL, int TILES, class Common>
 __device__ __forceinline__ void scatter_tiles(const Snaps &s, const Tiles &g, const OutParts &o, const float *dinv,
@@ -1687,13 +1696,35 @@ __device__ __forceinline__ void scatter_tiles(const Snaps &s, const Tiles &g, co
 #pragma unroll
         for (int r = 0; r < UN; ++r)
           if (x[r] >> lane & 1ull) out[at[r]] = c[r];
-        for (int u = 0; u < g.k; ++u) {
-          float w[UN];
+        if (g.k > 2) {  // (more than 16)
+          const int32_t pieces = node_stride(g.k) / 4;
+          for (int q = 0; q < pieces; ++q) {
+            float4 w[UN];
 #pragma unroll
-          for (int r = 0; r < UN; ++r) w[r] = dinv_nk[(int64_t)c[r] * node_stride(g.k) + u];
+            for (int r = 0; r < UN; ++r) w[r] = reinterpret_cast<const float4 *>(dinv_nk)[(int64_t)c[r] * pieces + q];
+#pragma unroll
+            for (int r = 0; r < UN; ++r)
+              if (need[r] >> lane & 1ull) {
+                o.wc[4 * q][at[r]] = w[r].x;
+                if (4 * q + 1 < g.k) o.wc[4 * q + 1][at[r]] = w[r].y;
+                if (4 * q + 2 < g.k) o.wc[4 * q + 2][at[r]] = w[r].z;
+                if (4 * q + 3 < g.k) o.wc[4 * q + 3][at[r]] = w[r].w;
+              }
+          }
+        } else {
+          float2 w[UN];
+#pragma unroll
+          for (int r = 0; r < UN; ++r) {
+            const int32_t node = need[r] >> lane & 1ull ? c[r] : 0;
+            if (g.k == 2) w[r] = reinterpret_cast<const float2 *>(dinv_nk)[node];
+            else w[r].x = w[r].y = dinv_nk[node];
+          }
 #pragma unroll
           for (int r = 0; r < UN; ++r)
-            if (need[r] >> lane & 1ull) o.wc[u][at[r]] = w[r];
+            if (need[r] >> lane & 1ull) {
+              o.wc[0][at[r]] = w[r].x;
+              if (g.k == 2) o.wc[1][at[r]] = w[r].y;
+            }
         }
       }
     }

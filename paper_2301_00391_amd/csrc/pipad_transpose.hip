@@ -419,8 +419,8 @@ __device__ inline void fill_run(int32_t *rp, int32_t lo, int32_t hi, int32_t v, 
   }
 }
 
-// KV > 0: a node's k scales lie in KV 16-byte pieces, read together (FULL: k == 4 * KV); KV == 0: k <= 2 or
-// k > 16, one by one.
+// KV > 0: a node's k scales lie in KV 16-byte pieces, read together (FULL: k == 4 * KV); KV == 0: k <= 2, or k > 16, a piece after
+// the other.
 template <int KV, bool FULL>
 __global__ __launch_bounds__(kBlock) void k_finish_parts(FinishArgs g) {
   const int lane = threadIdx.x % kWave;
@@ -466,9 +466,22 @@ __global__ __launch_bounds__(kBlock) void k_finish_parts(FinishArgs g) {
         if (FULL || 4 * q + 2 < g.k) g.wc[4 * q + 2][e] = v[q].z;
         if (FULL || 4 * q + 3 < g.k) g.wc[4 * q + 3][e] = v[q].w;
       }
+    } else if (g.k > 2) {
+      const int32_t pieces = node_stride(g.k) / 4;
+      const float4 *row = reinterpret_cast<const float4 *>(g.dinv_nk) + (int64_t)c * pieces;
+      for (int q = 0; q < pieces; ++q) {
+        const float4 v = row[q];
+        g.wc[4 * q][e] = v.x;
+        if (4 * q + 1 < g.k) g.wc[4 * q + 1][e] = v.y;
+        if (4 * q + 2 < g.k) g.wc[4 * q + 2][e] = v.z;
+        if (4 * q + 3 < g.k) g.wc[4 * q + 3][e] = v.w;
+      }
+    } else if (g.k == 2) {
+      const float2 v = reinterpret_cast<const float2 *>(g.dinv_nk)[c];
+      g.wc[0][e] = v.x;
+      g.wc[1][e] = v.y;
     } else {
-      const float *row = g.dinv_nk + (int64_t)c * node_stride(g.k);
-      for (int t = 0; t < g.k; ++t) g.wc[t][e] = row[t];
+      g.wc[0][e] = g.dinv_nk[c];
     }
   } else {
     g.wd[p - 1][e] = g.dinv[(int64_t)(p - 1) * g.n + c];
