@@ -97,6 +97,7 @@ struct AggArgs {
   int32_t nt;         // non-temporal hints (bit 0: Y stores, bit 1: index streams)
   int32_t sg;         // coalescent kernel: snapshots per lane team (slices are snapshot groups)
   int32_t products;   // ... the sums are those of kTable
+  int32_t longest_first;  // ... a wave's short rows in order of their common entries where those differ a lot
   int32_t whole_units;  // coalescent kernel: one partial sum per hub unit, not one per class part
   int32_t plain;        // hub units are walked by a workgroup each, from the lists of the parts (nclass is 1 then)
   int32_t direct;       // ... and every hub row is one unit: the row is finished there, no partial sums
@@ -590,6 +591,39 @@ __device__ __forceinline__ float *partial_slot(const AggArgs &a, int slice_seq, 
   return a.partial + (((int64_t)slice_seq * a.nvp + slot) << a.ls_log2) * vec + fl * vec;
 }
 
+// Short rows: as many as there are lane teams are walked side by side and a step lasts as long as its longest
+// row.  Where the lengths within a batch differ a lot (skewed graphs: the longest row takes more
+// than 1.5 times the mean number of gather rounds plus one) the wave takes its rows in order of
+// decreasing work: a stable 5-bit radix sort over the lanes, ballots and one cross-lane move per
+// bit.  Returns the index within the batch of the row taken as number `lane`; which rows a wave
+// works on does not change.  Not for batches of similar rows, where the natural order keeps the
+// rows of a step next to each other in memory (R-MAT frames, k = 8, F = 64: N = 200k 610 -> 585 us,
+// 1M 3926 -> 3865; Chung-Lu frames, where it is not triggered, 1 % slower when applied regardless).
+__device__ __forceinline__ int longest_first(int rounds, int rows_here, int lane) {
+  int order = lane;
+#ifndef PIPAD_NO_ROW_ORDER
+  int mx = rounds, sm = rounds;
+#pragma unroll
+  for (int m = kWave >> 1; m >= 1; m >>= 1) {
+    mx = max(mx, __shfl_xor(mx, m, kWave));
+    sm += __shfl_xor(sm, m, kWave);
+  }
+  if (2 * mx * rows_here > PIPAD_ROW_ORDER_A * sm + PIPAD_ROW_ORDER_B * rows_here) {  // wave-uniform
+    int packed = (min(rounds, 31) << 8) | lane;
+#pragma unroll
+    for (int bit = 8; bit < 13; ++bit) {
+      const bool one = (packed >> bit) & 1;
+      const uint64_t ones = __ballot(one);
+      const int below = __builtin_amdgcn_mbcnt_hi((uint32_t)(ones >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)ones, 0));
+      const int dest = one ? below : __popcll(ones) + (lane - below);
+      packed = __builtin_amdgcn_ds_permute(dest << 2, packed);
+    }
+    order = packed & 0xff;
+  }
+#endif
+  return order;
+}
+
 #ifndef PIPAD_AGG_DEPTH
 #define PIPAD_AGG_DEPTH 4  // row gathers in flight per lane
 #endif
@@ -799,40 +833,9 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
       mdi = s.dv[r];
     }
   }
-  // Short rows: nteams rows are walked side by side and a step lasts as long as its longest
-  // row.  Where the lengths within a batch differ a lot (skewed graphs: the longest row takes more
-  // than 1.5 times the mean number of gather rounds plus one) the wave takes its rows in order of
-  // decreasing work: a stable 5-bit radix sort over the lanes, ballots and one cross-lane move per
-  // bit.  order = index within the batch of the row taken as number `lane`; which rows a wave
-  // works on does not change.  Not for slices narrower than a cache line, where neighbouring
-  // rows share lines, and not for batches of similar rows, where the natural order keeps the
-  // rows of a step next to each other in memory (R-MAT frames, k = 8, F = 64: N = 200k 610 -> 585 us,
-  // 1M 3926 -> 3865; Chung-Lu frames, where it is not triggered, 1 % slower when applied regardless).
   int order = lane;
-#ifndef PIPAD_NO_ROW_ORDER
-  if (!wide && ((VEC * 4) << a.ls_log2) >= 128) {
-    constexpr int gpl = U;  // entries a lane group gathers per round
-    const int rounds = lane < rows_here ? (mc1 - mc0 + md1 - md0 + gpl - 1) / gpl : 0;
-    int mx = rounds, sm = rounds;
-#pragma unroll
-    for (int m = kWave >> 1; m >= 1; m >>= 1) {
-      mx = max(mx, __shfl_xor(mx, m, kWave));
-      sm += __shfl_xor(sm, m, kWave);
-    }
-    if (2 * mx * rows_here > PIPAD_ROW_ORDER_A * sm + PIPAD_ROW_ORDER_B * rows_here) {  // wave-uniform
-      int packed = (min(rounds, 31) << 8) | lane;
-#pragma unroll
-      for (int bit = 8; bit < 13; ++bit) {
-        const bool one = (packed >> bit) & 1;
-        const uint64_t ones = __ballot(one);
-        const int below = __builtin_amdgcn_mbcnt_hi((uint32_t)(ones >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)ones, 0));
-        const int dest = one ? below : __popcll(ones) + (lane - below);
-        packed = __builtin_amdgcn_ds_permute(dest << 2, packed);
-      }
-      order = packed & 0xff;
-    }
-  }
-#endif
+  if (!wide && ((VEC * 4) << a.ls_log2) >= 128)  // (not for slices narrower than a cache line, where neighbouring rows share lines)
+    order = longest_first(lane < rows_here ? (mc1 - mc0 + md1 - md0 + U - 1) / U : 0, rows_here, lane);
   const int per_step = wide ? 1 : nteams;          // elements worked on side by side
   const int team_base = wide ? 0 : team << a.ls_log2;
   const int team_lanes = wide ? kWave : ls;
@@ -1302,6 +1305,9 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_coalescent(const AggArgs a
     mc0 = pc[0];
     mc1 = pc[split ? n_items : 1];
   }
+  int order = lane;
+  if (!wide && a.longest_first && batch > nteams)
+    order = longest_first(lane < rows_here ? (mc1 - mc0 + U - 1) / U : 0, rows_here, lane);  // (by the common entries)
   const int per_step = wide ? 1 : nteams;
   const int team_lanes = wide ? nteams * fetchers : fetchers;
   const int q = (wide ? team * fetchers : 0) + ((fl - u * lps) & (fetchers - 1));
@@ -1312,7 +1318,7 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_coalescent(const AggArgs a
     CoalItem it;
     const int li = step * per_step + (wide ? 0 : team);
     const bool have = li < rows_here;
-    const int src = have ? li : 0;
+    const int src = __shfl(order, have ? li : 0, kWave);
     it.i = __shfl(r, src, kWave);
     it.cs = __shfl(mc0, src, kWave);
     it.clen = __shfl(mc1, src, kWave) - it.cs;
@@ -1740,6 +1746,11 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
       a.ls_log2 = lanes_log2;  // lanes per team (<= 64)
     }
     a.fchunks = 1;
+    // Short rows longest first where the common entries tell the lengths and rows are not narrow: 28 bytes of a team's row per
+    // entry of a snapshot's that is common.  R-MAT 1M, k = 8, F = 1 / 2 / 4 / 8 / 16 310 / 366 / 476 / 788 / 1540 -> 294 / 348 / 447 /
+    // 728 / 1444 us, 61k, k = 16, F = 3 68.7 -> 62, Chung-Lu 162k, k = 8, F = 3 92 -> 85; on the other side of it Chung-Lu 89k, k = 3,
+    // F = 2 34 -> 36.4, 150k, k = 8, F = 2, churn 0.3 71 -> 74.
+    a.longest_first = (int64_t)a.sg * F * 4 * f->nnz_c >= 28 * entries;
     // The gathered rows multiplied by their scales first (k_scale_rows), so that a walk only reads indices: one pass over the
     // operand against 4 bytes per entry and snapshot, of which an instruction of the walk touched up to 64 lines.  Measured,
     // that saves 1.5 us per million entries of all snapshots, whatever F is, and the pass takes 5 us and its bytes at 4.4 TB/s:

@@ -57,3 +57,18 @@ def test_against_the_oracle_and_without_room(pipad, n, entries, k, F, pad, plain
         assert torch.equal(out[:, pad:], want[:, pad:])
     frame.close()
     fresh.close()
+
+
+@pytest.mark.parametrize("k,F,products", [(16, 1, False), (16, 2, False), (16, 4, False), (16, 2, True)])
+def test_short_rows_longest_first(pipad, k, F, products):  # noqa: F811
+    """Batches of several steps: 600,000 rows, most of them short, of very different lengths."""
+    n = 600_000
+    s = synth.graphs(n, 2_400_000 if products else 600_000, k, 0.01, "rmat", (0.57, 0.19, 0.19, 0.05), 5)
+    assert (3 * k * min(len(s.col[t]) for t in range(k)) > 10_000_000 + k * n * (4 * F + 1)) == products
+    frame = pipad.frame_build_overlap([(torch.from_numpy(s.rowptr[t]).cuda(), torch.from_numpy(s.col[t]).cuda()) for t in range(k)])
+    x = torch.empty((n, k, F), device="cuda:0").uniform_(-1, 1)
+    y = pipad.frame_aggregate(frame, x)
+    for t in (0, k - 1):
+        _, yd, bound, _ = oracle.aggregate(n, *csr_to_coo(n, s.rowptr[t], s.col[t]), x[:, t].cpu().numpy(), threads=8)
+        check_y(y[:, t].cpu().numpy(), yd, bound, f"snapshot {t}")
+    frame.close()
