@@ -17,13 +17,14 @@
 //            and the exclusive entries of every snapshot are written out next to each other
 //   scan     prefix sums over the tiles' and the row blocks' counts; with them every data-dependent
 //            size is known and goes to the host
-//   rows     a thread per row, while the host sizes the outputs: row pointers of all parts and the
-//            work lists of the aggregation (short, mid, hub rows; very long rows cut into units)
+//   rows     a thread per row, while the host sizes the outputs or next to the scatter step: row pointers of all
+//            parts and the work lists of the aggregation (short, mid, hub rows; very long rows cut into units)
 //   scatter  a wave per tile (or four) and part writes the entries in order, with their column scales
 //   fill     the entries of the hub rows a second time, grouped by column class, with their scales
 //
-// Small frames, whose launches take longer than their work, go in two: prepare and mark (a tile finds its own bounds), then the
-// sums, rows and scatter (every workgroup makes the sums that it needs), into room for as many entries as the parts can have.
+// Frames that are not large get room for as many entries as the parts can have, so that scatter need not wait for the sizes: rows
+// and scatter are one launch there.  Small frames, whose launches take longer than their work, go in two launches altogether:
+// prepare and mark (a tile finds its own bounds), then the sums, rows and scatter (every workgroup makes the sums it needs).
 //
 // All integer work; the outputs are unique, so they are bit-exact regardless of scheduling.
 #include <algorithm>
@@ -1777,35 +1778,40 @@ __global__ __launch_bounds__(kBlock) void k_scatter(Snaps s, Tiles g, OutParts o
                                  [&](int32_t x) __attribute__((always_inline)) { return g.tile_pre[x].x; });
 }
 
-// Rows and entries of small frames in one launch behind k_prepare_mark: `row_wgs` workgroups make the rows (the first of them
-// sends the sizes to the host), those behind them write the entries, a wave per tile and part.  The outputs have room
-// for as many entries as the parts can have, so that nothing waits for the host; where a tile's flag says that the
-// snapshots are not canonical, no entries are written.
-template <int KV, bool FULL>
+// Rows and entries in one launch: `row_wgs` workgroups make the rows, those behind them write the entries, a wave per tile and
+// part.  The outputs have room for as many entries as the parts can have, so that nothing waits for the host; where the
+// snapshots are not canonical, no entries are written.  SUM: behind k_prepare_mark, with nothing summed up yet (the first
+// workgroup sends the sizes to the host).
+template <int KV, bool FULL, bool SUM>
 __global__ __launch_bounds__(kBlock) void k_rows_scatter(Snaps s, Tiles g, RowArgs r, ListArgs q, OutParts o, int32_t row_wgs,
                                                          const float *dinv, const float *dinv_nk, FrameTotals *out, uint32_t seq) {
   if ((int32_t)blockIdx.x < row_wgs) {
-    make_rows<true>(s, g, r, q, out, seq);
+    make_rows<SUM>(s, g, r, q, out, seq);
     return;
   }
   const int32_t groups = (g.ntiles + kWavesPerBlock - 1) / kWavesPerBlock, b = (int32_t)blockIdx.x - row_wgs;
   const int part = b / groups;
   const int32_t first = (b - part * groups) * kWavesPerBlock, tile0 = first + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  uint32_t mine[kWavesPerBlock];  // of the workgroup's tiles
+  if constexpr (SUM) {
+    uint32_t mine[kWavesPerBlock];  // of the workgroup's tiles
 #pragma unroll
-  for (int w = 0; w < kWavesPerBlock; ++w) mine[w] = g.tile_cnt[min(first + w, g.ntiles - 1)].x;
-  bool bad;
-  uint32_t front = sum_tiles_before(g, first, &bad);
-  if (bad || tile0 >= g.ntiles) return;
-  uint32_t here = mine[0];
+    for (int w = 0; w < kWavesPerBlock; ++w) mine[w] = g.tile_cnt[min(first + w, g.ntiles - 1)].x;
+    bool bad;
+    uint32_t front = sum_tiles_before(g, first, &bad);
+    if (bad || tile0 >= g.ntiles) return;
+    uint32_t here = mine[0];
 #pragma unroll
-  for (int w = 1; w < kWavesPerBlock; ++w)
-    if (tile0 >= first + w) {
-      front += mine[w - 1];
-      here = mine[w];
-    }
-  scatter_tiles<KV, FULL, 1>(s, g, o, dinv, dinv_nk, part, tile0,
-                             [&](int32_t x) __attribute__((always_inline)) { return x == tile0 ? front : front + here; });
+    for (int w = 1; w < kWavesPerBlock; ++w)
+      if (tile0 >= first + w) {
+        front += mine[w - 1];
+        here = mine[w];
+      }
+    scatter_tiles<KV, FULL, 1>(s, g, o, dinv, dinv_nk, part, tile0,
+                               [&](int32_t x) __attribute__((always_inline)) { return x == tile0 ? front : front + here; });
+  } else {
+    if (tile0 >= g.ntiles || *g.bad != 0) return;
+    scatter_tiles<KV, FULL, 1>(s, g, o, dinv, dinv_nk, part, tile0, [&](int32_t x) __attribute__((always_inline)) { return g.tile_pre[x].x; });
+  }
 }
 
 }  // namespace
@@ -1870,6 +1876,8 @@ int wait_totals(const TotalsTicket &ticket, hipStream_t st, FrameTotals *out) {
 // would be among them.)  Of 200 frames below the line with hub rows, in the mean: steps 6 to 14 % faster, backward passes 3 to 11,
 // aggregations alone 4 to 26, the more the fewer entries, with operands in the caches and without; at worst 14 % slower
 // (R-MAT, N = 62k, k = 2, F = 32, aggregation alone).
+constexpr int64_t kEarlyEntries = (int64_t)1 << 25;
+constexpr int32_t kManyTiles = 16384;  // from here on a wave of k_scatter takes four
 constexpr int32_t kPlainNodes = 65536, kPlainRow = 512;
 constexpr int64_t kPlainEntries = (int64_t)4 << 20;
 
@@ -2112,6 +2120,11 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
   // which 8192 run together: N = 107k, k = 8 with 2000 tiles 190 -> 186, N = 45k, k = 12 with 1520 181 -> 178, but N = 113k,
   // k = 16 with 1590 180 -> 187; with 3000 to 4000 tiles and k = 2 .. 6 3 to 13 % slower.
   const bool small = g.ntiles <= kSumTiles && row_blocks <= kSumRowBlocks && (int64_t)g.ntiles * k <= 20000;
+  // Frames of up to 33 M entries in all snapshots get that room as well (400 MB at most), and their rows are made next to the
+  // entries, in the launch that would wait for the host otherwise: steps and slides N = 100k R-MAT, k = 5 198 -> 191 us,
+  // N = 200k, k = 8 269 -> 263 (slide), 124k, k = 2 88 -> 77, 140k, k = 3 119 -> 111; of 40 frames past the small ones 1 to 10 % less,
+  // the more the shorter.
+  const bool early = small || (entries <= kEarlyEntries && g.ntiles < kManyTiles);
   int32_t most_common = s.nnz[0];
   for (int t = 1; t < k; ++t) most_common = std::min(most_common, s.nnz[t]);
 
@@ -2129,7 +2142,7 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
       a.want(&f->wd[t], (size_t)exclusive[t]);
     }
   };
-  if (small) want_parts(keep1, most_common, s.nnz);
+  if (early) want_parts(keep1, most_common, s.nnz);
   {
     void *base_ptr = A.get(keep1.total);
     if (!base_ptr) return fail(PIPAD_ERR_ALLOC);
@@ -2211,14 +2224,6 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
     if (n > 0)
       hipLaunchKernelGGL((k <= 16 ? k_prepare_mark<512, 1> : k_prepare_mark<256, 2>), dim3((unsigned)(g.ntiles + row_wgs)),
                          dim3((unsigned)threads), mark_lds, st, s, g, hub_min, row_classes(f), f->dinv, f->dinv_nk);
-    using RowsScatter = void (*)(Snaps, Tiles, RowArgs, ListArgs, OutParts, int32_t, const float *, const float *, FrameTotals *, uint32_t);
-    static const RowsScatter kernels[9] = {k_rows_scatter<0, false>, k_rows_scatter<1, false>, k_rows_scatter<1, true>,
-                                           k_rows_scatter<2, false>, k_rows_scatter<2, true>, k_rows_scatter<3, false>,
-                                           k_rows_scatter<3, true>, k_rows_scatter<4, false>, k_rows_scatter<4, true>};
-    const int32_t row_groups = (int32_t)grid1((int64_t)n + 1, kBlock).x;
-    const int32_t tile_groups = (int32_t)grid1(g.ntiles, kWavesPerBlock).x;
-    hipLaunchKernelGGL(kernels[kv], dim3((unsigned)(row_groups + tile_groups * (k + 1))), dim3(kBlock), 0, st, s, g, rows,
-                       list_args(f), out_parts(), row_groups, f->dinv, f->dinv_nk, ticket.where, ticket.seq);
   } else {
     const int32_t bound_blocks = (int32_t)(((int64_t)g.ntiles + 1 + kWavesPerBlock * 8 - 1) / (kWavesPerBlock * 8));
     hipLaunchKernelGGL(k_prepare, dim3((unsigned)(bound_blocks + row_blocks)), dim3(kBlock), 0, st, s, g, row_classes(f),
@@ -2243,12 +2248,26 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
     a.tiles_per_block = (int32_t)std::min<int64_t>((runs + blocks - 1) / blocks * kTileScanRun, 1 << 30);
     a.rows_per_block = (row_runs + blocks - 1) / blocks * kTileScanBlock;
     hipLaunchKernelGGL(k_scan_counts, dim3((unsigned)blocks), dim3(kTileScanBlock), 0, st, a, ticket.where, ticket.seq);
-    hipLaunchKernelGGL(k_rows, grid1((int64_t)n + 1, kBlock), dim3(kBlock), 0, st, s, g, rows, list_args(f));
+    if (!early)
+      hipLaunchKernelGGL(k_rows, grid1((int64_t)n + 1, kBlock), dim3(kBlock), 0, st, s, g, rows, list_args(f));
+  }
+  if (early) {
+    using RowsScatter = void (*)(Snaps, Tiles, RowArgs, ListArgs, OutParts, int32_t, const float *, const float *, FrameTotals *, uint32_t);
+    static const RowsScatter kernels[2][9] = {
+        {k_rows_scatter<0, false, false>, k_rows_scatter<1, false, false>, k_rows_scatter<1, true, false>,
+         k_rows_scatter<2, false, false>, k_rows_scatter<2, true, false>, k_rows_scatter<3, false, false>,
+         k_rows_scatter<3, true, false>, k_rows_scatter<4, false, false>, k_rows_scatter<4, true, false>},
+        {k_rows_scatter<0, false, true>, k_rows_scatter<1, false, true>, k_rows_scatter<1, true, true>,
+         k_rows_scatter<2, false, true>, k_rows_scatter<2, true, true>, k_rows_scatter<3, false, true>,
+         k_rows_scatter<3, true, true>, k_rows_scatter<4, false, true>, k_rows_scatter<4, true, true>}};
+    const int32_t row_groups = (int32_t)grid1((int64_t)n + 1, kBlock).x;
+    const int32_t tile_groups = (int32_t)grid1(g.ntiles, kWavesPerBlock).x;
+    hipLaunchKernelGGL(kernels[small ? 1 : 0][kv], dim3((unsigned)(row_groups + tile_groups * (k + 1))), dim3(kBlock), 0, st, s, g,
+                       rows, list_args(f), out_parts(), row_groups, f->dinv, f->dinv_nk, ticket.where, ticket.seq);
   }
   PIPAD_TRY(hipGetLastError());
 
-  // ---- the one host synchronisation: sizes of the data-dependent outputs (k_rows, or what is left of
-  // k_rows_scatter, runs meanwhile)
+  // ---- the one host synchronisation: sizes of the data-dependent outputs (k_rows, or k_rows_scatter, runs meanwhile)
   FrameTotals v;
   {
     const int rc = wait_totals(ticket, st, &v);
@@ -2263,18 +2282,18 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
   }
 
   Arena keep2;
-  if (!small) want_parts(keep2, f->nnz_c, f->nnz_d);
+  if (!early) want_parts(keep2, f->nnz_c, f->nnz_d);
   want_split(keep2, f);
-  if (!small || (f->n_items > 0 && !f->plain_units)) {
+  if (!early || (f->n_items > 0 && !f->plain_units)) {
     void *base_ptr = A.get(keep2.total);
     if (!base_ptr) return fail(PIPAD_ERR_ALLOC);
     keep2.assign(base_ptr);
   }
-  if (g.ntiles > 0 && !small) {
+  if (!early && g.ntiles > 0) {
     // A wave per tile has the shortest chain of dependent loads (0.2M nodes: 65 us against 74 with four
     // tiles per wave); with 8M entries and more per snapshot there
     // are waves enough and fewer of them do better (1M nodes, 20M entries: 313 us against 339).
-    const int per_wave = g.ntiles < 16384 ? 1 : 4;
+    const int per_wave = g.ntiles < kManyTiles ? 1 : 4;
     using Scatter = void (*)(Snaps, Tiles, OutParts, const float *, const float *);
     static const Scatter kernels[2][9] = {
         {k_scatter<0, false, 1>, k_scatter<1, false, 1>, k_scatter<1, true, 1>, k_scatter<2, false, 1>,

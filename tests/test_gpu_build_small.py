@@ -38,3 +38,40 @@ def test_row_lengths(pipad, length, behind):  # noqa: F811
     base = np.concatenate([lead, row(5, 2500, 800), rest, row(11, 12, 600)])  # the second tile starts at (5, 2996)
     other = np.concatenate([lead[::2], row(5, 3000 if behind else 2996 - length, length), rest[1::2]])
     run_case(pipad, n, [csr(n, base), csr(n, other)], 4, seed=length)
+
+
+@pytest.mark.parametrize("entries", [3000, 600_000, 2048 * 512 + 1])
+@pytest.mark.parametrize("which", ["largest", "another"])
+def test_column_twice(pipad, entries, which):  # noqa: F811
+    """Noticed without validation, with nothing written past the room of the parts, which is there before the sizes are known."""
+    import ctypes
+
+    from paper_2301_00391_amd import binding
+    n = 3000
+    rng = np.random.default_rng(entries)
+    keys = np.unique(rng.integers(0, n * n, 2 * entries + 4000))
+    keys = keys[keys // n != keys % n]
+    keys = np.sort(rng.permutation(keys)[:entries])
+    pairs = np.stack([keys // n, keys % n], 1)
+    good, fewer = csr(n, pairs), csr(n, pairs[:-1])
+    rowptr, col = good if which == "largest" else fewer
+    at = int(rowptr[np.flatnonzero(np.diff(rowptr) > 1)[len(rowptr) // 9]])
+    bad = rowptr, np.concatenate([col[:at + 1], col[at:at + 1], col[at + 2:]])
+    lists = [bad, fewer, fewer] if which == "largest" else [fewer, bad, good]
+    snaps = [(torch.from_numpy(rp).cuda(), torch.from_numpy(c.astype(np.int32)).cuda()) for rp, c in lists]
+    arr = (binding._Csr * len(snaps))()
+    for t, (rp, c) in enumerate(snaps):
+        arr[t].n, arr[t].nnz, arr[t].rowptr, arr[t].colidx = n, c.numel(), rp.data_ptr(), c.data_ptr()
+    kept, guard = [], 4096
+
+    def alloc(nbytes, _ctx):
+        kept.append(torch.full((int(nbytes) + guard,), 0x5a, dtype=torch.uint8, device="cuda:0"))
+        return kept[-1].data_ptr()
+
+    cb, out = binding.ALLOC_FN(alloc), ctypes.c_void_p()
+    status = pipad.load_library().pipad_frame_build_overlap(n, len(snaps), arr, 0, ctypes.cast(cb, ctypes.c_void_p), None,
+                                                            torch.cuda.current_stream().cuda_stream, ctypes.byref(out))
+    assert status == -2 and out.value is None
+    torch.cuda.synchronize()
+    for buf in kept:
+        assert bool((buf[-guard:] == 0x5a).all())
