@@ -1141,32 +1141,43 @@ constexpr int kTilesEach = 8;  // per thread
 constexpr int kSumTiles = kTilesEach * kBlock;
 constexpr int kSumRowBlocks = 4 * kBlock;
 
-// The counts of tiles kTilesEach * threadIdx.x and those behind it, without the flags; returns whether a flag is set.
-__device__ __forceinline__ bool load_tiles(const Tiles &g, uint32_t (&c)[2][kTilesEach]) {
+// The counts of tiles kTilesEach * threadIdx.x and those behind it, as they lie in memory (read two at a time).
+struct TileCounts {
+  uint4 pair[kTilesEach / 2];
+};
+__device__ __forceinline__ TileCounts request_tiles(const Tiles &g) {
+  const int t0 = kTilesEach * (int)threadIdx.x;
+  TileCounts x;
+#pragma unroll
+  for (int q = 0; q < kTilesEach; q += 2) {
+    x.pair[q / 2] = make_uint4(0, 0, 0, 0);
+    if (t0 + q < g.ntiles) x.pair[q / 2] = *reinterpret_cast<const uint4 *>(g.tile_cnt + t0 + q);
+  }
+  return x;
+}
+// ... without the flags; returns whether a flag is set.
+__device__ __forceinline__ bool split_tiles(const Tiles &g, const TileCounts &x, uint32_t (&c)[2][kTilesEach]) {
   const int t0 = kTilesEach * (int)threadIdx.x;
   uint32_t flags = 0;
 #pragma unroll
-  for (int q = 0; q < kTilesEach; ++q) c[0][q] = c[1][q] = 0;
-#pragma unroll
-  for (int q = 0; q < kTilesEach; q += 2)
-    if (t0 + q < g.ntiles) {
-      const uint4 x = *reinterpret_cast<const uint4 *>(g.tile_cnt + t0 + q);  // (padded to a pair)
-      const bool both = t0 + q + 1 < g.ntiles;
-      c[0][q] = x.x;
-      c[1][q] = x.y & (kBadTile - 1u);
-      c[0][q + 1] = both ? x.z : 0u;
-      c[1][q + 1] = both ? x.w & (kBadTile - 1u) : 0u;
-      flags |= x.y | (both ? x.w : 0u);
-    }
+  for (int q = 0; q < kTilesEach; q += 2) {
+    const uint4 v = x.pair[q / 2];
+    const bool both = t0 + q + 1 < g.ntiles;
+    c[0][q] = v.x;
+    c[1][q] = v.y & (kBadTile - 1u);
+    c[0][q + 1] = both ? v.z : 0u;
+    c[1][q + 1] = both ? v.w & (kBadTile - 1u) : 0u;
+    flags |= v.y | (both ? v.w : 0u);
+  }
   return (flags & kBadTile) != 0;
 }
 
 // What lies in front of every tile, and of all of them, into `pre`; returns whether a tile's flag is set.
-__device__ inline bool sum_tiles(const Tiles &g, uint2 *pre) {
+__device__ inline bool sum_tiles(const Tiles &g, const TileCounts &x, uint2 *pre) {
   __shared__ uint32_t front[2][kWavesPerBlock];
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, t0 = kTilesEach * (int)threadIdx.x;
   uint32_t c[2][kTilesEach];
-  const bool bad = load_tiles(g, c);
+  const bool bad = split_tiles(g, x, c);
   uint32_t at[2];
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
@@ -1197,7 +1208,7 @@ __device__ inline uint32_t sum_tiles_before(const Tiles &g, int32_t upto, bool *
   __shared__ uint32_t front[kWavesPerBlock], flag[kWavesPerBlock];
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, t0 = kTilesEach * (int)threadIdx.x;
   uint32_t c[2][kTilesEach], mine = 0;
-  const bool here = load_tiles(g, c);
+  const bool here = split_tiles(g, request_tiles(g), c);
 #pragma unroll
   for (int q = 0; q < kTilesEach; ++q) mine += t0 + q < upto ? c[0][q] : 0u;
   const uint32_t incl = wave_sum(mine);
@@ -1238,8 +1249,9 @@ __device__ __forceinline__ void make_rows(const Snaps &s, Tiles g, const RowArgs
   RowCounts first, total;
   if constexpr (SUM) {
     __shared__ uint2 pre[kSumTiles + 1];
+    const TileCounts tiles = request_tiles(g);  // (under way while the rows' counts are summed up)
     sum_row_counts(g.row_cnt, (int32_t)(((int64_t)g.n + kBlock - 1) / kBlock), (int32_t)blockIdx.x, &first, &total);
-    const bool bad = sum_tiles(g, pre);
+    const bool bad = sum_tiles(g, tiles, pre);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
       const uint2 all = pre[g.ntiles];
       send_totals(total, all.x, all.y, total.entries - (uint64_t)g.k * all.y, bad, out, seq);

@@ -707,7 +707,7 @@ int transpose_frame(const pipad_frame *f, pipad_alloc_fn alloc, void *alloc_ctx,
 
   Arena lists;
   want_split(lists, g);
-  {
+  if (g->n_items > 0 && !g->plain_units) {
     void *base = A.get(lists.total);
     if (!base) return fail(PIPAD_ERR_ALLOC);
     lists.assign(base);
