@@ -98,6 +98,7 @@ struct AggArgs {
   int32_t sg;         // coalescent kernel: snapshots per lane team (slices are snapshot groups)
   int32_t products;   // ... the sums are those of kTable
   int32_t longest_first;  // ... a wave's short rows in order of their common entries where those differ a lot
+  int32_t share;        // ... the lanes of a quad fetch common entries for each other (walk_front)
   int32_t whole_units;  // coalescent kernel: one partial sum per hub unit, not one per class part
   int32_t plain;        // hub units are walked by a workgroup each, from the lists of the parts (nclass is 1 then)
   int32_t direct;       // ... and every hub row is one unit: the row is finished there, no partial sums
@@ -309,24 +310,27 @@ enum Scales {
   kProducts,  // out of the lists, with the products and sums of kTable: the same bits
 };
 
-// The same without the scale: weight 1, past the end 0.
-__device__ __forceinline__ Raw fetch_index(const Lists &l, int32_t cs, int32_t clen, int32_t ds, int32_t total, int32_t pos,
-                                           int32_t self) {
+// The same without the scale: column -1 past the end, so that no weight takes a register.
+__device__ __forceinline__ Raw fetch_index(const Lists &l, int32_t cs, int32_t clen, int32_t ds, int32_t total, int32_t pos) {
   Raw r;
-  r.c = self;
+  r.c = -1;
   r.w = 0.f;
   if (pos < total) {
     const bool common = pos < clen;
     r.c = (common ? l.colc : l.cold)[common ? cs + pos : ds + (pos - clen)];
-    r.w = 1.f;
   }
   return r;
 }
 template <Scales S>
 __device__ __forceinline__ Raw fetch(const Lists &l, int32_t cs, int32_t clen, int32_t ds, int32_t total, int32_t pos,
                                      int32_t self, bool nt) {
-  return S == kTable ? fetch_index(l, cs, clen, ds, total, pos, self) : fetch_entry(l, cs, clen, ds, total, pos, self, nt);
+  return S == kTable ? fetch_index(l, cs, clen, ds, total, pos) : fetch_entry(l, cs, clen, ds, total, pos, self, nt);
 }
+
+template <Scales S>
+__device__ __forceinline__ uint32_t entry_column(const Raw &r) { return (uint32_t)(S == kTable ? max(r.c, 0) : r.c); }
+template <Scales S>
+__device__ __forceinline__ float entry_weight(const Raw &r) { return S == kTable ? (r.c >= 0 ? 1.f : 0.f) : r.w; }
 
 // Adds the (up to) four gathered rows of one step to the sum.
 template <int VEC, Scales S, int N>
@@ -396,11 +400,11 @@ __device__ __forceinline__ void walk(const Lists &l, int32_t cs, int32_t clen, i
       float w[EPL];
 #pragma unroll
       for (int j = 0; j < EPL; ++j) {
-        w[j] = mine[j].w;
+        w[j] = entry_weight<S>(mine[j]);
 #ifdef PIPAD_NO_GATHER
         x[j] = VT::zero();
 #else
-        x[j] = VT::load(reinterpret_cast<const float *>(xbytes + ((uint32_t)mine[j].c * row_bytes + lane_bytes)));
+        x[j] = VT::load(reinterpret_cast<const float *>(xbytes + (entry_column<S>(mine[j]) * row_bytes + lane_bytes)));
 #endif
       }
       add_step<VEC, S>(w, x, acc);
@@ -411,8 +415,8 @@ __device__ __forceinline__ void walk(const Lists &l, int32_t cs, int32_t clen, i
 #pragma unroll
     for (int j = 0; j < EPL; ++j) {
       Staged st;
-      st.off = FAST ? (uint32_t)mine[j].c * row_bytes : (uint32_t)mine[j].c;
-      st.w = mine[j].w;
+      st.off = FAST ? entry_column<S>(mine[j]) * row_bytes : entry_column<S>(mine[j]);
+      st.w = entry_weight<S>(mine[j]);
       mine_lds[j * team_lanes + q] = st;
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -1149,7 +1153,34 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
 // 139; 5k, k = 16, F = 5 74 -> 19; 200k, k = 8, F = 16 173 -> 175.
 struct CoalItem {
   int32_t i, cs, clen, ds, len;  // len: both lists together (0: this lane has nothing to do)
+  int32_t front;                 // common entries in front of these, for walk_front
 };
+
+// The value of lane J of the quad.
+template <int J>
+__device__ __forceinline__ uint32_t of_quad(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, J * 0x55, 0xf, 0xf, true);
+}
+
+// Adds `front` common entries of a row, a multiple of the chunk of 4 * team_lanes: where the lanes of a team are one snapshot
+// each, they all take the same ones, and a lane of a quad fetches one and turns it into an offset for all four, where it
+// fetched four for itself (walk).  at: the place of this lane's first one in colc, of which `c` is the column.
+// The same sums as walk's.
+template <int VEC>
+__device__ __forceinline__ void walk_front(const int32_t *colc, int32_t at, int32_t c, int32_t front, int32_t chunk, const float *table,
+                                           uint32_t row_bytes, uint32_t lane_bytes, typename V<VEC>::T &acc) {
+  using VT = V<VEC>;
+  const char *const bytes = reinterpret_cast<const char *>(table);
+  const float w[4] = {1.f, 1.f, 1.f, 1.f};
+  auto row = [&](uint32_t off) __attribute__((always_inline)) { return VT::load(reinterpret_cast<const float *>(bytes + (off + lane_bytes))); };
+  for (int32_t left = front; left > 0; left -= chunk) {
+    const uint32_t off = (uint32_t)c * row_bytes;
+    at += chunk;
+    if (left > chunk) c = colc[at];
+    const typename VT::T x[4] = {row(of_quad<0>(off)), row(of_quad<1>(off)), row(of_quad<2>(off)), row(of_quad<3>(off))};
+    add_step<VEC, kTable>(w, x, acc);
+  }
+}
 
 // Where snapshot group g's partial sums of class part `cls` of a hub unit (of the whole unit, where that
 // is summed at once) start, as the place of column 0 of the wide row: the groups one after the other, in
@@ -1314,6 +1345,8 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_coalescent(const AggArgs a
   const int team_base = (wide ? u * nteams : team * a.sg + u) * fetchers;
   const int slot = wide ? team : 0;
   const int nslots = wide ? nteams : 1;
+  const bool share = ALONE && S == kTable && a.share;
+  const int32_t chunk = 4 * team_lanes, place = (fl & 3) * team_lanes + q;
   auto meta = [&](int step, int part) __attribute__((always_inline)) {
     CoalItem it;
     const int li = step * per_step + (wide ? 0 : team);
@@ -1322,6 +1355,9 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_coalescent(const AggArgs a
     it.i = __shfl(r, src, kWave);
     it.cs = __shfl(mc0, src, kWave);
     it.clen = __shfl(mc1, src, kWave) - it.cs;
+    it.front = share && have ? it.clen & -chunk : 0;  // (the lanes without columns take part)
+    it.cs += it.front;
+    it.clen -= it.front;
     int64_t stride = 1;
     const int32_t *pd = rpd + it.i;
     if (split) {
@@ -1335,9 +1371,13 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_coalescent(const AggArgs a
   };
   struct Fetched {
     Raw e[EPL];
+    int32_t c;  // of walk_front
   };
   auto fetch = [&](const CoalItem &it) __attribute__((always_inline)) {
     Fetched f;
+    f.c = 0;
+    if constexpr (ALONE && S == kTable)
+      if (it.front > 0) f.c = lists.colc[it.cs - it.front + place];
 #pragma unroll
     for (int v = 0; v < EPL; ++v)
       f.e[v] = pipad::fetch<S>(lists, it.cs, it.clen, it.ds, it.len, v * team_lanes + q, it.i, false);
@@ -1345,6 +1385,8 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_coalescent(const AggArgs a
   };
   auto walk_item = [&](const CoalItem &it, const Fetched &f) __attribute__((always_inline)) {
     typename VT::T acc = VT::zero();
+    if constexpr (ALONE && S == kTable)
+      walk_front<VEC>(lists.colc, it.cs - it.front + place, f.c, it.front, chunk, s.xt, (uint32_t)ldg * 4u, lane_bytes, acc);
     walk<VEC, U, true, EPL, ALONE, S>(lists, it.cs, it.clen, it.ds, it.len, f.e, team_base, team_lanes, q, slot, nslots, s,
                                       ldg, it.i, false, lds, acc);
     return acc;
@@ -1380,6 +1422,7 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_coalescent(const AggArgs a
           const int64_t c0 = a.sptr[(int64_t)part * n_items + first + step];
           const int64_t c1 = a.sptr[(int64_t)(part + 1) * n_items + first + step];
           const int32_t dlen = it.len - it.clen;
+          it.front = 0;
           it.cs = (int32_t)c0;
           it.clen = (int32_t)(c1 - c0);
           it.len = valid ? it.clen + dlen : 0;
@@ -1751,6 +1794,11 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
     // 728 / 1444 us, 61k, k = 16, F = 3 68.7 -> 62, Chung-Lu 162k, k = 8, F = 3 92 -> 85; on the other side of it Chung-Lu 89k, k = 3,
     // F = 2 34 -> 36.4, 150k, k = 8, F = 2, churn 0.3 71 -> 74.
     a.longest_first = (int64_t)a.sg * F * 4 * f->nnz_c >= 28 * entries;
+    // Common entries fetched once for the lanes of a quad (which lies within a team then) from 10 common entries per row on: R-MAT 1M,
+    // k = 8, F = 1 / 2 / 4 290 / 350 / 442 -> 281 / 341 / 431 us, 300k, F = 2 116 -> 109, 700k, k = 3 177 -> 168, Chung-Lu 217k, k = 4,
+    // F = 2 57.8 -> 55.0; 147k, k = 6, F = 1 50.2 -> 49.9.  With fewer, whose rows end soon after the common entries that make up whole
+    // chunks, between 3 % faster and 3 % slower (Chung-Lu 260k, k = 8, F = 2 64.8 -> 66.5, 118k, k = 12, 70.8 -> 71.9).
+    a.share = a.ls_log2 >= 2 && (int64_t)f->nnz_c >= 10 * (int64_t)f->n;
     // The gathered rows multiplied by their scales first (k_scale_rows), so that a walk only reads indices: one pass over the
     // operand against 4 bytes per entry and snapshot, of which an instruction of the walk touched up to 64 lines.  Measured,
     // that saves 1.5 us per million entries of all snapshots, whatever F is, and the pass takes 5 us and its bytes at 4.4 TB/s:

@@ -72,3 +72,38 @@ def test_short_rows_longest_first(pipad, k, F, products):  # noqa: F811
         _, yd, bound, _ = oracle.aggregate(n, *csr_to_coo(n, s.rowptr[t], s.col[t]), x[:, t].cpu().numpy(), threads=8)
         check_y(y[:, t].cpu().numpy(), yd, bound, f"snapshot {t}")
     frame.close()
+
+
+@pytest.mark.parametrize("k,F,classes", [(3, 1, False), (4, 4, True), (5, 2, True), (7, 1, False), (16, 2, True), (16, 4, False)])
+def test_entries_shared_by_a_quad(pipad, k, F, classes):  # noqa: F811
+    """Rows whose common entries are fetched once for a team's snapshots: teams of 4 to 64 lanes, idle lanes among them, short,
+    mid and hub rows; the products that the kernel makes itself are summed up without that."""
+    n = 20_000 if classes else 70_000
+    pipad.set_option("agg_coalescent", 2)
+    if classes:  # hub rows by column class in a small frame, too
+        pipad.set_option("mid_max", 300)
+    s = synth.graphs(n, 1_300_000, k, 0.02, "rmat", (0.57, 0.19, 0.19, 0.05), 9)
+    frame = pipad.frame_build_overlap([(torch.from_numpy(s.rowptr[t]).cuda(), torch.from_numpy(s.col[t]).cuda()) for t in range(k)])
+    assert frame.common()[1].numel() >= 10 * n
+    assert 3 * k * min(len(s.col[t]) for t in range(k)) > 10_000_000 + k * n * (4 * F + 1)
+    x = torch.empty((n, k, F), device="cuda:0").uniform_(-1, 1)
+    y = pipad.frame_aggregate(frame, x)
+    for t in (0, k - 1):
+        _, yd, bound, _ = oracle.aggregate(n, *csr_to_coo(n, s.rowptr[t], s.col[t]), x[:, t].cpu().numpy(), threads=8)
+        check_y(y[:, t].cpu().numpy(), yd, bound, f"snapshot {t}")
+    # recorded on a frame whose scratch holds the partial sums and no more: no room for the products
+    fresh = pipad.frame_build_overlap([(torch.from_numpy(s.rowptr[t]).cuda(), torch.from_numpy(s.col[t]).cuda()) for t in range(k)])
+    parts = [torch.zeros((n, F), device="cuda:0") for _ in range(k)]
+    pipad.frame_aggregate(fresh, parts, [torch.empty_like(p) for p in parts])
+    torch.cuda.synchronize()
+    out = torch.full_like(y, float("nan"))
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        pipad.frame_aggregate(fresh, x, out)
+    for _ in range(2):
+        out.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, y)
+    frame.close()
+    fresh.close()
