@@ -103,7 +103,8 @@ int pipad_frame_build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, ui
 /* With a caller allocator, one of the buffers a build (or pipad_frame_transpose) obtained holds
  * only temporaries: the frame never touches it again once the work that the build enqueued on its
  * stream has completed.  This call reports that buffer (*ptr, *bytes as requested from the
- * callback; NULL / 0 with the library's own allocator, which frees its temporaries itself, or
+ * callback; NULL / 0 where a small frame got them together with its own memory, which is 32 MB at
+ * most then, and with the library's own allocator, which frees its temporaries itself, or
  * when it was already taken) and the frame forgets it: the caller may release it after a
  * stream-ordered point behind the build, long before pipad_frame_destroy(). */
 int pipad_frame_temporaries(pipad_frame_t *frame, void **ptr, size_t *bytes);

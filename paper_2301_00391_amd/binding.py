@@ -12,8 +12,10 @@ The names mirror ``include/pipad.h``:
 from __future__ import annotations
 
 import ctypes
+import functools
 import itertools
 import os
+import struct
 from typing import List, Optional, Sequence, Tuple, Union
 
 import torch
@@ -39,25 +41,21 @@ class _Csr(ctypes.Structure):
 
 ALLOC_FN = ctypes.CFUNCTYPE(ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p)
 
-# symbol -> (restype, argtypes); also the list the ABI test checks against include/pipad.h
+# symbol -> (restype, argtypes); also the list the ABI test checks against include/pipad.h.  Arrays that a call
+# only reads are plain pointers: packed bytes are made in a fraction of the time that a ctypes array takes (16
+# descriptors 8.6 us, packed 0.8).
 _vp, _i32, _i64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64
 SIGNATURES = {
-    "pipad_frame_build_overlap": (ctypes.c_int, [_i32, _i32, ctypes.POINTER(_Csr), ctypes.c_uint32,
-                                                 _vp, _vp, _vp, ctypes.POINTER(_vp)]),
+    "pipad_frame_build_overlap": (ctypes.c_int, [_i32, _i32, _vp, ctypes.c_uint32, _vp, _vp, _vp, ctypes.POINTER(_vp)]),
     "pipad_frame_common": (ctypes.c_int, [_vp, ctypes.POINTER(_Csr)]),
     "pipad_frame_delta": (ctypes.c_int, [_vp, _i32, ctypes.POINTER(_Csr)]),
     "pipad_frame_dinv": (ctypes.c_int, [_vp, ctypes.POINTER(_vp), ctypes.POINTER(_i64),
                                         ctypes.POINTER(_i64)]),
     "pipad_frame_shape": (ctypes.c_int, [_vp, ctypes.POINTER(_i32), ctypes.POINTER(_i32)]),
-    "pipad_frame_aggregate": (ctypes.c_int, [_vp, _i32, ctypes.POINTER(_vp), _i64,
-                                             ctypes.POINTER(_vp), _i64, _vp]),
-    "pipad_frame_aggregate_subset": (ctypes.c_int, [_vp, _i32, ctypes.POINTER(_i32), _i32,
-                                                    ctypes.POINTER(_vp), _i64, ctypes.POINTER(_vp), _i64, _vp]),
-    "pipad_frame_aggregate_static": (ctypes.c_int, [_vp, _i32, ctypes.POINTER(_vp), _i64,
-                                                    ctypes.POINTER(_vp), _i64, _vp]),
-    "pipad_frame_aggregate_update": (ctypes.c_int, [_vp, _i32, ctypes.POINTER(_vp), _i64, _vp, _i64,
-                                                    _vp, _i32, ctypes.POINTER(_vp), _i64,
-                                                    ctypes.POINTER(_vp), _i64, _vp]),
+    "pipad_frame_aggregate": (ctypes.c_int, [_vp, _i32, _vp, _i64, _vp, _i64, _vp]),
+    "pipad_frame_aggregate_subset": (ctypes.c_int, [_vp, _i32, _vp, _i32, _vp, _i64, _vp, _i64, _vp]),
+    "pipad_frame_aggregate_static": (ctypes.c_int, [_vp, _i32, _vp, _i64, _vp, _i64, _vp]),
+    "pipad_frame_aggregate_update": (ctypes.c_int, [_vp, _i32, _vp, _i64, _vp, _i64, _vp, _i32, _vp, _i64, _vp, _i64, _vp]),
     "pipad_frame_transpose": (ctypes.c_int, [_vp, _vp, _vp, _vp, ctypes.POINTER(_vp)]),
     "pipad_frame_temporaries": (ctypes.c_int, [_vp, ctypes.POINTER(_vp), ctypes.POINTER(ctypes.c_size_t)]),
     "pipad_recommended_row_stride": (ctypes.c_int64, [_i32]),
@@ -72,6 +70,11 @@ SIGNATURES = {
     "pipad_ceiling_sink_floats": (ctypes.c_size_t, []),
     "pipad_get_option": (ctypes.c_int, [ctypes.c_char_p, ctypes.POINTER(_i64)]),
 }
+
+
+# The packed forms of k snapshot descriptors and of k pointers.
+_pack_csr = functools.lru_cache(64)(lambda k: struct.Struct("IIPP" * k).pack)  # (pipad_csr_t, sizes mod 2^32)
+_pack_pointers = functools.lru_cache(64)(lambda k: struct.Struct(f"{k}P").pack)
 
 
 def load_library():
@@ -127,6 +130,8 @@ def _copy_from_device(ptr: Optional[int], count: int, dtype: torch.dtype, device
     return torch.as_tensor(_DevArray(ptr, count, typestr), device=device).clone()
 
 
+_unused_size = ctypes.byref(ctypes.c_size_t())  # where calls put a size that nobody asks for
+
 # The current stream of a device as a plain handle and the current device's index, without the
 # objects that torch.cuda.current_stream() and torch.cuda.device() make on every call: on small
 # frames the host side of a call takes longer than its kernels.
@@ -152,12 +157,12 @@ Snapshot = Tuple[torch.Tensor, torch.Tensor]  # (rowptr int32[n+1], colidx int32
 class Frame:
     """Owner of one ``pipad_frame_t``.  Built by :func:`frame_build_overlap`."""
 
-    def __init__(self, handle: int, n: int, k: int, device, buffers: list, key: Optional[int] = None,
+    def __init__(self, handle: int, n: int, k: int, device, buffers: dict, key: Optional[int] = None,
                  stream=None):
         self._h = handle
         self.n, self.k, self.device = n, k, device
         self._index = _device_index(device)
-        self._buffers = buffers  # torch tensors handed to the library through the allocator
+        self._buffers = buffers  # torch tensors handed to the library through the allocator, by address
         self._key = key  # names the buffers to the library's callback, which it may use again (aggregate scratch)
         # torch's allocator hands memory out, and takes it back, in the order of the stream that
         # was current at the allocation; work on any other stream has to be waited for in close()
@@ -168,16 +173,15 @@ class Frame:
         if key is not None:
             # the build's temporaries can go back to the allocator as soon as the build's kernels have
             # run: at once where its order is that of the build's stream, else behind an event
-            ptr, size = _vp(), ctypes.c_size_t()
-            _check(load_library().pipad_frame_temporaries(handle, ctypes.byref(ptr), ctypes.byref(size)))
+            ptr = _vp()
+            _check(_lib.pipad_frame_temporaries(handle, ctypes.byref(ptr), _unused_size))
             if ptr.value:
-                held = [b for b in buffers if b.data_ptr() == ptr.value]
                 if built_on == self._alloc_stream:
-                    self._drop(held)
+                    self._buffers.pop(ptr.value, None)
                 else:
                     event = torch.cuda.Event()
                     event.record(self._other_streams[built_on])
-                    self._temp = (held, event)
+                    self._temp = (ptr.value, event)
 
     def _stream(self, stream) -> int:
         """Handle of the stream a call runs on; streams other than the allocator's are remembered."""
@@ -186,15 +190,9 @@ class Frame:
             self._other_streams[raw] = stream if stream is not None else torch.cuda.current_stream(self._index)
         return raw
 
-    def _drop(self, held: list) -> None:
-        gone = {id(b) for b in held}
-        self._buffers[:] = [b for b in self._buffers if id(b) not in gone]
-
-    def _release_temporaries(self, wait: bool = False) -> None:
-        if self._temp is not None and (wait or self._temp[1].query()):
-            if wait:
-                self._temp[1].synchronize()
-            self._drop(self._temp[0])
+    def _release_temporaries(self) -> None:
+        if self._temp is not None and self._temp[1].query():
+            self._buffers.pop(self._temp[0], None)
             self._temp = None
 
     def close(self) -> None:
@@ -249,16 +247,17 @@ class Frame:
 # buffers by the key it is called with.  One callback for all frames: a ctypes callback sits in a
 # reference cycle, and with one per frame the garbage collector walked the whole program every few
 # hundred frames (10 us per build, of 52, for frames of a thousand nodes).
-_owners: dict = {}  # key -> (list that keeps the handed-out tensors alive, device)
+_owners: dict = {}  # key -> (the tensors handed out, by address, which keeps them alive; device)
 _next_key = itertools.count(1).__next__
 
 
 def _allocate(nbytes, key):
     try:
         buffers, device = _owners[key]
-        buf = torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
-        buffers.append(buf)
-        return buf.data_ptr()
+        buf = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
+        ptr = buf.data_ptr()
+        buffers[ptr] = buf
+        return ptr
     except Exception:  # out of memory -> NULL -> PIPAD_ERR_ALLOC
         return None
 
@@ -271,7 +270,7 @@ def _build(index: int, n: int, k: int, device, allocator: str, stream, fn, *args
     """The frame that fn(*args, allocator, its context, stream, result) makes."""
     if allocator not in ("torch", "library"):
         raise ValueError("allocator must be 'torch' or 'library'")
-    buffers: list = []
+    buffers: dict = {}
     key = None
     if allocator == "torch":
         key = _next_key()
@@ -316,9 +315,9 @@ def frame_build_overlap(snapshots: Sequence[Snapshot], validate: bool = False,
                 col.dtype is not int32 or col.get_device() != index or not col.is_contiguous():
             raise ValueError("snapshots must be contiguous int32 tensors on one GPU")
         nnz = col.numel()
-        descr.append((rp.numel() - 1, nnz, rp.data_ptr(), col.data_ptr() if nnz else None))
+        descr += (rp.numel() - 1 & 0xffffffff, nnz & 0xffffffff, rp.data_ptr(), col.data_ptr() if nnz else 0)
     return _build(index, n, k, device, allocator, stream, lib.pipad_frame_build_overlap,
-                  n, k, (_Csr * k)(*descr), VALIDATE if validate else 0)
+                  n, k, _pack_csr(k)(*descr), VALIDATE if validate else 0)
 
 
 Features = Union[torch.Tensor, Sequence[torch.Tensor]]
@@ -329,11 +328,12 @@ def _operand(x: Features, n: int, k: int, name: str) -> Tuple[List[int], int, in
     sharing one row stride, or one [n, k, F] tensor (the physically concatenated coalescent operand)."""
     float32 = torch.float32
     if isinstance(x, torch.Tensor):
-        if x.dim() != 3 or x.shape[0] != n or x.shape[1] != k:
+        shape = x.shape
+        if len(shape) != 3 or shape[0] != n or shape[1] != k:
             raise ValueError(f"{name}: a single tensor must have shape [n, k, F]")
-        if x.dtype != float32 or not x.is_cuda:
+        if x.dtype is not float32 or not x.is_cuda:
             raise ValueError(f"{name}: every matrix must be float32 [n, F] on the GPU")
-        F = x.shape[2]
+        F = shape[2]
         s0, s1, s2 = x.stride()
         if F > 1 and s2 != 1:
             raise ValueError(f"{name}: feature columns must be contiguous")
@@ -351,7 +351,7 @@ def _operand(x: Features, n: int, k: int, name: str) -> Tuple[List[int], int, in
         raise ValueError(f"{name}: feature columns must be contiguous")
     ptrs = []
     for m in mats:
-        if m.dtype != float32 or not m.is_cuda or m.shape != shape:
+        if m.dtype is not float32 or not m.is_cuda or m.shape != shape:
             raise ValueError(f"{name}: every matrix must be float32 [n, F] on the GPU")
         if m.stride() != strides:
             if F > 1 and m.stride(1) != 1:
@@ -380,10 +380,10 @@ def frame_aggregate(frame: Frame, X: Features, Y: Optional[Features] = None, str
     yp, ldy, Fy = _operand(Y, n, k, "Y")
     if Fy != F:
         raise ValueError("X and Y must have the same number of feature columns")
-    array = _vp * k
+    pack = _pack_pointers(k)
     frame._release_temporaries()
     fn = lib.pipad_frame_aggregate_static if static_scratch else lib.pipad_frame_aggregate
-    _check(_on_device(frame._index, fn, frame._h, F, array(*xp), ldx, array(*yp), ldy, frame._stream(stream)))
+    _check(_on_device(frame._index, fn, frame._h, F, pack(*xp), ldx, pack(*yp), ldy, frame._stream(stream)))
     return Y
 
 
@@ -400,7 +400,7 @@ def frame_aggregate_subset(frame: Frame, snapshots: Sequence[int], X: Sequence[O
     if len(X) != k or len(Y) != k:
         raise ValueError("X and Y must have k entries")
     F, ldx, ldy = None, None, None
-    xa, ya = (_vp * k)(), (_vp * k)()
+    xa, ya = [0] * k, [0] * k
     for t in sel:
         for m, name in ((X[t], "X"), (Y[t], "Y")):
             if m is None or m.dtype != torch.float32 or not m.is_cuda or m.dim() != 2 or m.shape[0] != n:
@@ -415,9 +415,10 @@ def frame_aggregate_subset(frame: Frame, snapshots: Sequence[int], X: Sequence[O
             raise ValueError("the chosen matrices must share their shape and row strides")
         xa[t], ya[t] = X[t].data_ptr(), Y[t].data_ptr()
     arr = (_i32 * len(sel))(*sel)
+    pack = _pack_pointers(k)
     frame._release_temporaries()
-    _check(_on_device(frame._index, lib.pipad_frame_aggregate_subset, frame._h, len(sel), arr, F, xa, ldx, ya, ldy,
-                      frame._stream(stream)))
+    _check(_on_device(frame._index, lib.pipad_frame_aggregate_subset, frame._h, len(sel), arr, F, pack(*xa), ldx,
+                      pack(*ya), ldy, frame._stream(stream)))
 
 
 def frame_aggregate_update(frame: Frame, X: Features, W: torch.Tensor,
@@ -441,14 +442,14 @@ def frame_aggregate_update(frame: Frame, X: Features, W: torch.Tensor,
     hp, ldh, Fh = _operand(H, n, k, "H")
     if Fh != Fo:
         raise ValueError("H must have Fo feature columns")
-    xa = (_vp * k)(*xp)
-    ha = (_vp * k)(*hp)
+    pack = _pack_pointers(k)
+    xa, ha = pack(*xp), pack(*hp)
     aa, lda = None, F
     if A is not None:
         ap, lda, Fa = _operand(A, n, k, "A")
         if Fa != F:
             raise ValueError("A must have F feature columns")
-        aa = (_vp * k)(*ap)
+        aa = pack(*ap)
     frame._release_temporaries()
     _check(_on_device(
         frame._index, lib.pipad_frame_aggregate_update,

@@ -2155,11 +2155,6 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
     }
   };
   if (early) want_parts(keep1, most_common, s.nnz);
-  {
-    void *base_ptr = A.get(keep1.total);
-    if (!base_ptr) return fail(PIPAD_ERR_ALLOC);
-    keep1.assign(base_ptr);
-  }
 
   Arena tmp;
   FrameTotals *totals = nullptr;
@@ -2178,7 +2173,13 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
   tmp.want(&g.bad, 1);
   tmp.want(&totals, 1);
   tmp.want(&dflags, (size_t)64);
-  if (alloc) {
+  const bool together = small && one_request(f, keep1.total + tmp.total);
+  void *const base_ptr = A.get(keep1.total + (together ? tmp.total : 0));
+  if (!base_ptr) return fail(PIPAD_ERR_ALLOC);
+  keep1.assign(base_ptr);
+  if (together) {
+    tmp.assign(static_cast<char *>(base_ptr) + keep1.total);
+  } else if (alloc) {
     temp = alloc(tmp.total, alloc_ctx);
     f->temp_ptr = temp;
     f->temp_bytes = temp ? tmp.total : 0;
@@ -2186,8 +2187,10 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
     (void)hipGetLastError();
     temp = nullptr;
   }
-  if (!temp) return fail(PIPAD_ERR_ALLOC);
-  tmp.assign(temp);
+  if (!together) {
+    if (!temp) return fail(PIPAD_ERR_ALLOC);
+    tmp.assign(temp);
+  }
 
   auto hipcheck = [&](hipError_t e, const char *what) { return e == hipSuccess ? 0 : hip_fail(e, what); };
 #define PIPAD_TRY(call)                                   \

@@ -545,12 +545,10 @@ int transpose_frame(const pipad_frame *f, pipad_alloc_fn alloc, void *alloc_ctx,
     for (int t = 0; t < k; ++t) entries += g->nnz_d[t];
     want_lists(keep, g, entries);
   }
-  {
+  if (n == 0) {
     void *base = A.get(keep.total);
     if (!base) return fail(PIPAD_ERR_ALLOC);
     keep.assign(base);
-  }
-  if (n == 0) {
     *out = g;
     return PIPAD_OK;
   }
@@ -568,7 +566,6 @@ int transpose_frame(const pipad_frame *f, pipad_alloc_fn alloc, void *alloc_ctx,
     total += nnz;
     s.rowptr[p] = p == 0 ? f->rowptr_c : f->rowptr_d[p - 1];
     s.col[p] = p == 0 ? f->col_c : f->col_d[p - 1];
-    s.col_out[p] = p == 0 ? g->col_c : g->col_d[p - 1];
   }
   s.part_off[k + 1] = (uint32_t)total;
   if (total >= ((int64_t)1 << 31)) return fail(PIPAD_ERR_TOO_LARGE);
@@ -602,7 +599,14 @@ int transpose_frame(const pipad_frame *f, pipad_alloc_fn alloc, void *alloc_ctx,
   tmp.want(&row_cnt, row_count_slots(n));
   tmp.want(&row_pre, row_count_slots(n));
   tmp.want(&totals, 1);
-  if (alloc) {
+  const bool together = one_request(g, keep.total + tmp.total);
+  void *const base_ptr = A.get(keep.total + (together ? tmp.total : 0));
+  if (!base_ptr) return fail(PIPAD_ERR_ALLOC);
+  keep.assign(base_ptr);
+  for (int p = 0; p <= k; ++p) s.col_out[p] = p == 0 ? g->col_c : g->col_d[p - 1];
+  if (together) {
+    tmp.assign(static_cast<char *>(base_ptr) + keep.total);
+  } else if (alloc) {
     temp = alloc(tmp.total, alloc_ctx);
     g->temp_ptr = temp;
     g->temp_bytes = temp ? tmp.total : 0;
@@ -610,8 +614,10 @@ int transpose_frame(const pipad_frame *f, pipad_alloc_fn alloc, void *alloc_ctx,
     (void)hipGetLastError();
     temp = nullptr;
   }
-  if (!temp) return fail(PIPAD_ERR_ALLOC);
-  tmp.assign(temp);
+  if (!together) {
+    if (!temp) return fail(PIPAD_ERR_ALLOC);
+    tmp.assign(temp);
+  }
 
   launched = true;
   // The two copies of D^-1/2 lie next to each other in every frame, padded to 256 bytes.

@@ -75,3 +75,43 @@ def test_column_twice(pipad, entries, which):  # noqa: F811
     torch.cuda.synchronize()
     for buf in kept:
         assert bool((buf[-guard:] == 0x5a).all())
+
+
+@pytest.mark.parametrize("n,edges,k,requests", [(500, 3000, 3, 1), (60_000, 300_000, 2, 1), (60_000, 900_000, 2, 2), (70_000, 300_000, 2, 2)])
+def test_temporaries_in_one_request(pipad, n, edges, k, requests):  # noqa: F811
+    """Small frames and their transposes, with nothing to hand back, and frames past either line."""
+    import ctypes
+
+    from paper_2301_00391_amd import binding
+    rng = np.random.default_rng(n + edges)
+    lists = []
+    for _ in range(k):
+        keys = np.unique(rng.integers(0, n * n, edges))
+        keys = keys[keys // n != keys % n]
+        lists.append(csr(n, np.stack([keys // n, keys % n], 1)))
+    snaps = [(torch.from_numpy(rp).cuda(), torch.from_numpy(c.astype(np.int32)).cuda()) for rp, c in lists]
+    arr = (binding._Csr * k)()
+    for t, (rp, c) in enumerate(snaps):
+        arr[t].n, arr[t].nnz, arr[t].rowptr, arr[t].colidx = n, c.numel(), rp.data_ptr(), c.data_ptr()
+    kept = []
+
+    def alloc(nbytes, _ctx):
+        kept.append(torch.full((int(nbytes),), 0x5a, dtype=torch.uint8, device="cuda:0"))
+        return kept[-1].data_ptr()
+
+    lib, cb = pipad.load_library(), binding.ALLOC_FN(alloc)
+    stream = torch.cuda.current_stream().cuda_stream
+    made = []
+    for back in (False, True):
+        out, ptr, size = ctypes.c_void_p(), ctypes.c_void_p(), ctypes.c_size_t(1)
+        before = len(kept)
+        ctx = (ctypes.cast(cb, ctypes.c_void_p), None, stream, ctypes.byref(out))
+        assert (lib.pipad_frame_transpose(made[0], *ctx) if back else lib.pipad_frame_build_overlap(n, k, arr, 0, *ctx)) == 0
+        made.append(out)
+        assert len(kept) - before == requests
+        assert lib.pipad_frame_temporaries(out, ctypes.byref(ptr), ctypes.byref(size)) == 0
+        assert bool(ptr.value) == (requests > 1) and bool(size.value) == (requests > 1)
+    torch.cuda.synchronize()
+    for h in made:
+        lib.pipad_frame_destroy(h)
+    run_case(pipad, n, lists, 4, seed=n)
