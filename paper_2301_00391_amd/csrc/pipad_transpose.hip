@@ -5,7 +5,7 @@
 // same launches.  Transposing a CSR pattern is a stable sort of its entries by column: rows arrive
 // in ascending order, so they leave in ascending order within every column, which makes the result
 // canonical CSR again.  The sort is a least-significant-digit radix sort with two digits of up to 10
-// bits for up to a million nodes (three, then four, beyond), written for 64-lane waves:
+// bits for up to a million nodes (three, then four, beyond; one of up to 12 for a few thousand nodes), written for 64-lane waves:
 //
 //   tiles      a part is cut into tiles of 2048, 4096 or 8192 consecutive entries, a workgroup of 8
 //              waves each
@@ -41,6 +41,20 @@ constexpr int32_t kRowsWalked = 4096;                // a wave's entries find th
 // takes as long as k_radix_scan but no launch: with the lists' sums made the same way (k_list_rows) N = 2k and
 // 8k, k = 3 and 4, transposition and aggregation 80 -> 69 us, N = 20k R-MAT 84 -> 79; with 32 tiles at most 81.
 constexpr uint32_t kFewTiles = 64;
+// Up to 8 tiles it counts the part's digits itself, straight from the keys (k_radix_hist and its launch take longer than the
+// four round trips), and up to 4096 nodes, with digits of up to 12 bits and 32 tiles, the whole sort is one launch instead of
+// four: 5 launches for a small transposition and the aggregation behind it, not 8.  Medians of whole backward passes: N = 1100,
+// k = 1 65 -> 48 us, N = 2000, k = 6 69 -> 52, N = 2341, 16 k entries in the overlap part 66 -> 50, N = 4000, 20 k 67 -> 54, 55 k
+// 66 -> 57 (on a faster host 51 -> 52); two passes: N = 6000, k = 8, 13 k 72 -> 61, N = 5000, 15 k 66 -> 57.  Digits of 12 bits where 11
+// do are 6 % slower.
+constexpr uint32_t kCountTiles = 8, kCountTilesOnce = 32;
+constexpr int kMostDigitBits = 12;
+// Where k_radix_scatter has the counts of the digits from.
+enum Counts {
+  kScanned,  // summed up by k_radix_scan
+  kTiles,    // each tile's, from k_radix_hist
+  kKeys,     // counted here
+};
 struct SortArgs {
   int32_t nparts;                       // 1 + k
   int32_t n;
@@ -89,15 +103,19 @@ __device__ inline const int32_t *tile_keys(const SortArgs &g, const TileRange &r
   return (g.first ? g.col[r.p] : g.key_in + g.part_off[r.p]) + r.begin;
 }
 
+// D^-1/2 for the new frame, by workgroups behind those of the first launch (5 us as a copy of its own, there hardly any).
+__device__ inline void copy_dinv(const SortArgs &g, uint32_t block, uint32_t blocks) {
+  for (int64_t x = (int64_t)block * kSortBlock + threadIdx.x; x < g.dinv_pieces; x += (int64_t)blocks * kSortBlock)
+    g.dinv_to[x] = g.dinv_from[x];
+}
+
 // R entries per thread; a wave's share of a tile is R * 64 consecutive entries.
 template <int R>
 __global__ __launch_bounds__(kSortBlock) void k_radix_hist(SortArgs g) {
   __shared__ uint32_t cnt[kMaxDigits];
   const uint32_t tiles = g.tile_off[g.nparts];
-  if (blockIdx.x >= tiles) {  // (5 us as a copy of its own, here hardly any)
-    const int64_t step = (int64_t)(gridDim.x - tiles) * kSortBlock;
-    for (int64_t x = (int64_t)(blockIdx.x - tiles) * kSortBlock + threadIdx.x; x < g.dinv_pieces; x += step)
-      g.dinv_to[x] = g.dinv_from[x];
+  if (blockIdx.x >= tiles) {
+    copy_dinv(g, blockIdx.x - tiles, gridDim.x - tiles);
     return;
   }
   const TileRange r = tile_range<R>(g, blockIdx.x);
@@ -177,10 +195,11 @@ __global__ __launch_bounds__(kScanWaves * kWave) void k_radix_scan(SortArgs g) {
 }
 
 // The lanes of the wave whose digit equals this lane's, lanes with `live` false excluded.
+template <int BITS>
 __device__ inline uint64_t same_digit(uint32_t digit, int bits, bool live) {
   uint64_t mask = __ballot(live);
 #pragma unroll
-  for (int b = 0; b < kMaxDigitBits; ++b)
+  for (int b = 0; b < BITS; ++b)
     if (b < bits) {
       const bool bit = (digit >> b) & 1u;
       const uint64_t bal = __ballot(bit);
@@ -210,17 +229,22 @@ __device__ inline int32_t wave_row_of_entry(const int32_t *rp, int32_t n, int32_
 // place.  The next tile's go right behind them, so an XCD takes a run of tiles and its L2 puts the lines
 // together (3.4 M entries: 38 -> 33 us; tiles dealt to the XCDs in turn, whole lines never met).  With rows
 // found by a running maximum instead of a binary search per entry 43 -> 38 us.
-// FEW: no part has more than kFewTiles tiles (an instance of its own: as a branch it took 24 registers more).
+// (An instance for every kind of counts: as a branch those of the tiles took 24 registers more.)
 // (With 16 entries per thread held to the 128 registers that two workgroups per CU allow: 150 took the transposition of 58M
 // entries from 810 to 980 us.)
-template <int R, bool FEW = false>
+template <int R, Counts C = kScanned, int BITS = kMaxDigitBits>
 __global__ __launch_bounds__(kSortBlock) __attribute__((amdgpu_waves_per_eu(R == 16 ? 4 : 1))) void k_radix_scatter(SortArgs g) {
-  __shared__ uint16_t rank_of[kSortWaves][kMaxDigits];  // counts, then the first place in the tile, per wave
-  __shared__ int32_t stage[kSortBlock * R];             // the tile's keys, then its values, in digit order
-  __shared__ uint32_t to[kMaxDigits];                   // place in the part minus place in the tile
+  constexpr int kDigits = 1 << BITS;
+  __shared__ uint16_t rank_of[kSortWaves][kDigits];  // counts, then the first place in the tile, per wave
+  __shared__ int32_t stage[kSortBlock * R];          // the tile's keys, then its values, in digit order
+  __shared__ uint32_t to[kDigits];                   // place in the part minus place in the tile
   __shared__ uint32_t wave_total[kSortWaves], wave_front[kSortWaves];
   const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
   const uint32_t tiles = g.tile_off[g.nparts], tile = (uint32_t)xcd_run((int32_t)blockIdx.x, (int32_t)tiles);
+  if (C == kKeys && (int32_t)blockIdx.x >= align_xcd((int32_t)tiles)) {
+    copy_dinv(g, blockIdx.x - align_xcd((int32_t)tiles), gridDim.x - align_xcd((int32_t)tiles));
+    return;
+  }
   if (tile >= tiles) return;
   const TileRange r = tile_range<R>(g, tile);
   const int digits = 1 << g.bits;
@@ -229,6 +253,26 @@ __global__ __launch_bounds__(kSortBlock) __attribute__((amdgpu_waves_per_eu(R ==
   int32_t key[R], val[R];
 #pragma unroll
   for (int q = 0; q < R; ++q) key[q] = keys[min(first + q * kWave + lane, r.count - 1)];
+  // entries of the part in the tiles in front, and behind, by digit
+  __shared__ uint32_t in_front[C == kKeys ? kDigits : 1], behind[C == kKeys ? kDigits : 1];
+  if constexpr (C == kKeys) {
+    for (int d = tid; d < digits; d += kSortBlock) in_front[d] = behind[d] = 0;
+    __syncthreads();
+    const int32_t *const part = keys - r.begin;
+    const uint32_t entries = g.part_off[r.p + 1] - g.part_off[r.p];
+    constexpr int AHEAD = 8;
+    for (uint32_t base = tid; base < entries; base += AHEAD * kSortBlock) {
+      uint32_t d[AHEAD];
+#pragma unroll
+      for (int q = 0; q < AHEAD; ++q) d[q] = (uint32_t)part[min(base + q * kSortBlock, entries - 1)];
+#pragma unroll
+      for (int q = 0; q < AHEAD; ++q) {
+        const uint32_t e = base + q * kSortBlock;
+        if (e < entries && e - r.begin >= r.count)  // (e < r.begin wraps)
+          atomicAdd((e < r.begin ? in_front : behind) + ((d[q] >> g.shift) & (digits - 1)), 1u);
+      }
+    }
+  }
   if (!g.first) {
 #pragma unroll
     for (int q = 0; q < R; ++q)
@@ -282,7 +326,7 @@ __global__ __launch_bounds__(kSortBlock) __attribute__((amdgpu_waves_per_eu(R ==
         }
     }
   }
-  for (int x = tid; x < kSortWaves * kMaxDigits / 2; x += kSortBlock) reinterpret_cast<uint32_t *>(rank_of)[x] = 0;
+  for (int x = tid; x < kSortWaves * kDigits / 2; x += kSortBlock) reinterpret_cast<uint32_t *>(rank_of)[x] = 0;
   __syncthreads();
   uint16_t *const mine = rank_of[wave];
   uint32_t rank[R];  // entries of the same digit in front, within the wave
@@ -290,7 +334,7 @@ __global__ __launch_bounds__(kSortBlock) __attribute__((amdgpu_waves_per_eu(R ==
   for (int q = 0; q < R; ++q) {
     const bool live = first + q * kWave + lane < r.count;
     const uint32_t digit = ((uint32_t)key[q] >> g.shift) & (digits - 1);
-    const uint64_t mask = same_digit(digit, g.bits, live);
+    const uint64_t mask = same_digit<BITS>(digit, g.bits, live);
     const uint64_t below = mask & ((1ull << lane) - 1ull);
     const uint32_t before = mine[digit];
     rank[q] = before + (uint32_t)__popcll(below);
@@ -301,11 +345,11 @@ __global__ __launch_bounds__(kSortBlock) __attribute__((amdgpu_waves_per_eu(R ==
   __syncthreads();
   {
     // places of the digits in the tile, and of the part's digits in the part: thread t takes digits
-    // 2 t and 2 t + 1
-    constexpr int PER = kMaxDigits / kSortBlock;
+    // 2 t and 2 t + 1 (8 t and so on of 4096)
+    constexpr int PER = kDigits / kSortBlock;
     const uint32_t *hist = g.hist + ((uint64_t)tile << g.bits), *total = g.total + ((uint64_t)r.p << g.bits);
     uint32_t in_tile[PER], in_part[PER], before[PER], all = 0, all_part = 0;
-    if constexpr (FEW) {
+    if constexpr (C == kTiles) {
       // (all counts of the part, of which there are few, instead of a launch that adds them up)
 #pragma unroll
       for (int q = 0; q < PER; ++q) before[q] = in_part[q] = 0;
@@ -318,7 +362,7 @@ __global__ __launch_bounds__(kSortBlock) __attribute__((amdgpu_waves_per_eu(R ==
           before[q] += t < r.tile ? c : 0u;
           in_part[q] += c;
         }
-    } else {
+    } else if constexpr (C == kScanned) {
 #pragma unroll
       for (int q = 0; q < PER; ++q) {
         before[q] = hist[min(tid * PER + q, digits - 1)];
@@ -326,12 +370,15 @@ __global__ __launch_bounds__(kSortBlock) __attribute__((amdgpu_waves_per_eu(R ==
       }
     }
 #pragma unroll
-    for (int q = 0; q < PER; ++q)
-      if (tid * PER + q >= digits) in_part[q] = 0;
-#pragma unroll
     for (int q = 0; q < PER; ++q) {
       in_tile[q] = 0;
       for (int w = 0; w < kSortWaves; ++w) in_tile[q] += rank_of[w][tid * PER + q];
+      if constexpr (C == kKeys) {
+        const int d = min(tid * PER + q, digits - 1);
+        before[q] = in_front[d];
+        in_part[q] = in_front[d] + in_tile[q] + behind[d];
+      }
+      if (tid * PER + q >= digits) in_part[q] = 0;
       all += in_tile[q];
       all_part += in_part[q];
     }
@@ -580,10 +627,12 @@ int transpose_frame(const pipad_frame *f, pipad_alloc_fn alloc, void *alloc_ctx,
   s.tile_off[k + 1] = (uint32_t)tiles;
   uint32_t most_tiles = 0;
   for (int p = 0; p <= k; ++p) most_tiles = std::max(most_tiles, s.tile_off[p + 1] - s.tile_off[p]);
-  const bool few = per_thread == 4 && most_tiles <= kFewTiles;
   int bits = 1;
   while (((int64_t)1 << bits) < n) ++bits;
-  const int passes = bits <= kMaxDigitBits - 1 ? 1 : (bits + kMaxDigitBits - 1) / kMaxDigitBits;
+  const bool few = per_thread == 4 && most_tiles <= kFewTiles;
+  const bool keys = few && most_tiles <= (bits > kMostDigitBits ? kCountTiles : kCountTilesOnce);
+  const bool wide = keys && bits > kMaxDigitBits && bits <= kMostDigitBits;  // digits of more than 10 bits
+  const int passes = wide ? 1 : (bits + kMaxDigitBits - 1) / kMaxDigitBits;
   s.bits = (bits + passes - 1) / passes;
 
   Arena tmp;
@@ -594,8 +643,8 @@ int transpose_frame(const pipad_frame *f, pipad_alloc_fn alloc, void *alloc_ctx,
   tmp.want(&key_b, passes > 1 ? (size_t)total : 0);
   tmp.want(&val_a, passes > 1 ? (size_t)total : 0);
   tmp.want(&val_b, passes > 2 ? (size_t)total : 0);
-  tmp.want(&s.hist, (size_t)tiles << s.bits);
-  tmp.want(&s.total, (size_t)s.nparts << s.bits);
+  tmp.want(&s.hist, keys ? 0 : (size_t)tiles << s.bits);
+  tmp.want(&s.total, few ? 0 : (size_t)s.nparts << s.bits);
   tmp.want(&row_cnt, row_count_slots(n));
   tmp.want(&row_pre, row_count_slots(n));
   tmp.want(&totals, 1);
@@ -645,13 +694,15 @@ int transpose_frame(const pipad_frame *f, pipad_alloc_fn alloc, void *alloc_ctx,
       s.val_out = pass % 2 == 0 ? val_a : val_b;
       auto hist = per_thread == 16 ? k_radix_hist<16> : per_thread == 8 ? k_radix_hist<8> : k_radix_hist<4>;
       auto scatter = per_thread == 16 ? k_radix_scatter<16> : per_thread == 8 ? k_radix_scatter<8>
-                     : few             ? k_radix_scatter<4, true>
+                     : wide            ? (s.bits > 11 ? k_radix_scatter<4, kKeys, 12> : k_radix_scatter<4, kKeys, 11>)
+                     : keys            ? k_radix_scatter<4, kKeys>
+                     : few             ? k_radix_scatter<4, kTiles>
                                        : k_radix_scatter<4>;
       const int64_t copiers = pass == 0 ? std::min<int64_t>((s.dinv_pieces + kSortBlock - 1) / kSortBlock, 2048) : 0;
-      hipLaunchKernelGGL(hist, dim3((unsigned)(tiles + copiers)), dim3(kSortBlock), 0, st, s);
+      if (!keys) hipLaunchKernelGGL(hist, dim3((unsigned)(tiles + copiers)), dim3(kSortBlock), 0, st, s);
       if (!few)
         hipLaunchKernelGGL(k_radix_scan, grid1(1 << s.bits, kWave, k + 1), dim3(kScanWaves * kWave), 0, st, s);
-      hipLaunchKernelGGL(scatter, dim3((unsigned)align_xcd((int32_t)tiles)), dim3(kSortBlock), 0, st, s);
+      hipLaunchKernelGGL(scatter, dim3((unsigned)(align_xcd((int32_t)tiles) + (keys ? copiers : 0))), dim3(kSortBlock), 0, st, s);
       PIPAD_TRY_T(hipGetLastError());
       sorted_keys = s.key_out;
     }

@@ -47,3 +47,29 @@ def test_parts_against_a_sort(pipad, n, nnz, k):  # noqa: F811
     assert torch.equal(frame.dinv(), back.dinv())
     back.close()
     frame.close()
+
+
+# 8 and 32 tiles of 2048 entries are the last whose digits are counted by the sort itself (10 bits and more nodes than 4096, up to
+# 4096 nodes); digits of 10, 11 and 12 bits, then two
+@pytest.mark.parametrize("n,entries", [(1024, 8 * 2048), (1025, 32 * 2048), (1025, 32 * 2048 + 1), (2048, 2047), (2049, 2049), (4096, 32 * 2048),
+                                       (4096, 32 * 2048 + 1), (4097, 8 * 2048), (4097, 8 * 2048 + 1), (60_000, 8 * 2048 - 1)])
+@pytest.mark.parametrize("skewed", [False, True])
+def test_digits_counted_by_the_sort(pipad, n, entries, skewed):  # noqa: F811
+    rng = np.random.default_rng(n + entries)
+    cols = (n * rng.random(4 * entries) ** (3 if skewed else 1)).astype(np.int64)
+    key = np.unique(rng.integers(0, n, 4 * entries) * n + cols)
+    key = rng.permutation(key[key // n != key % n])[:entries]
+    key = torch.from_numpy(np.sort(key)).cuda()
+    assert len(key) == entries
+    half = key[torch.arange(entries, device="cuda:0") % 2 == 0]
+    for keys in ([key], [key, half, half]):
+        frame = pipad.frame_build_overlap([csr_of(n, q) for q in keys])
+        back = pipad.frame_transpose(frame)
+        for part in [None, *range(len(keys))]:
+            rp, col = frame.common() if part is None else frame.delta(part)
+            want = transposed(n, torch.repeat_interleave(torch.arange(n, device="cuda:0"), torch.diff(rp.long())) * n + col.long())
+            got = back.common() if part is None else back.delta(part)
+            assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]), part
+        assert torch.equal(frame.dinv(), back.dinv())
+        back.close()
+        frame.close()
