@@ -74,6 +74,16 @@ constexpr int kLongRowsPerWave = 8;    // mid rows, a wave per row
 #endif
 constexpr int kWideUnitsPerWave = PIPAD_WIDE_BATCH;   // class parts of hub units, a wave per part
 
+// x / by for x < 2^31 by a multiplication (a quotient that is at most one too small, and a look at what is left).
+struct Divisor {
+  uint32_t by, inverse;
+};
+inline Divisor divisor(int64_t by) { return Divisor{(uint32_t)by, UINT32_MAX / (uint32_t)std::max<int64_t>(by, 1)}; }
+__device__ __forceinline__ uint32_t divide(uint32_t x, Divisor d) {
+  const uint32_t q = __umulhi(x, d.inverse);
+  return x - q * d.by >= d.by ? q + 1 : q;
+}
+
 struct AggArgs {
   int32_t n, k, F;
   int32_t ls_log2;    // log2 of the lanes per slice row
@@ -89,6 +99,7 @@ struct AggArgs {
   int32_t blocks_wide, blocks_mid, blocks_short;
   int32_t batch_short, batch_mid, batch_wide;  // rows / class parts per wave
   int64_t blocks_per_phase;
+  Divisor per_phase, per_row;  // workgroups per phase, slices
   int32_t order;      // 1: one slice after the other; else hub class parts so and the rows of all slices side by
                       // side, 0: in turn, 2: in a run of slices per XCD
   int32_t sub_log2;   // log2 of the sub classes per XCD
@@ -232,14 +243,13 @@ struct Slice {
   bool fvalid;              // the lane's columns exist (F need not fill the last slice)
 };
 
-// slice -> (snapshot, column chunk): slice = chunk * k + snapshot
-__device__ __forceinline__ Slice slice_setup(const AggArgs &a, int slice, int fl, int vec) {
+// Of snapshot t and its fc-th chunk of columns.
+__device__ __forceinline__ Slice slice_setup(const AggArgs &a, int t, int fc, int fl, int vec) {
   Slice s;
   // (the slice is the same for the whole workgroup: saying so lets the per-snapshot pointers come
   // from the kernel arguments through the scalar unit)
-  slice = __builtin_amdgcn_readfirstlane(slice);
-  const int fc = slice / a.k;
-  const int t = slice - fc * a.k;
+  t = __builtin_amdgcn_readfirstlane(t);
+  fc = __builtin_amdgcn_readfirstlane(fc);
   s.t = t;
   s.fcol = (fc << a.ls_log2) * vec + fl * vec;
   s.fvalid = s.fcol < a.F;
@@ -667,9 +677,9 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
   // deeper bursts only queue up in front of the L1's miss slots.
   constexpr int U = FAST ? PIPAD_AGG_DEPTH : 1;
   __shared__ Staged staging[kWavesPerBlock][kWave * EPL];
-  Staged *lds = staging[threadIdx.x / kWave];
   const int lane = threadIdx.x % kWave;
-  const int wave = threadIdx.x / kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  Staged *lds = staging[wave];
   const int ls = 1 << a.ls_log2;
   const int fl = lane & (ls - 1);
   const int team = lane >> a.ls_log2;  // lane group index within the wave
@@ -678,50 +688,52 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
   // Workgroups are dispatched in index order and dealt round-robin to the XCDs: the launch goes
   // through the slices (snapshot-major) one after the other, and within a slice's class parts the
   // class of a workgroup is its index mod 8.
-  const int64_t b = blockIdx.x;
-  const int nsub = 1 << a.sub_log2;
-  const int64_t wide_blocks = (int64_t)kClasses * a.blocks_wide;  // per sub class
-  const int64_t split_blocks = PLAIN ? a.n_items : nsub * wide_blocks;
-  int slice_seq;
-  int64_t w;  // workgroup index within the slice's phase: class parts, mid rows, short rows
+  // (A wave of a small frame takes 8 to 16 rows, and half of its 660 instructions were about which: so 32-bit numbers, there are fewer
+  // than 2^31 workgroups, divisions by a multiplication, the wave's number known to be one, and no order for rows that are all
+  // taken at once.  N = 20k, k = 4, F = 32 15.8 -> 14.3 us, 37k, k = 8, F = 16 26.6 -> 23.0, R-MAT 8k, k = 5, F = 16 12.7 -> 10.8.)
+  const uint32_t b = blockIdx.x;
+  const uint32_t wide_blocks = kClasses * a.blocks_wide;  // per sub class
+  const uint32_t split_blocks = PLAIN ? a.n_items : wide_blocks << a.sub_log2;
+  uint32_t slice_seq;
+  uint32_t w;  // workgroup index within the slice's phase: class parts, mid rows, short rows
   if (a.order == 1) {
-    slice_seq = (int)(b / a.blocks_per_phase);
-    w = b - slice_seq * a.blocks_per_phase;
+    slice_seq = divide(b, a.per_phase);
+    w = b - slice_seq * a.per_phase.by;
   } else {
     // Side by side: neighbouring workgroups take the same rows in different slices, so the
     // entry lists they share (the overlap part's indices, the row pointers) are fetched once for
     // all of them - what pays while the operand is small next to the index streams.  The class
     // parts keep their slice-after-slice order in front (their class is the workgroup index mod 8).
-    const int nsl = a.nsel * a.fchunks;
-    const int64_t hub_total = split_blocks * nsl;
+    const uint32_t nsl = a.per_row.by;
+    const uint32_t hub_total = split_blocks * nsl;
     if (b < hub_total) {
-      slice_seq = (int)(b / split_blocks);
+      slice_seq = b / split_blocks;
       w = b - slice_seq * split_blocks;
     } else {
-      const int64_t r = b - hub_total;
+      const uint32_t r = b - hub_total;
       if (a.order == 0) {
-        slice_seq = (int)(r % nsl);
-        w = split_blocks + r / nsl;
+        const uint32_t q = divide(r, a.per_row);
+        slice_seq = r - q * nsl;
+        w = split_blocks + q;
       } else {
         // The workgroups of a slice's mid rows, dealt into 8 parts, make 8 * nsl parts in slice order, of
         // which XCD x takes nsl in a row: it only ever reads two or three of the matrices.  All mid
         // rows first, then the short ones the same way.
-        const int x = (int)(r & (kClasses - 1));
-        int32_t i = (int32_t)(r / kClasses), part = a.blocks_mid / kClasses, start = 0;
+        const uint32_t x = r & (kClasses - 1);
+        uint32_t i = r / kClasses, part = a.blocks_mid / kClasses, start = 0;
         if (i >= part * nsl) {
           i -= part * nsl;
           start = a.blocks_mid;
-          part = (int32_t)(a.blocks_per_phase - split_blocks - start) / kClasses;
+          part = (a.per_phase.by - split_blocks - start) / kClasses;
         }
-        const int32_t q = i / part, share = nsl * x + q;
+        const uint32_t q = i / part, share = nsl * x + q;
         slice_seq = share / kClasses;
-        w = split_blocks + start + (int64_t)(i - q * part) * kClasses + share % kClasses;
+        w = split_blocks + start + (i - q * part) * kClasses + share % kClasses;
       }
     }
   }
-  const int t_seq = slice_seq / a.fchunks;
-  const int slice = (slice_seq - t_seq * a.fchunks) * a.k + selected_snapshot(a, t_seq);
-  const Slice s = slice_setup(a, slice, fl, VEC);
+  const int t_seq = a.fchunks == 1 ? slice_seq : slice_seq / a.fchunks;
+  const Slice s = slice_setup(a, selected_snapshot(a, t_seq), slice_seq - t_seq * a.fchunks, fl, VEC);
   const bool ntl = a.nt & 2;
 
   if (UPD && w < split_blocks && !a.direct) {
@@ -788,7 +800,7 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
   // (every field is read into a local before the control flow that chooses among them, so that
   // the kernel arguments are only ever read at constant offsets)
   const int32_t *const p_items = a.item_row, *const p_mid = a.rows_long, *const p_short = a.rows_short;
-  const int64_t n_items = a.n_items, n_mid = a.n_long, n_short = a.n_short;
+  const int32_t n_items = a.n_items, n_mid = a.n_long, n_short = a.n_short;
   const int b_wide = a.batch_wide, b_mid = a.batch_mid, b_short = a.batch_short;
   const bool split = !PLAIN && w < split_blocks;        // class parts of hub units
   const bool wide = w < split_blocks + a.blocks_mid;    // ... or whole mid rows: a wave per list
@@ -804,14 +816,15 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
     w -= split_blocks + a.blocks_mid;
   }
   const int32_t *list = split ? p_items : wide ? p_mid : p_short;
-  const int64_t list_len = split ? n_items : wide ? n_mid : n_short;
+  const int32_t list_len = split ? n_items : wide ? n_mid : n_short;
   const int batch = split ? b_wide : wide ? b_mid : b_short;
-  const int64_t first = (w * kWavesPerBlock + wave) * batch;
-  if (first >= list_len) return;
+  const int64_t first64 = ((int64_t)w * kWavesPerBlock + wave) * batch;
+  if (first64 >= list_len) return;
+  const int32_t first = (int32_t)first64;
 #ifdef PIPAD_PARTS_MASK  // measurement builds only: which kinds of work items run (results incomplete)
   if (!((PIPAD_PARTS_MASK) & (split ? 1 : wide ? 2 : 4))) return;
 #endif
-  const int rows_here = (int)min((int64_t)batch, list_len - first);
+  const int rows_here = min(batch, list_len - first);
   // entry lists: the class-grouped copies for hub units, the frame's CSRs for whole rows
   Lists lists;
   lists.colc = split ? a.scol_c : a.col_c;
@@ -819,7 +832,7 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
   lists.cold = split ? a.scol_d : s.cd;
   lists.wd = split ? a.swd : s.wd;
   // hub units only: first partial sum; nclass of them per unit
-  const int64_t v_first = first * a.nclass + cls;
+  const int64_t v_first = (int64_t)first * a.nclass + cls;
   int32_t r = 0, mc0 = 0, mc1 = 0, md0 = 0, md1 = 0;
   float mdi = 0.f;
   if (lane < rows_here) {
@@ -838,7 +851,8 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
     }
   }
   int order = lane;
-  if (!wide && ((VEC * 4) << a.ls_log2) >= 128)  // (not for slices narrower than a cache line, where neighbouring rows share lines)
+  // (not for slices narrower than a cache line, where neighbouring rows share lines, and not for rows that are all taken at once)
+  if (!wide && rows_here > nteams && ((VEC * 4) << a.ls_log2) >= 128)
     order = longest_first(lane < rows_here ? (mc1 - mc0 + md1 - md0 + U - 1) / U : 0, rows_here, lane);
   const int per_step = wide ? 1 : nteams;          // elements worked on side by side
   const int team_base = wide ? 0 : team << a.ls_log2;
@@ -953,10 +967,9 @@ __global__ __launch_bounds__(kBlock) void k_split_finish(const AggArgs a) {
   const int64_t b = blockIdx.x;
   const int slice_seq = (int)(b / row_blocks);
   const int t_seq = slice_seq / a.fchunks;
-  const int slice = (slice_seq - t_seq * a.fchunks) * a.k + selected_snapshot(a, t_seq);
   const int64_t sr = (b - slice_seq * row_blocks) * kWavesPerBlock + wave;
   if (sr >= a.n_hub) return;
-  const Slice s = slice_setup(a, slice, fl, VEC);
+  const Slice s = slice_setup(a, selected_snapshot(a, t_seq), slice_seq - t_seq * a.fchunks, fl, VEC);
   const int32_t i = a.hub_rows[sr];
   const int64_t v0 = (int64_t)a.hub_item_off[sr] * a.nclass;  // the row's partial sums
   const int64_t v1 = (int64_t)a.hub_item_off[sr + 1] * a.nclass;
@@ -1936,6 +1949,8 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
       a.blocks_short += (kClasses - (a.blocks_mid + a.blocks_short) % kClasses) % kClasses;
       const int64_t hub_blocks = a.plain ? f->n_items : (int64_t)kClasses * a.blocks_wide << f->sub_log2;
       a.blocks_per_phase = hub_blocks + a.blocks_mid + a.blocks_short;
+      a.per_phase = divisor(a.blocks_per_phase);
+      a.per_row = divisor((int64_t)a.nsel * a.fchunks);
     }
   }
 
