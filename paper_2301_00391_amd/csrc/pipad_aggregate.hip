@@ -353,7 +353,7 @@ __device__ __forceinline__ void add_step(const float (&w)[N], const typename V<V
     static_assert(N == 4, "");
     typename VT::T p[N];
 #pragma unroll
-    for (int j = 0; j < N; ++j) p[j] = S == kProducts ? VT::product(w[j], x[j]) : w[j] != 0.f ? x[j] : VT::zero();
+    for (int j = 0; j < N; ++j) p[j] = w[j] == 0.f ? VT::zero() : S == kProducts ? VT::product(w[j], x[j]) : x[j];  // (a filler may be infinite)
     VT::add(p[0], p[1]);
     VT::add(p[2], p[3]);
     VT::add(p[0], p[2]);

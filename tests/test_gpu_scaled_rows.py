@@ -107,3 +107,34 @@ def test_entries_shared_by_a_quad(pipad, k, F, classes):  # noqa: F811
         assert torch.equal(out, y)
     frame.close()
     fresh.close()
+
+
+@pytest.mark.parametrize("F", [2, 5])
+def test_infinite_rows_are_infinite_either_way(pipad, F):  # noqa: F811
+    """What fills up a step of four entries is the row itself with weight 0 where the kernel makes the products: it takes no part."""
+    n, k = 6000, 7
+    pipad.set_option("agg_coalescent", 2)
+    lists = power_law(n, 350_000, k, F)
+    assert 3 * k * min(len(c) for _, c in lists) > 10_000_000 + k * n * (4 * F + 1)
+    frame = pipad.frame_build_overlap([(torch.from_numpy(rp).cuda(), torch.from_numpy(c).cuda()) for rp, c in lists])
+    x = torch.empty((n, k, F), device="cuda:0").uniform_(-1, 1)
+    x[::50] = float("inf")
+    y = pipad.frame_aggregate(frame, x)
+    assert not y.isnan().any() and y[::50].isinf().all()
+    assert torch.equal(pipad.frame_aggregate(frame, x, static_scratch=True), y)
+    # recorded with room for the partial sums and no more
+    fresh = pipad.frame_build_overlap([(torch.from_numpy(rp).cuda(), torch.from_numpy(c).cuda()) for rp, c in lists])
+    parts = [torch.zeros((n, F), device="cuda:0") for _ in range(k)]
+    pipad.frame_aggregate(fresh, parts, [torch.empty_like(p) for p in parts])
+    torch.cuda.synchronize()
+    out = torch.full_like(y, float("nan"))
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        pipad.frame_aggregate(fresh, x, out)
+    for _ in range(2):
+        out.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, y)
+    frame.close()
+    fresh.close()
