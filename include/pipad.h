@@ -148,19 +148,21 @@ int pipad_frame_shape(const pipad_frame_t *frame, int32_t *n, int32_t *k);
  *        (columns >= F of a wider row are not touched).  Y must not overlap X.
  *   The current HIP device must be the one the frame was built on (else PIPAD_ERR_INVALID_ARG).
  *   The frame is only read, except for its scratch buffer (hence the non-const pointer): the
- *   partial sums of rows that are summed in several parts go through it, and on the concatenated
- *   operand with few columns, in frames with many entries, the operand times its scales (4 bytes per
- *   element, rows padded to a power of two up to 128 bytes; 1 GiB at most).  The first call of a
- *   frame, and any call with a larger k*F than all before or the first of its form, allocates it (through the frame's
+ *   partial sums of rows that are summed in several parts go through it.  The first call of a
+ *   frame, and any call with a larger k*F than all before, allocates it (through the frame's
  *   allocator; with the library's own allocator a buffer that is replaced is freed after a
- *   hipDeviceSynchronize).  All other calls only enqueue kernels on `stream`, without host
+ *   hipDeviceSynchronize).  On the concatenated operand with few columns, in frames with many
+ *   entries, the operand times its scales goes through a second buffer (4 bytes per element, rows
+ *   padded to a power of two up to 128 bytes; 1 GiB at most), which the first such call allocates
+ *   and such a call with a larger one replaces; what is replaced, at most half as large, stays with
+ *   the frame until pipad_frame_destroy().  All other calls only enqueue kernels on `stream`, without host
  *   synchronisation, so they can be recorded into a HIP graph (stream capture) once an eager call
  *   with the same or a larger k*F has sized the scratch, whichever form (one matrix per snapshot,
  *   concatenated, with the update) either of them has.  A recorded call whose form takes more than
  *   the eager one left (rows padded to the slice width do, and the scaled operand) makes do with it, in
  *   several launches or without the scaled operand, with the same bits; a call with a larger k*F than all before, which would have to allocate while
  *   `stream` is being captured, returns PIPAD_ERR_SCRATCH with nothing enqueued.
- *   Two aggregations of the SAME frame must not run concurrently (they share that scratch).
+ *   Two aggregations of the SAME frame must not run concurrently (they share the scratch).
  *   Results are deterministic: same inputs, same bits.
  */
 int pipad_frame_aggregate(pipad_frame_t *frame, int32_t F, const float *const *X, int64_t ldx,

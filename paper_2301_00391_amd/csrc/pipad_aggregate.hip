@@ -1678,6 +1678,11 @@ int static_scratch(float **ptr, size_t *floats) {
   return PIPAD_OK;
 }
 
+constexpr int64_t kTableFloats = (int64_t)1 << 28;  // of kTable's table: 1 GiB at most
+// It starts so far into its memory: allocations start at multiples of 2 MB, and with a row of the products at the same place in
+// them as the operand's R-MAT 1M, k = 8, F = 2 takes 351 us, not 343.5 (3 MB in 344.5).
+constexpr size_t kTableSkip = 16384 + 448;
+
 int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int64_t ldx,
                      float *const *Y, int64_t ldy, hipStream_t st, ScratchRef scratch,
                      const UpdateSpec *upd, const int32_t *subset, int32_t nsubset) {
@@ -1822,7 +1827,7 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
     const int64_t cols = (int64_t)f->k * F;
     // row stride: up to a cache line so that hardly any row lies on two, else whole 16 bytes
     a.ldt = cols > 32 ? (cols + 3) / 4 * 4 : cols > 8 && cols <= 12 ? 12 : (int64_t)4 << ceil_log2((cols + 3) / 4);
-    a.products = 3 * f->k * entries > 10000000 + (int64_t)f->k * f->n * (4 * F + 1) && (int64_t)f->n * a.ldt * 4 <= ((int64_t)1 << 30);
+    a.products = 3 * f->k * entries > 10000000 + (int64_t)f->k * f->n * (4 * F + 1) && f->n * a.ldt <= kTableFloats;
   }
   // slice geometry: LS lanes of VEC columns each, 64 columns per slice (a gathered piece of a row is then
   // at most 256 bytes: two cache lines) or 128.  Rows of 65 to 128 columns go in one slice where
@@ -1962,20 +1967,33 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
   // It cannot grow where it is the fixed array, and not while the stream is being captured into a graph:
   // growing means allocating.  Captured, a call with a larger k * F than all before is refused; with
   // no larger one it is only the padding of its slices that can be missing.
-  bool fixed = scratch.fixed;
-  if ((table ? sums + table : need) > *scratch.floats && !fixed) {
+  bool fixed = !scratch.frame;
+  if (!fixed && (need > *scratch.floats || table > f->table_floats)) {
     hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &capturing) != hipSuccess) (void)hipGetLastError();
     fixed = capturing != hipStreamCaptureStatusNone;
     if (fixed && (size_t)a.nvp * (size_t)a.nsel * (size_t)F > *scratch.floats) return PIPAD_ERR_SCRATCH;
   }
-  // (without room for the table the kernel makes its products itself)
-  const bool use_table = table && (sums + table <= *scratch.floats || !fixed);
-  if (use_table) need = sums + table;
+  // The table goes behind the sums in the fixed array, into memory of its own otherwise.  Without room for it the kernel makes its
+  // products itself.
+  if (table && !scratch.frame) {
+    if (sums + table <= *scratch.floats) a.table = *scratch.ptr + sums;
+  } else if (table) {
+    if (table > f->table_floats && !fixed) {
+      const size_t floats = std::max(table, std::min<size_t>(2 * f->table_floats, kTableFloats));
+      pipad_frame *const to = scratch.frame;
+      if (void *ptr = Allocator{to->alloc, to->alloc_ctx, to}.get((kTableSkip + floats) * sizeof(float))) {
+        to->table = static_cast<float *>(ptr) + kTableSkip;
+        to->table_floats = floats;
+      }
+    }
+    if (table <= f->table_floats) a.table = f->table;
+  }
   if (need > *scratch.floats && fixed) {
     if (coalescent) {
       // one partial sum per hub unit then, the same sums
       a.whole_units = 1;
+      a.table = nullptr;  // (without the products: the same bits)
       need /= (size_t)a.nclass;
       if (need > *scratch.floats) return PIPAD_ERR_SCRATCH;
     } else {
@@ -2019,7 +2037,6 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
     *scratch.floats = need;
   }
   a.partial = *scratch.ptr;
-  if (use_table) a.table = a.partial + sums;
   if (coalescent)
     return cvec == 4 ? launch_coalescent<4>(a, st)
                      : cvec == 2 ? launch_coalescent<2>(a, st) : launch_coalescent<1>(a, st);

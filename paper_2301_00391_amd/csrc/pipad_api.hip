@@ -95,9 +95,9 @@ int pipad_frame_aggregate(pipad_frame_t *frame, int32_t F, const float *const *X
     if (hipGetDevice(&dev) != hipSuccess) return pipad::hip_fail(hipGetLastError(), "hipGetDevice");
     if (dev != frame->device) return PIPAD_ERR_INVALID_ARG;  // frames are tied to their GPU
   }
-  // the frame's scratch buffer is the only state an aggregation changes
+  // the frame's scratch buffers are the only state an aggregation changes
   return pipad::aggregate_launch(frame, F, X, ldx, Y, ldy, static_cast<hipStream_t>(stream),
-                                 pipad::ScratchRef{&frame->partial, &frame->partial_floats, false});
+                                 pipad::ScratchRef{&frame->partial, &frame->partial_floats, frame});
 }
 
 int pipad_frame_aggregate_subset(pipad_frame_t *frame, int32_t nsel, const int32_t *snapshots,
@@ -127,7 +127,7 @@ int pipad_frame_aggregate_subset(pipad_frame_t *frame, int32_t nsel, const int32
     ys[snapshots[q]] = Y[snapshots[q]];
   }
   return pipad::aggregate_launch(frame, F, xs, ldx, ys, ldy, static_cast<hipStream_t>(stream),
-                                 pipad::ScratchRef{&frame->partial, &frame->partial_floats, false},
+                                 pipad::ScratchRef{&frame->partial, &frame->partial_floats, frame},
                                  nullptr, snapshots, nsel);
 }
 
@@ -148,7 +148,7 @@ int pipad_frame_aggregate_static(const pipad_frame_t *frame, int32_t F, const fl
   const int rc = pipad::static_scratch(&scratch_ptr, &scratch_floats);
   if (rc != PIPAD_OK) return rc;
   return pipad::aggregate_launch(frame, F, X, ldx, Y, ldy, static_cast<hipStream_t>(stream),
-                                 pipad::ScratchRef{&scratch_ptr, &scratch_floats, true});
+                                 pipad::ScratchRef{&scratch_ptr, &scratch_floats, nullptr});
 }
 
 int pipad_frame_aggregate_update(pipad_frame_t *frame, int32_t F, const float *const *X,
@@ -172,7 +172,7 @@ int pipad_frame_aggregate_update(pipad_frame_t *frame, int32_t F, const float *c
   }
   pipad::UpdateSpec u{W, ldw, bias, Fo, H, ldh};
   return pipad::aggregate_launch(frame, F, X, ldx, A, A ? lda : F, static_cast<hipStream_t>(stream),
-                                 pipad::ScratchRef{&frame->partial, &frame->partial_floats, false}, &u);
+                                 pipad::ScratchRef{&frame->partial, &frame->partial_floats, frame}, &u);
 }
 
 int pipad_frame_transpose(const pipad_frame_t *frame, pipad_alloc_fn alloc, void *alloc_ctx,

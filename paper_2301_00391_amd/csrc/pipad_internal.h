@@ -119,6 +119,10 @@ struct pipad_frame {
   // per unit, none where every hub row is one unit), grown on demand.
   float *partial = nullptr;
   size_t partial_floats = 0;
+  // The concatenated operand times its scales (pipad_aggregate.hip, kTable), memory of its own: one that is replaced stays until the
+  // frame goes, as recorded calls may hold it, and what replaces it is twice as large or more, or as large as any.
+  float *table = nullptr;
+  size_t table_floats = 0;
 };
 
 namespace pipad {
@@ -290,7 +294,7 @@ struct UpdateSpec {
 struct ScratchRef {
   float **ptr;
   size_t *floats;
-  bool fixed;
+  pipad_frame *frame;  // it grows, and gets a table next to it, through this frame's allocator; null: a fixed array
 };
 // Y may be null when `update` is given and the shape allows the fused kernel.  The frame itself
 // is only read.

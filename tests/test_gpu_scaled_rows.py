@@ -138,3 +138,47 @@ def test_infinite_rows_are_infinite_either_way(pipad, F):  # noqa: F811
         assert torch.equal(out, y)
     frame.close()
     fresh.close()
+
+
+def test_recorded_calls_outlive_later_products(pipad):  # noqa: F811
+    """Calls recorded before one that needs (more) room for products still find theirs, with the library's own allocator, too."""
+    n, k = 6000, 7
+    pipad.set_option("agg_coalescent", 2)
+    pipad.set_option("mid_max", 300)
+    pipad.set_option("hub_segment", 700)
+    pipad.set_option("hub_threshold", 700)
+    lists = power_law(n, 350_000, k, 4)
+    snaps = [(torch.from_numpy(rp).cuda(), torch.from_numpy(c).cuda()) for rp, c in lists]
+    frame = pipad.frame_build_overlap(snaps, allocator="library")
+    x = {F: torch.empty((n, k, F), device="cuda:0").uniform_(-1, 1) for F in (2, 4, 5)}
+    shared = [x[5][:, t].contiguous() for t in range(k)]
+    lists_out = [torch.empty_like(m) for m in shared]
+    pipad.frame_aggregate(frame, shared, lists_out)
+    torch.cuda.synchronize()
+    recorded = []
+
+    def record(operand, out):
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            pipad.frame_aggregate(frame, operand, out)
+        recorded.append((graph, out))
+
+    record(shared, lists_out)
+    for F in (2, 4, 5):  # the list's scratch is large enough for all of them, their products take more and more
+        assert 3 * k * min(len(c) for _, c in lists) > 10_000_000 + k * n * (4 * F + 1)
+        out = torch.empty_like(x[F])
+        pipad.frame_aggregate(frame, x[F], out)
+        torch.cuda.synchronize()
+        record(x[F], out)
+    fresh = pipad.frame_build_overlap(snaps)
+    want = [pipad.frame_aggregate(fresh, shared)] + [pipad.frame_aggregate(fresh, x[F]) for F in (2, 4, 5)]
+    for _ in range(2):
+        for (graph, out), expected in zip(recorded, want):
+            outs, expected = (out, expected) if isinstance(out, list) else ([out], [expected])
+            for o in outs:
+                o.fill_(float("nan"))
+            graph.replay()
+            torch.cuda.synchronize()
+            assert all(torch.equal(o, e) for o, e in zip(outs, expected))
+    frame.close()
+    fresh.close()
