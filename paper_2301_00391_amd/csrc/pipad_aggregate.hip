@@ -1225,29 +1225,37 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_coalescent(const AggArgs a
   using VT = V<VEC>;
   constexpr int U = 4;  // row gathers in flight per lane
   __shared__ Staged staging[kWavesPerBlock][kWave * EPL];
-  Staged *lds = staging[threadIdx.x / kWave];
   const int lane = threadIdx.x % kWave;
-  const int wave = threadIdx.x / kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  Staged *lds = staging[wave];
   const int fl = lane & ((1 << a.ls_log2) - 1);
   const int team = lane >> a.ls_log2;
   const int nteams = kWave >> a.ls_log2;
 
   // Class parts first, one snapshot group after the other (the class's XCD is the workgroup index
   // mod 8); then the whole rows, the groups side by side: they share the entry lists.
-  const int64_t b = blockIdx.x;
-  const int64_t wide_blocks = (int64_t)kClasses * a.blocks_wide;  // per sub class
-  const int64_t split_blocks = PLAIN ? a.n_items : a.whole_units ? a.blocks_wide : wide_blocks << a.sub_log2;
-  const int64_t r0 = b - split_blocks * a.nslices;
-  const bool unit = r0 < 0;
+  // (32-bit numbers, a scalar for the wave and no division by one group: with 64-bit ones the instances for four columns without
+  // products took 100 registers, four waves per SIMD; now 94 to 96, five.  F = 16, concatenated: Chung-Lu 36k, k = 16 64.4 -> 57.8 us, 70k,
+  // k = 8 56.1 -> 50.0, 51k, k = 4 23.7 -> 21.8, R-MAT 759k, k = 2 190 -> 167, 201k, k = 12 399 -> 373; F = 2 and 5 0 to 1 %; 12k, k = 6,
+  // F = 15 19.1 -> 19.4.  Divisions by a multiplication, as in k_aggregate, are 1 to 3 % slower here.)
+  const uint32_t b = blockIdx.x;
+  const uint32_t wide_blocks = kClasses * a.blocks_wide;  // per sub class
+  const uint32_t split_blocks = PLAIN ? a.n_items : a.whole_units ? a.blocks_wide : wide_blocks << a.sub_log2;
+  const uint32_t unit_blocks = split_blocks * a.nslices;
+  const bool unit = b < unit_blocks;
   const bool split = !PLAIN && unit;
-  int g;  // snapshot group
-  int64_t w;
+  int g = 0;  // snapshot group
+  uint32_t w;
   if (unit) {
-    g = (int)(b / split_blocks);
+    if (a.nslices > 1) g = b / split_blocks;
     w = b - g * split_blocks;
   } else {
-    g = (int)(r0 % a.nslices);
-    w = r0 / a.nslices;
+    const uint32_t r0 = b - unit_blocks;
+    w = r0;
+    if (a.nslices > 1) {
+      w = r0 / (uint32_t)a.nslices;
+      g = r0 - w * a.nslices;
+    }
   }
 
   // this lane's place in the group's row: VEC columns of snapshot t (F need not be a multiple of
@@ -1310,12 +1318,12 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_coalescent(const AggArgs a
   }
 
   const int32_t *const p_items = a.item_row, *const p_mid = a.rows_long, *const p_short = a.rows_short;
-  const int64_t n_items = a.n_items, n_mid = a.n_long, n_short = a.n_short;
+  const int32_t n_items = a.n_items, n_mid = a.n_long, n_short = a.n_short;
   const int b_wide = a.batch_wide, b_mid = a.batch_mid, b_short = a.batch_short;
-  const bool wide = split || w < a.blocks_mid;  // the whole wave on one list
+  const bool wide = split || w < (uint32_t)a.blocks_mid;  // the whole wave on one list
   int cls = 0;
   if (split && !a.whole_units) {
-    const int sub = (int)(w / wide_blocks);
+    const int sub = a.sub_log2 == 0 ? 0 : (int)(w / wide_blocks);
     w -= sub * wide_blocks;
     cls = ((int)(w & (kClasses - 1)) << a.sub_log2) + sub;
     w >>= 3;
@@ -1323,11 +1331,12 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_coalescent(const AggArgs a
     w -= a.blocks_mid;
   }
   const int32_t *list = split ? p_items : wide ? p_mid : p_short;
-  const int64_t list_len = split ? n_items : wide ? n_mid : n_short;
+  const int32_t list_len = split ? n_items : wide ? n_mid : n_short;
   const int batch = split ? b_wide : wide ? b_mid : b_short;
-  const int64_t first = (w * kWavesPerBlock + wave) * batch;
-  if (first >= list_len) return;
-  const int rows_here = (int)min((int64_t)batch, list_len - first);
+  const int64_t first64 = ((int64_t)w * kWavesPerBlock + wave) * batch;
+  if (first64 >= list_len) return;
+  const int32_t first = (int32_t)first64;
+  const int rows_here = min(batch, list_len - first);
 
   // entry lists: the class-grouped copies for hub units, the frame's CSRs for whole rows
   Lists lists;
@@ -1345,12 +1354,12 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_coalescent(const AggArgs a
   int32_t r = 0, mc0 = 0, mc1 = 0;
   if (lane < rows_here) {
     r = list[first + lane];
-    const int32_t *pc = split ? a.sptr + (int64_t)cls * n_items + first + lane : a.rowptr_c + r;
+    const int32_t *pc = split ? a.sptr + ((int64_t)cls * n_items + first + lane) : a.rowptr_c + r;
     mc0 = pc[0];
     mc1 = pc[split ? n_items : 1];
   }
   int order = lane;
-  if (!wide && a.longest_first && batch > nteams)
+  if (!wide && a.longest_first && rows_here > nteams)
     order = longest_first(lane < rows_here ? (mc1 - mc0 + U - 1) / U : 0, rows_here, lane);  // (by the common entries)
   const int per_step = wide ? 1 : nteams;
   const int team_lanes = wide ? nteams * fetchers : fetchers;
