@@ -226,8 +226,8 @@ int pipad_frame_aggregate_static(const pipad_frame_t *frame, int32_t F, const fl
  *          or NULL when they are not wanted.  NULL is only possible where the update is fused
  *          into the aggregation kernel: F and Fo multiples of 4 resp. 16 with 16 <= F, Fo <= 64,
  *          16-byte aligned X (and A) with ldx (lda) a multiple of 4, and a snapshot matrix below
- *          4 GiB.  With A other Fo <= 64 may be fused, too; the rest run the aggregation into A and then
- *          a separate multiplication; without A they return PIPAD_ERR_INVALID_ARG.
+ *          4 GiB.  With A other Fo <= 64 may be fused, too, and some of these are not; what is not runs the
+ *          aggregation into A and then a separate multiplication; without A they return PIPAD_ERR_INVALID_ARG.
  *   H      host array of k device pointers, row stride ldh >= Fo; written once per element.
  *          H, A, X, W must not overlap.
  *   Stream, device, scratch and determinism rules are those of pipad_frame_aggregate.

@@ -66,3 +66,52 @@ def test_blocks_of_columns_by_the_size_of_the_frame(pipad, n, k, F, Fo):  # noqa
         exact = A[t].double() @ W.double() + b.double()
         bound = A[t].double().abs() @ W.double().abs() + b.double().abs()
         assert bool(((H[t].double() - exact).abs() <= (F + 2) * 2.0 ** -24 * bound).all())
+
+
+@pytest.mark.parametrize("n,k,F,Fo,per_row", [(7_249, 2, 48, 48, 3), (7_251, 2, 48, 48, 3), (1_499, 10, 64, 64, 3), (1_501, 10, 36, 64, 3),
+                                              (11_999, 2, 64, 32, 25), (12_001, 2, 64, 32, 25),
+                                              (12_001, 2, 36, 16, 8), (28_990, 2, 64, 64, 12), (29_010, 2, 64, 64, 12)])
+def test_few_rows_and_whole_tiles_of_columns(pipad, n, k, F, Fo, per_row):  # noqa: F811
+    """Both sides of the numbers of rows from and up to which widths of whole tiles are multiplied behind the aggregation, where it
+    is kept; without room for it they stay inside.  Eager and recorded, at the scratch the aggregation leaves."""
+    rng = np.random.default_rng(n + Fo)
+    pool = np.concatenate([rand_pairs(rng, n, per_row * n), np.stack([np.full(900, 17), rng.integers(0, n, 900)], 1)])
+    lists = [csr(n, pool[rng.random(len(pool)) < 0.9]) for _ in range(k)]
+    snaps = [(torch.from_numpy(rp).cuda(), torch.from_numpy(c).cuda()) for rp, c in lists]
+    X = [torch.empty((n, F), device="cuda:0").uniform_(-1, 1) for _ in range(k)]
+    W, b = torch.empty((F, Fo), device="cuda:0").uniform_(-1, 1), torch.empty(Fo, device="cuda:0").uniform_(-1, 1)
+    for segment in (700, 300):  # hub rows in parts, too
+        pipad.set_option("mid_max", segment)
+        pipad.set_option("hub_segment", segment)
+        pipad.set_option("hub_threshold", segment)
+        frame = pipad.frame_build_overlap(snaps)
+        Y = pipad.frame_aggregate(frame, X)
+
+        def check(H, A):
+            for t in range(k):
+                assert A is None or torch.equal(A[t], Y[t])
+                exact = Y[t].double() @ W.double() + b.double()
+                bound = Y[t].double().abs() @ W.double().abs() + b.double().abs()
+                # (F products, F sums and the bias, each rounded once)
+                assert bool(((H[t][:, :Fo].double() - exact).abs() <= (F + 2) * 2.0 ** -24 * bound).all())
+                assert bool((H[t][:, Fo:] == 77.0).all())
+
+        for keep in (True, False):
+            wide = [torch.full((n, Fo + 4), 77.0, device="cuda:0") for _ in range(k)]
+            H = [h[:, :Fo] for h in wide]
+            A = [torch.zeros((n, F), device="cuda:0") for _ in range(k)] if keep else None
+            torch.cuda.synchronize()
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph):
+                pipad.frame_aggregate_update(frame, X, W, b, H=H, A=A)
+            for _ in range(2):
+                for m in H + (A or []):
+                    m.fill_(float("nan"))
+                graph.replay()
+                torch.cuda.synchronize()
+                check(wide, A)
+            for m in H + (A or []):
+                m.fill_(float("nan"))
+            pipad.frame_aggregate_update(frame, X, W, b, H=H, A=A)
+            check(wide, A)
+        frame.close()
