@@ -148,7 +148,7 @@ __device__ __forceinline__ float rounded(float w, float x) {
   return p;
 }
 
-// d * (a + d * x), rounded once.
+// d * (a + d * x) in 64 bits, rounded to 32 at the end.
 __device__ __forceinline__ float done(float d, float x, float a) {
   return (float)((double)d * ((double)a + (double)d * (double)x));
 }
@@ -1207,8 +1207,8 @@ __device__ __forceinline__ float *unit_partial(const AggArgs &a, int g, int64_t 
   return a.partial + col0 * (a.n_items * parts) + (unit * parts + cls) * width - col0;
 }
 
-// Self-loop term, row scale, store.  (With the products of kTable in one rounding, which is more than their own ones cost: the
-// error of whole results against 64 bits is below that of kStreams.)
+// Self-loop term, row scale, store.  (With the products of kTable in 64 bits up to the store, which saves more than their own
+// roundings cost: the error of whole results against 64 bits is below that of kStreams, also in rows that are summed up in parts.)
 template <int VEC, Scales S>
 __device__ __forceinline__ void finish_coalescent(float *y, float di, typename V<VEC>::T xi, typename V<VEC>::T acc, bool nt) {
   using VT = V<VEC>;
@@ -1503,8 +1503,10 @@ __global__ __launch_bounds__(kBlock) void k_hub_finish_coalescent(const AggArgs 
   reduce_slots<VEC>(a.ls_log2, acc);
   if (team == 0 && valid) {
     const float di = a.dinv[(int64_t)t * a.n + i];
-    VT::fma(acc, di, VT::load(a.X[0] + lane_col + (int64_t)i * a.ldx));
-    VT::store(a.Y[0] + lane_col + (int64_t)i * a.ldy, VT::scale(di, acc), a.nt & 1);
+    const typename VT::T xi = VT::load(a.X[0] + lane_col + (int64_t)i * a.ldx);
+    float *const y = a.Y[0] + lane_col + (int64_t)i * a.ldy;
+    if (a.products) finish_coalescent<VEC, kProducts>(y, di, xi, acc, a.nt & 1);
+    else finish_coalescent<VEC, kStreams>(y, di, xi, acc, a.nt & 1);
   }
 }
 

@@ -182,3 +182,29 @@ def test_recorded_calls_outlive_later_products(pipad):  # noqa: F811
             assert all(torch.equal(o, e) for o, e in zip(outs, expected))
     frame.close()
     fresh.close()
+
+
+@pytest.mark.parametrize("hubs,length,classes,F", [(600, 1500, True, 4), (600, 1500, True, 7), (190, 5000, False, 2), (190, 5000, False, 12)])
+def test_rows_in_parts_are_finished_in_64_bits(pipad, hubs, length, classes, F):  # noqa: F811
+    """Sums without a rounding (scales of 1/2, features of few bits): what is left is the finish of the rows, summed by column class
+    or in units, which has to be that of 64 bits rounded once."""
+    n, k = 8000, 4
+    pipad.set_option("agg_coalescent", 2)
+    if classes:
+        pipad.set_option("mid_max", 500)
+    rng = np.random.default_rng(hubs + F)
+    rows = [np.sort(rng.choice(n - hubs, length, replace=False) + hubs) for _ in range(hubs)]
+    few = (np.arange(n - hubs)[:, None] + np.arange(1, 4)) % (n - hubs) + hubs  # three entries each: scales of 1/2
+    rowptr = np.concatenate([[0], np.cumsum([length] * hubs + [3] * (n - hubs))]).astype(np.int32)
+    col = np.concatenate(rows + [np.sort(few, axis=1).ravel()]).astype(np.int32)
+    assert 3 * k * len(col) > 10_000_000 + k * n * (4 * F + 1)
+    snap = (torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
+    frame = pipad.frame_build_overlap([snap] * k, validate=True)
+    x = torch.from_numpy(rng.integers(-512, 513, (n, k, F)).astype(np.float32) / 512).cuda()
+    d = frame.dinv()[0].double().cpu().numpy()
+    xd = x.double().cpu().numpy()
+    want = np.stack([d[i] * ((d[rows[i], None, None] * xd[rows[i]]).sum(0) + d[i] * xd[i]) for i in range(hubs)]).astype(np.float32)
+    y = pipad.frame_aggregate(frame, x)
+    assert np.array_equal(y[:hubs].cpu().numpy(), want)
+    assert torch.equal(pipad.frame_aggregate(frame, x, static_scratch=True), y)
+    frame.close()
