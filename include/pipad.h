@@ -202,10 +202,14 @@ int pipad_frame_aggregate_subset(pipad_frame_t *frame, int32_t nsel, const int32
  *   snapshot, groups of 3.)  A concatenated operand of F < 32 takes units * classes * k * F floats,
  *   and where these do not fit units * k * F (the classes of a unit one after the other: slower,
  *   same bits).
+ *   Behind the partial sums of a concatenated operand the array takes the operand times its scales
+ *   (see pipad_frame_aggregate) where both fit and there are partial sums; elsewhere the products are
+ *   made entry by entry (slower, same bits).
  *   All calls on one GPU share the array: calls that overlap in time on that GPU (different
  *   streams, or different frames) race on it and give wrong results; calls ordered on one stream
- *   are safe.  Nothing in the array has to be cleared between calls: every partial sum is written
- *   before it is read within the same call. */
+ *   are safe, and so are calls on frames without a row longer than "mid_max", which do not touch
+ *   it.  Nothing in the array has to be cleared between calls: all of it is written before it is read within the
+ *   same call. */
 #define PIPAD_STATIC_SCRATCH_BYTES ((size_t)64 << 20)
 int pipad_frame_aggregate_static(const pipad_frame_t *frame, int32_t F, const float *const *X,
                                  int64_t ldx, float *const *Y, int64_t ldy, void *stream);

@@ -2000,9 +2000,9 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
     if (fixed && (size_t)a.nvp * (size_t)a.nsel * (size_t)F > *scratch.floats) return PIPAD_ERR_SCRATCH;
   }
   // The table goes behind the sums in the fixed array, into memory of its own otherwise.  Without room for it the kernel makes its
-  // products itself.
+  // products itself; so it does in a call that has no sums to put into the fixed array, and does not touch what all calls share.
   if (table && !scratch.frame) {
-    if (sums + table <= *scratch.floats) a.table = *scratch.ptr + sums;
+    if (need > 0 && sums + table <= *scratch.floats) a.table = *scratch.ptr + sums;
   } else if (table) {
     if (table > f->table_floats && !fixed) {
       const size_t floats = std::max(table, std::min<size_t>(2 * f->table_floats, kTableFloats));

@@ -208,3 +208,31 @@ def test_rows_in_parts_are_finished_in_64_bits(pipad, hubs, length, classes, F):
     assert np.array_equal(y[:hubs].cpu().numpy(), want)
     assert torch.equal(pipad.frame_aggregate(frame, x, static_scratch=True), y)
     frame.close()
+
+
+def test_calls_without_partial_sums_share_no_scratch(pipad):  # noqa: F811
+    """Calls that allocate nothing, side by side on two streams: where no row is summed up in parts there is nothing they share,
+    the products among it."""
+    n, k, F = 20_000, 4, 4
+    pipad.set_option("agg_coalescent", 2)
+    rng = np.random.default_rng(11)
+    pairs = np.unique(rng.integers(0, n * n, 1_200_000))
+    pairs = np.stack([pairs // n, pairs % n], 1)
+    pairs = pairs[pairs[:, 0] != pairs[:, 1]]
+    counts = np.bincount(pairs[:, 0], minlength=n)
+    assert counts.max() <= 500 and 3 * k * len(pairs) > 10_000_000 + k * n * (4 * F + 1)
+    snap = (torch.from_numpy(np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)).cuda(),
+            torch.from_numpy(pairs[:, 1].astype(np.int32)).cuda())
+    frame = pipad.frame_build_overlap([snap] * k, validate=True)
+    x = [torch.empty((n, k, F), device="cuda:0").uniform_(-1, 1) for _ in range(2)]
+    want = [pipad.frame_aggregate(frame, m) for m in x]
+    got = [[torch.full_like(w, float("nan")) for _ in range(20)] for w in want]
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    torch.cuda.synchronize()
+    for i in range(20):
+        for m, outs, stream in zip(x, got, streams):
+            pipad.frame_aggregate(frame, m, outs[i], stream=stream, static_scratch=True)
+    torch.cuda.synchronize()
+    for outs, w in zip(got, want):
+        assert all(torch.equal(y, w) for y in outs)
+    frame.close()
