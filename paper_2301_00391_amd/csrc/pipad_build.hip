@@ -2141,12 +2141,12 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
   // 50 to 70; R-MAT 74k, k = 2 93 -> 78, Chung-Lu 125k, k = 1 62 -> 56.  Up to 2048 tiles and 20000 waves of k_prepare_mark, of
   // which 8192 run together: N = 107k, k = 8 with 2000 tiles 190 -> 186, N = 45k, k = 12 with 1520 181 -> 178, but N = 113k,
   // k = 16 with 1590 180 -> 187; with 3000 to 4000 tiles and k = 2 .. 6 3 to 13 % slower.
-  const bool small = g.ntiles <= kSumTiles && row_blocks <= kSumRowBlocks && (int64_t)g.ntiles * k <= 20000;
+  bool small = g.ntiles <= kSumTiles && row_blocks <= kSumRowBlocks && (int64_t)g.ntiles * k <= 20000;
   // Frames of up to 33 M entries in all snapshots get that room as well (400 MB at most), and their rows are made next to the
   // entries, in the launch that would wait for the host otherwise: steps and slides N = 100k R-MAT, k = 5 198 -> 191 us,
   // N = 200k, k = 8 269 -> 263 (slide), 124k, k = 2 88 -> 77, 140k, k = 3 119 -> 111; of 40 frames past the small ones 1 to 10 % less,
   // the more the shorter.
-  const bool early = small || (entries <= kEarlyEntries && g.ntiles < kManyTiles);
+  bool early = small || (entries <= kEarlyEntries && g.ntiles < kManyTiles);
   int32_t most_common = s.nnz[0];
   for (int t = 1; t < k; ++t) most_common = std::min(most_common, s.nnz[t]);
 
@@ -2164,6 +2164,7 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
       a.want(&f->wd[t], (size_t)exclusive[t]);
     }
   };
+  const size_t up_front = keep1.total;
   if (early) want_parts(keep1, most_common, s.nnz);
 
   Arena tmp;
@@ -2174,33 +2175,42 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
   tmp.want(&g.bits, base_words);
   tmp.want(&g.hub_bits, base_words);
   tmp.want(&g.wpre, base_words);
-  tmp.want(&g.brow, small ? 0 : (size_t)g.ntiles + 1);
+  tmp.want(&g.brow, (size_t)g.ntiles + 1);
   tmp.want(&g.bound, ((size_t)g.ntiles + 1) * k);
   tmp.want(&g.tile_cnt, (size_t)g.ntiles + 1);  // (read two at a time)
-  tmp.want(&g.tile_pre, small ? 0 : (size_t)g.ntiles + 1);
+  tmp.want(&g.tile_pre, (size_t)g.ntiles + 1);
   tmp.want(&g.row_cnt, row_count_slots(n));
-  tmp.want(&g.row_pre, small ? 0 : row_count_slots(n));
+  tmp.want(&g.row_pre, row_count_slots(n));
   tmp.want(&g.bad, 1);
   tmp.want(&totals, 1);
   tmp.want(&dflags, (size_t)64);
-  const bool together = small && one_request(f, keep1.total + tmp.total);
-  void *const base_ptr = A.get(keep1.total + (together ? tmp.total : 0));
-  if (!base_ptr) return fail(PIPAD_ERR_ALLOC);
-  keep1.assign(base_ptr);
+  bool together = small && one_request(f, keep1.total + tmp.total);
+  void *base_ptr = nullptr;
   if (together) {
-    tmp.assign(static_cast<char *>(base_ptr) + keep1.total);
-  } else if (alloc) {
-    temp = alloc(tmp.total, alloc_ctx);
-    f->temp_ptr = temp;
-    f->temp_bytes = temp ? tmp.total : 0;
-  } else if (hipMalloc(&temp, tmp.total) != hipSuccess) {
-    (void)hipGetLastError();
-    temp = nullptr;
+    base_ptr = A.get(keep1.total + tmp.total);
+    if (base_ptr) tmp.assign(static_cast<char *>(base_ptr) + keep1.total);
+    else together = early = false;
   }
   if (!together) {
+    if (alloc) {
+      temp = alloc(tmp.total, alloc_ctx);
+      f->temp_ptr = temp;
+      f->temp_bytes = temp ? tmp.total : 0;
+    } else if (hipMalloc(&temp, tmp.total) != hipSuccess) {
+      (void)hipGetLastError();
+      temp = nullptr;
+    }
     if (!temp) return fail(PIPAD_ERR_ALLOC);
     tmp.assign(temp);
+    if (early) base_ptr = A.get(keep1.total);
   }
+  // (where there is no room for as many entries as the parts can have, there may be for as many as they do have)
+  if (!base_ptr) {
+    small = early = false;
+    base_ptr = A.get(up_front);
+  }
+  if (!base_ptr) return fail(PIPAD_ERR_ALLOC);
+  keep1.assign(base_ptr);
 
   auto hipcheck = [&](hipError_t e, const char *what) { return e == hipSuccess ? 0 : hip_fail(e, what); };
 #define PIPAD_TRY(call)                                   \

@@ -1,4 +1,5 @@
-"""A build that fails gives its memory back at once, so nothing of it may still be running when it returns."""
+"""A build that fails gives its memory back at once, so nothing of it may still be running when it returns; one that gets no room
+for what its parts can hold at most is made with what they do hold."""
 import ctypes
 
 import numpy as np
@@ -7,6 +8,7 @@ import pytest
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
+from test_gpu_build_tiles import csr  # noqa: E402
 from test_gpu_parity import pipad, churned, _reset_options  # noqa: E402,F401
 
 
@@ -68,3 +70,52 @@ def test_snapshots_that_turn_out_not_to_be_canonical(pipad):  # noqa: F811
         pipad.frame_build_overlap([(rowptr, good)] * (k - 1) + [(longer, twice)], stream=side)
     assert info.value.status == -2
     assert side.query(), "work is left on the stream"
+
+
+# in one request with the temporaries; two launches, requests of their own; two launches, k > 16; entries behind a scan, for every
+# instance that writes them
+@pytest.mark.parametrize("n,entries,k,refused", [(500, 3000, 3, 1), (60_000, 1_000_000, 2, 2), (3000, 50_000, 17, 1),
+                                                 (70_000, 1_300_000, 1, 2), (70_000, 1_300_000, 2, 2), (70_000, 1_300_000, 3, 2),
+                                                 (70_000, 1_300_000, 4, 2), (70_000, 1_300_000, 5, 2), (70_000, 1_300_000, 8, 2),
+                                                 (70_000, 600_000, 17, 2)])
+def test_room_refused(pipad, n, entries, k, refused):  # noqa: F811
+    from paper_2301_00391_amd import binding
+    lib = pipad.load_library()
+    rng = np.random.default_rng(n + k)
+    keys = np.unique(rng.integers(0, n * n, entries + entries // 8))
+    keys = np.sort(rng.permutation(keys[keys // n != keys % n])[:entries])
+    pairs = np.stack([keys // n, keys % n], 1)
+    arr, snaps = descriptors(binding, [csr(n, pairs[rng.random(len(pairs)) < 0.9]) for _ in range(k)])
+    stream = torch.cuda.current_stream()
+    want = pipad.frame_build_overlap(snaps)
+    x = [torch.empty((n, 8), device="cuda:0").uniform_(-1, 1) for _ in range(k)]
+    kept, sizes, refuse = [], [], {refused}
+
+    def alloc(nbytes, _ctx):
+        sizes.append(nbytes)
+        if len(sizes) in refuse:
+            return None
+        kept.append(torch.full((max(int(nbytes), 256),), 0x5a, dtype=torch.uint8, device="cuda:0"))
+        return kept[-1].data_ptr()
+
+    cb, out = binding.ALLOC_FN(alloc), ctypes.c_void_p()
+
+    def build():
+        return lib.pipad_frame_build_overlap(n, k, arr, 0, ctypes.cast(cb, ctypes.c_void_p), None, stream.cuda_stream, ctypes.byref(out))
+
+    assert build() == 0
+    again = refused + 1
+    assert sizes[2] < sizes[refused - 1]
+    frame = binding.Frame(out.value, n, k, want.device, {})
+    for t in [None, *range(k)]:
+        for a, b in zip(frame.common() if t is None else frame.delta(t), want.common() if t is None else want.delta(t)):
+            assert torch.equal(a, b), t
+    for a, b in zip(pipad.frame_aggregate(frame, x), pipad.frame_aggregate(want, x)):
+        assert torch.equal(a, b)
+    torch.cuda.synchronize()
+    frame.close()
+    want.close()
+    sizes.clear()
+    out.value = None
+    refuse.add(again)
+    assert build() == -3 and out.value is None
