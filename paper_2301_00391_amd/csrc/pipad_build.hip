@@ -2184,14 +2184,15 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
   tmp.want(&g.bad, 1);
   tmp.want(&totals, 1);
   tmp.want(&dflags, (size_t)64);
-  bool together = small && one_request(f, keep1.total + tmp.total);
-  void *base_ptr = nullptr;
-  if (together) {
-    base_ptr = A.get(keep1.total + tmp.total);
-    if (base_ptr) tmp.assign(static_cast<char *>(base_ptr) + keep1.total);
-    else together = early = false;
-  }
-  if (!together) {
+  // where there is no room for the parts before they are known there may be for what they take (less than a megabyte is not worth it)
+  const bool tight = !early || keep1.total - up_front > (1u << 20);
+  const bool together = small && one_request(f, keep1.total + tmp.total);
+  void *base_ptr = together ? A.get(keep1.total + tmp.total) : nullptr;
+  const bool refused = together && !base_ptr;
+  if (refused && !tight) return fail(PIPAD_ERR_ALLOC);
+  if (base_ptr) {
+    tmp.assign(static_cast<char *>(base_ptr) + keep1.total);
+  } else {
     if (alloc) {
       temp = alloc(tmp.total, alloc_ctx);
       f->temp_ptr = temp;
@@ -2202,10 +2203,9 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
     }
     if (!temp) return fail(PIPAD_ERR_ALLOC);
     tmp.assign(temp);
-    if (early) base_ptr = A.get(keep1.total);
+    if (early && !refused) base_ptr = A.get(keep1.total);
   }
-  // (where there is no room for as many entries as the parts can have, there may be for as many as they do have)
-  if (!base_ptr) {
+  if (!base_ptr && tight) {
     small = early = false;
     base_ptr = A.get(up_front);
   }

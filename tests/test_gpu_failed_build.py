@@ -74,7 +74,7 @@ def test_snapshots_that_turn_out_not_to_be_canonical(pipad):  # noqa: F811
 
 # in one request with the temporaries; two launches, requests of their own; two launches, k > 16; entries behind a scan, for every
 # instance that writes them
-@pytest.mark.parametrize("n,entries,k,refused", [(500, 3000, 3, 1), (60_000, 1_000_000, 2, 2), (3000, 50_000, 17, 1),
+@pytest.mark.parametrize("n,entries,k,refused", [(5000, 200_000, 3, 1), (60_000, 1_000_000, 2, 2), (3000, 50_000, 17, 1),
                                                  (70_000, 1_300_000, 1, 2), (70_000, 1_300_000, 2, 2), (70_000, 1_300_000, 3, 2),
                                                  (70_000, 1_300_000, 4, 2), (70_000, 1_300_000, 5, 2), (70_000, 1_300_000, 8, 2),
                                                  (70_000, 600_000, 17, 2)])
