@@ -1213,25 +1213,32 @@ __device__ inline bool sum_tiles(const Tiles &g, const TileCounts &x, uint2 *pre
   return __syncthreads_or(bad);
 }
 
-// Common entries in front of tile `upto` (the same for the workgroup), for every thread; `bad`: a tile's flag is set.
-__device__ inline uint32_t sum_tiles_before(const Tiles &g, int32_t upto, bool *bad) {
-  __shared__ uint32_t front[kWavesPerBlock], flag[kWavesPerBlock];
+// Common entries in front of tile `upto` (the same for the workgroup), and of all tiles, for every thread; `bad`: a tile's flag is
+// set.
+__device__ inline uint32_t sum_tiles_before(const Tiles &g, int32_t upto, uint32_t *all, bool *bad) {
+  __shared__ uint32_t front[kWavesPerBlock], every[kWavesPerBlock], flag[kWavesPerBlock];
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, t0 = kTilesEach * (int)threadIdx.x;
-  uint32_t c[2][kTilesEach], mine = 0;
+  uint32_t c[2][kTilesEach], mine = 0, total = 0;
   const bool here = split_tiles(g, request_tiles(g), c);
 #pragma unroll
-  for (int q = 0; q < kTilesEach; ++q) mine += t0 + q < upto ? c[0][q] : 0u;
-  const uint32_t incl = wave_sum(mine);
+  for (int q = 0; q < kTilesEach; ++q) {
+    mine += t0 + q < upto ? c[0][q] : 0u;
+    total += c[0][q];
+  }
+  const uint32_t incl = wave_sum(mine), incl_all = wave_sum(total);
   const uint64_t any = __ballot(here);
   if (lane == kWave - 1) {
     front[wave] = incl;
+    every[wave] = incl_all;
     flag[wave] = any != 0;
   }
   __syncthreads();
   uint32_t sum = 0, flags = 0;
+  *all = 0;
 #pragma unroll
   for (int w = 0; w < kWavesPerBlock; ++w) {
     sum += front[w];
+    *all += every[w];
     flags |= flag[w];
   }
   *bad = flags != 0;
@@ -1623,6 +1630,18 @@ struct OutParts {
   float *wd[PIPAD_MAX_K];
 };
 
+// Parts that are written before their sizes are known share their room, so that it need hold no more than the entries of the input,
+// and a scale for each: the columns of all parts lie one behind the other, snapshot t's common and exclusive scales as well.  How
+// far the exclusive ones move up depends on the common entries alone: OutParts has their places without any, and
+// `common` entries put exclusive part t's columns behind by cols(t), its scales by scales().  Pieces start at multiples of 256 bytes.
+constexpr int32_t kRoomPiece = 64;
+__host__ __device__ inline int64_t room_pieces(int64_t entries) { return (entries + kRoomPiece - 1) / kRoomPiece * kRoomPiece; }
+struct RoomShift {
+  int32_t common;
+  __host__ __device__ int64_t scales() const { return room_pieces(common); }
+  __host__ __device__ int64_t cols(int t) const { return room_pieces(common) - (int64_t)t * (common / kRoomPiece * kRoomPiece); }
+};
+
 constexpr int kScatterAhead = 4;  // words whose entries a wave has in flight
 
 __device__ inline int running_count(uint64_t sel, int lane) {  // selected entries up to and including this word
@@ -1643,10 +1662,11 @@ __device__ inline uint64_t lane_word(uint64_t x, int l) {
 // KV > 0: a node's k scales lie in KV 16-byte pieces, read together (FULL: k == 4 * KV); KV == 0: k <= 2, read at once (500k-node
 // R-MAT frame, k = 2, 65 us one after the other, now 44; k_split_fill 31 and 25), or k > 16, a piece after the other (150k nodes,
 // k = 18, 353 us a scale after the other, now 277).
-// common(x): common entries in front of tile x.
+// common(x): common entries in front of tile x; col_shift, scale_shift: how far the exclusive part lies behind its place in OutParts.
 template <int KV, bool FULL, int TILES, class Common>
 __device__ __forceinline__ void scatter_tiles(const Snaps &s, const Tiles &g, const OutParts &o, const float *dinv,
-                                              const float *dinv_nk, int part, int32_t tile0, Common common) {
+                                              const float *dinv_nk, int part, int32_t tile0, Common common,
+                                              int64_t col_shift = 0, int64_t scale_shift = 0) {
   constexpr int WPT = kWave / TILES;  // words of a tile a wave takes at once
   const int lane = threadIdx.x % kWave;
   const int t = part == 0 ? g.base : part - 1;
@@ -1765,8 +1785,8 @@ __device__ __forceinline__ void scatter_tiles(const Snaps &s, const Tiles &g, co
     upto[q] = total;
   }
   const int32_t *excl = g.excl[t];
-  int32_t *const out_col = o.col[part] + (bound[tile0] - c0);
-  float *const out_w = o.wd[t] + (bound[tile0] - c0);
+  int32_t *const out_col = o.col[part] + (col_shift + (bound[tile0] - c0));
+  float *const out_w = o.wd[t] + (scale_shift + (bound[tile0] - c0));
   const float *dinv_t = dinv + (int64_t)t * g.n;
   constexpr int UN = kScatterAhead;
   for (int32_t j0 = lane; j0 - lane < total; j0 += UN * kWave) {
@@ -1801,7 +1821,7 @@ __global__ __launch_bounds__(kBlock) void k_scatter(Snaps s, Tiles g, OutParts o
 }
 
 // Rows and entries in one launch: `row_wgs` workgroups make the rows, those behind them write the entries, a wave per tile and
-// part.  The outputs have room for as many entries as the parts can have, so that nothing waits for the host; where the
+// part.  The outputs have room for whatever entries the parts have (RoomShift), so that nothing waits for the host; where the
 // snapshots are not canonical, no entries are written.  SUM: behind k_prepare_mark, with nothing summed up yet (the first
 // workgroup sends the sizes to the host).
 template <int KV, bool FULL, bool SUM>
@@ -1819,7 +1839,7 @@ __global__ __launch_bounds__(kBlock) void k_rows_scatter(Snaps s, Tiles g, RowAr
 #pragma unroll
     for (int w = 0; w < kWavesPerBlock; ++w) mine[w] = g.tile_cnt[min(first + w, g.ntiles - 1)].x;
     bool bad;
-    uint32_t front = sum_tiles_before(g, first, &bad);
+    uint32_t all, front = sum_tiles_before(g, first, &all, &bad);
     if (bad || tile0 >= g.ntiles) return;
     uint32_t here = mine[0];
 #pragma unroll
@@ -1828,11 +1848,15 @@ __global__ __launch_bounds__(kBlock) void k_rows_scatter(Snaps s, Tiles g, RowAr
         front += mine[w - 1];
         here = mine[w];
       }
+    const RoomShift shift{(int32_t)all};
     scatter_tiles<KV, FULL, 1>(s, g, o, dinv, dinv_nk, part, tile0,
-                               [&](int32_t x) __attribute__((always_inline)) { return x == tile0 ? front : front + here; });
+                               [&](int32_t x) __attribute__((always_inline)) { return x == tile0 ? front : front + here; },
+                               shift.cols(part - 1), shift.scales());
   } else {
     if (tile0 >= g.ntiles || *g.bad != 0) return;
-    scatter_tiles<KV, FULL, 1>(s, g, o, dinv, dinv_nk, part, tile0, [&](int32_t x) __attribute__((always_inline)) { return g.tile_pre[x].x; });
+    const RoomShift shift{(int32_t)g.tile_pre[g.ntiles].x};
+    scatter_tiles<KV, FULL, 1>(s, g, o, dinv, dinv_nk, part, tile0, [&](int32_t x) __attribute__((always_inline)) { return g.tile_pre[x].x; },
+                               shift.cols(part - 1), shift.scales());
   }
 }
 
@@ -2134,21 +2158,21 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
   g.ntiles = (int32_t)(((int64_t)s.nnz[base] + (1 << g.tile_log2) - 1) >> g.tile_log2);
 
   const int64_t row_blocks = ((int64_t)n + kBlock - 1) / kBlock;
-  // Small frames take two launches instead of four (or five, with the sums in a launch of their own), and get room for as
-  // many entries as the parts can have (the overlap part at most those of the smallest snapshot, an exclusive part its
-  // snapshot's: 120 MB at most for all) together with what is sized up front, so that nothing waits for the host before
+  // Small frames take two launches instead of four (or five, with the sums in a launch of their own), and get room for their
+  // parts before these are known (RoomShift: 8 bytes per input entry, 82 MB at most here) together with what is sized up front, so
+  // that nothing waits for the host before
   // it has the sizes.  Whole steps and slides: N = 2k, k = 4 55 -> 48 us, N = 20k, k = 4 59 -> 50, N = 1k .. 60k 60 to 80 ->
   // 50 to 70; R-MAT 74k, k = 2 93 -> 78, Chung-Lu 125k, k = 1 62 -> 56.  Up to 2048 tiles and 20000 waves of k_prepare_mark, of
   // which 8192 run together: N = 107k, k = 8 with 2000 tiles 190 -> 186, N = 45k, k = 12 with 1520 181 -> 178, but N = 113k,
   // k = 16 with 1590 180 -> 187; with 3000 to 4000 tiles and k = 2 .. 6 3 to 13 % slower.
   bool small = g.ntiles <= kSumTiles && row_blocks <= kSumRowBlocks && (int64_t)g.ntiles * k <= 20000;
-  // Frames of up to 33 M entries in all snapshots get that room as well (400 MB at most), and their rows are made next to the
+  // Frames of up to 33 M entries in all snapshots get that room as well (270 MB at most), and their rows are made next to the
   // entries, in the launch that would wait for the host otherwise: steps and slides N = 100k R-MAT, k = 5 198 -> 191 us,
   // N = 200k, k = 8 269 -> 263 (slide), 124k, k = 2 88 -> 77, 140k, k = 3 119 -> 111; of 40 frames past the small ones 1 to 10 % less,
-  // the more the shorter.
+  // the more the shorter.  What stays unused of it, for as long as the frame is there, are 4 (k - 1) bytes per common entry: less
+  // than 4 per input entry, and than what is used.  (With room for every part at its largest it was up to twice as much, and
+  // 200k nodes, k = 8, 81 % in common took 320 MB; now 205 of which 132 are used.)
   bool early = small || (entries <= kEarlyEntries && g.ntiles < kManyTiles);
-  int32_t most_common = s.nnz[0];
-  for (int t = 1; t < k; ++t) most_common = std::min(most_common, s.nnz[t]);
 
   Arena keep1;
   keep1.want(&f->rowptr_c, (size_t)n + 1);
@@ -2156,16 +2180,11 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
   keep1.want(&f->dinv, (size_t)k * n);
   keep1.want(&f->dinv_nk, (size_t)node_stride(k) * n);
   want_lists(keep1, f, entries);
-  auto want_parts = [&](Arena &a, int32_t common, const int32_t *exclusive) {
-    a.want(&f->col_c, (size_t)common);
-    for (int t = 0; t < k; ++t) {
-      a.want(&f->col_d[t], (size_t)exclusive[t]);
-      a.want(&f->wc[t], (size_t)common);
-      a.want(&f->wd[t], (size_t)exclusive[t]);
-    }
-  };
-  const size_t up_front = keep1.total;
-  if (early) want_parts(keep1, most_common, s.nnz);
+  // room of the parts that are written before their sizes are known (RoomShift)
+  int64_t room_at[PIPAD_MAX_K + 1] = {0};  // snapshot t's entries start here without common ones
+  for (int t = 0; t < k; ++t) room_at[t + 1] = room_at[t] + room_pieces(s.nnz[t]);
+  auto scales_at = [&](int t) { return room_at[t] + (int64_t)t * kRoomPiece; };
+  const size_t room = (size_t)(room_at[k] + kRoomPiece + scales_at(k)) * 4;
 
   Arena tmp;
   FrameTotals *totals = nullptr;
@@ -2185,13 +2204,13 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
   tmp.want(&totals, 1);
   tmp.want(&dflags, (size_t)64);
   // where there is no room for the parts before they are known there may be for what they take (less than a megabyte is not worth it)
-  const bool tight = !early || keep1.total - up_front > (1u << 20);
-  const bool together = small && one_request(f, keep1.total + tmp.total);
-  void *base_ptr = together ? A.get(keep1.total + tmp.total) : nullptr;
+  const bool tight = !early || room > (1u << 20);
+  const bool together = small && one_request(f, keep1.total + room + tmp.total, kBuildTogether);
+  void *base_ptr = together ? A.get(keep1.total + room + tmp.total) : nullptr;
   const bool refused = together && !base_ptr;
   if (refused && !tight) return fail(PIPAD_ERR_ALLOC);
   if (base_ptr) {
-    tmp.assign(static_cast<char *>(base_ptr) + keep1.total);
+    tmp.assign(static_cast<char *>(base_ptr) + keep1.total + room);
   } else {
     if (alloc) {
       temp = alloc(tmp.total, alloc_ctx);
@@ -2203,14 +2222,27 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
     }
     if (!temp) return fail(PIPAD_ERR_ALLOC);
     tmp.assign(temp);
-    if (early && !refused) base_ptr = A.get(keep1.total);
+    if (early && !refused) base_ptr = A.get(keep1.total + room);
   }
   if (!base_ptr && tight) {
     small = early = false;
-    base_ptr = A.get(up_front);
+    base_ptr = A.get(keep1.total);
   }
   if (!base_ptr) return fail(PIPAD_ERR_ALLOC);
   keep1.assign(base_ptr);
+  int32_t *const room_cols = reinterpret_cast<int32_t *>(static_cast<char *>(base_ptr) + keep1.total);
+  float *const room_scales = reinterpret_cast<float *>(room_cols + (room_at[k] + kRoomPiece));
+  // Where the parts are in that room, with so many common entries (none: where OutParts has them).
+  auto place_parts = [&](int32_t common) {
+    const RoomShift shift{common};
+    f->col_c = room_cols;
+    for (int t = 0; t < k; ++t) {
+      f->col_d[t] = room_cols + (room_at[t] + shift.cols(t));
+      f->wc[t] = room_scales + scales_at(t);
+      f->wd[t] = f->wc[t] + shift.scales();
+    }
+  };
+  if (early) place_parts(0);
 
   auto hipcheck = [&](hipError_t e, const char *what) { return e == hipSuccess ? 0 : hip_fail(e, what); };
 #define PIPAD_TRY(call)                                   \
@@ -2317,7 +2349,16 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
   }
 
   Arena keep2;
-  if (!early) want_parts(keep2, f->nnz_c, f->nnz_d);
+  if (early) {
+    place_parts(f->nnz_c);
+  } else {
+    keep2.want(&f->col_c, (size_t)f->nnz_c);
+    for (int t = 0; t < k; ++t) {
+      keep2.want(&f->col_d[t], (size_t)f->nnz_d[t]);
+      keep2.want(&f->wc[t], (size_t)f->nnz_c);
+      keep2.want(&f->wd[t], (size_t)f->nnz_d[t]);
+    }
+  }
   want_split(keep2, f);
   if (!early || (f->n_items > 0 && !f->plain_units)) {
     void *base_ptr = A.get(keep2.total);
@@ -2327,7 +2368,8 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
   if (!early && g.ntiles > 0) {
     // A wave per tile has the shortest chain of dependent loads (0.2M nodes: 65 us against 74 with four
     // tiles per wave); with 8M entries and more per snapshot there
-    // are waves enough and fewer of them do better (1M nodes, 20M entries: 313 us against 339).
+    // are waves enough and fewer of them do better (1M nodes, 20M entries: 313 us against 339).  (With so few tiles
+    // that a wave takes one, three and four snapshots are here only where the room for `early` was refused.)
     const int per_wave = g.ntiles < kManyTiles ? 1 : 4;
     using Scatter = void (*)(Snaps, Tiles, OutParts, const float *, const float *);
     static const Scatter kernels[2][9] = {

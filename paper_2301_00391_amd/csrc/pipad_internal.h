@@ -175,7 +175,8 @@ inline void release(pipad_frame *f) {
 // A small frame's temporaries come with the frame's own memory, in one request to the caller's allocator, and stay as long: a
 // request takes 3 us of a host whose work is most of a small frame's step (20 of 45 us), and so does handing the
 // temporaries back.  They are a third of that memory at most.
-inline bool one_request(const pipad_frame *f, size_t bytes) { return f->alloc && f->plain_units && bytes <= ((size_t)32 << 20); }
+inline bool one_request(const pipad_frame *f, size_t bytes, size_t most) { return f->alloc && f->plain_units && bytes <= most; }
+constexpr size_t kBuildTogether = (size_t)22 << 20, kTransposeTogether = (size_t)32 << 20;  // (1.7 to 1.9 and about 1.5 M entries)
 
 // A build that gives up hands its memory back at once (hipFree, or the caller's allocator, which may
 // give it to anyone): the kernels it has enqueued must have stopped writing to it by then.

@@ -648,7 +648,7 @@ int transpose_frame(const pipad_frame *f, pipad_alloc_fn alloc, void *alloc_ctx,
   tmp.want(&row_cnt, row_count_slots(n));
   tmp.want(&row_pre, row_count_slots(n));
   tmp.want(&totals, 1);
-  const bool together = one_request(g, keep.total + tmp.total);
+  const bool together = one_request(g, keep.total + tmp.total, kTransposeTogether);
   void *const base_ptr = A.get(keep.total + (together ? tmp.total : 0));
   if (!base_ptr) return fail(PIPAD_ERR_ALLOC);
   keep.assign(base_ptr);

@@ -115,3 +115,61 @@ def test_temporaries_in_one_request(pipad, n, edges, k, requests):  # noqa: F811
     for h in made:
         lib.pipad_frame_destroy(h)
     run_case(pipad, n, lists, 4, seed=n)
+
+
+@pytest.mark.parametrize("n,entries,k,kept", [(3000, 1_000_000, 2, 0.95), (3000, 1_300_000, 4, 0.95), (3000, 1_300_000, 5, 0.3), (40_000, 1_300_000, 8, 0.99),
+                                              (3000, 700_000, 17, 0.99), (5000, 1_200_000, 1, 1.0)])
+def test_room_for_parts(pipad, n, entries, k, kept):  # noqa: F811
+    """What a frame holds whose parts are written before their sizes are known: less than 4 bytes per input entry more than they
+    need, and all of it there (the last one of every part as well)."""
+    import ctypes
+
+    from paper_2301_00391_amd import binding
+    rng = np.random.default_rng(n + k)
+    keys = np.unique(rng.integers(0, n * n, entries + entries // 4))
+    keys = np.sort(rng.permutation(keys[keys // n != keys % n])[:entries])
+    pairs = np.stack([keys // n, keys % n], 1)
+    lists = [csr(n, pairs[rng.random(len(pairs)) <= kept]) for _ in range(k)]
+    snaps = [(torch.from_numpy(rp).cuda(), torch.from_numpy(c.astype(np.int32)).cuda()) for rp, c in lists]
+    arr = (binding._Csr * k)()
+    for t, (rp, c) in enumerate(snaps):
+        arr[t].n, arr[t].nnz, arr[t].rowptr, arr[t].colidx = n, c.numel(), rp.data_ptr(), c.data_ptr()
+    buffers, guard = [], 4096
+
+    def alloc(nbytes, _ctx):
+        buffers.append((int(nbytes), torch.full((int(nbytes) + guard,), 0x5a, dtype=torch.uint8, device="cuda:0")))
+        return buffers[-1][1].data_ptr()
+
+    lib, cb, out = pipad.load_library(), binding.ALLOC_FN(alloc), ctypes.c_void_p()
+    pipad.set_option("mid_max", 1 << 20)  # no copies of long rows
+    assert lib.pipad_frame_build_overlap(n, k, arr, 0, ctypes.cast(cb, ctypes.c_void_p), None,
+                                         torch.cuda.current_stream().cuda_stream, ctypes.byref(out)) == 0
+    pipad.set_option("mid_max", 512)
+    ptr, size = ctypes.c_void_p(), ctypes.c_size_t()
+    assert lib.pipad_frame_temporaries(out, ctypes.byref(ptr), ctypes.byref(size)) == 0 and ptr.value
+    held = sum(b for b, _ in buffers) - size.value
+    torch.cuda.synchronize()
+    for b, buf in buffers:
+        assert bool((buf[b:] == 0x5a).all())
+    frame = binding.Frame(out.value, n, k, snaps[0][0].device, {})
+    common = frame.common()[1].numel()
+    assert common >= 100
+    total = sum(c.numel() for _, c in snaps)
+    parts = 4 * common * (1 + k) + 8 * (total - k * common)
+    nodes = 4 * n * (3 * k + 8) + 65_536  # row pointers, scales, row lists
+    assert parts <= held < parts + 4 * total + nodes
+    assert held < 2 * parts + nodes
+    x = [torch.empty((n, 4), device="cuda:0").uniform_(-1, 1) for _ in range(k)]
+    want = pipad.frame_build_overlap(snaps)
+    for t in [None, *range(k)]:
+        for a, b in zip(frame.common() if t is None else frame.delta(t), want.common() if t is None else want.delta(t)):
+            assert torch.equal(a, b), t
+    dinv = want.dinv().double()
+    for t, (a, (rp, c)) in enumerate(zip(pipad.frame_aggregate(frame, x), snaps)):
+        row = torch.repeat_interleave(torch.arange(n, device="cuda:0"), torch.diff(rp.long()))
+        scaled = x[t].double() * dinv[t][:, None]
+        full = scaled.clone().index_add_(0, row, scaled[c.long()]) * dinv[t][:, None]
+        size_of = scaled.abs().index_add_(0, row, scaled.abs()[c.long()]) * dinv[t][:, None]
+        assert bool(((a.double() - full).abs() <= 1e-5 * size_of).all()), t
+    frame.close()
+    want.close()
