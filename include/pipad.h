@@ -158,9 +158,11 @@ int pipad_frame_shape(const pipad_frame_t *frame, int32_t *n, int32_t *k);
  *   allocator; with the library's own allocator a buffer that is replaced is freed after a
  *   hipDeviceSynchronize).  On the concatenated operand with few columns, in frames with many
  *   entries, the operand times its scales goes through a second buffer (4 bytes per element, rows
- *   padded to a power of two up to 128 bytes; 1 GiB at most), which the first such call allocates
+ *   padded to a power of two from 16 to 128 bytes, to 48 where they have 9 to 12 elements and to a multiple
+ *   of 16 bytes where they are longer than 128; 1 GiB at most), which the first such call allocates
  *   and such a call with a larger one replaces; what is replaced, at most half as large, stays with
- *   the frame until pipad_frame_destroy().  All other calls only enqueue kernels on `stream`, without host
+ *   the frame until pipad_frame_destroy().  Where it is refused the call does without, with the same
+ *   bits, and no later call of the frame asks for as much.  All other calls only enqueue kernels on `stream`, without host
  *   synchronisation, so they can be recorded into a HIP graph (stream capture) once an eager call
  *   with the same or a larger k*F has sized the scratch, whichever form (one matrix per snapshot,
  *   concatenated, with the update) either of them has.  A recorded call whose form takes more than

@@ -1999,26 +1999,10 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
     fixed = capturing != hipStreamCaptureStatusNone;
     if (fixed && (size_t)a.nvp * (size_t)a.nsel * (size_t)F > *scratch.floats) return PIPAD_ERR_SCRATCH;
   }
-  // The table goes behind the sums in the fixed array, into memory of its own otherwise.  Without room for it the kernel makes its
-  // products itself; so it does in a call that has no sums to put into the fixed array, and does not touch what all calls share.
-  if (table && !scratch.frame) {
-    if (need > 0 && sums + table <= *scratch.floats) a.table = *scratch.ptr + sums;
-  } else if (table) {
-    if (table > f->table_floats && !fixed) {
-      const size_t floats = std::max(table, std::min<size_t>(2 * f->table_floats, kTableFloats));
-      pipad_frame *const to = scratch.frame;
-      if (void *ptr = Allocator{to->alloc, to->alloc_ctx, to}.get((kTableSkip + floats) * sizeof(float))) {
-        to->table = static_cast<float *>(ptr) + kTableSkip;
-        to->table_floats = floats;
-      }
-    }
-    if (table <= f->table_floats) a.table = f->table;
-  }
   if (need > *scratch.floats && fixed) {
     if (coalescent) {
       // one partial sum per hub unit then, the same sums
       a.whole_units = 1;
-      a.table = nullptr;  // (without the products: the same bits)
       need /= (size_t)a.nclass;
       if (need > *scratch.floats) return PIPAD_ERR_SCRATCH;
     } else {
@@ -2062,6 +2046,25 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
     *scratch.floats = need;
   }
   a.partial = *scratch.ptr;
+  // The table goes behind the sums in the fixed array, into memory of its own otherwise (asked for last, and not again where as
+  // much was refused before).  Without room for it the kernel makes its products itself, with the same bits; so it does in a
+  // call that has no sums to put into the fixed array, and does not touch what all calls share, and with one sum per unit.
+  if (table && !a.whole_units) {
+    if (pipad_frame *const to = scratch.frame) {
+      if (table > to->table_floats && table < to->table_refused && !fixed) {
+        const size_t floats = std::max(table, std::min<size_t>(2 * to->table_floats, kTableFloats));
+        if (void *ptr = Allocator{to->alloc, to->alloc_ctx, to}.get((kTableSkip + floats) * sizeof(float))) {
+          to->table = static_cast<float *>(ptr) + kTableSkip;
+          to->table_floats = floats;
+        } else {
+          to->table_refused = table;
+        }
+      }
+      if (table <= to->table_floats) a.table = to->table;
+    } else if (need > 0 && sums + table <= *scratch.floats) {
+      a.table = *scratch.ptr + sums;
+    }
+  }
   if (coalescent)
     return cvec == 4 ? launch_coalescent<4>(a, st)
                      : cvec == 2 ? launch_coalescent<2>(a, st) : launch_coalescent<1>(a, st);

@@ -123,6 +123,7 @@ struct pipad_frame {
   // frame goes, as recorded calls may hold it, and what replaces it is twice as large or more, or as large as any.
   float *table = nullptr;
   size_t table_floats = 0;
+  size_t table_refused = SIZE_MAX;  // the least that could not be had (a request that fails may empty the allocator's cache)
 };
 
 namespace pipad {

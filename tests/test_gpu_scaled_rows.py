@@ -236,3 +236,43 @@ def test_calls_without_partial_sums_share_no_scratch(pipad):  # noqa: F811
     for outs, w in zip(got, want):
         assert all(torch.equal(y, w) for y in outs)
     frame.close()
+
+
+def test_products_that_cannot_be_had_are_asked_for_once(pipad):  # noqa: F811
+    """Behind the partial sums, which a call cannot do without; then the kernel makes the products itself, with the same bits."""
+    import ctypes
+
+    from paper_2301_00391_amd import binding
+    n, k = 6000, 7
+    pipad.set_option("agg_coalescent", 2)
+    pipad.set_option("mid_max", 300)
+    lists = power_law(n, 350_000, k, 4)
+    snaps = [(torch.from_numpy(rp).cuda(), torch.from_numpy(c).cuda()) for rp, c in lists]
+    arr = (binding._Csr * k)()
+    for t, (rp, c) in enumerate(snaps):
+        arr[t].n, arr[t].nnz, arr[t].rowptr, arr[t].colidx = n, c.numel(), rp.data_ptr(), c.data_ptr()
+    kept, requests, refuse = [], [], set()
+
+    def alloc(nbytes, _ctx):
+        requests.append(nbytes)
+        if len(requests) in refuse:
+            return None
+        kept.append(torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device="cuda:0"))
+        return kept[-1].data_ptr()
+
+    lib, cb, out = pipad.load_library(), binding.ALLOC_FN(alloc), ctypes.c_void_p()
+    assert lib.pipad_frame_build_overlap(n, k, arr, 0, ctypes.cast(cb, ctypes.c_void_p), None,
+                                         torch.cuda.current_stream().cuda_stream, ctypes.byref(out)) == 0
+    frame, usual = binding.Frame(out.value, n, k, snaps[0][0].device, {}), pipad.frame_build_overlap(snaps)
+    x = {F: torch.empty((n, k, F), device="cuda:0").uniform_(-1, 1) for F in (2, 5)}
+    want = {F: pipad.frame_aggregate(usual, x[F]) for F in x}
+    requests.clear()
+    refuse.add(2)
+    for F, asked in ((5, 2), (5, 2), (5, 2), (2, 3), (2, 3), (5, 3)):  # the sums and the products; nothing; fewer products
+        assert 3 * k * min(len(c) for _, c in lists) > 10_000_000 + k * n * (4 * F + 1)
+        assert torch.equal(pipad.frame_aggregate(frame, x[F]), want[F])
+        assert len(requests) == asked
+    assert requests[1] > 4 * n * k * 5 > requests[2] > 4 * n * k * 2
+    torch.cuda.synchronize()
+    frame.close()
+    usual.close()
