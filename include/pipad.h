@@ -239,6 +239,7 @@ int pipad_frame_aggregate_static(const pipad_frame_t *frame, int32_t F, const fl
  *          16-byte aligned X (and A) with ldx (lda) a multiple of 4, and a snapshot matrix below
  *          4 GiB.  With A other Fo <= 64 may be fused, too, and some of these are not; what is not runs the
  *          aggregation into A and then a separate multiplication; without A they return PIPAD_ERR_INVALID_ARG.
+ *          Where NULL is possible H has the same bits without A and with one that is aligned like that.
  *   H      host array of k device pointers, row stride ldh >= Fo; written once per element.
  *          H, A, X, W must not overlap.
  *   Stream, device, scratch and determinism rules are those of pipad_frame_aggregate.

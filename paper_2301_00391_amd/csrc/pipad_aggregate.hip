@@ -1048,22 +1048,28 @@ constexpr int kUpdTiles = 8;       // row tiles per wave at most
 constexpr int kUpdMaxCols = 128;   // output columns per column block (8 accumulator tiles)
 constexpr int kUpdPad = 4;         // floats behind an LDS row of W: the lane groups' rows lie 16 banks apart
 
-template <int NT>  // 16-column accumulator tiles a wave keeps
+// LIKE_INSIDE: rows of 33 to 64 columns are summed up in the order of the multiplication inside the aggregation (sink_flush: step j
+// takes columns j, 16 + j, 32 + j and 48 + j), for calls that without A go there: H has the same bits with A and without.  A lane
+// group takes 16 consecutive columns then, and rows of W lie a word further apart, so that those of the groups are 16 banks apart.
+// (Against the order of the other instances -2 to 1 % of aggregation and update, with 40 columns, which take as many steps as 64,
+// 30.9 -> 32.2 us for N = 15k, k = 3, Fo = 64.)
+template <int NT, bool LIKE_INSIDE = false>  // 16-column accumulator tiles a wave keeps
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_update_resident(const AggArgs a, int kpad, int per_wave) {
   constexpr int cbw = 16 * NT;
+  constexpr int GROUP = LIKE_INSIDE ? 16 : 4, BLOCK = LIKE_INSIDE ? 4 : 16;  // columns from a lane group, a block, to the next
   using VT = V<4>;
   extern __shared__ __align__(16) float upd_lds[];
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   const int m = lane & 15, g = lane >> 4;
-  const int ws = cbw + kUpdPad;
+  const int ws = cbw + (LIKE_INSIDE ? 1 : kUpdPad);
   const int col0 = blockIdx.y * cbw;
   stage_weights(a, upd_lds, kpad, cbw, col0, ws);
   __syncthreads();
   const int64_t tiles = ((int64_t)a.n + 15) / 16;
   const int64_t first = ((int64_t)blockIdx.x * kWavesPerBlock + wave) * per_wave;
   const int64_t last = min(first + per_wave, tiles * a.k);
-  const int blocks = a.F / 16;                      // whole blocks of 16 columns
-  const int tail = (a.F - 16 * blocks + 3) / 4;     // steps behind them
+  const int blocks = LIKE_INSIDE ? 4 : a.F / 16;    // whole blocks of 16 columns
+  const int tail = LIKE_INSIDE ? 0 : (a.F - 16 * blocks + 3) / 4;  // steps behind them
   const int chunks = max((blocks + 3) / 4, 1);
   // four blocks of this lane's row (those past the last whole one repeat it; without a whole one they
   // are not there) and, with the last chunk, the tail
@@ -1072,7 +1078,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     const float *src = a.Y[t] + min((id - t * tiles) * 16 + m, (int64_t)a.n - 1) * a.ldy;
     if (blocks > 0)
 #pragma unroll
-      for (int b = 0; b < 4; ++b) v[b] = VT::load(src + 16 * min(4 * chunk + b, blocks - 1) + 4 * g);
+      for (int b = 0; b < 4; ++b) {
+        const int col = BLOCK * min(4 * chunk + b, blocks - 1) + GROUP * g;
+        v[b] = VT::load(src + (LIKE_INSIDE ? min(col, a.F - 4) : col));
+      }
     if (tail > 0 && chunk == chunks - 1)
 #pragma unroll
       for (int j = 0; j < 4; ++j) tv[j] = src[min(16 * blocks + 4 * j + g, a.F - 1)];
@@ -1101,8 +1110,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
       for (int b = 0; b < 4; ++b) {
         __builtin_amdgcn_sched_barrier(0);  // (all blocks' operands at once would take too many registers)
         if (4 * chunk + b >= blocks) break;
+        const int col = BLOCK * (4 * chunk + b) + GROUP * g;
+        if (LIKE_INSIDE && col >= a.F) cur[b] = VT::zero();
         const float y[4] = {cur[b].x, cur[b].y, cur[b].z, cur[b].w};
-        const float *w = upd_lds + (64 * chunk + 16 * b + 4 * g) * ws + m;
+        const float *w = upd_lds + col * ws + m;
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
@@ -1586,8 +1597,9 @@ int launch(const AggArgs &a, bool fast, hipStream_t st, bool fused_update = fals
   return PIPAD_OK;
 }
 
-// The update behind the aggregation, from the stored results of all snapshots.
-int launch_update(const AggArgs &a, hipStream_t st) {
+// The update behind the aggregation, from the stored results of all snapshots (like_inside: of 36 to 64 columns in whole 16-byte
+// pieces, up to 64 columns of H in whole tiles).
+int launch_update(const AggArgs &a, bool like_inside, hipStream_t st) {
   const int64_t tiles = ((int64_t)a.n + 15) / 16 * a.k;
   // Weights resident in LDS, in as few blocks of columns of the same width as fit (every block reads all of Y), else
   // straight from memory.  64 KB of LDS, for two workgroups per CU, where Y is past the memory-side cache (256 MB): with
@@ -1596,7 +1608,7 @@ int launch_update(const AggArgs &a, hipStream_t st) {
   // Fo = 112 with 64 KB 79 us, now 55, F = 160, Fo = 96 87 and 61, F = 200, Fo = 64 72 and 49.  And 40 KB where there are fewer than
   // 1024 workgroups for a block of columns, or 512 of longer rows: N = 3000, k = 1, F = 128, Fo = 112 15 and 11, N = 12k, k = 2 24 and 19, F = 200,
   // Fo = 200 56 and 39, F = 384, Fo = 64 39 and 34; N = 30k, k = 2, F = 112, Fo = 96 38 and 31, but F = 384, Fo = 128 98 and 122.
-  const int kpad = (a.F + 3) / 4 * 4;
+  const int kpad = like_inside ? 64 : (a.F + 3) / 4 * 4;
   const size_t two = 64u << 10, three = 53u << 10, four = 40u << 10;  // workgroups per CU
   const bool far = (int64_t)a.n * a.k * a.F * 4 > (256 << 20), few = !far && tiles < (a.F < 256 ? 4096 : 2048);
   int64_t col_blocks = 0;
@@ -1615,7 +1627,9 @@ int launch_update(const AggArgs &a, hipStream_t st) {
     void (*const kern[])(AggArgs, int, int) = {k_update_resident<1>, k_update_resident<2>, k_update_resident<3>,
                                                k_update_resident<4>, k_update_resident<5>, k_update_resident<6>,
                                                k_update_resident<7>, k_update_resident<8>};
-    hipLaunchKernelGGL(kern[cbw / 16 - 1], grid, dim3(kBlock), lds, st, a, kpad, per_wave);
+    void (*const like[])(AggArgs, int, int) = {k_update_resident<1, true>, k_update_resident<2, true>, k_update_resident<3, true>,
+                                               k_update_resident<4, true>};
+    hipLaunchKernelGGL((like_inside ? like : kern)[cbw / 16 - 1], grid, dim3(kBlock), lds, st, a, kpad, per_wave);
   } else {
     hipLaunchKernelGGL(k_update, dim3((unsigned)((tiles + kWavesPerBlock - 1) / kWavesPerBlock)),
                        dim3(kBlock), 0, st, a);
@@ -1761,7 +1775,7 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
   // The update rides inside the aggregation kernel when a slice is a whole row of one snapshot
   // (F <= 64 in float4 pieces), W fits next to the row tiles in LDS and the fast addressing
   // applies; other shapes aggregate into Y first and multiply afterwards.
-  bool fused = false;
+  bool fused = false, like_inside = false;
   if (upd) {
     a.W = upd->W;
     a.bias = upd->bias;
@@ -1791,7 +1805,9 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
                            (all_rows >= 24000 ? all_rows < 58000 && all_entries > 500000
                                               : all_rows >= 14500 && f->k > 1 && f->n >= 1500 && upd->Fo > 32);
     const bool inside = tiles ? !few_tiles : Y && (F <= 32 || all_rows >= 400000);
-    fused = aligned && F >= 16 && F <= 64 && upd->Fo <= 64 && inside && fast;
+    const bool fusable = aligned && F >= 16 && F <= 64 && upd->Fo <= 64 && fast;
+    fused = fusable && inside;
+    like_inside = fusable && tiles && few_tiles;
     if (!fused && !Y) return PIPAD_ERR_INVALID_ARG;  // the two-step form needs Y as its workspace
   }
   int64_t entries = f->nnz_c;  // of a snapshot
@@ -2018,7 +2034,7 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
                                         std::min<int>((int)group, a.nsel - start));
         if (rc != PIPAD_OK) return rc;
       }
-      return upd && !fused ? launch_update(a, st) : PIPAD_OK;
+      return upd && !fused ? launch_update(a, like_inside, st) : PIPAD_OK;
     }
   }
   if (need > *scratch.floats) {
@@ -2071,7 +2087,7 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
   if (fused) return launch<4>(a, fast, st, true);
   const int rc = vec4 ? launch<4>(a, fast, st) : launch<1>(a, fast, st);
   if (rc != PIPAD_OK || !upd) return rc;
-  return launch_update(a, st);
+  return launch_update(a, like_inside, st);
 }
 
 }  // namespace pipad

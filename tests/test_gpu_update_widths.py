@@ -115,3 +115,24 @@ def test_few_rows_and_whole_tiles_of_columns(pipad, n, k, F, Fo, per_row):  # no
             pipad.frame_aggregate_update(frame, X, W, b, H=H, A=A)
             check(wide, A)
         frame.close()
+
+
+@pytest.mark.parametrize("n,k,F,Fo,bias", [(7_251, 2, 48, 48, True), (1_501, 10, 36, 64, False), (12_001, 2, 64, 32, True), (12_001, 2, 40, 16, True),
+                                           (28_990, 2, 64, 64, True), (15_003, 3, 60, 48, False), (15_003, 3, 44, 16, True)])
+def test_same_bits_with_and_without_the_aggregation(pipad, n, k, F, Fo, bias):  # noqa: F811
+    """Shapes that are multiplied behind the aggregation where it is kept, inside where it is not."""
+    rng = np.random.default_rng(n + Fo)
+    pool = np.concatenate([rand_pairs(rng, n, 25 * n), np.stack([np.full(900, 17), rng.integers(0, n, 900)], 1)])
+    snaps = [(torch.from_numpy(rp).cuda(), torch.from_numpy(c).cuda()) for rp, c in
+             [csr(n, pool[rng.random(len(pool)) < 0.9]) for _ in range(k)]]
+    frame = pipad.frame_build_overlap(snaps)
+    X = [torch.empty((n, F), device="cuda:0").uniform_(-1, 1) for _ in range(k)]
+    X[0][5, F - 1] = float("inf")  # (columns past the last one take no part)
+    W = torch.empty((F, Fo), device="cuda:0").uniform_(-1, 1)
+    b = torch.empty(Fo, device="cuda:0").uniform_(-1, 1) if bias else None
+    H, A = [[torch.full((n, Fo), 77.0, device="cuda:0") for _ in range(k)] for _ in range(2)], [torch.empty((n, F), device="cuda:0") for _ in range(k)]
+    pipad.frame_aggregate_update(frame, X, W, b, H=H[0], A=A)
+    pipad.frame_aggregate_update(frame, X, W, b, H=H[1])
+    for t in range(k):
+        assert torch.equal(H[0][t].view(torch.int32), H[1][t].view(torch.int32)), t
+    frame.close()
