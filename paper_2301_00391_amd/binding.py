@@ -165,7 +165,9 @@ class Frame:
         self._buffers = buffers  # torch tensors handed to the library through the allocator, by address
         self._key = key  # names the buffers to the library's callback, which it may use again (aggregate scratch)
         # torch's allocator hands memory out, and takes it back, in the order of the stream that
-        # was current at the allocation; work on any other stream has to be waited for in close()
+        # was current at the allocation; work on any other stream has to be waited for in close().  Scratch
+        # that a later call asks for is ordered by the stream that is current then, and the frame's own has to be
+        # waited for as well from there on.
         self._alloc_stream = _current_raw_stream(self._index)
         self._other_streams = {}
         self._temp = None
@@ -185,9 +187,13 @@ class Frame:
 
     def _stream(self, stream) -> int:
         """Handle of the stream a call runs on; streams other than the allocator's are remembered."""
-        raw = int(stream.cuda_stream) if stream is not None else _current_raw_stream(self._index)
+        current = _current_raw_stream(self._index)
+        raw = int(stream.cuda_stream) if stream is not None else current
         if raw != self._alloc_stream and raw not in self._other_streams:
             self._other_streams[raw] = stream if stream is not None else torch.cuda.current_stream(self._index)
+        if current != self._alloc_stream and self._alloc_stream not in self._other_streams:
+            own = self._alloc_stream
+            self._other_streams[own] = torch.cuda.ExternalStream(own, self.device) if own else torch.cuda.default_stream(self.device)
         return raw
 
     def _release_temporaries(self) -> None:

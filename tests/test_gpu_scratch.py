@@ -126,3 +126,31 @@ def test_fixed_array_and_many_units_on_the_concatenated_operand(pipad, k, F, row
         _, yd, bound, _ = oracle.aggregate(rows, r, c, synth.features(4, t, rows, F), threads=8)
         check_y(y[:, t].cpu().numpy(), yd, bound, f"snapshot {t}")
     frame.close()
+
+
+def test_scratch_taken_under_another_stream(pipad):  # noqa: F811
+    """PyTorch's allocator may give memory out again, in the order of the stream it was asked for under, as soon as the frame is
+    closed: the frame's own stream must be done with it by then."""
+    rng = np.random.default_rng(7)
+    n, k = 500, 3
+    pipad.set_option("short_max", 2)
+    pipad.set_option("mid_max", 4)
+    pipad.set_option("hub_threshold", 6)  # rows in several parts: the first aggregation asks for scratch
+    pipad.set_option("hub_segment", 4)
+    snaps = [(torch.from_numpy(rp).cuda(), torch.from_numpy(c).cuda()) for rp, c in churned(rng, n, k, 0.05, 0.8)]
+    X = [torch.empty((n, 8), device="cuda:0").uniform_(-1, 1) for _ in range(k)]
+    own, other = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for first, then in ((own, other), (torch.cuda.default_stream(), other)):
+        with torch.cuda.stream(first):
+            frame = pipad.frame_build_overlap(snaps)
+        first.synchronize()
+        with torch.cuda.stream(then):
+            want = pipad.frame_aggregate(frame, X)
+        then.synchronize()
+        with torch.cuda.stream(first):
+            torch.cuda._sleep(20_000_000)
+            got = pipad.frame_aggregate(frame, X)
+        frame.close()
+        assert first.query()
+        assert all(torch.equal(a, b) for a, b in zip(got, want))
