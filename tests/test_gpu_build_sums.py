@@ -1,5 +1,6 @@
-"""Frames at the edges of what k_rows adds up itself: 1024 tiles of the base (512 entries each, 256 with more than 16
-snapshots) and 256 blocks of rows; hub rows, whose places depend on the sums, among them."""
+"""Frames at the edges of what k_rows_scatter adds up itself: 2048 tiles of the base (512 entries each, 256 with more than 16
+snapshots), 1024 blocks of rows and 20,000 waves of tiles; hub rows, whose places depend on the sums, among them, and sizes at which
+the lanes that add up take one more tile or block each."""
 import numpy as np
 import pytest
 
@@ -13,7 +14,9 @@ from test_gpu_parity import pipad, _reset_options  # noqa: E402,F401
 
 
 @pytest.mark.parametrize("n,tiles,over,k", [(3000, 3, 1, 2), (5000, 1024, 0, 2), (5000, 1024, 1, 2), (65_536, 700, 0, 3),
-                                            (65_537, 700, 0, 3), (4000, 1024, 0, 17), (4000, 1024, 1, 17)])
+                                            (65_537, 700, 0, 3), (4000, 1024, 0, 17), (4000, 1024, 1, 17),
+                                            (5000, 2048, 0, 2), (5000, 2048, 1, 2), (262_144, 700, 0, 3), (262_145, 700, 0, 3),
+                                            (4000, 1176, 0, 17), (4000, 1176, 1, 17), (5000, 1250, 0, 16), (5000, 1250, 1, 16)])
 def test_edges(pipad, n, tiles, over, k):  # noqa: F811
     rng = np.random.default_rng(n + tiles + over)
     entries = tiles * (512 if k <= 16 else 256) + over

@@ -31,10 +31,11 @@ def test_rows_of_a_share(pipad, n, every, per_row):  # noqa: F811
     assert torch.equal(frame.dinv(), back.dinv())
 
 
-@pytest.mark.parametrize("n", [700, 5000, 65_536, 65_537])
+@pytest.mark.parametrize("n", [700, 5000, 65_536, 65_537, 262_144, 262_145])
 @pytest.mark.parametrize("entries", [2049, 64 * 2048, 64 * 2048 + 1])
 def test_sums_without_a_launch(pipad, n, entries):  # noqa: F811
-    """Up to 64 tiles of 2048 entries in a part, and up to 256 blocks of 256 rows, are added up where they are needed."""
+    """Up to 64 tiles of 2048 entries in a part, and up to 1024 blocks of 256 rows, are added up where they are needed (a
+    thread takes a second block from 65,537 rows on)."""
     rng = np.random.default_rng(n + entries)
     keys = np.unique(rng.integers(0, n * n, entries + entries // 2 + 5000))
     keys = np.sort(rng.permutation(keys[keys // n != keys % n])[:entries])
