@@ -265,23 +265,6 @@ __global__ __launch_bounds__(kBlock) void k_prepare(Snaps s, Tiles g, RowClasses
   prepare_rows(s, g, rc, (int64_t)blockIdx.x - bound_blocks, dinv, dinv_nk);
 }
 
-// The row of a tile's first entry (lanes 0 .. 31) and of the next tile's (lanes 32 .. 63) in the base: 32 places are looked at
-// in one round trip.  (e: the half's entry, which exists)
-__device__ __forceinline__ int32_t half_row_of_entry(const int32_t *rp, int32_t n, int32_t e, int lane) {
-  constexpr int H = kWave / 2;
-  const int sub = lane % H, shift = lane / H * H;
-  int32_t lo = 0, hi = n;  // rp[lo] <= e < rp[hi]
-  while (__any(hi - lo > 1)) {
-    const int32_t step = (int32_t)(((int64_t)hi - lo + H) / (H + 1));
-    const int64_t idx = lo + (int64_t)(sub + 1) * step;
-    const int32_t v = rp[min(idx, (int64_t)n)];
-    const int m = __popc((uint32_t)(__ballot(idx < hi && v <= e) >> shift));
-    lo += m * step;
-    hi = (int32_t)min((int64_t)hi, (int64_t)lo + max(step, 1));
-  }
-  return lo;
-}
-
 // First position in col[lo, hi) (ascending) that holds c or more, by half a wave.
 __device__ __forceinline__ int32_t half_lower_bound(const int32_t *col, int32_t lo, int32_t hi, int32_t c, int lane) {
   constexpr int H = kWave / 2;
@@ -1395,18 +1378,13 @@ __device__ __forceinline__ void store_scales(const SplitArgs &g, const int32_t (
                                              const int32_t (&live)[UN]) {
   if (g.k > 2) {
     const int32_t stride = node_stride(g.k);
-    for (int t = 0; t < g.k; t += 4) {
+    for (int q = 0; 4 * q < g.k; ++q) {
       float4 w[UN];
 #pragma unroll
-      for (int r = 0; r < UN; ++r) w[r] = *reinterpret_cast<const float4 *>(g.dinv_nk + (int64_t)c[r] * stride + t);
+      for (int r = 0; r < UN; ++r) w[r] = *reinterpret_cast<const float4 *>(g.dinv_nk + (int64_t)c[r] * stride + 4 * q);
 #pragma unroll
       for (int r = 0; r < UN; ++r)
-        if (live[r]) {
-          g.swc[t][to[r]] = w[r].x;
-          if (t + 1 < g.k) g.swc[t + 1][to[r]] = w[r].y;
-          if (t + 2 < g.k) g.swc[t + 2][to[r]] = w[r].z;
-          if (t + 3 < g.k) g.swc[t + 3][to[r]] = w[r].w;
-        }
+        if (live[r]) put_scales(g.swc, q, g.k, to[r], w[r]);
     }
   } else if (g.k == 2) {
     float2 w[UN];
@@ -1728,12 +1706,7 @@ __device__ __forceinline__ void scatter_tiles(const Snaps &s, const Tiles &g, co
           if (x[r] >> lane & 1ull) out[at[r]] = c[r];
           if (need[r] >> lane & 1ull)
 #pragma unroll
-            for (int q = 0; q < KV; ++q) {
-              o.wc[4 * q + 0][at[r]] = v[r][q].x;
-              if (FULL || 4 * q + 1 < g.k) o.wc[4 * q + 1][at[r]] = v[r][q].y;
-              if (FULL || 4 * q + 2 < g.k) o.wc[4 * q + 2][at[r]] = v[r][q].z;
-              if (FULL || 4 * q + 3 < g.k) o.wc[4 * q + 3][at[r]] = v[r][q].w;
-            }
+            for (int q = 0; q < KV; ++q) put_scales<FULL>(o.wc, q, g.k, at[r], v[r][q]);
         }
       } else {
 #pragma unroll
@@ -1747,12 +1720,7 @@ __device__ __forceinline__ void scatter_tiles(const Snaps &s, const Tiles &g, co
             for (int r = 0; r < UN; ++r) w[r] = reinterpret_cast<const float4 *>(dinv_nk)[(int64_t)c[r] * pieces + q];
 #pragma unroll
             for (int r = 0; r < UN; ++r)
-              if (need[r] >> lane & 1ull) {
-                o.wc[4 * q][at[r]] = w[r].x;
-                if (4 * q + 1 < g.k) o.wc[4 * q + 1][at[r]] = w[r].y;
-                if (4 * q + 2 < g.k) o.wc[4 * q + 2][at[r]] = w[r].z;
-                if (4 * q + 3 < g.k) o.wc[4 * q + 3][at[r]] = w[r].w;
-              }
+              if (need[r] >> lane & 1ull) put_scales(o.wc, q, g.k, at[r], w[r]);
           }
         } else {
           float2 w[UN];

@@ -258,6 +258,32 @@ __device__ inline int32_t xcd_run(int32_t b, int32_t blocks) {
   return b % kClasses * (align_xcd(blocks) / kClasses) + b / kClasses;
 }
 
+// The rows of two entries by a whole wave, half of it each (e: the half's entry, which exists): 32 places are looked at in one
+// round trip.  Returns the half's own answer.
+__device__ __forceinline__ int32_t half_row_of_entry(const int32_t *rp, int32_t n, int32_t e, int lane) {
+  constexpr int H = kWave / 2;
+  const int sub = lane % H, shift = lane / H * H;
+  int32_t lo = 0, hi = n;  // rp[lo] <= e < rp[hi]
+  while (__any(hi - lo > 1)) {
+    const int32_t step = (int32_t)(((int64_t)hi - lo + H) / (H + 1));
+    const int64_t idx = lo + (int64_t)(sub + 1) * step;
+    const int32_t v = rp[min(idx, (int64_t)n)];
+    const int m = __popc((uint32_t)(__ballot(idx < hi && v <= e) >> shift));
+    lo += m * step;
+    hi = (int32_t)min((int64_t)hi, (int64_t)lo + max(step, 1));
+  }
+  return lo;
+}
+
+// A node's scales of snapshots 4 q .. 4 q + 3 (of k; FULL: all four exist) into place `at` of their streams.
+template <bool FULL = false>
+__device__ __forceinline__ void put_scales(float *const (&w)[PIPAD_MAX_K], int q, int32_t k, int32_t at, float4 v) {
+  w[4 * q][at] = v.x;
+  if (FULL || 4 * q + 1 < k) w[4 * q + 1][at] = v.y;
+  if (FULL || 4 * q + 2 < k) w[4 * q + 2][at] = v.z;
+  if (FULL || 4 * q + 3 < k) w[4 * q + 3][at] = v.w;
+}
+
 // Inclusive sum over the lanes up to this one: within rows of 16 lanes, then across the rows.
 __device__ __forceinline__ uint32_t wave_sum(uint32_t x) {
   x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);  // row_shr:1

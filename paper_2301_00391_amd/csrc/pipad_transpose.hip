@@ -208,23 +208,6 @@ __device__ inline uint64_t same_digit(uint32_t digit, int bits, bool live) {
   return mask;
 }
 
-// The rows of two entries by a whole wave, half of it each: 32 places are looked at in one round trip.
-// Returns the half's own answer.
-__device__ inline int32_t wave_row_of_entry(const int32_t *rp, int32_t n, int32_t e, int lane) {
-  constexpr int H = kWave / 2;
-  const int sub = lane % H, shift = lane / H * H;
-  int32_t lo = 0, hi = n;  // rp[lo] <= e < rp[hi]
-  while (__any(hi - lo > 1)) {
-    const int32_t step = (int32_t)(((int64_t)hi - lo + H) / (H + 1));
-    const int64_t idx = lo + (int64_t)(sub + 1) * step;
-    const int32_t v = rp[min(idx, (int64_t)n)];
-    const int m = __popc((uint32_t)(__ballot(idx < hi && v <= e) >> shift));
-    lo += m * step;
-    hi = (int32_t)min((int64_t)hi, (int64_t)lo + max(step, 1));
-  }
-  return lo;
-}
-
 // Bound by the stores of the first pass: a tile of 4096 entries has 8 of each of 512 digits, 32 bytes to a
 // place.  The next tile's go right behind them, so an XCD takes a run of tiles and its L2 puts the lines
 // together (3.4 M entries: 38 -> 33 us; tiles dealt to the XCDs in turn, whole lines never met).  With rows
@@ -280,7 +263,7 @@ __global__ __launch_bounds__(kSortBlock) __attribute__((amdgpu_waves_per_eu(R ==
   } else if (first < r.count) {
     const int32_t *rp = g.rowptr[r.p];
     const int32_t e0 = (int32_t)(r.begin + first), e1 = (int32_t)(r.begin + min(first + R * kWave, r.count)) - 1;
-    const int32_t end = wave_row_of_entry(rp, g.n, lane < kWave / 2 ? e0 : e1, lane);
+    const int32_t end = half_row_of_entry(rp, g.n, lane < kWave / 2 ? e0 : e1, lane);
     const int32_t r0 = __builtin_amdgcn_readlane(end, 0), r1 = __builtin_amdgcn_readlane(end, kWave - 1);
     if (r1 - r0 < kRowsWalked) {
       // where a row starts in the share goes to LDS (rows without entries start nowhere), and a running
@@ -507,22 +490,11 @@ __global__ __launch_bounds__(kBlock) void k_finish_parts(FinishArgs g) {
 #pragma unroll
       for (int q = 0; q < KV; ++q) v[q] = row[q];
 #pragma unroll
-      for (int q = 0; q < KV; ++q) {
-        g.wc[4 * q + 0][e] = v[q].x;
-        if (FULL || 4 * q + 1 < g.k) g.wc[4 * q + 1][e] = v[q].y;
-        if (FULL || 4 * q + 2 < g.k) g.wc[4 * q + 2][e] = v[q].z;
-        if (FULL || 4 * q + 3 < g.k) g.wc[4 * q + 3][e] = v[q].w;
-      }
+      for (int q = 0; q < KV; ++q) put_scales<FULL>(g.wc, q, g.k, e, v[q]);
     } else if (g.k > 2) {
       const int32_t pieces = node_stride(g.k) / 4;
       const float4 *row = reinterpret_cast<const float4 *>(g.dinv_nk) + (int64_t)c * pieces;
-      for (int q = 0; q < pieces; ++q) {
-        const float4 v = row[q];
-        g.wc[4 * q][e] = v.x;
-        if (4 * q + 1 < g.k) g.wc[4 * q + 1][e] = v.y;
-        if (4 * q + 2 < g.k) g.wc[4 * q + 2][e] = v.z;
-        if (4 * q + 3 < g.k) g.wc[4 * q + 3][e] = v.w;
-      }
+      for (int q = 0; q < pieces; ++q) put_scales(g.wc, q, g.k, e, row[q]);
     } else if (g.k == 2) {
       const float2 v = reinterpret_cast<const float2 *>(g.dinv_nk)[c];
       g.wc[0][e] = v.x;
