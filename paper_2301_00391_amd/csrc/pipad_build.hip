@@ -497,8 +497,9 @@ __device__ __forceinline__ bool mark_twice(const K *keys, int32_t here, int lane
   return twice;
 }
 
-// (Held to eight waves per SIMD with 32-bit keys.  Without spilled registers: a variant that kept 48 bytes of them in private
-// memory took 1337 us for the build of the 1M-node R-MAT frame, not 948.)
+// (Held to eight waves per SIMD with 32-bit keys.  k_mark<512, 1> has no spilled registers: a variant that kept 48 bytes of them in
+// private memory took 1337 us for the build of the 1M-node R-MAT frame, not 948.  k_prepare_mark<512, 1>, with the searches, keeps
+// two, 12 bytes per lane, and k_mark<256, 2> one.)
 // SELF: the waves find where the tile starts in their snapshots themselves (k_prepare_mark).
 template <int T, int L, class K, bool SELF>  // L: snapshots per wave; K: 32- or 64-bit keys
 __device__ __forceinline__ void mark_tile(const Snaps &s, const Tiles &g, int32_t mid_max) {

@@ -175,7 +175,9 @@ inline void release(pipad_frame *f) {
 
 // A small frame's temporaries come with the frame's own memory, in one request to the caller's allocator, and stay as long: a
 // request takes 3 us of a host whose work is most of a small frame's step (20 of 45 us), and so does handing the
-// temporaries back.  They are a third of that memory at most.
+// temporaries back.  In a build they are about a third of that memory.  In a transposition with two digits they take 12 bytes per
+// entry next to the 8 (k = 1, or nothing in common) and more that the frame keeps: up to 60 %, 56 for 60k nodes, k = 1, 0.9 M
+// entries.  So what a frame may hold that way is bounded.
 inline bool one_request(const pipad_frame *f, size_t bytes, size_t most) { return f->alloc && f->plain_units && bytes <= most; }
 constexpr size_t kBuildTogether = (size_t)22 << 20, kTransposeTogether = (size_t)32 << 20;  // (1.7 to 1.9 and about 1.5 M entries)
 
@@ -315,10 +317,10 @@ struct UpdateSpec {
   float *const *H;    // k device pointers, row stride ldh
   int64_t ldh;
 };
-// Where the partial sums of a call go: a buffer and its capacity in floats.  `fixed`: the buffer
-// cannot grow (the call then allocates nothing and fails with PIPAD_ERR_SCRATCH when the partial
-// sums do not fit); otherwise it is the frame's own buffer, which the call may replace by a larger
-// one (through the frame's allocator).
+// Where the partial sums of a call go: a buffer and its capacity in floats.  With a frame it is the
+// frame's own buffer, which the call may replace by a larger one (through the frame's allocator);
+// else it cannot grow (the call then allocates nothing and fails with PIPAD_ERR_SCRATCH when the
+// partial sums do not fit).
 struct ScratchRef {
   float **ptr;
   size_t *floats;
