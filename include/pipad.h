@@ -162,8 +162,8 @@ int pipad_frame_shape(const pipad_frame_t *frame, int32_t *n, int32_t *k);
  *   of 16 bytes where they are longer than 128; 1 GiB at most), which the first such call allocates
  *   and such a call with a larger one replaces; what is replaced, at most half as large, stays with
  *   the frame until pipad_frame_destroy().  Where it is refused the call does without, with the same
- *   bits, and no later call of the frame asks for as much.  All other calls only enqueue kernels on `stream`, without host
- *   synchronisation, so they can be recorded into a HIP graph (stream capture) once an eager call
+ *   bits, and no later call of the frame asks for as much.  All other calls only enqueue kernels on
+ *   `stream`, without host synchronisation, so they can be recorded into a HIP graph (stream capture) once an eager call
  *   with the same or a larger k*F has sized the scratch, whichever form (one matrix per snapshot,
  *   concatenated, with the update) either of them has.  A recorded call whose form takes more than
  *   the eager one left (rows padded to the slice width do, and the scaled operand) makes do with it, in
@@ -215,8 +215,8 @@ int pipad_frame_aggregate_subset(pipad_frame_t *frame, int32_t nsel, const int32
  *   All calls on one GPU share the array: calls that overlap in time on that GPU (different
  *   streams, or different frames) race on it and give wrong results; calls ordered on one stream
  *   are safe, and so are calls on frames without a row longer than "mid_max", which do not touch
- *   it.  Nothing in the array has to be cleared between calls: all of it is written before it is read within the
- *   same call. */
+ *   it.  Nothing in the array has to be cleared between calls: all of it is written before it is
+ *   read within the same call. */
 #define PIPAD_STATIC_SCRATCH_BYTES ((size_t)64 << 20)
 int pipad_frame_aggregate_static(const pipad_frame_t *frame, int32_t F, const float *const *X,
                                  int64_t ldx, float *const *Y, int64_t ldy, void *stream);

@@ -1792,15 +1792,16 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
     // a time take up to 1.5 times as long as rows of their own and a second launch; 32 and less are 4 to 30 % faster, but for
     // R-MAT frames with N = 300k .. 450k, k = 4 and 8, F = 16, Fo <= 24: with fresh operands up to 8 % slower.)
     const bool tiles = upd->Fo >= 16 && upd->Fo % 16 == 0;
-    // Widths that are multiples of 16 go inside, with the aggregation wanted and more than 32 columns but for two
-    // kinds of frames.  A wave inside takes 16 rows where that makes 2048 waves, those of mid and hub rows among them (`min_short`
-    // below; 32768 rows where all are short), else 4.  With 16 there are too few such waves (3600 at 58000 rows) to hide
-    // what the longest of its rows costs: with many entries, rows of their own and a second launch are faster.  With 4 it still
-    // multiplies 16: more than a second launch costs with more than 32 columns of H.  The lines are those of the frames that were
-    // measured, in rows and entries: 24000 rows with more than 500000 entries, which have long rows, mostly make the 2048 waves.  Of 1500 random frames and widths of both kinds, 1 to 16 snapshots, Chung-Lu and R-MAT, 1 to 40 % churn, behind is 1.25x as
-    // fast in the mean (0.94x to 1.65x; 98 in 100 gain; 2200 others the same): F = Fo = 64, n = 2k, k = 8, R-MAT of degree 16 26.0 -> 18.1 us, 24k, k = 2 48.3 -> 38.8,
-    // 36k, k = 1 43.2 -> 33.5.  With fewer rows behind is 0.8 to 1.1x, with half the entries (24k, k = 2, degree 6) 26.4 -> 27.7, from
-    // 58k rows on 0.85 to 1.3x without a rule that tells which, from 300k on 0.75 to 1.1x.
+    // Widths that are multiples of 16 go inside, with the aggregation wanted and more than 32 columns but for two kinds of frames.
+    // A wave inside takes 16 rows where that makes 2048 waves, those of mid and hub rows among them (`min_short` below; 32768 rows
+    // where all are short), else 4.  With 16 there are too few such waves (3600 at 58000 rows) to hide what the longest of its
+    // rows costs: with many entries, rows of their own and a second launch are faster.  With 4 it still multiplies 16: more than a
+    // second launch costs with more than 32 columns of H.  The lines are those of the frames that were measured, in rows and
+    // entries: 24000 rows with more than 500000 entries, which have long rows, mostly make the 2048 waves.  Of 1500 random frames
+    // and widths of both kinds, 1 to 16 snapshots, Chung-Lu and R-MAT, 1 to 40 % churn, behind is 1.25x as fast in the mean (0.94x
+    // to 1.65x; 98 in 100 gain; 2200 others the same): F = Fo = 64, n = 2k, k = 8, R-MAT of degree 16 26.0 -> 18.1 us, 24k, k = 2
+    // 48.3 -> 38.8, 36k, k = 1 43.2 -> 33.5.  With fewer rows behind is 0.8 to 1.1x, with half the entries (24k, k = 2, degree 6)
+    // 26.4 -> 27.7, from 58k rows on 0.85 to 1.3x without a rule that tells which, from 300k on 0.75 to 1.1x.
     const int64_t all_rows = (int64_t)f->n * f->k;
     int64_t all_entries = (int64_t)f->nnz_c * f->k;
     for (int t = 0; t < f->k; ++t) all_entries += f->nnz_d[t];

@@ -2128,12 +2128,11 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
 
   const int64_t row_blocks = ((int64_t)n + kBlock - 1) / kBlock;
   // Small frames take two launches instead of four (or five, with the sums in a launch of their own), and get room for their
-  // parts before these are known (RoomShift: 8 bytes per input entry, 82 MB at most here) together with what is sized up front, so
-  // that nothing waits for the host before
-  // it has the sizes.  Whole steps and slides: N = 2k, k = 4 55 -> 48 us, N = 20k, k = 4 59 -> 50, N = 1k .. 60k 60 to 80 ->
-  // 50 to 70; R-MAT 74k, k = 2 93 -> 78, Chung-Lu 125k, k = 1 62 -> 56.  Up to 2048 tiles and 20000 waves of k_prepare_mark, of
-  // which 8192 run together: N = 107k, k = 8 with 2000 tiles 190 -> 186, N = 45k, k = 12 with 1520 181 -> 178, but N = 113k,
-  // k = 16 with 1590 180 -> 187; with 3000 to 4000 tiles and k = 2 .. 6 3 to 13 % slower.
+  // parts before these are known (RoomShift: 8 bytes per input entry, 82 MB at most here) together with what is sized up front,
+  // so that nothing waits for the host before it has the sizes.  Whole steps and slides: N = 2k, k = 4 55 -> 48 us, N = 20k, k =
+  // 4 59 -> 50, N = 1k .. 60k 60 to 80 -> 50 to 70; R-MAT 74k, k = 2 93 -> 78, Chung-Lu 125k, k = 1 62 -> 56.  Up to 2048 tiles
+  // and 20000 waves of k_prepare_mark, of which 8192 run together: N = 107k, k = 8 with 2000 tiles 190 -> 186, N = 45k, k = 12
+  // with 1520 181 -> 178, but N = 113k, k = 16 with 1590 180 -> 187; with 3000 to 4000 tiles and k = 2 .. 6 3 to 13 % slower.
   bool small = g.ntiles <= kSumTiles && row_blocks <= kSumRowBlocks && (int64_t)g.ntiles * k <= 20000;
   // Frames of up to 33 M entries in all snapshots get that room as well (270 MB at most), and their rows are made next to the
   // entries, in the launch that would wait for the host otherwise: steps and slides N = 100k R-MAT, k = 5 198 -> 191 us,
