@@ -1385,7 +1385,7 @@ __device__ __forceinline__ void store_scales(const SplitArgs &g, const int32_t (
       for (int r = 0; r < UN; ++r) w[r] = *reinterpret_cast<const float4 *>(g.dinv_nk + (int64_t)c[r] * stride + 4 * q);
 #pragma unroll
       for (int r = 0; r < UN; ++r)
-        if (live[r]) put_scales(g.swc, q, g.k, to[r], w[r]);
+        if (live[r]) put_scales_nt(g.swc, q, g.k, to[r], w[r]);
     }
   } else if (g.k == 2) {
     float2 w[UN];
@@ -1394,8 +1394,8 @@ __device__ __forceinline__ void store_scales(const SplitArgs &g, const int32_t (
 #pragma unroll
     for (int r = 0; r < UN; ++r)
       if (live[r]) {
-        g.swc[0][to[r]] = w[r].x;
-        g.swc[1][to[r]] = w[r].y;
+        __builtin_nontemporal_store(w[r].x, g.swc[0] + to[r]);
+        __builtin_nontemporal_store(w[r].y, g.swc[1] + to[r]);
       }
   } else {
     float w[UN];
@@ -1403,7 +1403,7 @@ __device__ __forceinline__ void store_scales(const SplitArgs &g, const int32_t (
     for (int r = 0; r < UN; ++r) w[r] = g.dinv_nk[c[r]];
 #pragma unroll
     for (int r = 0; r < UN; ++r)
-      if (live[r]) g.swc[0][to[r]] = w[r];
+      if (live[r]) __builtin_nontemporal_store(w[r], g.swc[0] + to[r]);
   }
 }
 
@@ -1542,8 +1542,8 @@ __device__ __forceinline__ void fill_part(const SplitArgs &g, int32_t u, int p, 
 #pragma unroll
         for (int r = 0; r < UN; ++r)
           if (j0 + r * W * kWave < here) {
-            g.scol_d[to[r]] = c[r];
-            g.swd[to[r]] = w[r];
+            __builtin_nontemporal_store(c[r], g.scol_d + to[r]);
+            __builtin_nontemporal_store(w[r], g.swd + to[r]);
           }
       } else {
         int32_t live[UN];
@@ -1551,7 +1551,7 @@ __device__ __forceinline__ void fill_part(const SplitArgs &g, int32_t u, int p, 
         for (int r = 0; r < UN; ++r) live[r] = j0 + r * W * kWave < here;
 #pragma unroll
         for (int r = 0; r < UN; ++r)
-          if (live[r]) g.scol_c[to[r]] = c[r];
+          if (live[r]) __builtin_nontemporal_store(c[r], g.scol_c + to[r]);
         store_scales<UN>(g, c, to, live);
       }
     }
@@ -1563,8 +1563,10 @@ __device__ __forceinline__ void fill_part(const SplitArgs &g, int32_t u, int p, 
 // (build_split_arrays): a wave alone goes through 2048 entries in 32 steps of memory round trips, and on
 // all but the largest frames there are too few of them to hide that.  A wave per unit of every part took
 // 35 us on an R-MAT frame with N = 100k, k = 5, now 14; N = 200k Chung-Lu, k = 8 28, now 21.  On the
-// 1M-node R-MAT frame 0.25 ms either way: most of what is fetched are lines of D^-1/2 for a few scales
+// 1M-node R-MAT frame the same either way (0.25 ms then): most of what is fetched are lines of D^-1/2 for a few scales
 // each, and 0.36 GB are written.
+// Its stores go past the caches: they were in the way of the lines that scales are gathered from, and the aggregation
+// reads them only after the caches hold other things.  R-MAT 1M 239 -> 216 us, N = 200k, k = 8 18.0 -> 16.8.
 // An XCD takes a run of the exclusive parts' units, so that it reads one or two snapshots' D^-1/2 instead
 // of all: N = 200k, k = 8 60 -> 38 MB fetched, 21 -> 18.5 us; R-MAT 1M 250 -> 242; N = 100k 14 -> 13.2.  The runs hold as
 // many entries each, as far as the parts' sizes tell: with as many workgroups each, N = 1M Chung-Lu, k = 4, one snapshot of 10M

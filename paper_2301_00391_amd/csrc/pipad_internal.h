@@ -285,6 +285,13 @@ __device__ __forceinline__ void put_scales(float *const (&w)[PIPAD_MAX_K], int q
   if (FULL || 4 * q + 2 < k) w[4 * q + 2][at] = v.z;
   if (FULL || 4 * q + 3 < k) w[4 * q + 3][at] = v.w;
 }
+// The same past the caches.
+__device__ __forceinline__ void put_scales_nt(float *const (&w)[PIPAD_MAX_K], int q, int32_t k, int32_t at, float4 v) {
+  __builtin_nontemporal_store(v.x, w[4 * q] + at);
+  if (4 * q + 1 < k) __builtin_nontemporal_store(v.y, w[4 * q + 1] + at);
+  if (4 * q + 2 < k) __builtin_nontemporal_store(v.z, w[4 * q + 2] + at);
+  if (4 * q + 3 < k) __builtin_nontemporal_store(v.w, w[4 * q + 3] + at);
+}
 
 // Inclusive sum over the lanes up to this one: within rows of 16 lanes, then across the rows.
 __device__ __forceinline__ uint32_t wave_sum(uint32_t x) {
