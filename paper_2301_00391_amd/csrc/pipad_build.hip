@@ -172,11 +172,13 @@ __device__ inline void count_rows(const RowClasses &rc, bool live, int64_t L, in
   }
 }
 
-// Eight lanes per tile boundary: they find its row together (a 9-way search: seven round trips to
+// G lanes per tile boundary: they find its row together (eight, a 9-way search: seven round trips to
 // memory for a million rows instead of twenty), then each of them its column in some of the
-// snapshots.
+// snapshots, one after the other.  Bound: that chain of round trips; so 16 lanes for more than eight snapshots, one
+// for each up to 16 (whole k_prepare: N = 103k, k = 16 22.2 -> 16.1 us, R-MAT 168k, k = 12 17.3 -> 13.0; 572k, k = 16, where
+// the rows take longer, 53.6 -> 52.7; 16 for up to eight snapshots 9.0 -> 9.4).
+template <int G>
 __device__ inline void find_bounds(const Snaps &s, const Tiles &g, int64_t wave, int lane) {
-  constexpr int G = 8;
   const int sub = lane & (G - 1), group0 = lane & ~(G - 1);
   const int64_t c64 = wave * (kWave / G) + lane / G;
   const bool search = c64 < g.ntiles;
@@ -254,12 +256,13 @@ __device__ __forceinline__ void prepare_rows(const Snaps &s, const Tiles &g, con
 
 // The first `bound_blocks` workgroups find the tiles' bounds (they wait for memory most of the
 // time), the others take 256 rows each.
+template <int G>
 __global__ __launch_bounds__(kBlock) void k_prepare(Snaps s, Tiles g, RowClasses rc, int32_t bound_blocks,
                                                      float *dinv, float *dinv_nk) {
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   if ((int32_t)blockIdx.x < bound_blocks) {
     if (blockIdx.x == 0 && threadIdx.x == 0) *g.bad = 0;
-    find_bounds(s, g, (int64_t)blockIdx.x * kWavesPerBlock + wave, lane);
+    find_bounds<G>(s, g, (int64_t)blockIdx.x * kWavesPerBlock + wave, lane);
     return;
   }
   prepare_rows(s, g, rc, (int64_t)blockIdx.x - bound_blocks, dinv, dinv_nk);
@@ -2262,9 +2265,10 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
       hipLaunchKernelGGL((k <= 16 ? k_prepare_mark<512, 1> : k_prepare_mark<256, 2>), dim3((unsigned)(g.ntiles + row_wgs)),
                          dim3((unsigned)threads), mark_lds, st, s, g, hub_min, row_classes(f), f->dinv, f->dinv_nk);
   } else {
-    const int32_t bound_blocks = (int32_t)(((int64_t)g.ntiles + 1 + kWavesPerBlock * 8 - 1) / (kWavesPerBlock * 8));
-    hipLaunchKernelGGL(k_prepare, dim3((unsigned)(bound_blocks + row_blocks)), dim3(kBlock), 0, st, s, g, row_classes(f),
-                       bound_blocks, f->dinv, f->dinv_nk);
+    const int per_block = kBlock / (k > 8 ? 16 : 8);  // bounds
+    const int32_t bound_blocks = (int32_t)(((int64_t)g.ntiles + 1 + per_block - 1) / per_block);
+    hipLaunchKernelGGL((k > 8 ? k_prepare<16> : k_prepare<8>), dim3((unsigned)(bound_blocks + row_blocks)), dim3(kBlock), 0, st,
+                       s, g, row_classes(f), bound_blocks, f->dinv, f->dinv_nk);
     if (g.ntiles > 0) {
       auto mark = k <= 16 ? (large ? k_mark<512, 1, uint64_t> : k_mark<512, 1, uint32_t>)
                           : (large ? k_mark<256, 2, uint64_t> : k_mark<256, 2, uint32_t>);
