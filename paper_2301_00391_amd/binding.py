@@ -1,4 +1,5 @@
-"""Thin ctypes binding of libpipad.so: argument marshalling only.
+"""Thin binding of libpipad.so: argument marshalling only, by ctypes and, for plain arguments of the calls that a
+step makes, by _host (csrc/pipad_host.cpp), which hands anything else back to the code here.
 
 Every step of the path (overlap extraction, normalisation, aggregation) runs in the HIP kernels of
 the library; nothing here computes.  PyTorch supplies device memory and streams.  There is no CPU
@@ -13,7 +14,7 @@ from __future__ import annotations
 
 import ctypes
 import functools
-import itertools
+import importlib
 import os
 import struct
 from typing import List, Optional, Sequence, Tuple, Union
@@ -26,6 +27,8 @@ MAX_K = 32
 VALIDATE = 1
 
 _lib = None
+_host = None      # the native half of this module
+_address: dict = {}  # the library's functions for it
 
 
 class PipadError(RuntimeError):
@@ -81,8 +84,9 @@ def load_library():
     """Loads libpipad.so (building it first only if it does not exist yet).  The environment
     variable PIPAD_LIBRARY names another build of the library to load instead (measurement builds,
     see build.py); a missing file is an error, never a fallback."""
-    global _lib
+    global _lib, _host
     if _lib is None:
+        _host = _load_host()
         path = os.environ.get("PIPAD_LIBRARY") or LIB_PATH
         if path == LIB_PATH and not os.path.exists(LIB_PATH):
             from . import build as _build
@@ -92,8 +96,17 @@ def load_library():
             fn = getattr(lib, name)
             fn.restype = res
             fn.argtypes = args
+            _address[name] = ctypes.cast(fn, _vp).value
         _lib = lib
     return _lib
+
+
+def _load_host():
+    """The native half of this module (built first only if it does not exist yet)."""
+    from . import build as _build
+    if not os.path.exists(_build.HOST):
+        _build.build_host()
+    return importlib.import_module("._host", __package__)
 
 
 def _check(status: int) -> None:
@@ -157,22 +170,22 @@ Snapshot = Tuple[torch.Tensor, torch.Tensor]  # (rowptr int32[n+1], colidx int32
 class Frame:
     """Owner of one ``pipad_frame_t``.  Built by :func:`frame_build_overlap`."""
 
-    def __init__(self, handle: int, n: int, k: int, device, buffers: dict, key: Optional[int] = None,
+    def __init__(self, handle: int, n: int, k: int, device, buffers, key: Optional[int] = None,
                  stream=None):
         self._h = handle
         self.n, self.k, self.device = n, k, device
-        self._index = _device_index(device)
-        self._buffers = buffers  # torch tensors handed to the library through the allocator, by address
-        self._key = key  # names the buffers to the library's callback, which it may use again (aggregate scratch)
+        self._index = index = _device_index(device)
+        self._buffers = buffers  # what the library got through the allocator callback, by address
         # torch's allocator hands memory out, and takes it back, in the order of the stream that
         # was current at the allocation; work on any other stream has to be waited for in close().  Scratch
         # that a later call asks for is ordered by the stream that is current then, and the frame's own has to be
         # waited for as well from there on.
-        self._alloc_stream = _current_raw_stream(self._index)
+        self._alloc_stream = _current_raw_stream(index)
         self._other_streams = {}
         self._temp = None
-        built_on = self._stream(stream)
-        if key is not None:
+        built_on = self._alloc_stream if stream is None else self._stream(stream)
+        # (key: the memory is torch's.  In one piece it holds no temporaries of their own.)
+        if key is not None and len(buffers) != 1:
             # the build's temporaries can go back to the allocator as soon as the build's kernels have
             # run: at once where its order is that of the build's stream, else behind an event
             ptr = _vp()
@@ -210,7 +223,6 @@ class Frame:
             load_library().pipad_frame_destroy(self._h)
             self._h = None
             self._temp = None
-            _owners.pop(self._key, None)
             self._buffers.clear()
 
     def __del__(self):
@@ -249,52 +261,35 @@ class Frame:
         return _copy_from_device(ptr.value, self.k * self.n, torch.float32, self.device).view(self.k, self.n)
 
 
-# The callback through which the library takes memory from PyTorch's caching allocator, and the frames'
-# buffers by the key it is called with.  One callback for all frames: a ctypes callback sits in a
-# reference cycle, and with one per frame the garbage collector walked the whole program every few
-# hundred frames (10 us per build, of 52, for frames of a thousand nodes).
-_owners: dict = {}  # key -> (the tensors handed out, by address, which keeps them alive; device)
-_next_key = itertools.count(1).__next__
-
-
-def _allocate(nbytes, key):
-    try:
-        buffers, device = _owners[key]
-        buf = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
-        ptr = buf.data_ptr()
-        buffers[ptr] = buf
-        return ptr
-    except Exception:  # out of memory -> NULL -> PIPAD_ERR_ALLOC
-        return None
-
-
-_allocate_callback = ALLOC_FN(_allocate)
-_ALLOCATE = ctypes.cast(_allocate_callback, _vp)
-
-
 def _build(index: int, n: int, k: int, device, allocator: str, stream, fn, *args) -> Frame:
     """The frame that fn(*args, allocator, its context, stream, result) makes."""
     if allocator not in ("torch", "library"):
         raise ValueError("allocator must be 'torch' or 'library'")
-    buffers: dict = {}
-    key = None
+    # (the library takes memory from PyTorch's caching allocator through a native callback, which keeps it in `buffers`)
+    buffers, callback, context = {}, None, None
     if allocator == "torch":
-        key = _next_key()
-        _owners[key] = (buffers, device)
+        buffers = _host.Buffers()
+        callback, context = _host.ALLOCATE, buffers.context()
     out = _vp()
     raw = int(stream.cuda_stream) if stream is not None else _current_raw_stream(index)
-    try:
-        _check(_on_device(index, fn, *args, _ALLOCATE if key is not None else None, key, raw, ctypes.byref(out)))
-    except BaseException:
-        _owners.pop(key, None)
-        raise
-    return Frame(out.value, n, k, device, buffers, key, stream)
+    _check(_on_device(index, fn, *args, callback, context, raw, ctypes.byref(out)))
+    return Frame(out.value, n, k, device, buffers, context, stream)
 
 
 def frame_transpose(frame: Frame, allocator: str = "torch", stream=None) -> Frame:
     """pipad_frame_transpose: the frame of the transposed patterns with the same D^-1/2; aggregating
     with it applies the transposed operator (the backward pass for directed patterns)."""
-    return _build(frame._index, frame.n, frame.k, frame.device, allocator, stream,
+    index = frame._index
+    if allocator == "torch" and _current_device() == index:
+        buffers = _host.Buffers()
+        made = _host.transpose(_address["pipad_frame_transpose"], frame._h, buffers,
+                               int(stream.cuda_stream) if stream is not None else _current_raw_stream(index))
+        if made is not None:
+            status, handle = made
+            if status:
+                _check(status)
+            return Frame(handle, frame.n, frame.k, frame.device, buffers, 1, stream)
+    return _build(index, frame.n, frame.k, frame.device, allocator, stream,
                   load_library().pipad_frame_transpose, frame._h)
 
 
@@ -314,6 +309,16 @@ def frame_build_overlap(snapshots: Sequence[Snapshot], validate: bool = False,
     if not rp0.is_cuda:
         raise ValueError("snapshots must be contiguous int32 tensors on one GPU")
     index = _device_index(device)
+    flags = VALIDATE if validate else 0
+    if allocator == "torch" and _current_device() == index:
+        buffers = _host.Buffers()
+        made = _host.build(_address["pipad_frame_build_overlap"], snapshots, index, flags, buffers,
+                           int(stream.cuda_stream) if stream is not None else _current_raw_stream(index))
+        if made is not None:
+            status, handle, n = made
+            if status:
+                _check(status)
+            return Frame(handle, n, k, device, buffers, 1, stream)
     int32 = torch.int32
     descr = []
     for rp, col in snapshots:
@@ -323,7 +328,7 @@ def frame_build_overlap(snapshots: Sequence[Snapshot], validate: bool = False,
         nnz = col.numel()
         descr += (rp.numel() - 1 & 0xffffffff, nnz & 0xffffffff, rp.data_ptr(), col.data_ptr() if nnz else 0)
     return _build(index, n, k, device, allocator, stream, lib.pipad_frame_build_overlap,
-                  n, k, _pack_csr(k)(*descr), VALIDATE if validate else 0)
+                  n, k, _pack_csr(k)(*descr), flags)
 
 
 Features = Union[torch.Tensor, Sequence[torch.Tensor]]
@@ -377,6 +382,14 @@ def frame_aggregate(frame: Frame, X: Features, Y: Optional[Features] = None, str
     the library; pass Y, or this wrapper allocates it before the call)."""
     lib = load_library()
     n, k = frame.n, frame.k
+    if Y is not None and _current_device() == frame._index:
+        frame._release_temporaries()
+        status = _host.aggregate(_address["pipad_frame_aggregate_static" if static_scratch else "pipad_frame_aggregate"],
+                                 frame._h, n, k, X, Y, frame._stream(stream))
+        if status is not None:
+            if status:
+                _check(status)
+            return Y
     xp, ldx, F = _operand(X, n, k, "X")
     if Y is None:
         if isinstance(X, torch.Tensor):
@@ -405,6 +418,13 @@ def frame_aggregate_subset(frame: Frame, snapshots: Sequence[int], X: Sequence[O
         return
     if len(X) != k or len(Y) != k:
         raise ValueError("X and Y must have k entries")
+    if _current_device() == frame._index:
+        frame._release_temporaries()
+        status = _host.subset(_address["pipad_frame_aggregate_subset"], frame._h, n, k, sel, X, Y, frame._stream(stream))
+        if status is not None:
+            if status:
+                _check(status)
+            return
     F, ldx, ldy = None, None, None
     xa, ya = [0] * k, [0] * k
     for t in sel:
@@ -436,6 +456,13 @@ def frame_aggregate_update(frame: Frame, X: Features, W: torch.Tensor,
     receives the aggregation results.  Only enqueues work on the stream."""
     lib = load_library()
     n, k = frame.n, frame.k
+    if H is not None and _current_device() == frame._index:
+        frame._release_temporaries()
+        status = _host.update(_address["pipad_frame_aggregate_update"], frame._h, n, k, X, W, bias, A, H, frame._stream(stream))
+        if status is not None:
+            if status:
+                _check(status)
+            return H
     xp, ldx, F = _operand(X, n, k, "X")
     if W.dtype != torch.float32 or W.dim() != 2 or W.shape[0] != F or W.stride(1) != 1:
         raise ValueError("W must be a float32 [F, Fo] matrix with unit column stride")

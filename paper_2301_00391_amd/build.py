@@ -1,4 +1,4 @@
-"""Builds libpipad.so (HIP, gfx950 only) in-tree with hipcc.
+"""Builds libpipad.so (HIP, gfx950 only) in-tree with hipcc, and _host.so, the native half of the binding, with g++.
 
     python -m paper_2301_00391_amd.build [-v] [-D NAME[=VALUE] ...] [-o PATH]
 
@@ -18,6 +18,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpipad.so")
+HOST = os.path.join(HERE, "_host.so")
 SOURCES = ["pipad_api.hip", "pipad_build.hip", "pipad_aggregate.hip", "pipad_transpose.hip",
            "pipad_ceilings.hip"]
 
@@ -76,6 +77,22 @@ def build(verbose: bool = False, defines=(), output: str = LIB) -> str:
     subprocess.run(link, check=True)
     for o in objs:
         os.remove(o)
+    return output
+
+
+def build_host(verbose: bool = False, output: str = HOST) -> str:
+    """Compiles the native half of the binding against this interpreter and its torch.  Always rebuilds."""
+    import sysconfig
+    import torch
+    root = os.path.dirname(torch.__file__)
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           *[a for d in (os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
+                         sysconfig.get_paths()["include"]) for a in ("-isystem", d)],
+           "-I", os.path.join(ROOT, "include"), os.path.join(CSRC, "pipad_host.cpp"), "-o", output,
+           "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
     return output
 
 
