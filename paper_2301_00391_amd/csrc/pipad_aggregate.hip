@@ -48,6 +48,7 @@
 #include <algorithm>
 #include <cstring>
 #include <mutex>
+#include <type_traits>
 
 #include "pipad_internal.h"
 
@@ -120,16 +121,16 @@ struct AggArgs {
   const int32_t *item_row, *item_v0, *item_v1, *hub_rows, *hub_item_off;
   const int32_t *sptr;    // class parts of the hub rows: see pipad_frame
   const int32_t *scol_c, *scol_d;
-  const float *swd;
+  const void *swd;
   float *partial;
   const int32_t *rowptr_d[PIPAD_MAX_K];
   const int32_t *col_d[PIPAD_MAX_K];
-  const float *wc[PIPAD_MAX_K];
-  const float *wd[PIPAD_MAX_K];
-  const float *swc[PIPAD_MAX_K];
+  const void *wc[PIPAD_MAX_K];  // the scales: floats, or codes where `coded`
+  const void *wd[PIPAD_MAX_K];
+  const void *swc[PIPAD_MAX_K];
+  int32_t coded;
   const float *table;     // coalescent kernel: the rows times their scales, row stride ldt (k_scale_rows)
   int64_t ldt;
-  const float *dinv_nk;
   const float *X[PIPAD_MAX_K];
   float *Y[PIPAD_MAX_K];   // aggregation results (optional when the update is fused in)
   // fused update: H_t = Y_t W + bias
@@ -236,9 +237,9 @@ struct Slice {
   float *yb;                // Y_t + feature column of this lane (null: not wanted)
   float *ht;                // H_t (fused update only)
   const float *dv;          // dinv_t
-  const float *wc, *wd;     // per-entry column scales of the common / exclusive part (short rows)
+  const void *wc, *wd;      // per-entry column scales of the common / exclusive part (short rows)
   const int32_t *rpd, *cd;  // exclusive CSR of snapshot t (short rows)
-  const float *swc;         // column scales of the common region of the class-grouped entries
+  const void *swc;          // column scales of the common region of the class-grouped entries
   int fcol;
   bool fvalid;              // the lane's columns exist (F need not fill the last slice)
 };
@@ -272,10 +273,10 @@ __device__ __forceinline__ Slice slice_setup(const AggArgs &a, int t, int fc, in
   return s;
 }
 
-// One entry as fetched (column index and column scale) ...
+// One entry as fetched (column index, and the column scale's bits or code) ...
 struct Raw {
   int32_t c;
-  float w;
+  uint32_t w;
 };
 // ... and as staged in LDS for the lane groups: where its feature row starts, and the scale.
 struct Staged {
@@ -286,22 +287,33 @@ struct Staged {
 // A row's two entry lists, walked as one: the common entries, then the exclusive ones.
 struct Lists {
   const int32_t *colc, *cold;  // (the same for the whole wave)
-  const float *wc, *wd;
+  const void *wc, *wd;
 };
+
+// Where the column scales of a row's entries come from.
+enum Scales {
+  kStreams,   // out of the lists of scales, each product added in one operation
+  kTable,     // the gathered rows hold the products (k_scale_rows); four of them are added up, then to the sum
+  kProducts,  // out of the lists, with the products and sums of kTable: the same bits
+  kCodes, kCodeProducts  // as kStreams and kProducts, out of lists of codes (scale_code)
+};
+constexpr bool coded(Scales s) { return s == kCodes || s == kCodeProducts; }
 
 // Entry `pos` of a row whose lists start at cs / ds and hold clen / total - clen entries, or (own row,
 // weight 0) past their end: such a filler may be gathered harmlessly, which lets the FAST inner loop
 // run without bounds checks.
+template <Scales S>
 __device__ __forceinline__ Raw fetch_entry(const Lists &l, int32_t cs, int32_t clen, int32_t ds, int32_t total,
                                            int32_t pos, int32_t self, bool nt) {
   Raw r;
   r.c = self;
-  r.w = 0.f;
+  r.w = 0;
   if (pos < total) {
     const bool common = pos < clen;
     const int32_t at = common ? cs + pos : ds + (pos - clen);
     const int32_t *pc = (common ? l.colc : l.cold) + at;
-    const float *pw = (common ? l.wc : l.wd) + at;
+    using W = std::conditional_t<coded(S), uint16_t, uint32_t>;
+    const W *pw = static_cast<const W *>(common ? l.wc : l.wd) + at;
     if (nt) {
       r.c = __builtin_nontemporal_load(pc);
       r.w = __builtin_nontemporal_load(pw);
@@ -313,18 +325,11 @@ __device__ __forceinline__ Raw fetch_entry(const Lists &l, int32_t cs, int32_t c
   return r;
 }
 
-// Where the column scales of a row's entries come from.
-enum Scales {
-  kStreams,   // out of the lists of scales, each product added in one operation
-  kTable,     // the gathered rows hold the products (k_scale_rows); four of them are added up, then to the sum
-  kProducts,  // out of the lists, with the products and sums of kTable: the same bits
-};
-
 // The same without the scale: column -1 past the end, so that no weight takes a register.
 __device__ __forceinline__ Raw fetch_index(const Lists &l, int32_t cs, int32_t clen, int32_t ds, int32_t total, int32_t pos) {
   Raw r;
   r.c = -1;
-  r.w = 0.f;
+  r.w = 0;
   if (pos < total) {
     const bool common = pos < clen;
     r.c = (common ? l.colc : l.cold)[common ? cs + pos : ds + (pos - clen)];
@@ -334,26 +339,28 @@ __device__ __forceinline__ Raw fetch_index(const Lists &l, int32_t cs, int32_t c
 template <Scales S>
 __device__ __forceinline__ Raw fetch(const Lists &l, int32_t cs, int32_t clen, int32_t ds, int32_t total, int32_t pos,
                                      int32_t self, bool nt) {
-  return S == kTable ? fetch_index(l, cs, clen, ds, total, pos) : fetch_entry(l, cs, clen, ds, total, pos, self, nt);
+  return S == kTable ? fetch_index(l, cs, clen, ds, total, pos) : fetch_entry<S>(l, cs, clen, ds, total, pos, self, nt);
 }
 
 template <Scales S>
 __device__ __forceinline__ uint32_t entry_column(const Raw &r) { return (uint32_t)(S == kTable ? max(r.c, 0) : r.c); }
 template <Scales S>
-__device__ __forceinline__ float entry_weight(const Raw &r) { return S == kTable ? (r.c >= 0 ? 1.f : 0.f) : r.w; }
+__device__ __forceinline__ float entry_weight(const Raw &r) {
+  return S == kTable ? (r.c >= 0 ? 1.f : 0.f) : coded(S) ? scale_of(r.w) : __uint_as_float(r.w);
+}
 
 // Adds the (up to) four gathered rows of one step to the sum.
 template <int VEC, Scales S, int N>
 __device__ __forceinline__ void add_step(const float (&w)[N], const typename V<VEC>::T (&x)[N], typename V<VEC>::T &acc) {
   using VT = V<VEC>;
-  if constexpr (S == kStreams) {
+  if constexpr (S == kStreams || S == kCodes) {
 #pragma unroll
     for (int j = 0; j < N; ++j) VT::fma(acc, w[j], x[j]);
   } else {
     static_assert(N == 4, "");
     typename VT::T p[N];
 #pragma unroll
-    for (int j = 0; j < N; ++j) p[j] = w[j] == 0.f ? VT::zero() : S == kProducts ? VT::product(w[j], x[j]) : x[j];  // (a filler may be infinite)
+    for (int j = 0; j < N; ++j) p[j] = w[j] == 0.f ? VT::zero() : S != kTable ? VT::product(w[j], x[j]) : x[j];  // (a filler may be infinite)
     VT::add(p[0], p[1]);
     VT::add(p[2], p[3]);
     VT::add(p[0], p[2]);
@@ -667,7 +674,7 @@ __device__ __forceinline__ Piece unit_piece(const AggArgs &a, int64_t unit, cons
 }
 
 // PLAIN: hub units as they are in a frame with plain_units.
-template <int VEC, bool FAST, int EPL, bool UPD, bool PLAIN, bool ALONE = false>
+template <int VEC, bool FAST, int EPL, bool UPD, bool PLAIN, bool ALONE = false, Scales S = kStreams>
 __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
   using VT = V<VEC>;
   static_assert(!UPD || (VEC == 4 && FAST), "the fused update rides on the fast float4 path");
@@ -766,11 +773,11 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
     l.wd = s.wd;
     Raw head[EPL];
 #pragma unroll
-    for (int j = 0; j < EPL; ++j) head[j] = fetch_entry(l, p.cs, p.clen, p.ds, p.len, j * kWave + lane, p.i, ntl);
+    for (int j = 0; j < EPL; ++j) head[j] = fetch_entry<S>(l, p.cs, p.clen, p.ds, p.len, j * kWave + lane, p.i, ntl);
     const typename VT::T xi = VT::load(s.xb + (int64_t)p.i * a.ldx);
     const float di = s.dv[p.i];
     typename VT::T acc = VT::zero();
-    walk<VEC, U, FAST, EPL, ALONE>(l, p.cs, p.clen, p.ds, p.len, head, 0, kWave, lane, team, nteams, s, a.ldx, p.i, ntl, lds,
+    walk<VEC, U, FAST, EPL, ALONE, S>(l, p.cs, p.clen, p.ds, p.len, head, 0, kWave, lane, team, nteams, s, a.ldx, p.i, ntl, lds,
                                    acc);
     reduce_slots<VEC>(a.ls_log2, acc);
     if (team == 0) sums[wave][fl] = acc;
@@ -882,7 +889,7 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
     if (!it.have) { it.clen = 0; it.len = 0; }
 #pragma unroll
     for (int j = 0; j < EPL; ++j)
-      it.first[j] = fetch_entry(lists, it.cs, it.clen, it.ds, it.len, j * team_lanes + q, it.i, ntl);
+      it.first[j] = fetch_entry<S>(lists, it.cs, it.clen, it.ds, it.len, j * team_lanes + q, it.i, ntl);
     it.xi = VT::zero();
     if (!split) it.xi = VT::load(s.xb + (int64_t)it.i * a.ldx);
     return it;
@@ -901,7 +908,7 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
     if (step + 1 < nsteps) nxt = prefetch(step + 1);
     typename VT::T acc = VT::zero();
     if (wide) {
-      walk<VEC, U, FAST, EPL, ALONE>(lists, cur.cs, cur.clen, cur.ds, cur.len, cur.first, team_base, team_lanes, q, slot, nslots,
+      walk<VEC, U, FAST, EPL, ALONE, S>(lists, cur.cs, cur.clen, cur.ds, cur.len, cur.first, team_base, team_lanes, q, slot, nslots,
                           s, a.ldx, cur.i, ntl, lds, acc);
       reduce_slots<VEC>(a.ls_log2, acc);
       if (split) {
@@ -915,7 +922,7 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
       }
     } else {
       if (cur.have)
-        walk<VEC, U, FAST, EPL, ALONE>(lists, cur.cs, cur.clen, cur.ds, cur.len, cur.first, team_base, team_lanes, q, slot, nslots,
+        walk<VEC, U, FAST, EPL, ALONE, S>(lists, cur.cs, cur.clen, cur.ds, cur.len, cur.first, team_base, team_lanes, q, slot, nslots,
                             s, a.ldx, cur.i, ntl, lds, acc);
       if constexpr (UPD) {
         if (cur.have) finish_row_to_sink(a, s, sink, sink.cnt + team, fl, cur.i, cur.di, cur.xi, acc);
@@ -935,18 +942,18 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
 // EPL: entries per lane and chunk; teams of 8 lanes and more get on with 1.  (Teams of 1 and 2 lanes with
 // one entry per lane, fetched and gathered one after the other: N = 500k, k = 4, F = 4 486 us, with 4
 // entries 375; 8 entries take too many registers.)
-template <int VEC, bool FAST, int EPL, bool PLAIN, bool ALONE = false>
+template <int VEC, bool FAST, int EPL, bool PLAIN, bool ALONE = false, Scales S = kStreams>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(PIPAD_AGG_WAVES)))
 void k_aggregate(const AggArgs a) {
-  aggregate_body<VEC, FAST, EPL, false, PLAIN, ALONE>(a);
+  aggregate_body<VEC, FAST, EPL, false, PLAIN, ALONE, S>(a);
 }
 
 // The same walk with the update fused in, held to the four waves per SIMD that its 120 registers allow
 // (left to the compiler: 853 us against 851 on N = 200k, k = 8, F = Fo = 64).
-template <bool PLAIN>
+template <bool PLAIN, Scales S = kStreams>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void k_aggregate_update(const AggArgs a) {
-  aggregate_body<4, true, 1, true, PLAIN>(a);
+  aggregate_body<4, true, 1, true, PLAIN, false, S>(a);
 }
 
 // Adds the partial sums of every hub row in a fixed order and finishes the row.  One wave per
@@ -1224,7 +1231,7 @@ __device__ __forceinline__ float *unit_partial(const AggArgs &a, int g, int64_t 
 template <int VEC, Scales S>
 __device__ __forceinline__ void finish_coalescent(float *y, float di, typename V<VEC>::T xi, typename V<VEC>::T acc, bool nt) {
   using VT = V<VEC>;
-  if constexpr (S == kStreams) {
+  if constexpr (S == kStreams || S == kCodes) {
     VT::fma(acc, di, xi);
     VT::store(y, VT::scale(di, acc), nt);
   } else {
@@ -1353,9 +1360,9 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_coalescent(const AggArgs a
   // entry lists: the class-grouped copies for hub units, the frame's CSRs for whole rows
   Lists lists;
   {
-    const float *w_plain = a.wc[t], *w_grouped = a.swc[t];
+    const void *w_plain = a.wc[t], *w_grouped = a.swc[t];
     const int32_t *d_plain = a.col_d[t];
-    const float *wd_plain = a.wd[t];
+    const void *wd_plain = a.wd[t];
     lists.colc = split ? a.scol_c : a.col_c;
     lists.cold = split ? a.scol_d : d_plain;
     lists.wc = split ? w_grouped : w_plain;
@@ -1531,7 +1538,7 @@ __global__ __launch_bounds__(kBlock) void k_scale_rows(const AggArgs a, float *t
   if (x >= (int64_t)a.n * quads) return;
   const int32_t i = (int32_t)(x / quads);
   const uint32_t c = 4 * (uint32_t)(x - (int64_t)i * quads);
-  const float *scales = a.dinv_nk + (int64_t)i * node_stride(a.k), *row = a.X[0] + (int64_t)i * a.ldx;
+  const float *row = a.X[0] + (int64_t)i * a.ldx;
   float v[4], w[4];
   if (VECTOR) {
     const float4 q = V<4>::load(row + c);
@@ -1541,7 +1548,7 @@ __global__ __launch_bounds__(kBlock) void k_scale_rows(const AggArgs a, float *t
   for (int j = 0; j < 4; ++j) {
     const uint32_t at = min(c + j, cols - 1);
     if (!VECTOR) v[j] = row[at];
-    w[j] = scales[at / (uint32_t)a.F];
+    w[j] = a.dinv[(int64_t)(at / (uint32_t)a.F) * a.n + i];
   }
   // (the table's rows are padded to 16 bytes)
   *reinterpret_cast<float4 *>(table + (int64_t)i * a.ldt + c) =
@@ -1563,13 +1570,13 @@ inline size_t update_lds_bytes(const AggArgs &a) {
 }
 
 // The instance for teams of 1 << ls_log2 lanes (rows of one column at a time have at most four columns).
-template <int VEC, bool PLAIN>
+template <int VEC, bool PLAIN, Scales S = kStreams>
 void (*aggregate_kernel(bool fast, int ls_log2))(AggArgs) {
-  if (!fast) return k_aggregate<VEC, false, 1, PLAIN>;
+  if (!fast) return k_aggregate<VEC, false, 1, PLAIN, false, S>;
   if constexpr (VEC > 1)
-    if (ls_log2 >= 3) return k_aggregate<VEC, true, 1, PLAIN>;
-  return ls_log2 >= 2 ? k_aggregate<VEC, true, 2, PLAIN>
-         : ls_log2 == 1 ? k_aggregate<VEC, true, 4, PLAIN> : k_aggregate<VEC, true, 4, PLAIN, true>;
+    if (ls_log2 >= 3) return k_aggregate<VEC, true, 1, PLAIN, false, S>;
+  return ls_log2 >= 2 ? k_aggregate<VEC, true, 2, PLAIN, false, S>
+         : ls_log2 == 1 ? k_aggregate<VEC, true, 4, PLAIN, false, S> : k_aggregate<VEC, true, 4, PLAIN, true, S>;
 }
 
 template <int VEC>
@@ -1583,7 +1590,7 @@ int launch(const AggArgs &a, bool fast, hipStream_t st, bool fused_update = fals
   if constexpr (VEC == 4) {
     if (fused_update) {
       if (!fast || a.ls_log2 < 2) return PIPAD_ERR_INVALID_ARG;  // the caller checked the shape
-      auto kern = a.plain ? k_aggregate_update<true> : k_aggregate_update<false>;
+      auto kern = a.plain ? k_aggregate_update<true> : a.coded ? k_aggregate_update<false, kCodes> : k_aggregate_update<false>;
       if (blocks > 0) hipLaunchKernelGGL(kern, grid, block, update_lds_bytes(a), st, a);
       if (fin > 0)
         hipLaunchKernelGGL((k_split_finish<4, true>), dim3((unsigned)fin), dim3(kBlock), 0, st, a);
@@ -1591,7 +1598,8 @@ int launch(const AggArgs &a, bool fast, hipStream_t st, bool fused_update = fals
       return PIPAD_OK;
     }
   }
-  auto kern = a.plain ? aggregate_kernel<VEC, true>(fast, a.ls_log2) : aggregate_kernel<VEC, false>(fast, a.ls_log2);
+  auto kern = a.plain   ? aggregate_kernel<VEC, true>(fast, a.ls_log2)
+              : a.coded ? aggregate_kernel<VEC, false, kCodes>(fast, a.ls_log2) : aggregate_kernel<VEC, false>(fast, a.ls_log2);
   if (blocks > 0) hipLaunchKernelGGL(kern, grid, block, 0, st, a);
   if (fin > 0) hipLaunchKernelGGL((k_split_finish<VEC>), dim3((unsigned)fin), dim3(kBlock), 0, st, a);
   PIPAD_HIP(hipGetLastError());
@@ -1643,13 +1651,14 @@ int launch_update(const AggArgs &a, bool like_inside, hipStream_t st) {
 // two lanes per snapshot (F <= 4), 2 for two and more; F == VEC is one lane per snapshot.
 template <int VEC, Scales S>
 void (*coalescent_kernel(const AggArgs &a))(AggArgs) {
+  constexpr bool PLAIN = !coded(S);  // (a frame of plain units has no codes)
   if constexpr (VEC > 1) {  // (VEC is F up to two columns, two for three, and four)
     constexpr int EPL = VEC == 4 ? 2 : 4;
     if (a.F > VEC) {
-      return a.plain ? k_aggregate_coalescent<VEC, EPL, true, false, S> : k_aggregate_coalescent<VEC, EPL, false, false, S>;
+      return a.plain ? k_aggregate_coalescent<VEC, EPL, PLAIN, false, S> : k_aggregate_coalescent<VEC, EPL, false, false, S>;
     }
   }
-  return a.plain ? k_aggregate_coalescent<VEC, 4, true, true, S> : k_aggregate_coalescent<VEC, 4, false, true, S>;
+  return a.plain ? k_aggregate_coalescent<VEC, 4, PLAIN, true, S> : k_aggregate_coalescent<VEC, 4, false, true, S>;
 }
 
 template <int VEC>
@@ -1664,7 +1673,8 @@ int launch_coalescent(const AggArgs &a, hipStream_t st) {
     hipLaunchKernelGGL(scale, grid1(threads, kBlock), dim3(kBlock), 0, st, a, const_cast<float *>(a.table));
     kern = coalescent_kernel<VEC, kTable>(a);
   } else {
-    kern = a.products ? coalescent_kernel<VEC, kProducts>(a) : coalescent_kernel<VEC, kStreams>(a);
+    kern = a.coded ? (a.products ? coalescent_kernel<VEC, kCodeProducts> : coalescent_kernel<VEC, kCodes>)(a)
+                   : (a.products ? coalescent_kernel<VEC, kProducts> : coalescent_kernel<VEC, kStreams>)(a);
   }
   if (blocks > 0) hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kBlock), 0, st, a);
   if (a.n_hub > 0 && !a.direct) {
@@ -1725,7 +1735,7 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
   a.rowptr_c = f->rowptr_c;
   a.col_c = f->col_c;
   a.dinv = f->dinv;
-  a.dinv_nk = f->dinv_nk;
+  a.coded = f->coded;
   a.rows_short = f->rows_short;
   a.rows_long = f->rows_long;
   a.item_row = f->item_row;

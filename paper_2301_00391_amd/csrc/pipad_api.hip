@@ -237,6 +237,7 @@ static int64_t *option_slot(const char *key, int64_t *max_value) {
       {"sub_classes", &o.sub_classes, 4},       {"agg_order", &o.agg_order, 2},
       {"agg_nt", &o.agg_nt, 3},                 {"agg_generic", &o.agg_generic, 1},
       {"slice_cols", &o.slice_cols, 64},        {"agg_coalescent", &o.agg_coalescent, 2},
+      {"scale_codes", &o.scale_codes, 2},
   };
   for (const Slot &sl : slots)
     if (!std::strcmp(key, sl.name)) {

@@ -130,7 +130,7 @@ struct RowClasses {  // the thresholds of the row classes
 __device__ inline void count_rows(const RowClasses &rc, bool live, int64_t L, int64_t entries, int32_t common,
                                   RowCounts *out) {
   constexpr int W = 16;  // waves of a workgroup at most
-  __shared__ uint32_t w_mid[W], w_hub[W], w_units[W], w_common[W], w_short[W];
+  __shared__ uint32_t w_mid[W], w_hub[W], w_units[W], w_common[W], w_short[W], w_uncoded[W];
   __shared__ uint64_t w_all[W];
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   const int cls = row_class(L, rc.short_max, rc.mid_max);
@@ -150,7 +150,9 @@ __device__ inline void count_rows(const RowClasses &rc, bool live, int64_t L, in
     }
   }
   const uint32_t in_short = wave_sum(live && cls == 0 ? (uint32_t)L : 0u);
+  const uint64_t uncoded = __ballot(live && L >= kUncoded - 1);
   if (lane == kWave - 1) {
+    w_uncoded[wave] = (uint32_t)__popcll(uncoded);
     w_short[wave] = in_short;
     w_mid[wave] = (uint32_t)__popcll(is_mid);
     w_hub[wave] = (uint32_t)__popcll(is_hub);
@@ -160,11 +162,12 @@ __device__ inline void count_rows(const RowClasses &rc, bool live, int64_t L, in
   }
   __syncthreads();
   if (threadIdx.x % kBlock == 0 && out) {
-    RowCounts c = {0, 0, 0, 0, 0, 0};
+    RowCounts c = {};
 #pragma unroll
     for (int u = 0; u < kWavesPerBlock; ++u) {
       const int w = wave + u;
       c.short_entries += w_short[w];
+      c.uncoded += w_uncoded[w];
       c.common += w_common[w];
       c.mid += w_mid[w]; c.hub += w_hub[w]; c.units += w_units[w]; c.entries += w_all[w];
     }
@@ -211,10 +214,18 @@ __device__ inline void find_bounds(const Snaps &s, const Tiles &g, int64_t wave,
   }
 }
 
-// 256 rows (block rb of them): dinv_t[i] = (1 + |row i of snapshot t|)^-1/2, evaluated in double and rounded once, and
-// the counts the row lists are laid out by.
+template <class W>
+__device__ __forceinline__ void put_node(W *nk, int32_t k, Quad<W> v) {
+  if (k > 2) *reinterpret_cast<Quad<W> *>(nk) = v;
+  else nk[0] = v.x;
+  if (k == 2) nk[1] = v.y;
+}
+
+// 256 rows (block rb of them): dinv_t[i] = (1 + |row i of snapshot t|)^-1/2, rounded once, and the counts the row lists are laid
+// out by.  The node-major copy for the scatter step (one line per node) holds the scales, or where `code` is given their codes,
+// which go there snapshot-major as well.
 __device__ __forceinline__ void prepare_rows(const Snaps &s, const Tiles &g, const RowClasses &rc, int64_t rb, float *dinv,
-                                             float *dinv_nk) {
+                                             float *dinv_nk, uint16_t *code) {
   const int64_t i64 = rb * kBlock + threadIdx.x % kBlock;
   const bool live = i64 < g.n;
   const int32_t i = (int32_t)min(i64, (int64_t)g.n - 1);
@@ -230,25 +241,26 @@ __device__ __forceinline__ void prepare_rows(const Snaps &s, const Tiles &g, con
       b[u] = rp[i + 1];
     }
     float v[CH];
+    uint16_t c[CH];
 #pragma unroll
     for (int u = 0; u < CH; ++u) {
       const int32_t len = b[u] - a[u];
-      v[u] = (float)(1.0 / sqrt((double)(len + 1)));
+      c[u] = scale_code(len);
+      v[u] = scale_of_length(c[u]);  // (in double: 1M nodes, k = 8 45.6 us, so 40.5)
+      if (len >= kUncoded) v[u] = (float)(1.0 / sqrt((double)(len + 1)));
       if (t0 + u < g.k) {
         longest = max(longest, len);
         all += len;
-        if (live) dinv[(int64_t)(t0 + u) * g.n + i] = v[u];
+        if (live) {
+          dinv[(int64_t)(t0 + u) * g.n + i] = v[u];
+          if (code) code[(int64_t)(t0 + u) * g.n + i] = c[u];
+        }
       }
     }
-    if (live) {  // node-major copy for the scatter step (one line per node)
-      float *nk = dinv_nk + (int64_t)i * node_stride(g.k) + t0;
-      if (g.k > 2) {  // (what lies behind the k-th value repeats it)
-        *reinterpret_cast<float4 *>(nk) = make_float4(v[0], v[1], v[2], v[3]);
-      } else {
-#pragma unroll
-        for (int u = 0; u < CH; ++u)
-          if (t0 + u < g.k) nk[u] = v[u];
-      }
+    if (live) {  // (what lies behind the k-th value repeats it)
+      const int64_t at = (int64_t)i * node_stride(g.k) + t0;
+      if (code) put_node(reinterpret_cast<uint16_t *>(dinv_nk) + at, g.k, Quad<uint16_t>{c[0], c[1], c[2], c[3]});
+      else put_node(dinv_nk + at, g.k, Quad<float>{v[0], v[1], v[2], v[3]});
     }
   }
   count_rows(rc, live, longest, all, 0, rb * kBlock < g.n ? g.row_cnt + rb : nullptr);
@@ -258,14 +270,14 @@ __device__ __forceinline__ void prepare_rows(const Snaps &s, const Tiles &g, con
 // time), the others take 256 rows each.
 template <int G>
 __global__ __launch_bounds__(kBlock) void k_prepare(Snaps s, Tiles g, RowClasses rc, int32_t bound_blocks,
-                                                     float *dinv, float *dinv_nk) {
+                                                     float *dinv, float *dinv_nk, uint16_t *code) {
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   if ((int32_t)blockIdx.x < bound_blocks) {
     if (blockIdx.x == 0 && threadIdx.x == 0) *g.bad = 0;
     find_bounds<G>(s, g, (int64_t)blockIdx.x * kWavesPerBlock + wave, lane);
     return;
   }
-  prepare_rows(s, g, rc, (int64_t)blockIdx.x - bound_blocks, dinv, dinv_nk);
+  prepare_rows(s, g, rc, (int64_t)blockIdx.x - bound_blocks, dinv, dinv_nk, code);
 }
 
 // First position in col[lo, hi) (ascending) that holds c or more, by half a wave.
@@ -845,7 +857,7 @@ __global__ __launch_bounds__(16 * kWave) __attribute__((amdgpu_waves_per_eu(8)))
   }
   const int blocks = blockDim.x / kBlock, sub = threadIdx.x / kBlock;
   if (sub >= blocks) return;  // (a whole wave: the number of threads need not divide)
-  prepare_rows(s, g, rc, (int64_t)((int32_t)blockIdx.x - g.ntiles) * blocks + sub, dinv, dinv_nk);
+  prepare_rows(s, g, rc, (int64_t)((int32_t)blockIdx.x - g.ntiles) * blocks + sub, dinv, dinv_nk, nullptr);
 }
 
 // ---- scan over the tiles and the row blocks -----------------------------------------------------
@@ -883,7 +895,7 @@ __device__ inline void sum_block(const uint32_t (&v)[N], uint32_t (&before)[N], 
 }
 
 // RowCounts as 32-bit values whose sums over a workgroup do not overflow.
-constexpr int kRowSums = 7;
+constexpr int kRowSums = 8;
 __device__ inline void split_counts(const RowCounts &c, bool in, uint32_t (&v)[kRowSums]) {
   v[0] = in ? c.mid : 0u;
   v[1] = in ? c.hub : 0u;
@@ -891,6 +903,7 @@ __device__ inline void split_counts(const RowCounts &c, bool in, uint32_t (&v)[k
   v[3] = in ? c.common : 0u;
   v[4] = in ? (uint32_t)(c.entries & 0xfffffu) : 0u;
   v[6] = in ? c.short_entries : 0u;
+  v[7] = in ? c.uncoded : 0u;
   v[5] = in ? (uint32_t)(c.entries >> 20) : 0u;  // (a workgroup's rows hold fewer than 2^36 entries)
 }
 __device__ inline RowCounts join_counts(const RowCounts &front, const uint32_t (&v)[kRowSums]) {
@@ -898,6 +911,7 @@ __device__ inline RowCounts join_counts(const RowCounts &front, const uint32_t (
   c.entries = front.entries + (uint64_t)v[4] + ((uint64_t)v[5] << 20);
   c.common = front.common + v[3];
   c.short_entries = front.short_entries + v[6];
+  c.uncoded = front.uncoded + v[7];
   c.mid = front.mid + v[0];
   c.hub = front.hub + v[1];
   c.units = front.units + v[2];
@@ -907,7 +921,7 @@ __device__ inline RowCounts join_counts(const RowCounts &front, const uint32_t (
 // Blocks [b0, b1) of `cnt`, scanned into `pre`; returns the counts in front of b1.  b0 is a multiple
 // of kTileScanBlock, or b1.
 __device__ inline RowCounts scan_rows(const RowCounts *cnt, RowCounts *pre, int64_t b0, int64_t b1) {
-  RowCounts front = {0, 0, 0, 0, 0, 0};
+  RowCounts front = {};
   for (int64_t base = 0; base < b1; base += kTileScanBlock) {
     const int64_t at = base + threadIdx.x;
     uint32_t v[kRowSums], before[kRowSums], total[kRowSums];
@@ -928,6 +942,7 @@ __device__ inline void send_totals(const RowCounts &all, uint32_t common, uint64
   v.hub = all.hub;
   v.units = all.units;
   v.short_entries = all.short_entries;
+  v.uncoded = all.uncoded;
   v.split_c = in_hubs;
   v.split_d = exclusive;
   v.bad = bad;
@@ -1128,7 +1143,7 @@ __device__ inline void sum_row_counts(const RowCounts *cnt, int32_t blocks, int3
 #pragma unroll
       for (int w = 0; w < kWavesPerBlock; ++w) v[u][x] += sums[u][x][w];
     }
-  const RowCounts none = {0, 0, 0, 0, 0, 0};
+  const RowCounts none = {};
   *front = join_counts(none, v[0]);
   *all = join_counts(none, v[1]);
 }
@@ -1358,16 +1373,17 @@ __global__ __launch_bounds__(kBlock) void k_list_rows(PartRows p, int32_t n, int
 }
 
 // ---- class-grouped copies of the hub rows' entries ------------------------------------------------
+template <class W>
 struct SplitArgs {
   int32_t n_units, k, sub_log2;
   const int32_t *item_row, *item_v0, *item_v1, *item_c0, *item_d0;
   const int32_t *rowptr[PIPAD_MAX_K + 1];  // parts: common, then exclusive
   const int32_t *col[PIPAD_MAX_K + 1];
   int32_t n;
-  const float *dinv, *dinv_nk;             // [k][n], [n][node_stride(k)]
+  NodeScales<W> scales;
   int32_t *sptr, *scol_c, *scol_d;
-  float *swc[PIPAD_MAX_K];
-  float *swd;
+  void *swc[PIPAD_MAX_K];
+  W *swd;
   int32_t block_off[PIPAD_MAX_K + 2];      // first workgroup of every part, in their natural order
   int32_t run_off[kClasses + 1];           // first workgroup of every XCD's run of the exclusive parts
   uint64_t whole;                          // bit p: part p takes a workgroup per unit, not a wave
@@ -1377,36 +1393,36 @@ constexpr int kFillRounds = 8;                        // entries per lane and pi
 constexpr int kFillPiece = kFillRounds * kBlock;      // entries a workgroup puts in class order in LDS at a time
 
 // The k scales of UN entries of the common copy, where `live`.
-template <int UN>
-__device__ __forceinline__ void store_scales(const SplitArgs &g, const int32_t (&c)[UN], const int32_t (&to)[UN],
+template <class W, int UN>
+__device__ __forceinline__ void store_scales(const SplitArgs<W> &g, const int32_t (&c)[UN], const int32_t (&to)[UN],
                                              const int32_t (&live)[UN]) {
   if (g.k > 2) {
     const int32_t stride = node_stride(g.k);
     for (int q = 0; 4 * q < g.k; ++q) {
-      float4 w[UN];
+      Quad<W> w[UN];
 #pragma unroll
-      for (int r = 0; r < UN; ++r) w[r] = *reinterpret_cast<const float4 *>(g.dinv_nk + (int64_t)c[r] * stride + 4 * q);
+      for (int r = 0; r < UN; ++r) w[r] = *reinterpret_cast<const Quad<W> *>(g.scales.nk + (int64_t)c[r] * stride + 4 * q);
 #pragma unroll
       for (int r = 0; r < UN; ++r)
         if (live[r]) put_scales_nt(g.swc, q, g.k, to[r], w[r]);
     }
   } else if (g.k == 2) {
-    float2 w[UN];
+    Pair<W> w[UN];
 #pragma unroll
-    for (int r = 0; r < UN; ++r) w[r] = reinterpret_cast<const float2 *>(g.dinv_nk)[c[r]];
+    for (int r = 0; r < UN; ++r) w[r] = reinterpret_cast<const Pair<W> *>(g.scales.nk)[c[r]];
 #pragma unroll
     for (int r = 0; r < UN; ++r)
       if (live[r]) {
-        __builtin_nontemporal_store(w[r].x, g.swc[0] + to[r]);
-        __builtin_nontemporal_store(w[r].y, g.swc[1] + to[r]);
+        __builtin_nontemporal_store(w[r].x, static_cast<W *>(g.swc[0]) + to[r]);
+        __builtin_nontemporal_store(w[r].y, static_cast<W *>(g.swc[1]) + to[r]);
       }
   } else {
-    float w[UN];
+    W w[UN];
 #pragma unroll
-    for (int r = 0; r < UN; ++r) w[r] = g.dinv_nk[c[r]];
+    for (int r = 0; r < UN; ++r) w[r] = g.scales.nk[c[r]];
 #pragma unroll
     for (int r = 0; r < UN; ++r)
-      if (live[r]) __builtin_nontemporal_store(w[r], g.swc[0] + to[r]);
+      if (live[r]) __builtin_nontemporal_store(w[r], static_cast<W *>(g.swc[0]) + to[r]);
   }
 }
 
@@ -1414,8 +1430,8 @@ __device__ __forceinline__ void store_scales(const SplitArgs &g, const int32_t (
 // lane) is read into registers, counted and put in class order in LDS with one ballot per class and 64
 // entries, and written out in that order with the scales, so that neighbouring lanes store to
 // neighbouring addresses.
-template <int NC, int W>
-__device__ __forceinline__ void fill_part(const SplitArgs &g, int32_t u, int p, int lane, int wave, int32_t *stage,
+template <int NC, int W, class Scale>
+__device__ __forceinline__ void fill_part(const SplitArgs<Scale> &g, int32_t u, int p, int lane, int wave, int32_t *stage,
                                           int32_t (*s_cnt)[NC], int32_t *s_off) {
   constexpr int32_t piece = W * kFillRounds * kWave;  // of the team
   auto sync = [&]() __attribute__((always_inline)) {
@@ -1539,9 +1555,9 @@ __device__ __forceinline__ void fill_part(const SplitArgs &g, int32_t u, int p, 
         to[r] = s_off[column_class(c[r], g.sub_log2)] + j;
       }
       if (p > 0) {
-        float w[UN];
+        Scale w[UN];
 #pragma unroll
-        for (int r = 0; r < UN; ++r) w[r] = g.dinv[(int64_t)(p - 1) * g.n + c[r]];
+        for (int r = 0; r < UN; ++r) w[r] = g.scales.of[(int64_t)(p - 1) * g.n + c[r]];
 #pragma unroll
         for (int r = 0; r < UN; ++r)
           if (j0 + r * W * kWave < here) {
@@ -1555,7 +1571,7 @@ __device__ __forceinline__ void fill_part(const SplitArgs &g, int32_t u, int p, 
 #pragma unroll
         for (int r = 0; r < UN; ++r)
           if (live[r]) __builtin_nontemporal_store(c[r], g.scol_c + to[r]);
-        store_scales<UN>(g, c, to, live);
+        store_scales<Scale, UN>(g, c, to, live);
       }
     }
     sync();
@@ -1577,8 +1593,8 @@ __device__ __forceinline__ void fill_part(const SplitArgs &g, int32_t u, int p, 
 // k_scatter fetches a quarter less and takes as long: the L2s' requests bound it, one per gathered scale.)  A kernel for the scales alone that
 // runs every class on the XCD that gathers it later fetches a third of that but shares the lines it
 // writes between XCDs, and the two together were slower (0.26 ms).
-template <int NC>
-__global__ __launch_bounds__(kBlock) void k_split_fill(SplitArgs g) {
+template <int NC, class Scale>
+__global__ __launch_bounds__(kBlock) void k_split_fill(SplitArgs<Scale> g) {
   __shared__ int32_t stage[kFillPiece];
   __shared__ int32_t s_cnt[kWavesPerBlock][NC], s_off[kWavesPerBlock][NC];
   const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -1610,8 +1626,8 @@ __global__ __launch_bounds__(kBlock) void k_split_fill(SplitArgs g) {
 // written in 0.31 ms: 4.5 TB/s, the rate of a plain copy.
 struct OutParts {
   int32_t *col[PIPAD_MAX_K + 1];
-  float *wc[PIPAD_MAX_K];
-  float *wd[PIPAD_MAX_K];
+  void *wc[PIPAD_MAX_K];
+  void *wd[PIPAD_MAX_K];
 };
 
 // Parts that are written before their sizes are known share their room, so that it need hold no more than the entries of the input,
@@ -1647,9 +1663,8 @@ __device__ inline uint64_t lane_word(uint64_t x, int l) {
 // R-MAT frame, k = 2, 65 us one after the other, now 44; k_split_fill 31 and 25), or k > 16, a piece after the other (150k nodes,
 // k = 18, 353 us a scale after the other, now 277).
 // common(x): common entries in front of tile x; col_shift, scale_shift: how far the exclusive part lies behind its place in OutParts.
-template <int KV, bool FULL, int TILES, class Common>
-__device__ __forceinline__ void scatter_tiles(const Snaps &s, const Tiles &g, const OutParts &o, const float *dinv,
-                                              const float *dinv_nk, int part, int32_t tile0, Common common,
+template <class W, int KV, bool FULL, int TILES, class Common>
+__device__ __forceinline__ void scatter_tiles(const Snaps &s, const Tiles &g, const OutParts &o, NodeScales<W> scales_of, int part, int32_t tile0, Common common,
                                               int64_t col_shift = 0, int64_t scale_shift = 0) {
   constexpr int WPT = kWave / TILES;  // words of a tile a wave takes at once
   const int lane = threadIdx.x % kWave;
@@ -1700,19 +1715,19 @@ __device__ __forceinline__ void scatter_tiles(const Snaps &s, const Tiles &g, co
         for (int r = 0; r < UN; ++r)
           if (x[r] >> lane & 1ull) out[at[r]] = c[r];
       } else if (KV > 0) {
-        float4 v[UN][KV > 0 ? KV : 1];
+        Quad<W> v[UN][KV > 0 ? KV : 1];
 #pragma unroll
         for (int r = 0; r < UN; ++r) {
           const int64_t node = need[r] >> lane & 1ull ? c[r] : 0;  // (one line for the lanes that need none)
 #pragma unroll
-          for (int q = 0; q < KV; ++q) v[r][q] = (reinterpret_cast<const float4 *>(dinv_nk) + node * KV)[q];
+          for (int q = 0; q < KV; ++q) v[r][q] = (reinterpret_cast<const Quad<W> *>(scales_of.nk) + node * KV)[q];
         }
 #pragma unroll
         for (int r = 0; r < UN; ++r) {
           if (x[r] >> lane & 1ull) out[at[r]] = c[r];
           if (need[r] >> lane & 1ull)
 #pragma unroll
-            for (int q = 0; q < KV; ++q) put_scales<FULL>(o.wc, q, g.k, at[r], v[r][q]);
+            for (int q = 0; q < KV; ++q) put_scales<W, FULL>(o.wc, q, g.k, at[r], v[r][q]);
         }
       } else {
 #pragma unroll
@@ -1721,26 +1736,26 @@ __device__ __forceinline__ void scatter_tiles(const Snaps &s, const Tiles &g, co
         if (g.k > 2) {  // (more than 16)
           const int32_t pieces = node_stride(g.k) / 4;
           for (int q = 0; q < pieces; ++q) {
-            float4 w[UN];
+            Quad<W> w[UN];
 #pragma unroll
-            for (int r = 0; r < UN; ++r) w[r] = reinterpret_cast<const float4 *>(dinv_nk)[(int64_t)c[r] * pieces + q];
+            for (int r = 0; r < UN; ++r) w[r] = reinterpret_cast<const Quad<W> *>(scales_of.nk)[(int64_t)c[r] * pieces + q];
 #pragma unroll
             for (int r = 0; r < UN; ++r)
               if (need[r] >> lane & 1ull) put_scales(o.wc, q, g.k, at[r], w[r]);
           }
         } else {
-          float2 w[UN];
+          Pair<W> w[UN];
 #pragma unroll
           for (int r = 0; r < UN; ++r) {
             const int32_t node = need[r] >> lane & 1ull ? c[r] : 0;
-            if (g.k == 2) w[r] = reinterpret_cast<const float2 *>(dinv_nk)[node];
-            else w[r].x = w[r].y = dinv_nk[node];
+            if (g.k == 2) w[r] = reinterpret_cast<const Pair<W> *>(scales_of.nk)[node];
+            else w[r].x = w[r].y = scales_of.nk[node];
           }
 #pragma unroll
           for (int r = 0; r < UN; ++r)
             if (need[r] >> lane & 1ull) {
-              o.wc[0][at[r]] = w[r].x;
-              if (g.k == 2) o.wc[1][at[r]] = w[r].y;
+              static_cast<W *>(o.wc[0])[at[r]] = w[r].x;
+              if (g.k == 2) static_cast<W *>(o.wc[1])[at[r]] = w[r].y;
             }
         }
       }
@@ -1760,12 +1775,12 @@ __device__ __forceinline__ void scatter_tiles(const Snaps &s, const Tiles &g, co
   }
   const int32_t *excl = g.excl[t];
   int32_t *const out_col = o.col[part] + (col_shift + (bound[tile0] - c0));
-  float *const out_w = o.wd[t] + (scale_shift + (bound[tile0] - c0));
-  const float *dinv_t = dinv + (int64_t)t * g.n;
+  W *const out_w = static_cast<W *>(o.wd[t]) + (scale_shift + (bound[tile0] - c0));
+  const W *of_t = scales_of.of + (int64_t)t * g.n;
   constexpr int UN = kScatterAhead;
   for (int32_t j0 = lane; j0 - lane < total; j0 += UN * kWave) {
     int32_t c[UN];
-    float d[UN];
+    W d[UN];
 #pragma unroll
     for (int r = 0; r < UN; ++r) {
       const int32_t j = min(j0 + r * kWave, total - 1);
@@ -1775,7 +1790,7 @@ __device__ __forceinline__ void scatter_tiles(const Snaps &s, const Tiles &g, co
       c[r] = excl[at + j];
     }
 #pragma unroll
-    for (int r = 0; r < UN; ++r) d[r] = dinv_t[c[r]];
+    for (int r = 0; r < UN; ++r) d[r] = of_t[c[r]];
 #pragma unroll
     for (int r = 0; r < UN; ++r)
       if (j0 + r * kWave < total) {
@@ -1785,12 +1800,11 @@ __device__ __forceinline__ void scatter_tiles(const Snaps &s, const Tiles &g, co
   }
 }
 
-template <int KV, bool FULL, int TILES>
-__global__ __launch_bounds__(kBlock) void k_scatter(Snaps s, Tiles g, OutParts o, const float *dinv,
-                                                     const float *dinv_nk) {
+template <class W, int KV, bool FULL, int TILES>
+__global__ __launch_bounds__(kBlock) void k_scatter(Snaps s, Tiles g, OutParts o, NodeScales<W> scales) {
   const int64_t tile64 = ((int64_t)blockIdx.x * kWavesPerBlock + threadIdx.x / kWave) * TILES;
   if (tile64 >= g.ntiles) return;
-  scatter_tiles<KV, FULL, TILES>(s, g, o, dinv, dinv_nk, (int)blockIdx.y, __builtin_amdgcn_readfirstlane((int32_t)tile64),
+  scatter_tiles<W, KV, FULL, TILES>(s, g, o, scales, (int)blockIdx.y, __builtin_amdgcn_readfirstlane((int32_t)tile64),
                                  [&](int32_t x) __attribute__((always_inline)) { return g.tile_pre[x].x; });
 }
 
@@ -1800,7 +1814,7 @@ __global__ __launch_bounds__(kBlock) void k_scatter(Snaps s, Tiles g, OutParts o
 // workgroup sends the sizes to the host).
 template <int KV, bool FULL, bool SUM>
 __global__ __launch_bounds__(kBlock) void k_rows_scatter(Snaps s, Tiles g, RowArgs r, ListArgs q, OutParts o, int32_t row_wgs,
-                                                         const float *dinv, const float *dinv_nk, FrameTotals *out, uint32_t seq) {
+                                                         NodeScales<float> scales, FrameTotals *out, uint32_t seq) {
   if ((int32_t)blockIdx.x < row_wgs) {
     make_rows<SUM>(s, g, r, q, out, seq);
     return;
@@ -1823,15 +1837,22 @@ __global__ __launch_bounds__(kBlock) void k_rows_scatter(Snaps s, Tiles g, RowAr
         here = mine[w];
       }
     const RoomShift shift{(int32_t)all};
-    scatter_tiles<KV, FULL, 1>(s, g, o, dinv, dinv_nk, part, tile0,
+    scatter_tiles<float, KV, FULL, 1>(s, g, o, scales, part, tile0,
                                [&](int32_t x) __attribute__((always_inline)) { return x == tile0 ? front : front + here; },
                                shift.cols(part - 1), shift.scales());
   } else {
     if (tile0 >= g.ntiles || *g.bad != 0) return;
     const RoomShift shift{(int32_t)g.tile_pre[g.ntiles].x};
-    scatter_tiles<KV, FULL, 1>(s, g, o, dinv, dinv_nk, part, tile0, [&](int32_t x) __attribute__((always_inline)) { return g.tile_pre[x].x; },
+    scatter_tiles<float, KV, FULL, 1>(s, g, o, scales, part, tile0, [&](int32_t x) __attribute__((always_inline)) { return g.tile_pre[x].x; },
                                shift.cols(part - 1), shift.scales());
   }
+}
+
+// The node-major scales of a frame that was to have codes and has a row too long for one.
+__global__ __launch_bounds__(kBlock) void k_node_scales(int32_t n, int32_t k, const float *dinv, float *dinv_nk) {
+  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (i >= n) return;
+  for (int t = 0; t < node_stride(k); ++t) dinv_nk[i * node_stride(k) + t] = dinv[(int64_t)min(t, k - 1) * n + i];
 }
 
 }  // namespace
@@ -1896,7 +1917,7 @@ int wait_totals(const TotalsTicket &ticket, hipStream_t st, FrameTotals *out) {
 // would be among them.)  Of 200 frames below the line with hub rows, in the mean: steps 6 to 14 % faster, backward passes 3 to 11,
 // aggregations alone 4 to 26, the more the fewer entries, with operands in the caches and without; at worst 14 % slower
 // (R-MAT, N = 62k, k = 2, F = 32, aggregation alone).
-constexpr int64_t kEarlyEntries = (int64_t)1 << 25;
+constexpr int64_t kEarlyEntries = 24000000;  // (build_overlap)
 constexpr int32_t kManyTiles = 16384;  // from here on a wave of k_scatter takes four
 constexpr int32_t kPlainNodes = 65536, kPlainRow = 512;
 constexpr int64_t kPlainEntries = (int64_t)4 << 20;
@@ -1924,7 +1945,7 @@ void frame_take_options(pipad_frame *f, int64_t entries) {
   f->hub_segment = (int32_t)std::clamp<int64_t>(f->opt.hub_segment, 1, lim);
   f->sub_log2 = f->opt.sub_classes >= 4 ? 2 : f->opt.sub_classes >= 2 ? 1 : 0;
   f->nclass = kClasses << f->sub_log2;
-  f->plain_units = f->n <= kPlainNodes && entries <= kPlainEntries && f->mid_max >= kPlainRow;
+  f->plain_units = f->opt.scale_codes != 2 && f->n <= kPlainNodes && entries <= kPlainEntries && f->mid_max >= kPlainRow;
 }
 
 void want_lists(Arena &a, pipad_frame *f, int64_t entries) {
@@ -2001,13 +2022,13 @@ void want_split(Arena &a, pipad_frame *f) {
   a.want(&f->sptr, (size_t)(f->k + 1) * (f->nclass + 1) * f->n_items);
   a.want(&f->scol_c, (size_t)f->split_c);
   a.want(&f->scol_d, (size_t)f->split_d);
-  for (int t = 0; t < f->k; ++t) a.want(&f->swc[t], (size_t)f->split_c);
-  a.want(&f->swd, (size_t)f->split_d);
+  for (int t = 0; t < f->k; ++t) a.want_bytes(&f->swc[t], (size_t)f->split_c * scale_bytes(f));
+  a.want_bytes(&f->swd, (size_t)f->split_d * scale_bytes(f));
 }
 
-int build_split_arrays(pipad_frame *f, hipStream_t st) {
-  if (f->n_items == 0 || f->plain_units) return PIPAD_OK;
-  SplitArgs g;
+template <class W>
+static int fill_split_arrays(pipad_frame *f, hipStream_t st) {
+  SplitArgs<W> g;
   std::memset(&g, 0, sizeof(g));
   g.n_units = f->n_items;
   g.k = f->k;
@@ -2020,8 +2041,7 @@ int build_split_arrays(pipad_frame *f, hipStream_t st) {
   g.rowptr[0] = f->rowptr_c;
   g.col[0] = f->col_c;
   g.n = f->n;
-  g.dinv = f->dinv;
-  g.dinv_nk = f->dinv_nk;
+  g.scales = node_scales<W>(f);
   for (int t = 0; t < f->k; ++t) {
     g.rowptr[1 + t] = f->rowptr_d[t];
     g.col[1 + t] = f->col_d[t];
@@ -2030,8 +2050,8 @@ int build_split_arrays(pipad_frame *f, hipStream_t st) {
   g.sptr = f->sptr;
   g.scol_c = f->scol_c;
   g.scol_d = f->scol_d;
-  g.swd = f->swd;
-  auto fill = f->sub_log2 == 0 ? k_split_fill<8> : f->sub_log2 == 1 ? k_split_fill<16> : k_split_fill<32>;
+  g.swd = static_cast<W *>(f->swd);
+  auto fill = f->sub_log2 == 0 ? k_split_fill<8, W> : f->sub_log2 == 1 ? k_split_fill<16, W> : k_split_fill<32, W>;
   // a workgroup per unit for the parts that hold more than a quarter of a snapshot's entries, a wave elsewhere
   int32_t blocks = 0;
   int64_t snapshot = f->nnz_c, longest = 0;
@@ -2077,6 +2097,30 @@ int build_split_arrays(pipad_frame *f, hipStream_t st) {
   hipLaunchKernelGGL(fill, dim3((unsigned)(align_xcd(g.block_off[1]) + kClasses * longest_run)), dim3(kBlock), 0, st, g);
   PIPAD_HIP(hipGetLastError());
   return PIPAD_OK;
+}
+
+int build_split_arrays(pipad_frame *f, hipStream_t st) {
+  if (f->n_items == 0 || f->plain_units) return PIPAD_OK;
+  return f->coded ? fill_split_arrays<uint16_t>(f, st) : fill_split_arrays<float>(f, st);
+}
+
+template <class W>
+static void launch_scatter(const pipad_frame *f, const Snaps &s, const Tiles &g, const OutParts &o, int instance, hipStream_t st) {
+  // A wave per tile has the shortest chain of dependent loads (0.2M nodes: 65 us against 74 with four
+  // tiles per wave); with 8M entries and more per snapshot there
+  // are waves enough and fewer of them do better (1M nodes, 20M entries: 313 us against 339).  (With so few tiles
+  // that a wave takes one, three and four snapshots are here only where the room for `early` was refused.)
+  const int per_wave = g.ntiles < kManyTiles ? 1 : 4;
+  using Scatter = void (*)(Snaps, Tiles, OutParts, NodeScales<W>);
+  static const Scatter kernels[2][9] = {
+      {k_scatter<W, 0, false, 1>, k_scatter<W, 1, false, 1>, k_scatter<W, 1, true, 1>, k_scatter<W, 2, false, 1>,
+       k_scatter<W, 2, true, 1>, k_scatter<W, 3, false, 1>, k_scatter<W, 3, true, 1>, k_scatter<W, 4, false, 1>,
+       k_scatter<W, 4, true, 1>},
+      {k_scatter<W, 0, false, 4>, k_scatter<W, 1, false, 4>, k_scatter<W, 1, true, 4>, k_scatter<W, 2, false, 4>,
+       k_scatter<W, 2, true, 4>, k_scatter<W, 3, false, 4>, k_scatter<W, 3, true, 4>, k_scatter<W, 4, false, 4>,
+       k_scatter<W, 4, true, 4>}};
+  hipLaunchKernelGGL(kernels[per_wave == 1 ? 0 : 1][instance], grid1(g.ntiles, kWavesPerBlock * per_wave, f->k + 1), dim3(kBlock), 0,
+                     st, s, g, o, node_scales<W>(f));
 }
 
 int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags,
@@ -2139,13 +2183,19 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
   // and 20000 waves of k_prepare_mark, of which 8192 run together: N = 107k, k = 8 with 2000 tiles 190 -> 186, N = 45k, k = 12
   // with 1520 181 -> 178, but N = 113k, k = 16 with 1590 180 -> 187; with 3000 to 4000 tiles and k = 2 .. 6 3 to 13 % slower.
   bool small = g.ntiles <= kSumTiles && row_blocks <= kSumRowBlocks && (int64_t)g.ntiles * k <= 20000;
-  // Frames of up to 33 M entries in all snapshots get that room as well (270 MB at most), and their rows are made next to the
+  // Frames of up to 24 M entries in all snapshots get that room as well (190 MB at most), and their rows are made next to the
   // entries, in the launch that would wait for the host otherwise: steps and slides N = 100k R-MAT, k = 5 198 -> 191 us,
   // N = 200k, k = 8 269 -> 263 (slide), 124k, k = 2 88 -> 77, 140k, k = 3 119 -> 111; of 40 frames past the small ones 1 to 10 % less,
   // the more the shorter.  What stays unused of it, for as long as the frame is there, are 4 (k - 1) bytes per common entry: less
   // than 4 per input entry, and than what is used.  (With room for every part at its largest it was up to twice as much, and
-  // 200k nodes, k = 8, 81 % in common took 320 MB; now 205 of which 132 are used.)
+  // 200k nodes, k = 8, 81 % in common took 320 MB; now 205 of which 132 are used.)  From there on waiting for the sizes costs less than
+  // codes for the scales give (scale_code), which only entries whose form is known before they are written can have: 24 to 33 M
+  // entries, 24 of 28 drawn steps, slides, layers and backward passes 1 to 13 % faster, 4.7 in the mean, the others the same but
+  // one; 14 to 24 M between 7 % faster and 4 % slower, fewer up to 18 % slower.
   bool early = small || (entries <= kEarlyEntries && g.ntiles < kManyTiles);
+  // Past that the scales are stored as codes, unless a row turns out to be too long for one.
+  if (f->opt.scale_codes == 2) small = early = false;
+  const bool codes = !early && f->opt.scale_codes > 0;
 
   Arena keep1;
   keep1.want(&f->rowptr_c, (size_t)n + 1);
@@ -2212,7 +2262,7 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
     for (int t = 0; t < k; ++t) {
       f->col_d[t] = room_cols + (room_at[t] + shift.cols(t));
       f->wc[t] = room_scales + scales_at(t);
-      f->wd[t] = f->wc[t] + shift.scales();
+      f->wd[t] = room_scales + (scales_at(t) + shift.scales());
     }
   };
   if (early) place_parts(0);
@@ -2268,7 +2318,8 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
     const int per_block = kBlock / (k > 8 ? 16 : 8);  // bounds
     const int32_t bound_blocks = (int32_t)(((int64_t)g.ntiles + 1 + per_block - 1) / per_block);
     hipLaunchKernelGGL((k > 8 ? k_prepare<16> : k_prepare<8>), dim3((unsigned)(bound_blocks + row_blocks)), dim3(kBlock), 0, st,
-                       s, g, row_classes(f), bound_blocks, f->dinv, f->dinv_nk);
+                       s, g, row_classes(f), bound_blocks, f->dinv, f->dinv_nk,
+                       codes ? codes_nk(f) + (size_t)node_stride(k) * n : nullptr);
     if (g.ntiles > 0) {
       auto mark = k <= 16 ? (large ? k_mark<512, 1, uint64_t> : k_mark<512, 1, uint32_t>)
                           : (large ? k_mark<256, 2, uint64_t> : k_mark<256, 2, uint32_t>);
@@ -2293,7 +2344,7 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
       hipLaunchKernelGGL(k_rows, grid1((int64_t)n + 1, kBlock), dim3(kBlock), 0, st, s, g, rows, list_args(f));
   }
   if (early) {
-    using RowsScatter = void (*)(Snaps, Tiles, RowArgs, ListArgs, OutParts, int32_t, const float *, const float *, FrameTotals *, uint32_t);
+    using RowsScatter = void (*)(Snaps, Tiles, RowArgs, ListArgs, OutParts, int32_t, NodeScales<float>, FrameTotals *, uint32_t);
     static const RowsScatter kernels[2][9] = {
         {k_rows_scatter<0, false, false>, k_rows_scatter<1, false, false>, k_rows_scatter<1, true, false>,
          k_rows_scatter<2, false, false>, k_rows_scatter<2, true, false>, k_rows_scatter<3, false, false>,
@@ -2304,7 +2355,7 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
     const int32_t row_groups = (int32_t)grid1((int64_t)n + 1, kBlock).x;
     const int32_t tile_groups = (int32_t)grid1(g.ntiles, kWavesPerBlock).x;
     hipLaunchKernelGGL(kernels[small ? 1 : 0][kv], dim3((unsigned)(row_groups + tile_groups * (k + 1))), dim3(kBlock), 0, st, s, g,
-                       rows, list_args(f), out_parts(), row_groups, f->dinv, f->dinv_nk, ticket.where, ticket.seq);
+                       rows, list_args(f), out_parts(), row_groups, node_scales<float>(f), ticket.where, ticket.seq);
   }
   PIPAD_TRY(hipGetLastError());
 
@@ -2322,6 +2373,9 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
     if (rc != 0) return fail(rc);
   }
 
+  f->coded = codes && v.uncoded == 0;
+  if (codes && !f->coded && n > 0) hipLaunchKernelGGL(k_node_scales, grid1(n, kBlock), dim3(kBlock), 0, st, n, k, f->dinv, f->dinv_nk);
+
   Arena keep2;
   if (early) {
     place_parts(f->nnz_c);
@@ -2329,8 +2383,8 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
     keep2.want(&f->col_c, (size_t)f->nnz_c);
     for (int t = 0; t < k; ++t) {
       keep2.want(&f->col_d[t], (size_t)f->nnz_d[t]);
-      keep2.want(&f->wc[t], (size_t)f->nnz_c);
-      keep2.want(&f->wd[t], (size_t)f->nnz_d[t]);
+      keep2.want_bytes(&f->wc[t], (size_t)f->nnz_c * scale_bytes(f));
+      keep2.want_bytes(&f->wd[t], (size_t)f->nnz_d[t] * scale_bytes(f));
     }
   }
   want_split(keep2, f);
@@ -2340,21 +2394,8 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
     keep2.assign(base_ptr);
   }
   if (!early && g.ntiles > 0) {
-    // A wave per tile has the shortest chain of dependent loads (0.2M nodes: 65 us against 74 with four
-    // tiles per wave); with 8M entries and more per snapshot there
-    // are waves enough and fewer of them do better (1M nodes, 20M entries: 313 us against 339).  (With so few tiles
-    // that a wave takes one, three and four snapshots are here only where the room for `early` was refused.)
-    const int per_wave = g.ntiles < kManyTiles ? 1 : 4;
-    using Scatter = void (*)(Snaps, Tiles, OutParts, const float *, const float *);
-    static const Scatter kernels[2][9] = {
-        {k_scatter<0, false, 1>, k_scatter<1, false, 1>, k_scatter<1, true, 1>, k_scatter<2, false, 1>,
-         k_scatter<2, true, 1>, k_scatter<3, false, 1>, k_scatter<3, true, 1>, k_scatter<4, false, 1>,
-         k_scatter<4, true, 1>},
-        {k_scatter<0, false, 4>, k_scatter<1, false, 4>, k_scatter<1, true, 4>, k_scatter<2, false, 4>,
-         k_scatter<2, true, 4>, k_scatter<3, false, 4>, k_scatter<3, true, 4>, k_scatter<4, false, 4>,
-         k_scatter<4, true, 4>}};
-    hipLaunchKernelGGL(kernels[per_wave == 1 ? 0 : 1][kv], grid1(g.ntiles, kWavesPerBlock * per_wave, k + 1), dim3(kBlock), 0, st,
-                       s, g, out_parts(), f->dinv, f->dinv_nk);
+    if (f->coded) launch_scatter<uint16_t>(f, s, g, out_parts(), kv, st);
+    else launch_scatter<float>(f, s, g, out_parts(), kv, st);
     PIPAD_TRY(hipGetLastError());
   }
   {

@@ -421,6 +421,7 @@ __global__ __launch_bounds__(kSortBlock) __attribute__((amdgpu_waves_per_eu(R ==
 // pointers of the rows in between (many at once by the whole wave).  wc_t[e] = dinv_t[col_c[e]] for the
 // overlap part (a node's k scales from the node-major copy of D^-1/2), wd_t[e] = dinv_t[col_d_t[e]] for
 // the exclusive part of snapshot t.
+template <class W>  // what a scale is stored as
 struct FinishArgs {
   int32_t nparts, n, k;
   uint32_t block_off[PIPAD_MAX_K + 2];    // first workgroup of every part, in their natural order
@@ -429,9 +430,9 @@ struct FinishArgs {
   const int32_t *key;                     // sorted columns of the source, part by part
   const int32_t *col[PIPAD_MAX_K + 1];    // columns of the transposed parts
   int32_t *rowptr[PIPAD_MAX_K + 1];
-  const float *dinv, *dinv_nk;
-  float *wc[PIPAD_MAX_K];
-  float *wd[PIPAD_MAX_K];
+  NodeScales<W> scales;
+  void *wc[PIPAD_MAX_K];
+  void *wd[PIPAD_MAX_K];
 };
 
 // rp[lo .. hi] = v, per lane; long runs by the whole wave.
@@ -451,8 +452,8 @@ __device__ inline void fill_run(int32_t *rp, int32_t lo, int32_t hi, int32_t v, 
 
 // KV > 0: a node's k scales lie in KV 16-byte pieces, read together (FULL: k == 4 * KV); KV == 0: k <= 2, or k > 16, a piece after
 // the other.
-template <int KV, bool FULL>
-__global__ __launch_bounds__(kBlock) void k_finish_parts(FinishArgs g) {
+template <class W, int KV, bool FULL>
+__global__ __launch_bounds__(kBlock) void k_finish_parts(FinishArgs<W> g) {
   const int lane = threadIdx.x % kWave;
   // (an XCD takes a run of the exclusive parts, so that it reads one or two snapshots' D^-1/2; no workgroup
   // is launched for nothing where the parts differ in size: N = 200k, k = 4 27 -> 25 us; with more than eight snapshots
@@ -485,26 +486,64 @@ __global__ __launch_bounds__(kBlock) void k_finish_parts(FinishArgs g) {
   if (!live) return;
   if (p == 0) {
     if (KV > 0) {
-      const float4 *row = reinterpret_cast<const float4 *>(g.dinv_nk) + (int64_t)c * KV;
-      float4 v[KV > 0 ? KV : 1];
+      const Quad<W> *row = reinterpret_cast<const Quad<W> *>(g.scales.nk) + (int64_t)c * KV;
+      Quad<W> v[KV > 0 ? KV : 1];
 #pragma unroll
       for (int q = 0; q < KV; ++q) v[q] = row[q];
 #pragma unroll
-      for (int q = 0; q < KV; ++q) put_scales<FULL>(g.wc, q, g.k, e, v[q]);
+      for (int q = 0; q < KV; ++q) put_scales<W, FULL>(g.wc, q, g.k, e, v[q]);
     } else if (g.k > 2) {
       const int32_t pieces = node_stride(g.k) / 4;
-      const float4 *row = reinterpret_cast<const float4 *>(g.dinv_nk) + (int64_t)c * pieces;
+      const Quad<W> *row = reinterpret_cast<const Quad<W> *>(g.scales.nk) + (int64_t)c * pieces;
       for (int q = 0; q < pieces; ++q) put_scales(g.wc, q, g.k, e, row[q]);
     } else if (g.k == 2) {
-      const float2 v = reinterpret_cast<const float2 *>(g.dinv_nk)[c];
-      g.wc[0][e] = v.x;
-      g.wc[1][e] = v.y;
+      const Pair<W> v = reinterpret_cast<const Pair<W> *>(g.scales.nk)[c];
+      static_cast<W *>(g.wc[0])[e] = v.x;
+      static_cast<W *>(g.wc[1])[e] = v.y;
     } else {
-      g.wc[0][e] = g.dinv_nk[c];
+      static_cast<W *>(g.wc[0])[e] = g.scales.nk[c];
     }
   } else {
-    g.wd[p - 1][e] = g.dinv[(int64_t)(p - 1) * g.n + c];
+    static_cast<W *>(g.wd[p - 1])[e] = g.scales.of[(int64_t)(p - 1) * g.n + c];
   }
+}
+
+template <class W>
+void launch_finish(const pipad_frame *g, const SortArgs &s, const int32_t *sorted_keys, hipStream_t st) {
+  const int32_t n = g->n, k = g->k;
+  FinishArgs<W> c;
+  std::memset(&c, 0, sizeof(c));
+  c.nparts = k + 1;
+  c.n = n;
+  c.k = k;
+  for (int p = 0; p <= k + 1; ++p) c.part_off[p] = s.part_off[p];
+  c.key = sorted_keys;
+  c.scales = node_scales<W>(g);
+  for (int p = 0; p <= k; ++p) {
+    c.col[p] = s.col_out[p];
+    c.rowptr[p] = p == 0 ? g->rowptr_c : g->rowptr_d[p - 1];
+  }
+  for (int t = 0; t < k; ++t) {
+    c.wc[t] = g->wc[t];
+    c.wd[t] = g->wd[t];
+  }
+  using Finish = void (*)(FinishArgs<W>);
+  static const Finish kernels[] = {k_finish_parts<W, 0, false>, k_finish_parts<W, 1, false>, k_finish_parts<W, 1, true>,
+                                   k_finish_parts<W, 2, false>, k_finish_parts<W, 2, true>,  k_finish_parts<W, 3, false>,
+                                   k_finish_parts<W, 3, true>,  k_finish_parts<W, 4, false>, k_finish_parts<W, 4, true>};
+  auto finish = kernels[k <= 2 || k > 16 ? 0 : node_stride(k) / 2 - (k % 4 ? 1 : 0)];
+  int64_t blocks = 0;
+  for (int p = 0; p <= k; ++p) {
+    const int64_t nnz = (int64_t)(s.part_off[p + 1] - s.part_off[p]);
+    c.block_off[p] = (uint32_t)blocks;
+    blocks += nnz > 0 ? (nnz + kBlock - 1) / kBlock : std::min<int64_t>((int64_t)n / kBlock + 1, 1024);
+  }
+  c.block_off[k + 1] = (uint32_t)blocks;
+  const int32_t first_excl = align_xcd(c.block_off[1]);
+  const int32_t excl_blocks = align_xcd((int32_t)blocks - c.block_off[1]);
+  c.step_xcd = k <= 8 ? excl_blocks / kClasses : 1;
+  c.step_block = k <= 8 ? 1 : kClasses;
+  hipLaunchKernelGGL(finish, dim3((unsigned)(first_excl + excl_blocks)), dim3(kBlock), 0, st, c);
 }
 
 }  // namespace
@@ -530,6 +569,7 @@ int transpose_frame(const pipad_frame *f, pipad_alloc_fn alloc, void *alloc_ctx,
   g->sub_log2 = f->sub_log2;
   g->nclass = f->nclass;
   g->plain_units = f->plain_units;
+  g->coded = f->coded;
   g->nnz_c = f->nnz_c;
   for (int t = 0; t < k; ++t) g->nnz_d[t] = f->nnz_d[t];
   Allocator A{alloc, alloc_ctx, g};
@@ -556,8 +596,8 @@ int transpose_frame(const pipad_frame *f, pipad_alloc_fn alloc, void *alloc_ctx,
   keep.want(&g->col_c, (size_t)g->nnz_c);
   for (int t = 0; t < k; ++t) {
     keep.want(&g->col_d[t], (size_t)g->nnz_d[t]);
-    keep.want(&g->wc[t], (size_t)g->nnz_c);
-    keep.want(&g->wd[t], (size_t)g->nnz_d[t]);
+    keep.want_bytes(&g->wc[t], (size_t)g->nnz_c * scale_bytes(g));
+    keep.want_bytes(&g->wd[t], (size_t)g->nnz_d[t] * scale_bytes(g));
   }
   {
     int64_t entries = g->nnz_c;  // a row's length counts its longest exclusive row only
@@ -679,43 +719,8 @@ int transpose_frame(const pipad_frame *f, pipad_alloc_fn alloc, void *alloc_ctx,
       sorted_keys = s.key_out;
     }
   }
-  {
-    FinishArgs c;
-    std::memset(&c, 0, sizeof(c));
-    c.nparts = k + 1;
-    c.n = n;
-    c.k = k;
-    for (int p = 0; p <= k + 1; ++p) c.part_off[p] = s.part_off[p];
-    c.key = sorted_keys;
-    c.dinv = g->dinv;
-    c.dinv_nk = g->dinv_nk;
-    for (int p = 0; p <= k; ++p) {
-      c.col[p] = s.col_out[p];
-      c.rowptr[p] = p == 0 ? g->rowptr_c : g->rowptr_d[p - 1];
-    }
-    for (int t = 0; t < k; ++t) {
-      c.wc[t] = g->wc[t];
-      c.wd[t] = g->wd[t];
-    }
-    using Finish = void (*)(FinishArgs);
-    static const Finish kernels[] = {k_finish_parts<0, false>, k_finish_parts<1, false>, k_finish_parts<1, true>,
-                                     k_finish_parts<2, false>, k_finish_parts<2, true>,  k_finish_parts<3, false>,
-                                     k_finish_parts<3, true>,  k_finish_parts<4, false>, k_finish_parts<4, true>};
-    auto finish = kernels[k <= 2 || k > 16 ? 0 : node_stride(k) / 2 - (k % 4 ? 1 : 0)];
-    int64_t blocks = 0;
-    for (int p = 0; p <= k; ++p) {
-      const int64_t nnz = (int64_t)(s.part_off[p + 1] - s.part_off[p]);
-      c.block_off[p] = (uint32_t)blocks;
-      blocks += nnz > 0 ? (nnz + kBlock - 1) / kBlock : std::min<int64_t>((int64_t)n / kBlock + 1, 1024);
-    }
-    c.block_off[k + 1] = (uint32_t)blocks;
-    const int32_t first_excl = align_xcd(c.block_off[1]);
-    const int32_t excl_blocks = align_xcd((int32_t)blocks - c.block_off[1]);
-    c.step_xcd = k <= 8 ? excl_blocks / kClasses : 1;
-    c.step_block = k <= 8 ? 1 : kClasses;
-    hipLaunchKernelGGL(finish, dim3((unsigned)(first_excl + excl_blocks)), dim3(kBlock), 0,
-                       st, c);
-  }
+  if (g->coded) launch_finish<uint16_t>(g, s, sorted_keys, st);
+  else launch_finish<float>(g, s, sorted_keys, st);
   PIPAD_TRY_T(hipGetLastError());
 
   // ---- row classes, work lists and the class-grouped copies, as in the build
