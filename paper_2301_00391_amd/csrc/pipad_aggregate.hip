@@ -98,6 +98,7 @@ struct AggArgs {
   // blocks_short (padded so that every phase starts at a multiple of 8 and the XCD a workgroup is
   // meant for is the one it runs on)
   int32_t blocks_wide, blocks_mid, blocks_short;
+  int32_t team_log2;      // log2 of the lanes that walk a short row: those of a slice, or more (short_row_team)
   int32_t batch_short, batch_mid, batch_wide;  // rows / class parts per wave
   int64_t blocks_per_phase;
   Divisor per_phase, per_row;  // workgroups per phase, slices
@@ -382,12 +383,14 @@ __device__ __forceinline__ void add_step(const float (&w)[N], const typename V<V
 // (One walk over both lists instead of one each: most rows have only a few exclusive entries, and a
 // walk of their own cost them a whole round of gathers.)
 // The FAST inner loop needs nslots * UNR to divide team_lanes * EPL.
+// BLOCKS: a lane group takes UNR entries next to each other at a time and leaves out a block that lies past the end, so that no
+// more of the row is filled up than by one group alone.
 // ALONE: a lane takes exactly the entries that it fetches (one lane per row and snapshot, so that the lane
 // groups are the lanes of the team): nothing goes through LDS, whose bank conflicts took a third of the
 // coalescent kernel's time.  Same order of the sum.  N = 200k, k = 8, concatenated, F = 1 / 2 / 4 102 / 107 /
 // 111 -> 97 / 102 / 107 us; R-MAT 60k, k = 5 29 / 32.5 / 33.8 -> 27.7 / 30.8 / 32.4, 1M, k = 8 534 / 588 / 627 ->
 // 532 / 576 / 619.
-template <int VEC, int UNR, bool FAST, int EPL, bool ALONE = false, Scales S = kStreams>
+template <int VEC, int UNR, bool FAST, int EPL, bool ALONE = false, Scales S = kStreams, bool BLOCKS = false>
 __device__ __forceinline__ void walk(const Lists &l, int32_t cs, int32_t clen, int32_t ds, int32_t len,
                             const Raw (&first)[EPL],
                             int team_base, int team_lanes,
@@ -437,12 +440,13 @@ __device__ __forceinline__ void walk(const Lists &l, int32_t cs, int32_t clen, i
       mine_lds[j * team_lanes + q] = st;
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    for (int32_t e0 = 0; e0 < cnt; e0 += nslots * UNR) {
+    static_assert(FAST || !BLOCKS, "");
+    for (int32_t e0 = BLOCKS ? slot * UNR : 0; e0 < cnt; e0 += nslots * UNR) {
       Staged en[UNR];
       typename VT::T x[UNR];
 #pragma unroll
       for (int u = 0; u < UNR; ++u) {
-        int32_t e = e0 + u * nslots + slot;
+        int32_t e = BLOCKS ? e0 + u : e0 + u * nslots + slot;
         if (!FAST) e = min(e, chunk - 1);
         en[u] = mine_lds[e];
         if (!FAST && e0 + u * nslots + slot >= cnt) en[u].w = 0.f;
@@ -673,10 +677,12 @@ __device__ __forceinline__ Piece unit_piece(const AggArgs &a, int64_t unit, cons
   return p;
 }
 
-// PLAIN: hub units as they are in a frame with plain_units.
-template <int VEC, bool FAST, int EPL, bool UPD, bool PLAIN, bool ALONE = false, Scales S = kStreams>
+// PLAIN: hub units as they are in a frame with plain_units.  TEAMS: a short row is walked by several lane groups (see
+// short_row_team).
+template <int VEC, bool FAST, int EPL, bool UPD, bool PLAIN, bool ALONE = false, Scales S = kStreams, bool TEAMS = false>
 __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
   using VT = V<VEC>;
+  static_assert(!TEAMS || (FAST && !ALONE), "");
   static_assert(!UPD || (VEC == 4 && FAST), "the fused update rides on the fast float4 path");
   extern __shared__ __align__(16) float upd_lds[];  // UPD: W [K][Fo + 1], then the waves' tiles and row ids
   Sink sink;
@@ -857,16 +863,18 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
       mdi = s.dv[r];
     }
   }
+  const int team_log2 = TEAMS ? a.team_log2 : a.ls_log2;  // of a short row
+  const int per_step = wide ? 1 : kWave >> team_log2;     // elements worked on side by side
   int order = lane;
   // (not for slices narrower than a cache line, where neighbouring rows share lines, and not for rows that are all taken at once)
-  if (!wide && rows_here > nteams && ((VEC * 4) << a.ls_log2) >= 128)
+  if (!wide && rows_here > per_step && ((VEC * 4) << a.ls_log2) >= 128)
     order = longest_first(lane < rows_here ? (mc1 - mc0 + md1 - md0 + U - 1) / U : 0, rows_here, lane);
-  const int per_step = wide ? 1 : nteams;          // elements worked on side by side
-  const int team_base = wide ? 0 : team << a.ls_log2;
-  const int team_lanes = wide ? kWave : ls;
-  const int q = wide ? lane : fl;
-  const int slot = wide ? team : 0;
-  const int nslots = wide ? nteams : 1;
+  const int short_team = TEAMS ? lane >> team_log2 : team;
+  const int team_base = wide ? 0 : short_team << team_log2;
+  const int team_lanes = wide ? kWave : 1 << team_log2;
+  const int q = wide ? lane : TEAMS ? lane - team_base : fl;
+  const int slot = wide ? team : TEAMS ? q >> a.ls_log2 : 0;
+  const int nslots = wide ? nteams : TEAMS ? team_lanes >> a.ls_log2 : 1;
 
   struct Item {
     int32_t i, cs, clen, ds, len;  // len: both lists together
@@ -877,7 +885,7 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
   };
   auto prefetch = [&](int step) __attribute__((always_inline)) {
     Item it;
-    const int li = step * per_step + (wide ? 0 : team);
+    const int li = step * per_step + (wide ? 0 : short_team);
     it.have = li < rows_here;
     const int src = __shfl(order, it.have ? li : 0, kWave);
     it.i = __shfl(r, src, kWave);
@@ -922,13 +930,15 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
       }
     } else {
       if (cur.have)
-        walk<VEC, U, FAST, EPL, ALONE, S>(lists, cur.cs, cur.clen, cur.ds, cur.len, cur.first, team_base, team_lanes, q, slot, nslots,
-                            s, a.ldx, cur.i, ntl, lds, acc);
+        walk<VEC, U, FAST, EPL, ALONE, S, TEAMS>(lists, cur.cs, cur.clen, cur.ds, cur.len, cur.first, team_base, team_lanes, q, slot,
+                            nslots, s, a.ldx, cur.i, ntl, lds, acc);
+      if constexpr (TEAMS)
+        for (int m = team_lanes >> 1; m >= ls; m >>= 1) VT::add(acc, VT::shfl_xor(acc, m));
       if constexpr (UPD) {
-        if (cur.have) finish_row_to_sink(a, s, sink, sink.cnt + team, fl, cur.i, cur.di, cur.xi, acc);
+        if (cur.have && (!TEAMS || slot == 0)) finish_row_to_sink(a, s, sink, sink.cnt + short_team, fl, cur.i, cur.di, cur.xi, acc);
         sink.cnt += rows_now;  // teams 0 .. rows_now - 1 had a row
       } else {
-        if (cur.have && s.fvalid) finish_row<VEC>(a, s, cur.i, cur.di, cur.xi, acc);
+        if (cur.have && (!TEAMS || slot == 0) && s.fvalid) finish_row<VEC>(a, s, cur.i, cur.di, cur.xi, acc);
       }
     }
   }
@@ -942,18 +952,18 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
 // EPL: entries per lane and chunk; teams of 8 lanes and more get on with 1.  (Teams of 1 and 2 lanes with
 // one entry per lane, fetched and gathered one after the other: N = 500k, k = 4, F = 4 486 us, with 4
 // entries 375; 8 entries take too many registers.)
-template <int VEC, bool FAST, int EPL, bool PLAIN, bool ALONE = false, Scales S = kStreams>
+template <int VEC, bool FAST, int EPL, bool PLAIN, bool ALONE = false, Scales S = kStreams, bool TEAMS = false>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(PIPAD_AGG_WAVES)))
 void k_aggregate(const AggArgs a) {
-  aggregate_body<VEC, FAST, EPL, false, PLAIN, ALONE, S>(a);
+  aggregate_body<VEC, FAST, EPL, false, PLAIN, ALONE, S, TEAMS>(a);
 }
 
 // The same walk with the update fused in, held to the four waves per SIMD that its 120 registers allow
 // (left to the compiler: 853 us against 851 on N = 200k, k = 8, F = Fo = 64).
-template <bool PLAIN, Scales S = kStreams>
+template <bool PLAIN, Scales S = kStreams, bool TEAMS = false>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void k_aggregate_update(const AggArgs a) {
-  aggregate_body<4, true, 1, true, PLAIN, false, S>(a);
+  aggregate_body<4, true, 1, true, PLAIN, false, S, TEAMS>(a);
 }
 
 // Adds the partial sums of every hub row in a fixed order and finishes the row.  One wave per
@@ -1579,6 +1589,34 @@ void (*aggregate_kernel(bool fast, int ls_log2))(AggArgs) {
          : ls_log2 == 1 ? k_aggregate<VEC, true, 4, PLAIN, false, S> : k_aggregate<VEC, true, 4, PLAIN, true, S>;
 }
 
+// The same with several lane groups per short row, for slices of up to eight lanes.
+template <int VEC>
+void (*teams_kernel(int ls_log2))(AggArgs) {
+  if constexpr (VEC > 1)
+    if (ls_log2 >= 3) return k_aggregate<VEC, true, 1, true, false, kStreams, true>;
+  return ls_log2 == 2 ? k_aggregate<VEC, true, 2, true, false, kStreams, true> : k_aggregate<VEC, true, 4, true, false, kStreams, true>;
+}
+
+// log2 of the lanes that walk a short row.  A small frame of few columns has few waves: 64 / LS rows each where a slice takes LS
+// lanes (so short rows by one lane group), and a wave takes as long as the longest of them, a chain of up to 16 gathers that the chip
+// waits for.  So there several lane groups walk a row, four entries each at a time, and their sums are added up in a fixed order:
+// more waves, and shorter chains.  GPU time per call (calls recorded one behind the other), one group against the rule: Chung-Lu 1083
+// nodes, k = 8, F = 16 7.1 -> 4.8 us, 2985, k = 5, F = 5 8.4 -> 5.1, 9127, k = 5, F = 7 9.0 -> 6.6, R-MAT 3683, k = 8, F = 16 7.2 -> 6.4;
+// the update, 1623, k = 5, F = 16, Fo = 32 9.3 -> 7.0.  Once the waves fill the chip the sums are only more work.  Two groups pay up
+// to 4096 waves, as many as run together at four per SIMD, and with more than four snapshots up to 8192 (9216 nodes, k = 6, F = 4
+// 8.3 -> 6.9 us; with fewer 14,119, k = 3, F = 16 7.6 -> 8.0; past it 15,639, k = 8, F = 16 11.3 -> 13.8); more groups up to 3072 (1656, k = 4,
+// F = 16: two 4.8 us, four 4.2, eight 4.7).  From 16 columns on, where the update may do the same sums in its own kernel, whose
+// waves take 16 rows, two groups stop at 3072 as well (3223, k = 8, F = Fo = 16 11.3 -> 11.8, 4302, k = 6, F = 32, Fo = 64 12.8 -> 18.2).
+// It looks at the whole frame, so that a row's sum is the same whichever snapshots a call takes and with the update or without;
+// slices of 16 lanes and more, whose waves hold four rows at most, gain nothing (7121, k = 3, F = 58 11.5 -> 12.2).
+int short_row_team(const pipad_frame *f, int ls_log2, int32_t F, int fchunks) {
+  int log2 = ls_log2;
+  const int64_t rows = (int64_t)f->n_short * f->k * fchunks;
+  if (f->plain_units && ls_log2 > 0 && ls_log2 <= 3)
+    while (log2 < ls_log2 + 3 && (rows << (log2 + 1)) / kWave <= (log2 > ls_log2 || F >= 16 ? 3072 : f->k > 4 ? 8192 : 4096)) ++log2;
+  return log2;
+}
+
 template <int VEC>
 int launch(const AggArgs &a, bool fast, hipStream_t st, bool fused_update = false) {
   const int64_t phases = (int64_t)a.nsel * a.fchunks;
@@ -1590,7 +1628,8 @@ int launch(const AggArgs &a, bool fast, hipStream_t st, bool fused_update = fals
   if constexpr (VEC == 4) {
     if (fused_update) {
       if (!fast || a.ls_log2 < 2) return PIPAD_ERR_INVALID_ARG;  // the caller checked the shape
-      auto kern = a.plain ? k_aggregate_update<true> : a.coded ? k_aggregate_update<false, kCodes> : k_aggregate_update<false>;
+      auto kern = a.team_log2 > a.ls_log2 ? k_aggregate_update<true, kStreams, true>
+                  : a.plain ? k_aggregate_update<true> : a.coded ? k_aggregate_update<false, kCodes> : k_aggregate_update<false>;
       if (blocks > 0) hipLaunchKernelGGL(kern, grid, block, update_lds_bytes(a), st, a);
       if (fin > 0)
         hipLaunchKernelGGL((k_split_finish<4, true>), dim3((unsigned)fin), dim3(kBlock), 0, st, a);
@@ -1598,7 +1637,8 @@ int launch(const AggArgs &a, bool fast, hipStream_t st, bool fused_update = fals
       return PIPAD_OK;
     }
   }
-  auto kern = a.plain   ? aggregate_kernel<VEC, true>(fast, a.ls_log2)
+  auto kern = a.team_log2 > a.ls_log2 ? teams_kernel<VEC>(a.ls_log2)
+              : a.plain ? aggregate_kernel<VEC, true>(fast, a.ls_log2)
               : a.coded ? aggregate_kernel<VEC, false, kCodes>(fast, a.ls_log2) : aggregate_kernel<VEC, false>(fast, a.ls_log2);
   if (blocks > 0) hipLaunchKernelGGL(kern, grid, block, 0, st, a);
   if (fin > 0) hipLaunchKernelGGL((k_split_finish<VEC>), dim3((unsigned)fin), dim3(kBlock), 0, st, a);
@@ -1924,7 +1964,8 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
     a.nslices = f->k * a.fchunks;
   }
   const int sw = (1 << a.ls_log2) * vec;
-  const int nteams = kWave >> a.ls_log2;
+  a.team_log2 = coalescent || !fast ? a.ls_log2 : short_row_team(f, a.ls_log2, F, a.fchunks);
+  const int nteams = kWave >> a.team_log2;
   if (a.order < 0) {
     const int64_t matrix = (int64_t)f->n * sw * 4, slices = (int64_t)a.nsel * a.fchunks;
     a.order = matrix >= (int64_t)PIPAD_ORDER_BYTES ? 1 : 0;
