@@ -99,6 +99,7 @@ struct AggArgs {
   // meant for is the one it runs on)
   int32_t blocks_wide, blocks_mid, blocks_short;
   int32_t team_log2;      // log2 of the lanes that walk a short row: those of a slice, or more (short_row_team)
+  int32_t uneven;         // ... lanes by the length of the row (uneven_rows)
   int32_t batch_short, batch_mid, batch_wide;  // rows / class parts per wave
   int64_t blocks_per_phase;
   Divisor per_phase, per_row;  // workgroups per phase, slices
@@ -677,12 +678,24 @@ __device__ __forceinline__ Piece unit_piece(const AggArgs &a, int64_t unit, cons
   return p;
 }
 
-// PLAIN: hub units as they are in a frame with plain_units.  TEAMS: a short row is walked by several lane groups (see
-// short_row_team).
-template <int VEC, bool FAST, int EPL, bool UPD, bool PLAIN, bool ALONE = false, Scales S = kStreams, bool TEAMS = false>
+// Lane groups that walk a short row.
+enum Teams {
+  kOneGroup,
+  kSeveral,   // the same number for every row (short_row_team)
+  kByLength,  // up to 8 entries one, up to 32 four, from there on eight (uneven_rows)
+};
+
+// Lanes of a mask below this one.
+__device__ __forceinline__ int lanes_below(uint64_t mask) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
+}
+
+// PLAIN: hub units as they are in a frame with plain_units.
+template <int VEC, bool FAST, int EPL, bool UPD, bool PLAIN, bool ALONE = false, Scales S = kStreams, Teams TEAMS = kOneGroup>
 __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
   using VT = V<VEC>;
-  static_assert(!TEAMS || (FAST && !ALONE), "");
+  static_assert(TEAMS == kOneGroup || (FAST && !ALONE), "");
+  static_assert(TEAMS != kByLength || !UPD, "");
   static_assert(!UPD || (VEC == 4 && FAST), "the fused update rides on the fast float4 path");
   extern __shared__ __align__(16) float upd_lds[];  // UPD: W [K][Fo + 1], then the waves' tiles and row ids
   Sink sink;
@@ -863,18 +876,68 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
       mdi = s.dv[r];
     }
   }
-  const int team_log2 = TEAMS ? a.team_log2 : a.ls_log2;  // of a short row
+  const int team_log2 = TEAMS == kSeveral ? a.team_log2 : a.ls_log2;  // of a short row (kByLength: at least)
   const int per_step = wide ? 1 : kWave >> team_log2;     // elements worked on side by side
   int order = lane;
-  // (not for slices narrower than a cache line, where neighbouring rows share lines, and not for rows that are all taken at once)
-  if (!wide && rows_here > per_step && ((VEC * 4) << a.ls_log2) >= 128)
+  int n8 = 0, n4 = 0;  // kByLength: rows of eight and of four lane groups, which come first
+  if constexpr (TEAMS == kByLength) {
+    if (!wide) {
+      const int len = lane < rows_here ? mc1 - mc0 + md1 - md0 : 0;
+      const uint64_t eight = __ballot(len > 32), four = __ballot(len > 8) & ~eight;
+      n8 = __popcll(eight);
+      n4 = __popcll(four);
+      if (n8 + n4 > 0) {
+        const bool in8 = eight >> lane & 1ull, in4 = four >> lane & 1ull;
+        const int at = lanes_below(in8 ? eight : in4 ? four : ~(eight | four)) + (in8 ? 0 : in4 ? n8 : n8 + n4);
+        order = __builtin_amdgcn_ds_permute(at << 2, lane);
+      }
+    }
+  } else if (!wide && rows_here > per_step && ((VEC * 4) << a.ls_log2) >= 128) {
+    // (not for slices narrower than a cache line, where neighbouring rows share lines, and not for rows that are all taken at once)
     order = longest_first(lane < rows_here ? (mc1 - mc0 + md1 - md0 + U - 1) / U : 0, rows_here, lane);
-  const int short_team = TEAMS ? lane >> team_log2 : team;
-  const int team_base = wide ? 0 : short_team << team_log2;
-  const int team_lanes = wide ? kWave : 1 << team_log2;
-  const int q = wide ? lane : TEAMS ? lane - team_base : fl;
-  const int slot = wide ? team : TEAMS ? q >> a.ls_log2 : 0;
-  const int nslots = wide ? nteams : TEAMS ? team_lanes >> a.ls_log2 : 1;
+  }
+  const int steps8 = (8 * n8 + nteams - 1) / nteams, steps4 = (4 * n4 + nteams - 1) / nteams;
+
+  // What a step takes: elements at, at + 1, ... in front of `end`, each by a team of 1 << log2 lanes.
+  struct Shape {
+    int at, end, log2;
+  };
+  auto shape = [&](int step) __attribute__((always_inline)) {
+    Shape h = {step * per_step, rows_here, wide ? 6 : team_log2};
+    if constexpr (TEAMS == kByLength) {
+      if (step < steps8) {
+        h = {step * (nteams / 8), n8, team_log2 + 3};
+      } else if (step < steps8 + steps4) {
+        h = {n8 + (step - steps8) * (nteams / 4), n8 + n4, team_log2 + 2};
+      } else {
+        h.at = n8 + n4 + (step - steps8 - steps4) * per_step;
+      }
+    }
+    return h;
+  };
+  // This lane's place in its team, the same in every step but for kByLength.
+  struct Place {
+    int team, base, lanes, q, slot, nslots;
+  };
+  Place same;
+  same.team = wide ? 0 : TEAMS == kOneGroup ? team : lane >> team_log2;
+  same.base = wide ? 0 : same.team << team_log2;
+  same.lanes = wide ? kWave : 1 << team_log2;
+  same.q = wide ? lane : TEAMS == kOneGroup ? fl : lane - same.base;
+  same.slot = wide ? team : TEAMS == kOneGroup ? 0 : same.q >> a.ls_log2;
+  same.nslots = wide ? nteams : TEAMS == kOneGroup ? 1 : same.lanes >> a.ls_log2;
+  auto place = [&](const Shape &h) __attribute__((always_inline)) {
+    Place p = same;
+    if (TEAMS == kByLength && !wide) {
+      p.team = lane >> h.log2;
+      p.base = p.team << h.log2;
+      p.lanes = 1 << h.log2;
+      p.q = lane - p.base;
+      p.slot = p.q >> a.ls_log2;
+      p.nslots = p.lanes >> a.ls_log2;
+    }
+    return p;
+  };
 
   struct Item {
     int32_t i, cs, clen, ds, len;  // len: both lists together
@@ -885,8 +948,10 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
   };
   auto prefetch = [&](int step) __attribute__((always_inline)) {
     Item it;
-    const int li = step * per_step + (wide ? 0 : short_team);
-    it.have = li < rows_here;
+    const Shape h = shape(step);
+    const Place p = place(h);
+    const int li = h.at + p.team;
+    it.have = li < h.end;
     const int src = __shfl(order, it.have ? li : 0, kWave);
     it.i = __shfl(r, src, kWave);
     it.cs = __shfl(mc0, src, kWave);
@@ -897,12 +962,12 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
     if (!it.have) { it.clen = 0; it.len = 0; }
 #pragma unroll
     for (int j = 0; j < EPL; ++j)
-      it.first[j] = fetch_entry<S>(lists, it.cs, it.clen, it.ds, it.len, j * team_lanes + q, it.i, ntl);
+      it.first[j] = fetch_entry<S>(lists, it.cs, it.clen, it.ds, it.len, j * p.lanes + p.q, it.i, ntl);
     it.xi = VT::zero();
     if (!split) it.xi = VT::load(s.xb + (int64_t)it.i * a.ldx);
     return it;
   };
-  const int nsteps = (rows_here + per_step - 1) / per_step;
+  const int nsteps = steps8 + steps4 + (rows_here - n8 - n4 + per_step - 1) / per_step;
   Item nxt = prefetch(0);
   for (int step = 0; step < nsteps; ++step) {
     const Item cur = nxt;
@@ -916,8 +981,8 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
     if (step + 1 < nsteps) nxt = prefetch(step + 1);
     typename VT::T acc = VT::zero();
     if (wide) {
-      walk<VEC, U, FAST, EPL, ALONE, S>(lists, cur.cs, cur.clen, cur.ds, cur.len, cur.first, team_base, team_lanes, q, slot, nslots,
-                          s, a.ldx, cur.i, ntl, lds, acc);
+      walk<VEC, U, FAST, EPL, ALONE, S>(lists, cur.cs, cur.clen, cur.ds, cur.len, cur.first, same.base, same.lanes, same.q, same.slot,
+                          same.nslots, s, a.ldx, cur.i, ntl, lds, acc);
       reduce_slots<VEC>(a.ls_log2, acc);
       if (split) {
         if (team == 0 && s.fvalid)
@@ -929,16 +994,17 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
         if (team == 0 && s.fvalid) finish_row<VEC>(a, s, cur.i, cur.di, cur.xi, acc);
       }
     } else {
+      const Place p = place(shape(step));
       if (cur.have)
-        walk<VEC, U, FAST, EPL, ALONE, S, TEAMS>(lists, cur.cs, cur.clen, cur.ds, cur.len, cur.first, team_base, team_lanes, q, slot,
-                            nslots, s, a.ldx, cur.i, ntl, lds, acc);
-      if constexpr (TEAMS)
-        for (int m = team_lanes >> 1; m >= ls; m >>= 1) VT::add(acc, VT::shfl_xor(acc, m));
+        walk<VEC, U, FAST, EPL, ALONE, S, TEAMS != kOneGroup>(lists, cur.cs, cur.clen, cur.ds, cur.len, cur.first, p.base, p.lanes, p.q,
+                            p.slot, p.nslots, s, a.ldx, cur.i, ntl, lds, acc);
+      if constexpr (TEAMS != kOneGroup)
+        for (int m = p.lanes >> 1; m >= ls; m >>= 1) VT::add(acc, VT::shfl_xor(acc, m));
       if constexpr (UPD) {
-        if (cur.have && (!TEAMS || slot == 0)) finish_row_to_sink(a, s, sink, sink.cnt + short_team, fl, cur.i, cur.di, cur.xi, acc);
+        if (cur.have && (TEAMS == kOneGroup || p.slot == 0)) finish_row_to_sink(a, s, sink, sink.cnt + p.team, fl, cur.i, cur.di, cur.xi, acc);
         sink.cnt += rows_now;  // teams 0 .. rows_now - 1 had a row
       } else {
-        if (cur.have && (!TEAMS || slot == 0) && s.fvalid) finish_row<VEC>(a, s, cur.i, cur.di, cur.xi, acc);
+        if (cur.have && (TEAMS == kOneGroup || p.slot == 0) && s.fvalid) finish_row<VEC>(a, s, cur.i, cur.di, cur.xi, acc);
       }
     }
   }
@@ -952,7 +1018,7 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
 // EPL: entries per lane and chunk; teams of 8 lanes and more get on with 1.  (Teams of 1 and 2 lanes with
 // one entry per lane, fetched and gathered one after the other: N = 500k, k = 4, F = 4 486 us, with 4
 // entries 375; 8 entries take too many registers.)
-template <int VEC, bool FAST, int EPL, bool PLAIN, bool ALONE = false, Scales S = kStreams, bool TEAMS = false>
+template <int VEC, bool FAST, int EPL, bool PLAIN, bool ALONE = false, Scales S = kStreams, Teams TEAMS = kOneGroup>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(PIPAD_AGG_WAVES)))
 void k_aggregate(const AggArgs a) {
   aggregate_body<VEC, FAST, EPL, false, PLAIN, ALONE, S, TEAMS>(a);
@@ -960,7 +1026,7 @@ void k_aggregate(const AggArgs a) {
 
 // The same walk with the update fused in, held to the four waves per SIMD that its 120 registers allow
 // (left to the compiler: 853 us against 851 on N = 200k, k = 8, F = Fo = 64).
-template <bool PLAIN, Scales S = kStreams, bool TEAMS = false>
+template <bool PLAIN, Scales S = kStreams, Teams TEAMS = kOneGroup>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void k_aggregate_update(const AggArgs a) {
   aggregate_body<4, true, 1, true, PLAIN, false, S, TEAMS>(a);
@@ -1593,8 +1659,26 @@ void (*aggregate_kernel(bool fast, int ls_log2))(AggArgs) {
 template <int VEC>
 void (*teams_kernel(int ls_log2))(AggArgs) {
   if constexpr (VEC > 1)
-    if (ls_log2 >= 3) return k_aggregate<VEC, true, 1, true, false, kStreams, true>;
-  return ls_log2 == 2 ? k_aggregate<VEC, true, 2, true, false, kStreams, true> : k_aggregate<VEC, true, 4, true, false, kStreams, true>;
+    if (ls_log2 >= 3) return k_aggregate<VEC, true, 1, true, false, kStreams, kSeveral>;
+  return ls_log2 == 2 ? k_aggregate<VEC, true, 2, true, false, kStreams, kSeveral> : k_aggregate<VEC, true, 4, true, false, kStreams, kSeveral>;
+}
+// The same with lane groups by the length of the row, for slices of two and four lanes.
+template <int VEC, Scales S>
+void (*uneven_kernel(int ls_log2))(AggArgs) {
+  return ls_log2 == 2 ? k_aggregate<VEC, true, 2, false, false, S, kByLength> : k_aggregate<VEC, true, 4, false, false, S, kByLength>;
+}
+
+// Whether lane groups go by the length of a short row.  A wave of narrow slices takes 16 or 32 rows side by side and as long as the
+// longest of them; in skewed frames, whose short rows hold the smaller part of the entries, most of the lanes wait for a few.
+// There the rows of a batch with more than 32 entries come first, by eight lane groups each, then those with more than 8 by four, then
+// the others: each is one chunk.  More sums and up to three part-filled steps, which take a batch of rows that differ: R-MAT 500k
+// nodes, k = 12, F = 5 682 -> 604 us, 657k, k = 8, F = 6 1101 -> 947, 365k, k = 8, F = 5 414 -> 354, 500k, k = 8, F = 3 410 -> 386; of 11 R-MAT
+// frames of more than a million rows in all snapshots none slower, with fewer between 2 % faster and 10 % slower; Chung-Lu frames,
+// whose short rows are alike, 7 % slower (369k, k = 16, F = 3 709 -> 760).  Not from 16 columns on, where the update would have to
+// add up in the same order (R-MAT 700k, k = 8, F = 16 657 -> 614).  Like short_row_team it looks at the whole frame.
+bool uneven_rows(const pipad_frame *f, int ls_log2, int32_t F, int64_t entries) {
+  return !f->plain_units && F < 16 && (ls_log2 == 1 || ls_log2 == 2) && 2 * f->short_entries < entries &&
+         (int64_t)f->n_short * f->k > 1000000;
 }
 
 // log2 of the lanes that walk a short row.  A small frame of few columns has few waves: 64 / LS rows each where a slice takes LS
@@ -1628,7 +1712,7 @@ int launch(const AggArgs &a, bool fast, hipStream_t st, bool fused_update = fals
   if constexpr (VEC == 4) {
     if (fused_update) {
       if (!fast || a.ls_log2 < 2) return PIPAD_ERR_INVALID_ARG;  // the caller checked the shape
-      auto kern = a.team_log2 > a.ls_log2 ? k_aggregate_update<true, kStreams, true>
+      auto kern = a.team_log2 > a.ls_log2 ? k_aggregate_update<true, kStreams, kSeveral>
                   : a.plain ? k_aggregate_update<true> : a.coded ? k_aggregate_update<false, kCodes> : k_aggregate_update<false>;
       if (blocks > 0) hipLaunchKernelGGL(kern, grid, block, update_lds_bytes(a), st, a);
       if (fin > 0)
@@ -1638,6 +1722,8 @@ int launch(const AggArgs &a, bool fast, hipStream_t st, bool fused_update = fals
     }
   }
   auto kern = a.team_log2 > a.ls_log2 ? teams_kernel<VEC>(a.ls_log2)
+              : a.uneven && a.coded ? uneven_kernel<VEC, kCodes>(a.ls_log2)
+              : a.uneven ? uneven_kernel<VEC, kStreams>(a.ls_log2)
               : a.plain ? aggregate_kernel<VEC, true>(fast, a.ls_log2)
               : a.coded ? aggregate_kernel<VEC, false, kCodes>(fast, a.ls_log2) : aggregate_kernel<VEC, false>(fast, a.ls_log2);
   if (blocks > 0) hipLaunchKernelGGL(kern, grid, block, 0, st, a);
@@ -1965,6 +2051,7 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
   }
   const int sw = (1 << a.ls_log2) * vec;
   a.team_log2 = coalescent || !fast ? a.ls_log2 : short_row_team(f, a.ls_log2, F, a.fchunks);
+  a.uneven = !coalescent && fast && !fused && uneven_rows(f, a.ls_log2, F, entries);
   const int nteams = kWave >> a.team_log2;
   if (a.order < 0) {
     const int64_t matrix = (int64_t)f->n * sw * 4, slices = (int64_t)a.nsel * a.fchunks;

@@ -57,3 +57,25 @@ def test_an_infinite_row_without_fillers_stays_infinite(pipad, F):  # noqa: F811
     for m in (4, 8, 16, 20, 32):
         assert bool(torch.isposinf(y[m]).all()), m
     assert bool(torch.isfinite(y[100:]).all())
+
+
+@pytest.mark.parametrize("F", [2, 4, 5, 8, 9, 15])
+@pytest.mark.parametrize("codes", [0, 2])
+def test_rows_of_uneven_length_in_many_rows(pipad, F, codes):  # noqa: F811
+    """More than a million rows in all snapshots, most entries in long rows: lane groups by the length of the row."""
+    pipad.set_option("scale_codes", codes)
+    n, k = 70_003, 16
+    rng = np.random.default_rng(F)
+    lengths = np.concatenate([np.tile(LENGTHS, 40), np.full(24, 40_000)])
+    at = rng.permutation(n)[:len(lengths)]
+    rows = np.concatenate([np.stack([np.full(m, at[q]), rng.integers(0, n, m)], 1) for q, m in enumerate(lengths)])
+    pool = np.concatenate([rows, rand_pairs(rng, n, 3 * n)])
+    full, less = csr(n, pool), csr(n, pool[rng.random(len(pool)) < 0.9])
+    lists = [full if t % 5 else less for t in range(k)]
+    run_case(pipad, n, lists, F, seed=F, check_csr=False)
+    frame = pipad.frame_build_overlap([(torch.from_numpy(rp).cuda(), torch.from_numpy(c).cuda()) for rp, c in lists])
+    xs = [torch.from_numpy(synth.features(4, t, n, F)).cuda() for t in range(k)]
+    Y = pipad.frame_aggregate(frame, xs)
+    some = [torch.zeros_like(y) for y in Y]
+    pipad.frame_aggregate_subset(frame, [7, 2], xs, some)
+    assert torch.equal(some[7], Y[7]) and torch.equal(some[2], Y[2])
