@@ -59,11 +59,16 @@ def test_an_infinite_row_without_fillers_stays_infinite(pipad, F):  # noqa: F811
     assert bool(torch.isfinite(y[100:]).all())
 
 
+@pytest.fixture(params=[0, 2])
+def scale_codes(pipad, request):  # noqa: F811
+    pipad.set_option("scale_codes", request.param)
+    yield
+    pipad.set_option("scale_codes", 1)
+
+
 @pytest.mark.parametrize("F", [2, 4, 5, 8, 9, 15])
-@pytest.mark.parametrize("codes", [0, 2])
-def test_rows_of_uneven_length_in_many_rows(pipad, F, codes):  # noqa: F811
+def test_rows_of_uneven_length_in_many_rows(pipad, F, scale_codes):  # noqa: F811
     """More than a million rows in all snapshots, most entries in long rows: lane groups by the length of the row."""
-    pipad.set_option("scale_codes", codes)
     n, k = 70_003, 16
     rng = np.random.default_rng(F)
     lengths = np.concatenate([np.tile(LENGTHS, 40), np.full(24, 40_000)])
