@@ -136,3 +136,30 @@ def test_same_bits_with_and_without_the_aggregation(pipad, n, k, F, Fo, bias):  
     for t in range(k):
         assert torch.equal(H[0][t].view(torch.int32), H[1][t].view(torch.int32)), t
     frame.close()
+
+
+@pytest.mark.parametrize("options", [{}, {"mid_max": 300}, {"mid_max": 600, "hub_segment": 300, "hub_threshold": 700}])
+@pytest.mark.parametrize("n,k,F,Fo,bias", [(7_251, 2, 48, 48, True), (1_501, 10, 36, 64, False), (28_990, 2, 64, 64, True),
+                                           (15_003, 3, 60, 48, False), (15_003, 3, 44, 16, True)])
+def test_same_bits_where_hub_rows_end_in_partial_sums(pipad, options, n, k, F, Fo, bias):  # noqa: F811
+    """The same shapes with rows that are summed in parts: longer than hub_threshold, or by column class."""
+    rng = np.random.default_rng(n + F)
+    hubs = [np.stack([np.full(length, row), rng.permutation(n)[:length]], 1) for row, length in ((17, min(n - 1, 5000)), (n - 1, 1400))]
+    pool = np.concatenate([rand_pairs(rng, n, 25 * n), *hubs])
+    lists = [csr(n, pool[rng.random(len(pool)) < 0.95]) for _ in range(k)]
+    assert min(np.diff(rp).max() for rp, _ in lists) > (2048 if n > 2048 and not options else 700)
+    for key, value in options.items():
+        pipad.set_option(key, value)
+    frame = pipad.frame_build_overlap([(torch.from_numpy(rp).cuda(), torch.from_numpy(c).cuda()) for rp, c in lists])
+    X = [torch.empty((n, F), device="cuda:0").uniform_(-1, 1) for _ in range(k)]
+    W = torch.empty((F, Fo), device="cuda:0").uniform_(-1, 1)
+    b = torch.empty(Fo, device="cuda:0").uniform_(-1, 1) if bias else None
+    H, A = [[torch.full((n, Fo), 77.0, device="cuda:0") for _ in range(k)] for _ in range(2)], [torch.empty((n, F), device="cuda:0") for _ in range(k)]
+    pipad.frame_aggregate_update(frame, X, W, b, H=H[0], A=A)
+    pipad.frame_aggregate_update(frame, X, W, b, H=H[1])
+    for t in range(k):
+        assert torch.equal(H[0][t].view(torch.int32), H[1][t].view(torch.int32)), t
+        exact = A[t].double() @ W.double() + (b.double() if bias else 0.0)
+        bound = A[t].double().abs() @ W.double().abs() + (b.double().abs() if bias else 0.0)
+        assert bool(((H[1][t].double() - exact).abs() <= (F + 2) * 2.0 ** -24 * bound).all())  # (F products, F sums, the bias)
+    frame.close()
