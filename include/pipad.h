@@ -96,9 +96,10 @@ typedef void *(*pipad_alloc_fn)(size_t bytes, void *ctx);
  *           inputs must stay valid, and the frame is used, in stream order.
  *   out     receives the new frame.
  *   Memory: the frame keeps (k + 1) (4 n) bytes of row pointers, about 8 k n of D^-1/2 and some 8 n
- *   of row lists; 4 + 4 k bytes per common entry and 8 per exclusive one; and for rows longer than
- *   "mid_max" their entries a second time.  Frames of up to 2^25 entries in all snapshots take 8 bytes
- *   per input entry instead, before the sizes are known: that is 4 (k - 1) bytes per common entry more,
+ *   of row lists; 4 + 4 k bytes per common entry and 8 per exclusive one, where scales are stored as codes
+ *   ("scale_codes") 4 + 2 k and 6; and for rows longer than "mid_max" their entries a second time.  Frames of up
+ *   to 2^25 entries in all snapshots, and fewer than 2^23 (k > 16: 2^22) in each, take 8 bytes per input entry instead where their
+ *   scales are not to be codes, before the sizes are known: that is 4 (k - 1) bytes per common entry more,
  *   less than twice as much.  Where that is refused they get by with the former.
  */
 int pipad_frame_build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags,

@@ -1917,7 +1917,7 @@ int wait_totals(const TotalsTicket &ticket, hipStream_t st, FrameTotals *out) {
 // would be among them.)  Of 200 frames below the line with hub rows, in the mean: steps 6 to 14 % faster, backward passes 3 to 11,
 // aggregations alone 4 to 26, the more the fewer entries, with operands in the caches and without; at worst 14 % slower
 // (R-MAT, N = 62k, k = 2, F = 32, aggregation alone).
-constexpr int64_t kEarlyEntries = 24000000;  // (build_overlap)
+constexpr int64_t kEarlyEntries = (int64_t)1 << 25, kCodeEntries = 24000000;  // (build_overlap)
 constexpr int32_t kManyTiles = 16384;  // from here on a wave of k_scatter takes four
 constexpr int32_t kPlainNodes = 65536, kPlainRow = 512;
 constexpr int64_t kPlainEntries = (int64_t)4 << 20;
@@ -2108,8 +2108,8 @@ template <class W>
 static void launch_scatter(const pipad_frame *f, const Snaps &s, const Tiles &g, const OutParts &o, int instance, hipStream_t st) {
   // A wave per tile has the shortest chain of dependent loads (0.2M nodes: 65 us against 74 with four
   // tiles per wave); with 8M entries and more per snapshot there
-  // are waves enough and fewer of them do better (1M nodes, 20M entries: 313 us against 339).  (With so few tiles
-  // that a wave takes one, three and four snapshots are here only where the room for `early` was refused.)
+  // are waves enough and fewer of them do better (1M nodes, 20M entries: 313 us against 339).  (Few tiles are here in frames with codes,
+  // from three snapshots on by default, and where the room for `early` was refused.)
   const int per_wave = g.ntiles < kManyTiles ? 1 : 4;
   using Scatter = void (*)(Snaps, Tiles, OutParts, NodeScales<W>);
   static const Scatter kernels[2][9] = {
@@ -2183,19 +2183,19 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
   // and 20000 waves of k_prepare_mark, of which 8192 run together: N = 107k, k = 8 with 2000 tiles 190 -> 186, N = 45k, k = 12
   // with 1520 181 -> 178, but N = 113k, k = 16 with 1590 180 -> 187; with 3000 to 4000 tiles and k = 2 .. 6 3 to 13 % slower.
   bool small = g.ntiles <= kSumTiles && row_blocks <= kSumRowBlocks && (int64_t)g.ntiles * k <= 20000;
-  // Frames of up to 24 M entries in all snapshots get that room as well (190 MB at most), and their rows are made next to the
+  // Frames of up to 33 M entries in all snapshots get that room as well (270 MB at most), and their rows are made next to the
   // entries, in the launch that would wait for the host otherwise: steps and slides N = 100k R-MAT, k = 5 198 -> 191 us,
-  // N = 200k, k = 8 269 -> 263 (slide), 124k, k = 2 88 -> 77, 140k, k = 3 119 -> 111; of 40 frames past the small ones 1 to 10 % less,
+  // 124k, k = 2 88 -> 77, 140k, k = 3 119 -> 111; of 40 frames past the small ones 1 to 10 % less,
   // the more the shorter.  What stays unused of it, for as long as the frame is there, are 4 (k - 1) bytes per common entry: less
-  // than 4 per input entry, and than what is used.  (With room for every part at its largest it was up to twice as much, and
-  // 200k nodes, k = 8, 81 % in common took 320 MB; now 205 of which 132 are used.)  From there on waiting for the sizes costs less than
-  // codes for the scales give (scale_code), which only entries whose form is known before they are written can have: 24 to 33 M
-  // entries, 24 of 28 drawn steps, slides, layers and backward passes 1 to 13 % faster, 4.7 in the mean, the others the same but
-  // one; 14 to 24 M between 7 % faster and 4 % slower, fewer up to 18 % slower.
+  // than 4 per input entry, and than what is used.  (With room for every part at its largest it was up to twice as much.)
   bool early = small || (entries <= kEarlyEntries && g.ntiles < kManyTiles);
-  // Past that the scales are stored as codes, unless a row turns out to be too long for one.
-  if (f->opt.scale_codes == 2) small = early = false;
-  const bool codes = !early && f->opt.scale_codes > 0;
+  // From 24 M entries on the scales are stored as codes (scale_code), unless a row turns out to be too long for one; which only entries
+  // whose form is known before they are written can be.  Up to 33 M entries, where that costs the room above and a wait: 24 of 28
+  // drawn steps, slides, layers and backward passes 1 to 13 % faster, 4.7 in the mean, the others the same but one; 14 to 24 M between
+  // 7 % faster and 4 % slower, fewer up to 18 % slower.  The line is one of entries alone: one snapshot of 10 M entries, which has no
+  // such room either way, aggregates up to 15 columns 10 to 23 % slower with codes.
+  const bool codes = f->opt.scale_codes == 2 || (f->opt.scale_codes == 1 && entries > kCodeEntries);
+  if (codes) small = early = false;
 
   Arena keep1;
   keep1.want(&f->rowptr_c, (size_t)n + 1);
