@@ -214,6 +214,11 @@ __device__ inline void find_bounds(const Snaps &s, const Tiles &g, int64_t wave,
   }
 }
 
+// (1 + len)^-1/2, rounded once.  (In double throughout: k_prepare, 1M nodes, k = 8 45.6 us, so 40.5.)
+__device__ __forceinline__ float node_scale(int32_t len) {
+  return len >= kUncoded ? (float)(1.0 / sqrt((double)(len + 1))) : scale_of_length(scale_code(len));
+}
+
 template <class W>
 __device__ __forceinline__ void put_node(W *nk, int32_t k, Quad<W> v) {
   if (k > 2) *reinterpret_cast<Quad<W> *>(nk) = v;
@@ -246,8 +251,7 @@ __device__ __forceinline__ void prepare_rows(const Snaps &s, const Tiles &g, con
     for (int u = 0; u < CH; ++u) {
       const int32_t len = b[u] - a[u];
       c[u] = scale_code(len);
-      v[u] = scale_of_length(c[u]);  // (in double: 1M nodes, k = 8 45.6 us, so 40.5)
-      if (len >= kUncoded) v[u] = (float)(1.0 / sqrt((double)(len + 1)));
+      v[u] = node_scale(len);
       if (t0 + u < g.k) {
         longest = max(longest, len);
         all += len;
@@ -1250,6 +1254,7 @@ __device__ inline uint32_t sum_tiles_before(const Tiles &g, int32_t upto, uint32
 struct RowArgs {
   int32_t *rowptr_c;
   int32_t *rowptr_d[PIPAD_MAX_K];
+  float *scales_nk;  // of a frame that is to have codes: where its node-major scales go if a row is too long for one
 };
 
 // A thread per row i in [0, n].  The exclusive row pointer is the input's minus the common one; the
@@ -1257,7 +1262,8 @@ struct RowArgs {
 // them).
 // SUM: neither the tiles' counts nor the row blocks' are summed up yet; they are few enough for every
 // workgroup to do that (k_rows_scatter).
-template <bool SUM>
+// CODES: of a frame that may be to have codes.
+template <bool SUM, bool CODES>
 __device__ __forceinline__ void make_rows(const Snaps &s, Tiles g, const RowArgs &o, const ListArgs &q, FrameTotals *out, uint32_t seq) {
   const int64_t i64 = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   const int32_t i = (int32_t)min(i64, (int64_t)g.n), i1 = min(i + 1, g.n);
@@ -1289,6 +1295,9 @@ __device__ __forceinline__ void make_rows(const Snaps &s, Tiles g, const RowArgs
   // (the clamps only ever act on snapshots that are not canonical: whatever they hold, the row
   // pointers stay within the parts)
   const int32_t nnz_c = (int32_t)g.tile_pre[g.ntiles].x;
+  // (In a launch of their own behind the host's wait: frames of 26 to 29 M entries with such a row 168 us to build, so 164, 258 and 254,
+  // 300 and 288; behind this loop 166, 255, 293.)
+  const bool uncoded = CODES && o.scales_nk && total.uncoded > 0;
   int64_t all = 0;
   constexpr int CH = 8;  // snapshots whose row pointers are requested together
   for (int t0 = 0; t0 < g.k; t0 += CH) {
@@ -1306,6 +1315,13 @@ __device__ __forceinline__ void make_rows(const Snaps &s, Tiles g, const RowArgs
         all += b[u] - a[u];
         if (i64 <= g.n) o.rowptr_d[t0 + u][i] = min(max(a[u] - before, 0), max(s.nnz[t0 + u] - nnz_c, 0));
       }
+    if (uncoded && live)
+#pragma unroll
+      for (int u = 0; u < CH; u += 4)
+        if (t0 + u < g.k)
+          put_node(o.scales_nk + (int64_t)i * node_stride(g.k) + t0 + u, g.k,
+                   Quad<float>{node_scale(b[u] - a[u]), node_scale(b[u + 1] - a[u + 1]), node_scale(b[u + 2] - a[u + 2]),
+                               node_scale(b[u + 3] - a[u + 3])});
   }
   if (i64 == g.n) q.hub_item_off[total.hub] = (int32_t)total.units;  // the end of the last hub row's units
   list_row(q, live, i, longest, after - before, all, first, [&](uint64_t entries, uint32_t, int32_t *c0, int32_t *d0) {
@@ -1315,7 +1331,7 @@ __device__ __forceinline__ void make_rows(const Snaps &s, Tiles g, const RowArgs
 }
 
 __global__ __launch_bounds__(kBlock) void k_rows(Snaps s, Tiles g, RowArgs o, ListArgs q) {
-  make_rows<false>(s, g, o, q, nullptr, 0);
+  make_rows<false, true>(s, g, o, q, nullptr, 0);
 }
 
 // The same for a frame whose row pointers are in place (the transposed frame): the counts, then the
@@ -1816,7 +1832,7 @@ template <int KV, bool FULL, bool SUM>
 __global__ __launch_bounds__(kBlock) void k_rows_scatter(Snaps s, Tiles g, RowArgs r, ListArgs q, OutParts o, int32_t row_wgs,
                                                          NodeScales<float> scales, FrameTotals *out, uint32_t seq) {
   if ((int32_t)blockIdx.x < row_wgs) {
-    make_rows<SUM>(s, g, r, q, out, seq);
+    make_rows<SUM, false>(s, g, r, q, out, seq);
     return;
   }
   const int32_t groups = (g.ntiles + kWavesPerBlock - 1) / kWavesPerBlock, b = (int32_t)blockIdx.x - row_wgs;
@@ -1846,13 +1862,6 @@ __global__ __launch_bounds__(kBlock) void k_rows_scatter(Snaps s, Tiles g, RowAr
     scatter_tiles<float, KV, FULL, 1>(s, g, o, scales, part, tile0, [&](int32_t x) __attribute__((always_inline)) { return g.tile_pre[x].x; },
                                shift.cols(part - 1), shift.scales());
   }
-}
-
-// The node-major scales of a frame that was to have codes and has a row too long for one.
-__global__ __launch_bounds__(kBlock) void k_node_scales(int32_t n, int32_t k, const float *dinv, float *dinv_nk) {
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i >= n) return;
-  for (int t = 0; t < node_stride(k); ++t) dinv_nk[i * node_stride(k) + t] = dinv[(int64_t)min(t, k - 1) * n + i];
 }
 
 }  // namespace
@@ -2295,6 +2304,7 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
   std::memset(&rows, 0, sizeof(rows));
   rows.rowptr_c = f->rowptr_c;
   for (int t = 0; t < k; ++t) rows.rowptr_d[t] = f->rowptr_d[t];
+  rows.scales_nk = codes ? f->dinv_nk : nullptr;
   auto out_parts = [&]() {
     OutParts o;
     std::memset(&o, 0, sizeof(o));
@@ -2374,7 +2384,6 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
   }
 
   f->coded = codes && v.uncoded == 0;
-  if (codes && !f->coded && n > 0) hipLaunchKernelGGL(k_node_scales, grid1(n, kBlock), dim3(kBlock), 0, st, n, k, f->dinv, f->dinv_nk);
 
   Arena keep2;
   if (early) {

@@ -151,7 +151,7 @@ def test_generic_kernel(pipad, option, F):
 
 
 # the longest row that has a code, and rows without one: floats then
-@pytest.mark.parametrize("k", [1, 2, 3, 8])
+@pytest.mark.parametrize("k", [1, 2, 3, 5, 8, 9, 18])
 @pytest.mark.parametrize("longest", [65_533, 65_534, 65_535, 70_000])
 def test_long_rows(pipad, option, longest, k):
     n, F = 70_001, 4
