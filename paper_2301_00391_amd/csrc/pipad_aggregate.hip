@@ -409,9 +409,19 @@ __device__ __forceinline__ void walk(const Lists &l, int32_t cs, int32_t clen, i
   Raw mine[EPL], next[EPL];
 #pragma unroll
   for (int j = 0; j < EPL; ++j) mine[j] = next[j] = first[j];
+  // Codes: the next chunk's become scales while the rows of this one are on their way, so that a row of many chunks does not wait
+  // for that in each: R-MAT 500k, k = 12, F = 10 848 -> 768 us, F = 16 810 -> 777, concatenated, 200k, k = 8, F = 12 246 -> 223.  (Lanes of
+  // one column fetch two entries, half of what they gather at a time: F = 1 492 -> 512, so not for these.)
+  constexpr bool AHEAD = coded(S) && VEC == 4 && FAST && !ALONE;
+  auto decode = [](Raw (&r)[EPL]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < EPL; ++j) r[j].w = __float_as_uint(scale_of(r[j].w));
+  };
+  if (AHEAD) decode(mine);
   for (int32_t base = 0; base < len; base += chunk) {
     const int32_t cnt = min(chunk, len - base);
-    if (base + chunk < len)
+    const bool more = base + chunk < len;
+    if (more)
 #pragma unroll
       for (int j = 0; j < EPL; ++j)
         next[j] = fetch<S>(l, cs, clen, ds, len, base + chunk + j * team_lanes + q, self, nt);
@@ -437,7 +447,7 @@ __device__ __forceinline__ void walk(const Lists &l, int32_t cs, int32_t clen, i
     for (int j = 0; j < EPL; ++j) {
       Staged st;
       st.off = FAST ? entry_column<S>(mine[j]) * row_bytes : entry_column<S>(mine[j]);
-      st.w = entry_weight<S>(mine[j]);
+      st.w = AHEAD ? __uint_as_float(mine[j].w) : entry_weight<S>(mine[j]);
       mine_lds[j * team_lanes + q] = st;
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -463,6 +473,7 @@ __device__ __forceinline__ void walk(const Lists &l, int32_t cs, int32_t clen, i
           x[u] = VT::load(xcol + (int64_t)en[u].off * ldx);
 #endif
       }
+      if (AHEAD && more && e0 == (BLOCKS ? slot * UNR : 0)) decode(next);  // (a chunk with one behind it is full: every lane group has some of it)
       float w[UNR];
 #pragma unroll
       for (int u = 0; u < UNR; ++u) w[u] = en[u].w;

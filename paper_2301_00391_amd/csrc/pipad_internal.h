@@ -288,22 +288,24 @@ __device__ __forceinline__ int32_t half_row_of_entry(const int32_t *rp, int32_t 
 
 // A scale as a code: 1 + the length of the node's row, in 16 bits (0: no entry, scale 0).  In frames of many entries the scales
 // are most of what a build stores, and an aggregation reads as many bytes of them as of column indices: half as many this
-// way, for ten instructions per entry that make the float again, bit for bit.  A frame with a row of kUncoded - 1 entries or more
+// way, for eight instructions per entry that make the float again, bit for bit.  A frame with a row of kUncoded - 1 entries or more
 // keeps floats.  R-MAT 1M, k = 8: k_scatter 311 -> 246 us, k_split_fill 216 -> 182, aggregation with F = 64 3875 -> 3844 (5058 -> 4990
 // for Chung-Lu 500k, F = 128); of 30 drawn frames of more than 33 M entries in all snapshots together, whole calls 0 to 13 % faster,
-// 5.6 in the mean.  Fewer entries lie in the caches, and rows of few columns are bound by instructions: aggregations alone 20k nodes,
-// k = 4, F = 1 8.2 -> 10.3 us, 147k, k = 6, F = 2 52 -> 61; R-MAT 500k, k = 12, F = 5 732 -> 827 also with 72 M entries.
+// 5.6 in the mean.  Aggregations alone, six frames of 25 to 80 M entries, F = 1 .. 100: 1 to 12 % faster.  Fewer entries lie in the caches, and
+// rows of one or two columns are bound by instructions: R-MAT 147k, k = 6, 8.4 M entries F = 2 74 -> 81 us, from 5 columns on 0 to 4 % faster.
 constexpr int32_t kUncoded = 65535;
 __device__ __forceinline__ uint16_t scale_code(int32_t row_length) { return (uint16_t)min((uint32_t)row_length + 1u, 65535u); }
 // x^-1/2 rounded to the nearest float, 1 <= x < 65536: the reciprocal square root of the hardware (an ulp off at most) and a
 // Newton step on its exact residual.  The same bits as (float)(1.0 / sqrt((double)x)) for every such x and any
-// start within three ulps.
+// start within three ulps.  (NaN for 0.)
 __device__ __forceinline__ float scale_of_length(uint32_t x) {
   const float xf = (float)x, r = __builtin_amdgcn_rsqf(xf);
   const float h = r * r, l = fmaf(r, r, -h);
   return fmaf(-0.5f * r, fmaf(xf, l, fmaf(xf, h, -1.f)), r);
 }
-__device__ __forceinline__ float scale_of(uint32_t code) { return code == 0 ? 0.f : scale_of_length(code); }
+// (The clamp rides on the last operation and makes 0 of a NaN.  With a test for 0 instead, which became a branch, R-MAT 500k, k = 12,
+// F = 16 847 us, so 810.)
+__device__ __forceinline__ float scale_of(uint32_t code) { return __builtin_amdgcn_fmed3f(scale_of_length(code), 0.f, 1.f); }
 
 // Two and four scales (float) or codes (uint16_t) next to each other.
 template <class W> struct alignas(2 * sizeof(W)) Pair { W x, y; };
