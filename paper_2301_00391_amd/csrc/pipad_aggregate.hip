@@ -1706,14 +1706,15 @@ void (*uneven_kernel(int ls_log2))(AggArgs) {
 // Whether lane groups go by the length of a short row.  A wave of narrow slices takes 16 or 32 rows side by side and as long as the
 // longest of them; in skewed frames, whose short rows hold the smaller part of the entries, most of the lanes wait for a few.
 // There the rows of a batch with more than 32 entries come first, by eight lane groups each, then those with more than 8 by four, then
-// the others: each is one chunk.  More sums and up to three part-filled steps, which take a batch of rows that differ: R-MAT 500k
-// nodes, k = 12, F = 5 682 -> 604 us, 657k, k = 8, F = 6 1101 -> 947, 365k, k = 8, F = 5 414 -> 354, 500k, k = 8, F = 3 410 -> 386; of 11 R-MAT
-// frames of more than a million rows in all snapshots none slower, with fewer between 2 % faster and 10 % slower; Chung-Lu frames,
-// whose short rows are alike, 7 % slower (369k, k = 16, F = 3 709 -> 760).  Not from 16 columns on, where the update would have to
-// add up in the same order (R-MAT 700k, k = 8, F = 16 657 -> 614).  Like short_row_team it looks at the whole frame.
+// the others: each is one chunk.  More sums and up to three part-filled steps, which take a batch of rows that differ and rows enough: with
+// two lanes per slice (5 to 8 columns) of 17 R-MAT frames of 1 to 6 M rows in all snapshots 14 1 to 8 % faster, the others the same but one, 1.5 %
+// slower; with four lanes 10 of 1 to 1.6 M rows 5 % slower to 4 % faster (300k, k = 4, 16 entries per row, F = 4 5 %), 7 of 1.8 to 6 M up to 8 %
+// faster, at worst 0.8 % slower.  500k, k = 12, F = 5 721 -> 694 us, 120k, k = 16, F = 2 8 %, 700k, k = 8, F = 4 4 %; frames of fewer rows up to 8 %
+// slower, Chung-Lu frames, whose short rows are alike, 7 % (369k, k = 16, F = 3 709 -> 760).  Not from 16 columns on, where the update would
+// have to add up in the same order (R-MAT 700k, k = 8, F = 16 657 -> 614).  Like short_row_team it looks at the whole frame.
 bool uneven_rows(const pipad_frame *f, int ls_log2, int32_t F, int64_t entries) {
   return !f->plain_units && F < 16 && (ls_log2 == 1 || ls_log2 == 2) && 2 * f->short_entries < entries &&
-         (int64_t)f->n_short * f->k > 1000000;
+         (int64_t)f->n_short * f->k > (ls_log2 == 1 ? 1000000 : 1750000);
 }
 
 // log2 of the lanes that walk a short row.  A small frame of few columns has few waves: 64 / LS rows each where a slice takes LS

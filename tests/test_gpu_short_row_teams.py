@@ -68,10 +68,10 @@ def scale_codes(pipad, request):  # noqa: F811
 
 @pytest.mark.parametrize("F", [2, 4, 5, 8, 9, 15])
 def test_rows_of_uneven_length_in_many_rows(pipad, F, scale_codes):  # noqa: F811
-    """More than a million rows in all snapshots, most entries in long rows: lane groups by the length of the row."""
-    n, k = 70_003, 16
+    """Enough rows in all snapshots (a million for slices of two lanes, 1.75 for four), most entries in long rows: lane groups by the length of the row."""
+    n, k = 112_003, 16
     rng = np.random.default_rng(F)
-    lengths = np.concatenate([np.tile(LENGTHS, 40), np.full(24, 40_000)])
+    lengths = np.concatenate([np.tile(LENGTHS, 40), np.full(36, 40_000)])
     at = rng.permutation(n)[:len(lengths)]
     rows = np.concatenate([np.stack([np.full(m, at[q]), rng.integers(0, n, m)], 1) for q, m in enumerate(lengths)])
     pool = np.concatenate([rows, rand_pairs(rng, n, 3 * n)])
