@@ -410,9 +410,9 @@ __device__ __forceinline__ void walk(const Lists &l, int32_t cs, int32_t clen, i
 #pragma unroll
   for (int j = 0; j < EPL; ++j) mine[j] = next[j] = first[j];
   // Codes: the next chunk's become scales while the rows of this one are on their way, so that a row of many chunks does not wait
-  // for that in each: R-MAT 500k, k = 12, F = 10 848 -> 768 us, F = 16 810 -> 777, concatenated, 200k, k = 8, F = 12 246 -> 223.  (Lanes of
-  // one column fetch two entries, half of what they gather at a time: F = 1 492 -> 512, so not for these.)
-  constexpr bool AHEAD = coded(S) && VEC == 4 && FAST && !ALONE;
+  // for that in each: R-MAT 500k, k = 12, F = 10 848 -> 768 us, F = 16 810 -> 777, 200k, k = 8, F = 1 152 -> 147, concatenated, F = 12 246 ->
+  // 223.  (Not by row length in lanes of one column: 76 registers, a wave fewer per SIMD, 500k, F = 1 492 -> 512.)
+  constexpr bool AHEAD = coded(S) && (VEC == 4 || !BLOCKS) && FAST && !ALONE;
   auto decode = [](Raw (&r)[EPL]) __attribute__((always_inline)) {
 #pragma unroll
     for (int j = 0; j < EPL; ++j) r[j].w = __float_as_uint(scale_of(r[j].w));
