@@ -133,6 +133,7 @@ struct AggArgs {
   int32_t coded;
   const float *table;     // coalescent kernel: the rows times their scales, row stride ldt (k_scale_rows)
   int64_t ldt;
+  const void *nk;         // the scales node-major, or their codes where `coded`
   const float *X[PIPAD_MAX_K];
   float *Y[PIPAD_MAX_K];   // aggregation results (optional when the update is fused in)
   // fused update: H_t = Y_t W + bias
@@ -1641,14 +1642,16 @@ __global__ __launch_bounds__(kBlock) void k_hub_finish_coalescent(const AggArgs 
 }
 
 // Every row of the concatenated operand times its column scales, dinv_t[i] X_t[i], rounded: what kTable gathers.  A thread takes
-// four columns of a node, 16 bytes at a time where the rows allow it (VECTOR).  Bound: the stream of X and of the table.
-template <bool VECTOR>
+// four columns of a node, 16 bytes at a time where the rows allow it (VECTOR), and gets its scales (W), or their codes, from one line
+// (k streams instead: R-MAT 200k, k = 8, F = 9 223 -> 232 us in all, 60k, k = 16 241 -> 249).  Bound: the stream of X and of the table.
+template <class W, bool VECTOR>
 __global__ __launch_bounds__(kBlock) void k_scale_rows(const AggArgs a, float *table) {
   const uint32_t cols = (uint32_t)(a.k * a.F), quads = (cols + 3) / 4;
   const int64_t x = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (x >= (int64_t)a.n * quads) return;
   const int32_t i = (int32_t)(x / quads);
   const uint32_t c = 4 * (uint32_t)(x - (int64_t)i * quads);
+  const W *scales = static_cast<const W *>(a.nk) + (int64_t)i * node_stride(a.k);
   const float *row = a.X[0] + (int64_t)i * a.ldx;
   float v[4], w[4];
   if (VECTOR) {
@@ -1659,7 +1662,8 @@ __global__ __launch_bounds__(kBlock) void k_scale_rows(const AggArgs a, float *t
   for (int j = 0; j < 4; ++j) {
     const uint32_t at = min(c + j, cols - 1);
     if (!VECTOR) v[j] = row[at];
-    w[j] = a.dinv[(int64_t)(at / (uint32_t)a.F) * a.n + i];
+    if constexpr (sizeof(W) == sizeof(float)) w[j] = scales[at / (uint32_t)a.F];
+    else w[j] = scale_of_length(scales[at / (uint32_t)a.F]);
   }
   // (the table's rows are padded to 16 bytes)
   *reinterpret_cast<float4 *>(table + (int64_t)i * a.ldt + c) =
@@ -1831,7 +1835,9 @@ int launch_coalescent(const AggArgs &a, hipStream_t st) {
   void (*kern)(AggArgs) = nullptr;
   if (a.table) {
     const int64_t threads = (int64_t)a.n * ((a.k * a.F + 3) / 4);
-    auto scale = a.k * a.F % 4 == 0 ? k_scale_rows<true> : k_scale_rows<false>;
+    const bool vector = a.k * a.F % 4 == 0;
+    auto scale = a.coded ? (vector ? k_scale_rows<uint16_t, true> : k_scale_rows<uint16_t, false>)
+                         : (vector ? k_scale_rows<float, true> : k_scale_rows<float, false>);
     hipLaunchKernelGGL(scale, grid1(threads, kBlock), dim3(kBlock), 0, st, a, const_cast<float *>(a.table));
     kern = coalescent_kernel<VEC, kTable>(a);
   } else {
@@ -1898,6 +1904,7 @@ int aggregate_launch(const pipad_frame *f, int32_t F, const float *const *X, int
   a.col_c = f->col_c;
   a.dinv = f->dinv;
   a.coded = f->coded;
+  a.nk = f->dinv_nk;
   a.rows_short = f->rows_short;
   a.rows_long = f->rows_long;
   a.item_row = f->item_row;
