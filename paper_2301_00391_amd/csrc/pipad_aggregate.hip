@@ -908,7 +908,9 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
     // (not for slices narrower than a cache line, where neighbouring rows share lines, and not for rows that are all taken at once)
     order = longest_first(lane < rows_here ? (mc1 - mc0 + md1 - md0 + U - 1) / U : 0, rows_here, lane);
   }
-  const int steps8 = (8 * n8 + nteams - 1) / nteams, steps4 = (4 * n4 + nteams - 1) / nteams;
+  // (kByLength alone: the compiler cannot know that the quotients are 0 elsewhere)
+  const int steps8 = TEAMS == kByLength ? (8 * n8 + nteams - 1) / nteams : 0;
+  const int steps4 = TEAMS == kByLength ? (4 * n4 + nteams - 1) / nteams : 0;
 
   // What a step takes: elements at, at + 1, ... in front of `end`, each by a team of 1 << log2 lanes.
   struct Shape {
@@ -1008,8 +1010,10 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
     } else {
       const Place p = place(shape(step));
       if (cur.have)
+        // (one group: said to the compiler, which gets a step's entries with two accesses to LDS then, not four.  With that and no
+        // divisions above R-MAT 100k, k = 5, F = 30 97.7 -> 96.2 us)
         walk<VEC, U, FAST, EPL, ALONE, S, TEAMS != kOneGroup>(lists, cur.cs, cur.clen, cur.ds, cur.len, cur.first, p.base, p.lanes, p.q,
-                            p.slot, p.nslots, s, a.ldx, cur.i, ntl, lds, acc);
+                            TEAMS == kOneGroup ? 0 : p.slot, TEAMS == kOneGroup ? 1 : p.nslots, s, a.ldx, cur.i, ntl, lds, acc);
       if constexpr (TEAMS != kOneGroup)
         for (int m = p.lanes >> 1; m >= ls; m >>= 1) VT::add(acc, VT::shfl_xor(acc, m));
       if constexpr (UPD) {
