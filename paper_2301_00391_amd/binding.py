@@ -1,5 +1,6 @@
 """Thin binding of libpipad.so: argument marshalling only, by ctypes and, for plain arguments of the calls that a
-step makes, by _host (csrc/pipad_host.cpp), which hands anything else back to the code here.
+step makes, by _host (csrc/pipad_host.cpp), which hands anything else back to the code here.  Where that native half is not
+there and cannot be built (no compiler, no headers) everything goes by ctypes, at 10 to 20 us more per step.
 
 Every step of the path (overlap extraction, normalisation, aggregation) runs in the HIP kernels of
 the library; nothing here computes.  PyTorch supplies device memory and streams.  There is no CPU
@@ -14,9 +15,13 @@ from __future__ import annotations
 
 import ctypes
 import functools
-import importlib
+import importlib.util
+import itertools
 import os
 import struct
+import subprocess
+import warnings
+import weakref
 from typing import List, Optional, Sequence, Tuple, Union
 
 import torch
@@ -27,7 +32,7 @@ MAX_K = 32
 VALIDATE = 1
 
 _lib = None
-_host = None      # the native half of this module
+_host = None      # the native half of this module, or None
 _address: dict = {}  # the library's functions for it
 
 
@@ -102,11 +107,20 @@ def load_library():
 
 
 def _load_host():
-    """The native half of this module (built first only if it does not exist yet)."""
+    """The native half of this module, built first where there is none for this interpreter and torch; None where that
+    cannot be done."""
     from . import build as _build
-    if not os.path.exists(_build.HOST):
-        _build.build_host()
-    return importlib.import_module("._host", __package__)
+    path = _build.host_path()
+    try:
+        if not os.path.exists(path):
+            _build.build_host()
+        spec = importlib.util.spec_from_file_location(f"{__package__}._host", path)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        return module
+    except (OSError, ImportError, subprocess.CalledProcessError) as why:
+        warnings.warn(f"the binding's native half is not there, calls take longer without it: {why}", RuntimeWarning, stacklevel=3)
+        return None
 
 
 def _check(status: int) -> None:
@@ -261,15 +275,48 @@ class Frame:
         return _copy_from_device(ptr.value, self.k * self.n, torch.float32, self.device).view(self.k, self.n)
 
 
+# Memory out of PyTorch's caching allocator without the native half.  One callback for all frames, which finds a frame's buffers by the
+# key it is called with: a ctypes callback sits in a reference cycle, and with one per frame the garbage collector walked
+# the whole program every few hundred frames.
+_owners: "weakref.WeakValueDictionary[int, _Buffers]" = weakref.WeakValueDictionary()
+_next_key = itertools.count(1).__next__
+
+
+class _Buffers(dict):
+    """The tensors handed out for a frame, by address, which keeps them alive."""
+
+    def __init__(self, device):
+        super().__init__()
+        self._device, self._key = device, _next_key()
+        _owners[self._key] = self
+
+    def context(self) -> int:
+        return self._key
+
+
+def _allocate(nbytes, key):
+    try:
+        buffers = _owners[key]
+        buf = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=buffers._device)
+        buffers[buf.data_ptr()] = buf
+        return buf.data_ptr()
+    except Exception:  # out of memory -> NULL -> PIPAD_ERR_ALLOC
+        return None
+
+
+_allocate_callback = ALLOC_FN(_allocate)
+_ALLOCATE = ctypes.cast(_allocate_callback, _vp).value
+
+
 def _build(index: int, n: int, k: int, device, allocator: str, stream, fn, *args) -> Frame:
     """The frame that fn(*args, allocator, its context, stream, result) makes."""
     if allocator not in ("torch", "library"):
         raise ValueError("allocator must be 'torch' or 'library'")
-    # (the library takes memory from PyTorch's caching allocator through a native callback, which keeps it in `buffers`)
+    # (the library takes memory from PyTorch's caching allocator through a callback, which keeps it in `buffers`)
     buffers, callback, context = {}, None, None
     if allocator == "torch":
-        buffers = _host.Buffers()
-        callback, context = _host.ALLOCATE, buffers.context()
+        buffers = _Buffers(device) if _host is None else _host.Buffers()
+        callback, context = _ALLOCATE if _host is None else _host.ALLOCATE, buffers.context()
     out = _vp()
     raw = int(stream.cuda_stream) if stream is not None else _current_raw_stream(index)
     _check(_on_device(index, fn, *args, callback, context, raw, ctypes.byref(out)))
@@ -280,7 +327,7 @@ def frame_transpose(frame: Frame, allocator: str = "torch", stream=None) -> Fram
     """pipad_frame_transpose: the frame of the transposed patterns with the same D^-1/2; aggregating
     with it applies the transposed operator (the backward pass for directed patterns)."""
     index = frame._index
-    if allocator == "torch" and _current_device() == index:
+    if _host is not None and allocator == "torch" and _current_device() == index:
         buffers = _host.Buffers()
         made = _host.transpose(_address["pipad_frame_transpose"], frame._h, buffers,
                                int(stream.cuda_stream) if stream is not None else _current_raw_stream(index))
@@ -310,7 +357,7 @@ def frame_build_overlap(snapshots: Sequence[Snapshot], validate: bool = False,
         raise ValueError("snapshots must be contiguous int32 tensors on one GPU")
     index = _device_index(device)
     flags = VALIDATE if validate else 0
-    if allocator == "torch" and _current_device() == index:
+    if _host is not None and allocator == "torch" and _current_device() == index:
         buffers = _host.Buffers()
         made = _host.build(_address["pipad_frame_build_overlap"], snapshots, index, flags, buffers,
                            int(stream.cuda_stream) if stream is not None else _current_raw_stream(index))
@@ -382,7 +429,7 @@ def frame_aggregate(frame: Frame, X: Features, Y: Optional[Features] = None, str
     the library; pass Y, or this wrapper allocates it before the call)."""
     lib = load_library()
     n, k = frame.n, frame.k
-    if Y is not None and _current_device() == frame._index:
+    if _host is not None and Y is not None and _current_device() == frame._index:
         frame._release_temporaries()
         status = _host.aggregate(_address["pipad_frame_aggregate_static" if static_scratch else "pipad_frame_aggregate"],
                                  frame._h, n, k, X, Y, frame._stream(stream))
@@ -418,7 +465,7 @@ def frame_aggregate_subset(frame: Frame, snapshots: Sequence[int], X: Sequence[O
         return
     if len(X) != k or len(Y) != k:
         raise ValueError("X and Y must have k entries")
-    if _current_device() == frame._index:
+    if _host is not None and _current_device() == frame._index:
         frame._release_temporaries()
         status = _host.subset(_address["pipad_frame_aggregate_subset"], frame._h, n, k, sel, X, Y, frame._stream(stream))
         if status is not None:
@@ -456,7 +503,7 @@ def frame_aggregate_update(frame: Frame, X: Features, W: torch.Tensor,
     receives the aggregation results.  Only enqueues work on the stream."""
     lib = load_library()
     n, k = frame.n, frame.k
-    if H is not None and _current_device() == frame._index:
+    if _host is not None and H is not None and _current_device() == frame._index:
         frame._release_temporaries()
         status = _host.update(_address["pipad_frame_aggregate_update"], frame._h, n, k, X, W, bias, A, H, frame._stream(stream))
         if status is not None:

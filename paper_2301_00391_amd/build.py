@@ -1,7 +1,9 @@
-"""Builds libpipad.so (HIP, gfx950 only) in-tree with hipcc, and _host.so, the native half of the binding, with g++.
+"""Builds libpipad.so (HIP, gfx950 only) in-tree with hipcc, and the native half of the binding with g++.
 
     python -m paper_2301_00391_amd.build [-v] [-D NAME[=VALUE] ...] [-o PATH]
 
+The native half is built for one interpreter and one torch, whose names its file bears (_host.*.so): another
+interpreter or torch does not meet it.  With -o, or -D, the library alone is built.
 -D passes a macro to every source: the measurement builds the profiles are taken with, e.g.
 -D PIPAD_PARTS_MASK=1 (only the class parts of the hub rows run: results incomplete),
 -D PIPAD_AGG_DEPTH=2, -D PIPAD_NO_ROW_ORDER.  -o writes the library somewhere else than in-tree;
@@ -10,6 +12,7 @@ the binding loads the file the environment variable PIPAD_LIBRARY names instead 
 from __future__ import annotations
 
 import os
+import re
 import shutil
 import subprocess
 import sys
@@ -18,7 +21,6 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpipad.so")
-HOST = os.path.join(HERE, "_host.so")
 SOURCES = ["pipad_api.hip", "pipad_build.hip", "pipad_aggregate.hip", "pipad_transpose.hip",
            "pipad_ceilings.hip"]
 
@@ -80,27 +82,46 @@ def build(verbose: bool = False, defines=(), output: str = LIB) -> str:
     return output
 
 
-def build_host(verbose: bool = False, output: str = HOST) -> str:
-    """Compiles the native half of the binding against this interpreter and its torch.  Always rebuilds."""
+def host_path() -> str:
+    """Where the native half of the binding for this interpreter and its torch lies."""
+    import torch
+    return os.path.join(HERE, f"_host.{sys.implementation.cache_tag}.torch-{re.sub('[^0-9A-Za-z.]', '_', torch.__version__)}.so")
+
+
+def build_host(verbose: bool = False, output: str = "") -> str:
+    """Compiles the native half of the binding against this interpreter and its torch.  Always rebuilds; the file is whole as soon as
+    it is there (other processes may load it meanwhile)."""
     import sysconfig
     import torch
-    root = os.path.dirname(torch.__file__)
+    output = output or host_path()
+    root, part = os.path.dirname(torch.__file__), f"{output}.{os.getpid()}.part"
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
            *[a for d in (os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
                          sysconfig.get_paths()["include"]) for a in ("-isystem", d)],
-           "-I", os.path.join(ROOT, "include"), os.path.join(CSRC, "pipad_host.cpp"), "-o", output,
+           "-I", os.path.join(ROOT, "include"), os.path.join(CSRC, "pipad_host.cpp"), "-o", part,
            "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
     if verbose:
         print(" ".join(cmd), flush=True)
-    subprocess.run(cmd, check=True)
+    try:
+        subprocess.run(cmd, check=True)
+        os.replace(part, output)
+    finally:
+        if os.path.exists(part):
+            os.remove(part)
     return output
 
 
-if __name__ == "__main__":
+def main(argv=None) -> None:
     import argparse
     ap = argparse.ArgumentParser(description=__doc__, formatter_class=argparse.RawDescriptionHelpFormatter)
     ap.add_argument("-v", action="store_true", help="print the compiler command lines")
     ap.add_argument("-D", action="append", default=[], metavar="NAME[=VALUE]")
     ap.add_argument("-o", default=LIB, metavar="PATH")
-    a = ap.parse_args()
+    a = ap.parse_args(argv)
     print(build(verbose=a.v, defines=a.D, output=a.o))
+    if a.o == LIB and not a.D:
+        print(build_host(verbose=a.v))
+
+
+if __name__ == "__main__":
+    main()

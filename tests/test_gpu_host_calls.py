@@ -63,7 +63,7 @@ def test_same_results_both_ways(pipad, monkeypatch, n, k, layout):
     snaps, X, W, bias = graph(n, k, n * k), matrices(F), torch.randn((F, 8), device="cuda"), torch.randn(8, device="cuda")
     results = []
     host = binding._host
-    for half in (Seen(host), Long(host)):
+    for half in (Seen(host), Long(host), None):  # (None: it could not be loaded)
         monkeypatch.setattr(binding, "_host", half)
         Y, Z, A, H = matrices(F, False), matrices(F, False), matrices(F, False), matrices(8, False)
         frame = pipad.frame_build_overlap(snaps, validate=True)
@@ -82,8 +82,9 @@ def test_same_results_both_ways(pipad, monkeypatch, n, k, layout):
             assert all(m == 0 if isinstance(m, int) else m[0] == 0 for m in half.made)
         back.close()
         frame.close()
-    for a, b in zip(*results):
-        assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1]) if isinstance(a, tuple) else torch.equal(a, b)
+    for other in results[1:]:
+        for a, b in zip(results[0], other):
+            assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1]) if isinstance(a, tuple) else torch.equal(a, b)
 
 
 def test_what_is_not_plain_goes_the_long_way(pipad, monkeypatch):
@@ -136,6 +137,31 @@ def test_what_is_not_plain_goes_the_long_way(pipad, monkeypatch):
     for call in (lambda: pipad.frame_aggregate(frame, X, Y), lambda: pipad.frame_transpose(frame)):
         with pytest.raises(pipad.PipadError):
             call()
+
+
+def test_memory_without_the_native_half(pipad, monkeypatch):
+    """Taken from torch's allocator and given back with the frame; more than there is ends the build with an error."""
+    from paper_2301_00391_amd import binding
+    monkeypatch.setattr(binding, "_host", None)
+    graphs, before = graph(200, 4, 1), torch.cuda.memory_allocated()
+    pipad.set_option("mid_max", 8)  # (rows in parts: scratch for the aggregation)
+    try:
+        frame = pipad.frame_build_overlap(graphs)
+    finally:
+        pipad.set_option("mid_max", 512)
+    built = torch.cuda.memory_allocated()
+    x = [torch.ones((200, 8), device="cuda") for _ in range(4)]
+    y = [torch.empty_like(m) for m in x]
+    pipad.frame_aggregate(frame, x, y)
+    assert before < built and torch.cuda.memory_allocated() > built and len(frame._buffers) >= 2
+    frame.close()
+    del frame, x, y
+    assert torch.cuda.memory_allocated() == before and not binding._owners
+    monkeypatch.setattr(binding.torch, "empty", lambda *a, **b: (_ for _ in ()).throw(RuntimeError("no memory")))
+    with pytest.raises(pipad.PipadError):
+        pipad.frame_build_overlap(graphs)
+    monkeypatch.undo()
+    assert torch.cuda.memory_allocated() == before and not binding._owners
 
 
 def test_memory_of_a_frame(pipad):
