@@ -172,8 +172,8 @@ def test_long_rows(pipad, option, longest, k):
         assert torch.equal(a, b)
 
 
-def test_scales_of_all_lengths(pipad, option):
-    """D^-1/2 is 1 / sqrt(1 + length) rounded once."""
+def test_scales_of_lengths_past_the_codes(pipad, option):
+    """D^-1/2 is 1 / sqrt(1 + length) rounded once, in a frame that keeps floats as well."""
     n = 70_000
     rng = np.random.default_rng(3)
     length = np.zeros(n, dtype=np.int64)
@@ -189,3 +189,34 @@ def test_scales_of_all_lengths(pipad, option):
         frame = pipad.frame_build_overlap([(rowptr.int(), col.int())])
         assert torch.equal(frame.dinv().reshape(-1), want)
         frame.close()
+
+
+@pytest.mark.parametrize("first", range(0, 65_534, 5000))
+def test_scale_of_every_code(pipad, option, first):
+    """A node of every length that has a code, and a row with an entry for each: what the aggregation makes of the code comes out as
+    the scale of the entry's column, bit for bit the one of D^-1/2, through lists of scales and the codes next to the rows."""
+    lengths = torch.arange(first, min(first + 5000, 65_534), device="cuda:0")
+    m = lengths.numel()
+    n = 2 * m + 65_534
+    # nodes [0, m): rows with one entry, column m + their number; nodes [m, 2 m): rows of the lengths, whose columns lie behind
+    rows = torch.cat([torch.ones(m, dtype=torch.int64, device="cuda:0"), lengths, torch.zeros(n - 2 * m, dtype=torch.int64, device="cuda:0")])
+    rowptr = torch.cat([torch.zeros(1, dtype=torch.int64, device="cuda:0"), rows.cumsum(0)])
+    assert int(rowptr[-1]) < 2 ** 31
+    at = torch.arange(int(rowptr[-1]) - m, device="cuda:0") - torch.repeat_interleave(rowptr[m:2 * m] - m, lengths) + 2 * m
+    col = torch.cat([m + torch.arange(m, device="cuda:0"), at]).int()
+    del at
+    snaps = [(rowptr.int(), col)]
+    option("scale_codes", 2)
+    option("mid_max", 1 << 30)
+    sizes, nnz = requests(pipad, snaps)
+    assert sizes[2:] == [parts_bytes(nnz, 2)]
+    frame = pipad.frame_build_overlap(snaps)
+    want = (1.0 / (1 + lengths).double().sqrt()).float()
+    dinv = frame.dinv().reshape(-1)
+    assert torch.equal(dinv[m:2 * m], want)
+    x = torch.zeros((n, 1), device="cuda:0")
+    x[m:2 * m] = 1.0
+    y = pipad.frame_aggregate(frame, [x])[0].reshape(-1)[:m]
+    own = dinv[0]  # of a row of one entry, whose own feature is 0
+    assert torch.equal(y, own * want)
+    frame.close()

@@ -18,8 +18,10 @@ from test_gpu_parity import pipad, _reset_options  # noqa: E402,F401
                                                      (6000, 1_100_000, 4, 4, 3, False), (6000, 1_400_000, 3, 3, 0, False),
                                                      (6000, 300_000, 16, 5, 0, True), (6000, 700_000, 6, 8, 1, False),
                                                      (6000, 700_000, 7, 13, 0, False), (6000, 1_950_000, 2, 31, 0, True)])
-def test_against_the_oracle_and_without_room(pipad, n, entries, k, F, pad, plain):  # noqa: F811
+@pytest.mark.parametrize("codes", [0, 2])  # (2: scales as codes, hub rows by class)
+def test_against_the_oracle_and_without_room(pipad, n, entries, k, F, pad, plain, codes):  # noqa: F811
     pipad.set_option("agg_coalescent", 2)
+    pipad.set_option("scale_codes", codes)
     if not plain:  # hub rows by class, several units each
         pipad.set_option("mid_max", 300)
         pipad.set_option("hub_segment", 700)
@@ -109,10 +111,12 @@ def test_entries_shared_by_a_quad(pipad, k, F, classes):  # noqa: F811
     fresh.close()
 
 
+@pytest.mark.parametrize("codes", [0, 2])
 @pytest.mark.parametrize("F", [2, 5])
-def test_infinite_rows_are_infinite_either_way(pipad, F):  # noqa: F811
+def test_infinite_rows_are_infinite_either_way(pipad, F, codes):  # noqa: F811
     """What fills up a step of four entries is the row itself with weight 0 where the kernel makes the products: it takes no part."""
     n, k = 6000, 7
+    pipad.set_option("scale_codes", codes)
     pipad.set_option("agg_coalescent", 2)
     lists = power_law(n, 350_000, k, F)
     assert 3 * k * min(len(c) for _, c in lists) > 10_000_000 + k * n * (4 * F + 1)
