@@ -1009,11 +1009,12 @@ __device__ __forceinline__ void aggregate_body(const AggArgs &a) {
       }
     } else {
       const Place p = place(shape(step));
+      constexpr bool ONE = TEAMS == kOneGroup && (VEC == 4 || !coded(S));
       if (cur.have)
         // (one group: said to the compiler, which gets a step's entries with two accesses to LDS then, not four.  With that and no
-        // divisions above R-MAT 100k, k = 5, F = 30 97.7 -> 96.2 us)
+        // divisions above R-MAT 100k, k = 5, F = 30 97.7 -> 96.2 us, 200k, k = 8, F = 1 145.2 -> 144.2; but 145.1 -> 149.3 with codes)
         walk<VEC, U, FAST, EPL, ALONE, S, TEAMS != kOneGroup>(lists, cur.cs, cur.clen, cur.ds, cur.len, cur.first, p.base, p.lanes, p.q,
-                            TEAMS == kOneGroup ? 0 : p.slot, TEAMS == kOneGroup ? 1 : p.nslots, s, a.ldx, cur.i, ntl, lds, acc);
+                            ONE ? 0 : p.slot, ONE ? 1 : p.nslots, s, a.ldx, cur.i, ntl, lds, acc);
       if constexpr (TEAMS != kOneGroup)
         for (int m = p.lanes >> 1; m >= ls; m >>= 1) VT::add(acc, VT::shfl_xor(acc, m));
       if constexpr (UPD) {

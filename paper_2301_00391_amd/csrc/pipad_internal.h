@@ -291,8 +291,9 @@ __device__ __forceinline__ int32_t half_row_of_entry(const int32_t *rp, int32_t 
 // way, for eight instructions per entry that make the float again, bit for bit.  A frame with a row of kUncoded - 1 entries or more
 // keeps floats.  R-MAT 1M, k = 8: k_scatter 311 -> 246 us, k_split_fill 216 -> 182, aggregation with F = 64 3875 -> 3844 (5058 -> 4990
 // for Chung-Lu 500k, F = 128); of 30 drawn frames of more than 33 M entries in all snapshots together, whole calls 0 to 13 % faster,
-// 5.6 in the mean.  Aggregations alone, six frames of 25 to 80 M entries, F = 1 .. 100: 1 to 12 % faster.  Fewer entries lie in the caches, and
-// rows of one or two columns are bound by instructions: R-MAT 147k, k = 6, 8.4 M entries F = 2 74 -> 81 us, from 5 columns on 0 to 4 % faster.
+// 5.6 in the mean.  Aggregations alone, seven frames of 25 to 80 M entries: 1 to 100 columns the same (R-MAT 200k, k = 8, F = 1) to 22 % faster
+// (60k, k = 16, F = 4 234 -> 195 us); concatenated, where most calls read no scales, 1.4 % slower to 8 % faster.  With fewer entries, which lie
+// in the caches, there is little to gain: R-MAT 147k, k = 6, 8.4 M entries F = 2 73.5 -> 73.9, to build 84 -> 87.
 constexpr int32_t kUncoded = 65535;
 __device__ __forceinline__ uint16_t scale_code(int32_t row_length) { return (uint16_t)min((uint32_t)row_length + 1u, 65535u); }
 // x^-1/2 rounded to the nearest float, 1 <= x < 65536: the reciprocal square root of the hardware (an ulp off at most) and a
