@@ -314,9 +314,9 @@ const char *pipad_last_hip_error(void);
  *                    allows it
  *   "scale_codes"    the column scales of a frame's entries as 16-bit codes that the aggregation turns
  *                    into the same floats: 0 never, 1 automatic (default: from 24 million entries in
- *                    all snapshots together on), 2 always; with a row of 65534 entries or more a
- *                    frame keeps floats.  Results do not depend on it in frames that are built alike
- *                    otherwise; with 2 small ones are built like large ones, hub rows by column class.
+ *                    all snapshots together on, or 2^23 in one of them, 2^22 where k > 16), 2 always; with a row of
+ *                    65534 entries or more a frame keeps floats.  Results do not depend on it in frames that are built
+ *                    alike otherwise; with 2 small ones are built like large ones, hub rows by column class.
  */
 int pipad_set_option(const char *key, int64_t value);
 int pipad_get_option(const char *key, int64_t *value);

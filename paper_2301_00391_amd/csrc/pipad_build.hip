@@ -2201,9 +2201,11 @@ int build_overlap(int32_t n, int32_t k, const pipad_csr_t *snaps, uint32_t flags
   // From 24 M entries on the scales are stored as codes (scale_code), unless a row turns out to be too long for one; which only entries
   // whose form is known before they are written can be.  Up to 33 M entries, where that costs the room above and a wait: 24 of 28
   // drawn steps, slides, layers and backward passes 1 to 13 % faster, 4.7 in the mean, the others the same but one; 14 to 24 M between
-  // 7 % faster and 4 % slower, fewer up to 18 % slower.  The line is one of entries alone: one snapshot of 10 M entries, which has no
-  // such room either way, aggregates up to 15 columns 10 to 23 % slower with codes.
-  const bool codes = f->opt.scale_codes == 2 || (f->opt.scale_codes == 1 && entries > kCodeEntries);
+  // 7 % faster and 4 % slower, fewer up to 18 % slower.  So are those of fewer entries with 16384 tiles (one or two snapshots), which have
+  // no such room to lose: R-MAT 800k, k = 1, 10 M entries 140 -> 130 us to build, aggregations alone of 1 to 64 columns 1 % slower to 3 % faster,
+  // k = 2, 18 M 178 -> 168 and 1 % slower to 5 % faster, Chung-Lu 600k, k = 2 168 -> 151 and 1 to 12 % faster.
+  const bool codes =
+      f->opt.scale_codes == 2 || (f->opt.scale_codes == 1 && (entries > kCodeEntries || g.ntiles >= kManyTiles));
   if (codes) small = early = false;
 
   Arena keep1;

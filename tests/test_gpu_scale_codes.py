@@ -98,10 +98,12 @@ def parts_bytes(nnz, scale):
     return (4 + k) * 256 + up(4 * nnz[0]) + k * up(scale * nnz[0]) + sum(up(4 * x) + up(scale * x) for x in nnz[1:])
 
 
-# codes from 24 million entries in all snapshots on, whatever their number; up to 2^25 entries floats get room before the sizes are known
-@pytest.mark.parametrize("k,entries,codes,room", [(1, 9_000_000, False, False), (2, 8_600_000, False, False), (2, 11_900_000, False, False),
-                                                  (2, 12_200_000, True, False), (3, 7_900_000, False, True), (3, 8_100_000, True, True),
-                                                  (5, 6_000_000, True, True), (4, 8_388_000, True, True), (4, 8_500_000, True, False)])
+# codes from 24 million entries in all snapshots on, or 2^23 in one; up to 2^25 entries, and fewer than 2^23 in one, floats get room
+# before the sizes are known
+@pytest.mark.parametrize("k,entries,codes,room", [(1, 8_300_000, False, True), (1, 9_000_000, True, False), (2, 8_300_000, False, True),
+                                                  (2, 8_600_000, True, False), (2, 12_200_000, True, False), (3, 7_900_000, False, True),
+                                                  (3, 8_100_000, True, True), (5, 6_000_000, True, True), (4, 8_388_000, True, True),
+                                                  (4, 8_500_000, True, False)])
 def test_form_of_the_scales(pipad, option, k, entries, codes, room):
     n = 200_000
     gen = torch.Generator(device="cuda:0")
